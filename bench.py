@@ -24,7 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3       # MI355X dense fp32 matrix peak
-PEAK_BF16_MFMA_TFLOPS = 2500.0      # MI355X dense bf16 matrix peak
+PEAK_16BIT_MFMA_TFLOPS = 2500.0     # MI355X dense f16 / bf16 matrix peak
 PEAK_HBM_GBS = 8000.0
 DEFAULT_STEPS = {"tiny": (300, 30), "kg_small": (500, 50), "social": (150, 15), "social_dot": (150, 15),
                  "kg_large": (150, 15), "wide": (100, 10)}
@@ -130,27 +130,30 @@ def run_workload(name, steps, warmup, edges=0, nodes=0, phase_events=True, cpu_b
         return hi - lo
 
     def contraction_roofline(flash_phase, prof_steps, prof_edges, split):
-        """Roofline record of the two contraction launches from their HIP-event times.  fp32: the algorithmic flops
-        (3 contractions x 2 sides x 2 n N d) against the fp32 matrix peak.  Split precision: the bf16 flops executed
-        (each pass computes the scores and one more product, every product as three bf16 products: 2 x 3 x 8 n N d)
-        against the bf16 matrix peak; `fp32_equivalent` is the algorithmic rate."""
+        """Roofline record of the two contraction launches from their HIP-event times.  Bilinear models: the 16-bit matrix
+        flops executed (each pass computes the scores and one more product, every product as three products of hi and lo
+        parts -- f16 at fp32 precision, bf16 in split precision: 2 x 3 x 8 n N d) against the 16-bit matrix peak;
+        `fp32_equivalent` is the algorithmic rate (3 contractions x 2 sides x 2 n N d).  TransE: the algorithmic flops
+        against the fp32 matrix peak."""
         per_launch = lambda ms: ms / max(prof_steps, 1) * 1e3                     # us per launch
         flops = lambda k: k * prof_edges * w.negs_per_chunk * w.dim / max(prof_steps, 1)
         tflops = lambda fl, us: fl / (us * 1e-6) / 1e12 if us > 0 else 0.0
         us1, us2 = per_launch(flash_phase[2]), per_launch(flash_phase[3])
-        if not split:
+        halves = w.model != 2
+        if not halves:
             peak, k1, k2, names = PEAK_FP32_MFMA_TFLOPS, 8.0, 4.0, ("k_flash", "k_flash_bwd")
             kernel = "k_flash + k_flash_bwd (the two contraction launches of every step)"
         else:
-            peak, k1, k2, names = PEAK_BF16_MFMA_TFLOPS, 24.0, 24.0, ("k_split_pass1", "k_split_pass2")
-            kernel = "k_split<.., 1> + k_split<.., 2> (the two contraction launches of every step, split precision)"
+            peak, k1, k2, names = PEAK_16BIT_MFMA_TFLOPS, 24.0, 24.0, ("k_split_pass1", "k_split_pass2")
+            kernel = "k_split<.., 1> + k_split<.., 2> (the two contraction launches of every step, %s)" % (
+                "bf16 hi + lo" if split else "f16 hi + lo with block exponents: fp32 accuracy")
         achieved = tflops(flops(k1 + k2), us1 + us2)
         r = {"bound": "mfma", "kernel": kernel, "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
              "traffic": None, "us_per_step": round(us1 + us2, 2),
              "algorithmic_flops_per_step": 12.0 * w.batch_size * w.negs_per_chunk * w.dim,
              names[0]: {"us": round(us1, 2), "flops": flops(k1), "frac": tflops(flops(k1), us1) / peak},
              names[1]: {"us": round(us2, 2), "flops": flops(k2), "frac": tflops(flops(k2), us2) / peak}}
-        if split:
+        if halves:
             r["executed_flops_per_step"] = 48.0 * w.batch_size * w.negs_per_chunk * w.dim
             r["fp32_equivalent_TFLOP/s"] = tflops(flops(12.0), us1 + us2)
         return r
@@ -207,10 +210,7 @@ def run_workload(name, steps, warmup, edges=0, nodes=0, phase_events=True, cpu_b
     chain_bytes = n * (2 * dk + 2 * roles * w.dim) * 4                               # operand gradients + s/r/d read, gradient rows written
     phases = {nm: round(per_step(ms) * 1e3, 2) for nm, ms in zip(mar.binding.PHASE_NAMES, phase_ms)}
     traffic = measured_traffic(w.name + ("_split" if precision else "")) if not nodes else {}   # per-launch bytes do not depend on the edge list
-    if not precision:
-        roof["traffic"] = (traffic.get("k_flash", 0.0) + traffic.get("k_flash_bwd", 0.0)) or None
-    else:
-        roof["traffic"] = traffic.get("k_split", 0.0) or None
+    roof["traffic"] = (traffic.get("k_flash", 0.0) + traffic.get("k_flash_bwd", 0.0) if w.model == 2 else traffic.get("k_split", 0.0)) or None
     # Bandwidth of the row phases two ways: algorithmic bytes (what the phase has to move) and the bytes the
     # rocprofv3 FETCH_SIZE / WRITE_SIZE counters saw per launch (profiles/traffic_<workload>.md), both over the
     # phase's time between HIP events on its stream.

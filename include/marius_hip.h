@@ -48,11 +48,12 @@ extern "C" {
                                /* rel ids are ignored (may be NULL) and relation rows are never touched  */
 
 /* Arithmetic of the two training contractions (scores with softmax and the edge-side gradient; the negatives'
- * gradient).  The paper trains in fp32 (Sec. 5.1).  SPLIT_BF16 writes every fp32 operand as the sum of two bf16
+ * gradient).  The paper trains in fp32 (Sec. 5.1).  FP32 is that accuracy (the bilinear models reach it with every
+ * operand as the sum of two scaled f16 numbers).  SPLIT_BF16 writes every fp32 operand as the sum of two bf16
  * numbers and takes each product as three bf16 matrix products accumulated in fp32 (relative error of a product
  * about 2^-16, i.e. an absolute error of a score q.n of about 2^-17 sum_k |q_k n_k|: as accurate as fp32 to the
  * 1e-4 level while |q| |n| stays below about 10); it serves the bilinear models (DistMult, ComplEx, Dot) only, and
- * evaluation always runs in fp32. */
+ * evaluation always runs at FP32 accuracy. */
 #define MAR_PRECISION_FP32        0
 #define MAR_PRECISION_SPLIT_BF16  1
 

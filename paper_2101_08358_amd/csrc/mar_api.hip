@@ -38,6 +38,68 @@ static int hip_fail(hipError_t e, const char* what) {
 #define MAR_FLASH_TARGET_WGS2 640
 #endif
 
+static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk) : mar_flash_wgs_per_cu(d.dk, pass); }
+
+// Small batches give too few (chunk-side, stripe) units to fill 256 CUs: several workgroups share a unit, each
+// streaming a slice of the other matrix.  TransE: until a pass has at least MAR_FLASH_TARGET_WGS workgroups (measured
+// best for a 10,000-edge batch).  Bilinear models: as many parts as the least estimated time of the busiest CU asks
+// for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its first tile and its
+// rows; a CU that holds one of two possible workgroups runs it at about 0.6 of its full rate.
+void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps) {
+  const int ty = mar_tile_rows(d, pass);
+  const int ntiles = (n_y + ty - 1) / ty;
+  long want = 1;
+  if (!d.bilinear) {
+    const long target = pass == 2 ? MAR_FLASH_TARGET_WGS2 : MAR_FLASH_TARGET_WGS1;
+    want = (target + units - 1) / units;
+    if (want > MAR_MAX_PARTS) want = MAR_MAX_PARTS;
+    if (want > ntiles) want = ntiles;
+  } else if (units < 256L * wgs_per_cu(d, pass) || pass == 3) {
+    double best = 1e30;
+    const bool two = wgs_per_cu(d, pass) == 2;
+    const int most = pass == 3 ? 64 : MAR_MAX_PARTS;
+    for (long k = 1; k <= most && k <= ntiles; ++k) {
+      const long t = (ntiles + k - 1) / k, per_cu = (units * k + 255) / 256;
+      const double cost = (two && per_cu == 1 ? 1.6 : (double)per_cu) * (double)(t + 3);
+      if (cost < best * 0.97) { best = cost; want = k; }
+    }
+  }
+  if (want < 1) want = 1;
+  *tps = (int32_t)((ntiles + want - 1) / want);
+  *sy = (int32_t)((ntiles + *tps - 1) / *tps);
+}
+
+// Large batches: the units of a pass rarely fill a whole number of rounds of the chip's workgroup slots (256 CUs x
+// workgroups per CU), and the last, partly filled round costs as much time as a full one.  The units beyond the last
+// whole round are split into k parts.  TransE (pass 1 only): as many as fill one round.  Bilinear models: the
+// remainder often exceeds half a round (units of 128 rows), so the parts may take several rounds of their own; every
+// part beyond the first costs a write and a read of the units' output rows.  Estimated in microseconds from the rates
+// these passes reach (about 1000 TFLOP/s of 16-bit work over all slots, 4.5 TB/s of memory traffic).
+static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, int sr, MarRem* r) {
+  r->whole_units = (int32_t)units; r->k = 1; r->tps = 0; r->rows = 0;
+  const long slots = 256L * wgs_per_cu(d, pass);
+  if (sy != 1 || units < slots || units % slots == 0 || (!d.bilinear && pass == 2)) return;
+  const int ty = mar_tile_rows(d, pass);
+  const long ntiles = (n_y + ty - 1) / ty, rem = units % slots;
+  long k = slots / rem;
+  if (k > MAR_MAX_PARTS) k = MAR_MAX_PARTS;
+  if (k > ntiles) k = ntiles;
+  if (d.bilinear) {
+    const double unit_us = 12.0 * sr * (double)n_y * d.dk * (double)slots / 1.0e9;
+    double best = 1e30;
+    k = 1;
+    for (long kk = 1; kk <= MAR_MAX_PARTS && kk <= ntiles; ++kk) {
+      const double cost = (double)((rem * kk + slots - 1) / slots) / (double)kk * unit_us + (double)(kk - 1) * rem * sr * d.dk * 8.0 / 4.5e6;
+      if (cost < best) { best = cost; k = kk; }
+    }
+  }
+  if (k < 2) return;
+  r->whole_units = (int32_t)(units - rem);
+  r->tps = (int32_t)((ntiles + k - 1) / k);
+  r->k = (int32_t)((ntiles + r->tps - 1) / r->tps);
+  r->rows = (int64_t)rem * sr;
+}
+
 static int check_config(const mar_config* cfg, MarDims* d) {
   if (!cfg) return fail(MAR_EINVAL, "config is NULL");
   if (cfg->num_nodes < 1 || cfg->num_rels < 1) return fail(MAR_EINVAL, "num_nodes and num_rels must be >= 1");
@@ -71,104 +133,25 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   d->ipw_log2 = ids <= ((int64_t)1 << 22) ? 2 : 5;       // small id spaces: one byte per id, no atomics
   d->nwords = (ids + (1 << d->ipw_log2) - 1) >> d->ipw_log2;
   if (!mar_flash_supported(d->dk)) return fail(MAR_ERANGE, "row width %d not supported by the contraction kernels", d->dk);
-  d->split = cfg->precision == MAR_PRECISION_SPLIT_BF16;
-  if (d->split && !mar_split_supported(d->dk)) return fail(MAR_ERANGE, "row width %d not supported by the split-precision kernels", d->dk);
-  // The contraction kernels address one chunk-side's rows of either operand, and its block of weights, with 32-bit
-  // byte offsets.
+  d->bilinear = cfg->model != MAR_MODEL_TRANSE;
+  d->split_bf16 = cfg->precision == MAR_PRECISION_SPLIT_BF16;
+  if (d->bilinear && !mar_split_supported(d->dk)) return fail(MAR_ERANGE, "row width %d not supported by the contraction kernels", d->dk);
+  // The contraction kernels of TransE address one chunk-side's rows of either operand, and its block of weights, with
+  // 32-bit byte offsets; the limit holds for every model.
   {
     const int64_t rows = d->S > d->N ? d->S : d->N;
     const int64_t tp = (d->N + 127) & ~(int64_t)127, tr_ = (d->S + 63) & ~(int64_t)63;
     if (rows * d->dk * 4 >= ((int64_t)1 << 31) || tp * tr_ * 4 >= ((int64_t)1 << 31))
       return fail(MAR_ERANGE, "chunk too large: rows x row bytes of a chunk's edges or negatives, and chunk edges x negatives x 4, must be below 2^31");
-    if (d->split && ((rows + 31) / 32) * (int64_t)mar_split_image_bytes(d->dk) >= ((int64_t)1 << 31))
+    if (d->split_bf16 && ((rows + 31) / 32) * (int64_t)mar_split_image_bytes(d->dk) >= ((int64_t)1 << 31))
       return fail(MAR_ERANGE, "chunk too large for the split-precision operand images (2^31 bytes per chunk and side)");
   }
-  const int sp = d->split;
-  auto stripe_rows = [&](int pass) { return sp ? mar_split_stripe_rows(d->dk, pass) : mar_flash_stripe_rows(d->dk, pass); };
-  auto tile_rows = [&](int pass) { return sp ? mar_split_tile_rows() : mar_flash_tile_rows(d->dk, pass); };
-  auto wgs_per_cu = [&](int pass) { return sp ? mar_split_wgs_per_cu(d->dk, pass) : mar_flash_wgs_per_cu(d->dk, pass); };
-  // Small batches give too few (chunk-side, 64-row stripe) workgroups to fill 256 CUs: let several
-  // workgroups share a stripe, each streaming a slice of the other matrix, until a pass has at least
-  // MAR_FLASH_TARGET_WGS workgroups (measured best for a 10,000-edge batch; the 50,000-edge shapes have
-  // enough stripes and are not split).
-  // Split precision: into how many parts to cut the (chunk-side, stripe) units beyond the last whole round.  The
-  // units are fewer and longer than the fp32 passes', and the remainder often exceeds half a round, so the parts may
-  // take several rounds of their own; every part beyond the first costs a write and a read of the stripes' output
-  // rows.  Estimated in microseconds from the rates these passes reach (about 600 TFLOP/s of bf16 work over all
-  // workgroup slots, 4.5 TB/s of memory traffic): the time of the last rounds plus the merge.
-  auto split_parts = [&](long rem_units, long slots, long ntiles, int sr, int n_y, long rows_per_cs) -> long {
-    const double unit_us = 12.0 * sr * (double)n_y * d->dk * (double)slots / 6.0e8;
-    const double rows = (double)rem_units / (double)((rows_per_cs + sr - 1) / sr) * (double)rows_per_cs;
-    long k = 1;
-    double best = 1e30;
-    for (long kk = 1; kk <= MAR_MAX_PARTS && kk <= ntiles; ++kk) {
-      const double cost = (double)((rem_units * kk + slots - 1) / slots) / (double)kk * unit_us
-                        + (double)(kk - 1) * rows * d->dk * 8.0 / 4.5e6;
-      if (cost < best) { best = cost; k = kk; }
-    }
-    return k;
-  };
-  auto split = [&](int pass, int n_x, int n_y, int32_t* sy, int32_t* tps) {
-    const long target = pass == 1 ? MAR_FLASH_TARGET_WGS1 : MAR_FLASH_TARGET_WGS2;
-    const int sr = stripe_rows(pass);
-    const long wgs = 2L * d->C * ((n_x + sr - 1) / sr);
-    const int ty = tile_rows(pass);
-    const int ntiles = (n_y + ty - 1) / ty;
-    long want = (target + wgs - 1) / wgs;
-    if (want > 8) want = 8;
-    if (want > ntiles) want = ntiles;
-    if (want < 1) want = 1;
-    *tps = (int32_t)((ntiles + want - 1) / want);
-    *sy = (int32_t)((ntiles + *tps - 1) / *tps);
-  };
-  split(1, d->S, d->N, &d->sy1, &d->tps1);
-  split(2, d->N, d->S, &d->sy2, &d->tps2);
-  // Large batches: the (chunk-side, stripe) units of pass 1 rarely fill a whole number of rounds of the chip's
-  // workgroup slots (256 CUs x workgroups per CU), and the last, partly filled round costs as much time as a full
-  // one.  Chunk-sides are dealt to the 8 XCDs in groups of 8; the groups beyond the last whole round have every
-  // stripe split into rem_k parts (each streaming rem_tps tiles), so that the last round is short.
-  d->rem_cs0 = 2 * d->C; d->rem_k = 1; d->rem_tps = 0; d->rem_rows = 0;
-  if (d->sy1 == 1) {
-    const long slots = 256L * wgs_per_cu(1);
-    const int sr1 = stripe_rows(1);
-    const long nstripes = (d->S + sr1 - 1) / sr1, groups = (2L * d->C + 7) / 8, per_group = 8 * nstripes;
-    const int ty = tile_rows(1);
-    const long ntiles = (d->N + ty - 1) / ty;
-    const long full_rounds = groups * per_group / slots;
-    const long whole_groups = full_rounds * slots / per_group;
-    if (full_rounds >= 1 && whole_groups < groups) {
-      const long rem_units = (2L * d->C - 8 * whole_groups) * nstripes;
-      long k = slots / rem_units;
-      if (k > MAR_MAX_PARTS) k = MAR_MAX_PARTS;
-      if (k > ntiles) k = ntiles;
-      if (sp) k = split_parts(rem_units, slots, ntiles, sr1, d->N, nstripes * sr1);
-      if (k >= 2) {
-        d->rem_cs0 = (int32_t)(8 * whole_groups);
-        d->rem_tps = (int32_t)((ntiles + k - 1) / k);
-        d->rem_k = (int32_t)((ntiles + d->rem_tps - 1) / d->rem_tps);
-        d->rem_rows = (int64_t)(2 * d->C - d->rem_cs0) * ((d->S + 63) & ~63);
-      }
-    }
-  }
-  d->rem2_cs0 = 2 * d->C; d->rem2_k = 1; d->rem2_tps = 0; d->rem2_rows = 0;
-  if (sp && d->sy2 == 1) {                                 // the same for pass 2 (split precision only)
-    const long slots = 256L * wgs_per_cu(2);
-    const int sr2 = stripe_rows(2);
-    const long nstripes = (d->N + sr2 - 1) / sr2, groups = (2L * d->C + 7) / 8, per_group = 8 * nstripes;
-    const long ntiles = (d->S + tile_rows(2) - 1) / tile_rows(2);
-    const long full_rounds = groups * per_group / slots;
-    const long whole_groups = full_rounds * slots / per_group;
-    if (full_rounds >= 1 && whole_groups < groups) {
-      const long rem_units = (2L * d->C - 8 * whole_groups) * nstripes;
-      const long k = split_parts(rem_units, slots, ntiles, sr2, d->S, nstripes * sr2);
-      if (k >= 2) {
-        d->rem2_cs0 = (int32_t)(8 * whole_groups);
-        d->rem2_tps = (int32_t)((ntiles + k - 1) / k);
-        d->rem2_k = (int32_t)((ntiles + d->rem2_tps - 1) / d->rem2_tps);
-        d->rem2_rows = (int64_t)(2 * d->C - d->rem2_cs0) * (nstripes * sr2);
-      }
-    }
-  }
+  const int sr1 = mar_stripe_rows(*d, 1), sr2 = mar_stripe_rows(*d, 2);
+  const long units1 = 2L * d->C * ((d->S + sr1 - 1) / sr1), units2 = 2L * d->C * ((d->N + sr2 - 1) / sr2);
+  mar_plan_parts(*d, 1, units1, d->N, &d->sy1, &d->tps1);
+  mar_plan_parts(*d, 2, units2, d->S, &d->sy2, &d->tps2);
+  plan_rem(*d, 1, units1, d->N, d->sy1, sr1, &d->rem1);
+  plan_rem(*d, 2, units2, d->S, d->sy2, sr2, &d->rem2);
   d->n_pos_max = roles * (int64_t)cfg->batch_size + 2 * cn * d->sy2;
   // Sort keys are ranks below u_max: as few passes as digits of at most MAR_SORT_MAX_BITS bits allow.
   int nbits = 1;
@@ -209,23 +192,31 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.perm = (int32_t*)take(n_pos * 4);
   l.rank_sorted = (int32_t*)take(n_pos * 4);
   l.owners = (int32_t*)take(blocks * 4);
-  l.Q = (float*)take(2 * B * dk * 4);
-  l.Km = (float*)take(2 * CN * dk * 4);
-  l.qq = (float*)take(2 * B * 4);
-  l.kk = (float*)take(2 * CN * 4);
+  // TransE: dense operands and stored weights; bilinear models: operand images, no weights (pass 2 computes the scores again)
+  const bool bl = d.bilinear != 0;
+  l.Q = (float*)take(bl ? 0 : 2 * B * dk * 4);
+  l.Km = (float*)take(bl ? 0 : 2 * CN * dk * 4);
+  l.qq = (float*)take(bl ? 0 : 2 * B * 4);
+  l.kk = (float*)take(bl ? 0 : 2 * CN * 4);
   l.pos = (float*)take(B * 4);
   l.lse = (float*)take(2 * B * 4);
   l.gQ = (float*)take((size_t)d.sy1 * 2 * B * dk * 4);
   l.ml = (float*)take((size_t)d.sy1 * 2 * B * 2 * 4);
-  l.gQx = (float*)take((size_t)(d.rem_k - 1) * (size_t)d.rem_rows * dk * 4);
-  l.mlx = (float*)take((size_t)(d.rem_k - 1) * (size_t)d.rem_rows * 2 * 4);
-  // the split-precision passes keep no weights: pass 2 computes the scores again
-  l.T = (float*)take(d.split ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)((d.N + 127) & ~127) * 4);
-  l.R = (float*)take(d.split ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)(((d.N + 127) & ~127) / 16) * 4);
-  l.Kimg = (char*)take(d.split ? 2 * (size_t)d.C * (size_t)((d.N + 31) / 32) * mar_split_image_bytes(d.dk) : 0);
-  l.Qimg = (char*)take(d.split ? 2 * (size_t)d.C * (size_t)((d.S + 31) / 32) * mar_split_image_bytes(d.dk) : 0);
-  l.Gx = (float*)take((size_t)(d.rem2_k - 1) * (size_t)d.rem2_rows * dk * 4);
+  l.gQx = (float*)take((size_t)(d.rem1.k - 1) * (size_t)d.rem1.rows * dk * 4);
+  l.mlx = (float*)take((size_t)(d.rem1.k - 1) * (size_t)d.rem1.rows * 2 * 4);
+  l.T = (float*)take(bl ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)((d.N + 127) & ~127) * 4);
+  l.R = (float*)take(bl ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)(((d.N + 127) & ~127) / 16) * 4);
+  const size_t ktiles = 2 * (size_t)d.C * (size_t)((d.N + 31) / 32), qtiles = 2 * (size_t)d.C * (size_t)((d.S + 31) / 32);
+  l.Kimg = (char*)take(bl ? ktiles * mar_split_image_bytes(d.dk) : 0);
+  l.Qimg = (char*)take(bl ? qtiles * mar_split_image_bytes(d.dk) : 0);
+  l.Gx = (float*)take((size_t)(d.rem2.k - 1) * (size_t)d.rem2.rows * dk * 4);
   l.G = (float*)take(n_pos * dk * 4);
+  // evaluation's norms, and with bf16 images (which have no exponents) its exponents, lie in the gradient rows that it has
+  // no other use for
+  const bool own_exp = bl && !d.split_bf16;
+  l.Kexp = own_exp ? (float*)take(ktiles * 8) : l.G;
+  l.Qexp = own_exp ? (float*)take(qtiles * 8) : l.G + ktiles * 2;
+  l.Knorm = l.G + ktiles * 2 + qtiles * 2;
   l.carry = (float*)take(blocks * 2 * dk * 4);
   l.loss_part = (float*)take((B / 4 + 2) * 4);
   l.metric_part = take((size_t)MAR_METRIC_MAX_PARTS * MAR_METRIC_PART_BYTES);
@@ -269,13 +260,6 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
   hipEvent_t* evs[4] = {&c->ev_fork, &c->ev_index, &c->ev_pass1, &c->ev_chain};
   for (int i = 0; i < 4 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(evs[i], hipEventDisableTiming);
   if (e == hipSuccess) e = mar_launch_init(c, fill, (hipStream_t)hip_stream);
-  if (e == hipSuccess && d.split) {
-    // the images' padding rows (beyond a chunk's rows, up to whole tiles of 32) are never written again: zeros
-    const size_t kb = 2 * (size_t)d.C * (size_t)((d.N + 31) / 32) * mar_split_image_bytes(d.dk);
-    const size_t qb = 2 * (size_t)d.C * (size_t)((d.S + 31) / 32) * mar_split_image_bytes(d.dk);
-    e = mar_launch_fill_u32((uint32_t*)c->L.Kimg, (int64_t)(kb / 4), 0u, (hipStream_t)hip_stream);
-    if (e == hipSuccess) e = mar_launch_fill_u32((uint32_t*)c->L.Qimg, (int64_t)(qb / 4), 0u, (hipStream_t)hip_stream);
-  }
   if (e != hipSuccess) { mar_destroy(c); return hip_fail(e, "context set-up"); }
   *out = c;
   return MAR_OK;
@@ -351,7 +335,7 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   // longer path to the reduce, so it starts first and the gather runs beside it.
   if (c->dm.index_after_gather) {
     MARK(1, 0, st);
-    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split, st), "gather kernel");
+    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
     MARK(1, 1, st);
   }
   HIP_TRY(hipEventRecord(c->ev_fork, st), "fork");
@@ -363,7 +347,7 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   HIP_TRY(hipEventRecord(c->ev_index, ax), "join");
   if (!c->dm.index_after_gather) {
     MARK(1, 0, st);
-    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split, st), "gather kernel");
+    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
     MARK(1, 1, st);
   }
   MARK(2, 0, st);
@@ -413,7 +397,7 @@ extern "C" int mar_eval_scores(mar_ctx* c, const int32_t* src, const int32_t* re
   if (!rank_dst || !rank_src) return fail(MAR_EINVAL, "a rank output pointer is NULL");
   if (n_edges == 0) return MAR_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  HIP_TRY(mar_launch_prep(c, b, pos_scores, 0, st), "gather kernel");
+  HIP_TRY(mar_launch_prep(c, b, pos_scores, 0, rank_dst, rank_src, st), "gather kernel");
   HIP_TRY(mar_launch_flash(c, b, 3, rank_dst, rank_src, st), "rank kernel");
   return MAR_OK;
 }
@@ -630,7 +614,7 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
   PIPE_TRY(hipEventRecord(ps.ev_in, p->s_in), "stage in");
   // ---- step on the caller's stream: staged rows, ranks as ids; node gradients are left in gsum, relation rows updated
   PIPE_TRY(hipStreamWaitEvent(st, ps.ev_in, 0), "step");
-  PIPE_TRY(mar_launch_prep(c, ps.b_rank, nullptr, c->dm.split, st), "gather kernel");
+  PIPE_TRY(mar_launch_prep(c, ps.b_rank, nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
   PIPE_TRY(mar_launch_flash(c, ps.b_rank, 1, nullptr, nullptr, st), "score/softmax kernel");
   PIPE_TRY(mar_launch_flash_merge(c, ps.b_rank, st), "stripe merge kernel");
   PIPE_TRY(mar_launch_chain(c, ps.b_rank, st), "chain-rule kernel");

@@ -26,27 +26,37 @@ struct MarLayout {
   int32_t*  perm;         // position in row-sorted order -> gradient row
   int32_t*  rank_sorted;  // position -> rank
   int32_t*  owners;       // [reduce blocks] workgroups of the reduce in which a segment begins that continues into later ones
-  float*    Q;            // [2][batch][dk] edge-side operands (side-major)
-  float*    Km;           // [2][chunks][N][dk] gathered negative rows
+  float*    Q;            // TransE: [2][batch][dk] edge-side operands (side-major)
+  float*    Km;           // TransE: [2][chunks][N][dk] gathered negative rows
   float*    qq;           // [2][batch] squared norms of Q rows (TransE)
   float*    kk;           // [2][chunks*N] squared norms of Km rows (TransE)
   float*    pos;          // [batch] positive scores
   float*    lse;          // [2][batch] log-sum-exp per edge and side
   float*    gQ;           // [sy1][2][batch][dk] per-part unnormalised gradient w.r.t. Q rows
-  float*    ml;           // [sy1][2][batch][2] per-part softmax reference and sum
-  float*    gQx;          // [rem_k - 1][rem_rows][dk] parts 1.. of the chunk-sides whose stripes are split to fill the last round
-  float*    mlx;          // [rem_k - 1][rem_rows][2]
-  float*    T;            // [2*chunks][S rounded up to 64][N rounded up to 128] softmax weights exp(score - reference)
-                          // (TransE: divided by the distance), pass 1 -> pass 2
-  float*    R;            // [2*chunks][N rounded up to 128, / 16][S rounded up to 64] the reference each 16-negative block of T was written with
-  char*     Kimg;         // split precision: [2*chunks][N / 32 rounded up][image] bf16 hi/lo planes of Km's rows
-  char*     Qimg;         // split precision: [2*chunks][S / 32 rounded up][image] the same of Q's rows
-  float*    Gx;           // [rem2_k - 1][rem2_rows][dk] parts 1.. of pass 2's split stripes (split precision)
+  float*    ml;           // [sy1][2][batch][2] per-part softmax reference (bilinear models: in log2 units) and sum
+  float*    gQx;          // [rem1.k - 1][rem1.rows][dk] parts 1.. of the stripes that are split to fill the last round
+  float*    mlx;          // [rem1.k - 1][rem1.rows][2]
+  float*    T;            // TransE: [2*chunks][S rounded up to 64][N rounded up to 128] softmax weights exp(score - reference)
+                          // divided by the distance, pass 1 -> pass 2
+  float*    R;            // TransE: [2*chunks][N rounded up to 128, / 16][S rounded up to 64] the reference each 16-negative block of T was written with
+  char*     Kimg;         // bilinear models: [2*chunks][N / 32 rounded up][image] hi/lo planes of the negatives' rows (mar_split.h)
+  char*     Qimg;         // bilinear models: [2*chunks][S / 32 rounded up][image] the same of the edge-side operands
+  float*    Kexp;         // exponents of the images' 16-row blocks, [2*chunks][2 * image tiles]
+  float*    Qexp;
+  float*    Knorm;        // evaluation: bounds of the norms of Kimg's scaled rows, per 16-row block
+  float*    Gx;           // [rem2.k - 1][rem2.rows][dk] parts 1.. of pass 2's split stripes (bilinear models)
   float*    G;            // [roles*n + 2*cn*sy2][dk] gradient rows: edge-side occurrence k < roles*n at row k, part i
                           // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i
   float*    carry;        // [reduce blocks][2][dk] partial sums of segments that cross workgroup borders
   float*    loss_part;    // per-block partial loss sums
   void*     metric_part;  // [MAR_METRIC_MAX_PARTS] partial records of the rank metrics
+};
+
+// A full batch's (chunk-side, stripe) units beyond the last whole round of the chip's workgroup slots: units from
+// whole_units on are each split into k parts of tps streamed tiles, which a small kernel merges.
+struct MarRem {
+  int32_t whole_units, k, tps;
+  int64_t rows;                    // stripe rows of all split units
 };
 
 struct MarDims {
@@ -58,22 +68,17 @@ struct MarDims {
   int64_t n_pos_max;               // roles*B + 2CN*sy2: gradient rows per step
   int32_t sy1, sy2;                // how many workgroups share the streamed rows of one stripe (pass 1 / 2)
   int32_t tps1, tps2;              // streamed tiles per workgroup
-  // Pass 1 of a full batch: (chunk-side, stripe) units beyond the last whole round of workgroups -- all stripes of the
-  // chunk-sides from rem_cs0 on -- are each split into rem_k parts of rem_tps tiles, which a small kernel merges.
-  int32_t rem_cs0, rem_k, rem_tps;
-  int64_t rem_rows;                // (2C - rem_cs0) * (S rounded up to 64)
-  // The same for pass 2 in split precision (chunk-sides counted in that pass's launch order): parts 1.. of a split
-  // stripe write their gradient rows to Gx, and a small kernel adds them to the regular rows.
-  int32_t rem2_cs0, rem2_k, rem2_tps;
-  int64_t rem2_rows;               // (2C - rem2_cs0) * (N rounded up to whole stripes)
+  MarRem rem1, rem2;               // split stripes of pass 1; of pass 2 (bilinear models): parts 1.. are added by a small kernel
   int64_t u_max;                   // min(num_nodes + num_rels, n_occ_max)
   int64_t nwords;                  // words of the touched-id map
   int32_t ipw_log2;                // ids per word: 5 = one bit per id (atomic marks), 2 = one byte per id (plain stores)
   int32_t sort_passes, sort_bits;  // radix sort of the gradient rows by rank: passes, bits per pass
-  int32_t split;                   // the contraction passes run in split precision (bf16 hi + lo operands)
+  int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
+  int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
 };
 
+#define MAR_LN2 0.69314718055994531f
 #define MAR_MAX_PARTS 8                   // most parts a stripe of pass 1 is split into
 #define MAR_MAX_PROFILE_STEPS 4096
 
@@ -127,8 +132,10 @@ struct MarBatch {
 };
 
 hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, hipStream_t st);
-// images != 0 (split-precision training): the operands are written as bf16 hi/lo images instead of fp32 rows
-hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int images, hipStream_t st);
+// bf16 != 0 (SPLIT_BF16 training): the operand images hold bf16 instead of scaled f16 parts
+// rank_dst / rank_src (evaluation): set to 1
+hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
+                           hipStream_t st);
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
                             hipStream_t st);
 hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, hipStream_t st);
@@ -154,10 +161,14 @@ int mar_flash_stripe_rows(int dk, int pass);
 hipError_t mar_flash_prepare();   // once per process and device before the first contraction launch (LDS size limits)
 int mar_flash_wgs_per_cu(int dk, int pass);        // workgroups of a pass that a CU holds at once
 hipError_t mar_launch_flash_merge(const mar_ctx* c, const MarBatch& b, hipStream_t st);   // after pass 1: merges split stripes
-// Split-precision passes (mar_split.hip): geometry for the planning of a configuration, and the launches.
+// Passes of the bilinear models (mar_split.hip): geometry for the planning of a configuration, and the launches.
 int mar_split_supported(int dk);
-int mar_split_stripe_rows(int dk, int pass);
-int mar_split_tile_rows();
-int mar_split_wgs_per_cu(int dk, int pass);
+int mar_split_wgs_per_cu(int dk);
+#define MAR_SPLIT_STRIPE_ROWS 128
+#define MAR_SPLIT_TILE_ROWS 32
+static inline int mar_stripe_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }
+static inline int mar_tile_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_TILE_ROWS : mar_flash_tile_rows(d.dk, pass); }
+// How many workgroups share one of `units` units of a pass, and the streamed tiles each takes (n_y streamed rows).
+void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps);
 size_t mar_split_image_bytes(int dk);
 hipError_t mar_split_prepare();

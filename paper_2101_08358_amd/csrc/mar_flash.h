@@ -20,11 +20,14 @@ struct FlashArgs {
   int32_t sy;          // workgroups sharing one stripe, each streaming `tps` tiles
   int32_t tps;
   int32_t sy_ml;       // parts pass 1 was split into
-  // pass 1 of a full batch: workgroup slots (per XCD) from whole_slots on take the stripes of chunk-sides
-  // rem_cs0.. in rem_k parts of rem_tps tiles each; parts 1.. write to mlx / outx [part - 1][rem_rows]
-  int32_t whole_slots, rem_cs0, rem_k, rem_tps;
+  // Units of work: unit = chunk-side * nstripes + stripe.  Units below whole_units are taken by `sy` workgroups each;
+  // the rest (full batches: what lies beyond the last whole round of the chip's workgroup slots) by rem_k workgroups of
+  // rem_tps tiles each, whose parts 1.. write to mlx / outx [part - 1][rem_rows] (sr rows per unit) and are merged by
+  // a small kernel.  wslots / rslots: workgroups per XCD for the two kinds.
+  int32_t units, whole_units, wslots, rslots, sr, rem_k, rem_tps;
   int64_t rem_rows;
   float* mlx; float* outx;
+  float ml_log2;       // natural-log units of one unit of the references in ml: 1, or ln 2 where they are kept in log2 units
   int32_t roles;       // edge-side occurrences per edge (3, or 2 for Dot)
   float* T;            // [2*nchunks][trows][tpitch] softmax weight exp(score - reference) of every (edge, negative)
                        // pair (TransE: divided by the distance): written by pass 1, read by the negatives' gradient
@@ -35,7 +38,31 @@ struct FlashArgs {
   // split-precision passes: bf16 hi/lo images of the streamed matrix, [2*nchunks][yimg_tiles][image bytes]
   const char* yimg; int32_t yimg_tiles;
   const char* ximg; int32_t ximg_tiles;   // the same of the stationary matrix
+  // evaluation of the bilinear models: fp32 edge-side operands [2][B][dk], the node table and the negatives' ids, from
+  // which close comparisons are settled
+  const float* qrows; const float* ynorm; const float* table; const int32_t* neg_dst; const int32_t* neg_src; int32_t dim;
+  const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
+
+// Which unit and part a workgroup takes.  Consecutive workgroup ids rotate over the 8 XCDs; XCD j is given a
+// contiguous eighth of the units, so that the workgroups of one chunk-side share an L2 and every XCD gets the same
+// number of units however few chunk-sides there are.
+struct FlashUnit { int unit, cs, stripe, part, tps; bool rem; };
+__device__ __forceinline__ bool flash_unit(const FlashArgs& a, FlashUnit& u) {
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  u.rem = slot >= a.wslots;
+  if (!u.rem) {
+    const int w = xcd * a.wslots + slot;
+    u.unit = w / a.sy; u.part = w % a.sy; u.tps = a.tps;
+    if (u.unit >= a.whole_units) return false;
+  } else {
+    const int w = xcd * a.rslots + (slot - a.wslots);
+    u.unit = a.whole_units + w / a.rem_k; u.part = w % a.rem_k; u.tps = a.rem_tps;
+    if (u.unit >= a.units) return false;
+  }
+  u.cs = u.unit / a.nstripes; u.stripe = u.unit % a.nstripes;
+  return true;
+}
 
 __device__ __forceinline__ v4f mfma16(float a, float b, v4f c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -89,5 +116,5 @@ __device__ __forceinline__ unsigned lds_address(const float* p) {
 // that this occupancy leaves to a wave, and does not trade spills for a higher occupancy.
 #define MAR_WAVES_PER_SIMD(n) __attribute__((amdgpu_waves_per_eu(n, n)))
 
-// Launch of a split-precision pass (mar_split.hip); `a` as filled by mar_launch_flash.
-hipError_t mar_split_launch(const FlashArgs& a, int pass, dim3 grid, hipStream_t st);
+// Launch of a pass of the bilinear models (mar_split.hip); `a` as filled by mar_launch_flash.
+hipError_t mar_split_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st);

@@ -48,7 +48,7 @@ __device__ __forceinline__ void load_orow(const float* __restrict__ yr, int m, f
 // Writes the accumulators of one stationary row back in row order, undoing the column grouping of
 // load_orow: lane (g, .) register t of block cb holds output row i = 4g + t.  `sub` (TransE) is
 // subtracted as xs[c] * ws.
-template <int NC, bool SUB>
+template <int NC>
 __device__ __forceinline__ void store_orow(float* __restrict__ orow, const float* __restrict__ xs, float ws, int dk, int g,
                                            const v4f (&o)[NC]) {
   constexpr int NG4 = NC / 4, NG2 = (NC % 4) / 2, NG1 = NC % 2;
@@ -59,7 +59,7 @@ __device__ __forceinline__ void store_orow(float* __restrict__ orow, const float
       const int col = 64 * q + 16 * g + 4 * t;
       if (col < dk) {
         float4 v = make_float4(o[4 * q][t], o[4 * q + 1][t], o[4 * q + 2][t], o[4 * q + 3][t]);
-        if (SUB) {
+        {
           const float4 x = *reinterpret_cast<const float4*>(xs + col);
           v.x -= x.x * ws; v.y -= x.y * ws; v.z -= x.z * ws; v.w -= x.w * ws;
         }
@@ -73,7 +73,7 @@ __device__ __forceinline__ void store_orow(float* __restrict__ orow, const float
       const int col = 64 * NG4 + 8 * g + 2 * t;
       if (col < dk) {
         float2 v = make_float2(o[4 * NG4][t], o[4 * NG4 + 1][t]);
-        if (SUB) {
+        {
           const float2 x = *reinterpret_cast<const float2*>(xs + col);
           v.x -= x.x * ws; v.y -= x.y * ws;
         }
@@ -85,7 +85,7 @@ __device__ __forceinline__ void store_orow(float* __restrict__ orow, const float
     const int col = 64 * NG4 + 32 * NG2 + 4 * g;
     if (col < dk) {
       float4 v = make_float4(o[NC - 1][0], o[NC - 1][1], o[NC - 1][2], o[NC - 1][3]);
-      if (SUB) {
+      {
         const float4 x = *reinterpret_cast<const float4*>(xs + col);
         v.x -= x.x * ws; v.y -= x.y * ws; v.z -= x.z * ws; v.w -= x.w * ws;
       }
@@ -116,7 +116,7 @@ struct StageMap {
   static_assert(!PO2 || TY % RPS == 0, "tile rows must be a multiple of the rows per staging step");
 };
 
-// PASS: 1 scores + online softmax + gQ (training), 3 rank counts (evaluation).  L2: TransE scores.
+// PASS: 1 scores + online softmax + gQ (training), 3 rank counts (evaluation; ranks start at 1 and parts of a stripe add their counts).
 // XB: 16-row x-blocks per wave (a workgroup's stripe has 64*XB stationary rows); every LDS
 // fragment of Y then feeds XB matrix instructions.
 // LDS reads run one phase ahead of the matrix instructions that consume them: the first
@@ -138,7 +138,7 @@ struct FwdGeom {
 // copied into LDS by buffer loads that write LDS directly (16 bytes per lane, 1 KB per wave instruction, zeros
 // beyond the chunk's rows), two tiles ahead of their use in two alternating buffers: no staging registers, no
 // LDS stores, one barrier per tile.  Otherwise tiles pass through registers into one padded LDS buffer.
-template <int NK, int NC, int VT, int TY, int XB, int PASS, int L2, int DMA>
+template <int NK, int NC, int VT, int TY, int XB, int PASS, int DMA>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD((NK * XB <= 64 ? 2 : 1))
 k_flash(FlashArgs a) {
   typedef FlashGeom<NK> GM;
@@ -156,24 +156,9 @@ k_flash(FlashArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, m = lane & 15;
 
-  // workgroup -> (chunk-side, stripe, part); consecutive workgroup ids rotate over the 8 XCDs, so
-  // all workgroups of one chunk-side are given ids with the same residue and share one L2.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int part, cs, stripe, tps = a.tps;
-  if (slot < a.whole_slots) {
-    part = slot % a.sy;
-    const int slot2 = slot / a.sy;
-    cs = (slot2 / a.nstripes) * 8 + xcd;
-    stripe = slot2 % a.nstripes;
-  } else {                                                // a part of a split stripe: these go round all XCDs
-    const int r = (slot - a.whole_slots) * 8 + xcd;
-    const int unit = r / a.rem_k;
-    part = r % a.rem_k;
-    cs = a.rem_cs0 + unit / a.nstripes;
-    stripe = unit % a.nstripes;
-    tps = a.rem_tps;
-  }
-  if (cs >= 2 * a.nchunks) return;
+  FlashUnit u;
+  if (!flash_unit(a, u)) return;
+  const int part = u.part, cs = u.cs, stripe = u.stripe, tps = u.tps;
   const int side = cs & 1, c = cs >> 1;
   const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
   const int n_x = ne;                                     // stationary: the chunk's edges
@@ -206,7 +191,7 @@ k_flash(FlashArgs a) {
       xf[b][4 * N16 + j] = (xv[b] && col < dk) ? xrow[b][col] : 0.f;
     }
     xnorm[b] = 0.f; posx[b] = 0.f;
-    if (L2) xnorm[b] = xv[b] ? a.xx[x_base + x[b]] : 0.f;
+    xnorm[b] = xv[b] ? a.xx[x_base + x[b]] : 0.f;
     if (PASS == 3) posx[b] = xv[b] ? a.pos[(size_t)c * a.S + x[b]] : 0.f;
   }
 
@@ -256,7 +241,7 @@ k_flash(FlashArgs a) {
   // meets zero fragments of the stationary rows in the score product and produces output columns that are
   // never stored.
   const BufRsrc ysrc = buf_rsrc(a.Y + y_base * dk, (uint32_t)n_y * dk * 4);
-  const BufRsrc yysrc = buf_rsrc(L2 ? a.yy + y_base : a.Y, L2 ? (uint32_t)n_y * 4 : 0u);
+  const BufRsrc yysrc = buf_rsrc(a.yy + y_base, (uint32_t)n_y * 4);
   int s_gofs[SM::PO2 ? 1 : NU];                            // wide rows: one offset per slot, kept in registers
   if (SM::PO2) s_gofs[0] = (s_r0 * dk + s_col) * 4;
   else {
@@ -270,13 +255,12 @@ k_flash(FlashArgs a) {
       if (SM::PO2) stage[u] = buf_load4(ysrc, s_gofs[0], tofs + u * SM::RPS * dk * 4);
       else stage[u] = buf_load4(ysrc, s_gofs[u], tofs);
     }
-    if (L2) st_auy = buf_load1(yysrc, (int)(threadIdx.x % TY) * 4, t * TY * 4);
+    st_auy = buf_load1(yysrc, (int)(threadIdx.x % TY) * 4, t * TY * 4);
   };
   // DMA path: wave w copies the tile's 1 KB pieces w, w + 4, ... ; a register load issued behind them is the
   // fence: memory operations complete in order, so once its value is there the pieces are in LDS.
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const v4i ywords = buf_words(a.Y + y_base * dk, (uint32_t)n_y * dk * 4);
-  float fence = 0.f;
   int token = 0;
   constexpr int NCH = TY * NK / 64;                        // 1 KB pieces per tile
   constexpr int NCW = (NCH + 3) / 4;                       // pieces per wave
@@ -288,19 +272,15 @@ k_flash(FlashArgs a) {
     if (c < NCH) buf_load4_to_lds(ywords, lds_address(smem) + (buf * FG::TILE + c * 256) * 4, lane * 16, tofs + c * 1024, token);
     if (q == NCW - 1) {
       // the fence load's offset passes through the copies, so it is issued behind them
-      if (L2) st_auy = buf_load1(yysrc, (int)(threadIdx.x % TY) * 4 + token, t * TY * 4);
-      else fence = buf_load1(ysrc, token, tofs);
+      st_auy = buf_load1(yysrc, (int)(threadIdx.x % TY) * 4 + token, t * TY * 4);
     }
   };
   auto dma_tile = [&](int t, int buf) {
 #pragma unroll
     for (int q = 0; q < NCW; ++q) dma_piece(t, buf, q);
   };
-  // the fence value is consumed (for TransE: stored) before the barrier that publishes tile t in buffer `buf`
-  auto dma_land = [&](int buf) {
-    if (L2) auy_all[buf * TY + threadIdx.x % TY] = st_auy;
-    else asm volatile("" : : "v"(fence));
-  };
+  // the fence value is stored before the barrier that publishes tile t in buffer `buf`
+  auto dma_land = [&](int buf) { auy_all[buf * TY + threadIdx.x % TY] = st_auy; };
   if (t_begin < ntiles) { if (DMA) dma_tile(t_begin, 0); else load_tile(t_begin); }
 
   // fragments of the score product: q16[s] = Y[yb*16 + m][16s + 4g .. +3], q1[j] the tail columns
@@ -323,7 +303,7 @@ k_flash(FlashArgs a) {
       slot_of(u, gofs, lofs);
       if (lofs >= 0) reinterpret_cast<v4f*>(smem)[lofs] = stage[u];
     }
-    if (L2) auy_all[threadIdx.x % TY] = st_auy;            // threads that share a row write the same value
+    auy_all[threadIdx.x % TY] = st_auy;                    // threads that share a row write the same value
   };
   if (t_begin < ntiles) {
     if (DMA) dma_land(0); else stage_tile();
@@ -390,17 +370,13 @@ k_flash(FlashArgs a) {
       }
       // -- scores and weights
       float w[XB][4];
-      float yy4[4] = {0.f, 0.f, 0.f, 0.f};
-      if (L2) {
+      float yy4[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) yy4[r] = auy[yl + r];
-      }
+      for (int r = 0; r < 4; ++r) yy4[r] = auy[yl + r];
 #pragma unroll
       for (int b = 0; b < XB; ++b) {
         float sc[4], dist[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sc[r] = tacc[b][r];
-        if (L2) {
+        {
           // |q - n|^2 = |q|^2 + |n|^2 - 2 q.n cancels when n is close to q: its rounding error is of the size of
           // 2^-22 (|q|^2 + |n|^2).  Pairs whose expanded value falls below 2^-8 of that sum (the expansion is
           // then left with fewer than ~14 good bits) are recomputed from the differences q_k - n_k themselves:
@@ -472,14 +448,14 @@ k_flash(FlashArgs a) {
 #pragma unroll
             for (int cb = 0; cb < NC; ++cb) oacc[b][cb] *= alpha;
             if (VT) otail[b] *= alpha;
-            if (L2) wsum[b] *= alpha;
+            wsum[b] *= alpha;
             mrun[b] = mnew;
           }
 #pragma unroll
           for (int r = 0; r < 4; ++r) w[b][r] = __expf(sc[r] - mrun[b]);
           lrun[b] += (w[b][0] + w[b][1]) + (w[b][2] + w[b][3]);
         }
-        if (PASS != 3 && L2) {
+        if (PASS != 3) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) w[b][r] = dist[r] > 0.f ? w[b][r] / dist[r] : 0.f;
           wsum[b] += (w[b][0] + w[b][1]) + (w[b][2] + w[b][3]);
@@ -550,15 +526,12 @@ k_flash(FlashArgs a) {
   if (t_begin < ntiles) do_tile(ntiles - 1, std::false_type());
 
   // ---- epilogue: the part's statistics and unnormalised gradient rows (row x of the chunk-side at index x)
-  float* ml_out = a.ml + ((size_t)part * 2 * a.B + x_base) * 2;
-  float* o_out = a.out + ((size_t)part * 2 * a.B + x_base) * dk;
-  if (slot >= a.whole_slots && part > 0) {                // parts 1.. of a split stripe
-    const size_t xr = (size_t)(part - 1) * a.rem_rows + (size_t)(cs - a.rem_cs0) * a.trows;
-    ml_out = a.mlx + xr * 2;
-    o_out = a.outx + xr * dk;
-  } else if (slot >= a.whole_slots) {                     // part 0 of a split stripe: the regular place
-    ml_out = a.ml + x_base * 2;
-    o_out = a.out + x_base * dk;
+  float* ml_out = a.ml + ((size_t)(u.rem ? 0 : part) * 2 * a.B + x_base) * 2;
+  float* o_out = a.out + ((size_t)(u.rem ? 0 : part) * 2 * a.B + x_base) * dk;
+  if (u.rem && part > 0) {                                // parts 1.. of a split stripe, its rows counted from the stripe's first
+    const size_t xr = (size_t)(part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SR;
+    ml_out = a.mlx + xr * 2 - (size_t)stripe * SR * 2;
+    o_out = a.outx + xr * dk - (size_t)stripe * SR * dk;
   }
 #pragma unroll
   for (int b = 0; b < XB; ++b) {
@@ -566,7 +539,7 @@ k_flash(FlashArgs a) {
       int cn = cnt[b];
       cn += __shfl_xor(cn, 16);
       cn += __shfl_xor(cn, 32);
-      if (g == 0 && xv[b]) (side == MAR_SIDE_DST ? a.rank_dst : a.rank_src)[(size_t)c * a.S + x[b]] = 1 + cn;
+      if (g == 0 && xv[b] && cn) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x[b], cn);
       continue;
     }
     if (PASS == 1) {
@@ -575,10 +548,8 @@ k_flash(FlashArgs a) {
       if (g == 0 && xv[b]) *reinterpret_cast<float2*>(ml_out + (size_t)x[b] * 2) = make_float2(mrun[b], ltot);
     }
     float ws = wsum[b];
-    if (L2) {
-      ws += __shfl_xor(ws, 16);
-      ws += __shfl_xor(ws, 32);
-    }
+    ws += __shfl_xor(ws, 16);
+    ws += __shfl_xor(ws, 32);
     float4 ot = make_float4(otail[b][0], otail[b][1], otail[b][2], otail[b][3]);
     if (VT) {
       ot.x += __shfl_xor(ot.x, 16); ot.y += __shfl_xor(ot.y, 16); ot.z += __shfl_xor(ot.z, 16); ot.w += __shfl_xor(ot.w, 16);
@@ -586,10 +557,10 @@ k_flash(FlashArgs a) {
     }
     if (!xv[b]) continue;
     float* orow = o_out + (size_t)x[b] * dk;
-    store_orow<NC, L2 != 0>(orow, xrow[b], ws, dk, g, oacc[b]);
+    store_orow<NC>(orow, xrow[b], ws, dk, g, oacc[b]);
     if (VT && g == 0 && 16 * NC < dk) {
       float4 o = ot;
-      if (L2) {
+      {
         const float4 xs = *reinterpret_cast<const float4*>(xrow[b] + 16 * NC);
         o.x -= xs.x * ws; o.y -= xs.y * ws; o.z -= xs.z * ws; o.w -= xs.w * ws;
       }
@@ -609,7 +580,7 @@ k_flash(FlashArgs a) {
 #ifndef MAR_BWD_WAVES
 #define MAR_BWD_WAVES 3
 #endif
-template <int NK, int NC, int VT, int TY, int XB, int L2>
+template <int NK, int NC, int VT, int TY, int XB>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD((NK * XB <= 32 ? MAR_BWD_WAVES : 2))
 k_flash_bwd(FlashArgs a) {
   typedef FlashGeom<NK> GM;
@@ -623,17 +594,11 @@ k_flash_bwd(FlashArgs a) {
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, m = lane & 15;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int part = slot % a.sy, slot2 = slot / a.sy;
-#ifdef MAR_BWD_FORWARD_ORDER
-  const int cs = (slot2 / a.nstripes) * 8 + xcd;
-#else
+  FlashUnit u;
+  if (!flash_unit(a, u)) return;
   // Chunk-sides are taken in the reverse of pass 1's order: the weights pass 1 wrote last are still in the
   // memory-side cache when this pass starts, and it reads them first.
-  const int cs = 2 * a.nchunks - 1 - ((slot2 / a.nstripes) * 8 + xcd);
-#endif
-  const int stripe = slot2 % a.nstripes;
-  if (cs < 0 || cs >= 2 * a.nchunks) return;
+  const int cs = 2 * a.nchunks - 1 - u.cs, stripe = u.stripe, part = u.part;
   const int side = cs & 1, c = cs >> 1;
   const int n_y = min(a.S, a.n - c * a.S);                // edges in this chunk (streamed)
   const int n_x = a.N;                                    // negatives (stationary)
@@ -772,7 +737,7 @@ k_flash_bwd(FlashArgs a) {
           for (int b = 0; b < XB; ++b) w[b][r] = tr[yb][b][r] * fs;
         }
         if (HAS_NEXT) load_scores(t + 1, yb);              // refill the registers just consumed
-        if (L2) {
+        {
 #pragma unroll
           for (int b = 0; b < XB; ++b) wsum[b] += (w[b][0] + w[b][1]) + (w[b][2] + w[b][3]);
         }
@@ -813,10 +778,8 @@ k_flash_bwd(FlashArgs a) {
 #pragma unroll
   for (int b = 0; b < XB; ++b) {
     float ws = wsum[b];
-    if (L2) {
-      ws += __shfl_xor(ws, 16);
-      ws += __shfl_xor(ws, 32);
-    }
+    ws += __shfl_xor(ws, 16);
+    ws += __shfl_xor(ws, 32);
     float4 ot = make_float4(otail[b][0], otail[b][1], otail[b][2], otail[b][3]);
     if (VT) {
       ot.x += __shfl_xor(ot.x, 16); ot.y += __shfl_xor(ot.y, 16); ot.z += __shfl_xor(ot.z, 16); ot.w += __shfl_xor(ot.w, 16);
@@ -828,10 +791,10 @@ k_flash_bwd(FlashArgs a) {
     // gradient row of part `part` of this negative's occurrence (occurrences: roles*n edge-side ones, then the
     // destination-replacing negatives, then the source-replacing ones)
     float* orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x) * a.sy + part) * dk;
-    store_orow<NC, L2 != 0>(orow, xrow, ws, dk, g_e, oacc[b]);
+    store_orow<NC>(orow, xrow, ws, dk, g_e, oacc[b]);
     if (VT && g_e == 0 && 16 * NC < dk) {
       float4 o = ot;
-      if (L2) {
+      {
         const float4 xs = *reinterpret_cast<const float4*>(xrow + 16 * NC);
         o.x -= xs.x * ws; o.y -= xs.y * ws; o.z -= xs.z * ws; o.w -= xs.w * ws;
       }
@@ -847,7 +810,8 @@ __global__ void __launch_bounds__(256) k_flash_merge(FlashArgs a) {
   const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
   const long rrow = (long)blockIdx.x * 8 + grp;
   if (rrow >= a.rem_rows) return;
-  const int cs = a.rem_cs0 + (int)(rrow / a.trows), x = (int)(rrow % a.trows);
+  const int unit = a.whole_units + (int)(rrow / a.sr);
+  const int cs = unit / a.nstripes, x = (unit % a.nstripes) * a.sr + (int)(rrow % a.sr);
   const int side = cs & 1, c = cs >> 1;
   if (x >= min(a.S, a.n - c * a.S)) return;
   const size_t row = (size_t)side * a.B + (size_t)c * a.S + x;
@@ -861,7 +825,7 @@ __global__ void __launch_bounds__(256) k_flash_merge(FlashArgs a) {
   for (int p = 1; p < MAR_MAX_PARTS; ++p) mx = fmaxf(mx, v[p].x);
   float fac[MAR_MAX_PARTS], ls = 0.f;
 #pragma unroll
-  for (int p = 0; p < MAR_MAX_PARTS; ++p) { fac[p] = __expf(v[p].x - mx); ls += fac[p] * v[p].y; }
+  for (int p = 0; p < MAR_MAX_PARTS; ++p) { fac[p] = __expf((v[p].x - mx) * a.ml_log2); ls += fac[p] * v[p].y; }
   float* o0 = a.out + row * a.dk;
   for (int k = 4 * l; k < a.dk; k += 128) {
     float4 o = *reinterpret_cast<const float4*>(o0 + k);
@@ -892,22 +856,19 @@ int mar_flash_stripe_rows(int dk, int pass) { return pass == 2 && dk / 4 <= 32 ?
 
 // NK, NC, VT, TY, XB: pass 1 / 3 instantiation; BNC, BVT, BXB, BTY: pass 2's.
 template <int NK, int NC, int VT, int TY, int XB, int BNC, int BVT, int BXB, int BTY>
-static hipError_t launch_sized(const FlashArgs& a, int pass, int l2, dim3 grid, hipStream_t st) {
+static hipError_t launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStream_t st) {
   // rows of exactly 4 NK floats take the direct-to-LDS copy (widths whose unpadded pitch is a multiple of 64 floats
   // would put every row of a block in the same LDS banks and stay on the padded register path)
   constexpr bool CAN_DMA = (4 * NK) % 64 != 0;
   constexpr int DM = CAN_DMA ? 1 : 0;
   constexpr size_t lds_dma = FwdGeom<NK, TY, DM>::LDS_BYTES, lds_reg = FwdGeom<NK, TY, 0>::LDS_BYTES;
   const bool dma = CAN_DMA && a.dk == 4 * NK;
-#define FL(P, L) do { \
-    if (dma) hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, L, DM>), grid, dim3(256), lds_dma, st, a); \
-    else hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, L, 0>), grid, dim3(256), lds_reg, st, a); } while (0)
-  if (pass == 1) { if (l2) FL(1, 1); else FL(1, 0); }
-  else if (pass == 2) {
-    if (l2) hipLaunchKernelGGL((k_flash_bwd<NK, BNC, BVT, BTY, BXB, 1>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((k_flash_bwd<NK, BNC, BVT, BTY, BXB, 0>), grid, dim3(256), 0, st, a);
-  }
-  else { if (l2) FL(3, 1); else FL(3, 0); }
+#define FL(P) do { \
+    if (dma) hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, DM>), grid, dim3(256), lds_dma, st, a); \
+    else hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, 0>), grid, dim3(256), lds_reg, st, a); } while (0)
+  if (pass == 1) FL(1);
+  else if (pass == 2) hipLaunchKernelGGL((k_flash_bwd<NK, BNC, BVT, BTY, BXB>), grid, dim3(256), 0, st, a);
+  else FL(3);
 #undef FL
   return hipGetLastError();
 }
@@ -918,8 +879,8 @@ static hipError_t prepare_sized() {
   constexpr size_t lds = FwdGeom<NK, TY, 1>::LDS_BYTES;
   if (lds <= 64 * 1024) return hipSuccess;
   hipError_t e = hipSuccess;
-#define PREP(P, L) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_flash<NK, NC, VT, TY, XB, P, L, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
-  PREP(1, 0); PREP(1, 1); PREP(3, 0); PREP(3, 1);
+#define PREP(P) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_flash<NK, NC, VT, TY, XB, P, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
+  PREP(1); PREP(3);
 #undef PREP
   return e;
 }
@@ -929,65 +890,59 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
                             hipStream_t st) {
   const MarDims& d = c->dm;
   const MarLayout& L = c->L;
-  FlashArgs a;
+  FlashArgs a = {};
   a.X = pass == 2 ? L.Km : L.Q;  a.Y = pass == 2 ? L.Q : L.Km;   // stationary / streamed matrix
   a.xx = L.qq; a.yy = L.kk;
-  a.ml = L.ml; a.pos = L.pos;
+  a.ml = L.ml; a.pos = L.pos; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
   a.T = L.T; a.R = L.R; a.tpitch = (d.N + 127) & ~127; a.trows = (d.S + 63) & ~63;
   a.out = pass == 1 ? L.gQ : L.G;
   a.rank_dst = rank_dst; a.rank_src = rank_src;
   a.n = b.n; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.cn = b.cn; a.nchunks = b.nchunks; a.dk = d.dk;
   const int max_nx = pass == 2 ? d.N : (b.n < d.S ? b.n : d.S);
-  const bool split = d.split && pass != 3;                 // evaluation always runs in fp32
-  const int sr = split ? mar_split_stripe_rows(d.dk, pass) : mar_flash_stripe_rows(d.dk, pass);
-  a.yimg = pass == 1 ? L.Kimg : L.Qimg;
-  a.yimg_tiles = ((pass == 1 ? d.N : d.S) + 31) / 32;
-  a.ximg = pass == 1 ? L.Qimg : L.Kimg;
-  a.ximg_tiles = ((pass == 1 ? d.S : d.N) + 31) / 32;
-  a.nstripes = (max_nx + sr - 1) / sr;
-  const int ncs = 2 * b.nchunks;
-  a.sy = pass == 1 ? d.sy1 : (pass == 2 ? d.sy2 : 1);
-  a.tps = pass == 1 ? d.tps1 : (pass == 2 ? d.tps2 : (1 << 30));
+  const bool f16 = !d.split_bf16 || pass == 3;             // evaluation always runs at fp32 precision
+  a.yimg = pass == 2 ? L.Qimg : L.Kimg; a.yexp = pass == 2 ? L.Qexp : L.Kexp; a.yimg_tiles = ((pass == 2 ? d.S : d.N) + 31) / 32;
+  a.ximg = pass == 2 ? L.Kimg : L.Qimg; a.xexp = pass == 2 ? L.Kexp : L.Qexp; a.ximg_tiles = ((pass == 2 ? d.N : d.S) + 31) / 32;
+  a.qrows = L.gQ; a.ynorm = L.Knorm; a.table = c->node_emb; a.neg_dst = b.neg_dst; a.neg_src = b.neg_src; a.dim = d.dim;
+  a.sr = mar_stripe_rows(d, pass);
+  a.nstripes = (max_nx + a.sr - 1) / a.sr;
+  a.units = a.whole_units = 2 * b.nchunks * a.nstripes;
+  a.sy = d.sy1; a.tps = d.tps1;
+  if (pass == 2) { a.sy = d.sy2; a.tps = d.tps2; }
+  if (pass == 3) mar_plan_parts(d, 3, a.units, d.N, &a.sy, &a.tps);
   a.sy_ml = d.sy1; a.roles = d.roles;
-  dim3 grid((unsigned)(8 * ((ncs + 7) / 8) * a.nstripes * a.sy));
-  a.whole_slots = 0x7fffffff; a.rem_cs0 = ncs; a.rem_k = 1; a.rem_tps = 0; a.rem_rows = 0; a.mlx = nullptr; a.outx = nullptr;
-  if (pass == 1 && d.rem_k > 1 && b.n == d.B) {            // full batch: split the stripes beyond the last whole round
-    a.whole_slots = d.rem_cs0 / 8 * a.nstripes;
-    a.rem_cs0 = d.rem_cs0; a.rem_k = d.rem_k; a.rem_tps = d.rem_tps; a.rem_rows = d.rem_rows;
-    a.mlx = L.mlx; a.outx = L.gQx;
-    const int rem_wgs = (ncs - d.rem_cs0) * a.nstripes * d.rem_k;
-    grid = dim3((unsigned)(8 * (a.whole_slots + (rem_wgs + 7) / 8)));
+  a.rem_k = 1; a.rem_tps = a.tps;
+  if (pass != 3 && b.n == d.B) {                           // full batch: split the stripes beyond the last whole round
+    const MarRem& r = pass == 1 ? d.rem1 : d.rem2;
+    if (r.k > 1) {
+      a.whole_units = r.whole_units; a.rem_k = r.k; a.rem_tps = r.tps; a.rem_rows = r.rows;
+      a.mlx = L.mlx; a.outx = pass == 1 ? L.gQx : L.Gx;
+    }
   }
-  if (split && pass == 2 && d.rem2_k > 1 && b.n == d.B) {   // full batch: split the stripes beyond the last whole round
-    a.whole_slots = d.rem2_cs0 / 8 * a.nstripes;
-    a.rem_cs0 = d.rem2_cs0; a.rem_k = d.rem2_k; a.rem_tps = d.rem2_tps; a.rem_rows = d.rem2_rows;
-    a.outx = L.Gx;
-    const int rem_wgs = (ncs - d.rem2_cs0) * a.nstripes * d.rem2_k;
-    grid = dim3((unsigned)(8 * (a.whole_slots + (rem_wgs + 7) / 8)));
-  }
-  if (split) return mar_split_launch(a, pass, grid, st);
-  const int l2 = c->cfg.model == MAR_MODEL_TRANSE;
+  a.wslots = (a.whole_units * a.sy + 7) / 8;
+  a.rslots = ((a.units - a.whole_units) * a.rem_k + 7) / 8;
+  const dim3 grid(8u * (unsigned)(a.wslots + a.rslots));
+  if (d.bilinear) return mar_split_launch(a, pass, f16, grid, st);
   const int nk = d.dk / 4;
 #ifndef MAR_BWD_TAIL_MFMA
 #define MAR_BWD_TAIL_MFMA 0
 #endif
   constexpr int BV = MAR_BWD_TAIL_MFMA ? 0 : 1;         // pass 2: last 4 columns on the vector ALU, or one more matrix block
-  if (nk <= 13) return launch_sized<13, 3, 1, 64, 1, 3 + (1 - BV), BV, MAR_BWD_XB, 64>(a, pass, l2, grid, st);
-  if (nk <= 25) return launch_sized<25, 6, 1, 64, 1, 6 + (1 - BV), BV, MAR_BWD_XB, 64>(a, pass, l2, grid, st);
-  if (nk <= 32) return launch_sized<32, 8, 0, 64, 1, 8, 0, MAR_BWD_XB, 64>(a, pass, l2, grid, st);
-  if (nk <= 64) return launch_sized<64, 16, 0, 32, 1, 16, 0, 1, 32>(a, pass, l2, grid, st);
-  return launch_sized<100, 25, 0, 32, 1, 25, 0, 1, MAR_BWD_WIDE_TY>(a, pass, l2, grid, st);
+  if (nk <= 13) return launch_sized<13, 3, 1, 64, 1, 3 + (1 - BV), BV, MAR_BWD_XB, 64>(a, pass, grid, st);
+  if (nk <= 25) return launch_sized<25, 6, 1, 64, 1, 6 + (1 - BV), BV, MAR_BWD_XB, 64>(a, pass, grid, st);
+  if (nk <= 32) return launch_sized<32, 8, 0, 64, 1, 8, 0, MAR_BWD_XB, 64>(a, pass, grid, st);
+  if (nk <= 64) return launch_sized<64, 16, 0, 32, 1, 16, 0, 1, 32>(a, pass, grid, st);
+  return launch_sized<100, 25, 0, 32, 1, 25, 0, 1, MAR_BWD_WIDE_TY>(a, pass, grid, st);
 }
 
 int mar_flash_wgs_per_cu(int dk, int pass) { return pass == 2 ? (dk / 4 <= 32 ? MAR_BWD_WAVES : 2) : (dk / 4 <= 64 ? 2 : 1); }
 
 hipError_t mar_launch_flash_merge(const mar_ctx* c, const MarBatch& b, hipStream_t st) {
   const MarDims& d = c->dm;
-  if (d.rem_k <= 1 || b.n != d.B) return hipSuccess;
+  if (d.rem1.k <= 1 || b.n != d.B) return hipSuccess;
   FlashArgs a = {};
-  a.ml = c->L.ml; a.mlx = c->L.mlx; a.out = c->L.gQ; a.outx = c->L.gQx;
-  a.n = b.n; a.B = d.B; a.S = d.S; a.dk = d.dk; a.trows = (d.S + 63) & ~63;
-  a.rem_cs0 = d.rem_cs0; a.rem_k = d.rem_k; a.rem_rows = d.rem_rows;
-  hipLaunchKernelGGL(k_flash_merge, dim3((unsigned)((d.rem_rows + 7) / 8)), dim3(256), 0, st, a);
+  a.ml = c->L.ml; a.mlx = c->L.mlx; a.out = c->L.gQ; a.outx = c->L.gQx; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
+  a.n = b.n; a.B = d.B; a.S = d.S; a.dk = d.dk; a.sr = mar_stripe_rows(d, 1); a.nstripes = (d.S + a.sr - 1) / a.sr;
+  a.whole_units = d.rem1.whole_units; a.rem_k = d.rem1.k; a.rem_rows = d.rem1.rows;
+  hipLaunchKernelGGL(k_flash_merge, dim3((unsigned)((d.rem1.rows + 7) / 8)), dim3(256), 0, st, a);
   return hipGetLastError();
 }

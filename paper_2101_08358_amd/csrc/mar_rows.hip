@@ -13,6 +13,7 @@ struct RowArgs {
   int32_t num_nodes;
   int32_t sy1, sy2;      // parts per stripe in the two contraction passes
   int32_t roles;         // 3, or 2 for the relation-free Dot score
+  float ml_log2;         // natural-log units of one unit of the softmax references (see FlashArgs)
 };
 
 template <int GL> __device__ __forceinline__ float group_sum(float v) {
@@ -22,260 +23,355 @@ template <int GL> __device__ __forceinline__ float group_sum(float v) {
 }
 
 // ---------------------------------------------------------------------- gather -----
-// Edge blocks: one lane group per PREP_EDGES edges builds the two edge-side operands of each
+// Edge blocks build the two edge-side operands of each edge
 //     side DST (negatives replace d): a_ej = <q, n_j>,  q = s*r (DistMult), s.r complex (ComplEx)
 //     side SRC (negatives replace s): b_ej = <q, m_j>,  q = r*d,            conj(r).d
 //   for TransE the scores are -|q - n_j| with q = s + r and q = d - r; also the positive score.
-// Negative blocks: one lane group per PREP_NEGS negatives copies their rows into the dense per-chunk matrix.
-// A group issues the loads of all its rows before the first use: the gathers are bound by the latency of
-// scattered row reads (address translation included), so bytes in flight per lane are what counts.
-// VEC: dim is a multiple of 4, rows are moved as float4 (float2 pairs for the two halves of a ComplEx row) and
-// a lane holds all its pieces of a row (NV per row); otherwise one element per lane and step.
-// MODEL: the score function, resolved at compile time.
-#ifndef PREP_EDGES
-#define PREP_EDGES 2
-#endif
-#ifndef PREP_NEGS
-#define PREP_NEGS 4
-#endif
+// Negative blocks bring the negatives' rows into the layout the contraction reads.
+// TransE: dense fp32 matrices, one row after the other.  Bilinear models: hi/lo images (mar_split.h); a workgroup takes
+// 16, 32 or 64 consecutive rows of one chunk (whole 16-row blocks, so a block's exponent is found through LDS), the
+// rows of the chunk's last tile beyond its own being written as zeros.
+// A lane group issues the loads of all its rows (E edges, P negatives) before the first use: the gathers are bound by
+// the latency of scattered row reads (address translation included), so bytes in flight per lane are what counts.
+// A lane holds NV float4s of a row.  VEC (dim is a multiple of 4): float4 v holds columns 4 (l + GL v) .. +3; for ComplEx
+// columns 2 (l + GL v), +1 of the real half and of the imaginary half (re, re, im, im).  Otherwise element c of float4 v
+// is column l + GL (4 v + c); for ComplEx columns l + GL 2v and l + GL (2v + 1) of either half (re, re, im, im).
+// MODEL: the score function, resolved at compile time.  BF16: the images hold bf16 parts without exponents.
+template <int GL, bool VEC, bool CPLX>
+__device__ __forceinline__ float4 load_cols(const float* __restrict__ row, int l, int v, int dim) {
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int h = dim >> 1;
+  if (VEC && CPLX) {
+    const int k = 2 * (l + GL * v);
+    if (k < h) {
+      const float2 re = *reinterpret_cast<const float2*>(row + k), im = *reinterpret_cast<const float2*>(row + h + k);
+      x = make_float4(re.x, re.y, im.x, im.y);
+    }
+  } else if (VEC) {
+    const int k = 4 * (l + GL * v);
+    if (k < dim) x = *reinterpret_cast<const float4*>(row + k);
+  } else if (CPLX) {
+    const int k0 = l + GL * (2 * v), k1 = k0 + GL;
+    if (k0 < h) { x.x = row[k0]; x.z = row[h + k0]; }
+    if (k1 < h) { x.y = row[k1]; x.w = row[h + k1]; }
+  } else {
+    const int k = l + GL * (4 * v);
+    if (k < dim) x.x = row[k];
+    if (k + GL < dim) x.y = row[k + GL];
+    if (k + 2 * GL < dim) x.z = row[k + 2 * GL];
+    if (k + 3 * GL < dim) x.w = row[k + 3 * GL];
+  }
+  return x;
+}
+// sum += x . y over a lane's float4, in the order of its columns
+template <bool VEC, bool CPLX> __device__ __forceinline__ void add_dot(float& sum, const float4& x, const float4& y) {
+  if (VEC && CPLX) sum += (x.x * y.x + x.z * y.z) + (x.y * y.y + x.w * y.w);
+  else if (VEC) sum += (x.x * y.x + x.y * y.y) + (x.z * y.z + x.w * y.w);
+  else if (CPLX) { sum += x.x * y.x + x.z * y.z; sum += x.y * y.y + x.w * y.w; }
+  else { sum += x.x * y.x; sum += x.y * y.y; sum += x.z * y.z; sum += x.w * y.w; }
+}
 
-template <int GL, int NV, bool VEC, int MODEL>
+// largest finite magnitude so far
+__device__ __forceinline__ float finite_max(float m, float v) { const float f = fabsf(v); return f <= 3.4028234663852886e38f ? fmaxf(m, f) : m; }
+__device__ __forceinline__ float finite_max4(float m, const float4& v) { return finite_max(finite_max(finite_max(finite_max(m, v.x), v.y), v.z), v.w); }
+__device__ __forceinline__ bool finite1(float v) { return fabsf(v) <= 3.4028234663852886e38f; }
+__device__ __forceinline__ bool finite4(const float4& v) { return finite1(v.x) && finite1(v.y) && finite1(v.z) && finite1(v.w); }
+
+template <int GL> __device__ __forceinline__ float group_max(float v) {
+#pragma unroll
+  for (int o = GL / 2; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+  return v;
+}
+
+// Calls f(column, value) for the elements, or f2 / f4 for aligned pairs / quadruples of columns, that a lane holds of a row.
+template <int GL, int NV, bool VEC, bool CPLX, class F1, class F2, class F4>
+__device__ __forceinline__ void each_col(const float4 (&v)[NV], int l, int dim, F1 f1, F2 f2, F4 f4) {
+  const int h = dim >> 1;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    if (VEC && CPLX) {
+      const int k = 2 * (l + GL * i);
+      if (k < h) { f2(k, make_float2(v[i].x, v[i].y)); f2(h + k, make_float2(v[i].z, v[i].w)); }
+    } else if (VEC) {
+      const int k = 4 * (l + GL * i);
+      if (k < dim) f4(k, v[i]);
+    } else if (CPLX) {
+      const int k0 = l + GL * (2 * i), k1 = k0 + GL;
+      if (k0 < h) { f1(k0, v[i].x); f1(h + k0, v[i].z); }
+      if (k1 < h) { f1(k1, v[i].y); f1(h + k1, v[i].w); }
+    } else {
+      const int k = l + GL * (4 * i);
+      if (k < dim) f1(k, v[i].x);
+      if (k + GL < dim) f1(k + GL, v[i].y);
+      if (k + 2 * GL < dim) f1(k + 2 * GL, v[i].z);
+      if (k + 3 * GL < dim) f1(k + 3 * GL, v[i].w);
+    }
+  }
+}
+
+// One image row from a lane group's registers: columns scaled and split, zeros from dim up to the images' width.
+template <int GL, int NV, bool VEC, bool CPLX, bool F16>
+__device__ __forceinline__ void store_image_row(const SplitImages& g, char* row, const float4 (&v)[NV], float scale, int l, int dim) {
+  if (VEC) {
+    for (int k = dim + 4 * l; k < g.dkp; k += 4 * GL) sp_store4<F16>(row, g.plane, k, make_float4(0.f, 0.f, 0.f, 0.f), 1.f);
+  } else {
+    for (int k = dim + l; k < g.dkp; k += GL) sp_store1<F16>(row, g.plane, k, 0.f, 1.f);
+  }
+  each_col<GL, NV, VEC, CPLX>(v, l, dim, [&](int k, float x) { sp_store1<F16>(row, g.plane, k, x, scale); },
+                              [&](int k, const float2& x) { sp_store2<F16>(row, g.plane, k, x, scale); },
+                              [&](int k, const float4& x) { sp_store4<F16>(row, g.plane, k, x, scale); });
+}
+
+// Dense fp32 row, zero-padded from dim to dk.
+template <int GL, int NV, bool VEC, bool CPLX>
+__device__ __forceinline__ void store_dense_row(float* row, const float4 (&v)[NV], int l, int dim, int dk) {
+  if (!VEC) { for (int k = dim + l; k < dk; k += GL) row[k] = 0.f; }
+  each_col<GL, NV, VEC, CPLX>(v, l, dim, [&](int k, float x) { row[k] = x; },
+                              [&](int k, const float2& x) { *reinterpret_cast<float2*>(row + k) = x; },
+                              [&](int k, const float4& x) { *reinterpret_cast<float4*>(row + k) = x; });
+}
+
+// Rows per lane group: edges, negatives.
+constexpr int prep_edges(int gl, bool img) { return img && gl == 64 ? 4 : 2; }
+constexpr int PREP_NEGS = 4;
+
+template <int GL, int NV, bool VEC, int MODEL, bool BF16>
 __global__ void __launch_bounds__(256)
-k_prep(RowArgs a, int nbB, float* __restrict__ Q, float* __restrict__ Km, float* __restrict__ qq,
-       float* __restrict__ kk, float* __restrict__ pos, float* __restrict__ pos_user, SplitImages qi, SplitImages ki) {
-  const int blk = blockIdx.x;
+k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* __restrict__ Km, float* __restrict__ qq,
+       float* __restrict__ kk, float* __restrict__ pos, float* __restrict__ pos_user, int32_t* __restrict__ rank_dst,
+       int32_t* __restrict__ rank_src, SplitImages qi, SplitImages ki) {
+  constexpr bool IMG = MODEL != MAR_MODEL_TRANSE, CPLX = MODEL == MAR_MODEL_COMPLEX, F16 = !BF16;
   constexpr int GPB = 256 / GL;                  // lane groups per block
+  constexpr int E = prep_edges(GL, IMG), P = PREP_NEGS;
+  constexpr int RE = GPB * E, RN = GPB * P;      // rows per workgroup
+  static_assert(!IMG || (RE % SP_EB == 0 && RN % SP_EB == 0 && SP_EB % E == 0 && SP_EB % P == 0), "whole 16-row blocks per workgroup");
+  constexpr int MB = (RN > RE ? RN : RE) / 16 + 1;
+  __shared__ int s_max[2][MB];                   // per 16-row block: bits of the largest finite magnitude (two operands of an edge block)
+  __shared__ int s_bad[2][MB];                   // the block holds an infinity or a NaN, or (evaluation) a row far below its largest
+  __shared__ int s_n2[MB];                       // evaluation: bits of the largest squared row norm of a block of negatives
+  const bool eval = rank_dst != nullptr;         // uniform
+  if (IMG && F16) {
+    if (threadIdx.x < 2 * MB) { (&s_max[0][0])[threadIdx.x] = 0; (&s_bad[0][0])[threadIdx.x] = 0; }
+    if (threadIdx.x < MB) s_n2[threadIdx.x] = 0;
+    __syncthreads();
+  }
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int dim = a.dim, dk = a.dk;
-  if (blk < nbB) {
-    const int e0 = (blk * GPB + grp) * PREP_EDGES;
-    if (e0 >= a.n) return;
-    const float *s_row[PREP_EDGES], *r_row[PREP_EDGES], *d_row[PREP_EDGES];
+  // exponent of the 16-row block of workgroup row `rw` (two operands: which), after all groups have put in their maxima
+  auto put_max = [&](int which, int rw, float mx, bool bad) {
+    mx = group_max<GL>(mx);
+    if (l == 0) atomicMax(&s_max[which][rw / SP_EB], __float_as_int(mx));
+    if (bad) s_bad[which][rw / SP_EB] = 1;
+  };
+  // Evaluation, between the maxima and the exponents: a row whose largest value is below 2^-14 of its block's keeps
+  // fewer bits than a comparison of its scores needs; its block is settled the long way (see k_split).
+  auto flag_small = [&](int which, int rw, float row_max) {
+    row_max = group_max<GL>(row_max);
+    if (l == 0 && row_max > 0.f && row_max < 0x1p-14f * __int_as_float(s_max[which][rw / SP_EB])) s_bad[which][rw / SP_EB] = 1;
+  };
+  if ((int)blockIdx.x < nbB) {
+    const int chunk = IMG ? blockIdx.x / wpc_e : 0;
+    const int r0 = (IMG ? blockIdx.x % wpc_e : blockIdx.x) * RE + grp * E;         // first row of the group in its chunk
+    const int nr = IMG ? min(a.S, a.n - chunk * a.S) : a.n;                         // edges of the chunk
+    if (IMG) { if (r0 - grp * E >= ((nr + SP_TY - 1) & ~(SP_TY - 1))) return; }     // uniform over the workgroup
+    else if (r0 >= nr) return;
+    const size_t eb = IMG ? (size_t)chunk * a.S : 0;
+    const float *s_row[E], *r_row[E], *d_row[E];
 #pragma unroll
-    for (int j = 0; j < PREP_EDGES; ++j) {
-      const int e = min(e0 + j, a.n - 1);                        // a group's surplus edge repeats the last one (not stored)
+    for (int j = 0; j < E; ++j) {
+      const size_t e = eb + min(r0 + j, nr - 1);                                    // surplus rows repeat the last edge (not stored)
       s_row[j] = a.node_emb + (size_t)a.src[e] * dim;
       r_row[j] = a.rel_emb + (size_t)(MODEL == MAR_MODEL_DOT ? 0 : a.rel[e]) * dim;     // unused by Dot
       d_row[j] = a.node_emb + (size_t)a.dst[e] * dim;
     }
-    float acc[PREP_EDGES], nd[PREP_EDGES], ns[PREP_EDGES];
+    float acc[E], nd[E], ns[E];
+    float4 u[E][NV], w[E][NV], s[E][NV], r[E][NV], d[E][NV];
 #pragma unroll
-    for (int j = 0; j < PREP_EDGES; ++j) acc[j] = nd[j] = ns[j] = 0.f;
-    if (VEC && MODEL == MAR_MODEL_COMPLEX) {
-      const int h = dim >> 1;
-      float2 sr[PREP_EDGES][NV], si[PREP_EDGES][NV], rr[PREP_EDGES][NV], ri[PREP_EDGES][NV], dr[PREP_EDGES][NV], di[PREP_EDGES][NV];
+    for (int j = 0; j < E; ++j) {
+      acc[j] = nd[j] = ns[j] = 0.f;
 #pragma unroll
-      for (int j = 0; j < PREP_EDGES; ++j) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int k = 2 * (l + GL * v);
-          if (k < h) {
-            sr[j][v] = *reinterpret_cast<const float2*>(s_row[j] + k); si[j][v] = *reinterpret_cast<const float2*>(s_row[j] + h + k);
-            rr[j][v] = *reinterpret_cast<const float2*>(r_row[j] + k); ri[j][v] = *reinterpret_cast<const float2*>(r_row[j] + h + k);
-            dr[j][v] = *reinterpret_cast<const float2*>(d_row[j] + k); di[j][v] = *reinterpret_cast<const float2*>(d_row[j] + h + k);
-          }
-        }
+      for (int v = 0; v < NV; ++v) {
+        s[j][v] = load_cols<GL, VEC, CPLX>(s_row[j], l, v, dim);
+        d[j][v] = load_cols<GL, VEC, CPLX>(d_row[j], l, v, dim);
+        r[j][v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : load_cols<GL, VEC, CPLX>(r_row[j], l, v, dim);
       }
+    }
+    float mxu = 0.f, mxw = 0.f;
+    bool badu = false, badw = false;
 #pragma unroll
-      for (int j = 0; j < PREP_EDGES; ++j) {
-        if (e0 + j < a.n) {
-          float* qd = Q + ((size_t)MAR_SIDE_DST * a.B + e0 + j) * dk;
-          float* qs = Q + ((size_t)MAR_SIDE_SRC * a.B + e0 + j) * dk;
-          char* id_ = nullptr; char* is_ = nullptr;          // split precision: the rows' places in the images
-          if (qi.base) {
-            const int ch = (e0 + j) / a.S, er = (e0 + j) % a.S;
-            id_ = sp_row(qi, 2 * ch + MAR_SIDE_DST, er); is_ = sp_row(qi, 2 * ch + MAR_SIDE_SRC, er);
-            for (int k = dim + 4 * l; k < qi.dkp; k += 4 * GL) {        // zero columns up to the images' width
-              sp_store4(id_, qi.plane, k, make_float4(0.f, 0.f, 0.f, 0.f)); sp_store4(is_, qi.plane, k, make_float4(0.f, 0.f, 0.f, 0.f));
-            }
-          }
+    for (int j = 0; j < E; ++j) {
 #pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            const int k = 2 * (l + GL * v);
-            if (k < h) {
-              const float2 ure = make_float2(sr[j][v].x * rr[j][v].x - si[j][v].x * ri[j][v].x, sr[j][v].y * rr[j][v].y - si[j][v].y * ri[j][v].y);
-              const float2 uim = make_float2(sr[j][v].x * ri[j][v].x + si[j][v].x * rr[j][v].x, sr[j][v].y * ri[j][v].y + si[j][v].y * rr[j][v].y);
-              const float2 wre = make_float2(rr[j][v].x * dr[j][v].x + ri[j][v].x * di[j][v].x, rr[j][v].y * dr[j][v].y + ri[j][v].y * di[j][v].y);
-              const float2 wim = make_float2(rr[j][v].x * di[j][v].x - ri[j][v].x * dr[j][v].x, rr[j][v].y * di[j][v].y - ri[j][v].y * dr[j][v].y);
-              acc[j] += (ure.x * dr[j][v].x + uim.x * di[j][v].x) + (ure.y * dr[j][v].y + uim.y * di[j][v].y);
-              if (qi.base) {
-                sp_store2(id_, qi.plane, k, ure); sp_store2(id_, qi.plane, h + k, uim);
-                sp_store2(is_, qi.plane, k, wre); sp_store2(is_, qi.plane, h + k, wim);
-              } else {
-                *reinterpret_cast<float2*>(qd + k) = ure; *reinterpret_cast<float2*>(qd + h + k) = uim;
-                *reinterpret_cast<float2*>(qs + k) = wre; *reinterpret_cast<float2*>(qs + h + k) = wim;
-              }
-            }
-          }
-        }
-      }
-    } else if (VEC) {
-      float4 s4[PREP_EDGES][NV], r4[PREP_EDGES][NV], d4[PREP_EDGES][NV];
-#pragma unroll
-      for (int j = 0; j < PREP_EDGES; ++j) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int k = 4 * (l + GL * v);
-          if (k < dim) {
-            s4[j][v] = *reinterpret_cast<const float4*>(s_row[j] + k); d4[j][v] = *reinterpret_cast<const float4*>(d_row[j] + k);
-            r4[j][v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(r_row[j] + k);
-          }
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < PREP_EDGES; ++j) {
-        if (e0 + j < a.n) {
-          float* qd = Q + ((size_t)MAR_SIDE_DST * a.B + e0 + j) * dk;
-          float* qs = Q + ((size_t)MAR_SIDE_SRC * a.B + e0 + j) * dk;
-          char* id_ = nullptr; char* is_ = nullptr;
-          if (qi.base) {
-            const int ch = (e0 + j) / a.S, er = (e0 + j) % a.S;
-            id_ = sp_row(qi, 2 * ch + MAR_SIDE_DST, er); is_ = sp_row(qi, 2 * ch + MAR_SIDE_SRC, er);
-            for (int k = dim + 4 * l; k < qi.dkp; k += 4 * GL) {
-              sp_store4(id_, qi.plane, k, make_float4(0.f, 0.f, 0.f, 0.f)); sp_store4(is_, qi.plane, k, make_float4(0.f, 0.f, 0.f, 0.f));
-            }
-          }
-#pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            const int k = 4 * (l + GL * v);
-            if (k < dim) {
-              const float4 s = s4[j][v], r = r4[j][v], d = d4[j][v];
-              float4 u, w;
-              if (MODEL == MAR_MODEL_DISTMULT) {
-                u = make_float4(s.x * r.x, s.y * r.y, s.z * r.z, s.w * r.w);
-                w = make_float4(r.x * d.x, r.y * d.y, r.z * d.z, r.w * d.w);
-                acc[j] += (u.x * d.x + u.y * d.y) + (u.z * d.z + u.w * d.w);
-              } else if (MODEL == MAR_MODEL_DOT) {
-                u = s; w = d;
-                acc[j] += (s.x * d.x + s.y * d.y) + (s.z * d.z + s.w * d.w);
-              } else {
-                u = make_float4(s.x + r.x, s.y + r.y, s.z + r.z, s.w + r.w);
-                w = make_float4(d.x - r.x, d.y - r.y, d.z - r.z, d.w - r.w);
-                const float4 df = make_float4(u.x - d.x, u.y - d.y, u.z - d.z, u.w - d.w);
-                acc[j] += (df.x * df.x + df.y * df.y) + (df.z * df.z + df.w * df.w);
-                nd[j] += (u.x * u.x + u.y * u.y) + (u.z * u.z + u.w * u.w);
-                ns[j] += (w.x * w.x + w.y * w.y) + (w.z * w.z + w.w * w.w);
-              }
-              if (qi.base) { sp_store4(id_, qi.plane, k, u); sp_store4(is_, qi.plane, k, w); }
-              else { *reinterpret_cast<float4*>(qd + k) = u; *reinterpret_cast<float4*>(qs + k) = w; }
-            }
-          }
-        }
-      }
-    } else {
-      for (int j = 0; j < PREP_EDGES; ++j) {
-        if (e0 + j >= a.n) break;
-        float* qd = Q + ((size_t)MAR_SIDE_DST * a.B + e0 + j) * dk;
-        float* qs = Q + ((size_t)MAR_SIDE_SRC * a.B + e0 + j) * dk;
-        char* id_ = nullptr; char* is_ = nullptr;
-        if (qi.base) {
-          const int ch = (e0 + j) / a.S, er = (e0 + j) % a.S;
-          id_ = sp_row(qi, 2 * ch + MAR_SIDE_DST, er); is_ = sp_row(qi, 2 * ch + MAR_SIDE_SRC, er);
-          for (int k = dim + l; k < qi.dkp; k += GL) { sp_store1(id_, qi.plane, k, 0.f); sp_store1(is_, qi.plane, k, 0.f); }
-        }
-        if (MODEL == MAR_MODEL_COMPLEX) {
-          const int h = dim >> 1;
-          for (int k = l; k < h; k += GL) {
-            const float sr = s_row[j][k], si = s_row[j][h + k], rr = r_row[j][k], ri = r_row[j][h + k], dr = d_row[j][k], di = d_row[j][h + k];
-            const float ure = sr * rr - si * ri, uim = sr * ri + si * rr;
-            const float wre = rr * dr + ri * di, wim = rr * di - ri * dr;
-            acc[j] += ure * dr + uim * di;
-            if (qi.base) {
-              sp_store1(id_, qi.plane, k, ure); sp_store1(id_, qi.plane, h + k, uim);
-              sp_store1(is_, qi.plane, k, wre); sp_store1(is_, qi.plane, h + k, wim);
-            } else { qd[k] = ure; qd[h + k] = uim; qs[k] = wre; qs[h + k] = wim; }
-          }
+      for (int v = 0; v < NV; ++v) {
+        const float4 S = s[j][v], R = r[j][v], D = d[j][v];
+        float4 U, W;
+        if (CPLX) {                                         // (re, re, im, im)
+          U = make_float4(S.x * R.x - S.z * R.z, S.y * R.y - S.w * R.w, S.x * R.z + S.z * R.x, S.y * R.w + S.w * R.y);
+          W = make_float4(R.x * D.x + R.z * D.z, R.y * D.y + R.w * D.w, R.x * D.z - R.z * D.x, R.y * D.w - R.w * D.y);
+          add_dot<VEC, true>(acc[j], U, D);
+        } else if (MODEL == MAR_MODEL_DISTMULT) {
+          U = make_float4(S.x * R.x, S.y * R.y, S.z * R.z, S.w * R.w);
+          W = make_float4(R.x * D.x, R.y * D.y, R.z * D.z, R.w * D.w);
+          add_dot<VEC, false>(acc[j], U, D);
+        } else if (MODEL == MAR_MODEL_DOT) {
+          U = S; W = D;
+          add_dot<VEC, false>(acc[j], S, D);
         } else {
-          for (int k = l; k < dim; k += GL) {
-            const float s = s_row[j][k], r = MODEL == MAR_MODEL_DOT ? 0.f : r_row[j][k], d = d_row[j][k];
-            float u, w;
-            if (MODEL == MAR_MODEL_DISTMULT) { u = s * r; w = r * d; acc[j] += u * d; }
-            else if (MODEL == MAR_MODEL_DOT) { u = s; w = d; acc[j] += s * d; }
-            else { u = s + r; w = d - r; const float df = u - d; acc[j] += df * df; nd[j] += u * u; ns[j] += w * w; }
-            if (qi.base) { sp_store1(id_, qi.plane, k, u); sp_store1(is_, qi.plane, k, w); }
-            else { qd[k] = u; qs[k] = w; }
-          }
+          U = make_float4(S.x + R.x, S.y + R.y, S.z + R.z, S.w + R.w);
+          W = make_float4(D.x - R.x, D.y - R.y, D.z - R.z, D.w - R.w);
+          const float4 df = make_float4(U.x - D.x, U.y - D.y, U.z - D.z, U.w - D.w);
+          add_dot<VEC, false>(acc[j], df, df);
+          add_dot<VEC, false>(nd[j], U, U);
+          add_dot<VEC, false>(ns[j], W, W);
         }
-        if (!qi.base) { for (int k = dim + l; k < dk; k += GL) { qd[k] = 0.f; qs[k] = 0.f; } }
+        u[j][v] = U; w[j][v] = W;
+        if (IMG && F16 && r0 + j < nr) {
+          mxu = finite_max4(mxu, U); mxw = finite_max4(mxw, W);
+          badu |= !finite4(U); badw |= !finite4(W);
+        }
+      }
+    }
+    if (IMG && F16) {
+      put_max(MAR_SIDE_DST, grp * E, mxu, badu);
+      put_max(MAR_SIDE_SRC, grp * E, mxw, badw);
+      __syncthreads();
+      if (eval) {
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          float mu = 0.f, mw = 0.f;
+#pragma unroll
+          for (int v = 0; v < NV; ++v) { mu = finite_max4(mu, u[j][v]); mw = finite_max4(mw, w[j][v]); }
+          if (r0 + j < nr) { flag_small(MAR_SIDE_DST, grp * E, mu); flag_small(MAR_SIDE_SRC, grp * E, mw); }
+        }
+        __syncthreads();
+      }
+    }
+    float scu = 1.f, scw = 1.f;
+    if (IMG && F16) {
+      const int eu = sp_exponent(s_max[MAR_SIDE_DST][grp * E / SP_EB]), ew = sp_exponent(s_max[MAR_SIDE_SRC][grp * E / SP_EB]);
+      scu = ldexpf(1.f, eu); scw = ldexpf(1.f, ew);
+      if (l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < qi.tiles) {
+        qi.exps[((size_t)(2 * chunk + MAR_SIDE_DST) * qi.tiles) * 2 + r0 / SP_EB] = (float)eu + (s_bad[MAR_SIDE_DST][grp * E / SP_EB] ? SP_NONFINITE : 0.f);
+        qi.exps[((size_t)(2 * chunk + MAR_SIDE_SRC) * qi.tiles) * 2 + r0 / SP_EB] = (float)ew + (s_bad[MAR_SIDE_SRC][grp * E / SP_EB] ? SP_NONFINITE : 0.f);
       }
     }
 #pragma unroll
-    for (int j = 0; j < PREP_EDGES; ++j) {
-      const int e = e0 + j;
+    for (int j = 0; j < E; ++j) {
+      const int row = r0 + j;
+      const size_t e = eb + row;
+      const bool valid = row < nr;
+      if (IMG) {
+        if (row / SP_TY < qi.tiles) {
+          if (!valid) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) u[j][v] = w[j][v] = make_float4(0.f, 0.f, 0.f, 0.f);
+          }
+          store_image_row<GL, NV, VEC, CPLX, F16>(qi, sp_row(qi, 2 * chunk + MAR_SIDE_DST, row), u[j], scu, l, dim);
+          store_image_row<GL, NV, VEC, CPLX, F16>(qi, sp_row(qi, 2 * chunk + MAR_SIDE_SRC, row), w[j], scw, l, dim);
+        }
+      }
+      if (valid && (!IMG || Q)) {                            // TransE; evaluation of the bilinear models
+        store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_DST * a.B + e) * dk, u[j], l, dim, dk);
+        store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_SRC * a.B + e) * dk, w[j], l, dim, dk);
+      }
       float sc = group_sum<GL>(acc[j]);
       if (MODEL == MAR_MODEL_TRANSE) {
         const float sd = group_sum<GL>(nd[j]), ss = group_sum<GL>(ns[j]);
         sc = -sqrtf(sc);
-        if (l == 0 && e < a.n) { qq[(size_t)MAR_SIDE_DST * a.B + e] = sd; qq[(size_t)MAR_SIDE_SRC * a.B + e] = ss; }
+        if (l == 0 && valid) { qq[(size_t)MAR_SIDE_DST * a.B + e] = sd; qq[(size_t)MAR_SIDE_SRC * a.B + e] = ss; }
       }
-      if (l == 0 && e < a.n) { pos[e] = sc; if (pos_user) pos_user[e] = sc; }
+      if (l == 0 && valid) {
+        pos[e] = sc;
+        if (pos_user) pos_user[e] = sc;
+        if (rank_dst) { rank_dst[e] = 1; rank_src[e] = 1; }
+      }
     }
     return;
   }
   {
-    const int rr0 = ((blk - nbB) * GPB + grp) * PREP_NEGS;       // first row among the 2*cn negatives
-    if (rr0 >= 2 * a.cn) return;
-    const float* row[PREP_NEGS];
-    size_t krow[PREP_NEGS];
-    char* irow[PREP_NEGS];                                       // split precision: the rows' places in the images
+    const int blk = (int)blockIdx.x - nbB;
+    const int cs = IMG ? blk / wpc_n : 0;                        // 2 * chunk + side
+    const int r0 = (IMG ? blk % wpc_n : blk) * RN + grp * P;     // first row: in its chunk-side, or among the 2*cn negatives
+    const int nr = IMG ? a.N : 2 * a.cn;
+    if (IMG) { if (r0 - grp * P >= ((nr + SP_TY - 1) & ~(SP_TY - 1))) return; }     // uniform over the workgroup
+    else if (r0 >= nr) return;
+    float4 x[P][NV];
+    size_t krow[P];
 #pragma unroll
-    for (int j = 0; j < PREP_NEGS; ++j) {
-      const int rr = min(rr0 + j, 2 * a.cn - 1);
-      const int side = rr >= a.cn ? MAR_SIDE_DST : MAR_SIDE_SRC;
-      const int cj = rr - (side == MAR_SIDE_DST ? a.cn : 0);    // chunk*N + j
+    for (int j = 0; j < P; ++j) {
+      const int rr = min(r0 + j, nr - 1);
+      const int side = IMG ? cs & 1 : (rr >= a.cn ? MAR_SIDE_DST : MAR_SIDE_SRC);
+      const size_t cj = IMG ? (size_t)(cs >> 1) * a.N + rr : (size_t)(rr - (side == MAR_SIDE_DST ? a.cn : 0));    // chunk*N + j
       const int32_t id = side == MAR_SIDE_DST ? a.neg_dst[cj] : a.neg_src[cj];
-      row[j] = a.node_emb + (size_t)id * dim;
+      const float* row = a.node_emb + (size_t)id * dim;
       krow[j] = (size_t)side * a.C * a.N + cj;
-      irow[j] = ki.base ? sp_row(ki, 2 * (cj / a.N) + side, cj % a.N) : nullptr;
-    }
-    if (VEC) {
-      float4 v4[PREP_NEGS][NV];
 #pragma unroll
-      for (int j = 0; j < PREP_NEGS; ++j) {
+      for (int v = 0; v < NV; ++v) {
+        x[j][v] = load_cols<GL, VEC, false>(row, l, v, dim);
+      }
+    }
+    float scale = 1.f;
+    if (IMG && F16) {
+      float mx = 0.f;
+      bool bad = false;
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-          const int k = 4 * (l + GL * v);
-          if (k < dim) v4[j][v] = *reinterpret_cast<const float4*>(row[j] + k);
+          if (r0 + j < nr) { mx = finite_max4(mx, x[j][v]); bad |= !finite4(x[j][v]); }
         }
       }
+      put_max(0, grp * P, mx, bad);
+      if (eval) {
 #pragma unroll
-      for (int j = 0; j < PREP_NEGS; ++j) {
-        float nn = 0.f;
-        if (rr0 + j < 2 * a.cn) {
-          if (ki.base) {
-            for (int k = dim + 4 * l; k < ki.dkp; k += 4 * GL) sp_store4(irow[j], ki.plane, k, make_float4(0.f, 0.f, 0.f, 0.f));
-          }
+        for (int j = 0; j < P; ++j) {
+          float n2 = 0.f;
 #pragma unroll
-          for (int v = 0; v < NV; ++v) {
-            const int k = 4 * (l + GL * v);
-            if (k < dim) {
-              const float4 x = v4[j][v];
-              nn += (x.x * x.x + x.y * x.y) + (x.z * x.z + x.w * x.w);
-              if (ki.base) sp_store4(irow[j], ki.plane, k, x);
-              else *reinterpret_cast<float4*>(Km + krow[j] * dk + k) = x;
-            }
-          }
-        }
-        if (MODEL == MAR_MODEL_TRANSE) {
-          nn = group_sum<GL>(nn);
-          if (l == 0 && rr0 + j < 2 * a.cn) kk[krow[j]] = nn;
+          for (int v = 0; v < NV; ++v) add_dot<VEC, false>(n2, x[j][v], x[j][v]);
+          n2 = group_sum<GL>(n2);
+          if (l == 0 && r0 + j < nr) atomicMax(&s_n2[grp * P / SP_EB], __float_as_int(fabsf(n2)));
         }
       }
-    } else {
-      for (int j = 0; j < PREP_NEGS; ++j) {
-        float nn = 0.f;
-        if (rr0 + j < 2 * a.cn) {
-          for (int k = l; k < (ki.base ? ki.dkp : dk); k += GL) {
-            const float x = k < dim ? row[j][k] : 0.f;
-            nn += x * x;
-            if (ki.base) sp_store1(irow[j], ki.plane, k, x);
-            else Km[krow[j] * dk + k] = x;
+      __syncthreads();
+      if (eval) {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+          float m = 0.f;
+#pragma unroll
+          for (int v = 0; v < NV; ++v) m = finite_max4(m, x[j][v]);
+          if (r0 + j < nr) flag_small(0, grp * P, m);
+        }
+        __syncthreads();
+      }
+      const int e = sp_exponent(s_max[0][grp * P / SP_EB]);
+      scale = ldexpf(1.f, e);
+      if (l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles)
+        ki.exps[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = (float)e + (s_bad[0][grp * P / SP_EB] ? SP_NONFINITE : 0.f);
+      if (eval && l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles) {
+        // bound of the scaled rows' norms: from the largest norm, or where its square leaves the range, from the scale
+        const float n2 = __int_as_float(s_n2[grp * P / SP_EB]), most = sqrtf((float)dk) * 0x1p15f;
+        ki.norms[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = n2 > 1e-25f && n2 < 1e37f ? fminf(most, 1.001f * sqrtf(n2) * scale) : most;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      const bool valid = r0 + j < nr;
+      if (IMG) {
+        if ((r0 + j) / SP_TY < ki.tiles) {
+          if (!valid) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) x[j][v] = make_float4(0.f, 0.f, 0.f, 0.f);
           }
+          store_image_row<GL, NV, VEC, false, F16>(ki, sp_row(ki, cs, r0 + j), x[j], scale, l, dim);
         }
-        if (MODEL == MAR_MODEL_TRANSE) {
-          nn = group_sum<GL>(nn);
-          if (l == 0 && rr0 + j < 2 * a.cn) kk[krow[j]] = nn;
-        }
+      } else if (valid) {
+        store_dense_row<GL, NV, VEC, false>(Km + krow[j] * dk, x[j], l, dim, dk);
+      }
+      if (MODEL == MAR_MODEL_TRANSE) {
+        float nn = 0.f;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) add_dot<VEC, false>(nn, x[j][v], x[j][v]);
+        nn = group_sum<GL>(nn);
+        if (l == 0 && valid) kk[krow[j]] = nn;
       }
     }
   }
@@ -290,7 +386,7 @@ k_prep(RowArgs a, int nbB, float* __restrict__ Q, float* __restrict__ Km, float*
 // O_p = sum_j exp(a_j - m_p) n_j.  merge_parts turns them into the log-sum-exp and one factor per part,
 // fac_p = exp(m_p - m) / l with m = max m_p and l = sum_p l_p exp(m_p - m), so that gq = sum_p fac_p O_p.
 
-__device__ __forceinline__ float merge_parts(const float* __restrict__ ml, size_t row, size_t part_rows, int sy1,
+__device__ __forceinline__ float merge_parts(const float* __restrict__ ml, size_t row, size_t part_rows, int sy1, float ml_log2,
                                              float (&fac)[MAR_MAX_PARTS]) {
   const float2* __restrict__ p2 = reinterpret_cast<const float2*>(ml) + row;
   float2 v[MAR_MAX_PARTS];
@@ -301,11 +397,11 @@ __device__ __forceinline__ float merge_parts(const float* __restrict__ ml, size_
   for (int p = 1; p < MAR_MAX_PARTS; ++p) mx = fmaxf(mx, v[p].x);
   float ls = 0.f;
 #pragma unroll
-  for (int p = 0; p < MAR_MAX_PARTS; ++p) { fac[p] = __expf(v[p].x - mx); ls += fac[p] * v[p].y; }
+  for (int p = 0; p < MAR_MAX_PARTS; ++p) { fac[p] = __expf((v[p].x - mx) * ml_log2); ls += fac[p] * v[p].y; }
   const float il = 1.f / ls;
 #pragma unroll
   for (int p = 0; p < MAR_MAX_PARTS; ++p) fac[p] *= il;
-  return mx + logf(ls);
+  return mx * ml_log2 + logf(ls);
 }
 
 // Chain rule of one element: from s, r, d, the merged operand gradients u (DST side) and w (SRC side).
@@ -353,8 +449,8 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
     // every lane of the group merges the parts of both sides (same addresses: one broadcast load each)
     float facu[MAR_MAX_PARTS], facw[MAR_MAX_PARTS];
     const size_t row_u = (size_t)MAR_SIDE_DST * a.B + e, row_w = (size_t)MAR_SIDE_SRC * a.B + e;
-    const float lse_u = merge_parts(ml, row_u, part_rows, sy1, facu);
-    const float lse_w = merge_parts(ml, row_w, part_rows, sy1, facw);
+    const float lse_u = merge_parts(ml, row_u, part_rows, sy1, a.ml_log2, facu);
+    const float lse_w = merge_parts(ml, row_w, part_rows, sy1, a.ml_log2, facw);
     const float pe = pos[e];
     if (l == 0) { lse[row_u] = lse_u; lse[row_w] = lse_w; }
     le = -2.f * pe + lse_u + lse_w;
@@ -984,32 +1080,42 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
   a.src = b.src; a.rel = b.rel; a.dst = b.dst; a.neg_src = b.neg_src; a.neg_dst = b.neg_dst;
   a.n = b.n; a.cn = b.cn; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.dim = d.dim; a.dk = d.dk; a.model = c->cfg.model;
   a.n_occ = b.n_occ; a.num_nodes = (int32_t)d.num_nodes;
-  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles;
+  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
   return a;
 }
 
-hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int images, hipStream_t st) {
+template <int GL, int NV, int MODEL, bool BF16>
+static void launch_prep(const RowArgs& a, const MarLayout& L, float* pos_out, int32_t* rank_dst, int32_t* rank_src, const SplitImages& qi,
+                        const SplitImages& ki, hipStream_t st) {
+  constexpr bool img = MODEL != MAR_MODEL_TRANSE;
+  constexpr int gpb = 256 / GL, re = gpb * prep_edges(GL, img), rn = gpb * PREP_NEGS;
+  const int wpc_e = (qi.tiles * SP_TY + re - 1) / re, wpc_n = (ki.tiles * SP_TY + rn - 1) / rn;
+  const int nchunks = a.cn / a.N;
+  const int nbB = img ? nchunks * wpc_e : (a.n + re - 1) / re;
+  const int nbC = img ? 2 * nchunks * wpc_n : (2 * a.cn + rn - 1) / rn;
+  const dim3 grid(nbB + nbC), blk(256);
+  float* q = img ? (rank_dst ? L.gQ : nullptr) : L.Q;        // evaluation keeps the fp32 operands for close comparisons
+  if (a.dim % 4 == 0) hipLaunchKernelGGL((k_prep<GL, NV, true, MODEL, BF16>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, L.Km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
+  else hipLaunchKernelGGL((k_prep<GL, NV, false, MODEL, BF16>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, L.Km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
+}
+
+hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
+                           hipStream_t st) {
   const MarLayout& L = c->L;
   RowArgs a = row_args(c, b);
-  const SplitImages qi = sp_images(images ? L.Qimg : nullptr, a.dk, c->dm.S), ki = sp_images(images ? L.Kimg : nullptr, a.dk, c->dm.N);
-  const int GL = mar_lane_group(a.dk), gpb = 256 / GL;
-  const int nbB = (b.n + gpb * PREP_EDGES - 1) / (gpb * PREP_EDGES);
-  const int nbC = (2 * b.cn + gpb * PREP_NEGS - 1) / (gpb * PREP_NEGS);
-  const dim3 grid(nbB + nbC), blk(256);
-#define PREP3(GLV, NVV, V, M) hipLaunchKernelGGL((k_prep<GLV, NVV, V, M>), grid, blk, 0, st, a, nbB, L.Q, L.Km, L.qq, L.kk, L.pos, pos_out, qi, ki)
-#define PREP(GLV, NVV, V) do { switch (a.model) { \
-    case MAR_MODEL_DISTMULT: PREP3(GLV, NVV, V, MAR_MODEL_DISTMULT); break; \
-    case MAR_MODEL_COMPLEX: PREP3(GLV, NVV, V, MAR_MODEL_COMPLEX); break; \
-    case MAR_MODEL_TRANSE: PREP3(GLV, NVV, V, MAR_MODEL_TRANSE); break; \
-    default: PREP3(GLV, NVV, V, MAR_MODEL_DOT); break; } } while (0)
+  const SplitImages qi = sp_images(L.Qimg, L.Qexp, nullptr, a.dk, c->dm.S), ki = sp_images(L.Kimg, L.Kexp, L.Knorm, a.dk, c->dm.N);
+  const int GL = mar_lane_group(a.dk);
+#define PREP(GLV, NVV) do { switch (a.model) { \
+    case MAR_MODEL_DISTMULT: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_DISTMULT, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+                             else launch_prep<GLV, NVV, MAR_MODEL_DISTMULT, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
+    case MAR_MODEL_COMPLEX: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_COMPLEX, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+                            else launch_prep<GLV, NVV, MAR_MODEL_COMPLEX, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
+    case MAR_MODEL_TRANSE: launch_prep<GLV, NVV, MAR_MODEL_TRANSE, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
+    default: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_DOT, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+             else launch_prep<GLV, NVV, MAR_MODEL_DOT, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; } } while (0)
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
-  if (a.dim % 4 == 0) {
-    if (GL == 16) PREP(16, 1, true); else if (GL == 32) PREP(32, 1, true); else if (a.dk <= 256) PREP(64, 1, true); else PREP(64, 2, true);
-  } else {
-    if (GL == 16) PREP(16, 1, false); else if (GL == 32) PREP(32, 1, false); else PREP(64, 1, false);
-  }
+  if (GL == 16) PREP(16, 1); else if (GL == 32) PREP(32, 1); else if (a.dk <= 256) PREP(64, 1); else PREP(64, 2);
 #undef PREP
-#undef PREP3
   return hipGetLastError();
 }
 

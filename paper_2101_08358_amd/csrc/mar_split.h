@@ -1,16 +1,21 @@
-// Operand images of the split-precision contraction passes (gfx950): geometry and the stores that build them.
+// Operand images of the contraction passes that split their operands (gfx950): geometry and the stores that build them.
 //
-// A matrix whose rows a pass streams (the chunk's negatives, the chunk's edge-side operands) is kept as "images":
-// per chunk-side and tile of 32 rows a plane of the rows' bf16 hi parts and a plane of their lo parts
-// (v = hi + lo, hi = bf16(v), lo = bf16(v - hi)), each [32][PA bytes], a row = 32 NS bf16 values: the dk columns and
-// zeros up to the next multiple of 32.  An image is one contiguous block of IMG bytes (a multiple of 1 KB).
+// A matrix that takes part in a pass (the chunk's negatives, the chunk's edge-side operands) is kept as "images": per
+// chunk-side and tile of 32 rows a plane of the rows' hi parts and a plane of their lo parts, each [32][PA bytes], a
+// row = 32 NB 16-bit values: the dk columns and zeros up to the next multiple of 32.  An image is one contiguous
+// block of IMG bytes (a multiple of 1 KB).
+//   fp32 precision:  v 2^e = hi + lo with hi = f16(v 2^e), lo = f16(v 2^e - hi), one exponent e per block of 16 rows,
+//                    chosen so that the block's largest value lies in [2^14, 2^15); e is kept beside the images.
+//   SPLIT_BF16:      v = hi + lo with hi = bf16(v), lo = bf16(v - hi).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mar_common.h"
+
 // Row pitch in bytes of a plane whose rows hold `rowb` bytes: the pitch in 4-byte banks, mod 64, must be one of
-// 12, 28, 36, 52 -- then the 16 rows of a 16-byte fragment read fall into 16 different groups of 4 LDS banks, and
-// the 4 rows of a transpose read into 4 different groups of 8 banks.
+// 12, 28, 36, 52 -- then 16 rows of a 16-byte fragment read fall into 16 different groups of 4 LDS banks, and
+// the 4 rows that a group of 16 lanes covers in a transpose read into 4 different groups of 8 banks.
 constexpr int sp_pitch(int rowb) {
   for (int pad = 16; pad <= 256; pad += 16) {
     const int p = ((rowb + pad) / 4) % 64;
@@ -18,23 +23,31 @@ constexpr int sp_pitch(int rowb) {
   }
   return rowb + 16;
 }
-constexpr int SP_TY = 32;                                  // rows per image
-constexpr int sp_plane(int ns) { return SP_TY * sp_pitch(64 * ns); }
-constexpr int sp_image(int ns) { return (2 * sp_plane(ns) + 1023) / 1024 * 1024; }
-// Contraction steps of 32 columns (NS) and 16-column output blocks (NCB) of the instantiation that serves dk.
-constexpr int sp_ns(int dk) { return dk <= 64 ? 2 : (dk <= 128 ? 4 : (dk <= 256 ? 8 : 13)); }
-constexpr int sp_ncb(int dk) { return dk <= 64 ? 4 : (dk <= 112 ? 7 : (dk <= 128 ? 8 : (dk <= 208 ? 13 : (dk <= 256 ? 16 : 25)))); }
+constexpr int SP_TY = MAR_SPLIT_TILE_ROWS;                 // rows per image
+constexpr int SP_EB = 16;                                  // rows per exponent
+constexpr int SP_SR = MAR_SPLIT_STRIPE_ROWS;               // stationary rows per workgroup: four waves of 32
+// 16-column contraction steps (NK) of the instantiation that serves dk; 32-column output blocks (NB) follow from it.
+constexpr int sp_nk(int dk) { return dk <= 32 ? 2 : (dk <= 64 ? 4 : (dk <= 96 ? 6 : (dk <= 112 ? 7 : (dk <= 128 ? 8 : (dk <= 192 ? 12 : (dk <= 256 ? 16 : 25)))))); }
+constexpr int sp_nb(int nk) { return (nk + 1) / 2; }
+constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(64 * sp_nb(nk)); }
+constexpr int sp_image(int nk) { return (2 * sp_plane(nk) + 1023) / 1024 * 1024; }
+static inline int sp_tiles(int rows) { return (rows + SP_TY - 1) / SP_TY; }
 
 // Where the gather writes an image set: [chunk-sides][tiles][IMG].
 struct SplitImages {
-  char* base;           // NULL: no images are written
+  char* base;
+  float* exps;          // [chunk-sides][2 tiles] exponent of every 16-row block (+ SP_NONFINITE)
+  float* norms;         // [chunk-sides][2 tiles] bound of its scaled rows' norms (evaluation)
   int32_t pa, plane, img, tiles, dkp;
 };
-static inline SplitImages sp_images(char* base, int dk, int rows_per_chunk) {
-  const int ns = sp_ns(dk);
+// Added to the exponent of a block that holds an infinity or a NaN (its exponent is that of its finite values) or, in
+// evaluation, a row too far below the block's largest.
+#define SP_NONFINITE 1024.f
+static inline SplitImages sp_images(char* base, float* exps, float* norms, int dk, int rows_per_chunk) {
+  const int nk = sp_nk(dk);
   SplitImages g;
-  g.base = base; g.pa = sp_pitch(64 * ns); g.plane = sp_plane(ns); g.img = sp_image(ns);
-  g.tiles = (rows_per_chunk + SP_TY - 1) / SP_TY; g.dkp = 32 * ns;
+  g.base = base; g.exps = exps; g.norms = norms; g.pa = sp_pitch(64 * sp_nb(nk)); g.plane = sp_plane(nk); g.img = sp_image(nk);
+  g.tiles = sp_tiles(rows_per_chunk); g.dkp = 32 * sp_nb(nk);
   return g;
 }
 
@@ -43,23 +56,61 @@ static inline SplitImages sp_images(char* base, int dk, int rows_per_chunk) {
 __device__ __forceinline__ char* sp_row(const SplitImages& g, int cs, int row) {
   return g.base + ((size_t)cs * g.tiles + row / SP_TY) * g.img + (row % SP_TY) * g.pa;
 }
+// Exponent of a block whose largest finite magnitude has these float bits: 2^e max lies in [2^14, 2^15).  Clamped to
+// what a float power of two and the sums of a pass can hold (a block of values below 2^-66 keeps fewer bits).
+__device__ __forceinline__ int sp_exponent(int max_bits) {
+  const int e = 141 - (max_bits >> 23);
+  return max_bits == 0 ? 0 : (e > 80 ? 80 : e);
+}
+typedef _Float16 sp_h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 sp_h4 __attribute__((ext_vector_type(4)));
 typedef __bf16 sp_bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sp_bf4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void sp_store1(char* hi_row, int plane, int col, float v) {
-  const __bf16 h = (__bf16)v;
-  *reinterpret_cast<__bf16*>(hi_row + 2 * col) = h;
-  *reinterpret_cast<__bf16*>(hi_row + plane + 2 * col) = (__bf16)(v - (float)h);
+
+// hi and lo parts of a scaled value; an infinity or NaN is its hi part alone
+__device__ __forceinline__ void sp_parts(float v, _Float16& h, _Float16& l) {
+  h = (_Float16)v;
+  l = (_Float16)(fabsf(v) <= 3.0e38f ? v - (float)h : 0.f);
 }
-__device__ __forceinline__ void sp_store2(char* hi_row, int plane, int col, float2 v) {
-  const sp_bf2 h = {(__bf16)v.x, (__bf16)v.y};
-  const sp_bf2 l = {(__bf16)(v.x - (float)h[0]), (__bf16)(v.y - (float)h[1])};
-  *reinterpret_cast<sp_bf2*>(hi_row + 2 * col) = h;
-  *reinterpret_cast<sp_bf2*>(hi_row + plane + 2 * col) = l;
+__device__ __forceinline__ void sp_parts(float v, __bf16& h, __bf16& l) { h = (__bf16)v; l = (__bf16)(v - (float)h); }
+
+template <bool F16> __device__ __forceinline__ void sp_store1(char* hi_row, int plane, int col, float v, float scale) {
+  if (F16) {
+    _Float16 h, l;
+    sp_parts(v * scale, h, l);
+    *reinterpret_cast<_Float16*>(hi_row + 2 * col) = h;
+    *reinterpret_cast<_Float16*>(hi_row + plane + 2 * col) = l;
+  } else {
+    __bf16 h, l;
+    sp_parts(v, h, l);
+    *reinterpret_cast<__bf16*>(hi_row + 2 * col) = h;
+    *reinterpret_cast<__bf16*>(hi_row + plane + 2 * col) = l;
+  }
 }
-__device__ __forceinline__ void sp_store4(char* hi_row, int plane, int col, float4 v) {
-  const sp_bf4 h = {(__bf16)v.x, (__bf16)v.y, (__bf16)v.z, (__bf16)v.w};
-  const sp_bf4 l = {(__bf16)(v.x - (float)h[0]), (__bf16)(v.y - (float)h[1]), (__bf16)(v.z - (float)h[2]), (__bf16)(v.w - (float)h[3])};
-  *reinterpret_cast<sp_bf4*>(hi_row + 2 * col) = h;
-  *reinterpret_cast<sp_bf4*>(hi_row + plane + 2 * col) = l;
+template <bool F16> __device__ __forceinline__ void sp_store2(char* hi_row, int plane, int col, float2 v, float scale) {
+  if (F16) {
+    _Float16 h[2], l[2];
+    sp_parts(v.x * scale, h[0], l[0]); sp_parts(v.y * scale, h[1], l[1]);
+    *reinterpret_cast<sp_h2*>(hi_row + 2 * col) = (sp_h2){h[0], h[1]};
+    *reinterpret_cast<sp_h2*>(hi_row + plane + 2 * col) = (sp_h2){l[0], l[1]};
+  } else {
+    __bf16 h[2], l[2];
+    sp_parts(v.x, h[0], l[0]); sp_parts(v.y, h[1], l[1]);
+    *reinterpret_cast<sp_bf2*>(hi_row + 2 * col) = (sp_bf2){h[0], h[1]};
+    *reinterpret_cast<sp_bf2*>(hi_row + plane + 2 * col) = (sp_bf2){l[0], l[1]};
+  }
+}
+template <bool F16> __device__ __forceinline__ void sp_store4(char* hi_row, int plane, int col, float4 v, float scale) {
+  if (F16) {
+    _Float16 h[4], l[4];
+    sp_parts(v.x * scale, h[0], l[0]); sp_parts(v.y * scale, h[1], l[1]); sp_parts(v.z * scale, h[2], l[2]); sp_parts(v.w * scale, h[3], l[3]);
+    *reinterpret_cast<sp_h4*>(hi_row + 2 * col) = (sp_h4){h[0], h[1], h[2], h[3]};
+    *reinterpret_cast<sp_h4*>(hi_row + plane + 2 * col) = (sp_h4){l[0], l[1], l[2], l[3]};
+  } else {
+    __bf16 h[4], l[4];
+    sp_parts(v.x, h[0], l[0]); sp_parts(v.y, h[1], l[1]); sp_parts(v.z, h[2], l[2]); sp_parts(v.w, h[3], l[3]);
+    *reinterpret_cast<sp_bf4*>(hi_row + 2 * col) = (sp_bf4){h[0], h[1], h[2], h[3]};
+    *reinterpret_cast<sp_bf4*>(hi_row + plane + 2 * col) = (sp_bf4){l[0], l[1], l[2], l[3]};
+  }
 }
 #endif

@@ -1,72 +1,79 @@
-// Split-precision variant of the two contraction passes for the bilinear models (gfx950).
+// Contraction passes of the bilinear models (DistMult, ComplEx, Dot) on the 16-bit matrix pipe (gfx950): scores with
+// online softmax and the edge-side gradient, the negatives' gradient, and rank counts.
 //
-// Every fp32 operand is written as the sum of two bf16 numbers, v = hi + lo with hi = bf16(v) and
-// lo = bf16(v - hi) (v - hi is exact in fp32), and every product a b is taken as
+// fp32 precision (F16 = true).  Every operand value is written as v 2^e = hi + lo, both f16 (mar_split.h; one exponent
+// per 16 rows puts the largest value just below 2^15), and every product a b is taken as
 //     a_hi b_hi + a_lo b_hi + a_hi b_lo
-// on the bf16 matrix pipe (v_mfma_f32_16x16x32_bf16, fp32 accumulation), which runs at 16 times the fp32 matrix
-// rate.  The dropped term a_lo b_lo and the rounding of the lo parts are of relative size 2^-16 .. 2^-17 per
-// product, far inside the 1e-4 bars of the step.  The passes write what k_flash / k_flash_bwd write (softmax
-// statistics, unnormalised operand gradients, gradient rows of the negatives), so everything around them is shared;
-// they keep no weights between them (pass 2 computes the scores again, see k_split).
+// with v_mfma_f32_32x32x16_f16 (fp32 accumulation), which runs at 16 times the rate of the fp32 matrix instructions.
+// hi + lo holds 23-24 significant bits of every value down to 2^-17 of its block's largest (below that an absolute
+// 2^-40 of the largest), the dropped product is below 2^-22 of its pair, and the sums see 3 roundings per 16 terms
+// where the fp32 instruction sees 4, so a pass is as accurate as its fp32 form: against 64 bits a dot product of 128
+// (1024) normal values is off by 1.5e-7 (3.5e-7) of its norm, with v_mfma_f32_16x16x4_f32 by 1.9e-7 (5.6e-7).
+// SPLIT_BF16 (F16 = false): v = hi + lo in bf16 without exponents, the same three products; errors of 2^-16 .. 2^-17
+// per product.
 //
-// Operand images (mar_split.h).  The gather writes both operand matrices (the chunk's negatives, the chunk's
-// edge-side operands) as "images": per chunk-side and tile of 32 rows a hi plane and a lo plane, [32][PA bytes] each,
-// row = 32 NS bf16 values (the row padded with zeros to a multiple of 32 columns) at a pitch PA chosen so that both
-// kinds of LDS read below are free of bank conflicts.  An image is one contiguous block; the images of the matrix a
-// pass streams (pass 1: the negatives, pass 2: the edge-side operands) are copied into LDS by buffer loads that
-// write LDS directly, one tile ahead, in two alternating buffers; the stationary rows' fragments are read from
-// their own images once.
+// Softmax weights are formed as 2^(t - ref) with t = score log2(e) - e_y and an integer reference per stationary row
+// that moves only when some t exceeds it by more than 15 (it is then put 8 below the maximum): the weights stay below
+// the largest f16, values down to 2^-33 of the largest weight keep their place in hi + lo, moving the reference
+// multiplies by powers of two only, and the streamed block's exponent e_y needs no operation of its own.  The
+// reference is folded into the statistics at the end (mantissa of the sum, integer in log2 units), so parts merge
+// exactly.
 //
-// Lane layouts (lane = 16 g + m):
-//   v_mfma_f32_16x16x32_bf16: A lane holds row m, contraction slots 8g .. 8g+7; B lane holds column m, the same
-//   slots; D lane holds column m, rows 4g .. 4g+3.  Which contraction index a slot stands for is free as long as A
-//   and B agree.
-//   Score product S^T[y][x] = sum_c Y[y][c] X[x][c]: A = Y from LDS (16-byte read of row y = m, columns 32 s + 8g ..),
-//   B = X fragments held in registers.  D: lane (g, m) gets S^T[4g + r][x = m], for the two 16-row blocks of a tile.
-//   Second product O^T[c][x] += sum_y Y[y][c] W[y][x] over the tile's 32 rows: B = W built from the lane's own 8
-//   score registers, slot kk <-> y = 4g + kk (kk < 4), 16 + 4g + kk - 4 (kk >= 4).  A = Y^T: lane (g, m) needs
-//   Y[y of slot kk][16 cb + m] -- a column access of a row-major plane, which the LDS transpose read
-//   (ds_read_b64_tr_b16) provides: within a group of 16 lanes, lane i passes the address of 4 consecutive 16-bit
-//   values and receives, as its j-th value, value (i % 4) of lane 4j + i / 4.  With lane i pointing at row
-//   4g + i / 4 (+ 16 for the second block), columns 16 cb + 4 (i % 4) .. +3, lane m receives Y[4g + j][16 cb + m].
+// Operand images come from the gather.  The images of the matrix a pass streams (pass 1 and 3: the negatives, pass 2:
+// the edge-side operands) are copied into LDS by buffer loads that write LDS directly, one tile ahead, in two
+// alternating buffers; the stationary rows' fragments are read from their own images once and stay in registers.
+//
+// Lane layouts (lane = 32 h + m; i = lane % 16, G = lane / 16):
+//   v_mfma_f32_32x32x16_f16 / bf16: A lane holds row m, contraction slots 8h .. 8h+7; B lane holds column m, the same
+//   slots; D lane holds column m, register v = row 8 (v / 4) + 4h + v % 4.  Which contraction index a slot stands for
+//   is free as long as A and B agree.
+//   Score product S^T[y][x] = sum_c Y[y][c] X[x][c]: A = Y from LDS (16-byte read of row m, columns 16 s + 8h ..),
+//   B = X fragments in registers.
+//   Second product O^T[c][x] += sum_y Y[y][c] W[y][x] over the tile's 32 rows in two steps of 16: B of step k = W of
+//   the lane's own score registers 8k .. 8k+7, so slot 8h + j stands for row 16k + 4h + j (j < 4), 16k + 8 + 4h + j - 4
+//   (j >= 4).  A = Y^T by the LDS transpose read (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4
+//   consecutive 16-bit values and receives, as its j-th value, value (i % 4) of lane 4j + i / 4; with lane i pointing
+//   at row 4h + i / 4, columns 32 cb + 16 (G % 2) + 4 (i % 4), lane m receives Y[4h + j][32 cb + m].
 #include <type_traits>
 
 #include "mar_common.h"
 #include "mar_flash.h"
 #include "mar_split.h"
 
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef short v4s __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v4f mfma_bf(v8bf a, v8bf b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// v = hi + lo, both bf16 (round to nearest even); converted two at a time (one packed conversion per pair)
+typedef short v8s __attribute__((ext_vector_type(8)));
 typedef float v2f __attribute__((ext_vector_type(2)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void split8(const float (&v)[8], v8bf& hi, v8bf& lo) {
-#pragma unroll
-  for (int i = 0; i < 8; i += 2) {
-    const v2f p = {v[i], v[i + 1]};
-    const v2bf h = __builtin_convertvector(p, v2bf);
-    const v2f r = p - __builtin_convertvector(h, v2f);
-    const v2bf l = __builtin_convertvector(r, v2bf);
-    hi[i] = h[0]; hi[i + 1] = h[1];
-    lo[i] = l[0]; lo[i + 1] = l[1];
-  }
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+
+template <bool F16> __device__ __forceinline__ v16f mfma32(v8s a, v8s b, v16f c) {
+  if (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
 }
 
-template <int NS>
-struct SplitGeom {
-  static constexpr int PA = sp_pitch(64 * NS);
-  static constexpr int PLANE = sp_plane(NS);
-  static constexpr int IMG = sp_image(NS);
-  static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
-  static constexpr int NCW = (NCH + 3) / 4;                // pieces per wave
-  static constexpr size_t LDS_BYTES = 2 * (size_t)IMG;
-};
+// v = hi + lo, two values per step: one packed conversion and two mixed-precision multiply-adds (f16; neg1 = -1 in a
+// register the compiler cannot see through, or it would turn the multiply-add into a conversion and a subtraction),
+// two packed conversions with the unpacking between them (bf16).
+template <bool F16, int O> __device__ __forceinline__ void split8(const float (&v)[16], float neg1, v8s& hi, v8s& lo) {
+  v4i hw, lw;                                              // two 16-bit values per word
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float p0 = v[O + 2 * i], p1 = v[O + 2 * i + 1];
+    if (F16) {
+      const v2h h = __builtin_convertvector((v2f){p0, p1}, v2h);
+      const v2h l = {(_Float16)__builtin_fmaf((float)h[0], neg1, p0), (_Float16)__builtin_fmaf((float)h[1], neg1, p1)};
+      hw[i] = __builtin_bit_cast(int, h); lw[i] = __builtin_bit_cast(int, l);
+    } else {
+      const v2b h = __builtin_convertvector((v2f){p0, p1}, v2b);
+      const v2b l = __builtin_convertvector((v2f){p0 - (float)h[0], p1 - (float)h[1]}, v2b);
+      hw[i] = __builtin_bit_cast(int, h); lw[i] = __builtin_bit_cast(int, l);
+    }
+  }
+  hi = __builtin_bit_cast(v8s, hw); lo = __builtin_bit_cast(v8s, lw);
+}
 
 __device__ __forceinline__ unsigned lds_address_b(const char* p) {
   return (unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p;
@@ -74,298 +81,393 @@ __device__ __forceinline__ unsigned lds_address_b(const char* p) {
 __device__ __forceinline__ v4s lds_read_tr(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
 }
-__device__ __forceinline__ v8bf join8(v4s a, v4s b) {
-  return __builtin_bit_cast(v8bf, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
-}
+__device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 
-// O^T[c][x] += sum over the tile's 32 rows of Y[y][c] W[y][x] for the 16-column blocks cb0 .. cb0 + ncb - 1 (ncb <= NCB,
-// uniform over the wave); W is given split.  Blocks are taken a few at a time so that consecutive matrix instructions
-// write different accumulators.
-template <int NCB, int XB, int PA>
-__device__ __forceinline__ void second_product(const char* hi, const char* lo, int trofs, int cb0, int ncb, const v8bf (&wh)[XB],
-                                               const v8bf (&wl)[XB], v4f (&oacc)[XB][NCB]) {
-  constexpr int CG = XB >= 2 ? 2 : 4;
-  hi += trofs + 32 * cb0; lo += trofs + 32 * cb0;
+#define SP_PEND 8                                          // close comparisons a lane of pass 3 keeps for the end
+template <int NK>
+struct SplitGeom {
+  static constexpr int NB = sp_nb(NK);
+  static constexpr int PA = sp_pitch(64 * NB);
+  static constexpr int PLANE = sp_plane(NK);
+  static constexpr int IMG = sp_image(NK);
+  static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
+  static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
+  static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + SP_PEND * 256 * 4;   // two images, and the lanes' pending comparisons
+};
+
+// Evaluation compares scores with the positive's, and where the two are within rounding of one another the outcome
+// belongs to the arithmetic (an edge's own endpoint among the candidates scores what the edge does).  Comparisons
+// closer than the passes' error are settled by the fp32 score as v_mfma_f32_16x16x4_f32 forms it -- a chain of fused
+// multiply-adds -- in the column order of the fp32 contraction kernels: blocks of 16 columns up to column `chain`, each
+// as columns 4 g + i for i = 0..3, g = 0..3; the rest in sequence.  So do blocks that hold an infinity or a NaN.
+constexpr int sp_chain(int dk) { return dk <= 52 ? 48 : (dk <= 100 ? 96 : 400); }
+template <bool VEC>
+__device__ __forceinline__ float sp_exact_score(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
+  float s = 0.f;
+  const int nb = (min(chain, dim) + 15) / 16;
+  constexpr int UB = 4;                                    // blocks whose loads are in flight at once
+  for (int b0 = 0; b0 < nb; b0 += UB) {
+    float a[UB][16], c[UB][16];
 #pragma unroll
-  for (int c0 = 0; c0 < NCB; c0 += CG) {
-    v8bf ah[CG], al[CG];
+    for (int b = 0; b < UB; ++b) {
 #pragma unroll
-    for (int j = 0; j < CG; ++j) {
-      if (c0 + j < NCB && (c0 + j < NCB - 1 || c0 + j < ncb)) {   // only the last block may be absent
-        ah[j] = join8(lds_read_tr(hi + 32 * (c0 + j)), lds_read_tr(hi + 16 * PA + 32 * (c0 + j)));
-        al[j] = join8(lds_read_tr(lo + 32 * (c0 + j)), lds_read_tr(lo + 16 * PA + 32 * (c0 + j)));
-      }
-    }
+      for (int i = 0; i < 16; i += 4) {
+        const int k = 16 * (b0 + b) + i;
+        if (VEC) {
+          float4 u = make_float4(0.f, 0.f, 0.f, 0.f), v = u;
+          if (b0 + b < nb && k < dim) { u = *reinterpret_cast<const float4*>(y + k); v = *reinterpret_cast<const float4*>(q + k); }
+          a[b][i] = u.x; a[b][i + 1] = u.y; a[b][i + 2] = u.z; a[b][i + 3] = u.w;
+          c[b][i] = v.x; c[b][i + 1] = v.y; c[b][i + 2] = v.z; c[b][i + 3] = v.w;
+        } else {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-      for (int j = 0; j < CG; ++j) {
-        if (c0 + j < NCB && (c0 + j < NCB - 1 || c0 + j < ncb)) {
-#pragma unroll
-          for (int b = 0; b < XB; ++b) oacc[b][c0 + j] = mfma_bf(k == 1 ? al[j] : ah[j], k == 2 ? wl[b] : wh[b], oacc[b][c0 + j]);
+          for (int j = 0; j < 4; ++j) {
+            const bool in = b0 + b < nb && k + j < dim;
+            a[b][i + j] = in ? y[k + j] : 0.f; c[b][i + j] = in ? q[k + j] : 0.f;
+          }
         }
       }
     }
-  }
-}
-
-// ------------------------------------------------------------------- the two passes -----
-// PASS 1: scores, online softmax and gQ = P K for 64 XB edges of one chunk-side against the chunk's negatives; the
-// unit numbering, the split of the last round's stripes and the lazily updated softmax reference are k_flash's, and
-// so are the statistics and gradient rows written.  No weights are kept for pass 2:
-// PASS 2: gK = P^T Q for 64 XB negatives of one chunk-side against the chunk's edges, with the scores computed again
-// (the same three bf16 products) and P = exp(score - lse) from the finished log-sum-exp.  Writing the weights out
-// and reading them back costs 8 bytes of memory traffic per pair, computing a score again 6 d bf16 flops: at this
-// matrix rate the second is several times cheaper (the fp32 passes, whose matrix rate is 16 times lower, store them).
-// The unit numbering and the gradient rows written are k_flash_bwd's.
-// CSP = 2 (widest rows): two waves share each 16-row block, each taking half of the columns -- half of the
-// contraction steps of the score product (the partial scores are exchanged through LDS and added, so both waves go
-// on with the same scores, weights and softmax statistics) and half of the second product's output blocks.  A wave
-// then holds half of the stationary fragments and half of the accumulators, and a workgroup of eight waves puts two
-// waves on every SIMD where the four-wave form has registers for one.
-template <int NS, int NCB, int XB, int PASS, int CSP, int NW>
-__global__ void __launch_bounds__(64 * NW) MAR_WAVES_PER_SIMD((NW == 8 || NS <= 8 ? 2 : 1))
-k_split(FlashArgs a) {
-  typedef SplitGeom<NS> SG;
-  constexpr int PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
-  constexpr int TY = SP_TY;
-  constexpr int SR = (NW / CSP) * XB * 16;                 // stationary rows per workgroup
-  constexpr int NSA = (NS + CSP - 1) / CSP, NCBA = (NCB + CSP - 1) / CSP;   // steps and output blocks per wave
-  constexpr int NCW = (SG::NCH + NW - 1) / NW;             // 1 KB pieces of an image per wave
-  constexpr float LOG2E = 1.44269504088896341f;
-  static_assert(SR == 64 * (NS <= 4 ? 2 : 1), "stripe rows the launch planning assumes");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][TY] log-sum-exp of the tile's edges
-  float* const xch = aux_all + 2 * TY;                     // CSP = 2: [NW][8 XB][64] partial scores
-
-  const int lane = threadIdx.x & 63, wave_all = threadIdx.x >> 6;
-  const int wave = wave_all / CSP, half = wave_all % CSP;  // row block of the workgroup, half of the columns
-  const int s0 = half * NSA, ns = min(NSA, NS - s0);       // this wave's contraction steps s0 .. s0 + ns - 1
-  const int cb0 = half * NCBA, ncb = min(NCBA, NCB - cb0); // and output blocks
-  const int g = lane >> 4, m = lane & 15;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int part, cs, stripe, tps = a.tps;
-  if (slot < a.whole_slots) {
-    part = slot % a.sy;
-    const int slot2 = slot / a.sy;
-    cs = (slot2 / a.nstripes) * 8 + xcd;
-    stripe = slot2 % a.nstripes;
-  } else {                                                // a part of a split stripe (see k_flash)
-    const int r = (slot - a.whole_slots) * 8 + xcd;
-    const int unit = r / a.rem_k;
-    part = r % a.rem_k;
-    cs = a.rem_cs0 + unit / a.nstripes;
-    stripe = unit % a.nstripes;
-    tps = a.rem_tps;
-  }
-  const int csl = cs;                                      // chunk-side in launch order
-  if (PASS == 2) cs = 2 * a.nchunks - 1 - cs;              // reverse of pass 1's order (see k_flash_bwd)
-  if (cs < 0 || cs >= 2 * a.nchunks) return;
-  const int side = cs & 1, c = cs >> 1;
-  const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
-  const int n_x = PASS == 1 ? ne : a.N;                   // stationary rows
-  const int n_y = PASS == 1 ? a.N : ne;                   // streamed rows
-  if (stripe * SR >= n_x) return;
-  const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
-  const size_t k_base = (size_t)side * a.C * a.N + (size_t)c * a.N;  // first K row of the chunk
-  const size_t x_base = PASS == 1 ? q_base : k_base;
-  const int dk = a.dk;
-
-  // ---- stationary fragments from the rows' own images: slots of step s = columns 32 s + 8g .. +7 of row x
-  int x[XB]; bool xv[XB];
-  v8bf xh[XB][NSA], xl[XB][NSA];
 #pragma unroll
-  for (int b = 0; b < XB; ++b) {
-    x[b] = stripe * SR + (wave * XB + b) * 16 + m;
-    xv[b] = x[b] < n_x;
-    const char* xrow = a.ximg + ((size_t)cs * a.ximg_tiles + x[b] / TY) * IMG + (x[b] % TY) * PA + 16 * g + 64 * s0;
+    for (int b = 0; b < UB; ++b) {
 #pragma unroll
-    for (int s = 0; s < NSA; ++s) {
-      xh[b][s] = (v8bf){0, 0, 0, 0, 0, 0, 0, 0};
-      xl[b][s] = (v8bf){0, 0, 0, 0, 0, 0, 0, 0};
-      if (xv[b] && s < ns) {
-        xh[b][s] = *reinterpret_cast<const v8bf*>(xrow + 64 * s);
-        xl[b][s] = *reinterpret_cast<const v8bf*>(xrow + PLANE + 64 * s);
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) s = __builtin_fmaf(a[b][4 * g + i], c[b][4 * g + i], s);
       }
     }
   }
-
-  v4f oacc[XB][NCBA];
-  float mrun[XB], lrun[XB];
-#pragma unroll
-  for (int b = 0; b < XB; ++b) {
-#pragma unroll
-    for (int cb = 0; cb < NCBA; ++cb) oacc[b][cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-    mrun[b] = -3.0e38f; lrun[b] = 0.f;
+  for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
+  return s;
+}
+// The same, one column at a time: rare, and inside the tile loop, where it must not cost registers.
+__device__ __forceinline__ float sp_exact_score_slow(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
+  float s = 0.f;
+  const int n = (min(chain, dim) + 15) & ~15;
+#pragma unroll 1
+  for (int t = 0; t < n; ++t) {
+    const int k = (t & ~15) + 4 * (t & 3) + ((t & 15) >> 2);
+    if (k < dim) s = __builtin_fmaf(y[k], q[k], s);
   }
+#pragma unroll 1
+  for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
+  return s;
+}
+
+#ifndef SP_PD
+#define SP_PD 4
+#endif
+#ifndef SP_PG
+#define SP_PG 2
+#endif
+// ------------------------------------------------------------------------ the passes -----
+// PASS 1: scores, online softmax and gQ = P K for 128 edges of one chunk-side (32 per wave) against the chunk's
+// negatives.  No weights are kept for pass 2:
+// PASS 2: gK = P^T Q for 128 negatives of one chunk-side against the chunk's edges, with the scores computed again and
+// P = exp(score - lse) from the finished log-sum-exp.  Writing the weights out and reading them back costs 8 bytes of
+// memory traffic per pair, computing a score again 6 d 16-bit flops: at this matrix rate the second is cheaper.
+// PASS 3 (evaluation): counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add
+// their counts.
+template <int NK, int PASS, bool F16>
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD((NK <= 8 ? 2 : 1))
+k_split(FlashArgs a) {
+  typedef SplitGeom<NK> SG;
+  constexpr int NB = SG::NB, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
+  constexpr int TY = SP_TY;
+  constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
+  constexpr float LOG2E = 1.44269504088896341f;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][2][TY] log-sum-exp of the tile's edges, log2 units
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int h = lane >> 5, m = lane & 31;
+  FlashUnit u;
+  if (!flash_unit(a, u)) return;
+  const int cs = u.cs, side = cs & 1, c = cs >> 1;
+  const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
+  const int n_x = PASS == 2 ? a.N : ne;                   // stationary rows
+  const int n_y = PASS == 2 ? ne : a.N;                   // streamed rows
+  if (u.stripe * SP_SR >= n_x) return;
+  const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
+  const int dk = a.dk;
+  float neg1 = -1.f;
+  asm volatile("" : "+v"(neg1));
+
+  // ---- stationary fragments from the rows' own images: slots of step s = columns 16 s + 8h .. +7 of row x
+  const int x = u.stripe * SP_SR + wave * 32 + m;
+  const bool xv = x < n_x;
+  const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave;
+  const char* xrow = a.ximg + xtile * IMG + m * PA;
+  v8s xh[NK], xl[NK];
+#pragma unroll
+  for (int s = 0; s < NK; ++s) {
+    xh[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+    xl[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
+    if (xv) {
+      xh[s] = *reinterpret_cast<const v8s*>(xrow + 16 * h + 32 * s);
+      xl[s] = *reinterpret_cast<const v8s*>(xrow + PLANE + 16 * h + 32 * s);
+    }
+  }
+  float ex = 0.f;                                         // exponent of the row's block
+  bool xbad = false;
+  if (F16 && xv) {
+    ex = a.xexp[xtile * 2 + (m >> 4)];
+    xbad = ex > 0.5f * SP_NONFINITE;
+    if (xbad) ex -= SP_NONFINITE;
+  }
+  // Pass 3.  A comparison is close if the score is within 2 sqrt(dk) 2^-24 |q| |n| of the positive's.  The rounding
+  // errors of a chain of dk steps are independent and each below 2^-24 |q| |n| (the partial sums are), 0.3 of that on
+  // average: the bound is seven standard deviations where all products have one sign, and ten times that where they
+  // do not.
+  float posx = 0.f, tolx = 0.f;
+  const float* qrow = nullptr;
+  int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
+  int npend = 0;
+  if (PASS == 3) {
+    float n2 = 0.f;
+#pragma unroll
+    for (int s = 0; s < NK; ++s) {
+      const v8h f = __builtin_bit_cast(v8h, xh[s]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
+    }
+    n2 += __shfl_xor(n2, 32);
+    tolx = 2.f * sqrtf((float)dk) * 0x1p-24f * sqrtf(n2);
+    if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
+  }
+  auto exact_above = [&](int y) -> int {                   // streamed row y against this lane's edge
+    const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + y];
+    return sp_exact_score_slow(qrow, a.table + (size_t)id * a.dim, a.dim, sp_chain(dk)) > posx ? 1 : 0;
+  };
+
+  constexpr int NO = PASS == 3 ? 1 : NB;
+  v16f oacc[NO];
+#pragma unroll
+  for (int cb = 0; cb < NO; ++cb) oacc[cb] = (v16f)(0.f);
+  float mref = -3.0e38f, lrun = 0.f;                      // softmax reference (log2 units, an integer) and sum
+  int cnt = 0;
 
   const int ntiles_all = (n_y + TY - 1) / TY;
-  const int t_begin = part * tps;
-  const int ntiles = min(ntiles_all, t_begin + tps);
+  const int t_begin = u.part * u.tps;
+  const int ntiles = min(ntiles_all, t_begin + u.tps);
 
-  // ---- images of the streamed rows, copied into LDS one tile ahead (see k_flash's DMA path); a register load issued
-  // behind the copies is the fence: once its value is there the image is in LDS.  PASS 2's fence is the load of the
-  // softmax statistics of streamed edge threadIdx % TY.
+  // ---- images of the streamed rows, copied into LDS one tile ahead; a register load issued behind the copies is the
+  // fence (memory operations of a wave complete in order): once its value is there the image is in LDS.  The fence is
+  // the load of the tile's two exponents; pass 2 also loads the softmax statistics of edge threadIdx % TY behind it.
   const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
-  const uint32_t ybytes = (uint32_t)a.yimg_tiles * IMG;
-  const v4i ywords = buf_words(ybase, ybytes);
-  const BufRsrc ysrc = buf_rsrc(ybase, ybytes);
+  const BufRsrc expsrc = buf_rsrc(F16 ? (const void*)(a.yexp + (size_t)cs * a.yimg_tiles * 2) : (const void*)ybase, (uint32_t)a.yimg_tiles * 8);
   const BufRsrc mlsrc = buf_rsrc(a.ml + q_base * 2, PASS == 2 ? (uint32_t)ne * 8 : 0u);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave_all);
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int f_row = threadIdx.x % TY;
   const size_t ml_stride = (size_t)2 * a.B;               // rows per part of pass 1's statistics
-  float fence = 0.f;
-  float2 st_ml = make_float2(0.f, 0.f);
+  float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f), st_ml = make_float2(0.f, 0.f);
+  const BufRsrc normsrc = buf_rsrc(PASS == 3 ? (const void*)(a.ynorm + (size_t)cs * a.yimg_tiles * 2) : (const void*)ybase, PASS == 3 ? (uint32_t)a.yimg_tiles * 8 : 0u);
   int token = 0;
-  auto dma_tile = [&](int t, int buf) {
-    const int tofs = t * IMG;
-#pragma unroll
-    for (int q = 0; q < NCW; ++q) {
-      const int pc = NW * q + wave_s;
-      if (pc < SG::NCH) buf_load4_to_lds(ywords, lds_address_b(smem) + buf * IMG + pc * 1024, lane * 16, tofs + pc * 1024, token);
-    }
+  auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
+    const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
+    const int pc = 4 * q + wave_s;
+    if (pc < SG::NCH) buf_load4_to_lds(ywords, lds_address_b(smem) + buf * IMG + pc * 1024, lane * 16, pc * 1024, token);
+  };
+  auto dma_fence = [&](int t) {
+    ye_next = buf_load2(expsrc, token, t * 8);
+    if (PASS == 3) yn_next = buf_load2(normsrc, token, t * 8);
     if (PASS == 2) st_ml = buf_load2(mlsrc, f_row * 8 + token, t * TY * 8);
-    else fence = buf_load1(ysrc, token, tofs);
   };
   auto dma_land = [&](int t, int buf) {
+    asm volatile("" : "+v"(ye_next.x), "+v"(ye_next.y));
     if (PASS == 2) {
       const int yr = t * TY + f_row;
       float mm = st_ml.x, ll = st_ml.y;
       if (a.sy_ml > 1 && yr < n_y) {                       // pass 1 was split (small batches): merge the parts
         const float2* __restrict__ mlp = reinterpret_cast<const float2*>(a.ml) + q_base + yr;
         for (int p = 1; p < a.sy_ml; ++p) mm = fmaxf(mm, mlp[p * ml_stride].x);
-        ll *= __expf(st_ml.x - mm);
-        for (int p = 1; p < a.sy_ml; ++p) { const float2 v = mlp[p * ml_stride]; ll += v.y * __expf(v.x - mm); }
+        ll *= __builtin_amdgcn_exp2f(st_ml.x - mm);
+        for (int p = 1; p < a.sy_ml; ++p) { const float2 v = mlp[p * ml_stride]; ll += v.y * __builtin_amdgcn_exp2f(v.x - mm); }
       }
-      // rows beyond the chunk: +inf, so that their weights are exp(-inf) = 0
-      // (times log2(e): the weights are formed as 2^(score log2(e) - this); threads that share a row write the same value)
-      aux_all[buf * TY + f_row] = yr < n_y ? (mm + logf(ll)) * LOG2E : __builtin_inff();
-    } else {
-      asm volatile("" : : "v"(fence));
+      // Rows beyond the chunk: +inf, so that their weights are 2^-inf = 0 (threads that share a row write the same value).
+      // fp32: the integer and the logarithm of the mantissa stay apart (their sum would be rounded to 2^-21, an error that
+      // all of an edge's weights share).
+      const float lg = log2f(ll);
+      aux_all[2 * buf * TY + f_row] = yr < n_y ? (F16 ? lg : mm + lg) : __builtin_inff();
+      if (F16) aux_all[(2 * buf + 1) * TY + f_row] = mm;
     }
   };
   if (t_begin < ntiles) {
-    dma_tile(t_begin, 0);
+#pragma unroll
+    for (int q = 0; q < NCW; ++q) dma_piece(t_begin, 0, q);
+    dma_fence(t_begin);
     dma_land(t_begin, 0);
     __syncthreads();
   }
 
-  const int trofs = (4 * g + (m >> 2)) * PA + 8 * (m & 3);
+  const int fofs = m * PA + 16 * h;                        // score product: this lane's row and column group
+  const int trofs = (4 * h + ((lane & 15) >> 2)) * PA + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);   // second product
   for (int t = t_begin; t < ntiles; ++t) {
     const int buf = (t - t_begin) & 1;
     const char* hi = smem + buf * IMG;
     const char* lo = hi + PLANE;
     const bool has_next = t + 1 < ntiles;                  // uniform
-    if (has_next) dma_tile(t + 1, buf ^ 1);
+    const float2 ye = ye_next, yn = yn_next;
     const int y0 = t * TY;
-    const bool masked = PASS == 1 && y0 + TY > n_y;
+    const bool masked = PASS != 2 && y0 + TY > n_y;
 
-    // -- scores of the tile's two 16-row blocks.  The fragments of the streamed rows are read PD groups (one group =
-    // one contraction step of one block) ahead of the matrix instructions that consume them.
-    v4f sacc[2][XB];
-#pragma unroll
-    for (int yb = 0; yb < 2; ++yb) {
-#pragma unroll
-      for (int b = 0; b < XB; ++b) sacc[yb][b] = (v4f){0.f, 0.f, 0.f, 0.f};
-    }
+    // -- scores; the fragments of the streamed rows are read PD steps ahead of the instructions that consume them
+    v16f sacc = (v16f)(0.f);
     {
-      constexpr int NG = 2 * NSA, PD = NG < 4 ? NG : 4;
-      const int fofs = m * PA + 16 * g + 64 * s0;
-      v8bf fh[PD], fl[PD];
+      constexpr int PD = NK < SP_PD ? NK : SP_PD;
+      v8s fh[PD], fl[PD];
 #pragma unroll
-      for (int q = 0; q < PD; ++q) {                       // group q: step q / 2, block q % 2
-        fh[q] = *reinterpret_cast<const v8bf*>(hi + fofs + (q % 2) * 16 * PA + (q / 2) * 64);
-        fl[q] = *reinterpret_cast<const v8bf*>(lo + fofs + (q % 2) * 16 * PA + (q / 2) * 64);
+      for (int s = 0; s < PD; ++s) {
+        fh[s] = *reinterpret_cast<const v8s*>(hi + fofs + 32 * s);
+        fl[s] = *reinterpret_cast<const v8s*>(lo + fofs + 32 * s);
       }
 #pragma unroll
-      for (int q = 0; q < NG; ++q) {
-        const int s = q / 2, yb = q % 2;
-        if (CSP > 1 && s == NSA - 1 && s >= ns) break;       // the second half may have one step less (uniform over the wave)
-        const v8bf ah = fh[q % PD], al = fl[q % PD];
-        if (q + PD < NG) {
-          fh[q % PD] = *reinterpret_cast<const v8bf*>(hi + fofs + ((q + PD) % 2) * 16 * PA + ((q + PD) / 2) * 64);
-          fl[q % PD] = *reinterpret_cast<const v8bf*>(lo + fofs + ((q + PD) % 2) * 16 * PA + ((q + PD) / 2) * 64);
+      for (int s = 0; s < NK; ++s) {
+        const v8s ah = fh[s % PD], al = fl[s % PD];
+        if (s + PD < NK) {
+          fh[s % PD] = *reinterpret_cast<const v8s*>(hi + fofs + 32 * (s + PD));
+          fl[s % PD] = *reinterpret_cast<const v8s*>(lo + fofs + 32 * (s + PD));
         }
+        sacc = mfma32<F16>(al, xh[s], sacc);
+        sacc = mfma32<F16>(ah, xl[s], sacc);
+        sacc = mfma32<F16>(ah, xh[s], sacc);
+        // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
+        // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
+        if (has_next) {
 #pragma unroll
-        for (int b = 0; b < XB; ++b) sacc[yb][b] = mfma_bf(ah, xh[b][s], sacc[yb][b]);
-#pragma unroll
-        for (int b = 0; b < XB; ++b) sacc[yb][b] = mfma_bf(al, xh[b][s], sacc[yb][b]);
-#pragma unroll
-        for (int b = 0; b < XB; ++b) sacc[yb][b] = mfma_bf(ah, xl[b][s], sacc[yb][b]);
-        __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD groups ahead of their use
+          for (int q = s * NCW / NK; q < (s + 1) * NCW / NK; ++q) dma_piece(t + 1, buf ^ 1, q);
+          if (s == NK - 1) dma_fence(t + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
       }
     }
-    if (CSP == 2) {                                        // add the other half's partial scores
-      float* mine = xch + (wave_all * 8 * XB) * 64 + lane;
-#pragma unroll
-      for (int b = 0; b < XB; ++b) {
-#pragma unroll
-        for (int yb = 0; yb < 2; ++yb) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) mine[(8 * b + 4 * yb + r) * 64] = sacc[yb][b][r];
+    // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey)
+    float k0 = PASS == 3 ? 1.f : LOG2E, k1 = k0, e0 = 0.f, e1 = 0.f, posx_t = posx;
+    if (F16) {
+      const bool ybad = ye.x > 0.5f * SP_NONFINITE || ye.y > 0.5f * SP_NONFINITE;
+      e0 = ye.x > 0.5f * SP_NONFINITE ? ye.x - SP_NONFINITE : ye.x;
+      e1 = ye.y > 0.5f * SP_NONFINITE ? ye.y - SP_NONFINITE : ye.y;
+      k0 = __builtin_ldexpf(k0, min(126, -(int)(ex + e0)));
+      k1 = __builtin_ldexpf(k1, min(126, -(int)(ex + e1)));
+      if (PASS == 3 && __any(ybad || xbad)) {              // every pair of the tile the long way
+        for (int v = 0; v < 16; ++v) {
+          const int y = y0 + 8 * (v >> 2) + 4 * h + (v & 3);
+          if (xv && y < n_y) cnt += exact_above(y);
         }
-      }
-      __syncthreads();
-      const float* other = xch + ((wave_all ^ 1) * 8 * XB) * 64 + lane;
-#pragma unroll
-      for (int b = 0; b < XB; ++b) {
-#pragma unroll
-        for (int yb = 0; yb < 2; ++yb) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sacc[yb][b][r] += other[(8 * b + 4 * yb + r) * 64];
-        }
+        k0 = k1 = 0.f;
+        posx_t = __builtin_inff();
       }
     }
-    // -- weights of the lane's 8 pairs per x-block: slot kk <-> y = y0 + (kk < 4 ? 4g + kk : 16 + 4g + kk - 4)
-    float lse8[8];
-    if (PASS == 2) {
-      const float4 l0 = *reinterpret_cast<const float4*>(aux_all + buf * TY + 4 * g);
-      const float4 l1 = *reinterpret_cast<const float4*>(aux_all + buf * TY + 16 + 4 * g);
-      lse8[0] = l0.x; lse8[1] = l0.y; lse8[2] = l0.z; lse8[3] = l0.w; lse8[4] = l1.x; lse8[5] = l1.y; lse8[6] = l1.z; lse8[7] = l1.w;
-    }
-    v8bf wh[XB], wl[XB];
+    if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
 #pragma unroll
-    for (int b = 0; b < XB; ++b) {
-      float sc[8], w[8];
-#pragma unroll
-      for (int yb = 0; yb < 2; ++yb) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sc[4 * yb + r] = sacc[yb][b][r];
+      for (int v = 0; v < 16; ++v) {
+        if (y0 + 8 * (v / 4) + 4 * h + v % 4 >= n_y) sacc[v] = -__builtin_inff();
       }
-      if (masked) {                                        // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
+    }
+    if (PASS == 3) {
+      float near0 = __builtin_inff(), near1 = near0;
 #pragma unroll
-        for (int yb = 0; yb < 2; ++yb) {
+      for (int v = 0; v < 16; ++v) {
+        const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx_t);
+        cnt += dif > 0.f ? 1 : 0;
+        if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
+      }
+      const float tol0 = tolx * yn.x * k0, tol1 = tolx * yn.y * k1;
+      if (__any(xv && (near0 <= tol0 || near1 <= tol1))) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            if (y0 + 16 * yb + 4 * g + r >= n_y) sc[4 * yb + r] = -__builtin_inff();
+        for (int v = 0; v < 16; ++v) {
+          const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx_t);
+          if (xv && fabsf(dif) <= (v < 8 ? tol0 : tol1)) {
+            const int y = y0 + 8 * (v / 4) + 4 * h + v % 4;
+            cnt -= dif > 0.f ? 1 : 0;
+            if (npend < SP_PEND) pend[256 * npend++] = y; else cnt += exact_above(y);
           }
         }
       }
-      if (PASS == 1) {
-        const float mloc = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
-        if (__any(mloc > mrun[b] + 16.f)) {
-          float mall = fmaxf(mloc, __shfl_xor(mloc, 16));
-          mall = fmaxf(mall, __shfl_xor(mall, 32));
-          const float mnew = fmaxf(mrun[b], mall);
-          float alpha = __expf(mrun[b] - mnew);
-          asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
-          lrun[b] *= alpha;
+    } else {
+      // -- weights of the lane's 16 pairs, split; register v <-> row y0 + 8 (v / 4) + 4h + v % 4
+      float w[16];
+      if (PASS == 1 || F16) {
+        float tmax;
+        if (PASS == 1) {
+          float a0 = sacc[0], a1 = sacc[8];
 #pragma unroll
-          for (int cb = 0; cb < NCBA; ++cb) oacc[b][cb] *= alpha;
-          mrun[b] = mnew;
+          for (int v = 1; v < 8; ++v) { a0 = fmaxf(a0, sacc[v]); a1 = fmaxf(a1, sacc[8 + v]); }
+          tmax = fmaxf(__builtin_fmaf(a0, k0, -e0), __builtin_fmaf(a1, k1, -e1));
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 8 * q + 4 * h);
+            const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 8 * q + 4 * h);
+            const float kq = q < 2 ? k0 : k1;
+            w[4 * q] = __builtin_fmaf(sacc[4 * q], kq, -l4.x) - m4.x;
+            w[4 * q + 1] = __builtin_fmaf(sacc[4 * q + 1], kq, -l4.y) - m4.y;
+            w[4 * q + 2] = __builtin_fmaf(sacc[4 * q + 2], kq, -l4.z) - m4.z;
+            w[4 * q + 3] = __builtin_fmaf(sacc[4 * q + 3], kq, -l4.w) - m4.w;
+          }
+          float a0 = w[0], a1 = w[8];
+#pragma unroll
+          for (int v = 1; v < 8; ++v) { a0 = fmaxf(a0, w[v]); a1 = fmaxf(a1, w[8 + v]); }
+          tmax = fmaxf(a0 - e0, a1 - e1);
         }
-        const float nm2 = -LOG2E * mrun[b];
+        if (__any(tmax > mref + 15.f)) {
+          const float tall = fmaxf(tmax, __shfl_xor(tmax, 32));
+          const float mnew = fmaxf(mref, __builtin_ceilf(tall) - 8.f);
+          float alpha = __builtin_amdgcn_exp2f(mref - mnew);
+          asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
+          lrun *= alpha;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) w[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[k], LOG2E, nm2));
-        lrun[b] += ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
-      } else {
+          for (int cb = 0; cb < NO; ++cb) {
+            if (NK > 8) asm volatile("" : "+a"(oacc[cb]));
+            oacc[cb] *= alpha;
+            if (NK > 8) asm volatile("" : "+a"(oacc[cb]));   // wide rows: back to the accumulation registers, one block at a time
+          }
+          mref = mnew;
+        }
+        const float r0 = e0 + mref, r1 = e1 + mref;        // integers: exact
+        if (PASS == 1) {
+          float l0 = 0.f, l1 = 0.f;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) w[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[k], LOG2E, -lse8[k]));
+          for (int v = 0; v < 16; ++v) w[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[v], v < 8 ? k0 : k1, v < 8 ? -r0 : -r1));
+#pragma unroll
+          for (int v = 0; v < 8; ++v) { l0 += w[v]; l1 += w[8 + v]; }
+          lrun += F16 ? __builtin_ldexpf(l0, (int)e0) + __builtin_ldexpf(l1, (int)e1) : l0 + l1;
+        } else {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) w[v] = __builtin_amdgcn_exp2f(w[v] - (v < 8 ? r0 : r1));
+        }
+      } else {                                             // pass 2, bf16: no reference needed
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 8 * q + 4 * h);
+          w[4 * q] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q], LOG2E, -l4.x));
+          w[4 * q + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 1], LOG2E, -l4.y));
+          w[4 * q + 2] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 2], LOG2E, -l4.z));
+          w[4 * q + 3] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 3], LOG2E, -l4.w));
+        }
       }
-      split8(w, wh[b], wl[b]);
+      v8s wh[2], wl[2];
+      split8<F16, 0>(w, neg1, wh[0], wl[0]);
+      split8<F16, 8>(w, neg1, wh[1], wl[1]);
+      // -- O^T[c][x] += sum_y Y[y][c] W[y][x]: group q = (column block q / 2, step q % 2), read PG groups ahead
+      constexpr int NG = 2 * NO, PG = SP_PG < NG ? SP_PG : NG;
+      v8s gh[PG], gl[PG];
+      auto read_group = [&](int q, v8s& vh, v8s& vl) {
+        const int o = trofs + (q % 2) * 16 * PA + (q / 2) * 64;
+        vh = join8(lds_read_tr(hi + o), lds_read_tr(hi + o + 8 * PA));
+        vl = join8(lds_read_tr(lo + o), lds_read_tr(lo + o + 8 * PA));
+      };
+#pragma unroll
+      for (int q = 0; q < PG; ++q) read_group(q, gh[q], gl[q]);
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        const v8s ah = gh[q % PG], al = gl[q % PG];
+        if (q + PG < NG) read_group(q + PG, gh[q % PG], gl[q % PG]);
+        oacc[q / 2] = mfma32<F16>(al, wh[q % 2], oacc[q / 2]);
+        oacc[q / 2] = mfma32<F16>(ah, wl[q % 2], oacc[q / 2]);
+        oacc[q / 2] = mfma32<F16>(ah, wh[q % 2], oacc[q / 2]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    // -- O^T[c][x] += sum_y Y[y][c] W[y][x]
-    second_product<NCBA, XB, PA>(hi, lo, trofs, cb0, ncb, wh, wl, oacc);
     if (has_next) {
       dma_land(t + 1, buf ^ 1);
       __syncthreads();                                     // tile t + 1 is in LDS; every wave is done with tile t
@@ -373,42 +475,46 @@ k_split(FlashArgs a) {
   }
 
   // ---- epilogue
+  if (PASS == 3) {
+    for (int i = 0; i < npend; ++i) {
+      const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + pend[256 * i]];
+      const float* yrow = a.table + (size_t)id * a.dim;
+      const float s = a.dim % 4 == 0 ? sp_exact_score<true>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false>(qrow, yrow, a.dim, sp_chain(dk));
+      cnt += s > posx ? 1 : 0;
+    }
+    cnt += __shfl_xor(cnt, 32);
+    if (h == 0 && xv && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x, cnt);
+    return;
+  }
+  int oshift = 0;                                          // gradient rows are written as accumulator x 2^oshift
+  float* orow;
   if (PASS == 1) {                                         // the part's statistics and unnormalised gradient rows
-    float* ml_out = a.ml + ((size_t)part * 2 * a.B + x_base) * 2;
-    float* o_out = a.out + ((size_t)part * 2 * a.B + x_base) * dk;
-    if (slot >= a.whole_slots && part > 0) {
-      const size_t xr = (size_t)(part - 1) * a.rem_rows + (size_t)(cs - a.rem_cs0) * a.trows;
-      ml_out = a.mlx + xr * 2;
-      o_out = a.outx + xr * dk;
-    } else if (slot >= a.whole_slots) {
-      ml_out = a.ml + x_base * 2;
-      o_out = a.out + x_base * dk;
-    }
-#pragma unroll
-    for (int b = 0; b < XB; ++b) {
-      float ltot = lrun[b] + __shfl_xor(lrun[b], 16);
-      ltot += __shfl_xor(ltot, 32);
-      if (!xv[b]) continue;
-      if (g == 0 && half == 0) *reinterpret_cast<float2*>(ml_out + (size_t)x[b] * 2) = make_float2(mrun[b], ltot);
-      float* orow = o_out + (size_t)x[b] * dk;
-#pragma unroll
-      for (int cb = 0; cb < NCBA; ++cb) {
-        const int col = 16 * (cb0 + cb) + 4 * g;
-        if (cb < ncb && col < dk) *reinterpret_cast<float4*>(orow + col) = make_float4(oacc[b][cb][0], oacc[b][cb][1], oacc[b][cb][2], oacc[b][cb][3]);
-      }
-    }
+    float ltot = lrun + __shfl_xor(lrun, 32);
+    // sum = mantissa 2^p, reference + p: the statistics' reference is close to the log-sum-exp itself
+    int p = 0;
+    if (F16 && ltot > 0.f && ltot < 3.0e38f) p = (int)((__float_as_uint(ltot) >> 23) & 255u) - 127;
+    oshift = -p;
+    const size_t part_row = (size_t)u.part * 2 * a.B + q_base + x;
+    const bool extra = u.rem && u.part > 0;                // parts 1.. of a split stripe
+    const size_t xr = (size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + m;
+    float* ml_out = extra ? a.mlx + xr * 2 : a.ml + (u.rem ? q_base + x : part_row) * 2;
+    orow = extra ? a.outx + xr * dk : a.out + (u.rem ? q_base + x : part_row) * dk;
+    if (h == 0 && xv) *reinterpret_cast<float2*>(ml_out) = make_float2(mref + (float)p, __builtin_ldexpf(ltot, -p));
   } else {                                                 // gradient row of part `part` of each negative's occurrence
+    if (F16) oshift = mref > -1.0e38f ? (int)mref : 0;     // weights were formed relative to the reference
+    orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x) * a.sy + (u.rem ? 0 : u.part)) * dk;
+    if (u.rem && u.part > 0) orow = a.outx + ((size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + m) * dk;
+  }
+  if (xv) {
 #pragma unroll
-    for (int b = 0; b < XB; ++b) {
-      if (!xv[b]) continue;
-      float* orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x[b]) * a.sy +
-                             (slot >= a.whole_slots ? 0 : part)) * dk;
-      if (slot >= a.whole_slots && part > 0)               // parts 1.. of a split stripe: added to the regular row afterwards
-        orow = a.outx + ((size_t)(part - 1) * a.rem_rows + (size_t)(csl - a.rem_cs0) * (a.nstripes * SR) + x[b]) * dk;
+    for (int cb = 0; cb < NO; ++cb) {
 #pragma unroll
-      for (int cb = 0; cb < NCBA; ++cb) {
-        const int col = 16 * (cb0 + cb) + 4 * g;
-        if (cb < ncb && col < dk) *reinterpret_cast<float4*>(orow + col) = make_float4(oacc[b][cb][0], oacc[b][cb][1], oacc[b][cb][2], oacc[b][cb][3]);
+      for (int q = 0; q < 4; ++q) {
+        const int col = 32 * cb + 8 * q + 4 * h;
+        if (col < dk)
+          *reinterpret_cast<float4*>(orow + col) =
+              make_float4(__builtin_ldexpf(oacc[cb][4 * q], oshift), __builtin_ldexpf(oacc[cb][4 * q + 1], oshift),
+                          __builtin_ldexpf(oacc[cb][4 * q + 2], oshift), __builtin_ldexpf(oacc[cb][4 * q + 3], oshift));
       }
     }
   }
@@ -416,13 +522,13 @@ k_split(FlashArgs a) {
 
 // Adds parts 1.. of pass 2's split stripes to the gradient rows that part 0 wrote, in the parts' order.  One group of
 // 32 lanes per row.
-__global__ void __launch_bounds__(256) k_split_merge2(FlashArgs a, int stripe_rows) {
+__global__ void __launch_bounds__(256) k_split_merge2(FlashArgs a) {
   const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
   const long rrow = (long)blockIdx.x * 8 + grp;
   if (rrow >= a.rem_rows) return;
-  const int pitch = a.nstripes * stripe_rows;
-  const int cs = 2 * a.nchunks - 1 - (a.rem_cs0 + (int)(rrow / pitch)), x = (int)(rrow % pitch);
-  if (cs < 0 || x >= a.N) return;
+  const int unit = a.whole_units + (int)(rrow / SP_SR);
+  const int cs = unit / a.nstripes, x = (unit % a.nstripes) * SP_SR + (int)(rrow % SP_SR);
+  if (x >= a.N) return;
   const int side = cs & 1, c = cs >> 1;
   float* o0 = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x)) * a.dk;
   for (int k = 4 * l; k < a.dk; k += 128) {
@@ -436,65 +542,55 @@ __global__ void __launch_bounds__(256) k_split_merge2(FlashArgs a, int stripe_ro
 }
 
 // ------------------------------------------------------------------- launchers -----
-// Form of the widest instantiation (d > 256): row blocks per wave and waves per workgroup (two waves share a block).
-#ifndef SP_WIDE_XB
-#define SP_WIDE_XB 1
-#endif
-#ifndef SP_WIDE_NW
-#define SP_WIDE_NW 8
-#endif
 int mar_split_supported(int dk) { return dk >= 4 && dk <= 400; }
-int mar_split_stripe_rows(int dk, int pass) { (void)pass; return sp_ns(dk) <= 4 ? 128 : 64; }
-int mar_split_tile_rows() { return SP_TY; }
-int mar_split_wgs_per_cu(int dk, int pass) { (void)pass; return sp_ns(dk) <= 8 ? 2 : 1; }
-size_t mar_split_image_bytes(int dk) { return (size_t)sp_image(sp_ns(dk)); }
+int mar_split_wgs_per_cu(int dk) { return sp_nk(dk) <= 8 ? 2 : 1; }
+size_t mar_split_image_bytes(int dk) { return (size_t)sp_image(sp_nk(dk)); }
 
-// LDS of a launch: two image buffers, the log-sum-exp of a tile's edges (pass 2), the exchange area (CSP = 2)
-template <int NS, int XB, int CSP, int NW>
-constexpr size_t sp_lds() { return SplitGeom<NS>::LDS_BYTES + 2 * SP_TY * 4 + (CSP == 2 ? NW * 8 * XB * 64 * 4 : 0); }
-
-template <int NS, int NCB, int XB, int CSP, int NW>
-static hipError_t sp_prepare() {
-  constexpr size_t lds = sp_lds<NS, XB, CSP, NW>();
+template <int NK> static hipError_t sp_prepare() {
+  constexpr size_t lds = SplitGeom<NK>::LDS_BYTES;
   hipError_t e = hipSuccess;
-  if (lds > 64 * 1024) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NS, NCB, XB, 1, CSP, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NS, NCB, XB, 2, CSP, NW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  }
+#define PREP(P, F) if (lds > 64 * 1024 && e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(P == 3 ? SplitGeom<NK>::LDS_BYTES3 : lds))
+  PREP(1, true); PREP(2, true); PREP(3, true); PREP(1, false); PREP(2, false);
+#undef PREP
   return e;
 }
 hipError_t mar_split_prepare() {
-  hipError_t e = sp_prepare<8, 13, 1, 1, 4>();
-  if (e == hipSuccess) e = sp_prepare<8, 16, 1, 1, 4>();
-  if (e == hipSuccess) e = sp_prepare<13, 25, SP_WIDE_XB, 2, SP_WIDE_NW>();
+  hipError_t e = sp_prepare<12>();
+  if (e == hipSuccess) e = sp_prepare<16>();
+  if (e == hipSuccess) e = sp_prepare<25>();
   return e;
 }
 
-template <int NS, int NCB, int XB, int CSP, int NW>
-static hipError_t sp_launch(const FlashArgs& a, int pass, dim3 grid, hipStream_t st) {
-  constexpr size_t lds = sp_lds<NS, XB, CSP, NW>();
-  if (pass == 1) hipLaunchKernelGGL((k_split<NS, NCB, XB, 1, CSP, NW>), grid, dim3(64 * NW), lds, st, a);
-  else hipLaunchKernelGGL((k_split<NS, NCB, XB, 2, CSP, NW>), grid, dim3(64 * NW), lds, st, a);
+template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st) {
+  constexpr size_t lds = SplitGeom<NK>::LDS_BYTES;
+  static_assert(SplitGeom<NK>::LDS_BYTES3 <= 160 * 1024, "two images in LDS");
+  if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
+  else if (pass == 1) {
+    if (f16) hipLaunchKernelGGL((k_split<NK, 1, true>), grid, dim3(256), lds, st, a);
+    else hipLaunchKernelGGL((k_split<NK, 1, false>), grid, dim3(256), lds, st, a);
+  } else {
+    if (f16) hipLaunchKernelGGL((k_split<NK, 2, true>), grid, dim3(256), lds, st, a);
+    else hipLaunchKernelGGL((k_split<NK, 2, false>), grid, dim3(256), lds, st, a);
+  }
   return hipGetLastError();
 }
 
 // `a` is filled by mar_launch_flash (units, parts, buffers); this picks the instantiation for a.dk.
-static hipError_t sp_launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStream_t st);
-
-hipError_t mar_split_launch(const FlashArgs& a, int pass, dim3 grid, hipStream_t st) {
-  hipError_t e = sp_launch_sized(a, pass, grid, st);
+hipError_t mar_split_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st) {
+  hipError_t e = hipErrorInvalidValue;
+  switch (sp_nk(a.dk)) {
+    case 2: e = sp_launch<2>(a, pass, f16, grid, st); break;
+    case 4: e = sp_launch<4>(a, pass, f16, grid, st); break;
+    case 6: e = sp_launch<6>(a, pass, f16, grid, st); break;
+    case 7: e = sp_launch<7>(a, pass, f16, grid, st); break;
+    case 8: e = sp_launch<8>(a, pass, f16, grid, st); break;
+    case 12: e = sp_launch<12>(a, pass, f16, grid, st); break;
+    case 16: e = sp_launch<16>(a, pass, f16, grid, st); break;
+    case 25: e = sp_launch<25>(a, pass, f16, grid, st); break;
+  }
   if (e == hipSuccess && pass == 2 && a.rem_k > 1) {
-    hipLaunchKernelGGL(k_split_merge2, dim3((unsigned)((a.rem_rows + 7) / 8)), dim3(256), 0, st, a, mar_split_stripe_rows(a.dk, 2));
+    hipLaunchKernelGGL(k_split_merge2, dim3((unsigned)((a.rem_rows + 7) / 8)), dim3(256), 0, st, a);
     e = hipGetLastError();
   }
   return e;
-}
-
-static hipError_t sp_launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStream_t st) {
-  const int ns = sp_ns(a.dk), ncb = sp_ncb(a.dk);
-  if (ns == 2) return sp_launch<2, 4, 2, 1, 4>(a, pass, grid, st);
-  if (ns == 4) return ncb == 7 ? sp_launch<4, 7, 2, 1, 4>(a, pass, grid, st) : sp_launch<4, 8, 2, 1, 4>(a, pass, grid, st);
-  if (ns == 8) return ncb == 13 ? sp_launch<8, 13, 1, 1, 4>(a, pass, grid, st) : sp_launch<8, 16, 1, 1, 4>(a, pass, grid, st);
-  return sp_launch<13, 25, SP_WIDE_XB, 2, SP_WIDE_NW>(a, pass, grid, st);
 }

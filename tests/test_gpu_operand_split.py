@@ -1,0 +1,76 @@
+"""The fp32 contraction on f16 hi + lo operands with block exponents: the edges of its instantiations, tiles and stripes,
+rows of very different size in one block, and evaluation's close comparisons."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_08358_amd as mar
+
+from parity_util import run_step_both, check_step
+
+pytestmark = pytest.mark.gpu
+
+DISTMULT, COMPLEX, DOT = 0, 1, 3
+
+
+@pytest.mark.parametrize("dim", (30, 32, 33, 64, 65, 96, 97, 112, 113, 129, 192, 193, 257))
+def test_width_at_the_edges_of_the_instantiations(dim):
+    print("case", dim, flush=True)
+    print(check_step(run_step_both(DISTMULT, 3000, 5, dim, 260, 2, 100, 260, seed=dim, std=0.3)), flush=True)
+
+
+@pytest.mark.parametrize("model,S,N", ((DOT, 31, 33), (DISTMULT, 32, 32), (COMPLEX, 127, 129), (DISTMULT, 129, 31), (DOT, 1, 1), (COMPLEX, 257, 385)))
+def test_chunk_and_candidate_counts_at_tile_and_stripe_edges(model, S, N):
+    print("case", model, S, N, flush=True)
+    for n in (3 * S, 2 * S + 1):
+        print(check_step(run_step_both(model, 4000, 3, 52, 3 * S, 3, N, n, seed=S + N, std=0.2)), flush=True)
+
+
+def test_rows_of_different_size_in_one_block():
+    """Rows 2^-12 .. 1 of the largest in every 16-row block: each keeps its bits (a block's values hold 23 bits down to
+    2^-17 of its largest), so the usual bars hold for every row of the gradient."""
+    V, R, dim, B, C, N = 2000, 3, 100, 512, 2, 256
+    rng = np.random.default_rng(5)
+    size = np.exp2(-rng.integers(0, 13, V)).astype(np.float32)
+    ne = (rng.standard_normal((V, dim)) * 0.3).astype(np.float32) * size[:, None]
+    out = run_step_both(DOT, V, R, dim, B, C, N, B, seed=9, tables=(ne, np.zeros((R, dim), np.float32)))
+    print(check_step(out), flush=True)
+
+
+def _chain(q, y):
+    """fp32 dot product as a chain of fused multiply-adds in the order of the fp32 matrix instructions (products are exact
+    in float64, every step is rounded to float32)."""
+    d = q.shape[-1]
+    chain = 48 if d <= 52 else (96 if d <= 100 else 400)
+    order = [16 * b + 4 * g + i for b in range((min(chain, d) + 15) // 16) for i in range(4) for g in range(4)]
+    s = np.zeros(np.broadcast_shapes(q.shape[:-1], y.shape[:-1]), np.float32)
+    for k in [k for k in order if k < d] + list(range(chain, d)):
+        s = (q[..., k].astype(np.float64) * y[..., k] + s).astype(np.float32)
+    return s
+
+
+@pytest.mark.parametrize("dim", (17, 52, 56, 100, 128, 400))
+@pytest.mark.parametrize("special", (False, True))
+def test_ranks_are_those_of_the_fp32_chain(dim, special):
+    """Every node is a candidate, so each edge meets its own endpoint, whose score differs from the positive's by rounding
+    only; with `special` the table holds infinities, a NaN, a huge and a zero row."""
+    V, S, C = 333, 70, 2
+    rng = np.random.default_rng(dim)
+    ne = (rng.standard_normal((V, dim)) * 0.3).astype(np.float32)
+    if special:
+        ne[3, 0], ne[5, dim // 2], ne[7, 1], ne[11] = np.inf, np.nan, -np.inf, 0.0
+        ne[9] *= np.float32(1e12)
+    src, dst = rng.integers(16, V, S * C).astype(np.int32), rng.integers(16, V, S * C).astype(np.int32)
+    tr = mar.Trainer(V, 1, dim, DOT, S * C, C, V, device="cuda:0", node_emb=ne, rel_emb=np.zeros((1, dim), np.float32))
+    every = torch.arange(V, dtype=torch.int32, device=tr.device).repeat(C)
+    pos = torch.zeros(S * C, device=tr.device)
+    ranks = torch.zeros(2 * S * C, dtype=torch.int32, device=tr.device)
+    d_src, d_dst = torch.from_numpy(src).to(tr.device), torch.from_numpy(dst).to(tr.device)
+    mar.mar_eval_scores(tr.ctx, d_src, d_src, d_dst, S * C, every, every, pos, ranks[:S * C], ranks[S * C:])
+    torch.cuda.synchronize()
+    p, r = pos.cpu().numpy(), ranks.cpu().numpy()
+    tr.close()
+    with np.errstate(all="ignore"):
+        for got, q in ((r[:S * C], ne[src]), (r[S * C:], ne[dst])):
+            want = 1 + (_chain(q[:, None, :], ne[None, :, :]) > p[:, None]).sum(1)
+            assert np.array_equal(got, want), (dim, special, int((got != want).sum()))
