@@ -130,8 +130,6 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   d->n_occ_max = n_occ;
   const int64_t ids = cfg->num_nodes + cfg->num_rels;
   d->u_max = ids < n_occ ? ids : n_occ;
-  d->ipw_log2 = ids <= ((int64_t)1 << 22) ? 2 : 5;       // small id spaces: one byte per id, no atomics
-  d->nwords = (ids + (1 << d->ipw_log2) - 1) >> d->ipw_log2;
   if (!mar_flash_supported(d->dk)) return fail(MAR_ERANGE, "row width %d not supported by the contraction kernels", d->dk);
   d->bilinear = cfg->model != MAR_MODEL_TRANSE;
   d->split_bf16 = cfg->precision == MAR_PRECISION_SPLIT_BF16;
@@ -153,11 +151,13 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   plan_rem(*d, 1, units1, d->N, d->sy1, sr1, &d->rem1);
   plan_rem(*d, 2, units2, d->S, d->sy2, sr2, &d->rem2);
   d->n_pos_max = roles * (int64_t)cfg->batch_size + 2 * cn * d->sy2;
-  // Sort keys are ranks below u_max: as few passes as digits of at most MAR_SORT_MAX_BITS bits allow.
+  // Sort keys are unified ids: as few passes as digits of at most MAR_SORT_MAX_BITS bits allow.
   int nbits = 1;
-  while (((int64_t)1 << nbits) < d->u_max) ++nbits;
+  while (((int64_t)1 << nbits) < ids) ++nbits;
   d->sort_passes = (nbits + MAR_SORT_MAX_BITS - 1) / MAR_SORT_MAX_BITS;
   d->sort_bits = (nbits + d->sort_passes - 1) / d->sort_passes;
+  // Every tile of a pass reads the counts of all tiles: small tiles while that is at most 128 KB.
+  d->sort_items = ((d->n_pos_max + 1023) / 1024) << d->sort_bits <= 32768 ? 4 : 16;
   // score pairs x row width per step: above ~2e9 the contraction passes are long enough to hide the index build
   d->index_after_gather = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 2.0e9;
   return MAR_OK;
@@ -173,23 +173,19 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   };
   const size_t n_pos = (size_t)d.n_pos_max, u1 = (size_t)d.u_max + 1;
   const size_t B = d.B, CN = (size_t)d.C * d.N, dk = d.dk;
-  const size_t scan_elems = (size_t)d.nwords > u1 ? (size_t)d.nwords : u1;
   const size_t blocks = (n_pos + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
-  const size_t tiles = (n_pos + MAR_SORT_TILE - 1) / MAR_SORT_TILE;
+  const size_t tiles = ((n_pos + 256 * d.sort_items - 1) / (256 * d.sort_items) + 3) & ~(size_t)3, rank_tiles = n_pos / MAR_RANK_TILE + 1;
   MarLayout l;
   l.scalars = (int32_t*)take(16 * 4);
-  l.bitmap = (uint32_t*)take((size_t)d.nwords * 4);
-  l.word_prefix = (uint32_t*)take((size_t)d.nwords * 4);
-  l.bsum = (uint32_t*)take((scan_elems / 4096 + 2) * 4);
   l.uniq = (int32_t*)take(u1 * 4);
-  l.seg_off = (uint32_t*)take((u1 + 1) * 4);
   l.keys0 = (uint32_t*)take(n_pos * 4);
   for (int i = 0; i < 2; ++i) {
     l.kbuf[i] = (uint32_t*)take(d.sort_passes > i + 1 ? n_pos * 4 : 0);
     l.vbuf[i] = (int32_t*)take(d.sort_passes > i + 1 ? n_pos * 4 : 0);
   }
-  l.hist = (uint32_t*)take((tiles << d.sort_bits) * 4);
+  l.hist = (uint32_t*)take(((tiles << d.sort_bits) > rank_tiles ? (tiles << d.sort_bits) : rank_tiles) * 4);
   l.perm = (int32_t*)take(n_pos * 4);
+  l.ids_sorted = (uint32_t*)take(n_pos * 4);
   l.rank_sorted = (int32_t*)take(n_pos * 4);
   l.owners = (int32_t*)take(blocks * 4);
   // TransE: dense operands and stored weights; bilinear models: operand images, no weights (pass 2 computes the scores again)
@@ -254,7 +250,7 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
   c->node_emb = node_emb; c->node_state = node_state; c->rel_emb = rel_emb; c->rel_state = rel_state;
   c->workspace = workspace; c->workspace_bytes = workspace_bytes;
   carve(d, (char*)workspace, &c->L);
-  c->bitmap_dirty = 0; c->prof_max = 0; c->prof_steps = 0; c->prof_mask = 0; c->prof_events = nullptr;
+  c->prof_max = 0; c->prof_steps = 0; c->prof_mask = 0; c->prof_events = nullptr;
   c->aux = nullptr; c->ev_fork = c->ev_index = c->ev_pass1 = c->ev_chain = nullptr;
   hipError_t e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
   hipEvent_t* evs[4] = {&c->ev_fork, &c->ev_index, &c->ev_pass1, &c->ev_chain};
@@ -306,7 +302,7 @@ static int make_batch(const mar_ctx* c, const int32_t* src, const int32_t* rel, 
   return MAR_OK;
 }
 
-#define HIP_TRY(expr, what) do { const hipError_t e_ = (expr); if (e_ != hipSuccess) { c->bitmap_dirty = 1; return hip_fail(e_, what); } } while (0)
+#define HIP_TRY(expr, what) do { const hipError_t e_ = (expr); if (e_ != hipSuccess) return hip_fail(e_, what); } while (0)
 
 extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* rel, const int32_t* dst, int32_t n_edges,
                                const int32_t* neg_src, const int32_t* neg_dst, float* loss_sum_out,
@@ -319,10 +315,6 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
     if (loss_sum_out) HIP_TRY(mar_launch_fill_u32((uint32_t*)loss_sum_out, 1, 0u, st), "loss reset");
     if (dbg && dbg->num_uniq) HIP_TRY(mar_launch_fill_u32((uint32_t*)dbg->num_uniq, 2, 0u, st), "debug reset");
     return MAR_OK;
-  }
-  if (c->bitmap_dirty) {
-    HIP_TRY(mar_launch_clear_bitmap(c, st), "bitmap reset");
-    c->bitmap_dirty = 0;
   }
   // Two streams: the caller's carries the gather and the two contraction passes; the index build
   // (needed only by the per-row reduce) and the chain rule (needs pass 1 only) run beside them on `aux`.
@@ -341,7 +333,8 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   HIP_TRY(hipEventRecord(c->ev_fork, st), "fork");
   HIP_TRY(hipStreamWaitEvent(ax, c->ev_fork, 0), "fork");
   MARK(0, 0, ax);
-  HIP_TRY(mar_launch_index(c, b, ax), "index kernels");
+  const int ranks = dbg && (dbg->num_uniq || dbg->uniq_nodes || dbg->uniq_rels || dbg->grad_rows);
+  HIP_TRY(mar_launch_index(c, b, ranks, ax), "index kernels");
   if (dbg) HIP_TRY(mar_launch_debug_copy(c, b, dbg, ax), "debug copy");
   MARK(0, 1, ax);
   HIP_TRY(hipEventRecord(c->ev_index, ax), "join");
@@ -608,8 +601,7 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
   ps.b_ids.src = ps.src; ps.b_ids.rel = ps.rel; ps.b_ids.dst = ps.dst; ps.b_ids.neg_src = ps.neg_src; ps.b_ids.neg_dst = ps.neg_dst;
   ps.b_rank = ps.b_ids;
   ps.b_rank.src = ps.sg.c_src; ps.b_rank.dst = ps.sg.c_dst; ps.b_rank.neg_src = ps.sg.c_neg_src; ps.b_rank.neg_dst = ps.sg.c_neg_dst;
-  if (c->bitmap_dirty) { PIPE_TRY(mar_launch_clear_bitmap(c, p->s_in), "bitmap reset"); c->bitmap_dirty = 0; }
-  PIPE_TRY(mar_launch_index(c, ps.b_ids, p->s_in), "index kernels");
+  PIPE_TRY(mar_launch_index(c, ps.b_ids, 1, p->s_in), "index kernels");
   PIPE_TRY(mar_launch_stage_in(c, ps.b_ids, ps.sg, p->s_in), "staging kernels");
   PIPE_TRY(hipEventRecord(ps.ev_in, p->s_in), "stage in");
   // ---- step on the caller's stream: staged rows, ranks as ids; node gradients are left in gsum, relation rows updated

@@ -13,18 +13,14 @@
 // Workspace carve-up (device pointers).
 struct MarLayout {
   int32_t*  scalars;      // [16]: 0 = unique rows (nodes + relations), 1 = unique nodes, 2 = number of entries in `owners`
-  uint32_t* bitmap;       // touched-id map over unified ids (node id, or num_nodes + relation id): one bit or
-                          // one byte per id, see ipw_log2
-  uint32_t* word_prefix;  // marked ids before each word of the map
-  uint32_t* bsum;         // scan scratch (block sums)
   int32_t*  uniq;         // ascending unified ids of the touched rows
-  uint32_t* seg_off;      // [unique rows + 1] first position of each row's segment in the row-sorted order
-  uint32_t* keys0;        // [n_pos] gradient row -> rank of its table row among the unique rows (sort keys)
+  uint32_t* keys0;        // [n_pos] gradient row -> unified id of its table row (sort keys); -> its rank, once ranks have been formed
   uint32_t* kbuf[2];      // [n_pos] each: keys between two passes of the radix sort
   int32_t*  vbuf[2];      // [n_pos] each: gradient row numbers between two passes
-  uint32_t* hist;         // [sort tiles][bins] digit counts of the current pass
+  uint32_t* hist;         // [bins][sort tiles] digit counts of the current pass; heads per tile of the rank kernels
   int32_t*  perm;         // position in row-sorted order -> gradient row
-  int32_t*  rank_sorted;  // position -> rank
+  uint32_t* ids_sorted;   // position -> unified id (node id, or num_nodes + relation id)
+  int32_t*  rank_sorted;  // position -> rank among the unique rows (where a caller asks for ranks)
   int32_t*  owners;       // [reduce blocks] workgroups of the reduce in which a segment begins that continues into later ones
   float*    Q;            // TransE: [2][batch][dk] edge-side operands (side-major)
   float*    Km;           // TransE: [2][chunks][N][dk] gathered negative rows
@@ -70,9 +66,7 @@ struct MarDims {
   int32_t tps1, tps2;              // streamed tiles per workgroup
   MarRem rem1, rem2;               // split stripes of pass 1; of pass 2 (bilinear models): parts 1.. are added by a small kernel
   int64_t u_max;                   // min(num_nodes + num_rels, n_occ_max)
-  int64_t nwords;                  // words of the touched-id map
-  int32_t ipw_log2;                // ids per word: 5 = one bit per id (atomic marks), 2 = one byte per id (plain stores)
-  int32_t sort_passes, sort_bits;  // radix sort of the gradient rows by rank: passes, bits per pass
+  int32_t sort_passes, sort_bits, sort_items;  // radix sort of the gradient rows by unified id: passes, bits per pass, elements per thread
   int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
@@ -88,7 +82,6 @@ struct mar_ctx {
   float *node_emb, *node_state, *rel_emb, *rel_state;
   void* workspace; size_t workspace_bytes;
   MarLayout L;
-  int bitmap_dirty;                // a failed step may leave bits set
   // second stream for work that is independent of the contraction passes, and its fork/join events
   hipStream_t aux;
   hipEvent_t ev_fork, ev_index, ev_pass1, ev_chain;
@@ -100,9 +93,9 @@ struct mar_ctx {
 
 void mar_set_error(const char* fmt, ...);
 
-// Radix sort of the gradient rows: elements per workgroup tile and the widest digit.
-#define MAR_SORT_TILE 4096
-#define MAR_SORT_MAX_BITS 10
+// Radix sort of the gradient rows by unified id: the widest digit.
+#define MAR_SORT_MAX_BITS 9
+#define MAR_RANK_TILE 1024        // positions per workgroup of the rank kernels
 
 // Rank metrics: ranks per partial record, records a scratch area holds, bytes per record.
 #define MAR_METRIC_TILE 4096
@@ -119,7 +112,6 @@ static inline int mar_lane_group(int dk) { return dk <= 64 ? 16 : (dk <= 128 ? 3
 hipError_t mar_launch_init(const mar_ctx* c, int fill, hipStream_t st);
 hipError_t mar_launch_sample(const mar_ctx* c, uint64_t step, const int32_t* es, const int32_t* ed,
                              int64_t num_edges, int32_t* neg_src, int32_t* neg_dst, hipStream_t st);
-hipError_t mar_launch_clear_bitmap(const mar_ctx* c, hipStream_t st);
 hipError_t mar_launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 
 struct MarBatch {
@@ -131,7 +123,8 @@ struct MarBatch {
   int64_t n_pos;    // roles*n + 2cn*sy2 gradient rows
 };
 
-hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, hipStream_t st);
+// ranks != 0: also the rows' ranks, the unique list and the counts in scalars
+hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, int ranks, hipStream_t st);
 // bf16 != 0 (SPLIT_BF16 training): the operand images hold bf16 instead of scaled f16 parts
 // rank_dst / rank_src (evaluation): set to 1
 hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,

@@ -660,10 +660,9 @@ struct ReduceArgs {
   float *node_emb, *node_state, *rel_emb, *rel_state;
   const float* G;            // [n_rows][dk] gradient rows
   float* carry;              // [blocks][2][dk] partial sums of segments that cross block borders
-  const int32_t* rank_sorted;
-  const int32_t* perm;       // position in row-sorted order -> gradient row
-  const uint32_t* seg_off;
-  const int32_t* uniq;
+  const uint32_t* ids;       // position in row-sorted order -> unified id
+  const int32_t* perm;       // position -> gradient row
+  const int32_t* rank_sorted;   // position -> rank among the unique rows; only with dbg_grad or defer_grad, else NULL
   int32_t* scalars;          // [2] = number of entries in `owners`
   int32_t* owners;           // blocks in which a segment begins that continues into later blocks
   float* dbg_grad;           // [unique rows][dim] summed gradients (debug output), or NULL
@@ -729,8 +728,9 @@ __device__ __forceinline__ void load_old4(const ReduceArgs& a, int32_t id, const
 }
 
 // A workgroup takes MAR_REDUCE_BLOCK consecutive positions, a group of GL lanes GL of them (a "task"; the
-// lanes of a group move one row as float4s, NV per lane).  Each lane first fetches the rank, gradient row,
-// segment bounds and table row id of one position of its task, so that no later load depends on another.
+// lanes of a group move one row as float4s, NV per lane).  Each lane first fetches the id and the gradient row of one
+// position of its task, and the group the ids on either side of it: equal neighbours are one segment, so the segments'
+// borders follow without further loads and no later load depends on another.
 // The task's rows are then fetched BATCH at a time -- together with the table row and accumulator row of
 // every position at which a segment ends that also began inside the task -- and added up in position
 // order; such a segment is finished by the Adagrad update right there.  A segment that crosses the task's
@@ -752,15 +752,24 @@ __global__ void __launch_bounds__(256) k_reduce_apply(ReduceArgs a) {
   const int64_t p1 = p0 + cnt;
   const int nq = a.dk >> 2;
 
-  int my_rank = 0, my_row = 0, my_id = 0, my_kind = 0;     // kind: 0 no segment end, 1 end of a segment inside the task,
-  int64_t my_lo = 0, my_hi = 0;                            //       2 end of a segment that began before the task
+  int my_rank = 0, my_row = 0, my_id = -1;
+  int id_before = -2, id_after = -2;                       // ids of the positions before and behind the task (-2: none)
   if (l < cnt) {
-    my_rank = a.rank_sorted[p0 + l];
+    my_id = (int)a.ids[p0 + l];
     my_row = a.perm[p0 + l];
-    my_lo = a.seg_off[my_rank];
-    my_hi = a.seg_off[my_rank + 1];
-    my_id = a.uniq[my_rank];
-    if (p0 + l == my_hi - 1) my_kind = my_lo >= p0 ? 1 : 2;
+    if (a.rank_sorted) my_rank = a.rank_sorted[p0 + l];
+    if (p0 > 0) id_before = (int)a.ids[p0 - 1];
+    if (p1 < a.n_rows) id_after = (int)a.ids[p1];
+  }
+  id_before = __shfl(id_before, 0, GL); id_after = __shfl(id_after, 0, GL);
+  const int id_first = __shfl(my_id, 0, GL), id_last = __shfl(my_id, cnt > 0 ? cnt - 1 : 0, GL);
+  const bool from_before = cnt > 0 && id_first == id_before;   // the first position's segment began before the task
+  const bool goes_on = cnt > 0 && id_last == id_after;         // the last position's segment continues behind it
+  int my_kind = 0;                                         // 0 no segment end, 1 end of a segment that began inside the task,
+  {                                                        // 2 end of a segment that began before it
+    const int right = __shfl_down(my_id, 1, GL);
+    const int next = l == cnt - 1 ? id_after : right;
+    if (l < cnt && next != my_id) my_kind = from_before && my_id == id_first ? 2 : 1;
   }
   float4 acc[NV];
 #pragma unroll
@@ -821,15 +830,11 @@ __global__ void __launch_bounds__(256) k_reduce_apply(ReduceArgs a) {
   }
   // what is left in acc belongs to the segment of the task's last position, if that segment continues
   int hs = 0, tf = 0;
-  if (cnt > 0) {
-    const int64_t lo_first = __shfl(my_lo, 0, GL), hi_first = __shfl(my_hi, 0, GL);
-    const int64_t lo_last = __shfl(my_lo, cnt - 1, GL), hi_last = __shfl(my_hi, cnt - 1, GL);
-    if (lo_first < p0) hs = hi_first <= p1 ? 1 : 2;
-    if (hi_last > p1) {
-      if (lo_last >= p0) tf = 1;
+  if (from_before) hs = (id_last == id_first && goes_on) ? 2 : 1;
+  if (goes_on) {
+    if (!(from_before && id_last == id_first)) tf = 1;
 #pragma unroll
-      for (int v = 0; v < NV; ++v) (tf ? s_tail : s_head)[grp][l + GL * v] = acc[v];
-    }
+    for (int v = 0; v < NV; ++v) (tf ? s_tail : s_head)[grp][l + GL * v] = acc[v];
   }
   if (l == 0) { s_hs[grp] = hs; s_tf[grp] = tf; s_fin[grp] = 0; }
   __syncthreads();
@@ -915,9 +920,18 @@ k_span_apply(ReduceArgs a, const float* __restrict__ loss_part, int n_loss_part,
   for (int o = blockIdx.x; o < n_owners; o += gridDim.x) {  // uniform over the workgroup
     const int64_t blk = a.owners[o];
     const int64_t pe = (blk + 1) * MAR_REDUCE_BLOCK < a.n_rows ? (blk + 1) * MAR_REDUCE_BLOCK : a.n_rows;
-    const int rank = a.rank_sorted[pe - 1];
-    const int64_t hi = a.seg_off[rank + 1];
-    const int64_t last_blk = (hi - 1) / MAR_REDUCE_BLOCK;
+    const uint32_t seg_id = a.ids[pe - 1];
+    const int rank = a.rank_sorted ? a.rank_sorted[pe - 1] : 0;
+    // the last block whose first position belongs to the segment: blocks blk + 1 .. last_blk do, 64 probes at a time
+    int64_t last_blk = blk, after = (a.n_rows + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
+    while (after - last_blk > 1) {
+      const int64_t stepb = (after - last_blk + 63) / 64, t = last_blk + (lane + 1) * stepb;
+      const bool in = t < after && a.ids[t * MAR_REDUCE_BLOCK] == seg_id;
+      const int k = __popcll(__ballot(in));                // ids ascend: the first k probes are in
+      const int64_t nxt = last_blk + (int64_t)(k + 1) * stepb;
+      last_blk += k * stepb;
+      if (nxt < after) after = nxt;
+    }
     float4 acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
@@ -950,7 +964,7 @@ k_span_apply(ReduceArgs a, const float* __restrict__ loss_part, int n_loss_part,
     __syncthreads();
     if (wave == 0) {
       float *emb, *st;
-      const int32_t fid = a.uniq[rank];
+      const int32_t fid = (int32_t)seg_id;
       table_rows(a, fid, emb, st);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -1168,7 +1182,7 @@ hipError_t mar_launch_reduce(const mar_ctx* c, const MarBatch& b, float* loss_ou
   const MarDims& d = c->dm;
   ReduceArgs a;
   a.node_emb = c->node_emb; a.node_state = c->node_state; a.rel_emb = c->rel_emb; a.rel_state = c->rel_state;
-  a.G = L.G; a.carry = L.carry; a.rank_sorted = L.rank_sorted; a.perm = L.perm; a.seg_off = L.seg_off; a.uniq = L.uniq;
+  a.G = L.G; a.carry = L.carry; a.ids = L.ids_sorted; a.perm = L.perm; a.rank_sorted = dbg_grad || defer_grad ? L.rank_sorted : nullptr;
   a.scalars = L.scalars; a.owners = L.owners; a.dbg_grad = dbg_grad; a.defer_grad = defer_grad; a.n_rows = b.n_pos;
   a.num_nodes = (int32_t)d.num_nodes; a.dim = d.dim; a.dk = d.dk; a.lr = c->cfg.lr; a.eps = c->cfg.eps;
   const int64_t blocks = (b.n_pos + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
