@@ -38,13 +38,14 @@ static int hip_fail(hipError_t e, const char* what) {
 #define MAR_FLASH_TARGET_WGS2 640
 #endif
 
-static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk) : mar_flash_wgs_per_cu(d.dk, pass); }
+static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass); }
 
 // Small batches give too few (chunk-side, stripe) units to fill 256 CUs: several workgroups share a unit, each
 // streaming a slice of the other matrix.  TransE: until a pass has at least MAR_FLASH_TARGET_WGS workgroups (measured
 // best for a 10,000-edge batch).  Bilinear models: as many parts as the least estimated time of the busiest CU asks
 // for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its first tile and its
-// rows; a CU that holds one of two possible workgroups runs it at about 0.6 of its full rate.
+// rows (pass 3, whose tiles are half the work and whose close comparisons are settled at the end: eight); a CU that holds
+// one of two possible workgroups runs it at about 0.6 of its full rate.
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps) {
   const int ty = mar_tile_rows(d, pass);
   const int ntiles = (n_y + ty - 1) / ty;
@@ -56,11 +57,11 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
     if (want > ntiles) want = ntiles;
   } else if (units < 256L * wgs_per_cu(d, pass) || pass == 3) {
     double best = 1e30;
-    const bool two = wgs_per_cu(d, pass) == 2;
+    const bool two = wgs_per_cu(d, pass) >= 2;
     const int most = pass == 3 ? 64 : MAR_MAX_PARTS;
     for (long k = 1; k <= most && k <= ntiles; ++k) {
       const long t = (ntiles + k - 1) / k, per_cu = (units * k + 255) / 256;
-      const double cost = (two && per_cu == 1 ? 1.6 : (double)per_cu) * (double)(t + 3);
+      const double cost = (two && per_cu == 1 ? 1.6 : (double)per_cu) * (double)(t + (pass == 3 ? 8 : 3));
       if (cost < best * 0.97) { best = cost; want = k; }
     }
   }

@@ -156,7 +156,7 @@ int mar_flash_wgs_per_cu(int dk, int pass);        // workgroups of a pass that 
 hipError_t mar_launch_flash_merge(const mar_ctx* c, const MarBatch& b, hipStream_t st);   // after pass 1: merges split stripes
 // Passes of the bilinear models (mar_split.hip): geometry for the planning of a configuration, and the launches.
 int mar_split_supported(int dk);
-int mar_split_wgs_per_cu(int dk);
+int mar_split_wgs_per_cu(int dk, int pass);
 #define MAR_SPLIT_STRIPE_ROWS 128
 #define MAR_SPLIT_TILE_ROWS 32
 static inline int mar_stripe_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }

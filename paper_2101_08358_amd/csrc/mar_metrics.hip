@@ -13,42 +13,54 @@ struct MetricKs { int32_t k[8]; int32_t num; };
 struct MetricPart { double rr; unsigned long long hit[8]; };
 static_assert(sizeof(MetricPart) == MAR_METRIC_PART_BYTES, "partial record size");
 
-// Workgroup b sums the ranks of tiles b, b + gridDim.x, ...: thread t takes elements t, t + 256, ... of a
-// tile, then the 256 threads' sums are combined by a binary tree in LDS.
-__global__ void __launch_bounds__(256)
-k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, MetricPart* __restrict__ part) {
+// Adds up 256 threads' sums by the binary tree x[t] += x[t + o], o = 128, 64, .., 1: the two steps that cross waves
+// through LDS, the rest between the lanes of wave 0.  Thread 0 is left with the totals.
+__device__ __forceinline__ void block_totals(double& rr, unsigned long long (&hit)[8], int num) {
   __shared__ double s_rr[256];
   __shared__ unsigned long long s_hit[8][256];
+  s_rr[threadIdx.x] = rr;
+  for (int q = 0; q < num; ++q) s_hit[q][threadIdx.x] = hit[q];
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int t = threadIdx.x;
+  rr = (s_rr[t] + s_rr[t + 128]) + (s_rr[t + 64] + s_rr[t + 192]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) rr += __shfl_down(rr, o);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    if (q < num) {
+      hit[q] = s_hit[q][t] + s_hit[q][t + 64] + s_hit[q][t + 128] + s_hit[q][t + 192];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) hit[q] += __shfl_down(hit[q], o);
+    }
+  }
+}
+
+// Workgroup b sums the ranks of tiles b, b + gridDim.x, ...: thread t takes elements t, t + 256, ... of a
+// tile (all of a tile's loads in flight), then the 256 threads' sums are combined by a binary tree.
+__global__ void __launch_bounds__(256)
+k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, MetricPart* __restrict__ part) {
+  constexpr int PER = MAR_METRIC_TILE / 256;
   double rr = 0.0;
   unsigned long long hit[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int64_t t0 = (int64_t)blockIdx.x * MAR_METRIC_TILE; t0 < n; t0 += (int64_t)gridDim.x * MAR_METRIC_TILE) {
-#pragma unroll 4
-    for (int j = 0; j < MAR_METRIC_TILE / 256; ++j) {
-      const int64_t i = t0 + j * 256 + threadIdx.x;
-      if (i < n) {
-        const int r = ranks[i];
-        rr += 1.0 / (double)r;
+    int r[PER];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) if (q < ks.num && r <= ks.k[q]) hit[q]++;
+    for (int j = 0; j < PER; ++j) { const int64_t i = t0 + j * 256 + threadIdx.x; r[j] = ranks[i < n ? i : n - 1]; }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (t0 + j * 256 + threadIdx.x < n) {
+        rr += 1.0 / (double)r[j];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) if (q < ks.num && r[j] <= ks.k[q]) hit[q]++;
       }
     }
   }
-  s_rr[threadIdx.x] = rr;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) s_hit[q][threadIdx.x] = hit[q];
-  __syncthreads();
-  for (int o = 128; o >= 1; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      s_rr[threadIdx.x] += s_rr[threadIdx.x + o];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s_hit[q][threadIdx.x] += s_hit[q][threadIdx.x + o];
-    }
-    __syncthreads();
-  }
+  block_totals(rr, hit, ks.num);
   if (threadIdx.x == 0) {
     MetricPart p;
-    p.rr = s_rr[0];
-    for (int q = 0; q < 8; ++q) p.hit[q] = s_hit[q][0];
+    p.rr = rr;
+    for (int q = 0; q < 8; ++q) p.hit[q] = hit[q];
     part[blockIdx.x] = p;
   }
 }
@@ -56,8 +68,6 @@ k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, Metric
 // One workgroup: thread t adds records t, t + 256, ..., then the same tree; writes MRR and Hits@k.
 __global__ void __launch_bounds__(256)
 k_rank_final(const MetricPart* __restrict__ part, int nparts, int64_t n, MetricKs ks, double* __restrict__ out) {
-  __shared__ double s_rr[256];
-  __shared__ unsigned long long s_hit[8][256];
   double rr = 0.0;
   unsigned long long hit[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int i = threadIdx.x; i < nparts; i += 256) {
@@ -66,21 +76,11 @@ k_rank_final(const MetricPart* __restrict__ part, int nparts, int64_t n, MetricK
 #pragma unroll
     for (int q = 0; q < 8; ++q) hit[q] += p.hit[q];
   }
-  s_rr[threadIdx.x] = rr;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) s_hit[q][threadIdx.x] = hit[q];
-  __syncthreads();
-  for (int o = 128; o >= 1; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      s_rr[threadIdx.x] += s_rr[threadIdx.x + o];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s_hit[q][threadIdx.x] += s_hit[q][threadIdx.x + o];
-    }
-    __syncthreads();
-  }
+  block_totals(rr, hit, ks.num);
   if (threadIdx.x == 0) {
-    out[0] = n > 0 ? s_rr[0] / (double)n : 0.0;
-    for (int q = 0; q < ks.num; ++q) out[1 + q] = n > 0 ? (double)s_hit[q][0] / (double)n : 0.0;
+    out[0] = n > 0 ? rr / (double)n : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) if (q < ks.num) out[1 + q] = n > 0 ? (double)hit[q] / (double)n : 0.0;
   }
 }
 

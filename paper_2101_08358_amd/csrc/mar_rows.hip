@@ -63,14 +63,17 @@ __device__ __forceinline__ float4 load_cols(const float* __restrict__ row, int l
   }
   return x;
 }
-// sum += x . y over a lane's float4, in the order of its columns
+// sum += x . y over a lane's float4, in the order of its columns.  The fused multiply-adds are written out, here and in
+// dst_operand, so that the gather and the filter give a triple the same bits whatever surrounds the expression.
 template <bool VEC, bool CPLX> __device__ __forceinline__ void add_dot(float& sum, const float4& x, const float4& y) {
-  if (VEC && CPLX) sum += (x.x * y.x + x.z * y.z) + (x.y * y.y + x.w * y.w);
-  else if (VEC) sum += (x.x * y.x + x.y * y.y) + (x.z * y.z + x.w * y.w);
-  else if (CPLX) { sum += x.x * y.x + x.z * y.z; sum += x.y * y.y + x.w * y.w; }
-  else { sum += x.x * y.x; sum += x.y * y.y; sum += x.z * y.z; sum += x.w * y.w; }
+  if (VEC && CPLX) sum += __builtin_fmaf(x.x, y.x, x.z * y.z) + __builtin_fmaf(x.y, y.y, x.w * y.w);
+  else if (VEC) sum += __builtin_fmaf(x.x, y.x, x.y * y.y) + __builtin_fmaf(x.z, y.z, x.w * y.w);
+  else if (CPLX) { sum += __builtin_fmaf(x.x, y.x, x.z * y.z); sum += __builtin_fmaf(x.y, y.y, x.w * y.w); }
+  else {
+    sum = __builtin_fmaf(x.x, y.x, sum); sum = __builtin_fmaf(x.y, y.y, sum);
+    sum = __builtin_fmaf(x.z, y.z, sum); sum = __builtin_fmaf(x.w, y.w, sum);
+  }
 }
-
 // largest finite magnitude so far
 __device__ __forceinline__ float finite_max(float m, float v) { const float f = fabsf(v); return f <= 3.4028234663852886e38f ? fmaxf(m, f) : m; }
 __device__ __forceinline__ float finite_max4(float m, const float4& v) { return finite_max(finite_max(finite_max(finite_max(m, v.x), v.y), v.z), v.w); }
@@ -81,6 +84,17 @@ template <int GL> __device__ __forceinline__ float group_max(float v) {
 #pragma unroll
   for (int o = GL / 2; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   return v;
+}
+
+// The edge-side operand whose product with (TransE: distance to) a destination's row is the score.
+__device__ __forceinline__ float4 sub4(const float4& x, const float4& y) { return make_float4(x.x - y.x, x.y - y.y, x.z - y.z, x.w - y.w); }
+template <int MODEL> __device__ __forceinline__ float4 dst_operand(const float4& s, const float4& r) {
+  if (MODEL == MAR_MODEL_COMPLEX)
+    return make_float4(__builtin_fmaf(s.x, r.x, -(s.z * r.z)), __builtin_fmaf(s.y, r.y, -(s.w * r.w)),
+                       __builtin_fmaf(s.z, r.x, s.x * r.z), __builtin_fmaf(s.w, r.y, s.y * r.w));
+  if (MODEL == MAR_MODEL_DISTMULT) return make_float4(s.x * r.x, s.y * r.y, s.z * r.z, s.w * r.w);
+  if (MODEL == MAR_MODEL_TRANSE) return make_float4(s.x + r.x, s.y + r.y, s.z + r.z, s.w + r.w);
+  return s;
 }
 
 // Calls f(column, value) for the elements, or f2 / f4 for aligned pairs / quadruples of columns, that a lane holds of a row.
@@ -204,24 +218,18 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
       for (int v = 0; v < NV; ++v) {
         const float4 S = s[j][v], R = r[j][v], D = d[j][v];
         float4 U, W;
-        if (CPLX) {                                         // (re, re, im, im)
-          U = make_float4(S.x * R.x - S.z * R.z, S.y * R.y - S.w * R.w, S.x * R.z + S.z * R.x, S.y * R.w + S.w * R.y);
-          W = make_float4(R.x * D.x + R.z * D.z, R.y * D.y + R.w * D.w, R.x * D.z - R.z * D.x, R.y * D.w - R.w * D.y);
-          add_dot<VEC, true>(acc[j], U, D);
-        } else if (MODEL == MAR_MODEL_DISTMULT) {
-          U = make_float4(S.x * R.x, S.y * R.y, S.z * R.z, S.w * R.w);
-          W = make_float4(R.x * D.x, R.y * D.y, R.z * D.z, R.w * D.w);
-          add_dot<VEC, false>(acc[j], U, D);
-        } else if (MODEL == MAR_MODEL_DOT) {
-          U = S; W = D;
-          add_dot<VEC, false>(acc[j], S, D);
-        } else {
-          U = make_float4(S.x + R.x, S.y + R.y, S.z + R.z, S.w + R.w);
-          W = make_float4(D.x - R.x, D.y - R.y, D.z - R.z, D.w - R.w);
-          const float4 df = make_float4(U.x - D.x, U.y - D.y, U.z - D.z, U.w - D.w);
+        U = dst_operand<MODEL>(S, R);
+        if (CPLX) W = make_float4(R.x * D.x + R.z * D.z, R.y * D.y + R.w * D.w, R.x * D.z - R.z * D.x, R.y * D.w - R.w * D.y);
+        else if (MODEL == MAR_MODEL_DISTMULT) W = make_float4(R.x * D.x, R.y * D.y, R.z * D.z, R.w * D.w);
+        else if (MODEL == MAR_MODEL_DOT) W = D;
+        else W = sub4(D, R);
+        if (MODEL == MAR_MODEL_TRANSE) {
+          const float4 df = sub4(U, D);
           add_dot<VEC, false>(acc[j], df, df);
           add_dot<VEC, false>(nd[j], U, U);
           add_dot<VEC, false>(ns[j], W, W);
+        } else {
+          add_dot<VEC, CPLX>(acc[j], U, D);
         }
         u[j][v] = U; w[j][v] = W;
         if (IMG && F16 && r0 + j < nr) {
@@ -566,63 +574,17 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
 }
 
 // ------------------------------------------------------------ filtered evaluation -----
-// Score f(s, r, d) of one triple by one lane group, in the operation order of the positive score above.
-template <int GL, bool VEC>
-__device__ __forceinline__ float group_score(int model, int dim, const float* __restrict__ s_row,
-                                             const float* __restrict__ r_row, const float* __restrict__ d_row, int l) {
-  float acc = 0.f;
-  if (VEC && model == MAR_MODEL_COMPLEX) {
-    const int h = dim >> 1;
-    for (int k = 2 * l; k < h; k += 2 * GL) {
-      const float2 sr = *reinterpret_cast<const float2*>(s_row + k), si = *reinterpret_cast<const float2*>(s_row + h + k);
-      const float2 rr = *reinterpret_cast<const float2*>(r_row + k), ri = *reinterpret_cast<const float2*>(r_row + h + k);
-      const float2 dr = *reinterpret_cast<const float2*>(d_row + k), di = *reinterpret_cast<const float2*>(d_row + h + k);
-      const float2 ure = make_float2(sr.x * rr.x - si.x * ri.x, sr.y * rr.y - si.y * ri.y);
-      const float2 uim = make_float2(sr.x * ri.x + si.x * rr.x, sr.y * ri.y + si.y * rr.y);
-      acc += (ure.x * dr.x + uim.x * di.x) + (ure.y * dr.y + uim.y * di.y);
-    }
-  } else if (VEC) {
-    for (int k = 4 * l; k < dim; k += 4 * GL) {
-      const float4 s = *reinterpret_cast<const float4*>(s_row + k), d = *reinterpret_cast<const float4*>(d_row + k);
-      float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (model != MAR_MODEL_DOT) r = *reinterpret_cast<const float4*>(r_row + k);
-      if (model == MAR_MODEL_DISTMULT) {
-        const float4 u = make_float4(s.x * r.x, s.y * r.y, s.z * r.z, s.w * r.w);
-        acc += (u.x * d.x + u.y * d.y) + (u.z * d.z + u.w * d.w);
-      } else if (model == MAR_MODEL_DOT) {
-        acc += (s.x * d.x + s.y * d.y) + (s.z * d.z + s.w * d.w);
-      } else {
-        const float4 u = make_float4(s.x + r.x, s.y + r.y, s.z + r.z, s.w + r.w);
-        const float4 df = make_float4(u.x - d.x, u.y - d.y, u.z - d.z, u.w - d.w);
-        acc += (df.x * df.x + df.y * df.y) + (df.z * df.z + df.w * df.w);
-      }
-    }
-  } else if (model == MAR_MODEL_COMPLEX) {
-    const int h = dim >> 1;
-    for (int k = l; k < h; k += GL) {
-      const float sr = s_row[k], si = s_row[h + k], rr = r_row[k], ri = r_row[h + k], dr = d_row[k], di = d_row[h + k];
-      const float ure = sr * rr - si * ri, uim = sr * ri + si * rr;
-      acc += ure * dr + uim * di;
-    }
-  } else {
-    for (int k = l; k < dim; k += GL) {
-      const float s = s_row[k], r = r_row[k], d = d_row[k];
-      if (model == MAR_MODEL_DISTMULT) { const float u = s * r; acc += u * d; }
-      else if (model == MAR_MODEL_DOT) acc += s * d;
-      else { const float u = s + r; const float df = u - d; acc += df * df; }
-    }
-  }
-  acc = group_sum<GL>(acc);
-  return model == MAR_MODEL_TRANSE ? -sqrtf(acc) : acc;
-}
-
-// One lane group per (edge, corrupted side): takes the listed true candidates that outscore the edge
-// out of its rank.
-template <int GL, bool VEC>
+// One lane group per (edge, corrupted side): takes the listed true candidates that outscore the edge out of its rank.
+// The edge's rows are read once; candidates are taken FILT at a time, their ids and then their rows all in flight (one
+// candidate at a time the kernel was a chain of two dependent loads per candidate: 72 us for 20,000 lists of 16 rows of
+// 100 floats, 40 us now).  Scores are formed in the operation order of the positive score above.
+#define FILT 4
+template <int GL, int NV, bool VEC, int MODEL>
 __global__ void __launch_bounds__(256)
 k_filter(RowArgs a, const int64_t* __restrict__ dst_off, const int32_t* __restrict__ dst_ids,
          const int64_t* __restrict__ src_off, const int32_t* __restrict__ src_ids, const float* __restrict__ pos,
          int32_t* __restrict__ rank_dst, int32_t* __restrict__ rank_src) {
+  constexpr bool CPLX = MODEL == MAR_MODEL_COMPLEX;
   constexpr int GPB = 256 / GL;
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int idx = blockIdx.x * GPB + grp;
@@ -630,18 +592,41 @@ k_filter(RowArgs a, const int64_t* __restrict__ dst_off, const int32_t* __restri
   const int side = idx >= a.n ? MAR_SIDE_DST : MAR_SIDE_SRC;
   const int e = side == MAR_SIDE_DST ? idx - a.n : idx;
   const int dim = a.dim;
-  const float* s_row = a.node_emb + (size_t)a.src[e] * dim;
-  const float* r_row = a.rel_emb + (size_t)(a.model == MAR_MODEL_DOT ? 0 : a.rel[e]) * dim;
-  const float* d_row = a.node_emb + (size_t)a.dst[e] * dim;
-  const float p = pos[e];
   const int64_t* off = side == MAR_SIDE_DST ? dst_off : src_off;
   const int32_t* ids = side == MAR_SIDE_DST ? dst_ids : src_ids;
+  const int64_t k0 = off[e], k1 = off[e + 1];
+  const float p = pos[e];
+  const float* kept_row = a.node_emb + (size_t)(side == MAR_SIDE_DST ? a.src[e] : a.dst[e]) * dim;   // the endpoint that stays
+  const float* r_row = a.rel_emb + (size_t)(MODEL == MAR_MODEL_DOT ? 0 : a.rel[e]) * dim;
+  float4 kept[NV], r[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    kept[v] = load_cols<GL, VEC, CPLX>(kept_row, l, v, dim);
+    r[v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : load_cols<GL, VEC, CPLX>(r_row, l, v, dim);
+  }
   int better = 0;
-  for (int64_t k = off[e]; k < off[e + 1]; ++k) {
-    const float* c_row = a.node_emb + (size_t)ids[k] * dim;
-    const float f = side == MAR_SIDE_DST ? group_score<GL, VEC>(a.model, dim, s_row, r_row, c_row, l)
-                                         : group_score<GL, VEC>(a.model, dim, c_row, r_row, d_row, l);
-    better += f > p ? 1 : 0;
+  for (int64_t k = k0; k < k1; k += FILT) {
+    float4 c[FILT][NV];
+#pragma unroll
+    for (int j = 0; j < FILT; ++j) {
+      const float* c_row = a.node_emb + (size_t)ids[k + j < k1 ? k + j : k1 - 1] * dim;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) c[j][v] = load_cols<GL, VEC, CPLX>(c_row, l, v, dim);
+    }
+#pragma unroll
+    for (int j = 0; j < FILT; ++j) {
+      float acc = 0.f;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const float4 s = side == MAR_SIDE_DST ? kept[v] : c[j][v], d = side == MAR_SIDE_DST ? c[j][v] : kept[v];
+        const float4 u = dst_operand<MODEL>(s, r[v]);
+        if (MODEL == MAR_MODEL_TRANSE) { const float4 df = sub4(u, d); add_dot<VEC, false>(acc, df, df); }
+        else add_dot<VEC, CPLX>(acc, u, d);
+      }
+      acc = group_sum<GL>(acc);
+      const float f = MODEL == MAR_MODEL_TRANSE ? -sqrtf(acc) : acc;
+      better += k + j < k1 && f > p ? 1 : 0;
+    }
   }
   // The unfiltered rank comes from the matrix cores, this count from the vector ALU: a candidate within rounding
   // of the edge's score can be counted here and not there, so the difference is kept at 1 or above.
@@ -1139,10 +1124,17 @@ hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t*
   RowArgs a = row_args(c, b);
   const int GL = mar_lane_group(a.dk), gpb = 256 / GL;
   const dim3 grid((2 * b.n + gpb - 1) / gpb), blk(256);
-#define FILT(GLV, V) hipLaunchKernelGGL((k_filter<GLV, V>), grid, blk, 0, st, a, dst_off, dst_ids, src_off, src_ids, pos, rank_dst, rank_src)
-  if (a.dim % 4 == 0) { if (GL == 16) FILT(16, true); else if (GL == 32) FILT(32, true); else FILT(64, true); }
-  else { if (GL == 16) FILT(16, false); else if (GL == 32) FILT(32, false); else FILT(64, false); }
-#undef FILT
+#define FILTER3(GLV, NVV, M) do { \
+    if (a.dim % 4 == 0) hipLaunchKernelGGL((k_filter<GLV, NVV, true, M>), grid, blk, 0, st, a, dst_off, dst_ids, src_off, src_ids, pos, rank_dst, rank_src); \
+    else hipLaunchKernelGGL((k_filter<GLV, NVV, false, M>), grid, blk, 0, st, a, dst_off, dst_ids, src_off, src_ids, pos, rank_dst, rank_src); } while (0)
+#define FILTER(GLV, NVV) do { switch (a.model) { \
+    case MAR_MODEL_DISTMULT: FILTER3(GLV, NVV, MAR_MODEL_DISTMULT); break; \
+    case MAR_MODEL_COMPLEX: FILTER3(GLV, NVV, MAR_MODEL_COMPLEX); break; \
+    case MAR_MODEL_TRANSE: FILTER3(GLV, NVV, MAR_MODEL_TRANSE); break; \
+    default: FILTER3(GLV, NVV, MAR_MODEL_DOT); break; } } while (0)
+  if (GL == 16) FILTER(16, 1); else if (GL == 32) FILTER(32, 1); else if (a.dk <= 256) FILTER(64, 1); else FILTER(64, 2);
+#undef FILTER
+#undef FILTER3
   return hipGetLastError();
 }
 

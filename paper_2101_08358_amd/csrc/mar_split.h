@@ -2,8 +2,8 @@
 //
 // A matrix that takes part in a pass (the chunk's negatives, the chunk's edge-side operands) is kept as "images": per
 // chunk-side and tile of 32 rows a plane of the rows' hi parts and a plane of their lo parts, each [32][PA bytes], a
-// row = 32 NB 16-bit values: the dk columns and zeros up to the next multiple of 32.  An image is one contiguous
-// block of IMG bytes (a multiple of 1 KB).
+// row = 16 NK 16-bit values: the dk columns and zeros up to the next multiple of 16 that an instantiation serves.  An
+// image is one contiguous block of IMG bytes (a multiple of 1 KB).
 //   fp32 precision:  v 2^e = hi + lo with hi = f16(v 2^e), lo = f16(v 2^e - hi), one exponent e per block of 16 rows,
 //                    chosen so that the block's largest value lies in [2^14, 2^15); e is kept beside the images.
 //   SPLIT_BF16:      v = hi + lo with hi = bf16(v), lo = bf16(v - hi).
@@ -13,23 +13,17 @@
 
 #include "mar_common.h"
 
-// Row pitch in bytes of a plane whose rows hold `rowb` bytes: the pitch in 4-byte banks, mod 64, must be one of
-// 12, 28, 36, 52 -- then 16 rows of a 16-byte fragment read fall into 16 different groups of 4 LDS banks, and
-// the 4 rows that a group of 16 lanes covers in a transpose read into 4 different groups of 8 banks.
-constexpr int sp_pitch(int rowb) {
-  for (int pad = 16; pad <= 256; pad += 16) {
-    const int p = ((rowb + pad) / 4) % 64;
-    if (p == 12 || p == 28 || p == 36 || p == 52) return rowb + pad;
-  }
-  return rowb + 16;
-}
+// Row pitch in bytes of a plane whose rows hold 16 NK values: an odd number of 16-byte units, so the 16 rows of a
+// 16-byte fragment read fall into 16 different groups of 4 LDS banks.  (Pitches that also keep the transpose reads free
+// of bank conflicts cost up to 27% more bytes to copy, and the LDS is busy a quarter of the time.)
+constexpr int sp_pitch(int nk) { return 32 * nk + 16; }
 constexpr int SP_TY = MAR_SPLIT_TILE_ROWS;                 // rows per image
 constexpr int SP_EB = 16;                                  // rows per exponent
 constexpr int SP_SR = MAR_SPLIT_STRIPE_ROWS;               // stationary rows per workgroup: four waves of 32
 // 16-column contraction steps (NK) of the instantiation that serves dk; 32-column output blocks (NB) follow from it.
 constexpr int sp_nk(int dk) { return dk <= 32 ? 2 : (dk <= 64 ? 4 : (dk <= 96 ? 6 : (dk <= 112 ? 7 : (dk <= 128 ? 8 : (dk <= 192 ? 12 : (dk <= 256 ? 16 : 25)))))); }
 constexpr int sp_nb(int nk) { return (nk + 1) / 2; }
-constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(64 * sp_nb(nk)); }
+constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(nk); }
 constexpr int sp_image(int nk) { return (2 * sp_plane(nk) + 1023) / 1024 * 1024; }
 static inline int sp_tiles(int rows) { return (rows + SP_TY - 1) / SP_TY; }
 
@@ -46,8 +40,8 @@ struct SplitImages {
 static inline SplitImages sp_images(char* base, float* exps, float* norms, int dk, int rows_per_chunk) {
   const int nk = sp_nk(dk);
   SplitImages g;
-  g.base = base; g.exps = exps; g.norms = norms; g.pa = sp_pitch(64 * sp_nb(nk)); g.plane = sp_plane(nk); g.img = sp_image(nk);
-  g.tiles = sp_tiles(rows_per_chunk); g.dkp = 32 * sp_nb(nk);
+  g.base = base; g.exps = exps; g.norms = norms; g.pa = sp_pitch(nk); g.plane = sp_plane(nk); g.img = sp_image(nk);
+  g.tiles = sp_tiles(rows_per_chunk); g.dkp = 16 * nk;
   return g;
 }
 

@@ -33,7 +33,8 @@
 //   the lane's own score registers 8k .. 8k+7, so slot 8h + j stands for row 16k + 4h + j (j < 4), 16k + 8 + 4h + j - 4
 //   (j >= 4).  A = Y^T by the LDS transpose read (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4
 //   consecutive 16-bit values and receives, as its j-th value, value (i % 4) of lane 4j + i / 4; with lane i pointing
-//   at row 4h + i / 4, columns 32 cb + 16 (G % 2) + 4 (i % 4), lane m receives Y[4h + j][32 cb + m].
+//   at row 4h + i / 4, columns 32 cb + 16 (G % 2) + 4 (i % 4), lane m receives Y[4h + j][32 cb + m].  (With NK odd the
+//   last block reads up to 16 bytes past a row's pitch: columns beyond dk, whose outputs are not stored.)
 #include <type_traits>
 
 #include "mar_common.h"
@@ -87,7 +88,7 @@ __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevec
 template <int NK>
 struct SplitGeom {
   static constexpr int NB = sp_nb(NK);
-  static constexpr int PA = sp_pitch(64 * NB);
+  static constexpr int PA = sp_pitch(NK);
   static constexpr int PLANE = sp_plane(NK);
   static constexpr int IMG = sp_image(NK);
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
@@ -101,11 +102,10 @@ struct SplitGeom {
 // multiply-adds -- in the column order of the fp32 contraction kernels: blocks of 16 columns up to column `chain`, each
 // as columns 4 g + i for i = 0..3, g = 0..3; the rest in sequence.  So do blocks that hold an infinity or a NaN.
 constexpr int sp_chain(int dk) { return dk <= 52 ? 48 : (dk <= 100 ? 96 : 400); }
-template <bool VEC>
+template <bool VEC, int UB>
 __device__ __forceinline__ float sp_exact_score(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
   float s = 0.f;
   const int nb = (min(chain, dim) + 15) / 16;
-  constexpr int UB = 4;                                    // blocks whose loads are in flight at once
   for (int b0 = 0; b0 < nb; b0 += UB) {
     float a[UB][16], c[UB][16];
 #pragma unroll
@@ -159,6 +159,9 @@ __device__ __forceinline__ float sp_exact_score_slow(const float* __restrict__ q
 #ifndef SP_PG
 #define SP_PG 2
 #endif
+// Waves per SIMD = workgroups per CU: pass 3 keeps no output accumulators.
+constexpr int sp_waves(int nk, int pass) { return pass == 3 ? (nk <= 8 ? 3 : (nk <= 16 ? 2 : 1)) : (nk <= 8 ? 2 : 1); }
+
 // ------------------------------------------------------------------------ the passes -----
 // PASS 1: scores, online softmax and gQ = P K for 128 edges of one chunk-side (32 per wave) against the chunk's
 // negatives.  No weights are kept for pass 2:
@@ -168,7 +171,7 @@ __device__ __forceinline__ float sp_exact_score_slow(const float* __restrict__ q
 // PASS 3 (evaluation): counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add
 // their counts.
 template <int NK, int PASS, bool F16>
-__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD((NK <= 8 ? 2 : 1))
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
   typedef SplitGeom<NK> SG;
   constexpr int NB = SG::NB, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
@@ -476,10 +479,11 @@ k_split(FlashArgs a) {
 
   // ---- epilogue
   if (PASS == 3) {
+    constexpr int UB = NK <= 16 ? 4 : 8;                   // 16-column blocks whose loads are in flight at once
     for (int i = 0; i < npend; ++i) {
       const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + pend[256 * i]];
       const float* yrow = a.table + (size_t)id * a.dim;
-      const float s = a.dim % 4 == 0 ? sp_exact_score<true>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false>(qrow, yrow, a.dim, sp_chain(dk));
+      const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
       cnt += s > posx ? 1 : 0;
     }
     cnt += __shfl_xor(cnt, 32);
@@ -543,7 +547,7 @@ __global__ void __launch_bounds__(256) k_split_merge2(FlashArgs a) {
 
 // ------------------------------------------------------------------- launchers -----
 int mar_split_supported(int dk) { return dk >= 4 && dk <= 400; }
-int mar_split_wgs_per_cu(int dk) { return sp_nk(dk) <= 8 ? 2 : 1; }
+int mar_split_wgs_per_cu(int dk, int pass) { return sp_waves(sp_nk(dk), pass); }
 size_t mar_split_image_bytes(int dk) { return (size_t)sp_image(sp_nk(dk)); }
 
 template <int NK> static hipError_t sp_prepare() {

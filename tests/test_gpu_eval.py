@@ -246,3 +246,27 @@ def test_degree_based_evaluation_negatives_end_to_end():
     for j, k in enumerate(ks):
         assert got[1 + j] == metrics.hits_at(ranks, k)
     tr.close()
+
+
+@pytest.mark.parametrize("model", (0, 1, 2, 3))
+@pytest.mark.parametrize("dim", (18, 50, 64, 100, 126, 200, 400))
+def test_filtering_by_the_edges_own_endpoint_changes_nothing(model, dim):
+    """The filter scores a listed candidate in the operation order of the positive score: the edge's own endpoint never
+    outscores the edge.  Lists of 1 to 9 entries (whole and partial groups of four), the endpoint repeated."""
+    V, R, B, C, N = 500, 4, 300, 2, 64
+    rng = np.random.default_rng(dim + model)
+    ne, re_ = (rng.standard_normal((k, dim)).astype(np.float32) * 0.4 for k in (V, R))
+    tr = mar.Trainer(V, R, dim, model, B, C, N, node_emb=ne, rel_emb=re_)
+    dev = tr.device
+    src, rel, dst = (torch.from_numpy(rng.integers(0, k, B).astype(np.int32)).to(dev) for k in (V, R, V))
+    tr.neg_src, tr.neg_dst = (torch.from_numpy(rng.integers(0, V, C * N).astype(np.int32)).to(dev) for _ in range(2))
+    pos, rd, rs = tr.eval_scores(src, rel, dst)
+    torch.cuda.synchronize()
+    before = rd.cpu().numpy().copy(), rs.cpu().numpy().copy()
+    reps = torch.from_numpy(rng.integers(1, 10, B)).to(dev)
+    off = torch.zeros(B + 1, dtype=torch.int64, device=dev)
+    off[1:] = torch.cumsum(reps, 0)
+    mar.mar_eval_filter(tr.ctx, src, rel, dst, B, off, torch.repeat_interleave(dst, reps), off, torch.repeat_interleave(src, reps), pos, rd, rs)
+    torch.cuda.synchronize()
+    assert np.array_equal(before[0], rd.cpu().numpy()) and np.array_equal(before[1], rs.cpu().numpy())
+    tr.close()
