@@ -31,18 +31,14 @@ static int hip_fail(hipError_t e, const char* what) {
 }
 
 // ------------------------------------------------------------------ configuration -----
-#ifndef MAR_FLASH_TARGET_WGS1
-#define MAR_FLASH_TARGET_WGS1 640
-#endif
-#ifndef MAR_FLASH_TARGET_WGS2
-#define MAR_FLASH_TARGET_WGS2 640
-#endif
+#define MAR_FLASH_TARGET_WGS 640
 
 static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass); }
 
 // Small batches give too few (chunk-side, stripe) units to fill 256 CUs: several workgroups share a unit, each
-// streaming a slice of the other matrix.  TransE: until a pass has at least MAR_FLASH_TARGET_WGS workgroups (measured
-// best for a 10,000-edge batch).  Bilinear models: as many parts as the least estimated time of the busiest CU asks
+// streaming a slice of the other matrix.  TransE: until a pass has at least MAR_FLASH_TARGET_WGS workgroups; pass 1
+// then takes the number of parts with the least work on the busiest CU, a part costing its tiles and one more (10,000
+// edges, 100 floats: 4 parts 106 us, 2 parts 121, 8 parts 116).  Bilinear models: as many parts as the least estimated time of the busiest CU asks
 // for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its first tile and its
 // rows (pass 3, whose tiles are half the work and whose close comparisons are settled at the end: eight); a CU that holds
 // one of two possible workgroups runs it at about 0.6 of its full rate.
@@ -51,10 +47,16 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
   const int ntiles = (n_y + ty - 1) / ty;
   long want = 1;
   if (!d.bilinear) {
-    const long target = pass == 2 ? MAR_FLASH_TARGET_WGS2 : MAR_FLASH_TARGET_WGS1;
-    want = (target + units - 1) / units;
+    want = (MAR_FLASH_TARGET_WGS + units - 1) / units;
     if (want > MAR_MAX_PARTS) want = MAR_MAX_PARTS;
     if (want > ntiles) want = ntiles;
+    if (pass == 1 && want > 1) {
+      long best = 1L << 60;
+      for (long k = 1; k <= MAR_MAX_PARTS && k <= ntiles; ++k) {
+        const long cost = (units * k + 255) / 256 * ((ntiles + k - 1) / k + 1);
+        if (cost < best) { best = cost; want = k; }
+      }
+    }
   } else if (units < 256L * wgs_per_cu(d, pass) || pass == 3) {
     double best = 1e30;
     const bool two = wgs_per_cu(d, pass) >= 2;
@@ -462,11 +464,12 @@ static size_t pipe_slot_extra(const MarDims& d, char* base, PipeSlot* ps) {
   PipeSlot t;
   t.sg.compact = (float*)take(rows * d.dim * 4 + 16);
   t.sg.gsum = (float*)take((size_t)d.u_max * d.dk * 4);
+  t.sg.shared = (uint8_t*)take(rows);
   t.sg.c_src = (int32_t*)take(B * 4); t.sg.c_dst = (int32_t*)take(B * 4);
   t.sg.c_neg_dst = (int32_t*)take(CN * 4); t.sg.c_neg_src = (int32_t*)take(CN * 4);
   t.src = (int32_t*)take(B * 4); t.rel = (int32_t*)take(B * 4); t.dst = (int32_t*)take(B * 4);
   t.neg_src = (int32_t*)take(CN * 4); t.neg_dst = (int32_t*)take(CN * 4);
-  if (ps) { ps->sg.compact = t.sg.compact; ps->sg.gsum = t.sg.gsum; ps->sg.c_src = t.sg.c_src; ps->sg.c_dst = t.sg.c_dst;
+  if (ps) { ps->sg.compact = t.sg.compact; ps->sg.gsum = t.sg.gsum; ps->sg.shared = t.sg.shared; ps->sg.c_src = t.sg.c_src; ps->sg.c_dst = t.sg.c_dst;
             ps->sg.c_neg_dst = t.sg.c_neg_dst; ps->sg.c_neg_src = t.sg.c_neg_src; ps->src = t.src; ps->rel = t.rel; ps->dst = t.dst;
             ps->neg_src = t.neg_src; ps->neg_dst = t.neg_dst; }
   return off;
@@ -572,7 +575,11 @@ static int pipe_enqueue_update(mar_pipe* p, int64_t i, int64_t gather_of) {
   PipeSlot& ps = p->slots[i % p->depth];
   PIPE_TRY(hipStreamWaitEvent(p->s_out, ps.ev_step, 0), "update stage");
   if (gather_of >= 0) PIPE_TRY(hipStreamWaitEvent(p->s_out, p->slots[gather_of % p->depth].ev_in, 0), "update stage");
-  PIPE_TRY(mar_launch_stage_out(ps.ctx, ps.b_ids, ps.sg, p->s_out), "update kernel");
+  // a batch whose update a drain has enqueued already (a submit follows it) no longer has the staged values as the newest:
+  // everything is read from the host table
+  MarStage sg = ps.sg;
+  if (i < p->applied) sg.shared = nullptr;
+  PIPE_TRY(mar_launch_stage_out(ps.ctx, ps.b_ids, sg, p->s_out), "update kernel");
   PIPE_TRY(hipEventRecord(ps.ev_out, p->s_out), "update stage");
   p->applied = i + 1;
   return MAR_OK;
@@ -603,6 +610,14 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
   ps.b_rank = ps.b_ids;
   ps.b_rank.src = ps.sg.c_src; ps.b_rank.dst = ps.sg.c_dst; ps.b_rank.neg_src = ps.sg.c_neg_src; ps.b_rank.neg_dst = ps.sg.c_neg_dst;
   PIPE_TRY(mar_launch_index(c, ps.b_ids, 1, p->s_in), "index kernels");
+  // the updates of the batches between j - depth and j come after this batch's staging and before its own update; their
+  // unique lists were written earlier on s_in and stay until their slots are used again, also on s_in
+  const int64_t first = j - p->depth + 1 > 0 ? j - p->depth + 1 : 0;
+  ps.sg.num_prev = j - first <= MAR_STAGE_PREV ? (int32_t)(j - first) : -1;
+  for (int q = 0; q < MAR_STAGE_PREV; ++q) {
+    const mar_ctx* pc = q < ps.sg.num_prev ? p->slots[(first + q) % p->depth].ctx : nullptr;
+    ps.sg.prev_uniq[q] = pc ? pc->L.uniq : nullptr; ps.sg.prev_scalars[q] = pc ? pc->L.scalars : nullptr;
+  }
   PIPE_TRY(mar_launch_stage_in(c, ps.b_ids, ps.sg, p->s_in), "staging kernels");
   PIPE_TRY(hipEventRecord(ps.ev_in, p->s_in), "stage in");
   // ---- step on the caller's stream: staged rows, ranks as ids; node gradients are left in gsum, relation rows updated

@@ -137,11 +137,16 @@ hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t*
                              int32_t* rank_src, hipStream_t st);
 hipError_t mar_launch_reduce(const mar_ctx* c, const MarBatch& b, float* loss_out, float* dbg_grad, float* defer_grad, hipStream_t st);
 
+#define MAR_STAGE_PREV 8
 // Staging buffers of one batch of out-of-memory training (see mar_rows.hip).
 struct MarStage {
   float *host_emb, *host_state;                      // node table and accumulators in pinned host memory
   float *compact, *gsum;                             // [unique rows][dim] staged rows, [unique rows][dk] summed gradients
   int32_t *c_src, *c_dst, *c_neg_dst, *c_neg_src;    // the batch's node ids replaced by ranks
+  // batches whose updates may still change the host rows after they have been staged: their unique lists and counts
+  const int32_t* prev_uniq[MAR_STAGE_PREV]; const int32_t* prev_scalars[MAR_STAGE_PREV];
+  int32_t num_prev;                                  // -1: more than MAR_STAGE_PREV, every row counts as shared
+  uint8_t* shared;                                   // [unique rows] 1: the row is in one of those batches
 };
 hipError_t mar_launch_stage_in(const mar_ctx* c, const MarBatch& b, const MarStage& sg, hipStream_t st);
 hipError_t mar_launch_stage_out(const mar_ctx* c, const MarBatch& b, const MarStage& sg, hipStream_t st);

@@ -983,6 +983,9 @@ struct StageArgs {
   int32_t *c_src, *c_dst, *c_neg_dst, *c_neg_src;   // ids replaced by ranks
   int32_t n, cn, roles, sy2, dim, dk;
   float lr, eps;
+  const int32_t* prev_uniq[MAR_STAGE_PREV]; const int32_t* prev_scalars[MAR_STAGE_PREV];   // see MarStage
+  int32_t num_prev;
+  uint8_t* shared;
 };
 
 // Ranks in place of node ids, in the layout the step's entry arrays have.
@@ -997,15 +1000,31 @@ __global__ void __launch_bounds__(256) k_stage_ids(StageArgs a) {
 }
 
 #define STAGE_ROWS 4   // rows in flight per lane group
+// Workgroups of a staging kernel.  A few keep the host link full (51 GB/s read; 20,000-row batches of 100 floats, three
+// batches: 32 workgroups 3576 us, 64 3514, 128 3401 - 3434, one per 32 rows 3733): their outstanding host accesses hold
+// up every other memory access of the CUs they sit on, and the step of the next batch runs on the others.
+#define STAGE_WGS 128
 
-// compact[rank] = host table row of the rank-th unique node.  One lane group per STAGE_ROWS rows.
+// Whether `id` is in a batch's ascending unique list.
+__device__ __forceinline__ bool in_list(const int32_t* __restrict__ uniq, int n, int32_t id) {
+  int lo = 0, hi = n;
+  while (lo < hi) { const int mid = (lo + hi) >> 1; if (uniq[mid] < id) lo = mid + 1; else hi = mid; }
+  return lo < n && uniq[lo] == id;
+}
+
+// compact[rank] = host table row of the rank-th unique node; shared[rank] = whether a batch in flight, whose update is
+// still to come, has the node too.  One lane group per STAGE_ROWS rows.
 template <int GL, int NV, bool VEC>
 __global__ void __launch_bounds__(256) k_stage_gather(StageArgs a) {
   constexpr int GPB = 256 / GL;
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int un = a.scalars[1];
-  const int r0 = (blockIdx.x * GPB + grp) * STAGE_ROWS;
-  if (r0 >= un) return;
+  for (int r0 = (blockIdx.x * GPB + grp) * STAGE_ROWS; r0 < un; r0 += (int)gridDim.x * GPB * STAGE_ROWS) {
+  if (l < STAGE_ROWS && r0 + l < un) {
+    bool s = a.num_prev < 0;
+    for (int p = 0; p < a.num_prev && !s; ++p) s = in_list(a.prev_uniq[p], a.prev_scalars[p][1], a.uniq[r0 + l]);
+    a.shared[r0 + l] = s ? 1 : 0;
+  }
   float4 v4[STAGE_ROWS][NV];
 #pragma unroll
   for (int j = 0; j < STAGE_ROWS; ++j) {
@@ -1027,28 +1046,30 @@ __global__ void __launch_bounds__(256) k_stage_gather(StageArgs a) {
       }
     }
   }
+  }
 }
 
 // Adagrad on the host table rows of the batch's unique nodes with the summed gradients the step left in gsum
-// (Sec. 3, last stage: the update is applied to whatever the table holds now, in batch order).
+// (Sec. 3, last stage: the update is applied to whatever the table holds now, in batch order).  A row that no batch in
+// flight shared still holds what was staged, so its embedding is taken from the compact table instead of over the link.
 template <int GL, int NV, bool VEC>
 __global__ void __launch_bounds__(256) k_stage_apply(StageArgs a) {
   constexpr int GPB = 256 / GL;
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int un = a.scalars[1];
-  const int r0 = (blockIdx.x * GPB + grp) * STAGE_ROWS;
-  if (r0 >= un) return;
+  for (int r0 = (blockIdx.x * GPB + grp) * STAGE_ROWS; r0 < un; r0 += (int)gridDim.x * GPB * STAGE_ROWS) {
   float4 th[STAGE_ROWS][NV], s0[STAGE_ROWS][NV], g[STAGE_ROWS][NV];
   size_t off[STAGE_ROWS];
 #pragma unroll
   for (int j = 0; j < STAGE_ROWS; ++j) {
     const int r = min(r0 + j, un - 1);
     off[j] = (size_t)a.uniq[r] * a.dim;
+    const float* emb = !a.shared || a.shared[r] ? a.host_emb_rw + off[j] : a.compact + (size_t)r * a.dim;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int k = 4 * (l + GL * v);
       if (k < a.dim) {
-        th[j][v] = load_row4<VEC>(a.host_emb_rw + off[j], k, a.dim);
+        th[j][v] = load_row4<VEC>(emb, k, a.dim);
         s0[j][v] = load_row4<VEC>(a.host_state + off[j], k, a.dim);
         g[j][v] = *reinterpret_cast<const float4*>(a.gsum + (size_t)r * a.dk + k);
       }
@@ -1068,6 +1089,7 @@ __global__ void __launch_bounds__(256) k_stage_apply(StageArgs a) {
         }
       }
     }
+  }
   }
 }
 
@@ -1205,6 +1227,8 @@ static StageArgs stage_args(const mar_ctx* c, const MarBatch& b, const MarStage&
   a.c_src = sg.c_src; a.c_dst = sg.c_dst; a.c_neg_dst = sg.c_neg_dst; a.c_neg_src = sg.c_neg_src;
   a.n = b.n; a.cn = b.cn; a.roles = d.roles; a.sy2 = d.sy2; a.dim = d.dim; a.dk = d.dk;
   a.lr = c->cfg.lr; a.eps = c->cfg.eps;
+  for (int p = 0; p < MAR_STAGE_PREV; ++p) { a.prev_uniq[p] = sg.prev_uniq[p]; a.prev_scalars[p] = sg.prev_scalars[p]; }
+  a.num_prev = sg.num_prev; a.shared = sg.shared;
   return a;
 }
 
@@ -1216,7 +1240,8 @@ static int64_t stage_rows_max(const mar_ctx* c, const MarBatch& b) {
 
 #define STAGE_LAUNCH(KERNEL) do { \
     const int GL = mar_lane_group(a.dk), gpb = 256 / GL; \
-    const dim3 grid((unsigned)((stage_rows_max(c, b) + gpb * STAGE_ROWS - 1) / (gpb * STAGE_ROWS))), blk(256); \
+    const int64_t full = (stage_rows_max(c, b) + gpb * STAGE_ROWS - 1) / (gpb * STAGE_ROWS); \
+    const dim3 grid((unsigned)(full < STAGE_WGS ? full : STAGE_WGS)), blk(256); \
     const bool vec = a.dim % 4 == 0; \
     if (GL == 16) { if (vec) hipLaunchKernelGGL((KERNEL<16, 1, true>), grid, blk, 0, st, a); else hipLaunchKernelGGL((KERNEL<16, 1, false>), grid, blk, 0, st, a); } \
     else if (GL == 32) { if (vec) hipLaunchKernelGGL((KERNEL<32, 1, true>), grid, blk, 0, st, a); else hipLaunchKernelGGL((KERNEL<32, 1, false>), grid, blk, 0, st, a); } \

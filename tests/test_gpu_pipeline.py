@@ -121,3 +121,16 @@ def test_depth_k_follows_the_oracle_with_staleness_k_minus_one(depth):
     sne, sns, sre, srs = ne.copy(), ns.copy(), re_.copy(), rs.copy()
     opipe.train_pipelined(model, np.float32(0.1), np.float32(1e-10), B // C, sne, sns, sre, srs, batches, staleness=0)
     assert np.max(np.abs(sne - one)) / np.max(np.abs(one)) > 1e-3
+
+
+def test_more_batches_in_flight_than_are_searched_for_shared_rows():
+    """Depth 12: a batch's rows count as shared with the eleven batches in flight without a search, and every embedding is
+    read from the host table again; same oracle and bars as the shallower pipelines."""
+    model, V, R, dim, B, C, N, depth = mar.MODEL_DISTMULT, 2000, 4, 36, 120, 2, 50, 12
+    ne, ns, re_, rs, batches = _setup(model, V, R, dim, B, C, N, nb=16, seed=depth, state0=0.05)
+    got = _run_pipe(model, V, R, dim, B, C, N, depth, (ne, ns, re_, rs), batches)
+    one, ons, ore, ors = ne.copy(), ns.copy(), re_.copy(), rs.copy()
+    opipe.train_pipelined(model, np.float32(0.1), np.float32(1e-10), B // C, one, ons, ore, ors, batches, staleness=depth - 1)
+    for g, w, name in zip(got[:4], (one, ons, ore, ors), ("node_emb", "node_state", "rel_emb", "rel_state")):
+        err = np.max(np.abs(g.astype(np.float64) - w)) / np.max(np.abs(w))
+        assert err <= 1e-4, (name, err)
