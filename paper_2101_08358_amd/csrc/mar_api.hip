@@ -154,6 +154,10 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   plan_rem(*d, 1, units1, d->N, d->sy1, sr1, &d->rem1);
   plan_rem(*d, 2, units2, d->S, d->sy2, sr2, &d->rem2);
   d->n_pos_max = roles * (int64_t)cfg->batch_size + 2 * cn * d->sy2;
+  // Few positions per lane group while whole ones would leave CUs without a workgroup of the reduce.  Above that the
+  // segments that cross the smaller workgroups' borders cost more than the shorter chains gain (52,000 gradient rows of 75
+  // floats: a step 125 -> 116 us; 90,000 of 100: 147 -> 156).
+  d->reduce_small = d->n_pos_max < 256 * 256;
   // Sort keys are unified ids: as few passes as digits of at most MAR_SORT_MAX_BITS bits allow.
   int nbits = 1;
   while (((int64_t)1 << nbits) < ids) ++nbits;
@@ -176,7 +180,7 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   };
   const size_t n_pos = (size_t)d.n_pos_max, u1 = (size_t)d.u_max + 1;
   const size_t B = d.B, CN = (size_t)d.C * d.N, dk = d.dk;
-  const size_t blocks = (n_pos + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
+  const size_t rb = (size_t)mar_reduce_block(d), blocks = (n_pos + rb - 1) / rb;
   const size_t tiles = ((n_pos + 256 * d.sort_items - 1) / (256 * d.sort_items) + 3) & ~(size_t)3, rank_tiles = n_pos / MAR_RANK_TILE + 1;
   MarLayout l;
   l.scalars = (int32_t*)take(16 * 4);
@@ -245,8 +249,7 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
   if (!workspace || ((uintptr_t)workspace & 255)) return fail(MAR_EINVAL, "workspace must be non-NULL and 256-byte aligned");
   const size_t need = carve(d, nullptr, nullptr);
   if (workspace_bytes < need) return fail(MAR_ENOMEM, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
-  { const hipError_t e_ = mar_flash_prepare(); if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes"); }
-  { const hipError_t e_ = mar_split_prepare(); if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes"); }
+  { const hipError_t e_ = d.bilinear ? mar_split_prepare(d.dk) : mar_flash_prepare(d.dk); if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes"); }
   mar_ctx* c = new (std::nothrow) mar_ctx();
   if (!c) return fail(MAR_ENOMEM, "out of host memory");
   c->cfg = *cfg; c->dm = d;

@@ -68,6 +68,7 @@ struct MarDims {
   int64_t u_max;                   // min(num_nodes + num_rels, n_occ_max)
   int32_t sort_passes, sort_bits, sort_items;  // radix sort of the gradient rows by unified id: passes, bits per pass, elements per thread
   int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
+  int32_t reduce_small;            // the reduce gives a lane group MAR_REDUCE_SMALL positions instead of one per lane
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
 };
@@ -102,11 +103,13 @@ void mar_set_error(const char* fmt, ...);
 #define MAR_METRIC_MAX_PARTS 4096
 #define MAR_METRIC_PART_BYTES 72
 
-// Positions of the row-sorted order per workgroup of the reduce.
-#define MAR_REDUCE_BLOCK 256
+// Positions of the row-sorted order per lane group of the reduce in small batches (in large ones: as many as it has lanes),
+// and per workgroup.
+#define MAR_REDUCE_SMALL 8
 
 // Lanes that move one table row as float4s.
 static inline int mar_lane_group(int dk) { return dk <= 64 ? 16 : (dk <= 128 ? 32 : 64); }
+static inline int mar_reduce_block(const MarDims& d) { return d.reduce_small ? 256 / mar_lane_group(d.dk) * MAR_REDUCE_SMALL : 256; }
 
 // ---- launchers (each returns a hipError_t from the launch) --------------------------
 hipError_t mar_launch_init(const mar_ctx* c, int fill, hipStream_t st);
@@ -156,7 +159,7 @@ hipError_t mar_launch_rank_metrics(const int32_t* ranks, int64_t n, const int32_
 int mar_flash_supported(int dk);
 int mar_flash_tile_rows(int dk, int pass);
 int mar_flash_stripe_rows(int dk, int pass);
-hipError_t mar_flash_prepare();   // once per process and device before the first contraction launch (LDS size limits)
+hipError_t mar_flash_prepare(int dk);   // before the first contraction launch of a context (LDS size limits)
 int mar_flash_wgs_per_cu(int dk, int pass);        // workgroups of a pass that a CU holds at once
 hipError_t mar_launch_flash_merge(const mar_ctx* c, const MarBatch& b, hipStream_t st);   // after pass 1: merges split stripes
 // Passes of the bilinear models (mar_split.hip): geometry for the planning of a configuration, and the launches.
@@ -169,4 +172,4 @@ static inline int mar_tile_rows(const MarDims& d, int pass) { return d.bilinear 
 // How many workgroups share one of `units` units of a pass, and the streamed tiles each takes (n_y streamed rows).
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps);
 size_t mar_split_image_bytes(int dk);
-hipError_t mar_split_prepare();
+hipError_t mar_split_prepare(int dk);

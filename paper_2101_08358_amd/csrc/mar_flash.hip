@@ -873,7 +873,7 @@ static hipError_t launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStrea
   return hipGetLastError();
 }
 
-// Kernels whose LDS exceeds the default limit of a launch must be told so once per process and device.
+// Kernels whose LDS exceeds the default limit of a launch must be told so before their first launch on a device.
 template <int NK, int NC, int VT, int TY, int XB>
 static hipError_t prepare_sized() {
   constexpr size_t lds = FwdGeom<NK, TY, 1>::LDS_BYTES;
@@ -884,7 +884,7 @@ static hipError_t prepare_sized() {
 #undef PREP
   return e;
 }
-hipError_t mar_flash_prepare() { return prepare_sized<100, 25, 0, 32, 1>(); }
+hipError_t mar_flash_prepare(int dk) { return dk / 4 > 64 ? prepare_sized<100, 25, 0, 32, 1>() : hipSuccess; }
 
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
                             hipStream_t st) {

@@ -36,10 +36,18 @@ __device__ __forceinline__ void block_totals(double& rr, unsigned long long (&hi
   }
 }
 
+__device__ __forceinline__ void write_metrics(double rr, const unsigned long long (&hit)[8], int64_t n, const MetricKs& ks, double* __restrict__ out) {
+  out[0] = n > 0 ? rr / (double)n : 0.0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) if (q < ks.num) out[1 + q] = n > 0 ? (double)hit[q] / (double)n : 0.0;
+}
+
 // Workgroup b sums the ranks of tiles b, b + gridDim.x, ...: thread t takes elements t, t + 256, ... of a
-// tile (all of a tile's loads in flight), then the 256 threads' sums are combined by a binary tree.
+// tile (all of a tile's loads in flight), then the 256 threads' sums are combined by a binary tree.  SINGLE: the ranks fit
+// one tile, and its record is the result (adding it to nothing changes no bit).
+template <bool SINGLE>
 __global__ void __launch_bounds__(256)
-k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, MetricPart* __restrict__ part) {
+k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, MetricPart* __restrict__ part, double* __restrict__ out) {
   constexpr int PER = MAR_METRIC_TILE / 256;
   double rr = 0.0;
   unsigned long long hit[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -57,7 +65,9 @@ k_rank_partial(const int32_t* __restrict__ ranks, int64_t n, MetricKs ks, Metric
     }
   }
   block_totals(rr, hit, ks.num);
-  if (threadIdx.x == 0) {
+  if (SINGLE) {
+    if (threadIdx.x == 0) write_metrics(rr, hit, n, ks, out);
+  } else if (threadIdx.x == 0) {
     MetricPart p;
     p.rr = rr;
     for (int q = 0; q < 8; ++q) p.hit[q] = hit[q];
@@ -77,11 +87,7 @@ k_rank_final(const MetricPart* __restrict__ part, int nparts, int64_t n, MetricK
     for (int q = 0; q < 8; ++q) hit[q] += p.hit[q];
   }
   block_totals(rr, hit, ks.num);
-  if (threadIdx.x == 0) {
-    out[0] = n > 0 ? rr / (double)n : 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) if (q < ks.num) out[1 + q] = n > 0 ? (double)hit[q] / (double)n : 0.0;
-  }
+  if (threadIdx.x == 0) write_metrics(rr, hit, n, ks, out);
 }
 
 // `part` holds MAR_METRIC_MAX_PARTS records.  Every record the second kernel reads is written by the first
@@ -94,7 +100,11 @@ hipError_t mar_launch_rank_metrics(const int32_t* ranks, int64_t n, const int32_
   int64_t nparts = (n + MAR_METRIC_TILE - 1) / MAR_METRIC_TILE;
   if (nparts > MAR_METRIC_MAX_PARTS) nparts = MAR_METRIC_MAX_PARTS;
   MetricPart* p = reinterpret_cast<MetricPart*>(part);
-  if (nparts > 0) hipLaunchKernelGGL(k_rank_partial, dim3((unsigned)nparts), dim3(256), 0, st, ranks, n, m, p);
+  if (nparts == 1) {
+    hipLaunchKernelGGL(k_rank_partial<true>, dim3(1), dim3(256), 0, st, ranks, n, m, p, out);
+    return hipGetLastError();
+  }
+  if (nparts > 0) hipLaunchKernelGGL(k_rank_partial<false>, dim3((unsigned)nparts), dim3(256), 0, st, ranks, n, m, p, out);
   hipLaunchKernelGGL(k_rank_final, dim3(1), dim3(256), 0, st, p, (int)nparts, n, m, out);
   return hipGetLastError();
 }

@@ -654,6 +654,7 @@ struct ReduceArgs {
   float* defer_grad;         // [unique rows][dk], or NULL: if set, a node row's summed gradient is stored here and the row is
                              // left alone (its update is applied later, by k_stage_apply); relation rows are updated as usual
   int64_t n_rows;
+  int32_t block;             // positions per workgroup
   int32_t num_nodes, dim, dk;
   float lr, eps;
 };
@@ -712,8 +713,10 @@ __device__ __forceinline__ void load_old4(const ReduceArgs& a, int32_t id, const
   th = load_row4<VEC>(emb, col, a.dim); s0 = load_row4<VEC>(st, col, a.dim);
 }
 
-// A workgroup takes MAR_REDUCE_BLOCK consecutive positions, a group of GL lanes GL of them (a "task"; the
-// lanes of a group move one row as float4s, NV per lane).  Each lane first fetches the id and the gradient row of one
+// A workgroup takes 256 / GL tasks of PPT consecutive positions, one per group of GL lanes (the lanes of a group move one
+// row as float4s, NV per lane).  PPT = GL (256 positions per workgroup) for large batches, which are bound by memory;
+// MAR_REDUCE_SMALL = BATCH or twice that for small ones, which are bound by the latency of the batches a group works
+// through one after the other and of too few workgroups.  Each lane first fetches the id and the gradient row of one
 // position of its task, and the group the ids on either side of it: equal neighbours are one segment, so the segments'
 // borders follow without further loads and no later load depends on another.
 // The task's rows are then fetched BATCH at a time -- together with the table row and accumulator row of
@@ -723,17 +726,16 @@ __device__ __forceinline__ void load_old4(const ReduceArgs& a, int32_t id, const
 // partials of its tasks in order, finishes the segments that lie inside the workgroup, and writes those
 // that cross its own borders to `carry` (slot 0: began in an earlier workgroup, slot 1: continues into the
 // next; a workgroup with a slot-1 partial appends itself to `owners`).
-template <int GL, int NV, int BATCH, bool VEC>
+template <int GL, int NV, int BATCH, bool VEC, int PPT>
 __global__ void __launch_bounds__(256) k_reduce_apply(ReduceArgs a) {
   constexpr int GPB = 256 / GL;
   __shared__ float4 s_head[GPB][GL * NV], s_tail[GPB][GL * NV];
   __shared__ int s_hs[GPB], s_tf[GPB];       // head: 0 none, 1 ends inside the task, 2 runs through it; tail: 0 / 1
   __shared__ int s_fin[GPB];                 // the head slot of this task holds a finished sum (set by the chaining step)
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
-  const int64_t P0 = (int64_t)blockIdx.x * MAR_REDUCE_BLOCK;
-  const int64_t p0 = P0 + (int64_t)grp * GL;
+  const int64_t p0 = (int64_t)blockIdx.x * (GPB * PPT) + (int64_t)grp * PPT;
   const int64_t left = a.n_rows - p0;
-  const int cnt = left < 0 ? 0 : (left < GL ? (int)left : GL);
+  const int cnt = left < 0 ? 0 : (left < PPT ? (int)left : PPT);
   const int64_t p1 = p0 + cnt;
   const int nq = a.dk >> 2;
 
@@ -904,14 +906,14 @@ k_span_apply(ReduceArgs a, const float* __restrict__ loss_part, int n_loss_part,
   const int n_owners = a.scalars[2];
   for (int o = blockIdx.x; o < n_owners; o += gridDim.x) {  // uniform over the workgroup
     const int64_t blk = a.owners[o];
-    const int64_t pe = (blk + 1) * MAR_REDUCE_BLOCK < a.n_rows ? (blk + 1) * MAR_REDUCE_BLOCK : a.n_rows;
+    const int64_t pe = (blk + 1) * a.block < a.n_rows ? (blk + 1) * a.block : a.n_rows;
     const uint32_t seg_id = a.ids[pe - 1];
     const int rank = a.rank_sorted ? a.rank_sorted[pe - 1] : 0;
     // the last block whose first position belongs to the segment: blocks blk + 1 .. last_blk do, 64 probes at a time
-    int64_t last_blk = blk, after = (a.n_rows + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
+    int64_t last_blk = blk, after = (a.n_rows + a.block - 1) / a.block;
     while (after - last_blk > 1) {
       const int64_t stepb = (after - last_blk + 63) / 64, t = last_blk + (lane + 1) * stepb;
-      const bool in = t < after && a.ids[t * MAR_REDUCE_BLOCK] == seg_id;
+      const bool in = t < after && a.ids[t * a.block] == seg_id;
       const int k = __popcll(__ballot(in));                // ids ascend: the first k probes are in
       const int64_t nxt = last_blk + (int64_t)(k + 1) * stepb;
       last_blk += k * stepb;
@@ -1199,16 +1201,19 @@ hipError_t mar_launch_reduce(const mar_ctx* c, const MarBatch& b, float* loss_ou
   a.G = L.G; a.carry = L.carry; a.ids = L.ids_sorted; a.perm = L.perm; a.rank_sorted = dbg_grad || defer_grad ? L.rank_sorted : nullptr;
   a.scalars = L.scalars; a.owners = L.owners; a.dbg_grad = dbg_grad; a.defer_grad = defer_grad; a.n_rows = b.n_pos;
   a.num_nodes = (int32_t)d.num_nodes; a.dim = d.dim; a.dk = d.dk; a.lr = c->cfg.lr; a.eps = c->cfg.eps;
-  const int64_t blocks = (b.n_pos + MAR_REDUCE_BLOCK - 1) / MAR_REDUCE_BLOCK;
+  a.block = mar_reduce_block(d);
+  const int64_t blocks = (b.n_pos + a.block - 1) / a.block;
   const dim3 grid((unsigned)blocks), grids((unsigned)(blocks < 512 ? blocks : 512)), blk(256), blks(64 * SPAN_WAVES);
   const int GL = mar_lane_group(d.dk), gpb = 256 / GL;
   const int n_loss_part = (b.n + gpb - 1) / gpb;
   const bool vec = d.dim % 4 == 0;
-#define RED(GLV, NVV, BT) do { \
-    if (vec) hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, true>), grid, blk, 0, st, a); \
-    else hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, false>), grid, blk, 0, st, a); } while (0)
+#define RED2(GLV, NVV, BT, P) do { \
+    if (vec) hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, true, P>), grid, blk, 0, st, a); \
+    else hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, false, P>), grid, blk, 0, st, a); } while (0)
+#define RED(GLV, NVV, BT) do { if (d.reduce_small) RED2(GLV, NVV, BT, MAR_REDUCE_SMALL); else RED2(GLV, NVV, BT, GLV); } while (0)
   if (GL == 16) RED(16, 1, 8); else if (GL == 32) RED(32, 1, 8); else if (d.dk <= 256) RED(64, 1, 8); else RED(64, 2, 4);
 #undef RED
+#undef RED2
   if (d.dk <= 256) {
     if (vec) hipLaunchKernelGGL((k_span_apply<1, true>), grids, blks, 0, st, a, L.loss_part, n_loss_part, loss_out);
     else hipLaunchKernelGGL((k_span_apply<1, false>), grids, blks, 0, st, a, L.loss_part, n_loss_part, loss_out);

@@ -553,16 +553,17 @@ size_t mar_split_image_bytes(int dk) { return (size_t)sp_image(sp_nk(dk)); }
 template <int NK> static hipError_t sp_prepare() {
   constexpr size_t lds = SplitGeom<NK>::LDS_BYTES;
   hipError_t e = hipSuccess;
-#define PREP(P, F) if (lds > 64 * 1024 && e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(P == 3 ? SplitGeom<NK>::LDS_BYTES3 : lds))
+#define PREP(P, F) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(P == 3 ? SplitGeom<NK>::LDS_BYTES3 : lds))
   PREP(1, true); PREP(2, true); PREP(3, true); PREP(1, false); PREP(2, false);
 #undef PREP
   return e;
 }
-hipError_t mar_split_prepare() {
-  hipError_t e = sp_prepare<12>();
-  if (e == hipSuccess) e = sp_prepare<16>();
-  if (e == hipSuccess) e = sp_prepare<25>();
-  return e;
+hipError_t mar_split_prepare(int dk) {
+  switch (sp_nk(dk)) {
+    case 16: return sp_prepare<16>();
+    case 25: return sp_prepare<25>();
+    default: static_assert(SplitGeom<12>::LDS_BYTES3 <= 64 * 1024, "narrower instantiations stay below the default limit"); return hipSuccess;
+  }
 }
 
 template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st) {
