@@ -12,12 +12,15 @@
 // SPLIT_BF16 (F16 = false): v = hi + lo in bf16 without exponents, the same three products; errors of 2^-16 .. 2^-17
 // per product.
 //
-// Softmax weights are formed as 2^(t - ref) with t = score log2(e) - e_y and an integer reference per stationary row
+// fp32 precision: softmax weights are formed as 2^(t - ref) with t = score log2(e) - e_y and an integer reference per stationary row
 // that moves only when some t exceeds it by more than 15 (it is then put 8 below the maximum): the weights stay below
 // the largest f16, values down to 2^-33 of the largest weight keep their place in hi + lo, moving the reference
 // multiplies by powers of two only, and the streamed block's exponent e_y needs no operation of its own.  The
 // reference is folded into the statistics at the end (mantissa of the sum, integer in log2 units), so parts merge
 // exactly.
+// SPLIT_BF16: hi + lo of a weight is off by up to 2^-17 of it, the same in every copy of a repeated negative, while the
+// sum keeps the weight itself.  Pass 1's reference is therefore the running maximum (moved when some t exceeds it by more
+// than 16 in natural units): a negative that dominates its row has weight 1, which bf16 holds exactly.
 //
 // Operand images come from the gather.  The images of the matrix a pass streams (pass 1 and 3: the negatives, pass 2:
 // the edge-side operands) are copied into LDS by buffer loads that write LDS directly, one tile ahead, in two
@@ -246,7 +249,7 @@ k_split(FlashArgs a) {
   v16f oacc[NO];
 #pragma unroll
   for (int cb = 0; cb < NO; ++cb) oacc[cb] = (v16f)(0.f);
-  float mref = -3.0e38f, lrun = 0.f;                      // softmax reference (log2 units, an integer) and sum
+  float mref = -3.0e38f, lrun = 0.f;                      // softmax reference (log2 units; F16: an integer) and sum
   int cnt = 0;
 
   const int ntiles_all = (n_y + TY - 1) / TY;
@@ -412,9 +415,9 @@ k_split(FlashArgs a) {
           for (int v = 1; v < 8; ++v) { a0 = fmaxf(a0, w[v]); a1 = fmaxf(a1, w[8 + v]); }
           tmax = fmaxf(a0 - e0, a1 - e1);
         }
-        if (__any(tmax > mref + 15.f)) {
+        if (__any(tmax > mref + (F16 ? 15.f : 16.f * LOG2E))) {
           const float tall = fmaxf(tmax, __shfl_xor(tmax, 32));
-          const float mnew = fmaxf(mref, __builtin_ceilf(tall) - 8.f);
+          const float mnew = fmaxf(mref, F16 ? __builtin_ceilf(tall) - 8.f : tall);
           float alpha = __builtin_amdgcn_exp2f(mref - mnew);
           asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
           lrun *= alpha;
@@ -426,7 +429,7 @@ k_split(FlashArgs a) {
           }
           mref = mnew;
         }
-        const float r0 = e0 + mref, r1 = e1 + mref;        // integers: exact
+        const float r0 = e0 + mref, r1 = e1 + mref;        // exact: integers (bf16: no exponents)
         if (PASS == 1) {
           float l0 = 0.f, l1 = 0.f;
 #pragma unroll
