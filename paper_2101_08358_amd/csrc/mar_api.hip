@@ -452,7 +452,8 @@ struct mar_pipe {
   hipStream_t s_in, s_out;
   hipEvent_t ev_call;
   PipeSlot* slots;
-  int64_t submitted, applied;  // batches submitted / batches whose update has been enqueued
+  int64_t submitted, applied;  // batches submitted / the batch behind the one whose update was enqueued last
+  int64_t drained;             // batches submitted when the last drain was called: it enqueued all their updates
 };
 
 static size_t pipe_slot_extra(const MarDims& d, char* base, PipeSlot* ps) {
@@ -539,7 +540,7 @@ extern "C" int mar_pipe_create(const mar_config* cfg, float* host_node_emb, floa
   if (!p) return fail(MAR_ENOMEM, "out of host memory");
   p->cfg = *cfg; p->dm = d; p->depth = depth;
   p->host_emb = host_node_emb; p->host_state = host_node_state; p->rel_emb = rel_emb; p->rel_state = rel_state;
-  p->s_in = p->s_out = nullptr; p->ev_call = nullptr; p->submitted = p->applied = 0;
+  p->s_in = p->s_out = nullptr; p->ev_call = nullptr; p->submitted = p->applied = p->drained = 0;
   p->slots = new (std::nothrow) PipeSlot[depth]();
   if (!p->slots) { delete p; return fail(MAR_ENOMEM, "out of host memory"); }
   hipError_t e = hipStreamCreateWithFlags(&p->s_in, hipStreamNonBlocking);
@@ -578,10 +579,10 @@ static int pipe_enqueue_update(mar_pipe* p, int64_t i, int64_t gather_of) {
   PipeSlot& ps = p->slots[i % p->depth];
   PIPE_TRY(hipStreamWaitEvent(p->s_out, ps.ev_step, 0), "update stage");
   if (gather_of >= 0) PIPE_TRY(hipStreamWaitEvent(p->s_out, p->slots[gather_of % p->depth].ev_in, 0), "update stage");
-  // a batch whose update a drain has enqueued already (a submit follows it) no longer has the staged values as the newest:
-  // everything is read from the host table
+  // The staged values of a batch whose update a drain has enqueued already are not the newest: a submit that follows the
+  // drain reads everything from the host table.
   MarStage sg = ps.sg;
-  if (i < p->applied) sg.shared = nullptr;
+  if (i < p->drained) sg.shared = nullptr;
   PIPE_TRY(mar_launch_stage_out(ps.ctx, ps.b_ids, sg, p->s_out), "update kernel");
   PIPE_TRY(hipEventRecord(ps.ev_out, p->s_out), "update stage");
   p->applied = i + 1;
@@ -642,6 +643,7 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
 extern "C" int mar_pipe_drain(mar_pipe* p, void* hip_stream) {
   if (!p) return fail(MAR_EINVAL, "pipeline is NULL");
   for (int64_t i = p->applied; i < p->submitted; ++i) { const int rc = pipe_enqueue_update(p, i, -1); if (rc) return rc; }
+  p->drained = p->submitted;
   if (p->submitted > 0)
     PIPE_TRY(hipStreamWaitEvent((hipStream_t)hip_stream, p->slots[(p->submitted - 1) % p->depth].ev_out, 0), "drain");
   return MAR_OK;

@@ -134,3 +134,73 @@ def test_more_batches_in_flight_than_are_searched_for_shared_rows():
     for g, w, name in zip(got[:4], (one, ons, ore, ors), ("node_emb", "node_state", "rel_emb", "rel_state")):
         err = np.max(np.abs(g.astype(np.float64) - w)) / np.max(np.abs(w))
         assert err <= 1e-4, (name, err)
+
+
+def _run_segments(model, V, R, dim, B, C, N, depth, tables, segments, sync=True):
+    """Submits the batches of each segment, drains after each; sync: the host waits after each drain."""
+    ne, ns, re_, rs = tables
+    dev = torch.device("cuda:0")
+    h_ne, h_ns = (torch.from_numpy(x.copy()).pin_memory() for x in (ne, ns))
+    d_re, d_rs = (torch.from_numpy(x.copy()).to(dev) for x in (re_, rs))
+    cfg = mar.MarConfig(V, R, dim, model, B, C, N, 0, 0.1, 1e-10, 0.001, 0, 0, 0)
+    nbytes = mar.mar_pipe_workspace_bytes(cfg, depth)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    pipe = mar.mar_pipe_create(cfg, h_ne, h_ns, d_re, d_rs, ws, nbytes, depth)
+    ids_stream = torch.cuda.Stream()
+    with torch.cuda.stream(ids_stream):
+        dbs = [[[torch.from_numpy(x.reshape(-1)).to(dev) for x in bt] for bt in seg] for seg in segments]
+    loss = torch.zeros(1, device=dev)
+    torch.cuda.synchronize()
+    for seg, db in zip(segments, dbs):
+        for bt, x in zip(seg, db):
+            mar.mar_pipe_submit(pipe, x[0], x[1], x[2], bt[0].shape[0], x[3], x[4], loss, ids_stream=ids_stream)
+        mar.mar_pipe_drain(pipe)
+        if sync:
+            torch.cuda.synchronize()
+    torch.cuda.synchronize()
+    out = (h_ne.numpy().copy(), h_ns.numpy().copy(), d_re.cpu().numpy(), d_rs.cpu().numpy())
+    mar.mar_pipe_destroy(pipe)
+    return out
+
+
+def _segments_oracle(model, chunk, depth, tables, segments):
+    """The order of the pipeline's stages, batch by batch: batch j reads the host rows, and behind its staging the update of
+    batch j - depth + 1 is enqueued; a drain enqueues what lies behind the newest update.  A submit that follows a drain
+    enqueues the update of batch j - depth + 1 although the drain has applied it: its gradient goes once more to the rows
+    as they are then."""
+    from oracle import step as ostep
+    ne, ns, re_, rs = (x.copy() for x in tables)
+    lr, eps = np.float32(0.1), np.float32(1e-10)
+    done, applied = [], 0
+
+    def update(i):
+        ostep.adagrad_rows(ne, ns, done[i].uniq_nodes.astype(np.int64), done[i].G_nodes, lr, eps)
+        return i + 1
+
+    for seg in segments:
+        for bt in seg:
+            j = len(done)
+            res = ostep.train_batch(model, lr, eps, chunk, ne, ns, re_, rs, *bt, apply_update=False)
+            ostep.adagrad_rows(re_, rs, res.uniq_rels.astype(np.int64), res.G_rels, lr, eps)
+            done.append(res)
+            if j - depth + 1 >= 0:
+                applied = update(j - depth + 1)
+        while applied < len(done):
+            applied = update(applied)
+    return ne, ns, re_, rs
+
+
+@pytest.mark.parametrize("depth,counts", ((2, (3, 3)), (3, (3, 4)), (3, (4, 1, 3)), (4, (5, 6)), (4, (2, 5))))
+def test_updates_after_a_drain_start_from_the_host_rows(depth, counts):
+    """Batches that a drain has applied already have newer rows on the host than were staged for them: whatever a later
+    submit or drain applies of them starts from the host table, for each of them and not only for the first."""
+    model, V, R, dim, B, C, N = mar.MODEL_DISTMULT, 4000, 5, 36, 200, 2, 50
+    ne, ns, re_, rs, batches = _setup(model, V, R, dim, B, C, N, nb=sum(counts), seed=depth, hot=0.05, state0=0.05)
+    ends = np.cumsum(counts)
+    segments = [batches[e - k:e] for e, k in zip(ends, counts)]
+    got = _run_segments(model, V, R, dim, B, C, N, depth, (ne, ns, re_, rs), segments)
+    want = _segments_oracle(model, B // C, depth, (ne, ns, re_, rs), segments)
+    for g, w, name in zip(got, want, ("node_emb", "node_state", "rel_emb", "rel_state")):
+        err = np.max(np.abs(g.astype(np.float64) - w)) / np.max(np.abs(w))
+        print(name, "%.1e" % err, flush=True)
+        assert err <= 1e-4, (name, err)
