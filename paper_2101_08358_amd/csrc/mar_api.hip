@@ -606,6 +606,9 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
   PIPE_TRY(hipEventRecord(p->ev_call, (hipStream_t)ids_stream), "submit");
   PIPE_TRY(hipStreamWaitEvent(p->s_in, p->ev_call, 0), "submit");
   if (j >= p->depth) PIPE_TRY(hipStreamWaitEvent(p->s_in, ps.ev_out, 0), "stage in");
+  // the first batch behind a drain: the drain enqueued the updates up to batch j - 1, and the staging must not run beside
+  // them (the caller need not have waited for the drain on the stream the ids come from)
+  if (j > 0 && j == p->drained) PIPE_TRY(hipStreamWaitEvent(p->s_in, p->slots[(j - 1) % p->depth].ev_out, 0), "stage in");
   const int work = n_edges > ps.b_ids.cn ? n_edges : ps.b_ids.cn;
   hipLaunchKernelGGL(k_copy_ids, dim3((work + 255) / 256), dim3(256), 0, p->s_in, src, roles == 3 ? rel : nullptr, dst, neg_src, neg_dst,
                      n_edges, ps.b_ids.cn, ps.src, ps.rel, ps.dst, ps.neg_src, ps.neg_dst);

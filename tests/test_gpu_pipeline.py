@@ -204,3 +204,15 @@ def test_updates_after_a_drain_start_from_the_host_rows(depth, counts):
         err = np.max(np.abs(g.astype(np.float64) - w)) / np.max(np.abs(w))
         print(name, "%.1e" % err, flush=True)
         assert err <= 1e-4, (name, err)
+
+
+@pytest.mark.parametrize("depth", (1, 2, 3))
+def test_a_submit_right_behind_a_drain_reads_the_drained_rows(depth):
+    """Nothing waits between a drain and the next submit, whose ids come from another stream: the staging waits for the
+    updates that the drain enqueued, so the tables have the same bits as with a wait by the host after each drain."""
+    model, V, R, dim, B, C, N = mar.MODEL_COMPLEX, 20000, 5, 100, 2000, 4, 500
+    ne, ns, re_, rs, batches = _setup(model, V, R, dim, B, C, N, nb=9, seed=depth, hot=0.2, state0=0.05)
+    segments = [batches[:3], batches[3:4], batches[4:9]]
+    got, want = (_run_segments(model, V, R, dim, B, C, N, depth, (ne, ns, re_, rs), segments, sync=sync) for sync in (False, True))
+    for g, w, name in zip(got, want, ("node_emb", "node_state", "rel_emb", "rel_state")):
+        assert np.array_equal(g, w), name
