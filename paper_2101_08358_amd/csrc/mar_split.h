@@ -51,10 +51,14 @@ __device__ __forceinline__ char* sp_row(const SplitImages& g, int cs, int row) {
   return g.base + ((size_t)cs * g.tiles + row / SP_TY) * g.img + (row % SP_TY) * g.pa;
 }
 // Exponent of a block whose largest finite magnitude has these float bits: 2^e max lies in [2^14, 2^15).  Clamped to
-// what a float power of two and the sums of a pass can hold (a block of values below 2^-66 keeps fewer bits).
+// what a float power of two and the sums of a pass can hold (a block of values below 2^-66 keeps fewer bits).  A block of
+// zeros takes the largest exponent: the softmax reference follows score log2(e) - e, and such a block, whose rows carry
+// nothing, must not move it away from the others, whose weights would lose bits to the f16 range (worst gradient row beside
+// such a block, values of 1e-5: 9e-7 off, with exponent 0 9e-3).
+#define SP_EMAX 80
 __device__ __forceinline__ int sp_exponent(int max_bits) {
   const int e = 141 - (max_bits >> 23);
-  return max_bits == 0 ? 0 : (e > 80 ? 80 : e);
+  return e > SP_EMAX ? SP_EMAX : e;
 }
 typedef _Float16 sp_h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 sp_h4 __attribute__((ext_vector_type(4)));

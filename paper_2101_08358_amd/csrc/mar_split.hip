@@ -346,14 +346,15 @@ k_split(FlashArgs a) {
         __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
       }
     }
-    // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey)
+    // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey); never 0, or a masked row's -inf would become NaN
+    // (two blocks at the largest exponent: scores below 2^-100 either way)
     float k0 = PASS == 3 ? 1.f : LOG2E, k1 = k0, e0 = 0.f, e1 = 0.f, posx_t = posx;
     if (F16) {
       const bool ybad = ye.x > 0.5f * SP_NONFINITE || ye.y > 0.5f * SP_NONFINITE;
       e0 = ye.x > 0.5f * SP_NONFINITE ? ye.x - SP_NONFINITE : ye.x;
       e1 = ye.y > 0.5f * SP_NONFINITE ? ye.y - SP_NONFINITE : ye.y;
-      k0 = __builtin_ldexpf(k0, min(126, -(int)(ex + e0)));
-      k1 = __builtin_ldexpf(k1, min(126, -(int)(ex + e1)));
+      k0 = __builtin_ldexpf(k0, max(-140, min(126, -(int)(ex + e0))));
+      k1 = __builtin_ldexpf(k1, max(-140, min(126, -(int)(ex + e1))));
       if (PASS == 3 && __any(ybad || xbad)) {              // every pair of the tile the long way
         for (int v = 0; v < 16; ++v) {
           const int y = y0 + 8 * (v >> 2) + 4 * h + (v & 3);

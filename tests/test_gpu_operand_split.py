@@ -74,3 +74,30 @@ def test_ranks_are_those_of_the_fp32_chain(dim, special):
         for got, q in ((r[:S * C], ne[src]), (r[S * C:], ne[dst])):
             want = 1 + (_chain(q[:, None, :], ne[None, :, :]) > p[:, None]).sum(1)
             assert np.array_equal(got, want), (dim, special, int((got != want).sum()))
+
+
+@pytest.mark.parametrize("small", (0.3, 1e-3, 1e-5))
+@pytest.mark.parametrize("where", ("negatives", "edges"))
+def test_a_block_of_zero_rows_beside_others(small, where):
+    """Sixteen aligned zero rows among the negatives (first pass) or the edges' destinations (second pass), the other rows of
+    the same operand being small and those of the other operand so large that scores are of order 1.  Zero rows carry
+    nothing: the softmax reference that the others' weights are formed against must not be theirs.  Every gradient row
+    within 1e-4 of its own largest entry."""
+    V, dim, B, C, N = 3000, 64, 512, 2, 200
+    rng = np.random.default_rng(3)
+    ne = rng.standard_normal((V, dim)) * small                   # 0 .. 15 zero, 16 .. 1999 small, 2000 .. large
+    ne[:16] = 0
+    ne[2000:] *= 0.25 / small ** 2
+    src, dst = rng.integers(2000, V, B).astype(np.int32), rng.integers(16, 2000, B).astype(np.int32)
+    neg_src, neg_dst = rng.integers(2000, V, (C, N)).astype(np.int32), rng.integers(16, 2000, (C, N)).astype(np.int32)
+    if where == "negatives":
+        neg_dst[:, 64:80] = np.arange(16)
+    else:
+        dst[32:48] = np.arange(16)
+    out = run_step_both(DOT, V, 1, dim, B, C, N, B, seed=9, ids=(src, np.zeros(B, np.int32), dst, neg_src, neg_dst),
+                        tables=(ne.astype(np.float32), np.zeros((1, dim), np.float32)))
+    G = out["ora"]["res"].G_nodes
+    top = np.abs(G).max(1)
+    err = np.abs(out["gpu"]["G"][:G.shape[0]] - G).max(1)[top > 0] / top[top > 0]
+    print("worst row %.1e" % err.max(), flush=True)
+    assert err.max() <= 1e-4
