@@ -239,6 +239,7 @@ k_split(FlashArgs a) {
     n2 += __shfl_xor(n2, 32);
     tolx = 2.f * sqrtf((float)dk) * 0x1p-24f * sqrtf(n2);
     if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
+    xbad |= !(fabsf(posx) <= 3.4028234663852886e38f);     // no difference to a positive score outside the range
   }
   auto exact_above = [&](int y) -> int {                   // streamed row y against this lane's edge
     const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + y];

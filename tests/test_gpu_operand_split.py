@@ -101,3 +101,38 @@ def test_a_block_of_zero_rows_beside_others(small, where):
     err = np.abs(out["gpu"]["G"][:G.shape[0]] - G).max(1)[top > 0] / top[top > 0]
     print("worst row %.1e" % err.max(), flush=True)
     assert err.max() <= 1e-4
+
+
+def _dot_ranks(ne, src, dst, C, neg_src, neg_dst):
+    """Ranks under the Dot score through the library, and those of the fp32 chain."""
+    V, dim = ne.shape
+    n, N = src.size, neg_src.shape[1]
+    tr = mar.Trainer(V, 1, dim, DOT, n, C, N, device="cuda:0", node_emb=ne, rel_emb=np.zeros((1, dim), np.float32))
+    d_src, d_dst, d_ns, d_nd = (torch.from_numpy(np.ascontiguousarray(x).reshape(-1)).to(tr.device) for x in (src, dst, neg_src, neg_dst))
+    pos = torch.zeros(n, device=tr.device)
+    ranks = torch.zeros(2 * n, dtype=torch.int32, device=tr.device)
+    mar.mar_eval_scores(tr.ctx, d_src, d_src, d_dst, n, d_ns, d_nd, pos, ranks[:n], ranks[n:])
+    torch.cuda.synchronize()
+    got, p = ranks.cpu().numpy().reshape(2, n), pos.cpu().numpy()
+    tr.close()
+    want = np.ones((2, n), np.int64)
+    with np.errstate(all="ignore"):
+        for c in range(C):
+            e = slice(c * (n // C), (c + 1) * (n // C))
+            for k, (q, neg) in enumerate(((ne[src], neg_dst), (ne[dst], neg_src))):
+                want[k, e] += (_chain(q[e][:, None, :], ne[neg[c]][None, :, :]) > p[e][:, None]).sum(1)
+    return got, want
+
+
+@pytest.mark.parametrize("dim", (36, 100, 260))
+def test_ranks_when_positive_scores_leave_the_range(dim):
+    """Rows of 1e20 with one sign each: the positive score of an edge between rows of different sign is -inf, which no
+    candidate whose score is -inf too outscores."""
+    rng = np.random.default_rng(dim)
+    V, n, C, N = 400, 96, 2, 64
+    sign = np.where(rng.random(V) < 0.5, -1, 1)
+    ne = (sign[:, None] * rng.uniform(0.5e20, 2e20, (V, dim))).astype(np.float32)
+    src, dst = (rng.integers(0, V, n).astype(np.int32) for _ in range(2))
+    neg = [rng.integers(0, V, (C, N)).astype(np.int32) for _ in range(2)]
+    got, want = _dot_ranks(ne, src, dst, C, *neg)
+    assert np.array_equal(got, want), int((got != want).sum())
