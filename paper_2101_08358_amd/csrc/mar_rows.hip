@@ -161,7 +161,7 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
   static_assert(!IMG || (RE % SP_EB == 0 && RN % SP_EB == 0 && SP_EB % E == 0 && SP_EB % P == 0), "whole 16-row blocks per workgroup");
   constexpr int MB = (RN > RE ? RN : RE) / 16 + 1;
   __shared__ int s_max[2][MB];                   // per 16-row block: bits of the largest finite magnitude (two operands of an edge block)
-  __shared__ int s_bad[2][MB];                   // the block holds an infinity or a NaN, or (evaluation) a row far below its largest
+  __shared__ int s_bad[2][MB];                   // the block holds an infinity or a NaN
   __shared__ int s_n2[MB];                       // evaluation: bits of the largest squared row norm of a block of negatives
   const bool eval = rank_dst != nullptr;         // uniform
   if (IMG && F16) {
@@ -176,12 +176,6 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
     mx = group_max<GL>(mx);
     if (l == 0) atomicMax(&s_max[which][rw / SP_EB], __float_as_int(mx));
     if (bad) s_bad[which][rw / SP_EB] = 1;
-  };
-  // Evaluation, between the maxima and the exponents: a row whose largest value is below 2^-14 of its block's keeps
-  // fewer bits than a comparison of its scores needs; its block is settled the long way (see k_split).
-  auto flag_small = [&](int which, int rw, float row_max) {
-    row_max = group_max<GL>(row_max);
-    if (l == 0 && row_max > 0.f && row_max < 0x1p-14f * __int_as_float(s_max[which][rw / SP_EB])) s_bad[which][rw / SP_EB] = 1;
   };
   if ((int)blockIdx.x < nbB) {
     const int chunk = IMG ? blockIdx.x / wpc_e : 0;
@@ -242,16 +236,6 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
       put_max(MAR_SIDE_DST, grp * E, mxu, badu);
       put_max(MAR_SIDE_SRC, grp * E, mxw, badw);
       __syncthreads();
-      if (eval) {
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-          float mu = 0.f, mw = 0.f;
-#pragma unroll
-          for (int v = 0; v < NV; ++v) { mu = finite_max4(mu, u[j][v]); mw = finite_max4(mw, w[j][v]); }
-          if (r0 + j < nr) { flag_small(MAR_SIDE_DST, grp * E, mu); flag_small(MAR_SIDE_SRC, grp * E, mw); }
-        }
-        __syncthreads();
-      }
     }
     float scu = 1.f, scw = 1.f;
     if (IMG && F16) {
@@ -340,23 +324,13 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
         }
       }
       __syncthreads();
-      if (eval) {
-#pragma unroll
-        for (int j = 0; j < P; ++j) {
-          float m = 0.f;
-#pragma unroll
-          for (int v = 0; v < NV; ++v) m = finite_max4(m, x[j][v]);
-          if (r0 + j < nr) flag_small(0, grp * P, m);
-        }
-        __syncthreads();
-      }
       const int e = sp_exponent(s_max[0][grp * P / SP_EB]);
       scale = ldexpf(1.f, e);
       if (l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles)
         ki.exps[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = (float)e + (s_bad[0][grp * P / SP_EB] ? SP_NONFINITE : 0.f);
       if (eval && l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles) {
         // bound of the scaled rows' norms: from the largest norm, or where its square leaves the range, from the scale
-        const float n2 = __int_as_float(s_n2[grp * P / SP_EB]), most = sqrtf((float)dk) * 0x1p15f;
+        const float n2 = __int_as_float(s_n2[grp * P / SP_EB]), most = s_max[0][grp * P / SP_EB] ? sqrtf((float)dk) * 0x1p15f : 0.f;
         ki.norms[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = n2 > 1e-25f && n2 < 1e37f ? fminf(most, 1.001f * sqrtf(n2) * scale) : most;
       }
     }

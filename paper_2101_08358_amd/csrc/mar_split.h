@@ -31,11 +31,10 @@ static inline int sp_tiles(int rows) { return (rows + SP_TY - 1) / SP_TY; }
 struct SplitImages {
   char* base;
   float* exps;          // [chunk-sides][2 tiles] exponent of every 16-row block (+ SP_NONFINITE)
-  float* norms;         // [chunk-sides][2 tiles] bound of its scaled rows' norms (evaluation)
+  float* norms;         // [chunk-sides][2 tiles] bound of its scaled rows' norms, 0 for a block of zeros (evaluation)
   int32_t pa, plane, img, tiles, dkp;
 };
-// Added to the exponent of a block that holds an infinity or a NaN (its exponent is that of its finite values) or, in
-// evaluation, a row too far below the block's largest.
+// Added to the exponent of a block that holds an infinity or a NaN (its exponent is that of its finite values).
 #define SP_NONFINITE 1024.f
 static inline SplitImages sp_images(char* base, float* exps, float* norms, int dk, int rows_per_chunk) {
   const int nk = sp_nk(dk);

@@ -220,10 +220,13 @@ k_split(FlashArgs a) {
     xbad = ex > 0.5f * SP_NONFINITE;
     if (xbad) ex -= SP_NONFINITE;
   }
-  // Pass 3.  A comparison is close if the score is within 2 sqrt(dk) 2^-24 |q| |n| of the positive's.  The rounding
-  // errors of a chain of dk steps are independent and each below 2^-24 |q| |n| (the partial sums are), 0.3 of that on
-  // average: the bound is seven standard deviations where all products have one sign, and ten times that where they
-  // do not.
+  // Pass 3.  A comparison is close if the score is within sqrt(dk) (2^-23 |q| + 2^-25) |n| of the positive's, q and n
+  // scaled by their blocks' exponents, |n| the largest of the block.  The rounding errors of a chain of dk steps are
+  // independent and each below 2^-24 |q| |n| (the partial sums are), 0.3 of that on average: the first term is seven
+  // standard deviations where all products have one sign, and ten times that where they do not.  hi + lo holds a value to
+  // 2^-24 of itself and no better than 2^-25: over a row that is the second term, which matters where q is far below its
+  // block's largest row (or its block's exponent at the limit); for n it lies inside the first, the block's |n| being
+  // 2^14 at least.  A zero row's scores are exactly zero.
   float posx = 0.f, tolx = 0.f;
   const float* qrow = nullptr;
   int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
@@ -237,8 +240,16 @@ k_split(FlashArgs a) {
       for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
     }
     n2 += __shfl_xor(n2, 32);
-    tolx = 2.f * sqrtf((float)dk) * 0x1p-24f * sqrtf(n2);
     if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
+    bool zero = n2 == 0.f;
+    if (xv && zero) {                                      // or merely below the f16 range
+      for (int k = 4 * h; k < dk; k += 8) {
+        const float4 q = *reinterpret_cast<const float4*>(qrow + k);
+        zero = zero && q.x == 0.f && q.y == 0.f && q.z == 0.f && q.w == 0.f;
+      }
+    }
+    zero = (__shfl_xor(zero ? 1 : 0, 32) & (zero ? 1 : 0)) != 0;
+    tolx = zero ? 0.f : sqrtf((float)dk) * (0x1p-23f * sqrtf(n2) + 0x1p-25f);
     xbad |= !(fabsf(posx) <= 3.4028234663852886e38f);     // no difference to a positive score outside the range
   }
   auto exact_above = [&](int y) -> int {                   // streamed row y against this lane's edge
@@ -379,12 +390,14 @@ k_split(FlashArgs a) {
         cnt += dif > 0.f ? 1 : 0;
         if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
       }
-      const float tol0 = tolx * yn.x * k0, tol1 = tolx * yn.y * k1;
-      if (__any(xv && (near0 <= tol0 || near1 <= tol1))) {
+      // scores at the ends of the exponents' range: every comparison is close
+      const bool end0 = fabsf(ex + e0) > 126.f, end1 = fabsf(ex + e1) > 126.f;
+      const float tol0 = tolx * yn.x * (end0 ? __builtin_inff() : k0), tol1 = tolx * yn.y * (end1 ? __builtin_inff() : k1);
+      if (__any(xv && (near0 < tol0 || near1 < tol1))) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx_t);
-          if (xv && fabsf(dif) <= (v < 8 ? tol0 : tol1)) {
+          if (xv && fabsf(dif) < (v < 8 ? tol0 : tol1)) {
             const int y = y0 + 8 * (v / 4) + 4 * h + v % 4;
             cnt -= dif > 0.f ? 1 : 0;
             if (npend < SP_PEND) pend[256 * npend++] = y; else cnt += exact_above(y);

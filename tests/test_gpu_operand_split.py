@@ -136,3 +136,37 @@ def test_ranks_when_positive_scores_leave_the_range(dim):
     neg = [rng.integers(0, V, (C, N)).astype(np.int32) for _ in range(2)]
     got, want = _dot_ranks(ne, src, dst, C, *neg)
     assert np.array_equal(got, want), int((got != want).sum())
+
+
+@pytest.mark.parametrize("size", (2.0 ** -60, 2.0 ** -95, 2.0 ** -110))
+def test_ranks_of_edges_with_tiny_rows(size):
+    """Edges from tiny rows to rows of ordinary size: the tiny operand's block exponent ends at its limit and the scaled
+    values keep fewer bits, so more comparisons are close."""
+    rng = np.random.default_rng(8)
+    V, dim, n, C, N = 600, 100, 128, 2, 300
+    ne = (rng.standard_normal((V, dim)) * 0.3).astype(np.float32)
+    ne[:200] *= np.float32(size)
+    src, dst = rng.integers(0, 200, n).astype(np.int32), rng.integers(200, V, n).astype(np.int32)
+    neg = [rng.integers(200, V, (C, N)).astype(np.int32) for _ in range(2)]
+    got, want = _dot_ranks(ne, src, dst, C, *neg)
+    assert np.array_equal(got, want), int((got != want).sum())
+
+
+@pytest.mark.parametrize("model", (DISTMULT, DOT))
+def test_ranks_with_rows_of_very_different_size_in_one_block(model):
+    """Rows 2^-40 .. 1 of the largest among edges and candidates (DistMult: the relation rows too), some of them zero, every
+    node a candidate: each rank is the one of the fp32 chain."""
+    rng = np.random.default_rng(model)
+    V, R, dim, n, C = 300, 9, 100, 128, 2
+    ne, re_ = (rng.standard_normal((k, dim)).astype(np.float32) * np.exp2(-rng.integers(0, 41, (k, 1))).astype(np.float32) for k in (V, R))
+    ne[rng.random(V) < 0.05], re_[0] = 0, 0
+    src, dst = (rng.integers(0, V, n).astype(np.int32) for _ in range(2))
+    rel = rng.integers(0, R, n).astype(np.int32)
+    tr = mar.Trainer(V, R, dim, model, n, C, V, device="cuda:0", node_emb=ne, rel_emb=re_)
+    tr.neg_src = tr.neg_dst = torch.arange(V, dtype=torch.int32, device=tr.device).repeat(C)
+    pos, rd, rs = (x.cpu().numpy() for x in tr.eval_scores(*(torch.from_numpy(x).to(tr.device) for x in (src, rel, dst))))
+    tr.close()
+    r = re_[rel] if model == DISTMULT else np.float32(1)
+    for got, q in ((rd, ne[src] * r), (rs, r * ne[dst])):
+        want = 1 + (_chain(q[:, None, :], ne[None, :, :]) > pos[:, None]).sum(1)
+        assert np.array_equal(got, want), int((got != want).sum())
