@@ -213,9 +213,10 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.Kimg = (char*)take(bl ? ktiles * mar_split_image_bytes(d.dk) : 0);
   l.Qimg = (char*)take(bl ? qtiles * mar_split_image_bytes(d.dk) : 0);
   l.Gx = (float*)take((size_t)(d.rem2.k - 1) * (size_t)d.rem2.rows * dk * 4);
-  l.G = (float*)take(n_pos * dk * 4);
-  // evaluation's norms, and with bf16 images (which have no exponents) its exponents, lie in the gradient rows that it has
-  // no other use for
+  const size_t eval_floats = bl ? ktiles * (2 + 2 + MAR_SPLIT_TILE_ROWS) + qtiles * 2 : 0;
+  l.G = (float*)take((n_pos * dk > eval_floats ? n_pos * dk : eval_floats) * 4);
+  // evaluation's norms, and with bf16 images (which have no exponents) its exponents, lie in the gradient rows, for which it
+  // has no other use
   const bool own_exp = bl && !d.split_bf16;
   l.Kexp = own_exp ? (float*)take(ktiles * 8) : l.G;
   l.Qexp = own_exp ? (float*)take(qtiles * 8) : l.G + ktiles * 2;

@@ -38,9 +38,9 @@ struct FlashArgs {
   // split-precision passes: bf16 hi/lo images of the streamed matrix, [2*nchunks][yimg_tiles][image bytes]
   const char* yimg; int32_t yimg_tiles;
   const char* ximg; int32_t ximg_tiles;   // the same of the stationary matrix
-  // evaluation of the bilinear models: fp32 edge-side operands [2][B][dk], the node table and the negatives' ids, from
-  // which close comparisons are settled
-  const float* qrows; const float* ynorm; const float* table; const int32_t* neg_dst; const int32_t* neg_src; int32_t dim;
+  // evaluation of the bilinear models: fp32 edge-side operands [2][B][dk], the node table and the ids, from which
+  // close comparisons are settled
+  const float *qrows, *ynorm, *table; const int32_t *neg_dst, *neg_src, *src, *dst; int32_t dim;
   const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
 

@@ -303,7 +303,7 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
     }
     float scale = 1.f;
     if (IMG && F16) {
-      float mx = 0.f;
+      float mx = 0.f, norm2[P];
       bool bad = false;
 #pragma unroll
       for (int j = 0; j < P; ++j) {
@@ -319,8 +319,8 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
           float n2 = 0.f;
 #pragma unroll
           for (int v = 0; v < NV; ++v) add_dot<VEC, false>(n2, x[j][v], x[j][v]);
-          n2 = group_sum<GL>(n2);
-          if (l == 0 && r0 + j < nr) atomicMax(&s_n2[grp * P / SP_EB], __float_as_int(fabsf(n2)));
+          norm2[j] = group_sum<GL>(n2);
+          if (l == 0 && r0 + j < nr) atomicMax(&s_n2[grp * P / SP_EB], __float_as_int(fabsf(norm2[j])));
         }
       }
       __syncthreads();
@@ -328,10 +328,21 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
       scale = ldexpf(1.f, e);
       if (l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles)
         ki.exps[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = (float)e + (s_bad[0][grp * P / SP_EB] ? SP_NONFINITE : 0.f);
-      if (eval && l == 0 && r0 % SP_EB == 0 && r0 / SP_TY < ki.tiles) {
-        // bound of the scaled rows' norms: from the largest norm, or where its square leaves the range, from the scale
-        const float n2 = __int_as_float(s_n2[grp * P / SP_EB]), most = s_max[0][grp * P / SP_EB] ? sqrtf((float)dk) * 0x1p15f : 0.f;
-        ki.norms[(size_t)cs * ki.tiles * 2 + r0 / SP_EB] = n2 > 1e-25f && n2 < 1e37f ? fminf(most, 1.001f * sqrtf(n2) * scale) : most;
+      if (eval && r0 / SP_TY < ki.tiles) {
+        // bounds of the scaled rows' norms: from the norm (a square that underflows is below 1e-25), or where its square
+        // leaves the range, from the scale
+        const float most = s_max[0][grp * P / SP_EB] ? sqrtf((float)dk) * 0x1p15f : 0.f;
+        auto bound = [&](float n2) { return n2 < 1e37f ? fminf(most, 1.001f * sqrtf(fmaxf(n2, 1e-25f)) * scale) : most; };
+        float* norms = ki.norms + ((size_t)cs * ki.tiles + r0 / SP_TY) * SP_NORMS;
+        if (l == 0 && r0 % SP_EB == 0) norms[r0 % SP_TY / SP_EB] = bound(__int_as_float(s_n2[grp * P / SP_EB]));
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+          float m = 0.f;
+#pragma unroll
+          for (int v = 0; v < NV; ++v) m = finite_max4(m, x[j][v]);
+          m = group_max<GL>(m);
+          if (l == 0) norms[2 + r0 % SP_TY + j] = m > 0.f ? bound(norm2[j]) : -1.f;
+        }
       }
     }
 #pragma unroll

@@ -25,13 +25,15 @@ constexpr int sp_nk(int dk) { return dk <= 32 ? 2 : (dk <= 64 ? 4 : (dk <= 96 ? 
 constexpr int sp_nb(int nk) { return (nk + 1) / 2; }
 constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(nk); }
 constexpr int sp_image(int nk) { return (2 * sp_plane(nk) + 1023) / 1024 * 1024; }
+constexpr int SP_NORMS = 2 + SP_TY;
 static inline int sp_tiles(int rows) { return (rows + SP_TY - 1) / SP_TY; }
 
 // Where the gather writes an image set: [chunk-sides][tiles][IMG].
 struct SplitImages {
   char* base;
   float* exps;          // [chunk-sides][2 tiles] exponent of every 16-row block (+ SP_NONFINITE)
-  float* norms;         // [chunk-sides][2 tiles] bound of its scaled rows' norms, 0 for a block of zeros (evaluation)
+  float* norms;         // evaluation: [chunk-sides][tiles][SP_NORMS] bounds of the scaled rows' norms: of the two blocks (0: all
+                        // zero), then of the 32 rows (-1: a zero row)
   int32_t pa, plane, img, tiles, dkp;
 };
 // Added to the exponent of a block that holds an infinity or a NaN (its exponent is that of its finite values).

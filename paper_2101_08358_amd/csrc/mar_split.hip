@@ -87,7 +87,8 @@ __device__ __forceinline__ v4s lds_read_tr(const char* p) {
 }
 __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 
-#define SP_PEND 8                                          // close comparisons a lane of pass 3 keeps for the end
+#define SP_PEND 6                                          // candidates whose comparisons a lane of pass 3 keeps for the end (5 bits of a word each)
+#define SP_FULL 8                                          // added to their number: this lane takes no more (above SP_PEND)
 template <int NK>
 struct SplitGeom {
   static constexpr int NB = sp_nb(NK);
@@ -96,7 +97,7 @@ struct SplitGeom {
   static constexpr int IMG = sp_image(NK);
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
   static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
-  static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + SP_PEND * 256 * 4;   // two images, and the lanes' pending comparisons
+  static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };
 
 // Evaluation compares scores with the positive's, and where the two are within rounding of one another the outcome
@@ -142,18 +143,46 @@ __device__ __forceinline__ float sp_exact_score(const float* __restrict__ q, con
   for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
   return s;
 }
-// The same, one column at a time: rare, and inside the tile loop, where it must not cost registers.
-__device__ __forceinline__ float sp_exact_score_slow(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
-  float s = 0.f;
-  const int n = (min(chain, dim) + 15) & ~15;
-#pragma unroll 1
-  for (int t = 0; t < n; ++t) {
-    const int k = (t & ~15) + 4 * (t & 3) + ((t & 15) >> 2);
-    if (k < dim) s = __builtin_fmaf(y[k], q[k], s);
+// Columns k .. k+3 of a row, zeros from column n on (VEC: n is a multiple of 4).
+template <bool VEC> __device__ __forceinline__ float4 sp_row_cols(const float* __restrict__ row, int k, int n) {
+  if (VEC) {
+    const float4 v = *reinterpret_cast<const float4*>(row + (k < n ? k : 0));
+    return k < n ? v : make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  float4 v;
+  v.x = k < n ? row[k] : 0.f; v.y = k + 1 < n ? row[k + 1] : 0.f; v.z = k + 2 < n ? row[k + 2] : 0.f; v.w = k + 3 < n ? row[k + 3] : 0.f;
+  return v;
+}
+// A whole tile settled: the wave's 32 edges (fp32 operands q0, q1 of edges i and 16 + i; i = lane % 16, G = lane / 16)
+// against 32 candidates (rows y0, y1 of candidates i and 16 + i) on v_mfma_f32_16x16x4_f32 itself, in the order above:
+// in step j of a 16-column block lane group G holds column 4 G + j of it.  acc[y half][x half]: register r is candidate
+// 4 G + r against edge i.  16 matrix instructions and four 16-byte loads a lane per 16 columns.  All 14,951 nodes as
+// candidates, 100 floats, half of the rows equal: 1,050 us; one comparison after the other 16,700, as fp32 contraction
+// throughout 1,110, no two rows equal 229.  (20,000 edges, 1,000 candidates of 400 floats, half equal: 1,075 us, 25,000
+// and 355; 233 without.  One wave per SIMD hides little of the loads.)
+template <bool VEC>
+__device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, const float* __restrict__ q1, const float* __restrict__ y0,
+                                              const float* __restrict__ y1, int G, int dim, int dk, int chain, v4f (&acc)[2][2]) {
+  const int nb = (min(chain, dim) + 15) / 16;
 #pragma unroll 1
-  for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
-  return s;
+  for (int b = 0; b < nb; ++b) {
+    const int k = 16 * b + 4 * G;
+    const float4 ya = sp_row_cols<VEC>(y0, k, dim), yb = sp_row_cols<VEC>(y1, k, dim);
+    const float4 qa = sp_row_cols<true>(q0, k, dk), qb = sp_row_cols<true>(q1, k, dk);
+    const float a0[4] = {ya.x, ya.y, ya.z, ya.w}, a1[4] = {yb.x, yb.y, yb.z, yb.w};
+    const float b0[4] = {qa.x, qa.y, qa.z, qa.w}, b1[4] = {qb.x, qb.y, qb.z, qb.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      acc[0][0] = mfma16(a0[j], b0[j], acc[0][0]); acc[0][1] = mfma16(a0[j], b1[j], acc[0][1]);
+      acc[1][0] = mfma16(a1[j], b0[j], acc[1][0]); acc[1][1] = mfma16(a1[j], b1[j], acc[1][1]);
+    }
+  }
+  if (chain < dim) {                                       // at most four columns are left: one step, a column per lane group
+    const int k = chain + G;
+    const float a0 = k < dim ? y0[k] : 0.f, a1 = k < dim ? y1[k] : 0.f, b0 = k < dim ? q0[k] : 0.f, b1 = k < dim ? q1[k] : 0.f;
+    acc[0][0] = mfma16(a0, b0, acc[0][0]); acc[0][1] = mfma16(a0, b1, acc[0][1]);
+    acc[1][0] = mfma16(a1, b0, acc[1][0]); acc[1][1] = mfma16(a1, b1, acc[1][1]);
+  }
 }
 
 #ifndef SP_PD
@@ -230,7 +259,7 @@ k_split(FlashArgs a) {
   float posx = 0.f, tolx = 0.f;
   const float* qrow = nullptr;
   int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
-  int npend = 0;
+  int npend = 0;                                           // pending candidates; + SP_FULL: no more are taken
   if (PASS == 3) {
     float n2 = 0.f;
 #pragma unroll
@@ -252,9 +281,33 @@ k_split(FlashArgs a) {
     tolx = zero ? 0.f : sqrtf((float)dk) * (0x1p-23f * sqrtf(n2) + 0x1p-25f);
     xbad |= !(fabsf(posx) <= 3.4028234663852886e38f);     // no difference to a positive score outside the range
   }
-  auto exact_above = [&](int y) -> int {                   // streamed row y against this lane's edge
-    const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + y];
-    return sp_exact_score_slow(qrow, a.table + (size_t)id * a.dim, a.dim, sp_chain(dk)) > posx ? 1 : 0;
+  const int32_t* const cand = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src) + (size_t)c * a.N;   // ids of the streamed rows
+  int own = -1, nown = 0;                                  // pass 3: the replaced endpoint's id, how often it came up close
+  if (PASS == 3 && xv) own = (side == MAR_SIDE_DST ? a.dst : a.src)[(size_t)c * a.S + x];
+  // Pass 3, all lanes of the wave: candidates of the tile at y0 that score above this lane's edge, settled as a whole (in
+  // the lanes of the wave's first half).
+  auto exact_tile = [&](int y0) -> int {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                          // what follows is rare: nothing of it is kept across tiles
+    const int i = ln & 15, G = ln >> 4, x0 = u.stripe * SP_SR + wave * 32;
+    const float* qr = a.qrows + q_base * dk;
+    v4f acc[2][2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k >> 1][k & 1] = (v4f)(0.f);
+    const float *q0 = qr + (size_t)min(x0 + i, n_x - 1) * dk, *q1 = qr + (size_t)min(x0 + 16 + i, n_x - 1) * dk;
+    const float *r0 = a.table + (size_t)cand[min(y0 + i, n_y - 1)] * a.dim, *r1 = a.table + (size_t)cand[min(y0 + 16 + i, n_y - 1)] * a.dim;
+    if (a.dim % 4 == 0) sp_exact_tile<true>(q0, q1, r0, r1, G, a.dim, dk, sp_chain(dk), acc);
+    else sp_exact_tile<false>(q0, q1, r0, r1, G, a.dim, dk, sp_chain(dk), acc);
+    int above[2] = {0, 0};
+#pragma unroll
+    for (int xb = 0; xb < 2; ++xb) {
+      const float p = __shfl(posx, 16 * xb + i);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) above[xb] += y0 + 16 * (k >> 2) + 4 * G + (k & 3) < n_y && acc[k >> 2][xb][k & 3] > p ? 1 : 0;
+      above[xb] += __shfl_xor(above[xb], 16);
+      above[xb] += __shfl_xor(above[xb], 32);
+    }
+    return h == 0 ? ((G & 1) ? above[1] : above[0]) : 0;
   };
 
   constexpr int NO = PASS == 3 ? 1 : NB;
@@ -278,7 +331,7 @@ k_split(FlashArgs a) {
   const int f_row = threadIdx.x % TY;
   const size_t ml_stride = (size_t)2 * a.B;               // rows per part of pass 1's statistics
   float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f), st_ml = make_float2(0.f, 0.f);
-  const BufRsrc normsrc = buf_rsrc(PASS == 3 ? (const void*)(a.ynorm + (size_t)cs * a.yimg_tiles * 2) : (const void*)ybase, PASS == 3 ? (uint32_t)a.yimg_tiles * 8 : 0u);
+  const BufRsrc normsrc = buf_rsrc(PASS == 3 ? (const void*)(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS) : (const void*)ybase, PASS == 3 ? (uint32_t)a.yimg_tiles * (SP_NORMS * 4) : 0u);
   int token = 0;
   auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
     const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
@@ -287,7 +340,7 @@ k_split(FlashArgs a) {
   };
   auto dma_fence = [&](int t) {
     ye_next = buf_load2(expsrc, token, t * 8);
-    if (PASS == 3) yn_next = buf_load2(normsrc, token, t * 8);
+    if (PASS == 3) yn_next = buf_load2(normsrc, token, t * (SP_NORMS * 4));
     if (PASS == 2) st_ml = buf_load2(mlsrc, f_row * 8 + token, t * TY * 8);
   };
   auto dma_land = [&](int t, int buf) {
@@ -360,21 +413,15 @@ k_split(FlashArgs a) {
     }
     // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey); never 0, or a masked row's -inf would become NaN
     // (two blocks at the largest exponent: scores below 2^-100 either way)
-    float k0 = PASS == 3 ? 1.f : LOG2E, k1 = k0, e0 = 0.f, e1 = 0.f, posx_t = posx;
+    float k0 = PASS == 3 ? 1.f : LOG2E, k1 = k0, e0 = 0.f, e1 = 0.f;
+    bool settle = false;                                   // pass 3, uniform over the wave: the tile is settled as a whole
     if (F16) {
       const bool ybad = ye.x > 0.5f * SP_NONFINITE || ye.y > 0.5f * SP_NONFINITE;
       e0 = ye.x > 0.5f * SP_NONFINITE ? ye.x - SP_NONFINITE : ye.x;
       e1 = ye.y > 0.5f * SP_NONFINITE ? ye.y - SP_NONFINITE : ye.y;
       k0 = __builtin_ldexpf(k0, max(-140, min(126, -(int)(ex + e0))));
       k1 = __builtin_ldexpf(k1, max(-140, min(126, -(int)(ex + e1))));
-      if (PASS == 3 && __any(ybad || xbad)) {              // every pair of the tile the long way
-        for (int v = 0; v < 16; ++v) {
-          const int y = y0 + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (xv && y < n_y) cnt += exact_above(y);
-        }
-        k0 = k1 = 0.f;
-        posx_t = __builtin_inff();
-      }
+      settle = PASS == 3 && __any(ybad || xbad);
     }
     if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
 #pragma unroll
@@ -383,27 +430,86 @@ k_split(FlashArgs a) {
       }
     }
     if (PASS == 3) {
-      float near0 = __builtin_inff(), near1 = near0;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx_t);
-        cnt += dif > 0.f ? 1 : 0;
-        if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
-      }
-      // scores at the ends of the exponents' range: every comparison is close
-      const bool end0 = fabsf(ex + e0) > 126.f, end1 = fabsf(ex + e1) > 126.f;
-      const float tol0 = tolx * yn.x * (end0 ? __builtin_inff() : k0), tol1 = tolx * yn.y * (end1 ? __builtin_inff() : k1);
-      if (__any(xv && (near0 < tol0 || near1 < tol1))) {
+      int ct = 0;
+      if (!settle) {
+        float near0 = __builtin_inff(), near1 = near0;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx_t);
-          if (xv && fabsf(dif) < (v < 8 ? tol0 : tol1)) {
-            const int y = y0 + 8 * (v / 4) + 4 * h + v % 4;
-            cnt -= dif > 0.f ? 1 : 0;
-            if (npend < SP_PEND) pend[256 * npend++] = y; else cnt += exact_above(y);
+          const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx);
+          ct += dif > 0.f ? 1 : 0;
+          if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
+        }
+        // scores at the ends of the exponents' range: every comparison is close
+        const float t0 = tolx * (fabsf(ex + e0) > 126.f ? __builtin_inff() : k0), t1 = tolx * (fabsf(ex + e1) > 126.f ? __builtin_inff() : k1);
+        const float tol0 = t0 * yn.x, tol1 = t1 * yn.y;
+        if (__any(xv && (near0 < tol0 || near1 < tol1))) {
+          // An edge's close candidates are mostly its own endpoint, as often as the candidates hold it: it is counted, and
+          // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
+          // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 75 to 88 us, 1,200 to 3,100 with
+          // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
+          unsigned close = 0u, same = 0u;                  // bit v: pair v is close / is with the own endpoint
+          float p = posx;
+          asm volatile("" : "+v"(p));                      // the comparisons are made again, one after the other: kept, their lane
+                                                           // masks would take 32 scalar registers
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p);
+            const bool cl = fabsf(dif) < (v < 8 ? tol0 : tol1);
+            close |= cl ? 1u << v : 0u;
+            ct -= cl && dif > 0.f ? 1 : 0;
+            asm volatile("" : "+v"(close), "+v"(ct));
+          }
+          if (!xv) close = 0u;
+          // Several in a lane, or again and again: most are copies of the own endpoint; the others are looked at with their
+          // own norms in place of the block's largest (2^-25 of q is at most a quarter of tolx).
+          settle = __any(close != 0u && npend >= SP_FULL);
+          if (!settle && __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2))) {
+            const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              same |= __shfl(id_t, 8 * (v / 4) + 4 * h + v % 4) == own ? 1u << v : 0u;
+              asm volatile("" : "+v"(same));
+            }
+            same &= close;
+            if (__any((close & ~same) != 0u)) {
+              const float nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4));
+#pragma unroll
+              for (int v = 0; v < 16; ++v) {
+                const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, 8 * (v / 4) + 4 * h + v % 4);
+                const bool far = ((close & ~same) >> v & 1u) && !(fabsf(dif) < (v < 8 ? t0 : t1) * (nv + 0.25f) && nv >= 0.f);
+                close &= far ? ~(1u << v) : ~0u;
+                ct += far && dif > 0.f ? 1 : 0;
+                asm volatile("" : "+v"(close), "+v"(ct));
+              }
+            }
+          }
+          unsigned rest = close & ~same, times = 0u;       // times: 5 bits per pending candidate, how often the tile has it
+          int npend_t = npend, nown_t = nown + __popc(same);
+          bool over = rest != 0u && npend >= SP_PEND;
+          settle = settle || __any(over);
+          if (!settle) {
+            for (; rest; rest &= rest - 1u) {
+              const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
+              int j = npend_t;
+#pragma unroll
+              for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
+              const bool put = id != own && j < SP_PEND;
+              if (put && j == npend_t) { pend[256 * j] = id; pend[256 * (SP_PEND + j)] = 0; ++npend_t; }
+              times += put ? 1u << (5 * j) : 0u;
+              nown_t += id == own ? 1 : 0;
+              over |= id != own && !put;
+            }
+            settle = __any(over);
+            if (over) npend += SP_FULL;                    // so many more at once: later tiles are settled without another look
+          }
+          if (!settle) {
+            nown = nown_t;
+            npend = npend_t;
+            for (int j = 0; times; ++j, times >>= 5) pend[256 * (SP_PEND + j)] += (int)(times & 31u);
           }
         }
       }
+      cnt += settle ? exact_tile(y0) : ct;
     } else {
       // -- weights of the lane's 16 pairs, split; register v <-> row y0 + 8 (v / 4) + 4h + v % 4
       float w[16];
@@ -498,11 +604,11 @@ k_split(FlashArgs a) {
   // ---- epilogue
   if (PASS == 3) {
     constexpr int UB = NK <= 16 ? 4 : 8;                   // 16-column blocks whose loads are in flight at once
-    for (int i = 0; i < npend; ++i) {
-      const int32_t id = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src)[(size_t)c * a.N + pend[256 * i]];
+    for (int i = nown ? -1 : 0; i < npend % SP_FULL; ++i) {
+      const int32_t id = i < 0 ? own : pend[256 * i];
       const float* yrow = a.table + (size_t)id * a.dim;
       const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
-      cnt += s > posx ? 1 : 0;
+      if (s > posx) cnt += i < 0 ? nown : pend[256 * (SP_PEND + i)];
     }
     cnt += __shfl_xor(cnt, 32);
     if (h == 0 && xv && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x, cnt);
