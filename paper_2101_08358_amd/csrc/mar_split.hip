@@ -445,17 +445,17 @@ k_split(FlashArgs a) {
         if (__any(xv && (near0 < tol0 || near1 < tol1))) {
           // An edge's close candidates are mostly its own endpoint, as often as the candidates hold it: it is counted, and
           // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
-          // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 75 to 88 us, 1,200 to 3,100 with
+          // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 90 us, 1,200 to 3,100 with
           // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
           unsigned close = 0u, same = 0u;                  // bit v: pair v is close / is with the own endpoint
           float p = posx;
           asm volatile("" : "+v"(p));                      // the comparisons are made again, one after the other: kept, their lane
                                                            // masks would take 32 scalar registers
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
+          for (int v = 15; v >= 0; --v) {
             const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p);
             const bool cl = fabsf(dif) < (v < 8 ? tol0 : tol1);
-            close |= cl ? 1u << v : 0u;
+            close = close + close + (cl ? 1u : 0u);
             ct -= cl && dif > 0.f ? 1 : 0;
             asm volatile("" : "+v"(close), "+v"(ct));
           }
@@ -463,7 +463,13 @@ k_split(FlashArgs a) {
           // Several in a lane, or again and again: most are copies of the own endpoint; the others are looked at with their
           // own norms in place of the block's largest (2^-25 of q is at most a quarter of tolx).
           settle = __any(close != 0u && npend >= SP_FULL);
-          if (!settle && __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2))) {
+          const bool many = __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2));
+          if (!settle && !many && close) {                 // one at most: by its place, without a look at its id
+            const int v = __ffs((int)close) - 1;
+            pend[256 * npend] = ~(y0 + 8 * (v >> 2) + 4 * h + (v & 3));
+            pend[256 * (SP_PEND + npend++)] = 1;
+          }
+          if (!settle && many) {
             const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -482,30 +488,30 @@ k_split(FlashArgs a) {
                 asm volatile("" : "+v"(close), "+v"(ct));
               }
             }
-          }
-          unsigned rest = close & ~same, times = 0u;       // times: 5 bits per pending candidate, how often the tile has it
-          int npend_t = npend, nown_t = nown + __popc(same);
-          bool over = rest != 0u && npend >= SP_PEND;
-          settle = settle || __any(over);
-          if (!settle) {
-            for (; rest; rest &= rest - 1u) {
-              const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
-              int j = npend_t;
-#pragma unroll
-              for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
-              const bool put = id != own && j < SP_PEND;
-              if (put && j == npend_t) { pend[256 * j] = id; pend[256 * (SP_PEND + j)] = 0; ++npend_t; }
-              times += put ? 1u << (5 * j) : 0u;
-              nown_t += id == own ? 1 : 0;
-              over |= id != own && !put;
-            }
+            unsigned rest = close & ~same, times = 0u;     // times: 5 bits per pending candidate, how often the tile has it
+            int npend_t = npend, nown_t = nown + __popc(same);
+            bool over = rest != 0u && npend >= SP_PEND;
             settle = __any(over);
-            if (over) npend += SP_FULL;                    // so many more at once: later tiles are settled without another look
-          }
-          if (!settle) {
-            nown = nown_t;
-            npend = npend_t;
-            for (int j = 0; times; ++j, times >>= 5) pend[256 * (SP_PEND + j)] += (int)(times & 31u);
+            if (!settle) {
+              for (; rest; rest &= rest - 1u) {
+                const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
+                int j = npend_t;
+#pragma unroll
+                for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
+                const bool put = id != own && j < SP_PEND;
+                if (put && j == npend_t) { pend[256 * j] = id; pend[256 * (SP_PEND + j)] = 0; ++npend_t; }
+                times += put ? 1u << (5 * j) : 0u;
+                nown_t += id == own ? 1 : 0;
+                over |= id != own && !put;
+              }
+              settle = __any(over);
+              if (over) npend += SP_FULL;                  // so many more at once: later tiles are settled without another look
+            }
+            if (!settle) {
+              nown = nown_t;
+              npend = npend_t;
+              for (int j = 0; times; ++j, times >>= 5) pend[256 * (SP_PEND + j)] += (int)(times & 31u);
+            }
           }
         }
       }
@@ -605,7 +611,7 @@ k_split(FlashArgs a) {
   if (PASS == 3) {
     constexpr int UB = NK <= 16 ? 4 : 8;                   // 16-column blocks whose loads are in flight at once
     for (int i = nown ? -1 : 0; i < npend % SP_FULL; ++i) {
-      const int32_t id = i < 0 ? own : pend[256 * i];
+      const int e = i < 0 ? own : pend[256 * i], id = e < 0 ? cand[~e] : e;
       const float* yrow = a.table + (size_t)id * a.dim;
       const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
       if (s > posx) cnt += i < 0 ? nown : pend[256 * (SP_PEND + i)];
