@@ -36,12 +36,13 @@ static int hip_fail(hipError_t e, const char* what) {
 static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass); }
 
 // Small batches give too few (chunk-side, stripe) units to fill 256 CUs: several workgroups share a unit, each
-// streaming a slice of the other matrix.  TransE: until a pass has at least MAR_FLASH_TARGET_WGS workgroups; pass 1
-// then takes the number of parts with the least work on the busiest CU, a part costing its tiles and one more (10,000
-// edges, 100 floats: 4 parts 106 us, 2 parts 121, 8 parts 116).  Bilinear models: as many parts as the least estimated time of the busiest CU asks
-// for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its first tile and its
-// rows (pass 3, whose tiles are half the work and whose close comparisons are settled at the end: eight); a CU that holds
-// one of two possible workgroups runs it at about 0.6 of its full rate.
+// streaming a slice of the other matrix.  fp32 instructions: until a pass has at least MAR_FLASH_TARGET_WGS workgroups;
+// passes 1 and 3 then take the number of parts with the least work on the busiest CU, a part costing its tiles and one
+// more (10,000 edges, 100 floats: 4 parts 106 us, 2 parts 121, 8 parts 116), in pass 3 two more (52 x 101 edges, 200
+// candidates of 400 floats: 1 part 48 us, 4 parts 60).  16-bit instructions: as many parts as the least estimated time
+// of the busiest CU asks for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its
+// first tile and its rows (pass 3, whose tiles are half the work and whose close comparisons are settled at the end:
+// eight); a CU that holds one of two possible workgroups runs it at about 0.6 of its full rate.
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps) {
   const int ty = mar_tile_rows(d, pass);
   const int ntiles = (n_y + ty - 1) / ty;
@@ -50,10 +51,10 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
     want = (MAR_FLASH_TARGET_WGS + units - 1) / units;
     if (want > MAR_MAX_PARTS) want = MAR_MAX_PARTS;
     if (want > ntiles) want = ntiles;
-    if (pass == 1 && want > 1) {
+    if (pass != 2 && want > 1) {
       long best = 1L << 60;
       for (long k = 1; k <= MAR_MAX_PARTS && k <= ntiles; ++k) {
-        const long cost = (units * k + 255) / 256 * ((ntiles + k - 1) / k + 1);
+        const long cost = (units * k + 255) / 256 * ((ntiles + k - 1) / k + (pass == 3 ? 2 : 1));
         if (cost < best) { best = cost; want = k; }
       }
     }
@@ -101,6 +102,19 @@ static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, in
   r->tps = (int32_t)((ntiles + k - 1) / k);
   r->k = (int32_t)((ntiles + r->tps - 1) / r->tps);
   r->rows = (int64_t)rem * sr;
+}
+
+// Evaluation of the bilinear models: on images and 16-bit products (mar_split.hip), or on dense fp32 operands and fp32
+// matrix instructions (k_flash, PASS 4), whose gather writes no images and whose two kernels are a third of the code to be
+// fetched.  What the images cost goes with a chunk's rows, S edges and N candidates, what the faster products save with
+// its S N pairs, so the line is one of S N / (S + N); and where all pairs together are few, latency decides.  Measured over
+// 16 to 400 floats, 1 to 100 chunks of 100 to 1,000 edges, 50 to 1,000 candidates (fp32 / images, us, 100 and 400 floats):
+// 20 x 400 edges, 100 candidates 18 / 24 and 41 / 54; 100 x 100, 300: 32 / 37 and 111 / 113; 100 x 300, 600: 90 / 82 and
+// 361 / 341; 100 x 1,000, 1,000: 374 / 235 and 1,577 / 1,021.  With 200 and 2 million no point is more than 3% slower than
+// fp32 throughout, and the mean is 2.4% off the better of the two at every point.  Ranks are the same bits either way.
+bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
+  const double S = b.n < d.S ? b.n : d.S, N = d.N;
+  return d.bilinear && (S * N <= 200.0 * (S + N) || (double)b.n * N <= 2.0e6);
 }
 
 static int check_config(const mar_config* cfg, MarDims* d) {
@@ -250,7 +264,11 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
   if (!workspace || ((uintptr_t)workspace & 255)) return fail(MAR_EINVAL, "workspace must be non-NULL and 256-byte aligned");
   const size_t need = carve(d, nullptr, nullptr);
   if (workspace_bytes < need) return fail(MAR_ENOMEM, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
-  { const hipError_t e_ = d.bilinear ? mar_split_prepare(d.dk) : mar_flash_prepare(d.dk); if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes"); }
+  {
+    hipError_t e_ = mar_flash_prepare(d.dk);
+    if (e_ == hipSuccess && d.bilinear) e_ = mar_split_prepare(d.dk);
+    if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes");
+  }
   mar_ctx* c = new (std::nothrow) mar_ctx();
   if (!c) return fail(MAR_ENOMEM, "out of host memory");
   c->cfg = *cfg; c->dm = d;

@@ -28,7 +28,7 @@ struct MarLayout {
   float*    kk;           // [2][chunks*N] squared norms of Km rows (TransE)
   float*    pos;          // [batch] positive scores
   float*    lse;          // [2][batch] log-sum-exp per edge and side
-  float*    gQ;           // [sy1][2][batch][dk] per-part unnormalised gradient w.r.t. Q rows
+  float*    gQ;           // [sy1][2][batch][dk] per-part unnormalised gradient w.r.t. Q rows; bilinear models' evaluation: fp32 operands
   float*    ml;           // [sy1][2][batch][2] per-part softmax reference (bilinear models: in log2 units) and sum
   float*    gQx;          // [rem1.k - 1][rem1.rows][dk] parts 1.. of the stripes that are split to fill the last round
   float*    mlx;          // [rem1.k - 1][rem1.rows][2]
@@ -42,7 +42,7 @@ struct MarLayout {
   float*    Knorm;        // evaluation: bounds of the norms of Kimg's scaled rows, per 16-row block and per row
   float*    Gx;           // [rem2.k - 1][rem2.rows][dk] parts 1.. of pass 2's split stripes (bilinear models)
   float*    G;            // [roles*n + 2*cn*sy2][dk] gradient rows: edge-side occurrence k < roles*n at row k, part i
-                          // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i
+                          // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i; bilinear models' evaluation: the negatives' fp32 rows, or exponents and norms
   float*    carry;        // [reduce blocks][2][dk] partial sums of segments that cross workgroup borders
   float*    loss_part;    // per-block partial loss sums
   void*     metric_part;  // [MAR_METRIC_MAX_PARTS] partial records of the rank metrics
@@ -132,6 +132,8 @@ hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, int ranks, hipS
 // rank_dst / rank_src (evaluation): set to 1
 hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
                            hipStream_t st);
+// Small evaluations of the bilinear models run on dense fp32 operands and fp32 matrix instructions (see mar_api.hip).
+bool mar_eval_dense(const MarDims& d, const MarBatch& b);
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
                             hipStream_t st);
 hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, hipStream_t st);

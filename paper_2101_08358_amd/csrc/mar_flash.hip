@@ -16,8 +16,8 @@
 // they were formed with (one float per edge and 16 negatives): fp32 matrix throughput is ~20 flop
 // per HBM byte on this chip while recomputing a score costs 2d flops, so k_flash_bwd reads them
 // back, scales them by exp(reference - lse) and runs only the second product, with the roles of Q
-// and K swapped.  Evaluation (PASS 3) only counts negatives scoring above
-// the positive.  TransE uses |q - n|^2 = |q|^2 + |n|^2 - 2 q.n for the scores (pairs for which that expansion
+// and K swapped.  Evaluation only counts negatives scoring above the positive: PASS 3 for TransE, PASS 4 for small
+// evaluations of the bilinear models, whose training runs in mar_split.hip.  TransE uses |q - n|^2 = |q|^2 + |n|^2 - 2 q.n for the scores (pairs for which that expansion
 // cancels are recomputed from the differences) and W = P / distance.
 #include <type_traits>
 
@@ -116,7 +116,8 @@ struct StageMap {
   static_assert(!PO2 || TY % RPS == 0, "tile rows must be a multiple of the rows per staging step");
 };
 
-// PASS: 1 scores + online softmax + gQ (training), 3 rank counts (evaluation; ranks start at 1 and parts of a stripe add their counts).
+// PASS: 1 scores + online softmax + gQ (training, TransE), 3 rank counts (evaluation; ranks start at 1 and parts of a stripe
+// add their counts), 4 rank counts of the bilinear models, whose scores are the products themselves (small evaluations).
 // XB: 16-row x-blocks per wave (a workgroup's stripe has 64*XB stationary rows); every LDS
 // fragment of Y then feeds XB matrix instructions.
 // LDS reads run one phase ahead of the matrix instructions that consume them: the first
@@ -191,8 +192,8 @@ k_flash(FlashArgs a) {
       xf[b][4 * N16 + j] = (xv[b] && col < dk) ? xrow[b][col] : 0.f;
     }
     xnorm[b] = 0.f; posx[b] = 0.f;
-    xnorm[b] = xv[b] ? a.xx[x_base + x[b]] : 0.f;
-    if (PASS == 3) posx[b] = xv[b] ? a.pos[(size_t)c * a.S + x[b]] : 0.f;
+    if (PASS != 4) xnorm[b] = xv[b] ? a.xx[x_base + x[b]] : 0.f;
+    if (PASS >= 3) posx[b] = xv[b] ? a.pos[(size_t)c * a.S + x[b]] : 0.f;
   }
 
   // Output columns [0, 16*NC) of the second product go through 16x16 matrix blocks; with VT the last
@@ -241,7 +242,7 @@ k_flash(FlashArgs a) {
   // meets zero fragments of the stationary rows in the score product and produces output columns that are
   // never stored.
   const BufRsrc ysrc = buf_rsrc(a.Y + y_base * dk, (uint32_t)n_y * dk * 4);
-  const BufRsrc yysrc = buf_rsrc(a.yy + y_base, (uint32_t)n_y * 4);
+  const BufRsrc yysrc = buf_rsrc((PASS == 4 ? a.Y : a.yy) + y_base, (uint32_t)n_y * 4);   // (PASS 4 has no norms: any place that can be read)
   int s_gofs[SM::PO2 ? 1 : NU];                            // wide rows: one offset per slot, kept in registers
   if (SM::PO2) s_gofs[0] = (s_r0 * dk + s_col) * 4;
   else {
@@ -338,7 +339,7 @@ k_flash(FlashArgs a) {
       const float* ycol = &tile[yl * PITCH];
       // row 0 of the second product's A operand, fetched under the score product
       float ya[NC > 0 ? NC : 1];
-      if (PASS != 3) load_orow<NC>(ycol, m, ya);
+      if (PASS < 3) load_orow<NC>(ycol, m, ya);
       // -- T[y][x]: lane (g, m), register r holds y = yb*16 + 4g + r, x = m
       v4f tacc[XB];
 #pragma unroll
@@ -376,7 +377,10 @@ k_flash(FlashArgs a) {
 #pragma unroll
       for (int b = 0; b < XB; ++b) {
         float sc[4], dist[4];
-        {
+        if (PASS == 4) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sc[r] = tacc[b][r];
+        } else {
           // |q - n|^2 = |q|^2 + |n|^2 - 2 q.n cancels when n is close to q: its rounding error is of the size of
           // 2^-22 (|q|^2 + |n|^2).  Pairs whose expanded value falls below 2^-8 of that sum (the expansion is
           // then left with fewer than ~14 good bits) are recomputed from the differences q_k - n_k themselves:
@@ -430,7 +434,7 @@ k_flash(FlashArgs a) {
         for (int r = 0; r < 4; ++r) {
           if (masked && y0 + yl + r >= n_y) sc[r] = -__builtin_inff();
         }
-        if (PASS == 3) {
+        if (PASS >= 3) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) cnt[b] += sc[r] > posx[b] ? 1 : 0;
         } else if (PASS == 1) {
@@ -455,7 +459,7 @@ k_flash(FlashArgs a) {
           for (int r = 0; r < 4; ++r) w[b][r] = __expf(sc[r] - mrun[b]);
           lrun[b] += (w[b][0] + w[b][1]) + (w[b][2] + w[b][3]);
         }
-        if (PASS != 3) {
+        if (PASS < 3) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) w[b][r] = dist[r] > 0.f ? w[b][r] / dist[r] : 0.f;
           wsum[b] += (w[b][0] + w[b][1]) + (w[b][2] + w[b][3]);
@@ -474,7 +478,7 @@ k_flash(FlashArgs a) {
       // the compiler from sinking the reads down to their uses, where their latency would be exposed)
       if (more) load_head(yb + 1);
       __builtin_amdgcn_sched_barrier(0);
-      if (PASS != 3) {
+      if (PASS < 3) {
         // -- O^T[c][x] += sum_y Y[y][c] W[y][x]: A = Y fragment (row c), B = W (lane x)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -535,7 +539,7 @@ k_flash(FlashArgs a) {
   }
 #pragma unroll
   for (int b = 0; b < XB; ++b) {
-    if (PASS == 3) {
+    if (PASS >= 3) {
       int cn = cnt[b];
       cn += __shfl_xor(cn, 16);
       cn += __shfl_xor(cn, 32);
@@ -867,6 +871,7 @@ static hipError_t launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStrea
     if (dma) hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, DM>), grid, dim3(256), lds_dma, st, a); \
     else hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, 0>), grid, dim3(256), lds_reg, st, a); } while (0)
   if (pass == 1) FL(1);
+  else if (pass == 4) FL(4);
   else if (pass == 2) hipLaunchKernelGGL((k_flash_bwd<NK, BNC, BVT, BTY, BXB>), grid, dim3(256), 0, st, a);
   else FL(3);
 #undef FL
@@ -880,7 +885,7 @@ static hipError_t prepare_sized() {
   if (lds <= 64 * 1024) return hipSuccess;
   hipError_t e = hipSuccess;
 #define PREP(P) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_flash<NK, NC, VT, TY, XB, P, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
-  PREP(1); PREP(3);
+  PREP(1); PREP(3); PREP(4);
 #undef PREP
   return e;
 }
@@ -888,10 +893,13 @@ hipError_t mar_flash_prepare(int dk) { return dk / 4 > 64 ? prepare_sized<100, 2
 
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
                             hipStream_t st) {
-  const MarDims& d = c->dm;
   const MarLayout& L = c->L;
+  const bool dense = pass == 3 && mar_eval_dense(c->dm, b);
+  MarDims d = c->dm;
+  if (dense) d.bilinear = 0;                               // geometry and parts of the fp32 kernel
   FlashArgs a = {};
   a.X = pass == 2 ? L.Km : L.Q;  a.Y = pass == 2 ? L.Q : L.Km;   // stationary / streamed matrix
+  if (dense) { a.X = L.gQ; a.Y = L.G; }
   a.xx = L.qq; a.yy = L.kk;
   a.ml = L.ml; a.pos = L.pos; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
   a.T = L.T; a.R = L.R; a.tpitch = (d.N + 127) & ~127; a.trows = (d.S + 63) & ~63;
@@ -921,6 +929,7 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   a.wslots = (a.whole_units * a.sy + 7) / 8;
   a.rslots = ((a.units - a.whole_units) * a.rem_k + 7) / 8;
   const dim3 grid(8u * (unsigned)(a.wslots + a.rslots));
+  if (dense) pass = 4;
   if (d.bilinear) return mar_split_launch(a, pass, f16, grid, st);
   const int nk = d.dk / 4;
 #ifndef MAR_BWD_TAIL_MFMA

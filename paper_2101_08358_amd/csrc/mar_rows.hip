@@ -28,7 +28,7 @@ template <int GL> __device__ __forceinline__ float group_sum(float v) {
 //     side SRC (negatives replace s): b_ej = <q, m_j>,  q = r*d,            conj(r).d
 //   for TransE the scores are -|q - n_j| with q = s + r and q = d - r; also the positive score.
 // Negative blocks bring the negatives' rows into the layout the contraction reads.
-// TransE: dense fp32 matrices, one row after the other.  Bilinear models: hi/lo images (mar_split.h); a workgroup takes
+// Dense fp32 matrices, one row after the other, or hi/lo images (mar_split.h); for images a workgroup takes
 // 16, 32 or 64 consecutive rows of one chunk (whole 16-row blocks, so a block's exponent is found through LDS), the
 // rows of the chunk's last tile beyond its own being written as zeros.
 // A lane group issues the loads of all its rows (E edges, P negatives) before the first use: the gathers are bound by
@@ -36,7 +36,9 @@ template <int GL> __device__ __forceinline__ float group_sum(float v) {
 // A lane holds NV float4s of a row.  VEC (dim is a multiple of 4): float4 v holds columns 4 (l + GL v) .. +3; for ComplEx
 // columns 2 (l + GL v), +1 of the real half and of the imaginary half (re, re, im, im).  Otherwise element c of float4 v
 // is column l + GL (4 v + c); for ComplEx columns l + GL 2v and l + GL (2v + 1) of either half (re, re, im, im).
-// MODEL: the score function, resolved at compile time.  BF16: the images hold bf16 parts without exponents.
+// MODEL: the score function, resolved at compile time.  FORM: images of scaled f16 parts, images of bf16 parts without
+// exponents, or dense matrices (TransE; small evaluations of the bilinear models).
+constexpr int PREP_F16 = 0, PREP_BF16 = 1, PREP_DENSE = 2;
 template <int GL, bool VEC, bool CPLX>
 __device__ __forceinline__ float4 load_cols(const float* __restrict__ row, int l, int v, int dim) {
   float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -149,12 +151,12 @@ __device__ __forceinline__ void store_dense_row(float* row, const float4 (&v)[NV
 constexpr int prep_edges(int gl, bool img) { return img && gl == 64 ? 4 : 2; }
 constexpr int PREP_NEGS = 4;
 
-template <int GL, int NV, bool VEC, int MODEL, bool BF16>
+template <int GL, int NV, bool VEC, int MODEL, int FORM>
 __global__ void __launch_bounds__(256)
 k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* __restrict__ Km, float* __restrict__ qq,
        float* __restrict__ kk, float* __restrict__ pos, float* __restrict__ pos_user, int32_t* __restrict__ rank_dst,
        int32_t* __restrict__ rank_src, SplitImages qi, SplitImages ki) {
-  constexpr bool IMG = MODEL != MAR_MODEL_TRANSE, CPLX = MODEL == MAR_MODEL_COMPLEX, F16 = !BF16;
+  constexpr bool IMG = FORM != PREP_DENSE, CPLX = MODEL == MAR_MODEL_COMPLEX, F16 = FORM == PREP_F16;
   constexpr int GPB = 256 / GL;                  // lane groups per block
   constexpr int E = prep_edges(GL, IMG), P = PREP_NEGS;
   constexpr int RE = GPB * E, RN = GPB * P;      // rows per workgroup
@@ -261,7 +263,7 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
           store_image_row<GL, NV, VEC, CPLX, F16>(qi, sp_row(qi, 2 * chunk + MAR_SIDE_SRC, row), w[j], scw, l, dim);
         }
       }
-      if (valid && (!IMG || Q)) {                            // TransE; evaluation of the bilinear models
+      if (valid && (!IMG || Q)) {                            // dense; evaluation
         store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_DST * a.B + e) * dk, u[j], l, dim, dk);
         store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_SRC * a.B + e) * dk, w[j], l, dim, dk);
       }
@@ -1092,19 +1094,21 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
   return a;
 }
 
-template <int GL, int NV, int MODEL, bool BF16>
+template <int GL, int NV, int MODEL, int FORM>
 static void launch_prep(const RowArgs& a, const MarLayout& L, float* pos_out, int32_t* rank_dst, int32_t* rank_src, const SplitImages& qi,
                         const SplitImages& ki, hipStream_t st) {
-  constexpr bool img = MODEL != MAR_MODEL_TRANSE;
+  constexpr bool img = FORM != PREP_DENSE;
   constexpr int gpb = 256 / GL, re = gpb * prep_edges(GL, img), rn = gpb * PREP_NEGS;
   const int wpc_e = (qi.tiles * SP_TY + re - 1) / re, wpc_n = (ki.tiles * SP_TY + rn - 1) / rn;
   const int nchunks = a.cn / a.N;
   const int nbB = img ? nchunks * wpc_e : (a.n + re - 1) / re;
   const int nbC = img ? 2 * nchunks * wpc_n : (2 * a.cn + rn - 1) / rn;
   const dim3 grid(nbB + nbC), blk(256);
-  float* q = img ? (rank_dst ? L.gQ : nullptr) : L.Q;        // evaluation keeps the fp32 operands for close comparisons
-  if (a.dim % 4 == 0) hipLaunchKernelGGL((k_prep<GL, NV, true, MODEL, BF16>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, L.Km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
-  else hipLaunchKernelGGL((k_prep<GL, NV, false, MODEL, BF16>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, L.Km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
+  // evaluation keeps the fp32 operands for close comparisons, or (dense) works on them: they lie in the gradients' places
+  float* q = MODEL == MAR_MODEL_TRANSE ? L.Q : (rank_dst ? L.gQ : nullptr);
+  float* km = MODEL == MAR_MODEL_TRANSE ? L.Km : L.G;
+  if (a.dim % 4 == 0) hipLaunchKernelGGL((k_prep<GL, NV, true, MODEL, FORM>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
+  else hipLaunchKernelGGL((k_prep<GL, NV, false, MODEL, FORM>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
 }
 
 hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
@@ -1113,17 +1117,20 @@ hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, 
   RowArgs a = row_args(c, b);
   const SplitImages qi = sp_images(L.Qimg, L.Qexp, nullptr, a.dk, c->dm.S), ki = sp_images(L.Kimg, L.Kexp, L.Knorm, a.dk, c->dm.N);
   const int GL = mar_lane_group(a.dk);
+  const int form = rank_dst && mar_eval_dense(c->dm, b) ? PREP_DENSE : (bf16 ? PREP_BF16 : PREP_F16);
+#define PREP3(GLV, NVV, M) do { \
+    if (form == PREP_F16) launch_prep<GLV, NVV, M, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+    else if (form == PREP_BF16) launch_prep<GLV, NVV, M, PREP_BF16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+    else launch_prep<GLV, NVV, M, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); } while (0)
 #define PREP(GLV, NVV) do { switch (a.model) { \
-    case MAR_MODEL_DISTMULT: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_DISTMULT, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-                             else launch_prep<GLV, NVV, MAR_MODEL_DISTMULT, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
-    case MAR_MODEL_COMPLEX: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_COMPLEX, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-                            else launch_prep<GLV, NVV, MAR_MODEL_COMPLEX, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
-    case MAR_MODEL_TRANSE: launch_prep<GLV, NVV, MAR_MODEL_TRANSE, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
-    default: if (bf16) launch_prep<GLV, NVV, MAR_MODEL_DOT, true>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-             else launch_prep<GLV, NVV, MAR_MODEL_DOT, false>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; } } while (0)
+    case MAR_MODEL_DISTMULT: PREP3(GLV, NVV, MAR_MODEL_DISTMULT); break; \
+    case MAR_MODEL_COMPLEX: PREP3(GLV, NVV, MAR_MODEL_COMPLEX); break; \
+    case MAR_MODEL_TRANSE: launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
+    default: PREP3(GLV, NVV, MAR_MODEL_DOT); break; } } while (0)
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
   if (GL == 16) PREP(16, 1); else if (GL == 32) PREP(32, 1); else if (a.dk <= 256) PREP(64, 1); else PREP(64, 2);
 #undef PREP
+#undef PREP3
   return hipGetLastError();
 }
 

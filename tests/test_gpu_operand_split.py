@@ -103,6 +103,18 @@ def test_a_block_of_zero_rows_beside_others(small, where):
     assert err.max() <= 1e-4
 
 
+def _above(q, y, p):
+    """Candidates whose score, the fp32 chain of `_chain`, is above the edge's: q [edges, d], y [candidates, d], p [edges]."""
+    d = q.shape[1]
+    chain = 48 if d <= 52 else (96 if d <= 100 else 400)
+    order = [16 * b + 4 * g + i for b in range((min(chain, d) + 15) // 16) for i in range(4) for g in range(4)]
+    q, y = (torch.from_numpy(np.ascontiguousarray(x.T)).to("cuda:0").double() for x in (q, y))
+    s = torch.zeros((q.shape[1], y.shape[1]), device="cuda:0")
+    for k in [k for k in order if k < d] + list(range(chain, d)):
+        s = (q[k][:, None] * y[k][None, :] + s).float()
+    return (s > torch.from_numpy(p).to("cuda:0")[:, None]).sum(1).cpu().numpy()
+
+
 def _dot_ranks(ne, src, dst, C, neg_src, neg_dst):
     """Ranks under the Dot score through the library, and those of the fp32 chain."""
     V, dim = ne.shape
@@ -116,20 +128,24 @@ def _dot_ranks(ne, src, dst, C, neg_src, neg_dst):
     got, p = ranks.cpu().numpy().reshape(2, n), pos.cpu().numpy()
     tr.close()
     want = np.ones((2, n), np.int64)
-    with np.errstate(all="ignore"):
-        for c in range(C):
-            e = slice(c * (n // C), (c + 1) * (n // C))
-            for k, (q, neg) in enumerate(((ne[src], neg_dst), (ne[dst], neg_src))):
-                want[k, e] += (_chain(q[e][:, None, :], ne[neg[c]][None, :, :]) > p[e][:, None]).sum(1)
+    for c in range(C):
+        e = slice(c * (n // C), (c + 1) * (n // C))
+        for k, (q, neg) in enumerate(((ne[src], neg_dst), (ne[dst], neg_src))):
+            want[k, e] += _above(q[e], ne[neg[c]], p[e])
     return got, want
 
 
+# Two chunks of 1,100 edges against some 1,000 candidates run on the images; small evaluations on dense fp32 operands.
+S_IMG = 1100
+
+
+@pytest.mark.parametrize("n,N", ((2 * 48, 64), (2 * S_IMG, 960)))
 @pytest.mark.parametrize("dim", (36, 100, 260))
-def test_ranks_when_positive_scores_leave_the_range(dim):
+def test_ranks_when_positive_scores_leave_the_range(dim, n, N):
     """Rows of 1e20 with one sign each: the positive score of an edge between rows of different sign is -inf, which no
     candidate whose score is -inf too outscores."""
     rng = np.random.default_rng(dim)
-    V, n, C, N = 400, 96, 2, 64
+    V, C = 400, 2
     sign = np.where(rng.random(V) < 0.5, -1, 1)
     ne = (sign[:, None] * rng.uniform(0.5e20, 2e20, (V, dim))).astype(np.float32)
     src, dst = (rng.integers(0, V, n).astype(np.int32) for _ in range(2))
@@ -138,12 +154,13 @@ def test_ranks_when_positive_scores_leave_the_range(dim):
     assert np.array_equal(got, want), int((got != want).sum())
 
 
+@pytest.mark.parametrize("n,N", ((2 * 64, 300), (2 * S_IMG, 960)))
 @pytest.mark.parametrize("size", (2.0 ** -60, 2.0 ** -95, 2.0 ** -110))
-def test_ranks_of_edges_with_tiny_rows(size):
+def test_ranks_of_edges_with_tiny_rows(size, n, N):
     """Edges from tiny rows to rows of ordinary size: the tiny operand's block exponent ends at its limit and the scaled
     values keep fewer bits, so more comparisons are close."""
     rng = np.random.default_rng(8)
-    V, dim, n, C, N = 600, 100, 128, 2, 300
+    V, dim, C = 600, 100, 2
     ne = (rng.standard_normal((V, dim)) * 0.3).astype(np.float32)
     ne[:200] *= np.float32(size)
     src, dst = rng.integers(0, 200, n).astype(np.int32), rng.integers(200, V, n).astype(np.int32)
@@ -152,12 +169,13 @@ def test_ranks_of_edges_with_tiny_rows(size):
     assert np.array_equal(got, want), int((got != want).sum())
 
 
+@pytest.mark.parametrize("n,V", ((2 * 64, 300), (2 * S_IMG, 990)))
 @pytest.mark.parametrize("model", (DISTMULT, DOT))
-def test_ranks_with_rows_of_very_different_size_in_one_block(model):
+def test_ranks_with_rows_of_very_different_size_in_one_block(model, n, V):
     """Rows 2^-40 .. 1 of the largest among edges and candidates (DistMult: the relation rows too), some of them zero, every
     node a candidate: each rank is the one of the fp32 chain."""
     rng = np.random.default_rng(model)
-    V, R, dim, n, C = 300, 9, 100, 128, 2
+    R, dim, C = 9, 100, 2
     ne, re_ = (rng.standard_normal((k, dim)).astype(np.float32) * np.exp2(-rng.integers(0, 41, (k, 1))).astype(np.float32) for k in (V, R))
     ne[rng.random(V) < 0.05], re_[0] = 0, 0
     src, dst = (rng.integers(0, V, n).astype(np.int32) for _ in range(2))
@@ -168,23 +186,25 @@ def test_ranks_with_rows_of_very_different_size_in_one_block(model):
     tr.close()
     r = re_[rel] if model == DISTMULT else np.float32(1)
     for got, q in ((rd, ne[src] * r), (rs, r * ne[dst])):
-        want = 1 + (_chain(q[:, None, :], ne[None, :, :]) > pos[:, None]).sum(1)
+        want = 1 + _above(q, ne, pos)
         assert np.array_equal(got, want), int((got != want).sum())
 
 
-@pytest.mark.parametrize("dim,N", ((20, 33), (50, 100), (75, 65), (99, 64), (100, 200), (128, 95), (190, 64), (256, 70), (400, 97)))
-@pytest.mark.parametrize("ties", ("one node", "equal rows", "all", "two edges"))
+@pytest.mark.parametrize("dim,N", ((20, 961), (50, 1000), (75, 965), (99, 992), (100, 1000), (128, 991), (190, 964), (256, 970), (400, 997), (100, 70)))
+@pytest.mark.parametrize("ties", ("one node", "equal rows", "all", "two edges", "not finite"))
 def test_ranks_where_most_comparisons_are_close(dim, N, ties):
     """More close comparisons than an edge keeps one by one: candidates that are the edge's own endpoint again and again
-    (counted), rows equal to it under other ids (whole tiles settled), every row of the table equal, and two edges of a
-    tile only.  Ranks are those of the fp32 chain; candidate counts end inside a tile."""
+    (counted), rows equal to it under other ids (whole tiles settled), every row of the table equal, two edges of a tile
+    only, and rows with infinities and NaN.  Ranks are those of the fp32 chain; candidate counts end inside a tile."""
     rng = np.random.default_rng(dim)
-    V, n, C = 300, 2 * 70, 2
+    V, n, C = 300, 2 * (S_IMG if N > 70 else 70), 2
     ne = (rng.standard_normal((V, dim)) * 0.3).astype(np.float32)
     if ties == "equal rows":
         ne[20:150] = ne[20]
     if ties == "all":
         ne[:] = ne[0]
+    if ties == "not finite":
+        ne[30, 0], ne[31, dim // 2], ne[160, 1], ne[161] = np.inf, np.nan, -np.inf, 0.0
     src, dst = (rng.integers(20, 150, n).astype(np.int32) for _ in range(2))
     if ties == "one node":
         dst[:], src[n // 2:] = 25, 26
@@ -196,6 +216,30 @@ def test_ranks_where_most_comparisons_are_close(dim, N, ties):
         src[[3, 19]], dst[[3, 19]] = 26, 25
     got, want = _dot_ranks(ne, src, dst, C, *neg)
     assert np.array_equal(got, want), int((got != want).sum())
+
+
+@pytest.mark.parametrize("model", (DISTMULT, COMPLEX, DOT))
+@pytest.mark.parametrize("dim", (18, 50, 64, 98, 100, 126, 200, 256, 330, 400))
+def test_small_and_large_evaluations_rank_alike(model, dim):
+    """Two chunks of 1,100 edges against 1,000 candidates are above the line of dense fp32 operands, one of them (a short
+    batch in the same context) and a part of one below it: the same edges have the same ranks and scores, bit for bit."""
+    rng = np.random.default_rng(dim + model)
+    V, R, C, N = 3000, 7, 2, 1000
+    B = C * S_IMG
+    ne, re_ = ((rng.standard_normal((k, dim)) * 0.3).astype(np.float32) for k in (V, R))
+    ids = [torch.from_numpy(rng.integers(0, k, B).astype(np.int32)).to("cuda:0") for k in (V, R, V)]
+    tr = mar.Trainer(V, R, dim, model, B, C, N, device="cuda:0", node_emb=ne, rel_emb=re_)
+    tr.sample_negatives(0)
+    tr.neg_dst[5:700:9] = ids[2][:78]                      # edges' own endpoints among the candidates
+    got = []
+    for n in (B, S_IMG, 333):
+        pos, rd, rs = tr.eval_scores(*(x[:n] for x in ids))
+        torch.cuda.synchronize()
+        got.append([x.cpu().numpy()[:333].copy() for x in (pos, rd, rs)])
+    tr.close()
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.array_equal(a, b)
 
 
 def test_close_comparisons_cost_about_as_much_as_others():

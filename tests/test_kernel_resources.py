@@ -13,7 +13,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not available")
 def test_dot_product_contraction_kernels_do_not_spill(tmp_path):
-    """fp32 matrix instructions (TransE): both passes and evaluation, rows copied straight to LDS (50, 100, 400 floats) or through registers."""
+    """fp32 matrix instructions (TransE; small evaluations of the others): rows copied straight to LDS or through registers."""
     src = os.path.join(ROOT, "paper_2101_08358_amd", "csrc", "mar_flash.hip")
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
            "-packed-fp32-ops", "-Rpass-analysis=kernel-resource-usage", "-c", src, "-o", str(tmp_path / "flash.o")]
@@ -31,7 +31,7 @@ def test_dot_product_contraction_kernels_do_not_spill(tmp_path):
         spill = int(re.search(r"VGPRs Spill: (\d+)", b).group(1))
         scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", b).group(1))
         assert spill == 0 and scratch == 0, (name, spill, scratch)
-    assert seen == {"forward, registers": 10, "forward, direct": 6, "backward": 5}, seen
+    assert seen == {"forward, registers": 15, "forward, direct": 9, "backward": 5}, seen
 
 
 @pytest.mark.skipif(not (os.path.exists(HIPCC) or shutil.which("hipcc")), reason="hipcc not available")
