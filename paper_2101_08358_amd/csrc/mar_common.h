@@ -42,7 +42,8 @@ struct MarLayout {
   float*    Knorm;        // evaluation: bounds of the norms of Kimg's scaled rows, per 16-row block and per row
   float*    Gx;           // [rem2.k - 1][rem2.rows][dk] parts 1.. of pass 2's split stripes (bilinear models)
   float*    G;            // [roles*n + 2*cn*sy2][dk] gradient rows: edge-side occurrence k < roles*n at row k, part i
-                          // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i; bilinear models' evaluation: the negatives' fp32 rows, or exponents and norms
+                          // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i
+                          // (bilinear models' evaluation: the negatives' fp32 rows, or the images' exponents and norms)
   float*    carry;        // [reduce blocks][2][dk] partial sums of segments that cross workgroup borders
   float*    loss_part;    // per-block partial loss sums
   void*     metric_part;  // [MAR_METRIC_MAX_PARTS] partial records of the rank metrics

@@ -2,6 +2,8 @@
 // rows into dense contraction operands, the chain rule from operand gradients back to the
 // source / relation / destination rows, the per-row gradient reduction over the row-sorted
 // order, and the sparse Adagrad scatter.
+#include <type_traits>
+
 #include "mar_common.h"
 #include "mar_split.h"
 
@@ -562,9 +564,10 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
 
 // ------------------------------------------------------------ filtered evaluation -----
 // One lane group per (edge, corrupted side): takes the listed true candidates that outscore the edge out of its rank.
-// The edge's rows are read once; candidates are taken FILT at a time, their ids and then their rows all in flight (one
-// candidate at a time the kernel was a chain of two dependent loads per candidate: 72 us for 20,000 lists of 16 rows of
-// 100 floats, 40 us now).  Scores are formed in the operation order of the positive score above.
+// The edge's rows are read once; candidates are taken FILT at a time, their ids and then their rows all in flight, in
+// lists of one or two one at a time (20,000 edges, both sides, always one / always FILT / so: lists of 1 row of 400 floats
+// 27 / 33 / 27 us, of 2: 39 / 37 / 38, of 16: 253 / 158 / 163, of 16 rows of 100 floats 114 / 59 / 60).  Scores are
+// formed in the operation order of the positive score above.
 #define FILT 4
 template <int GL, int NV, bool VEC, int MODEL>
 __global__ void __launch_bounds__(256)
@@ -582,6 +585,7 @@ k_filter(RowArgs a, const int64_t* __restrict__ dst_off, const int32_t* __restri
   const int64_t* off = side == MAR_SIDE_DST ? dst_off : src_off;
   const int32_t* ids = side == MAR_SIDE_DST ? dst_ids : src_ids;
   const int64_t k0 = off[e], k1 = off[e + 1];
+  if (k0 >= k1) return;
   const float p = pos[e];
   const float* kept_row = a.node_emb + (size_t)(side == MAR_SIDE_DST ? a.src[e] : a.dst[e]) * dim;   // the endpoint that stays
   const float* r_row = a.rel_emb + (size_t)(MODEL == MAR_MODEL_DOT ? 0 : a.rel[e]) * dim;
@@ -592,16 +596,18 @@ k_filter(RowArgs a, const int64_t* __restrict__ dst_off, const int32_t* __restri
     r[v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : load_cols<GL, VEC, CPLX>(r_row, l, v, dim);
   }
   int better = 0;
-  for (int64_t k = k0; k < k1; k += FILT) {
-    float4 c[FILT][NV];
+  // N candidates from k on, the list's last one again where there are fewer
+  auto take = [&](int64_t k, auto count) __attribute__((always_inline)) {
+    constexpr int N = decltype(count)::value;
+    float4 c[N][NV];
 #pragma unroll
-    for (int j = 0; j < FILT; ++j) {
+    for (int j = 0; j < N; ++j) {
       const float* c_row = a.node_emb + (size_t)ids[k + j < k1 ? k + j : k1 - 1] * dim;
 #pragma unroll
       for (int v = 0; v < NV; ++v) c[j][v] = load_cols<GL, VEC, CPLX>(c_row, l, v, dim);
     }
 #pragma unroll
-    for (int j = 0; j < FILT; ++j) {
+    for (int j = 0; j < N; ++j) {
       float acc = 0.f;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
@@ -614,6 +620,11 @@ k_filter(RowArgs a, const int64_t* __restrict__ dst_off, const int32_t* __restri
       const float f = MODEL == MAR_MODEL_TRANSE ? -sqrtf(acc) : acc;
       better += k + j < k1 && f > p ? 1 : 0;
     }
+  };
+  if (k1 - k0 <= 2) {
+    for (int64_t k = k0; k < k1; ++k) take(k, std::integral_constant<int, 1>());
+  } else {
+    for (int64_t k = k0; k < k1; k += FILT) take(k, std::integral_constant<int, FILT>());
   }
   // The unfiltered rank comes from the matrix cores, this count from the vector ALU: a candidate within rounding
   // of the edge's score can be counted here and not there, so the difference is kept at 1 or above.

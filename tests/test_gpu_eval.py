@@ -270,3 +270,34 @@ def test_filtering_by_the_edges_own_endpoint_changes_nothing(model, dim):
     torch.cuda.synchronize()
     assert np.array_equal(before[0], rd.cpu().numpy()) and np.array_equal(before[1], rs.cpu().numpy())
     tr.close()
+
+
+@pytest.mark.parametrize("model,dim", ((0, 50), (1, 100), (3, 400), (0, 17)))
+def test_filter_lists_of_every_short_length(model, dim):
+    """Lists of 0 to 9 entries on small-integer embeddings, whose scores are exact: ranks from a start of 1,000 fall by the
+    number of entries that outscore the edge."""
+    V, R, B = 400, 3, 300
+    rng = np.random.default_rng(dim)
+    ne, re_ = (rng.integers(-2, 3, (k, dim)).astype(np.float32) for k in (V, R))
+    tr = mar.Trainer(V, R, dim, model, B, 1, 8, node_emb=ne, rel_emb=re_)
+    src, rel, dst = (rng.integers(0, k, B).astype(np.int32) for k in (V, R, V))
+    off = np.concatenate([[0], np.cumsum(np.arange(B) % 10)]).astype(np.int64)
+    ids = rng.integers(0, V, off[-1]).astype(np.int32)
+
+    def score(s, r, d):
+        s, r, d = ne[s].astype(np.float64), re_[r].astype(np.float64), ne[d].astype(np.float64)
+        if model == 1:
+            c = lambda x: x[:, :dim // 2] + 1j * x[:, dim // 2:]
+            return (c(s) * c(r) * c(d).conj()).real.sum(1)
+        return (s * d * (1 if model == 3 else r)).sum(1)
+
+    e = np.repeat(np.arange(B), np.arange(B) % 10)
+    pos = score(src, rel, dst)
+    want = [1000 - np.bincount(e, weights=score(*ends) > pos[e], minlength=B) for ends in ((src[e], rel[e], ids), (ids, rel[e], dst[e]))]
+    dev = tr.device
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev)
+    rd, rs = (torch.full((B,), 1000, dtype=torch.int32, device=dev) for _ in range(2))
+    mar.mar_eval_filter(tr.ctx, t(src), t(rel), t(dst), B, t(off), t(ids), t(off), t(ids), t(pos.astype(np.float32)), rd, rs)
+    torch.cuda.synchronize()
+    assert np.array_equal(rd.cpu().numpy(), want[0]) and np.array_equal(rs.cpu().numpy(), want[1])
+    tr.close()
