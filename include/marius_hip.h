@@ -243,7 +243,10 @@ int64_t mar_beta_swap_count(int32_t p, int32_t c);
  * first stage, which waits for the work enqueued so far on ids_stream (the stream that wrote them; hip_stream itself
  * is allowed, but then the staging of a batch also waits for the step of the batch before it and nothing overlaps);
  * they may be reused once hip_stream has passed this call.  loss_sum_out receives the batch's loss on hip_stream.  mar_pipe_drain enqueues the updates
- * still outstanding and makes hip_stream wait for them: after it, work on hip_stream sees the final host tables.
+ * still outstanding and makes hip_stream wait for them: after it, work on hip_stream sees the final host tables.  Batches
+ * may be submitted after a drain; the staging of the first waits for the drained updates by itself.  With depth > 1 such
+ * submits enqueue the updates of the last depth - 1 drained batches once more, each on the rows as they are then: to
+ * train on without that, destroy the pipeline after the drain and create a new one.
  * Between the first submit and the drain the host tables must not be touched by anyone else.
  */
 #define MAR_PIPE_MAX_DEPTH 32

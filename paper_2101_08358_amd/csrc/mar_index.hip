@@ -145,7 +145,9 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
 // global offsets from the counts of all tiles and scatters its elements).  Counts are kept digit by digit, the tiles'
 // counts of a digit side by side, so that the thread that owns a digit reads them 16 bytes at a time.
 // Small batches take small tiles (few elements per thread, many workgroups: their time is latency), large ones tiles of
-// 4096 so that a tile does not read more counts than elements (see sort_items).
+// 4096 (see sort_items).  Every tile reads bins x tiles counts, so that the reads grow with the square of the batch:
+// 250,000 gradient rows and 27-bit ids (three passes of 9 bits) 62 tiles x 31,744 counts a pass, 8 MB of cached reads;
+// sixteen times the batch 2 GB.
 
 // Lanes of the wave that hold the same digit as this lane (valid lanes only).
 __device__ __forceinline__ uint64_t match_digit(uint32_t digit, int bits, bool valid) {
