@@ -129,15 +129,15 @@ __device__ __forceinline__ void each_col(const float4 (&v)[NV], int l, int dim, 
 
 // One image row from a lane group's registers: columns scaled and split, zeros from dim up to the images' width.
 template <int GL, int NV, bool VEC, bool CPLX, bool F16>
-__device__ __forceinline__ void store_image_row(const SplitImages& g, char* row, const float4 (&v)[NV], float scale, int l, int dim) {
+__device__ __forceinline__ void store_image_row(const SplitImages& g, const SplitRow& row, const float4 (&v)[NV], float scale, int l, int dim) {
   if (VEC) {
-    for (int k = dim + 4 * l; k < g.dkp; k += 4 * GL) sp_store4<F16>(row, g.plane, k, make_float4(0.f, 0.f, 0.f, 0.f), 1.f);
+    for (int k = dim + 4 * l; k < g.dkp; k += 4 * GL) sp_store4<F16>(row, k, make_float4(0.f, 0.f, 0.f, 0.f), 1.f);
   } else {
-    for (int k = dim + l; k < g.dkp; k += GL) sp_store1<F16>(row, g.plane, k, 0.f, 1.f);
+    for (int k = dim + l; k < g.dkp; k += GL) sp_store1<F16>(row, k, 0.f, 1.f);
   }
-  each_col<GL, NV, VEC, CPLX>(v, l, dim, [&](int k, float x) { sp_store1<F16>(row, g.plane, k, x, scale); },
-                              [&](int k, const float2& x) { sp_store2<F16>(row, g.plane, k, x, scale); },
-                              [&](int k, const float4& x) { sp_store4<F16>(row, g.plane, k, x, scale); });
+  each_col<GL, NV, VEC, CPLX>(v, l, dim, [&](int k, float x) { sp_store1<F16>(row, k, x, scale); },
+                              [&](int k, const float2& x) { sp_store2<F16>(row, k, x, scale); },
+                              [&](int k, const float4& x) { sp_store4<F16>(row, k, x, scale); });
 }
 
 // Dense fp32 row, zero-padded from dim to dk.

@@ -2,8 +2,9 @@
 //
 // A matrix that takes part in a pass (the chunk's negatives, the chunk's edge-side operands) is kept as "images": per
 // chunk-side and tile of 32 rows a plane of the rows' hi parts and a plane of their lo parts, each [32][PA bytes], a
-// row = 16 NK 16-bit values: the dk columns and zeros up to the next multiple of 16 that an instantiation serves.  An
-// image is one contiguous block of IMG bytes (a multiple of 1 KB).
+// row = 16 NK 16-bit values: the dk columns and zeros up to the next multiple of 16 that an instantiation serves.  The
+// 16-byte units of a row lie in an order of their own (sp_swizzle).  An image is one contiguous block of IMG bytes (a
+// multiple of 1 KB).
 //   fp32 precision:  v 2^e = hi + lo with hi = f16(v 2^e), lo = f16(v 2^e - hi), one exponent e per block of 16 rows,
 //                    chosen so that the block's largest value lies in [2^14, 2^15); e is kept beside the images.
 //   SPLIT_BF16:      v = hi + lo with hi = bf16(v), lo = bf16(v - hi).
@@ -13,10 +14,25 @@
 
 #include "mar_common.h"
 
-// Row pitch in bytes of a plane whose rows hold 16 NK values: an odd number of 16-byte units, so the 16 rows of a
-// 16-byte fragment read fall into 16 different groups of 4 LDS banks.  (Pitches that also keep the transpose reads free
-// of bank conflicts cost up to 27% more bytes to copy, and the LDS is busy a quarter of the time.)
-constexpr int sp_pitch(int nk) { return 32 * nk + 16; }
+#ifdef __HIPCC__
+#define MAR_HD __host__ __device__
+#else
+#define MAR_HD
+#endif
+
+// Row pitch of a plane whose rows hold 16 NK values, in 16-byte units: a multiple of 4.
+constexpr int sp_units(int nk) { return (2 * nk + 3) / 4 * 4; }
+constexpr int sp_pitch(int nk) { return 16 * sp_units(nk); }
+// Unit u of row y lies at unit u ^ sp_swizzle(units, y) of the row.  A pass reads a plane in two ways: 16 bytes of every
+// row at one unit (score product), and 32 bytes at an even unit of each of 4 consecutive rows y = 0 mod 4 (transpose reads).
+// With the pitch alone (16-byte units mod 16, the LDS's 64 banks) rows y % 4 start 4 or 12 units apart where units % 16 is
+// 4 or 12, 8 apart where it is 8, together where it is 0; the upper bits of the swizzle make up for what is missing, so
+// that four consecutive rows lie in four different groups of 4 units, and the lower bits put rows y, y + 4, y + 8, y + 12 at
+// different units of a group: both kinds of read are free of bank conflicts.
+constexpr int sp_group(int units) { return units % 16 == 0 ? 16 : (units % 16 == 8 ? 8 : 4); }   // units a swizzle permutes
+MAR_HD constexpr int sp_swizzle(int units, int y) {
+  return (units % 16 == 0 ? 4 * (y & 3) : (units % 16 == 8 ? 4 * ((y >> 1) & 1) : 0)) | ((y >> 2) & 3);
+}
 constexpr int SP_TY = MAR_SPLIT_TILE_ROWS;                 // rows per image
 constexpr int SP_EB = 16;                                  // rows per exponent
 constexpr int SP_SR = MAR_SPLIT_STRIPE_ROWS;               // stationary rows per workgroup: four waves of 32
@@ -34,22 +50,26 @@ struct SplitImages {
   float* exps;          // [chunk-sides][2 tiles] exponent of every 16-row block (+ SP_NONFINITE)
   float* norms;         // evaluation: [chunk-sides][tiles][SP_NORMS] bounds of the scaled rows' norms: of the two blocks (0: all
                         // zero), then of the 32 rows (-1: a zero row)
-  int32_t pa, plane, img, tiles, dkp;
+  int32_t units, plane, img, tiles, dkp;
 };
 // Added to the exponent of a block that holds an infinity or a NaN (its exponent is that of its finite values).
 #define SP_NONFINITE 1024.f
 static inline SplitImages sp_images(char* base, float* exps, float* norms, int dk, int rows_per_chunk) {
   const int nk = sp_nk(dk);
   SplitImages g;
-  g.base = base; g.exps = exps; g.norms = norms; g.pa = sp_pitch(nk); g.plane = sp_plane(nk); g.img = sp_image(nk);
+  g.base = base; g.exps = exps; g.norms = norms; g.units = sp_units(nk); g.plane = sp_plane(nk); g.img = sp_image(nk);
   g.tiles = sp_tiles(rows_per_chunk); g.dkp = 16 * nk;
   return g;
 }
 
 #ifdef __HIPCC__
-// start of row `row` of chunk-side `cs` in the hi plane; the lo plane's row is g.plane bytes further
-__device__ __forceinline__ char* sp_row(const SplitImages& g, int cs, int row) {
-  return g.base + ((size_t)cs * g.tiles + row / SP_TY) * g.img + (row % SP_TY) * g.pa;
+// Row `row` of chunk-side `cs`: its start in the hi plane (the lo plane's is g.plane bytes further) and its swizzle in bytes.
+struct SplitRow { char* hi; int plane, swz; };
+__device__ __forceinline__ SplitRow sp_row(const SplitImages& g, int cs, int row) {
+  SplitRow r;
+  r.hi = g.base + ((size_t)cs * g.tiles + row / SP_TY) * g.img + (row % SP_TY) * g.units * 16;
+  r.plane = g.plane; r.swz = 16 * sp_swizzle(g.units, row % SP_TY);
+  return r;
 }
 // Exponent of a block whose largest finite magnitude has these float bits: 2^e max lies in [2^14, 2^15).  Clamped to
 // what a float power of two and the sums of a pass can hold (a block of values below 2^-66 keeps fewer bits).  A block of
@@ -73,43 +93,46 @@ __device__ __forceinline__ void sp_parts(float v, _Float16& h, _Float16& l) {
 }
 __device__ __forceinline__ void sp_parts(float v, __bf16& h, __bf16& l) { h = (__bf16)v; l = (__bf16)(v - (float)h); }
 
-template <bool F16> __device__ __forceinline__ void sp_store1(char* hi_row, int plane, int col, float v, float scale) {
+template <bool F16> __device__ __forceinline__ void sp_store1(const SplitRow& row, int col, float v, float scale) {
+  char* const at = row.hi + ((2 * col) ^ row.swz);
   if (F16) {
     _Float16 h, l;
     sp_parts(v * scale, h, l);
-    *reinterpret_cast<_Float16*>(hi_row + 2 * col) = h;
-    *reinterpret_cast<_Float16*>(hi_row + plane + 2 * col) = l;
+    *reinterpret_cast<_Float16*>(at) = h;
+    *reinterpret_cast<_Float16*>(at + row.plane) = l;
   } else {
     __bf16 h, l;
     sp_parts(v, h, l);
-    *reinterpret_cast<__bf16*>(hi_row + 2 * col) = h;
-    *reinterpret_cast<__bf16*>(hi_row + plane + 2 * col) = l;
+    *reinterpret_cast<__bf16*>(at) = h;
+    *reinterpret_cast<__bf16*>(at + row.plane) = l;
   }
 }
-template <bool F16> __device__ __forceinline__ void sp_store2(char* hi_row, int plane, int col, float2 v, float scale) {
+template <bool F16> __device__ __forceinline__ void sp_store2(const SplitRow& row, int col, float2 v, float scale) {
+  char* const at = row.hi + ((2 * col) ^ row.swz);
   if (F16) {
     _Float16 h[2], l[2];
     sp_parts(v.x * scale, h[0], l[0]); sp_parts(v.y * scale, h[1], l[1]);
-    *reinterpret_cast<sp_h2*>(hi_row + 2 * col) = (sp_h2){h[0], h[1]};
-    *reinterpret_cast<sp_h2*>(hi_row + plane + 2 * col) = (sp_h2){l[0], l[1]};
+    *reinterpret_cast<sp_h2*>(at) = (sp_h2){h[0], h[1]};
+    *reinterpret_cast<sp_h2*>(at + row.plane) = (sp_h2){l[0], l[1]};
   } else {
     __bf16 h[2], l[2];
     sp_parts(v.x, h[0], l[0]); sp_parts(v.y, h[1], l[1]);
-    *reinterpret_cast<sp_bf2*>(hi_row + 2 * col) = (sp_bf2){h[0], h[1]};
-    *reinterpret_cast<sp_bf2*>(hi_row + plane + 2 * col) = (sp_bf2){l[0], l[1]};
+    *reinterpret_cast<sp_bf2*>(at) = (sp_bf2){h[0], h[1]};
+    *reinterpret_cast<sp_bf2*>(at + row.plane) = (sp_bf2){l[0], l[1]};
   }
 }
-template <bool F16> __device__ __forceinline__ void sp_store4(char* hi_row, int plane, int col, float4 v, float scale) {
+template <bool F16> __device__ __forceinline__ void sp_store4(const SplitRow& row, int col, float4 v, float scale) {
+  char* const at = row.hi + ((2 * col) ^ row.swz);
   if (F16) {
     _Float16 h[4], l[4];
     sp_parts(v.x * scale, h[0], l[0]); sp_parts(v.y * scale, h[1], l[1]); sp_parts(v.z * scale, h[2], l[2]); sp_parts(v.w * scale, h[3], l[3]);
-    *reinterpret_cast<sp_h4*>(hi_row + 2 * col) = (sp_h4){h[0], h[1], h[2], h[3]};
-    *reinterpret_cast<sp_h4*>(hi_row + plane + 2 * col) = (sp_h4){l[0], l[1], l[2], l[3]};
+    *reinterpret_cast<sp_h4*>(at) = (sp_h4){h[0], h[1], h[2], h[3]};
+    *reinterpret_cast<sp_h4*>(at + row.plane) = (sp_h4){l[0], l[1], l[2], l[3]};
   } else {
     __bf16 h[4], l[4];
     sp_parts(v.x, h[0], l[0]); sp_parts(v.y, h[1], l[1]); sp_parts(v.z, h[2], l[2]); sp_parts(v.w, h[3], l[3]);
-    *reinterpret_cast<sp_bf4*>(hi_row + 2 * col) = (sp_bf4){h[0], h[1], h[2], h[3]};
-    *reinterpret_cast<sp_bf4*>(hi_row + plane + 2 * col) = (sp_bf4){l[0], l[1], l[2], l[3]};
+    *reinterpret_cast<sp_bf4*>(at) = (sp_bf4){h[0], h[1], h[2], h[3]};
+    *reinterpret_cast<sp_bf4*>(at + row.plane) = (sp_bf4){l[0], l[1], l[2], l[3]};
   }
 }
 #endif

@@ -37,7 +37,7 @@
 //   (j >= 4).  A = Y^T by the LDS transpose read (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4
 //   consecutive 16-bit values and receives, as its j-th value, value (i % 4) of lane 4j + i / 4; with lane i pointing
 //   at row 4h + i / 4, columns 32 cb + 16 (G % 2) + 4 (i % 4), lane m receives Y[4h + j][32 cb + m].  (With NK odd the
-//   last block reads up to 16 bytes past a row's pitch: columns beyond dk, whose outputs are not stored.)
+//   last block reads units that no one has written: columns beyond dk, whose outputs are not stored.)
 #include <type_traits>
 
 #include "mar_common.h"
@@ -92,6 +92,7 @@ __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevec
 template <int NK>
 struct SplitGeom {
   static constexpr int NB = sp_nb(NK);
+  static constexpr int UNITS = sp_units(NK);
   static constexpr int PA = sp_pitch(NK);
   static constexpr int PLANE = sp_plane(NK);
   static constexpr int IMG = sp_image(NK);
@@ -206,7 +207,7 @@ template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
   typedef SplitGeom<NK> SG;
-  constexpr int NB = SG::NB, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
+  constexpr int NB = SG::NB, UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
   constexpr int TY = SP_TY;
   constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
   constexpr float LOG2E = 1.44269504088896341f;
@@ -231,6 +232,7 @@ k_split(FlashArgs a) {
   const int x = u.stripe * SP_SR + wave * 32 + m;
   const bool xv = x < n_x;
   const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave;
+  const int swz = 16 * sp_swizzle(UNITS, m);              // of row m of a tile, in bytes
   const char* xrow = a.ximg + xtile * IMG + m * PA;
   v8s xh[NK], xl[NK];
 #pragma unroll
@@ -238,8 +240,8 @@ k_split(FlashArgs a) {
     xh[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
     xl[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
     if (xv) {
-      xh[s] = *reinterpret_cast<const v8s*>(xrow + 16 * h + 32 * s);
-      xl[s] = *reinterpret_cast<const v8s*>(xrow + PLANE + 16 * h + 32 * s);
+      xh[s] = *reinterpret_cast<const v8s*>(xrow + ((16 * h + 32 * s) ^ swz));
+      xl[s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((16 * h + 32 * s) ^ swz));
     }
   }
   float ex = 0.f;                                         // exponent of the row's block
@@ -370,12 +372,17 @@ k_split(FlashArgs a) {
     __syncthreads();
   }
 
-  const int fofs = m * PA + 16 * h;                        // score product: this lane's row and column group
-  const int trofs = (4 * h + ((lane & 15) >> 2)) * PA + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);   // second product
+  // Where a lane reads in a tile's buffer: rows start at whole groups of units, so a unit of the same group is a bit pattern
+  // away and the other groups are immediate offsets.
+  constexpr int FB = sp_group(UNITS) / 2, TB = sp_group(UNITS) / 4;   // steps of the score product / column blocks to a group
+  const int fofs = m * PA + ((16 * h) ^ swz);              // score product, step s = FB q + j: (fofs ^ 32 j) + 32 FB q
+  const int ty = 4 * h + ((lane & 15) >> 2), tc = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);   // second product, rows ty and ty + 8
+  const int trofs0 = ty * PA + (tc ^ (16 * sp_swizzle(UNITS, ty))), trofs1 = (ty + 8) * PA + (tc ^ (16 * sp_swizzle(UNITS, ty + 8)));
+                                                           // column block cb = TB q + j: (trofs ^ 64 j) + 64 TB q
+  auto frag_at = [](int fb, int s) { return (fb ^ (s % FB * 32)) + s / FB * FB * 32; };
   for (int t = t_begin; t < ntiles; ++t) {
     const int buf = (t - t_begin) & 1;
-    const char* hi = smem + buf * IMG;
-    const char* lo = hi + PLANE;
+    const int fb = buf * IMG + fofs;
     const bool has_next = t + 1 < ntiles;                  // uniform
     const float2 ye = ye_next, yn = yn_next;
     const int y0 = t * TY;
@@ -388,15 +395,15 @@ k_split(FlashArgs a) {
       v8s fh[PD], fl[PD];
 #pragma unroll
       for (int s = 0; s < PD; ++s) {
-        fh[s] = *reinterpret_cast<const v8s*>(hi + fofs + 32 * s);
-        fl[s] = *reinterpret_cast<const v8s*>(lo + fofs + 32 * s);
+        fh[s] = *reinterpret_cast<const v8s*>(smem + frag_at(fb, s));
+        fl[s] = *reinterpret_cast<const v8s*>(smem + PLANE + frag_at(fb, s));
       }
 #pragma unroll
       for (int s = 0; s < NK; ++s) {
         const v8s ah = fh[s % PD], al = fl[s % PD];
         if (s + PD < NK) {
-          fh[s % PD] = *reinterpret_cast<const v8s*>(hi + fofs + 32 * (s + PD));
-          fl[s % PD] = *reinterpret_cast<const v8s*>(lo + fofs + 32 * (s + PD));
+          fh[s % PD] = *reinterpret_cast<const v8s*>(smem + frag_at(fb, s + PD));
+          fl[s % PD] = *reinterpret_cast<const v8s*>(smem + PLANE + frag_at(fb, s + PD));
         }
         sacc = mfma32<F16>(al, xh[s], sacc);
         sacc = mfma32<F16>(ah, xl[s], sacc);
@@ -583,11 +590,13 @@ k_split(FlashArgs a) {
       split8<F16, 8>(w, neg1, wh[1], wl[1]);
       // -- O^T[c][x] += sum_y Y[y][c] W[y][x]: group q = (column block q / 2, step q % 2), read PG groups ahead
       constexpr int NG = 2 * NO, PG = SP_PG < NG ? SP_PG : NG;
+      const int tb0 = buf * IMG + trofs0, tb1 = buf * IMG + trofs1;
       v8s gh[PG], gl[PG];
       auto read_group = [&](int q, v8s& vh, v8s& vl) {
-        const int o = trofs + (q % 2) * 16 * PA + (q / 2) * 64;
-        vh = join8(lds_read_tr(hi + o), lds_read_tr(hi + o + 8 * PA));
-        vl = join8(lds_read_tr(lo + o), lds_read_tr(lo + o + 8 * PA));
+        const int cb = q / 2, o = (q % 2) * 16 * PA + cb / TB * TB * 64;
+        const char *r0 = smem + ((tb0 ^ (cb % TB * 64)) + o), *r1 = smem + ((tb1 ^ (cb % TB * 64)) + o);
+        vh = join8(lds_read_tr(r0), lds_read_tr(r1));
+        vl = join8(lds_read_tr(r0 + PLANE), lds_read_tr(r1 + PLANE));
       };
 #pragma unroll
       for (int q = 0; q < PG; ++q) read_group(q, gh[q], gl[q]);
