@@ -23,22 +23,23 @@
 // Row pitch of a plane whose rows hold 16 NK values, in 16-byte units: a multiple of 4.
 constexpr int sp_units(int nk) { return (2 * nk + 3) / 4 * 4; }
 constexpr int sp_pitch(int nk) { return 16 * sp_units(nk); }
-// Unit u of row y lies at unit u ^ sp_swizzle(units, y) of the row.  A pass reads a plane in two ways: 16 bytes of every
-// row at one unit (score product), and 32 bytes at an even unit of each of 4 consecutive rows y = 0 mod 4 (transpose reads).
-// With the pitch alone (16-byte units mod 16, the LDS's 64 banks) rows y % 4 start 4 or 12 units apart where units % 16 is
-// 4 or 12, 8 apart where it is 8, together where it is 0; the upper bits of the swizzle make up for what is missing, so
-// that four consecutive rows lie in four different groups of 4 units, and the lower bits put rows y, y + 4, y + 8, y + 12 at
-// different units of a group: both kinds of read are free of bank conflicts.
+// Unit u of row y lies at unit u ^ sp_swizzle(units, y) of the row, chosen so that the reads of the passes are free of bank
+// conflicts (counted: none).  The LDS has 64 banks, 16 units; 16-byte reads are served in groups of 16 lanes -- 0-3, 12-15,
+// 20-23, 24-27, then the other lanes of the first 32 -- and transpose reads of 8 bytes in groups of 32.  With the pitch alone
+// rows y % 4 start 4 or 12 units apart (mod 16) where units % 16 is 4 or 12, 8 apart where it is 8, together where it is 0;
+// the upper bits make up for what is missing, so that four consecutive rows lie in four different groups of 4 units.
+// Score product: lane 16 g + i reads unit u + g of row i, u = 0 mod 4.  Transpose reads: lanes 16 g + i read 32 bytes at an even
+// unit of rows 4 g .. 4 g + 3.  So with L(q) the lower two bits for rows 4 q .. 4 q + 3: L(0), L(3), L(1) ^ 1, L(2) ^ 1 differ, and
+// L(0), L(1) and L(2), L(3) differ in the upper bit: 0, 2, 3, 1.
 constexpr int sp_group(int units) { return units % 16 == 0 ? 16 : (units % 16 == 8 ? 8 : 4); }   // units a swizzle permutes
 MAR_HD constexpr int sp_swizzle(int units, int y) {
-  return (units % 16 == 0 ? 4 * (y & 3) : (units % 16 == 8 ? 4 * ((y >> 1) & 1) : 0)) | ((y >> 2) & 3);
+  return (units % 16 == 0 ? 4 * (y & 3) : (units % 16 == 8 ? 4 * ((y >> 1) & 1) : 0)) | (((y >> 1) ^ (y >> 2)) & 2) | ((y >> 3) & 1);
 }
 constexpr int SP_TY = MAR_SPLIT_TILE_ROWS;                 // rows per image
 constexpr int SP_EB = 16;                                  // rows per exponent
 constexpr int SP_SR = MAR_SPLIT_STRIPE_ROWS;               // stationary rows per workgroup: four waves of 32
-// 16-column contraction steps (NK) of the instantiation that serves dk; 32-column output blocks (NB) follow from it.
+// 16-column blocks (NK) of the instantiation that serves dk.
 constexpr int sp_nk(int dk) { return dk <= 32 ? 2 : (dk <= 64 ? 4 : (dk <= 96 ? 6 : (dk <= 112 ? 7 : (dk <= 128 ? 8 : (dk <= 192 ? 12 : (dk <= 256 ? 16 : 25)))))); }
-constexpr int sp_nb(int nk) { return (nk + 1) / 2; }
 constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(nk); }
 constexpr int sp_image(int nk) { return (2 * sp_plane(nk) + 1023) / 1024 * 1024; }
 constexpr int SP_NORMS = 2 + SP_TY;

@@ -4,7 +4,7 @@
 // fp32 precision (F16 = true).  Every operand value is written as v 2^e = hi + lo, both f16 (mar_split.h; one exponent
 // per 16 rows puts the largest value just below 2^15), and every product a b is taken as
 //     a_hi b_hi + a_lo b_hi + a_hi b_lo
-// with v_mfma_f32_32x32x16_f16 (fp32 accumulation), which runs at 16 times the rate of the fp32 matrix instructions.
+// with 16-bit matrix instructions (fp32 accumulation), which run at 16 times the rate of the fp32 ones.
 // hi + lo holds 23-24 significant bits of every value down to 2^-17 of its block's largest (below that an absolute
 // 2^-40 of the largest), the dropped product is below 2^-22 of its pair, and the sums see 3 roundings per 16 terms
 // where the fp32 instruction sees 4, so a pass is as accurate as its fp32 form: against 64 bits a dot product of 128
@@ -26,80 +26,31 @@
 // the edge-side operands) are copied into LDS by buffer loads that write LDS directly, one tile ahead, in two
 // alternating buffers; the stationary rows' fragments are read from their own images once and stay in registers.
 //
-// Lane layouts (lane = 32 h + m; i = lane % 16, G = lane / 16):
-//   v_mfma_f32_32x32x16_f16 / bf16: A lane holds row m, contraction slots 8h .. 8h+7; B lane holds column m, the same
-//   slots; D lane holds column m, register v = row 8 (v / 4) + 4h + v % 4.  Which contraction index a slot stands for
-//   is free as long as A and B agree.
-//   Score product S^T[y][x] = sum_c Y[y][c] X[x][c]: A = Y from LDS (16-byte read of row m, columns 16 s + 8h ..),
-//   B = X fragments in registers.
-//   Second product O^T[c][x] += sum_y Y[y][c] W[y][x] over the tile's 32 rows in two steps of 16: B of step k = W of
-//   the lane's own score registers 8k .. 8k+7, so slot 8h + j stands for row 16k + 4h + j (j < 4), 16k + 8 + 4h + j - 4
-//   (j >= 4).  A = Y^T by the LDS transpose read (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4
-//   consecutive 16-bit values and receives, as its j-th value, value (i % 4) of lane 4j + i / 4; with lane i pointing
-//   at row 4h + i / 4, columns 32 cb + 16 (G % 2) + 4 (i % 4), lane m receives Y[4h + j][32 cb + m].  (With NK odd the
-//   last block reads units that no one has written: columns beyond dk, whose outputs are not stored.)
+// Training runs on v_mfma_f32_16x16x32_f16 / bf16: with operands as random as these the chip holds its power limit by its
+// clock, and a 16 x 16 block over 32 slots takes 12 % less energy a product than a 32 x 32 block over 16 (fed from LDS, two
+// waves a SIMD, 1,735 to 1,770 against 1,550 TFLOP/s whatever the order of the products; zeros 2,200), and pads less: rows of
+// 100 take 80 instructions of 16 cycles a tile, where 32 x 32 blocks took 45 of 32.  (50,000 edges, 100 floats: passes 127 and
+// 152 us -> 122 and 138; 100,000, 400 floats: 872 and 1,033 -> 852 and 1,027, where one wave a SIMD issues such an instruction
+// every 19.6 cycles.)  Evaluation, three waves a SIMD and no second product, is left on 32 x 32 blocks.
+// Tried: a tile's weights formed between the next tile's score products, three tiles in LDS: the same cycles; counters in LDS
+// in place of the barrier: 8 % slower.
+//
+// Lane layouts (lane = 16 g + i):
+//   v_mfma_f32_16x16x32: A lane holds row i, contraction slots 8 g .. 8 g + 7; B lane holds column i, the same slots; D lane
+//   holds column i, register r = row 4 g + r.  Which contraction index a slot stands for is free as long as A and B agree.
+//   Score product S^T[y][x] = sum_c Y[y][c] X[x][c], two halves of 16 of the tile's rows y, two of the wave's rows x: A = Y
+//   from LDS (16-byte read of row i, columns 32 s + 8 g ..), B = X fragments in registers.
+//   Second product O^T[c][x] += sum_y Y[y][c] W[y][x] over the tile's 32 rows: B = W of the lane's own score registers, so slot
+//   8 g + j stands for row 4 g + j (j < 4), 16 + 4 g + j - 4 (j >= 4).  A = Y^T by the LDS transpose read
+//   (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4 consecutive 16-bit values and receives, as its
+//   j-th value, value (i % 4) of lane 4 j + i / 4; with lane i pointing at row 4 g + i / 4, columns 16 cb + 4 (i % 4), it
+//   receives Y[4 g + j][16 cb + i].
+//   v_mfma_f32_32x32x16 (lane = 32 h + m): A lane holds row m, slots 8 h .. 8 h + 7; B lane column m; D lane holds column m,
+//   register v = row 8 (v / 4) + 4 h + v % 4.
 #include <type_traits>
 
 #include "mar_common.h"
-#include "mar_flash.h"
-#include "mar_split.h"
-
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef short v8s __attribute__((ext_vector_type(8)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-typedef __bf16 v2b __attribute__((ext_vector_type(2)));
-
-template <bool F16> __device__ __forceinline__ v16f mfma32(v8s a, v8s b, v16f c) {
-  if (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
-}
-
-// v = hi + lo, two values per step: one packed conversion and two mixed-precision multiply-adds (f16; neg1 = -1 in a
-// register the compiler cannot see through, or it would turn the multiply-add into a conversion and a subtraction),
-// two packed conversions with the unpacking between them (bf16).
-template <bool F16, int O> __device__ __forceinline__ void split8(const float (&v)[16], float neg1, v8s& hi, v8s& lo) {
-  v4i hw, lw;                                              // two 16-bit values per word
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float p0 = v[O + 2 * i], p1 = v[O + 2 * i + 1];
-    if (F16) {
-      const v2h h = __builtin_convertvector((v2f){p0, p1}, v2h);
-      const v2h l = {(_Float16)__builtin_fmaf((float)h[0], neg1, p0), (_Float16)__builtin_fmaf((float)h[1], neg1, p1)};
-      hw[i] = __builtin_bit_cast(int, h); lw[i] = __builtin_bit_cast(int, l);
-    } else {
-      const v2b h = __builtin_convertvector((v2f){p0, p1}, v2b);
-      const v2b l = __builtin_convertvector((v2f){p0 - (float)h[0], p1 - (float)h[1]}, v2b);
-      hw[i] = __builtin_bit_cast(int, h); lw[i] = __builtin_bit_cast(int, l);
-    }
-  }
-  hi = __builtin_bit_cast(v8s, hw); lo = __builtin_bit_cast(v8s, lw);
-}
-
-__device__ __forceinline__ unsigned lds_address_b(const char* p) {
-  return (unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p;
-}
-__device__ __forceinline__ v4s lds_read_tr(const char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);
-}
-__device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
-
-#define SP_PEND 6                                          // candidates whose comparisons a lane of pass 3 keeps for the end (5 bits of a word each)
-#define SP_FULL 8                                          // added to their number: this lane takes no more (above SP_PEND)
-template <int NK>
-struct SplitGeom {
-  static constexpr int NB = sp_nb(NK);
-  static constexpr int UNITS = sp_units(NK);
-  static constexpr int PA = sp_pitch(NK);
-  static constexpr int PLANE = sp_plane(NK);
-  static constexpr int IMG = sp_image(NK);
-  static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
-  static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
-  static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
-};
+#include "mar_split_dev.h"
 
 // Evaluation compares scores with the positive's, and where the two are within rounding of one another the outcome
 // belongs to the arithmetic (an edge's own endpoint among the candidates scores what the edge does).  Comparisons
@@ -187,7 +138,7 @@ __device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, cons
 }
 
 #ifndef SP_PD
-#define SP_PD 4
+#define SP_PD 2
 #endif
 #ifndef SP_PG
 #define SP_PG 2
@@ -195,24 +146,15 @@ __device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, cons
 // Waves per SIMD = workgroups per CU: pass 3 keeps no output accumulators.
 constexpr int sp_waves(int nk, int pass) { return pass == 3 ? (nk <= 8 ? 3 : (nk <= 16 ? 2 : 1)) : (nk <= 8 ? 2 : 1); }
 
-// ------------------------------------------------------------------------ the passes -----
-// PASS 1: scores, online softmax and gQ = P K for 128 edges of one chunk-side (32 per wave) against the chunk's
-// negatives.  No weights are kept for pass 2:
-// PASS 2: gK = P^T Q for 128 negatives of one chunk-side against the chunk's edges, with the scores computed again and
-// P = exp(score - lse) from the finished log-sum-exp.  Writing the weights out and reading them back costs 8 bytes of
-// memory traffic per pair, computing a score again 6 d 16-bit flops: at this matrix rate the second is cheaper.
-// PASS 3 (evaluation): counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add
-// their counts.
-template <int NK, int PASS, bool F16>
-__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
-k_split(FlashArgs a) {
+// ---------------------------------------------------------------------------- evaluation -----
+// PASS 3: counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add their counts.
+template <int NK>
+__device__ __forceinline__ void split_eval(const FlashArgs& a) {
   typedef SplitGeom<NK> SG;
-  constexpr int NB = SG::NB, UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
+  constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
   constexpr int TY = SP_TY;
   constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
-  constexpr float LOG2E = 1.44269504088896341f;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][2][TY] log-sum-exp of the tile's edges, log2 units
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int h = lane >> 5, m = lane & 31;
@@ -220,13 +162,10 @@ k_split(FlashArgs a) {
   if (!flash_unit(a, u)) return;
   const int cs = u.cs, side = cs & 1, c = cs >> 1;
   const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
-  const int n_x = PASS == 2 ? a.N : ne;                   // stationary rows
-  const int n_y = PASS == 2 ? ne : a.N;                   // streamed rows
+  const int n_x = ne, n_y = a.N;                           // stationary, streamed rows
   if (u.stripe * SP_SR >= n_x) return;
   const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
   const int dk = a.dk;
-  float neg1 = -1.f;
-  asm volatile("" : "+v"(neg1));
 
   // ---- stationary fragments from the rows' own images: slots of step s = columns 16 s + 8h .. +7 of row x
   const int x = u.stripe * SP_SR + wave * 32 + m;
@@ -246,12 +185,12 @@ k_split(FlashArgs a) {
   }
   float ex = 0.f;                                         // exponent of the row's block
   bool xbad = false;
-  if (F16 && xv) {
+  if (xv) {
     ex = a.xexp[xtile * 2 + (m >> 4)];
     xbad = ex > 0.5f * SP_NONFINITE;
     if (xbad) ex -= SP_NONFINITE;
   }
-  // Pass 3.  A comparison is close if the score is within sqrt(dk) (2^-23 |q| + 2^-25) |n| of the positive's, q and n
+  // A comparison is close if the score is within sqrt(dk) (2^-23 |q| + 2^-25) |n| of the positive's, q and n
   // scaled by their blocks' exponents, |n| the largest of the block.  The rounding errors of a chain of dk steps are
   // independent and each below 2^-24 |q| |n| (the partial sums are), 0.3 of that on average: the first term is seven
   // standard deviations where all products have one sign, and ten times that where they do not.  hi + lo holds a value to
@@ -262,31 +201,29 @@ k_split(FlashArgs a) {
   const float* qrow = nullptr;
   int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
   int npend = 0;                                           // pending candidates; + SP_FULL: no more are taken
-  if (PASS == 3) {
-    float n2 = 0.f;
+  float n2 = 0.f;
 #pragma unroll
-    for (int s = 0; s < NK; ++s) {
-      const v8h f = __builtin_bit_cast(v8h, xh[s]);
+  for (int s = 0; s < NK; ++s) {
+    const v8h f = __builtin_bit_cast(v8h, xh[s]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
-    }
-    n2 += __shfl_xor(n2, 32);
-    if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
-    bool zero = n2 == 0.f;
-    if (xv && zero) {                                      // or merely below the f16 range
-      for (int k = 4 * h; k < dk; k += 8) {
-        const float4 q = *reinterpret_cast<const float4*>(qrow + k);
-        zero = zero && q.x == 0.f && q.y == 0.f && q.z == 0.f && q.w == 0.f;
-      }
-    }
-    zero = (__shfl_xor(zero ? 1 : 0, 32) & (zero ? 1 : 0)) != 0;
-    tolx = zero ? 0.f : sqrtf((float)dk) * (0x1p-23f * sqrtf(n2) + 0x1p-25f);
-    xbad |= !(fabsf(posx) <= 3.4028234663852886e38f);     // no difference to a positive score outside the range
+    for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
   }
+  n2 += __shfl_xor(n2, 32);
+  if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
+  bool zero = n2 == 0.f;
+  if (xv && zero) {                                      // or merely below the f16 range
+    for (int k = 4 * h; k < dk; k += 8) {
+      const float4 q = *reinterpret_cast<const float4*>(qrow + k);
+      zero = zero && q.x == 0.f && q.y == 0.f && q.z == 0.f && q.w == 0.f;
+    }
+  }
+  zero = (__shfl_xor(zero ? 1 : 0, 32) & (zero ? 1 : 0)) != 0;
+  tolx = zero ? 0.f : sqrtf((float)dk) * (0x1p-23f * sqrtf(n2) + 0x1p-25f);
+  xbad |= !(fabsf(posx) <= 3.4028234663852886e38f);     // no difference to a positive score outside the range
   const int32_t* const cand = (side == MAR_SIDE_DST ? a.neg_dst : a.neg_src) + (size_t)c * a.N;   // ids of the streamed rows
-  int own = -1, nown = 0;                                  // pass 3: the replaced endpoint's id, how often it came up close
-  if (PASS == 3 && xv) own = (side == MAR_SIDE_DST ? a.dst : a.src)[(size_t)c * a.S + x];
-  // Pass 3, all lanes of the wave: candidates of the tile at y0 that score above this lane's edge, settled as a whole (in
+  int own = -1, nown = 0;                                  // the replaced endpoint's id, how often it came up close
+  if (xv) own = (side == MAR_SIDE_DST ? a.dst : a.src)[(size_t)c * a.S + x];
+  // All lanes of the wave: candidates of the tile at y0 that score above this lane's edge, settled as a whole (in
   // the lanes of the wave's first half).
   auto exact_tile = [&](int y0) -> int {
     int ln = lane;
@@ -312,12 +249,274 @@ k_split(FlashArgs a) {
     return h == 0 ? ((G & 1) ? above[1] : above[0]) : 0;
   };
 
-  constexpr int NO = PASS == 3 ? 1 : NB;
-  v16f oacc[NO];
-#pragma unroll
-  for (int cb = 0; cb < NO; ++cb) oacc[cb] = (v16f)(0.f);
-  float mref = -3.0e38f, lrun = 0.f;                      // softmax reference (log2 units; F16: an integer) and sum
   int cnt = 0;
+
+  const int ntiles_all = (n_y + TY - 1) / TY;
+  const int t_begin = u.part * u.tps;
+  const int ntiles = min(ntiles_all, t_begin + u.tps);
+
+  // ---- images of the streamed rows, copied into LDS one tile ahead; a register load issued behind the copies is the
+  // fence (memory operations of a wave complete in order): once its value is there the image is in LDS.  The fence is
+  // the load of the tile's two exponents and of its blocks' norms.
+  const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
+  const BufRsrc expsrc = buf_rsrc(a.yexp + (size_t)cs * a.yimg_tiles * 2, (uint32_t)a.yimg_tiles * 8);
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f);
+  const BufRsrc normsrc = buf_rsrc(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS, (uint32_t)a.yimg_tiles * (SP_NORMS * 4));
+  int token = 0;
+  auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
+    const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
+    const int pc = 4 * q + wave_s;
+    if (pc < SG::NCH) buf_load4_to_lds(ywords, lds_address_b(smem) + buf * IMG + pc * 1024, lane * 16, pc * 1024, token);
+  };
+  auto dma_fence = [&](int t) {
+    ye_next = buf_load2(expsrc, token, t * 8);
+    yn_next = buf_load2(normsrc, token, t * (SP_NORMS * 4));
+  };
+  auto dma_land = [&]() { asm volatile("" : "+v"(ye_next.x), "+v"(ye_next.y)); };
+  if (t_begin < ntiles) {
+#pragma unroll
+    for (int q = 0; q < NCW; ++q) dma_piece(t_begin, 0, q);
+    dma_fence(t_begin);
+    dma_land();
+    __syncthreads();
+  }
+
+  // Where a lane reads in a tile's buffer: rows start at whole groups of units, so a unit of the same group is a bit pattern
+  // away and the other groups are immediate offsets.
+  constexpr int FB = sp_group(UNITS) / 2;                  // steps to a group
+  const int fofs = m * PA + ((16 * h) ^ swz);              // step s = FB q + j: (fofs ^ 32 j) + 32 FB q
+  auto frag = [&](int fb, int s) { return *reinterpret_cast<const v8s*>(smem + ((fb ^ (s % FB * 32)) + s / FB * FB * 32)); };
+  for (int t = t_begin; t < ntiles; ++t) {
+    const int buf = (t - t_begin) & 1;
+    const int fb = buf * IMG + fofs;
+    const bool has_next = t + 1 < ntiles;                  // uniform
+    const float2 ye = ye_next, yn = yn_next;
+    const int y0 = t * TY;
+    const bool masked = y0 + TY > n_y;
+
+    // -- scores; the fragments of the streamed rows are read PD steps ahead of the instructions that consume them
+    v16f sacc = (v16f)(0.f);
+    {
+      constexpr int PD = NK < 4 ? NK : 4;
+      v8s fh[PD], fl[PD];
+#pragma unroll
+      for (int s = 0; s < PD; ++s) {
+        fh[s] = frag(fb, s);
+        fl[s] = frag(fb + PLANE, s);
+      }
+#pragma unroll
+      for (int s = 0; s < NK; ++s) {
+        const v8s ah = fh[s % PD], al = fl[s % PD];
+        if (s + PD < NK) {
+          fh[s % PD] = frag(fb, s + PD);
+          fl[s % PD] = frag(fb + PLANE, s + PD);
+        }
+        sacc = mfma32h(al, xh[s], sacc);
+        sacc = mfma32h(ah, xl[s], sacc);
+        sacc = mfma32h(ah, xh[s], sacc);
+        // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
+        // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
+        if (has_next) {
+#pragma unroll
+          for (int q = s * NCW / NK; q < (s + 1) * NCW / NK; ++q) dma_piece(t + 1, buf ^ 1, q);
+          if (s == NK - 1) dma_fence(t + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
+      }
+    }
+    // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey); never 0, or a masked row's -inf would become NaN
+    // (two blocks at the largest exponent: scores below 2^-100 either way)
+    const bool ybad = ye.x > 0.5f * SP_NONFINITE || ye.y > 0.5f * SP_NONFINITE;
+    const float e0 = ye.x > 0.5f * SP_NONFINITE ? ye.x - SP_NONFINITE : ye.x;
+    const float e1 = ye.y > 0.5f * SP_NONFINITE ? ye.y - SP_NONFINITE : ye.y;
+    const float k0 = __builtin_ldexpf(1.f, max(-140, min(126, -(int)(ex + e0))));
+    const float k1 = __builtin_ldexpf(1.f, max(-140, min(126, -(int)(ex + e1))));
+    bool settle = __any(ybad || xbad);                     // uniform over the wave: the tile is settled as a whole
+    if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        if (y0 + 8 * (v / 4) + 4 * h + v % 4 >= n_y) sacc[v] = -__builtin_inff();
+      }
+    }
+    int ct = 0;
+    if (!settle) {
+      float near0 = __builtin_inff(), near1 = near0;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx);
+        ct += dif > 0.f ? 1 : 0;
+        if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
+      }
+      // scores at the ends of the exponents' range: every comparison is close
+      const float t0 = tolx * (fabsf(ex + e0) > 126.f ? __builtin_inff() : k0), t1 = tolx * (fabsf(ex + e1) > 126.f ? __builtin_inff() : k1);
+      const float tol0 = t0 * yn.x, tol1 = t1 * yn.y;
+      if (__any(xv && (near0 < tol0 || near1 < tol1))) {
+        // An edge's close candidates are mostly its own endpoint, as often as the candidates hold it: it is counted, and
+        // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
+        // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 90 us, 1,200 to 3,100 with
+        // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
+        unsigned close = 0u, same = 0u;                  // bit v: pair v is close / is with the own endpoint
+        float p = posx;
+        asm volatile("" : "+v"(p));                      // the comparisons are made again, one after the other: kept, their lane
+                                                         // masks would take 32 scalar registers
+#pragma unroll
+        for (int v = 15; v >= 0; --v) {
+          const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p);
+          const bool cl = fabsf(dif) < (v < 8 ? tol0 : tol1);
+          close = close + close + (cl ? 1u : 0u);
+          ct -= cl && dif > 0.f ? 1 : 0;
+          asm volatile("" : "+v"(close), "+v"(ct));
+        }
+        if (!xv) close = 0u;
+        // Several in a lane, or again and again: most are copies of the own endpoint; the others are looked at with their
+        // own norms in place of the block's largest (2^-25 of q is at most a quarter of tolx).
+        settle = __any(close != 0u && npend >= SP_FULL);
+        const bool many = __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2));
+        if (!settle && !many && close) {                 // one at most: by its place, without a look at its id
+          const int v = __ffs((int)close) - 1;
+          pend[256 * npend] = ~(y0 + 8 * (v >> 2) + 4 * h + (v & 3));
+          pend[256 * (SP_PEND + npend++)] = 1;
+        }
+        if (!settle && many) {
+          const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            same |= __shfl(id_t, 8 * (v / 4) + 4 * h + v % 4) == own ? 1u << v : 0u;
+            asm volatile("" : "+v"(same));
+          }
+          same &= close;
+          if (__any((close & ~same) != 0u)) {
+            const float nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4));
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+              const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, 8 * (v / 4) + 4 * h + v % 4);
+              const bool far = ((close & ~same) >> v & 1u) && !(fabsf(dif) < (v < 8 ? t0 : t1) * (nv + 0.25f) && nv >= 0.f);
+              close &= far ? ~(1u << v) : ~0u;
+              ct += far && dif > 0.f ? 1 : 0;
+              asm volatile("" : "+v"(close), "+v"(ct));
+            }
+          }
+          unsigned rest = close & ~same, times = 0u;     // times: 5 bits per pending candidate, how often the tile has it
+          int npend_t = npend, nown_t = nown + __popc(same);
+          bool over = rest != 0u && npend >= SP_PEND;
+          settle = __any(over);
+          if (!settle) {
+            for (; rest; rest &= rest - 1u) {
+              const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
+              int j = npend_t;
+#pragma unroll
+              for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
+              const bool put = id != own && j < SP_PEND;
+              if (put && j == npend_t) { pend[256 * j] = id; pend[256 * (SP_PEND + j)] = 0; ++npend_t; }
+              times += put ? 1u << (5 * j) : 0u;
+              nown_t += id == own ? 1 : 0;
+              over |= id != own && !put;
+            }
+            settle = __any(over);
+            if (over) npend += SP_FULL;                  // so many more at once: later tiles are settled without another look
+          }
+          if (!settle) {
+            nown = nown_t;
+            npend = npend_t;
+            for (int j = 0; times; ++j, times >>= 5) pend[256 * (SP_PEND + j)] += (int)(times & 31u);
+          }
+        }
+      }
+    }
+    cnt += settle ? exact_tile(y0) : ct;
+    if (has_next) {
+      dma_land();
+      __syncthreads();                                     // tile t + 1 is in LDS; every wave is done with tile t
+    }
+  }
+
+  // ---- epilogue
+  constexpr int UB = NK <= 16 ? 4 : 8;                     // 16-column blocks whose loads are in flight at once
+  for (int i = nown ? -1 : 0; i < npend % SP_FULL; ++i) {
+    const int e = i < 0 ? own : pend[256 * i], id = e < 0 ? cand[~e] : e;
+    const float* yrow = a.table + (size_t)id * a.dim;
+    const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
+    if (s > posx) cnt += i < 0 ? nown : pend[256 * (SP_PEND + i)];
+  }
+  cnt += __shfl_xor(cnt, 32);
+  if (h == 0 && xv && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x, cnt);
+}
+
+// ------------------------------------------------------------------------ the training passes -----
+// PASS 1: scores, online softmax and gQ = P K for 128 edges of one chunk-side (32 per wave) against the chunk's
+// negatives.
+// PASS 2: gK = P^T Q for 128 negatives of one chunk-side against the chunk's edges, with the scores computed again and
+// P = exp(score - lse) from the finished log-sum-exp.  Writing the weights out and reading them back costs 8 bytes of
+// memory traffic per pair, computing a score again 6 d 16-bit flops: at this matrix rate the second is cheaper.
+template <int NK, int PASS, bool F16>
+__device__ __forceinline__ void split_pass(const FlashArgs& a) {
+  typedef SplitGeom<NK> SG;
+  constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
+  constexpr int TY = SP_TY;
+  constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
+  constexpr int NS = NK / 2;                               // whole steps of 32 columns of the score product
+  constexpr bool TAIL = NK % 2 != 0;                       // and 16 columns more
+  constexpr int NO = NK;                                   // 16-column output blocks
+  constexpr float LOG2E = 1.44269504088896341f;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][2][TY] log-sum-exp of the tile's edges, log2 units
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, i = lane & 15;
+  FlashUnit u;
+  if (!flash_unit(a, u)) return;
+  const int cs = u.cs, side = cs & 1, c = cs >> 1;
+  const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
+  const int n_x = PASS == 2 ? a.N : ne;                   // stationary rows
+  const int n_y = PASS == 2 ? ne : a.N;                   // streamed rows
+  if (u.stripe * SP_SR >= n_x) return;
+  const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
+  const int dk = a.dk;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  float neg1 = -1.f;
+  asm volatile("" : "+v"(neg1));
+
+  // ---- stationary fragments from the rows' own images: column b of lane (g, i) is row x0 + 16 b + i, its slots of step s
+  // are columns 32 s + 8 g .. +7
+  const int x0 = u.stripe * SP_SR + wave * 32;
+  const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave_s;
+  const int swz = 16 * sp_swizzle(UNITS, i);              // of rows i and 16 + i of a tile, in bytes
+  const v8s zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  v8s xh[2][NS], xl[2][NS], xt[2][2];
+  // Tail: 16 columns more as one or two steps of 32 slots.  At most 8 of them: lane groups 0, 1, 2 hold the first 8
+  // columns of hi * hi, lo * hi and hi * lo.  Else groups 0, 1 / 2, 3 hold both halves of hi * hi and lo * hi, and a second step hi * lo.
+  const bool tail2 = TAIL && dk > 16 * (NK - 1) + 8;      // uniform
+  bool xv[2];
+  int ex[2] = {0, 0};                                     // exponents of the rows' blocks
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    xv[b] = x0 + 16 * b + i < n_x;
+    const char* xrow = a.ximg + xtile * IMG + (16 * b + i) * PA;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      xh[b][s] = xl[b][s] = zero8;
+      if (xv[b]) {
+        xh[b][s] = *reinterpret_cast<const v8s*>(xrow + ((64 * s + 16 * g) ^ swz));
+        xl[b][s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((64 * s + 16 * g) ^ swz));
+      }
+    }
+    xt[b][0] = xt[b][1] = zero8;
+    if (TAIL && xv[b]) {
+      const int unit = 64 * NS + (tail2 ? 16 * (g & 1) : 0);
+      if (tail2 || g < 3) xt[b][0] = *reinterpret_cast<const v8s*>(xrow + (!tail2 && g == 2 ? PLANE : 0) + (unit ^ swz));
+      if (tail2 && g < 2) xt[b][1] = *reinterpret_cast<const v8s*>(xrow + PLANE + (unit ^ swz));
+    }
+    if (F16 && x0 + 16 * b < n_x) {                        // uniform
+      const float e = a.xexp[xtile * 2 + b];
+      ex[b] = __builtin_amdgcn_readfirstlane((int)(e > 0.5f * SP_NONFINITE ? e - SP_NONFINITE : e));
+    }
+  }
+
+  v4f oacc[NO][2];
+#pragma unroll
+  for (int cb = 0; cb < NO; ++cb) oacc[cb][0] = oacc[cb][1] = (v4f)(0.f);
+  float mref[2] = {-3.0e38f, -3.0e38f}, lrun[2] = {0.f, 0.f};   // softmax reference (log2 units; F16: an integer) and sum
 
   const int ntiles_all = (n_y + TY - 1) / TY;
   const int t_begin = u.part * u.tps;
@@ -329,11 +528,9 @@ k_split(FlashArgs a) {
   const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
   const BufRsrc expsrc = buf_rsrc(F16 ? (const void*)(a.yexp + (size_t)cs * a.yimg_tiles * 2) : (const void*)ybase, (uint32_t)a.yimg_tiles * 8);
   const BufRsrc mlsrc = buf_rsrc(a.ml + q_base * 2, PASS == 2 ? (uint32_t)ne * 8 : 0u);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int f_row = threadIdx.x % TY;
   const size_t ml_stride = (size_t)2 * a.B;               // rows per part of pass 1's statistics
-  float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f), st_ml = make_float2(0.f, 0.f);
-  const BufRsrc normsrc = buf_rsrc(PASS == 3 ? (const void*)(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS) : (const void*)ybase, PASS == 3 ? (uint32_t)a.yimg_tiles * (SP_NORMS * 4) : 0u);
+  float2 ye_next = make_float2(0.f, 0.f), st_ml = make_float2(0.f, 0.f);
   int token = 0;
   auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
     const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
@@ -342,7 +539,6 @@ k_split(FlashArgs a) {
   };
   auto dma_fence = [&](int t) {
     ye_next = buf_load2(expsrc, token, t * 8);
-    if (PASS == 3) yn_next = buf_load2(normsrc, token, t * (SP_NORMS * 4));
     if (PASS == 2) st_ml = buf_load2(mlsrc, f_row * 8 + token, t * TY * 8);
   };
   auto dma_land = [&](int t, int buf) {
@@ -373,242 +569,182 @@ k_split(FlashArgs a) {
   }
 
   // Where a lane reads in a tile's buffer: rows start at whole groups of units, so a unit of the same group is a bit pattern
-  // away and the other groups are immediate offsets.
-  constexpr int FB = sp_group(UNITS) / 2, TB = sp_group(UNITS) / 4;   // steps of the score product / column blocks to a group
-  const int fofs = m * PA + ((16 * h) ^ swz);              // score product, step s = FB q + j: (fofs ^ 32 j) + 32 FB q
-  const int ty = 4 * h + ((lane & 15) >> 2), tc = 32 * ((lane >> 4) & 1) + 8 * (lane & 3);   // second product, rows ty and ty + 8
-  const int trofs0 = ty * PA + (tc ^ (16 * sp_swizzle(UNITS, ty))), trofs1 = (ty + 8) * PA + (tc ^ (16 * sp_swizzle(UNITS, ty + 8)));
-                                                           // column block cb = TB q + j: (trofs ^ 64 j) + 64 TB q
-  auto frag_at = [](int fb, int s) { return (fb ^ (s % FB * 32)) + s / FB * FB * 32; };
+  // away and the other groups are immediate offsets.  Rows y and y + 16 have the same swizzle.
+  constexpr int GU = sp_group(UNITS);                      // units to a group
+  const int fofs = i * PA + ((16 * g) ^ swz);              // score product, row half a, step s: at(fofs, 64 s) + 16 a PA
+  const int tfofs = i * PA + (tail2 ? (g & 2 ? PLANE : 0) + ((64 * NS + 16 * (g & 1)) ^ swz) : (g == 1 ? PLANE : 0) + ((64 * NS) ^ swz));
+  const int ty = 4 * g + (i >> 2), tswz = 16 * sp_swizzle(UNITS, ty);   // second product: rows ty, ty + 16, columns 16 cb + 4 (i % 4) .. +3
+  const int trofs = ty * PA + ((8 * (i & 3)) ^ tswz);      // at(trofs, 32 cb)
+  auto at = [](int base, int byte) { return (base ^ (byte % (16 * GU))) + byte / (16 * GU) * (16 * GU); };
+  // Last output block: where at most 8 columns are left, its rows 0 .. 7 are their hi parts and 8 .. 15 their lo parts
+  const bool pack = dk <= 16 * (NO - 1) + 8;               // uniform
+  const int ptrofs = ty * PA + (pack && (i & 2) ? PLANE : 0) + ((32 * (NO - 1) + 8 * (i & (pack ? 1 : 3))) ^ tswz);
+
   for (int t = t_begin; t < ntiles; ++t) {
-    const int buf = (t - t_begin) & 1;
-    const int fb = buf * IMG + fofs;
+    const int buf = (t - t_begin) & 1, bofs = buf * IMG;
     const bool has_next = t + 1 < ntiles;                  // uniform
-    const float2 ye = ye_next, yn = yn_next;
+    const int e0 = F16 ? __builtin_amdgcn_readfirstlane((int)(ye_next.x > 0.5f * SP_NONFINITE ? ye_next.x - SP_NONFINITE : ye_next.x)) : 0;
+    const int e1 = F16 ? __builtin_amdgcn_readfirstlane((int)(ye_next.y > 0.5f * SP_NONFINITE ? ye_next.y - SP_NONFINITE : ye_next.y)) : 0;
     const int y0 = t * TY;
     const bool masked = PASS != 2 && y0 + TY > n_y;
 
-    // -- scores; the fragments of the streamed rows are read PD steps ahead of the instructions that consume them
-    v16f sacc = (v16f)(0.f);
+    // -- scores S^T: block (ah, b) = rows 16 ah + 4 g + r, column 16 b + i; the streamed rows' fragments are read PD steps ahead
+    v4f sc[2][2];
+    sc[0][0] = sc[0][1] = sc[1][0] = sc[1][1] = (v4f)(0.f);
     {
-      constexpr int PD = NK < SP_PD ? NK : SP_PD;
-      v8s fh[PD], fl[PD];
+      constexpr int PD = NS < SP_PD ? NS : SP_PD;
+      v8s fh[PD][2], fl[PD][2];
+      const int fb = bofs + fofs;
+      auto read_step = [&](int s, v8s (&vh)[2], v8s (&vl)[2]) {
+        const char* p = smem + at(fb, 64 * s);
 #pragma unroll
-      for (int s = 0; s < PD; ++s) {
-        fh[s] = *reinterpret_cast<const v8s*>(smem + frag_at(fb, s));
-        fl[s] = *reinterpret_cast<const v8s*>(smem + PLANE + frag_at(fb, s));
-      }
+        for (int r = 0; r < 2; ++r) { vh[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA); vl[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA + PLANE); }
+      };
 #pragma unroll
-      for (int s = 0; s < NK; ++s) {
-        const v8s ah = fh[s % PD], al = fl[s % PD];
-        if (s + PD < NK) {
-          fh[s % PD] = *reinterpret_cast<const v8s*>(smem + frag_at(fb, s + PD));
-          fl[s % PD] = *reinterpret_cast<const v8s*>(smem + PLANE + frag_at(fb, s + PD));
-        }
-        sacc = mfma32<F16>(al, xh[s], sacc);
-        sacc = mfma32<F16>(ah, xl[s], sacc);
-        sacc = mfma32<F16>(ah, xh[s], sacc);
+      for (int s = 0; s < PD; ++s) read_step(s, fh[s], fl[s]);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const v8s h0 = fh[s % PD][0], h1 = fh[s % PD][1], l0 = fl[s % PD][0], l1 = fl[s % PD][1];
+        if (s + PD < NS) read_step(s + PD, fh[s % PD], fl[s % PD]);
+        // consecutive instructions share an operand
+        sc[0][0] = mfma16h<F16>(h0, xl[0][s], sc[0][0]); sc[0][0] = mfma16h<F16>(h0, xh[0][s], sc[0][0]); sc[0][0] = mfma16h<F16>(l0, xh[0][s], sc[0][0]);
+        sc[0][1] = mfma16h<F16>(l0, xh[1][s], sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xh[1][s], sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xl[1][s], sc[0][1]);
+        sc[1][1] = mfma16h<F16>(h1, xl[1][s], sc[1][1]); sc[1][1] = mfma16h<F16>(h1, xh[1][s], sc[1][1]); sc[1][1] = mfma16h<F16>(l1, xh[1][s], sc[1][1]);
+        sc[1][0] = mfma16h<F16>(l1, xh[0][s], sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xh[0][s], sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xl[0][s], sc[1][0]);
         // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
         // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
         if (has_next) {
 #pragma unroll
-          for (int q = s * NCW / NK; q < (s + 1) * NCW / NK; ++q) dma_piece(t + 1, buf ^ 1, q);
-          if (s == NK - 1) dma_fence(t + 1);
+          for (int q = s * NCW / NS; q < (s + 1) * NCW / NS; ++q) dma_piece(t + 1, buf ^ 1, q);
+          if (s == NS - 1) dma_fence(t + 1);
         }
         __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
       }
+      if (TAIL) {
+        const char* p = smem + bofs + tfofs;
+        const v8s t0 = *reinterpret_cast<const v8s*>(p), t1 = *reinterpret_cast<const v8s*>(p + 16 * PA);
+        sc[0][0] = mfma16h<F16>(t0, xt[0][0], sc[0][0]); sc[0][1] = mfma16h<F16>(t0, xt[1][0], sc[0][1]);
+        sc[1][1] = mfma16h<F16>(t1, xt[1][0], sc[1][1]); sc[1][0] = mfma16h<F16>(t1, xt[0][0], sc[1][0]);
+        if (tail2) {                                       // its hi fragments again (groups 2, 3 meet zeros)
+          const char* p2 = smem + bofs + i * PA + ((64 * NS + 16 * (g & 1)) ^ swz);
+          const v8s s0 = *reinterpret_cast<const v8s*>(p2), s1 = *reinterpret_cast<const v8s*>(p2 + 16 * PA);
+          sc[0][0] = mfma16h<F16>(s0, xt[0][1], sc[0][0]); sc[0][1] = mfma16h<F16>(s0, xt[1][1], sc[0][1]);
+          sc[1][1] = mfma16h<F16>(s1, xt[1][1], sc[1][1]); sc[1][0] = mfma16h<F16>(s1, xt[0][1], sc[1][0]);
+        }
+      }
     }
-    // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey); never 0, or a masked row's -inf would become NaN
-    // (two blocks at the largest exponent: scores below 2^-100 either way)
-    float k0 = PASS == 3 ? 1.f : LOG2E, k1 = k0, e0 = 0.f, e1 = 0.f;
-    bool settle = false;                                   // pass 3, uniform over the wave: the tile is settled as a whole
-    if (F16) {
-      const bool ybad = ye.x > 0.5f * SP_NONFINITE || ye.y > 0.5f * SP_NONFINITE;
-      e0 = ye.x > 0.5f * SP_NONFINITE ? ye.x - SP_NONFINITE : ye.x;
-      e1 = ye.y > 0.5f * SP_NONFINITE ? ye.y - SP_NONFINITE : ye.y;
-      k0 = __builtin_ldexpf(k0, max(-140, min(126, -(int)(ex + e0))));
-      k1 = __builtin_ldexpf(k1, max(-140, min(126, -(int)(ex + e1))));
-      settle = PASS == 3 && __any(ybad || xbad);
+    // -- score log2(e) = sc k, k = log2(e) 2^-(ex + ey): never 0, or a masked row's -inf would become NaN (two blocks at the
+    // largest exponent: scores below 2^-85 either way)
+    float k[2][2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      k[0][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e0)) << 23)) : LOG2E;
+      k[1][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e1)) << 23)) : LOG2E;
     }
+    const float ef[2] = {(float)e0, (float)e1};
     if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (y0 + 8 * (v / 4) + 4 * h + v % 4 >= n_y) sacc[v] = -__builtin_inff();
+      for (int r = 0; r < 8; ++r) {
+        if (y0 + 16 * (r >> 2) + 4 * g + (r & 3) >= n_y) sc[r >> 2][0][r & 3] = sc[r >> 2][1][r & 3] = -__builtin_inff();
       }
     }
-    if (PASS == 3) {
-      int ct = 0;
-      if (!settle) {
-        float near0 = __builtin_inff(), near1 = near0;
+    // -- weights of the lane's 2 x 8 pairs, split: w[b][4 ah + r] is row 16 ah + 4 g + r against column 16 b + i
+    float w[2][8];
+    if (PASS == 1 || F16) {
+      float tmax[2];
+      if (PASS == 1) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -posx);
-          ct += dif > 0.f ? 1 : 0;
-          if (v < 8) near0 = fminf(near0, fabsf(dif)); else near1 = fminf(near1, fabsf(dif));
+        for (int b = 0; b < 2; ++b) {
+          float m[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) m[h] = __builtin_fmaf(fmaxf(fmaxf(sc[h][b][0], sc[h][b][1]), fmaxf(sc[h][b][2], sc[h][b][3])), k[h][b], -ef[h]);
+          tmax[b] = fmaxf(m[0], m[1]);
         }
-        // scores at the ends of the exponents' range: every comparison is close
-        const float t0 = tolx * (fabsf(ex + e0) > 126.f ? __builtin_inff() : k0), t1 = tolx * (fabsf(ex + e1) > 126.f ? __builtin_inff() : k1);
-        const float tol0 = t0 * yn.x, tol1 = t1 * yn.y;
-        if (__any(xv && (near0 < tol0 || near1 < tol1))) {
-          // An edge's close candidates are mostly its own endpoint, as often as the candidates hold it: it is counted, and
-          // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
-          // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 90 us, 1,200 to 3,100 with
-          // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
-          unsigned close = 0u, same = 0u;                  // bit v: pair v is close / is with the own endpoint
-          float p = posx;
-          asm volatile("" : "+v"(p));                      // the comparisons are made again, one after the other: kept, their lane
-                                                           // masks would take 32 scalar registers
+      } else {
+        float m[2][2];
 #pragma unroll
-          for (int v = 15; v >= 0; --v) {
-            const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p);
-            const bool cl = fabsf(dif) < (v < 8 ? tol0 : tol1);
-            close = close + close + (cl ? 1u : 0u);
-            ct -= cl && dif > 0.f ? 1 : 0;
-            asm volatile("" : "+v"(close), "+v"(ct));
-          }
-          if (!xv) close = 0u;
-          // Several in a lane, or again and again: most are copies of the own endpoint; the others are looked at with their
-          // own norms in place of the block's largest (2^-25 of q is at most a quarter of tolx).
-          settle = __any(close != 0u && npend >= SP_FULL);
-          const bool many = __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2));
-          if (!settle && !many && close) {                 // one at most: by its place, without a look at its id
-            const int v = __ffs((int)close) - 1;
-            pend[256 * npend] = ~(y0 + 8 * (v >> 2) + 4 * h + (v & 3));
-            pend[256 * (SP_PEND + npend++)] = 1;
-          }
-          if (!settle && many) {
-            const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
+        for (int h = 0; h < 2; ++h) {
+          const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+          const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 16 * h + 4 * g);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              same |= __shfl(id_t, 8 * (v / 4) + 4 * h + v % 4) == own ? 1u << v : 0u;
-              asm volatile("" : "+v"(same));
-            }
-            same &= close;
-            if (__any((close & ~same) != 0u)) {
-              const float nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4));
-#pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, 8 * (v / 4) + 4 * h + v % 4);
-                const bool far = ((close & ~same) >> v & 1u) && !(fabsf(dif) < (v < 8 ? t0 : t1) * (nv + 0.25f) && nv >= 0.f);
-                close &= far ? ~(1u << v) : ~0u;
-                ct += far && dif > 0.f ? 1 : 0;
-                asm volatile("" : "+v"(close), "+v"(ct));
-              }
-            }
-            unsigned rest = close & ~same, times = 0u;     // times: 5 bits per pending candidate, how often the tile has it
-            int npend_t = npend, nown_t = nown + __popc(same);
-            bool over = rest != 0u && npend >= SP_PEND;
-            settle = __any(over);
-            if (!settle) {
-              for (; rest; rest &= rest - 1u) {
-                const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
-                int j = npend_t;
-#pragma unroll
-                for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
-                const bool put = id != own && j < SP_PEND;
-                if (put && j == npend_t) { pend[256 * j] = id; pend[256 * (SP_PEND + j)] = 0; ++npend_t; }
-                times += put ? 1u << (5 * j) : 0u;
-                nown_t += id == own ? 1 : 0;
-                over |= id != own && !put;
-              }
-              settle = __any(over);
-              if (over) npend += SP_FULL;                  // so many more at once: later tiles are settled without another look
-            }
-            if (!settle) {
-              nown = nown_t;
-              npend = npend_t;
-              for (int j = 0; times; ++j, times >>= 5) pend[256 * (SP_PEND + j)] += (int)(times & 31u);
-            }
+          for (int b = 0; b < 2; ++b) {
+            w[b][4 * h] = __builtin_fmaf(sc[h][b][0], k[h][b], -l4.x) - m4.x;
+            w[b][4 * h + 1] = __builtin_fmaf(sc[h][b][1], k[h][b], -l4.y) - m4.y;
+            w[b][4 * h + 2] = __builtin_fmaf(sc[h][b][2], k[h][b], -l4.z) - m4.z;
+            w[b][4 * h + 3] = __builtin_fmaf(sc[h][b][3], k[h][b], -l4.w) - m4.w;
+            m[h][b] = fmaxf(fmaxf(w[b][4 * h], w[b][4 * h + 1]), fmaxf(w[b][4 * h + 2], w[b][4 * h + 3])) - ef[h];
           }
         }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) tmax[b] = fmaxf(m[0][b], m[1][b]);
       }
-      cnt += settle ? exact_tile(y0) : ct;
-    } else {
-      // -- weights of the lane's 16 pairs, split; register v <-> row y0 + 8 (v / 4) + 4h + v % 4
-      float w[16];
-      if (PASS == 1 || F16) {
-        float tmax;
-        if (PASS == 1) {
-          float a0 = sacc[0], a1 = sacc[8];
+      constexpr float SLACK = F16 ? 15.f : 16.f * LOG2E;
+      if (__any(tmax[0] > mref[0] + SLACK || tmax[1] > mref[1] + SLACK)) {
 #pragma unroll
-          for (int v = 1; v < 8; ++v) { a0 = fmaxf(a0, sacc[v]); a1 = fmaxf(a1, sacc[8 + v]); }
-          tmax = fmaxf(__builtin_fmaf(a0, k0, -e0), __builtin_fmaf(a1, k1, -e1));
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 8 * q + 4 * h);
-            const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 8 * q + 4 * h);
-            const float kq = q < 2 ? k0 : k1;
-            w[4 * q] = __builtin_fmaf(sacc[4 * q], kq, -l4.x) - m4.x;
-            w[4 * q + 1] = __builtin_fmaf(sacc[4 * q + 1], kq, -l4.y) - m4.y;
-            w[4 * q + 2] = __builtin_fmaf(sacc[4 * q + 2], kq, -l4.z) - m4.z;
-            w[4 * q + 3] = __builtin_fmaf(sacc[4 * q + 3], kq, -l4.w) - m4.w;
-          }
-          float a0 = w[0], a1 = w[8];
-#pragma unroll
-          for (int v = 1; v < 8; ++v) { a0 = fmaxf(a0, w[v]); a1 = fmaxf(a1, w[8 + v]); }
-          tmax = fmaxf(a0 - e0, a1 - e1);
-        }
-        if (__any(tmax > mref + (F16 ? 15.f : 16.f * LOG2E))) {
-          const float tall = fmaxf(tmax, __shfl_xor(tmax, 32));
-          const float mnew = fmaxf(mref, F16 ? __builtin_ceilf(tall) - 8.f : tall);
-          float alpha = __builtin_amdgcn_exp2f(mref - mnew);
+        for (int b = 0; b < 2; ++b) {
+          float tall = fmaxf(tmax[b], __shfl_xor(tmax[b], 16));
+          tall = fmaxf(tall, __shfl_xor(tall, 32));
+          const float mnew = fmaxf(mref[b], F16 ? __builtin_ceilf(tall) - 8.f : tall);
+          float alpha = __builtin_amdgcn_exp2f(mref[b] - mnew);
           asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
-          lrun *= alpha;
+          lrun[b] *= alpha;
 #pragma unroll
           for (int cb = 0; cb < NO; ++cb) {
-            if (NK > 8) asm volatile("" : "+a"(oacc[cb]));
-            oacc[cb] *= alpha;
-            if (NK > 8) asm volatile("" : "+a"(oacc[cb]));   // wide rows: back to the accumulation registers, one block at a time
+            if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));
+            oacc[cb][b] *= alpha;
+            if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));   // wide rows: back to the accumulation registers, one block at a time
           }
-          mref = mnew;
-        }
-        const float r0 = e0 + mref, r1 = e1 + mref;        // exact: integers (bf16: no exponents)
-        if (PASS == 1) {
-          float l0 = 0.f, l1 = 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) w[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[v], v < 8 ? k0 : k1, v < 8 ? -r0 : -r1));
-#pragma unroll
-          for (int v = 0; v < 8; ++v) { l0 += w[v]; l1 += w[8 + v]; }
-          lrun += F16 ? __builtin_ldexpf(l0, (int)e0) + __builtin_ldexpf(l1, (int)e1) : l0 + l1;
-        } else {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) w[v] = __builtin_amdgcn_exp2f(w[v] - (v < 8 ? r0 : r1));
-        }
-      } else {                                             // pass 2, bf16: no reference needed
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 8 * q + 4 * h);
-          w[4 * q] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q], LOG2E, -l4.x));
-          w[4 * q + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 1], LOG2E, -l4.y));
-          w[4 * q + 2] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 2], LOG2E, -l4.z));
-          w[4 * q + 3] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[4 * q + 3], LOG2E, -l4.w));
+          mref[b] = mnew;
         }
       }
-      v8s wh[2], wl[2];
-      split8<F16, 0>(w, neg1, wh[0], wl[0]);
-      split8<F16, 8>(w, neg1, wh[1], wl[1]);
-      // -- O^T[c][x] += sum_y Y[y][c] W[y][x]: group q = (column block q / 2, step q % 2), read PG groups ahead
-      constexpr int NG = 2 * NO, PG = SP_PG < NG ? SP_PG : NG;
-      const int tb0 = buf * IMG + trofs0, tb1 = buf * IMG + trofs1;
-      v8s gh[PG], gl[PG];
-      auto read_group = [&](int q, v8s& vh, v8s& vl) {
-        const int cb = q / 2, o = (q % 2) * 16 * PA + cb / TB * TB * 64;
-        const char *r0 = smem + ((tb0 ^ (cb % TB * 64)) + o), *r1 = smem + ((tb1 ^ (cb % TB * 64)) + o);
-        vh = join8(lds_read_tr(r0), lds_read_tr(r1));
-        vl = join8(lds_read_tr(r0 + PLANE), lds_read_tr(r1 + PLANE));
-      };
 #pragma unroll
-      for (int q = 0; q < PG; ++q) read_group(q, gh[q], gl[q]);
+      for (int b = 0; b < 2; ++b) {
+        float l[2] = {0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < NG; ++q) {
-        const v8s ah = gh[q % PG], al = gl[q % PG];
-        if (q + PG < NG) read_group(q + PG, gh[q % PG], gl[q % PG]);
-        oacc[q / 2] = mfma32<F16>(al, wh[q % 2], oacc[q / 2]);
-        oacc[q / 2] = mfma32<F16>(ah, wl[q % 2], oacc[q / 2]);
-        oacc[q / 2] = mfma32<F16>(ah, wh[q % 2], oacc[q / 2]);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int v = 0; v < 8; ++v) {
+          const float ref = ef[v >> 2] + mref[b];          // exact: integers (bf16: no exponents)
+          w[b][v] = __builtin_amdgcn_exp2f(PASS == 1 ? __builtin_fmaf(sc[v >> 2][b][v & 3], k[v >> 2][b], -ref) : w[b][v] - ref);
+          if (PASS == 1) l[v >> 2] += w[b][v];
+        }
+        if (PASS == 1) lrun[b] += F16 ? __builtin_ldexpf(l[0], e0) + __builtin_ldexpf(l[1], e1) : l[0] + l[1];
       }
+    } else {                                               // pass 2, bf16: no reference needed
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          w[b][4 * h] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][0], LOG2E, -l4.x));
+          w[b][4 * h + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][1], LOG2E, -l4.y));
+          w[b][4 * h + 2] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][2], LOG2E, -l4.z));
+          w[b][4 * h + 3] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][3], LOG2E, -l4.w));
+        }
+      }
+    }
+    v8s wh[2], wl[2];
+    split8<F16>(w[0], neg1, wh[0], wl[0]);
+    split8<F16>(w[1], neg1, wh[1], wl[1]);
+    // -- O^T[c][x] += sum_y Y[y][c] W[y][x], one 16-column block after the other, read PG blocks ahead
+    constexpr int PG = SP_PG < NO ? SP_PG : NO;
+    const int tb = bofs + trofs;
+    v8s gh[PG], gl[PG];
+    auto read_block = [&](int cb, v8s& vh, v8s& vl) {
+      const char* p = smem + (cb == NO - 1 ? bofs + ptrofs : at(tb, 32 * cb));
+      vh = join8(lds_read_tr(p), lds_read_tr(p + 16 * PA));
+      if (cb == NO - 1) p = smem + at(tb, 32 * cb);
+      if (cb < NO - 1 || !pack) vl = join8(lds_read_tr(p + PLANE), lds_read_tr(p + 16 * PA + PLANE));
+    };
+#pragma unroll
+    for (int cb = 0; cb < PG; ++cb) read_block(cb, gh[cb], gl[cb]);
+#pragma unroll
+    for (int cb = 0; cb < NO; ++cb) {
+      const v8s ah = gh[cb % PG], al = gl[cb % PG];
+      if (cb + PG < NO) read_block(cb + PG, gh[cb % PG], gl[cb % PG]);
+      const int p = cb & 1, q = p ^ 1;                     // consecutive instructions share an operand
+      oacc[cb][p] = mfma16h<F16>(ah, wl[p], oacc[cb][p]); oacc[cb][p] = mfma16h<F16>(ah, wh[p], oacc[cb][p]);
+      if (cb < NO - 1 || !pack) { oacc[cb][p] = mfma16h<F16>(al, wh[p], oacc[cb][p]); oacc[cb][q] = mfma16h<F16>(al, wh[q], oacc[cb][q]); }
+      oacc[cb][q] = mfma16h<F16>(ah, wh[q], oacc[cb][q]); oacc[cb][q] = mfma16h<F16>(ah, wl[q], oacc[cb][q]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     if (has_next) {
       dma_land(t + 1, buf ^ 1);
@@ -617,50 +753,51 @@ k_split(FlashArgs a) {
   }
 
   // ---- epilogue
-  if (PASS == 3) {
-    constexpr int UB = NK <= 16 ? 4 : 8;                   // 16-column blocks whose loads are in flight at once
-    for (int i = nown ? -1 : 0; i < npend % SP_FULL; ++i) {
-      const int e = i < 0 ? own : pend[256 * i], id = e < 0 ? cand[~e] : e;
-      const float* yrow = a.table + (size_t)id * a.dim;
-      const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
-      if (s > posx) cnt += i < 0 ? nown : pend[256 * (SP_PEND + i)];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    if (pack) {                                            // lo parts back to the hi parts' columns
+#pragma unroll
+      for (int r = 0; r < 4; ++r) oacc[NO - 1][b][r] += __shfl_xor(oacc[NO - 1][b][r], 32);
     }
-    cnt += __shfl_xor(cnt, 32);
-    if (h == 0 && xv && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x, cnt);
-    return;
-  }
-  int oshift = 0;                                          // gradient rows are written as accumulator x 2^oshift
-  float* orow;
-  if (PASS == 1) {                                         // the part's statistics and unnormalised gradient rows
-    float ltot = lrun + __shfl_xor(lrun, 32);
-    // sum = mantissa 2^p, reference + p: the statistics' reference is close to the log-sum-exp itself
-    int p = 0;
-    if (F16 && ltot > 0.f && ltot < 3.0e38f) p = (int)((__float_as_uint(ltot) >> 23) & 255u) - 127;
-    oshift = -p;
-    const size_t part_row = (size_t)u.part * 2 * a.B + q_base + x;
-    const bool extra = u.rem && u.part > 0;                // parts 1.. of a split stripe
-    const size_t xr = (size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + m;
-    float* ml_out = extra ? a.mlx + xr * 2 : a.ml + (u.rem ? q_base + x : part_row) * 2;
-    orow = extra ? a.outx + xr * dk : a.out + (u.rem ? q_base + x : part_row) * dk;
-    if (h == 0 && xv) *reinterpret_cast<float2*>(ml_out) = make_float2(mref + (float)p, __builtin_ldexpf(ltot, -p));
-  } else {                                                 // gradient row of part `part` of each negative's occurrence
-    if (F16) oshift = mref > -1.0e38f ? (int)mref : 0;     // weights were formed relative to the reference
-    orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x) * a.sy + (u.rem ? 0 : u.part)) * dk;
-    if (u.rem && u.part > 0) orow = a.outx + ((size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + m) * dk;
-  }
-  if (xv) {
+    const int x = x0 + 16 * b + i;
+    int oshift = 0;                                        // gradient rows are written as accumulator x 2^oshift
+    float* orow;
+    if (PASS == 1) {                                       // the part's statistics and unnormalised gradient rows
+      float ltot = lrun[b] + __shfl_xor(lrun[b], 16);
+      ltot += __shfl_xor(ltot, 32);
+      // sum = mantissa 2^p, reference + p: the statistics' reference is close to the log-sum-exp itself
+      int p = 0;
+      if (F16 && ltot > 0.f && ltot < 3.0e38f) p = (int)((__float_as_uint(ltot) >> 23) & 255u) - 127;
+      oshift = -p;
+      const size_t part_row = (size_t)u.part * 2 * a.B + q_base + x;
+      const bool extra = u.rem && u.part > 0;              // parts 1.. of a split stripe
+      const size_t xr = (size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + 16 * b + i;
+      float* ml_out = extra ? a.mlx + xr * 2 : a.ml + (u.rem ? q_base + x : part_row) * 2;
+      orow = extra ? a.outx + xr * dk : a.out + (u.rem ? q_base + x : part_row) * dk;
+      if (g == 0 && xv[b]) *reinterpret_cast<float2*>(ml_out) = make_float2(mref[b] + (float)p, __builtin_ldexpf(ltot, -p));
+    } else {                                               // gradient row of part `part` of each negative's occurrence
+      if (F16) oshift = mref[b] > -1.0e38f ? (int)mref[b] : 0;   // weights were formed relative to the reference
+      orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x) * a.sy + (u.rem ? 0 : u.part)) * dk;
+      if (u.rem && u.part > 0) orow = a.outx + ((size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + 16 * b + i) * dk;
+    }
+    if (xv[b]) {
 #pragma unroll
-    for (int cb = 0; cb < NO; ++cb) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = 32 * cb + 8 * q + 4 * h;
-        if (col < dk)
+      for (int cb = 0; cb < NO; ++cb) {
+        const int col = 16 * cb + 4 * g;
+        if (col < dk && (cb < NO - 1 || !pack || g < 2))
           *reinterpret_cast<float4*>(orow + col) =
-              make_float4(__builtin_ldexpf(oacc[cb][4 * q], oshift), __builtin_ldexpf(oacc[cb][4 * q + 1], oshift),
-                          __builtin_ldexpf(oacc[cb][4 * q + 2], oshift), __builtin_ldexpf(oacc[cb][4 * q + 3], oshift));
+              make_float4(__builtin_ldexpf(oacc[cb][b][0], oshift), __builtin_ldexpf(oacc[cb][b][1], oshift),
+                          __builtin_ldexpf(oacc[cb][b][2], oshift), __builtin_ldexpf(oacc[cb][b][3], oshift));
       }
     }
   }
+}
+
+template <int NK, int PASS, bool F16>
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
+k_split(FlashArgs a) {
+  if constexpr (PASS == 3) split_eval<NK>(a);
+  else split_pass<NK, PASS, F16>(a);
 }
 
 // Adds parts 1.. of pass 2's split stripes to the gradient rows that part 0 wrote, in the parts' order.  One group of
@@ -699,9 +836,10 @@ template <int NK> static hipError_t sp_prepare() {
 }
 hipError_t mar_split_prepare(int dk) {
   switch (sp_nk(dk)) {
+    case 12: return sp_prepare<12>();
     case 16: return sp_prepare<16>();
     case 25: return sp_prepare<25>();
-    default: static_assert(SplitGeom<12>::LDS_BYTES3 <= 64 * 1024, "narrower instantiations stay below the default limit"); return hipSuccess;
+    default: static_assert(SplitGeom<8>::LDS_BYTES <= 64 * 1024 && SplitGeom<8>::LDS_BYTES3 <= 64 * 1024, "narrower instantiations stay below the default limit"); return hipSuccess;
   }
 }
 

@@ -13,19 +13,24 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef __bf16 v2b __attribute__((ext_vector_type(2)));
 
-template <bool F16> __device__ __forceinline__ v16f mfma32(v8s a, v8s b, v16f c) {
-  if (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
+// Evaluation: 32 x 32 blocks, 16 slots an instruction; training: 16 x 16 blocks, 32 slots.
+__device__ __forceinline__ v16f mfma32h(v8s a, v8s b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+}
+
+template <bool F16> __device__ __forceinline__ v4f mfma16h(v8s a, v8s b, v4f c) {
+  if (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
 }
 
 // v = hi + lo, two values per step: one packed conversion and two mixed-precision multiply-adds (f16; neg1 = -1 in a
 // register the compiler cannot see through, or it would turn the multiply-add into a conversion and a subtraction),
 // two packed conversions with the unpacking between them (bf16).
-template <bool F16, int O> __device__ __forceinline__ void split8(const float (&v)[16], float neg1, v8s& hi, v8s& lo) {
+template <bool F16> __device__ __forceinline__ void split8(const float (&v)[8], float neg1, v8s& hi, v8s& lo) {
   v4i hw, lw;                                              // two 16-bit values per word
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float p0 = v[O + 2 * i], p1 = v[O + 2 * i + 1];
+    const float p0 = v[2 * i], p1 = v[2 * i + 1];
     if (F16) {
       const v2h h = __builtin_convertvector((v2f){p0, p1}, v2h);
       const v2h l = {(_Float16)__builtin_fmaf((float)h[0], neg1, p0), (_Float16)__builtin_fmaf((float)h[1], neg1, p1)};
@@ -51,13 +56,11 @@ __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevec
 #define SP_FULL 8                                          // added to their number: this lane takes no more (above SP_PEND)
 template <int NK>
 struct SplitGeom {
-  static constexpr int NB = sp_nb(NK);
   static constexpr int UNITS = sp_units(NK);
   static constexpr int PA = sp_pitch(NK);
   static constexpr int PLANE = sp_plane(NK);
   static constexpr int IMG = sp_image(NK);
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
   static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
-  static constexpr size_t LDS_BYTES_GRAD = 2 * (size_t)IMG + 2 * 4 * 2 * SP_TY * 4;   // two images, the edges' factors for each wave
   static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };
