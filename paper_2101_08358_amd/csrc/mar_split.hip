@@ -26,12 +26,13 @@
 // the edge-side operands) are copied into LDS by buffer loads that write LDS directly, one tile ahead, in two
 // alternating buffers; the stationary rows' fragments are read from their own images once and stay in registers.
 //
-// Training runs on v_mfma_f32_16x16x32_f16 / bf16: with operands as random as these the chip holds its power limit by its
+// All passes run on v_mfma_f32_16x16x32_f16 / bf16: with operands as random as these the chip holds its power limit by its
 // clock, and a 16 x 16 block over 32 slots takes 12 % less energy a product than a 32 x 32 block over 16 (fed from LDS, two
 // waves a SIMD, 1,735 to 1,770 against 1,550 TFLOP/s whatever the order of the products; zeros 2,200), and pads less: rows of
 // 100 take 80 instructions of 16 cycles a tile, where 32 x 32 blocks took 45 of 32.  (50,000 edges, 100 floats: passes 127 and
 // 152 us -> 122 and 138; 100,000, 400 floats: 872 and 1,033 -> 852 and 1,027, where one wave a SIMD issues such an instruction
-// every 19.6 cycles.)  Evaluation, three waves a SIMD and no second product, is left on 32 x 32 blocks.
+// every 19.6 cycles; evaluation of 100,000 edges against 1,000 candidates of 400 floats, gather included, 995 -> 955, of 10,000
+// against 14,951 of 100 floats 217 -> 212.)
 // Tried: a tile's weights formed between the next tile's score products, three tiles in LDS: the same cycles; counters in LDS
 // in place of the barrier: 8 % slower.
 //
@@ -45,8 +46,8 @@
 //   (ds_read_b64_tr_b16): within 16 lanes, lane i passes the address of 4 consecutive 16-bit values and receives, as its
 //   j-th value, value (i % 4) of lane 4 j + i / 4; with lane i pointing at row 4 g + i / 4, columns 16 cb + 4 (i % 4), it
 //   receives Y[4 g + j][16 cb + i].
-//   v_mfma_f32_32x32x16 (lane = 32 h + m): A lane holds row m, slots 8 h .. 8 h + 7; B lane column m; D lane holds column m,
-//   register v = row 8 (v / 4) + 4 h + v % 4.
+//   Evaluation then swaps halves between the lane groups g and g ^ 1 (v_permlane16_swap, 8 a tile), so that lane 32 h + m holds
+//   half of the tile's rows against the one edge m, whose comparisons it keeps.
 #include <type_traits>
 
 #include "mar_common.h"
@@ -58,43 +59,6 @@
 // multiply-adds -- in the column order of the fp32 contraction kernels: blocks of 16 columns up to column `chain`, each
 // as columns 4 g + i for i = 0..3, g = 0..3; the rest in sequence.  So do blocks that hold an infinity or a NaN.
 constexpr int sp_chain(int dk) { return dk <= 52 ? 48 : (dk <= 100 ? 96 : 400); }
-template <bool VEC, int UB>
-__device__ __forceinline__ float sp_exact_score(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
-  float s = 0.f;
-  const int nb = (min(chain, dim) + 15) / 16;
-  for (int b0 = 0; b0 < nb; b0 += UB) {
-    float a[UB][16], c[UB][16];
-#pragma unroll
-    for (int b = 0; b < UB; ++b) {
-#pragma unroll
-      for (int i = 0; i < 16; i += 4) {
-        const int k = 16 * (b0 + b) + i;
-        if (VEC) {
-          float4 u = make_float4(0.f, 0.f, 0.f, 0.f), v = u;
-          if (b0 + b < nb && k < dim) { u = *reinterpret_cast<const float4*>(y + k); v = *reinterpret_cast<const float4*>(q + k); }
-          a[b][i] = u.x; a[b][i + 1] = u.y; a[b][i + 2] = u.z; a[b][i + 3] = u.w;
-          c[b][i] = v.x; c[b][i + 1] = v.y; c[b][i + 2] = v.z; c[b][i + 3] = v.w;
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const bool in = b0 + b < nb && k + j < dim;
-            a[b][i + j] = in ? y[k + j] : 0.f; c[b][i + j] = in ? q[k + j] : 0.f;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < UB; ++b) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) s = __builtin_fmaf(a[b][4 * g + i], c[b][4 * g + i], s);
-      }
-    }
-  }
-  for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
-  return s;
-}
 // Columns k .. k+3 of a row, zeros from column n on (VEC: n is a multiple of 4).
 template <bool VEC> __device__ __forceinline__ float4 sp_row_cols(const float* __restrict__ row, int k, int n) {
   if (VEC) {
@@ -137,12 +101,64 @@ __device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, cons
   }
 }
 
+// Up to 16 pairs settled: lanes (G, i) pass the rows of pair i; the lanes with G = i / 4 receive its score.  The loads of UB
+// blocks of 16 columns are in flight at once (blocks the rows do not have read the last one again), then comes their chain.
+template <bool VEC, int UB>
+__device__ __forceinline__ float sp_exact_pairs(const float* __restrict__ q, const float* __restrict__ y, int G, int i, int dim, int dk, int chain) {
+  const int end = min(chain, dim), whole = end / 16, part = 16 * whole + 4 * G;   // uniform: whole
+  const float4 ap = sp_row_cols<VEC>(y, part, end), bp = sp_row_cols<true>(q, part, min(chain, dk));
+  const bool rest = chain + G < dim;                       // at most four columns behind the chain: one step more
+  const float ar = rest ? y[chain + G] : 0.f, br = rest ? q[chain + G] : 0.f;
+  v4f acc = (v4f)(0.f);
+#pragma unroll 1
+  for (int n0 = 0; n0 < whole; n0 += UB) {
+    float4 a[UB], b[UB];
+#pragma unroll
+    for (int n = 0; n < UB; ++n) {
+      const int at = 4 * G + 16 * min(n0 + n, whole - 1);
+      a[n] = VEC ? *reinterpret_cast<const float4*>(y + at) : make_float4(y[at], y[at + 1], y[at + 2], y[at + 3]);
+      b[n] = *reinterpret_cast<const float4*>(q + at);
+    }
+#pragma unroll
+    for (int n = 0; n < UB; ++n) {
+      if (n0 + n < whole) {
+        acc = mfma16(a[n].x, b[n].x, acc); acc = mfma16(a[n].y, b[n].y, acc);
+        acc = mfma16(a[n].z, b[n].z, acc); acc = mfma16(a[n].w, b[n].w, acc);
+      }
+    }
+  }
+  acc = mfma16(ap.x, bp.x, acc); acc = mfma16(ap.y, bp.y, acc);
+  acc = mfma16(ap.z, bp.z, acc); acc = mfma16(ap.w, bp.w, acc);
+  acc = mfma16(ar, br, acc);
+  return i & 2 ? (i & 1 ? acc[3] : acc[2]) : (i & 1 ? acc[1] : acc[0]);
+}
+
 #ifndef SP_PD
 #define SP_PD 2
 #endif
 #ifndef SP_PG
 #define SP_PG 2
 #endif
+// One step of a score product: the three products of 32 rows' parts (0: rows i, 1: rows 16 + i) with 32 columns'.
+// Consecutive instructions share an operand.
+template <bool F16> __device__ __forceinline__ void sp_score_step(v8s h0, v8s h1, v8s l0, v8s l1, v8s xh0, v8s xh1, v8s xl0, v8s xl1, v4f (&sc)[2][2]) {
+  sc[0][0] = mfma16h<F16>(h0, xl0, sc[0][0]); sc[0][0] = mfma16h<F16>(h0, xh0, sc[0][0]); sc[0][0] = mfma16h<F16>(l0, xh0, sc[0][0]);
+  sc[0][1] = mfma16h<F16>(l0, xh1, sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xh1, sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xl1, sc[0][1]);
+  sc[1][1] = mfma16h<F16>(h1, xl1, sc[1][1]); sc[1][1] = mfma16h<F16>(h1, xh1, sc[1][1]); sc[1][1] = mfma16h<F16>(l1, xh1, sc[1][1]);
+  sc[1][0] = mfma16h<F16>(l1, xh0, sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xh0, sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xl0, sc[1][0]);
+}
+template <bool F16> __device__ __forceinline__ void sp_tail_step(v8s t0, v8s t1, v8s x0, v8s x1, v4f (&sc)[2][2]) {
+  sc[0][0] = mfma16h<F16>(t0, x0, sc[0][0]); sc[0][1] = mfma16h<F16>(t0, x1, sc[0][1]);
+  sc[1][1] = mfma16h<F16>(t1, x1, sc[1][1]); sc[1][0] = mfma16h<F16>(t1, x0, sc[1][0]);
+}
+__device__ __forceinline__ float sum_of_squares(v8s v) {
+  const v8h f = __builtin_bit_cast(v8h, v);
+  float n2 = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
+  return n2;
+}
+
 // Waves per SIMD = workgroups per CU: pass 3 keeps no output accumulators.
 constexpr int sp_waves(int nk, int pass) { return pass == 3 ? (nk <= 8 ? 3 : (nk <= 16 ? 2 : 1)) : (nk <= 8 ? 2 : 1); }
 
@@ -154,10 +170,13 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
   constexpr int TY = SP_TY;
   constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
+  constexpr int NS = NK / 2;                               // whole steps of 32 columns
+  constexpr bool TAIL = NK % 2 != 0;                       // and 16 columns more
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = lane >> 5, m = lane & 31;
+  const int g = lane >> 4, i = lane & 15;                  // of the matrix instructions
+  const int h = lane >> 5, m = lane & 31;                  // of the comparisons: edge m, half of the tile's rows
   FlashUnit u;
   if (!flash_unit(a, u)) return;
   const int cs = u.cs, side = cs & 1, c = cs >> 1;
@@ -167,20 +186,32 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
   const int dk = a.dk;
 
-  // ---- stationary fragments from the rows' own images: slots of step s = columns 16 s + 8h .. +7 of row x
-  const int x = u.stripe * SP_SR + wave * 32 + m;
+  // ---- stationary fragments and their tail, as in split_pass
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int x0 = u.stripe * SP_SR + wave_s * 32, x = x0 + m;   // the wave's first row, the lane's
   const bool xv = x < n_x;
-  const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave;
-  const int swz = 16 * sp_swizzle(UNITS, m);              // of row m of a tile, in bytes
-  const char* xrow = a.ximg + xtile * IMG + m * PA;
-  v8s xh[NK], xl[NK];
+  const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave_s;
+  const int swz = 16 * sp_swizzle(UNITS, i);              // of rows i and 16 + i of a tile, in bytes
+  const v8s zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  v8s xh[2][NS], xl[2][NS], xt[2][2];
+  const bool tail2 = TAIL && dk > 16 * (NK - 1) + 8;      // uniform
 #pragma unroll
-  for (int s = 0; s < NK; ++s) {
-    xh[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
-    xl[s] = (v8s){0, 0, 0, 0, 0, 0, 0, 0};
-    if (xv) {
-      xh[s] = *reinterpret_cast<const v8s*>(xrow + ((16 * h + 32 * s) ^ swz));
-      xl[s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((16 * h + 32 * s) ^ swz));
+  for (int b = 0; b < 2; ++b) {
+    const bool in = x0 + 16 * b + i < n_x;
+    const char* xrow = a.ximg + xtile * IMG + (16 * b + i) * PA;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      xh[b][s] = xl[b][s] = zero8;
+      if (in) {
+        xh[b][s] = *reinterpret_cast<const v8s*>(xrow + ((64 * s + 16 * g) ^ swz));
+        xl[b][s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((64 * s + 16 * g) ^ swz));
+      }
+    }
+    xt[b][0] = xt[b][1] = zero8;
+    if (TAIL && in) {
+      const int unit = 64 * NS + (tail2 ? 16 * (g & 1) : 0);
+      if (tail2 || g < 3) xt[b][0] = *reinterpret_cast<const v8s*>(xrow + (!tail2 && g == 2 ? PLANE : 0) + (unit ^ swz));
+      if (tail2 && g < 2) xt[b][1] = *reinterpret_cast<const v8s*>(xrow + PLANE + (unit ^ swz));
     }
   }
   float ex = 0.f;                                         // exponent of the row's block
@@ -201,14 +232,19 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   const float* qrow = nullptr;
   int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
   int npend = 0;                                           // pending candidates; + SP_FULL: no more are taken
-  float n2 = 0.f;
+  float n2;
+  {
+    float q[2] = {0.f, 0.f};
 #pragma unroll
-  for (int s = 0; s < NK; ++s) {
-    const v8h f = __builtin_bit_cast(v8h, xh[s]);
+    for (int b = 0; b < 2; ++b) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) n2 += (float)f[i] * (float)f[i];
+      for (int s = 0; s < NS; ++s) q[b] += sum_of_squares(xh[b][s]);
+      if (TAIL && g < (tail2 ? 2 : 1)) q[b] += sum_of_squares(xt[b][0]);
+      q[b] += __shfl_xor(q[b], 16);
+      q[b] += __shfl_xor(q[b], 32);
+    }
+    n2 = g & 1 ? q[1] : q[0];
   }
-  n2 += __shfl_xor(n2, 32);
   if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
   bool zero = n2 == 0.f;
   if (xv && zero) {                                      // or merely below the f16 range
@@ -228,7 +264,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   auto exact_tile = [&](int y0) -> int {
     int ln = lane;
     asm volatile("" : "+v"(ln));                          // what follows is rare: nothing of it is kept across tiles
-    const int i = ln & 15, G = ln >> 4, x0 = u.stripe * SP_SR + wave * 32;
+    const int i = ln & 15, G = ln >> 4;
     const float* qr = a.qrows + q_base * dk;
     v4f acc[2][2];
 #pragma unroll
@@ -250,6 +286,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   };
 
   int cnt = 0;
+  auto row_of = [&](int v) { return 16 * (v >> 3) + 8 * h + (v & 7); };   // of a lane's pair v within the tile
 
   const int ntiles_all = (n_y + TY - 1) / TY;
   const int t_begin = u.part * u.tps;
@@ -260,7 +297,6 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   // the load of the tile's two exponents and of its blocks' norms.
   const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
   const BufRsrc expsrc = buf_rsrc(a.yexp + (size_t)cs * a.yimg_tiles * 2, (uint32_t)a.yimg_tiles * 8);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f);
   const BufRsrc normsrc = buf_rsrc(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS, (uint32_t)a.yimg_tiles * (SP_NORMS * 4));
   int token = 0;
@@ -282,47 +318,62 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
     __syncthreads();
   }
 
-  // Where a lane reads in a tile's buffer: rows start at whole groups of units, so a unit of the same group is a bit pattern
-  // away and the other groups are immediate offsets.
-  constexpr int FB = sp_group(UNITS) / 2;                  // steps to a group
-  const int fofs = m * PA + ((16 * h) ^ swz);              // step s = FB q + j: (fofs ^ 32 j) + 32 FB q
-  auto frag = [&](int fb, int s) { return *reinterpret_cast<const v8s*>(smem + ((fb ^ (s % FB * 32)) + s / FB * FB * 32)); };
+  // Where a lane reads in a tile's buffer (as in split_pass)
+  constexpr int GU = sp_group(UNITS);
+  const int fofs = i * PA + ((16 * g) ^ swz);
+  const int tfofs = i * PA + (tail2 ? (g & 2 ? PLANE : 0) + ((64 * NS + 16 * (g & 1)) ^ swz) : (g == 1 ? PLANE : 0) + ((64 * NS) ^ swz));
+  auto at = [](int base, int byte) { return (base ^ (byte % (16 * GU))) + byte / (16 * GU) * (16 * GU); };
   for (int t = t_begin; t < ntiles; ++t) {
     const int buf = (t - t_begin) & 1;
-    const int fb = buf * IMG + fofs;
+    const int bofs = buf * IMG;
     const bool has_next = t + 1 < ntiles;                  // uniform
     const float2 ye = ye_next, yn = yn_next;
     const int y0 = t * TY;
     const bool masked = y0 + TY > n_y;
 
-    // -- scores; the fragments of the streamed rows are read PD steps ahead of the instructions that consume them
-    v16f sacc = (v16f)(0.f);
+    // -- scores as in split_pass; then lane groups g and g ^ 1 exchange halves, so that lane (h, m) holds its one edge's:
+    // sacc[v] = row 16 (v / 8) + 8 h + v % 8
+    float sacc[16];
     {
-      constexpr int PD = NK < 4 ? NK : 4;
-      v8s fh[PD], fl[PD];
+      v4f sc[2][2];
+      sc[0][0] = sc[0][1] = sc[1][0] = sc[1][1] = (v4f)(0.f);
+      constexpr int PD = NS < SP_PD ? NS : SP_PD;
+      v8s fh[PD][2], fl[PD][2];
+      const int fb = bofs + fofs;
+      auto read_step = [&](int s, v8s (&vh)[2], v8s (&vl)[2]) {
+        const char* p = smem + at(fb, 64 * s);
 #pragma unroll
-      for (int s = 0; s < PD; ++s) {
-        fh[s] = frag(fb, s);
-        fl[s] = frag(fb + PLANE, s);
-      }
+        for (int r = 0; r < 2; ++r) { vh[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA); vl[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA + PLANE); }
+      };
 #pragma unroll
-      for (int s = 0; s < NK; ++s) {
-        const v8s ah = fh[s % PD], al = fl[s % PD];
-        if (s + PD < NK) {
-          fh[s % PD] = frag(fb, s + PD);
-          fl[s % PD] = frag(fb + PLANE, s + PD);
-        }
-        sacc = mfma32h(al, xh[s], sacc);
-        sacc = mfma32h(ah, xl[s], sacc);
-        sacc = mfma32h(ah, xh[s], sacc);
+      for (int s = 0; s < PD; ++s) read_step(s, fh[s], fl[s]);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const v8s h0 = fh[s % PD][0], h1 = fh[s % PD][1], l0 = fl[s % PD][0], l1 = fl[s % PD][1];
+        if (s + PD < NS) read_step(s + PD, fh[s % PD], fl[s % PD]);
+        sp_score_step<true>(h0, h1, l0, l1, xh[0][s], xh[1][s], xl[0][s], xl[1][s], sc);
         // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
         // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
         if (has_next) {
 #pragma unroll
-          for (int q = s * NCW / NK; q < (s + 1) * NCW / NK; ++q) dma_piece(t + 1, buf ^ 1, q);
-          if (s == NK - 1) dma_fence(t + 1);
+          for (int q = s * NCW / NS; q < (s + 1) * NCW / NS; ++q) dma_piece(t + 1, buf ^ 1, q);
+          if (s == NS - 1) dma_fence(t + 1);
         }
         __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
+      }
+      if (TAIL) {
+        const char* p = smem + bofs + tfofs;
+        sp_tail_step<true>(*reinterpret_cast<const v8s*>(p), *reinterpret_cast<const v8s*>(p + 16 * PA), xt[0][0], xt[1][0], sc);
+        if (tail2) {                                       // its hi fragments again (groups 2, 3 meet zeros)
+          const char* p2 = smem + bofs + i * PA + ((64 * NS + 16 * (g & 1)) ^ swz);
+          sp_tail_step<true>(*reinterpret_cast<const v8s*>(p2), *reinterpret_cast<const v8s*>(p2 + 16 * PA), xt[0][1], xt[1][1], sc);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(sc[k >> 2][0][k & 3]), __float_as_uint(sc[k >> 2][1][k & 3]), false, false);
+        sacc[8 * (k >> 2) + (k & 3)] = __uint_as_float(w[0]);
+        sacc[8 * (k >> 2) + 4 + (k & 3)] = __uint_as_float(w[1]);
       }
     }
     // -- scale of the two 16-row blocks: score = sacc 2^-(ex + ey); never 0, or a masked row's -inf would become NaN
@@ -336,7 +387,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
     if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        if (y0 + 8 * (v / 4) + 4 * h + v % 4 >= n_y) sacc[v] = -__builtin_inff();
+        if (y0 + row_of(v) >= n_y) sacc[v] = -__builtin_inff();
       }
     }
     int ct = 0;
@@ -375,14 +426,14 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
         const bool many = __any((close & (close - 1u)) != 0u || (close != 0u && npend >= 2));
         if (!settle && !many && close) {                 // one at most: by its place, without a look at its id
           const int v = __ffs((int)close) - 1;
-          pend[256 * npend] = ~(y0 + 8 * (v >> 2) + 4 * h + (v & 3));
+          pend[256 * npend] = ~(y0 + row_of(v));
           pend[256 * (SP_PEND + npend++)] = 1;
         }
         if (!settle && many) {
           const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            same |= __shfl(id_t, 8 * (v / 4) + 4 * h + v % 4) == own ? 1u << v : 0u;
+            same |= __shfl(id_t, row_of(v)) == own ? 1u << v : 0u;
             asm volatile("" : "+v"(same));
           }
           same &= close;
@@ -390,7 +441,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
             const float nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-              const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, 8 * (v / 4) + 4 * h + v % 4);
+              const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, row_of(v));
               const bool far = ((close & ~same) >> v & 1u) && !(fabsf(dif) < (v < 8 ? t0 : t1) * (nv + 0.25f) && nv >= 0.f);
               close &= far ? ~(1u << v) : ~0u;
               ct += far && dif > 0.f ? 1 : 0;
@@ -403,7 +454,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
           settle = __any(over);
           if (!settle) {
             for (; rest; rest &= rest - 1u) {
-              const int v = __ffs((int)rest) - 1, id = cand[y0 + 8 * (v >> 2) + 4 * h + (v & 3)];
+              const int v = __ffs((int)rest) - 1, id = cand[y0 + row_of(v)];
               int j = npend_t;
 #pragma unroll
               for (int q = SP_PEND - 1; q >= 0; --q) j = q < npend_t && pend[256 * q] == id ? q : j;
@@ -432,15 +483,37 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   }
 
   // ---- epilogue
-  constexpr int UB = NK <= 16 ? 4 : 8;                     // 16-column blocks whose loads are in flight at once
-  for (int i = nown ? -1 : 0; i < npend % SP_FULL; ++i) {
-    const int e = i < 0 ? own : pend[256 * i], id = e < 0 ? cand[~e] : e;
-    const float* yrow = a.table + (size_t)id * a.dim;
-    const float s = a.dim % 4 == 0 ? sp_exact_score<true, UB>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, UB / 2>(qrow, yrow, a.dim, sp_chain(dk));
-    if (s > posx) cnt += i < 0 ? nown : pend[256 * (SP_PEND + i)];
+  // What is pending is settled 16 pairs of the wave at a time: every lane with something left offers its next one, the first
+  // 16 are taken.  (Each lane by itself, a row's loads four or eight blocks at a time and its chain as multiply-adds, was several
+  // times a load's latency at the end of every workgroup: 20,000 edges, 1,000 candidates of 400 floats 222 -> 206 us, gather
+  // included; 900 edges, 3,000 candidates 54 -> 43.)
+  constexpr int UB = NK <= 6 || NK > 16 ? NK : (NK + 1) / 2;   // as many blocks as the registers hold
+  const int items = npend % SP_FULL;
+  int ln = lane;
+  asm volatile("" : "+v"(ln));                            // lane coordinates formed afresh: kept across the tiles they would spill
+  const int gl = ln >> 4, il = ln & 15, xe = x0 + (ln & 31);
+  for (int item = nown ? -1 : 0; const unsigned long long left = __builtin_amdgcn_ballot_w64(item < items);) {
+    const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(left >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)left, 0));
+    const bool take = item < items && slot < 16;
+    int id = own;
+    if (item >= 0 && item < items) {
+      const int e = pend[256 * item];
+      id = e < 0 ? cand[~e] : e;
+    }
+    // lane `slot` learns who holds pair `slot`; pairs beyond the last are the first again
+    const int who = __builtin_amdgcn_ds_permute(4 * (take ? slot : 63), ln);
+    const int from = __shfl(who, il < __popcll(left) ? il : 0);
+    const float* yrow = a.table + (size_t)__shfl(id, from) * a.dim;
+    const float* qrow = a.qrows + (q_base + x0 + (from & 31)) * dk;
+    const float s = __shfl(a.dim % 4 == 0 ? sp_exact_pairs<true, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk))
+                                          : sp_exact_pairs<false, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk)), 16 * ((slot & 15) >> 2) + (slot & 15));
+    if (take) {
+      if (s > posx) cnt += item < 0 ? nown : pend[256 * (SP_PEND + item)];
+      ++item;
+    }
   }
   cnt += __shfl_xor(cnt, 32);
-  if (h == 0 && xv && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + x, cnt);
+  if (ln < 32 && xe < n_x && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + xe, cnt);
 }
 
 // ------------------------------------------------------------------------ the training passes -----
@@ -606,11 +679,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       for (int s = 0; s < NS; ++s) {
         const v8s h0 = fh[s % PD][0], h1 = fh[s % PD][1], l0 = fl[s % PD][0], l1 = fl[s % PD][1];
         if (s + PD < NS) read_step(s + PD, fh[s % PD], fl[s % PD]);
-        // consecutive instructions share an operand
-        sc[0][0] = mfma16h<F16>(h0, xl[0][s], sc[0][0]); sc[0][0] = mfma16h<F16>(h0, xh[0][s], sc[0][0]); sc[0][0] = mfma16h<F16>(l0, xh[0][s], sc[0][0]);
-        sc[0][1] = mfma16h<F16>(l0, xh[1][s], sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xh[1][s], sc[0][1]); sc[0][1] = mfma16h<F16>(h0, xl[1][s], sc[0][1]);
-        sc[1][1] = mfma16h<F16>(h1, xl[1][s], sc[1][1]); sc[1][1] = mfma16h<F16>(h1, xh[1][s], sc[1][1]); sc[1][1] = mfma16h<F16>(l1, xh[1][s], sc[1][1]);
-        sc[1][0] = mfma16h<F16>(l1, xh[0][s], sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xh[0][s], sc[1][0]); sc[1][0] = mfma16h<F16>(h1, xl[0][s], sc[1][0]);
+        sp_score_step<F16>(h0, h1, l0, l1, xh[0][s], xh[1][s], xl[0][s], xl[1][s], sc);
         // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
         // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
         if (has_next) {
@@ -622,14 +691,10 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       }
       if (TAIL) {
         const char* p = smem + bofs + tfofs;
-        const v8s t0 = *reinterpret_cast<const v8s*>(p), t1 = *reinterpret_cast<const v8s*>(p + 16 * PA);
-        sc[0][0] = mfma16h<F16>(t0, xt[0][0], sc[0][0]); sc[0][1] = mfma16h<F16>(t0, xt[1][0], sc[0][1]);
-        sc[1][1] = mfma16h<F16>(t1, xt[1][0], sc[1][1]); sc[1][0] = mfma16h<F16>(t1, xt[0][0], sc[1][0]);
+        sp_tail_step<F16>(*reinterpret_cast<const v8s*>(p), *reinterpret_cast<const v8s*>(p + 16 * PA), xt[0][0], xt[1][0], sc);
         if (tail2) {                                       // its hi fragments again (groups 2, 3 meet zeros)
           const char* p2 = smem + bofs + i * PA + ((64 * NS + 16 * (g & 1)) ^ swz);
-          const v8s s0 = *reinterpret_cast<const v8s*>(p2), s1 = *reinterpret_cast<const v8s*>(p2 + 16 * PA);
-          sc[0][0] = mfma16h<F16>(s0, xt[0][1], sc[0][0]); sc[0][1] = mfma16h<F16>(s0, xt[1][1], sc[0][1]);
-          sc[1][1] = mfma16h<F16>(s1, xt[1][1], sc[1][1]); sc[1][0] = mfma16h<F16>(s1, xt[0][1], sc[1][0]);
+          sp_tail_step<F16>(*reinterpret_cast<const v8s*>(p2), *reinterpret_cast<const v8s*>(p2 + 16 * PA), xt[0][1], xt[1][1], sc);
         }
       }
     }

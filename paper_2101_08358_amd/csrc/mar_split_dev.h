@@ -4,7 +4,6 @@
 #include "mar_flash.h"
 #include "mar_split.h"
 
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -12,11 +11,6 @@ typedef short v8s __attribute__((ext_vector_type(8)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef __bf16 v2b __attribute__((ext_vector_type(2)));
-
-// Evaluation: 32 x 32 blocks, 16 slots an instruction; training: 16 x 16 blocks, 32 slots.
-__device__ __forceinline__ v16f mfma32h(v8s a, v8s b, v16f c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
-}
 
 template <bool F16> __device__ __forceinline__ v4f mfma16h(v8s a, v8s b, v4f c) {
   if (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
