@@ -73,6 +73,17 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
   *sy = (int32_t)((ntiles + *tps - 1) / *tps);
 }
 
+// Evaluation of rows above 256 floats (a workgroup a CU): equal shares, one a CU, in place of parts.  A share has no last,
+// partly filled round, but its workgroup begins anew at every unit it enters; where that does not save a tenth by the estimate
+// above, parts of units stay.  400 floats, gather included, us (parts / shares): 20 x 1,000 edges, 1,000 candidates 206 / 188,
+// 37 x 611, 777: 207 / 204, 100 x 1,000, 1,000: 925 / 933, 1 x 900, 3,000: 43 / 48.  With two or three workgroups a CU the other
+// ones fill the round: shares of 100 floats took 2 to 8 % longer at all sizes.
+bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps) {
+  if (!mar_split_shares(d.dk) || units * ntiles < 8 * MAR_SHARES) return false;
+  const long share = (units * ntiles + MAR_SHARES - 1) / MAR_SHARES, pieces = 1 + (share - 2 + ntiles) / ntiles;
+  return (double)(share + 8 * pieces) < 0.9 * (double)((units * sy + 255) / 256 * (tps + 8));
+}
+
 // Large batches: the units of a pass rarely fill a whole number of rounds of the chip's workgroup slots (256 CUs x
 // workgroups per CU), and the last, partly filled round costs as much time as a full one.  The units beyond the last
 // whole round are split into k parts.  TransE (pass 1 only): as many as fill one round.  Bilinear models: the

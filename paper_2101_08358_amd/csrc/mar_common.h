@@ -170,9 +170,12 @@ int mar_split_supported(int dk);
 int mar_split_wgs_per_cu(int dk, int pass);
 #define MAR_SPLIT_STRIPE_ROWS 128
 #define MAR_SPLIT_TILE_ROWS 32
+#define MAR_SHARES 256            // workgroups of an evaluation cut into equal shares: one a CU
 static inline int mar_stripe_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }
 static inline int mar_tile_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_TILE_ROWS : mar_flash_tile_rows(d.dk, pass); }
 // How many workgroups share one of `units` units of a pass, and the streamed tiles each takes (n_y streamed rows).
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps);
+bool mar_split_shares(int dk);                     // an evaluation on images can cut all units' tiles into equal shares
+bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps);   // and should, rather than `sy` parts a unit
 size_t mar_split_image_bytes(int dk);
 hipError_t mar_split_prepare(int dk);

@@ -41,6 +41,8 @@ struct FlashArgs {
   // evaluation of the bilinear models: fp32 edge-side operands [2][B][dk], the node table and the ids, from which
   // close comparisons are settled
   const float *qrows, *ynorm, *table; const int32_t *neg_dst, *neg_src, *src, *dst; int32_t dim;
+  // evaluation on images, where share > 0: workgroup p takes `share` tiles of the units' tiles, one more if p < share_rest
+  int64_t share; int32_t share_rest;
   const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
 
@@ -48,7 +50,7 @@ struct FlashArgs {
 // contiguous eighth of the units, so that the workgroups of one chunk-side share an L2 and every XCD gets the same
 // number of units however few chunk-sides there are.
 struct FlashUnit { int unit, cs, stripe, part, tps; bool rem; };
-__device__ __forceinline__ bool flash_unit(const FlashArgs& a, FlashUnit& u) {
+template <typename A> __device__ __forceinline__ bool flash_unit(const A& a, FlashUnit& u) {
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   u.rem = slot >= a.wslots;
   if (!u.rem) {

@@ -928,7 +928,12 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   }
   a.wslots = (a.whole_units * a.sy + 7) / 8;
   a.rslots = ((a.units - a.whole_units) * a.rem_k + 7) / 8;
-  const dim3 grid(8u * (unsigned)(a.wslots + a.rslots));
+  dim3 grid(8u * (unsigned)(a.wslots + a.rslots));
+  if (d.bilinear && pass == 3 && mar_plan_shares(d, a.units, a.yimg_tiles, a.sy, a.tps)) {
+    const int64_t tiles = (int64_t)a.units * a.yimg_tiles;
+    grid.x = MAR_SHARES;
+    a.share = tiles / MAR_SHARES; a.share_rest = (int32_t)(tiles % MAR_SHARES);
+  }
   if (dense) pass = 4;
   if (d.bilinear) return mar_split_launch(a, pass, f16, grid, st);
   const int nk = d.dk / 4;

@@ -163,34 +163,92 @@ __device__ __forceinline__ float sum_of_squares(v8s v) {
 constexpr int sp_waves(int nk, int pass) { return pass == 3 ? (nk <= 8 ? 3 : (nk <= 16 ? 2 : 1)) : (nk <= 8 ? 2 : 1); }
 
 // ---------------------------------------------------------------------------- evaluation -----
+// What a workgroup takes of all units' tiles, counted one unit after the other: a unit's part, or (rows above 256 floats) an
+// equal share wherever it ends, for counts need no merging.  As in flash_unit an XCD's workgroups take neighbouring shares.
+// A border one tile off a unit's is moved there: a piece of one tile costs its stationary rows all the same.
+constexpr bool sp_shares(int nk) { return nk > 16; }
+template <typename A> __device__ __forceinline__ bool eval_tiles(const A& a, int64_t& at, int64_t& at_end) {
+  const int ntiles = (a.N + SP_TY - 1) / SP_TY;
+  if (!a.share) {
+    FlashUnit u;
+    if (!flash_unit(a, u)) return false;
+    at = (int64_t)u.unit * ntiles + u.part * a.tps;
+    at_end = min(at + a.tps, (int64_t)(u.unit + 1) * ntiles);
+    return true;
+  }
+  const int p = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  auto border = [&](int q) {
+    const int64_t b = q * a.share + min(q, a.share_rest), in = b % ntiles;
+    return in == 1 ? b - 1 : (in == ntiles - 1 ? b + 1 : b);
+  };
+  at = border(p);
+  at_end = border(p + 1);
+  return at < at_end;
+}
+typedef const __attribute__((address_space(4))) FlashArgs KernelArgs;
+
 // PASS 3: counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add their counts.
 template <int NK>
-__device__ __forceinline__ void split_eval(const FlashArgs& a) {
+__device__ __forceinline__ void split_eval() {
   typedef SplitGeom<NK> SG;
   constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
   constexpr int TY = SP_TY;
   constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
   constexpr int NS = NK / 2;                               // whole steps of 32 columns
+  constexpr bool SHARES = sp_shares(NK);
   constexpr bool TAIL = NK % 2 != 0;                       // and 16 columns more
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  KernelArgs* args = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  int64_t at, at_end;
+  if (!eval_tiles(*args, at, at_end)) return;
+  do {                                                     // one piece: tiles t_begin .. ntiles - 1 of one unit
+  // the arguments are read again, and the lane's coordinates formed again, for every piece: kept across them they spill
+  int tid = threadIdx.x;
+  if (SHARES) asm volatile("" : "+s"(args), "+v"(tid));
+  KernelArgs& a = *args;
+  const int lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, i = lane & 15;                  // of the matrix instructions
   const int h = lane >> 5, m = lane & 31;                  // of the comparisons: edge m, half of the tile's rows
-  FlashUnit u;
-  if (!flash_unit(a, u)) return;
-  const int cs = u.cs, side = cs & 1, c = cs >> 1;
-  const int ne = min(a.S, a.n - c * a.S);                 // edges in this chunk
-  const int n_x = ne, n_y = a.N;                           // stationary, streamed rows
-  if (u.stripe * SP_SR >= n_x) return;
+  const int n_y = a.N, ntiles_all = (n_y + TY - 1) / TY;  // streamed rows and their tiles
+  const int unit = (int)(at / ntiles_all), t_begin = (int)(at - (int64_t)unit * ntiles_all);
+  const int ntiles = (int)min((int64_t)ntiles_all, t_begin + (at_end - at));
+  at += ntiles - t_begin;
+  const int cs = unit / a.nstripes, stripe = unit % a.nstripes, side = cs & 1, c = cs >> 1;
+  const int n_x = min(a.S, a.n - c * a.S);                // stationary rows: edges in this chunk
+  if (stripe * SP_SR >= n_x) continue;
   const size_t q_base = (size_t)side * a.B + (size_t)c * a.S;        // first Q row of the chunk
   const int dk = a.dk;
 
-  // ---- stationary fragments and their tail, as in split_pass
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  const int x0 = u.stripe * SP_SR + wave_s * 32, x = x0 + m;   // the wave's first row, the lane's
+  // ---- images of the streamed rows, copied into LDS one tile ahead; a register load issued behind the copies is the
+  // fence (memory operations of a wave complete in order): once its value is there the image is in LDS.  The fence is
+  // the load of the tile's two exponents and of its blocks' norms.
+  const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
+  const BufRsrc expsrc = buf_rsrc(a.yexp + (size_t)cs * a.yimg_tiles * 2, (uint32_t)a.yimg_tiles * 8);
+  float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f);
+  const BufRsrc normsrc = buf_rsrc(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS, (uint32_t)a.yimg_tiles * (SP_NORMS * 4));
+  int token = 0;
+  auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
+    const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
+    const int pc = 4 * q + wave_s;
+    if (pc < SG::NCH) buf_load4_to_lds(ywords, lds_address_b(smem) + buf * IMG + pc * 1024, lane * 16, pc * 1024, token);
+  };
+  auto dma_fence = [&](int t) {
+    ye_next = buf_load2(expsrc, token, t * 8);
+    yn_next = buf_load2(normsrc, token, t * (SP_NORMS * 4));
+  };
+  auto dma_land = [&]() { asm volatile("" : "+v"(ye_next.x), "+v"(ye_next.y)); };
+  // The first tile is on its way while the stationary fragments are fetched.
+  if (SHARES) __syncthreads();                             // every wave is done with the piece before
+#pragma unroll
+  for (int q = 0; q < NCW; ++q) dma_piece(t_begin, 0, q);
+  dma_fence(t_begin);
+
+  // ---- stationary fragments and their tail, as in split_pass
+  const int x0 = stripe * SP_SR + wave_s * 32, x = x0 + m;   // the wave's first row, the lane's
   const bool xv = x < n_x;
-  const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave_s;
+  const size_t xtile = (size_t)cs * a.ximg_tiles + stripe * (SP_SR / TY) + wave_s;
   const int swz = 16 * sp_swizzle(UNITS, i);              // of rows i and 16 + i of a tile, in bytes
   const v8s zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   v8s xh[2][NS], xl[2][NS], xt[2][2];
@@ -230,7 +288,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   // 2^14 at least.  A zero row's scores are exactly zero.
   float posx = 0.f, tolx = 0.f;
   const float* qrow = nullptr;
-  int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + threadIdx.x;
+  int* const pend = reinterpret_cast<int*>(smem + 2 * IMG) + tid;
   int npend = 0;                                           // pending candidates; + SP_FULL: no more are taken
   float n2;
   {
@@ -288,41 +346,13 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   int cnt = 0;
   auto row_of = [&](int v) { return 16 * (v >> 3) + 8 * h + (v & 7); };   // of a lane's pair v within the tile
 
-  const int ntiles_all = (n_y + TY - 1) / TY;
-  const int t_begin = u.part * u.tps;
-  const int ntiles = min(ntiles_all, t_begin + u.tps);
-
-  // ---- images of the streamed rows, copied into LDS one tile ahead; a register load issued behind the copies is the
-  // fence (memory operations of a wave complete in order): once its value is there the image is in LDS.  The fence is
-  // the load of the tile's two exponents and of its blocks' norms.
-  const char* ybase = a.yimg + (size_t)cs * a.yimg_tiles * IMG;
-  const BufRsrc expsrc = buf_rsrc(a.yexp + (size_t)cs * a.yimg_tiles * 2, (uint32_t)a.yimg_tiles * 8);
-  float2 ye_next = make_float2(0.f, 0.f), yn_next = make_float2(0.f, 0.f);
-  const BufRsrc normsrc = buf_rsrc(a.ynorm + (size_t)cs * a.yimg_tiles * SP_NORMS, (uint32_t)a.yimg_tiles * (SP_NORMS * 4));
-  int token = 0;
-  auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
-    const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
-    const int pc = 4 * q + wave_s;
-    if (pc < SG::NCH) buf_load4_to_lds(ywords, lds_address_b(smem) + buf * IMG + pc * 1024, lane * 16, pc * 1024, token);
-  };
-  auto dma_fence = [&](int t) {
-    ye_next = buf_load2(expsrc, token, t * 8);
-    yn_next = buf_load2(normsrc, token, t * (SP_NORMS * 4));
-  };
-  auto dma_land = [&]() { asm volatile("" : "+v"(ye_next.x), "+v"(ye_next.y)); };
-  if (t_begin < ntiles) {
-#pragma unroll
-    for (int q = 0; q < NCW; ++q) dma_piece(t_begin, 0, q);
-    dma_fence(t_begin);
-    dma_land();
-    __syncthreads();
-  }
-
   // Where a lane reads in a tile's buffer (as in split_pass)
   constexpr int GU = sp_group(UNITS);
   const int fofs = i * PA + ((16 * g) ^ swz);
   const int tfofs = i * PA + (tail2 ? (g & 2 ? PLANE : 0) + ((64 * NS + 16 * (g & 1)) ^ swz) : (g == 1 ? PLANE : 0) + ((64 * NS) ^ swz));
   auto at = [](int base, int byte) { return (base ^ (byte % (16 * GU))) + byte / (16 * GU) * (16 * GU); };
+  dma_land();
+  __syncthreads();
   for (int t = t_begin; t < ntiles; ++t) {
     const int buf = (t - t_begin) & 1;
     const int bofs = buf * IMG;
@@ -514,6 +544,7 @@ __device__ __forceinline__ void split_eval(const FlashArgs& a) {
   }
   cnt += __shfl_xor(cnt, 32);
   if (ln < 32 && xe < n_x && cnt) atomicAdd((side == MAR_SIDE_DST ? a.rank_dst : a.rank_src) + (size_t)c * a.S + xe, cnt);
+  } while (SHARES && at < at_end);
 }
 
 // ------------------------------------------------------------------------ the training passes -----
@@ -861,7 +892,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
 template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
-  if constexpr (PASS == 3) split_eval<NK>(a);
+  if constexpr (PASS == 3) split_eval<NK>();
   else split_pass<NK, PASS, F16>(a);
 }
 
@@ -889,6 +920,7 @@ __global__ void __launch_bounds__(256) k_split_merge2(FlashArgs a) {
 // ------------------------------------------------------------------- launchers -----
 int mar_split_supported(int dk) { return dk >= 4 && dk <= 400; }
 int mar_split_wgs_per_cu(int dk, int pass) { return sp_waves(sp_nk(dk), pass); }
+bool mar_split_shares(int dk) { return sp_shares(sp_nk(dk)); }
 size_t mar_split_image_bytes(int dk) { return (size_t)sp_image(sp_nk(dk)); }
 
 template <int NK> static hipError_t sp_prepare() {
