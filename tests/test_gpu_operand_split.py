@@ -242,6 +242,40 @@ def test_small_and_large_evaluations_rank_alike(model, dim):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dim,C,S,N", ((4, 3, 1100, 1000), (24, 3, 1100, 1000), (28, 3, 1100, 1000), (104, 3, 1100, 1000), (105, 3, 1100, 1000),
+                                       (112, 3, 1100, 1000), (124, 3, 1100, 1000), (392, 3, 1100, 1000),
+                                       (400, 19, 1000, 997), (393, 33, 500, 333), (260, 34, 500, 338)))
+def test_chunks_evaluated_together_rank_as_each_alone(dim, C, S, N):
+    """A chunk alone takes the fp32 instructions, all together the operand images: rows whose last columns fill a whole, half or
+    quarter step, and (the last three) tiles cut into shares that end inside a stripe, with stripes of the last chunk empty."""
+    print("case", dim, C, S, N, flush=True)
+    rng = np.random.default_rng(dim)
+    V, R, B, n = 3000, 5, C * S, C * S - S // 2
+    ne, re_ = ((rng.standard_normal((k, dim)) * 0.3).astype(np.float32) for k in (V, R))
+    ids = [torch.from_numpy(rng.integers(0, k, n).astype(np.int32)).to("cuda:0") for k in (V, R, V)]
+    tr = mar.Trainer(V, R, dim, DISTMULT, B, C, N, device="cuda:0", node_emb=ne, rel_emb=re_)
+    tr.sample_negatives(0)
+    tr.neg_dst[3:N:7] = ids[2][:len(range(3, N, 7))]       # edges' own endpoints among the candidates
+    all_ = tr.eval_scores(*ids)
+    one = mar.Trainer(V, R, dim, DISTMULT, S, 1, N, device="cuda:0", node_emb=ne, rel_emb=re_)
+    for c in (0, 1, C // 2, C - 2, C - 1):
+        one.neg_src, one.neg_dst = tr.neg_src[c * N:(c + 1) * N].clone(), tr.neg_dst[c * N:(c + 1) * N].clone()
+        at = slice(c * S, min((c + 1) * S, n))
+        alone = one.eval_scores(*(x[at].clone() for x in ids))
+        for a, b in zip(all_, alone):
+            assert torch.equal(a[at], b), (dim, c, int((a[at] != b).sum()))
+    torch.cuda.synchronize()
+    tr.close()
+    one.close()
+
+
+@pytest.mark.parametrize("dim", (8, 24, 25, 56, 57, 104, 105, 120, 121, 184, 248, 392, 393))
+def test_step_where_the_last_columns_fill_half_a_block_or_a_little_more(dim):
+    """Up to 8 columns of the last block share their instructions (hi and lo parts side by side), from 9 on they do not."""
+    print("case", dim, flush=True)
+    print(check_step(run_step_both(DISTMULT, 2000, 3, dim, 130, 1, 70, 130, seed=dim, std=0.3)), flush=True)
+
+
 def test_close_comparisons_cost_about_as_much_as_others():
     """Candidates drawn by degree hold an edge's own endpoint many times, and rows may be equal: both evaluations within 6
     times that of candidates without ties (1.3 and 3.2 times here; one comparison after the other 20 to 60 times)."""
