@@ -390,30 +390,24 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
     HIP_TRY(hipEventRecord(c->ev_pass1, st), "fork");
     HIP_TRY(hipStreamWaitEvent(ax, c->ev_pass1, 0), "fork");
     MARK(4, 0, ax);
-    HIP_TRY(mar_launch_chain(c, b, ax), "chain-rule kernel");
+    HIP_TRY(mar_launch_chain(c, b, dbg, ax), "chain-rule kernel");
     MARK(4, 1, ax);
     HIP_TRY(hipEventRecord(c->ev_chain, ax), "join");
   } else {
     MARK(4, 0, st);
-    HIP_TRY(mar_launch_chain(c, b, st), "chain-rule kernel");
+    HIP_TRY(mar_launch_chain(c, b, dbg, st), "chain-rule kernel");
     MARK(4, 1, st);
-    HIP_TRY(hipEventRecord(c->ev_chain, st), "join");
   }
   MARK(3, 0, st);
   HIP_TRY(mar_launch_flash(c, b, 2, nullptr, nullptr, st), "negative-gradient kernel");
   MARK(3, 1, st);
   HIP_TRY(hipStreamWaitEvent(st, c->ev_index, 0), "join");
-  HIP_TRY(hipStreamWaitEvent(st, c->ev_chain, 0), "join");
+  if (c->dm.index_after_gather) HIP_TRY(hipStreamWaitEvent(st, c->ev_chain, 0), "join");
   MARK(5, 0, st);
   HIP_TRY(mar_launch_reduce(c, b, loss_sum_out, dbg ? dbg->grad_rows : nullptr, nullptr, st), "reduce/Adagrad kernels");
   MARK(5, 1, st);
 #undef MARK
   if (ev) c->prof_steps++;
-  if (dbg) {
-    const size_t nb = (size_t)n_edges * sizeof(float);
-    if (dbg->lse_dst) HIP_TRY(hipMemcpyAsync(dbg->lse_dst, c->L.lse + (size_t)MAR_SIDE_DST * c->dm.B, nb, hipMemcpyDeviceToDevice, st), "debug copy");
-    if (dbg->lse_src) HIP_TRY(hipMemcpyAsync(dbg->lse_src, c->L.lse + (size_t)MAR_SIDE_SRC * c->dm.B, nb, hipMemcpyDeviceToDevice, st), "debug copy");
-  }
   return MAR_OK;
 }
 
@@ -662,7 +656,7 @@ extern "C" int mar_pipe_submit(mar_pipe* p, const int32_t* src, const int32_t* r
   PIPE_TRY(mar_launch_prep(c, ps.b_rank, nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
   PIPE_TRY(mar_launch_flash(c, ps.b_rank, 1, nullptr, nullptr, st), "score/softmax kernel");
   PIPE_TRY(mar_launch_flash_merge(c, ps.b_rank, st), "stripe merge kernel");
-  PIPE_TRY(mar_launch_chain(c, ps.b_rank, st), "chain-rule kernel");
+  PIPE_TRY(mar_launch_chain(c, ps.b_rank, nullptr, st), "chain-rule kernel");
   PIPE_TRY(mar_launch_flash(c, ps.b_rank, 2, nullptr, nullptr, st), "negative-gradient kernel");
   PIPE_TRY(mar_launch_reduce(c, ps.b_ids, loss_sum_out, nullptr, ps.sg.gsum, st), "reduce kernels");
   PIPE_TRY(hipEventRecord(ps.ev_step, st), "step");

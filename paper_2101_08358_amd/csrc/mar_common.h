@@ -27,7 +27,7 @@ struct MarLayout {
   float*    qq;           // [2][batch] squared norms of Q rows (TransE)
   float*    kk;           // [2][chunks*N] squared norms of Km rows (TransE)
   float*    pos;          // [batch] positive scores
-  float*    lse;          // [2][batch] log-sum-exp per edge and side
+  float*    lse;          // [2][batch] log-sum-exp per edge and side, where no caller asks for it
   float*    gQ;           // [sy1][2][batch][dk] per-part unnormalised gradient w.r.t. Q rows; bilinear models' evaluation: fp32 operands
   float*    ml;           // [sy1][2][batch][2] per-part softmax reference (bilinear models: in log2 units) and sum
   float*    gQx;          // [rem1.k - 1][rem1.rows][dk] parts 1.. of the stripes that are split to fill the last round
@@ -137,7 +137,8 @@ hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, 
 bool mar_eval_dense(const MarDims& d, const MarBatch& b);
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
                             hipStream_t st);
-hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, hipStream_t st);
+// dbg: where the log-sum-exps go if a caller asks for them
+hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st);
 hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t* dst_off, const int32_t* dst_ids,
                              const int64_t* src_off, const int32_t* src_ids, const float* pos, int32_t* rank_dst,
                              int32_t* rank_src, hipStream_t st);

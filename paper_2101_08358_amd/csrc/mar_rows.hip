@@ -432,7 +432,7 @@ __device__ __forceinline__ void chain_complex(float sr, float si, float rr, floa
 template <int GL, int NV, int MODEL, bool VEC, int SY1>
 __global__ void __launch_bounds__(256)
 k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, const float* __restrict__ pos,
-        float* __restrict__ lse, float* __restrict__ G, float* __restrict__ loss_part) {
+        float* __restrict__ lse_dst, float* __restrict__ lse_src, float* __restrict__ G, float* __restrict__ loss_part) {
   constexpr int GPB = 256 / GL;
   constexpr int P = SY1 ? SY1 : MAR_MAX_PARTS;
   __shared__ float lsum[GPB];
@@ -449,7 +449,7 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
     const float lse_u = merge_parts(ml, row_u, part_rows, sy1, a.ml_log2, facu);
     const float lse_w = merge_parts(ml, row_w, part_rows, sy1, a.ml_log2, facw);
     const float pe = pos[e];
-    if (l == 0) { lse[row_u] = lse_u; lse[row_w] = lse_w; }
+    if (l == 0) { lse_dst[e] = lse_u; lse_src[e] = lse_w; }
     le = -2.f * pe + lse_u + lse_w;
     const float* gu0 = gQ + row_u * dk;
     const float* gw0 = gQ + row_w * dk;
@@ -1166,33 +1166,35 @@ hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t*
 }
 
 template <int GL, int NV, int MODEL>
-static void launch_chain(const RowArgs& a, const MarLayout& L, dim3 grid, hipStream_t st) {
-#define CHAIN(V, S) hipLaunchKernelGGL((k_chain<GL, NV, MODEL, V, S>), grid, dim3(256), 0, st, a, L.gQ, L.ml, L.pos, L.lse, L.G, L.loss_part)
+static void launch_chain(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, hipStream_t st) {
+#define CHAIN(V, S) hipLaunchKernelGGL((k_chain<GL, NV, MODEL, V, S>), grid, dim3(256), 0, st, a, L.gQ, L.ml, L.pos, lse_dst, lse_src, L.G, L.loss_part)
   if (a.dim % 4 == 0) { if (a.sy1 == 1) CHAIN(true, 1); else if (a.sy1 == 2) CHAIN(true, 2); else CHAIN(true, 0); }
   else CHAIN(false, 0);
 #undef CHAIN
 }
 
 template <int GL, int NV>
-static void launch_chain_model(const RowArgs& a, const MarLayout& L, dim3 grid, hipStream_t st) {
+static void launch_chain_model(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, hipStream_t st) {
   switch (a.model) {
-    case MAR_MODEL_DISTMULT: launch_chain<GL, NV, MAR_MODEL_DISTMULT>(a, L, grid, st); break;
-    case MAR_MODEL_COMPLEX:  launch_chain<GL, NV, MAR_MODEL_COMPLEX>(a, L, grid, st); break;
-    case MAR_MODEL_TRANSE:   launch_chain<GL, NV, MAR_MODEL_TRANSE>(a, L, grid, st); break;
-    default:                 launch_chain<GL, NV, MAR_MODEL_DOT>(a, L, grid, st); break;
+    case MAR_MODEL_DISTMULT: launch_chain<GL, NV, MAR_MODEL_DISTMULT>(a, L, lse_dst, lse_src, grid, st); break;
+    case MAR_MODEL_COMPLEX:  launch_chain<GL, NV, MAR_MODEL_COMPLEX>(a, L, lse_dst, lse_src, grid, st); break;
+    case MAR_MODEL_TRANSE:   launch_chain<GL, NV, MAR_MODEL_TRANSE>(a, L, lse_dst, lse_src, grid, st); break;
+    default:                 launch_chain<GL, NV, MAR_MODEL_DOT>(a, L, lse_dst, lse_src, grid, st); break;
   }
 }
 
-hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, hipStream_t st) {
+hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st) {
   const MarLayout& L = c->L;
   RowArgs a = row_args(c, b);
   const int GL = mar_lane_group(a.dk), gpb = 256 / GL;
   const dim3 grid((b.n + gpb - 1) / gpb);
+  float* lse_dst = dbg && dbg->lse_dst ? dbg->lse_dst : L.lse + (size_t)MAR_SIDE_DST * c->dm.B;
+  float* lse_src = dbg && dbg->lse_src ? dbg->lse_src : L.lse + (size_t)MAR_SIDE_SRC * c->dm.B;
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
-  if (GL == 16) launch_chain_model<16, 1>(a, L, grid, st);
-  else if (GL == 32) launch_chain_model<32, 1>(a, L, grid, st);
-  else if (a.dk <= 256) launch_chain_model<64, 1>(a, L, grid, st);
-  else launch_chain_model<64, 2>(a, L, grid, st);
+  if (GL == 16) launch_chain_model<16, 1>(a, L, lse_dst, lse_src, grid, st);
+  else if (GL == 32) launch_chain_model<32, 1>(a, L, lse_dst, lse_src, grid, st);
+  else if (a.dk <= 256) launch_chain_model<64, 1>(a, L, lse_dst, lse_src, grid, st);
+  else launch_chain_model<64, 2>(a, L, lse_dst, lse_src, grid, st);
   return hipGetLastError();
 }
 
