@@ -192,6 +192,12 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   d->sort_items = ((d->n_pos_max + 1023) / 1024) << d->sort_bits <= 32768 ? 4 : 16;
   // score pairs x row width per step: above ~2e9 the contraction passes are long enough to hide the index build
   d->index_after_gather = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 2.0e9;
+  // A small batch's order is one workgroup's work: one launch for two a pass, which the host cannot issue as fast as the step
+  // runs.  Above 256 floats the kernels take longer than the host, and 11,000 rows in one workgroup 4 % longer than they do.
+  d->sort_one = d->dk <= 256 ? MAR_SORT_ONE : MAR_SORT_ONE / 2;
+  // The smallest ones are ordered on the caller's stream: the fork and the join are half of the host's time (200 edges, 50
+  // negatives, 100 floats: a step 63 us forked, 48 on one stream; 1,000 edges, 100 negatives 72 and 76).
+  d->one_stream = d->n_pos_max <= MAR_SORT_ONE / 4 && !d->index_after_gather;
   return MAR_OK;
 }
 
@@ -354,7 +360,7 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   }
   // Two streams: the caller's carries the gather and the two contraction passes; the index build
   // (needed only by the per-row reduce) and the chain rule (needs pass 1 only) run beside them on `aux`.
-  hipStream_t ax = c->aux;
+  hipStream_t ax = c->dm.one_stream ? st : c->aux;
   hipEvent_t* ev = nullptr;
   if (c->prof_events && c->prof_steps < c->prof_max) ev = c->prof_events + (size_t)c->prof_steps * 2 * MAR_NUM_PHASES;
 #define MARK(phase, end, stream) do { if (ev && (c->prof_mask >> (phase) & 1u)) HIP_TRY(hipEventRecord(ev[2 * (phase) + (end)], stream), "event record"); } while (0)
@@ -366,14 +372,16 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
     HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
     MARK(1, 1, st);
   }
-  HIP_TRY(hipEventRecord(c->ev_fork, st), "fork");
-  HIP_TRY(hipStreamWaitEvent(ax, c->ev_fork, 0), "fork");
+  if (ax != st) {
+    HIP_TRY(hipEventRecord(c->ev_fork, st), "fork");
+    HIP_TRY(hipStreamWaitEvent(ax, c->ev_fork, 0), "fork");
+  }
   MARK(0, 0, ax);
   const int ranks = dbg && (dbg->num_uniq || dbg->uniq_nodes || dbg->uniq_rels || dbg->grad_rows);
   HIP_TRY(mar_launch_index(c, b, ranks, ax), "index kernels");
   if (dbg) HIP_TRY(mar_launch_debug_copy(c, b, dbg, ax), "debug copy");
   MARK(0, 1, ax);
-  HIP_TRY(hipEventRecord(c->ev_index, ax), "join");
+  if (ax != st) HIP_TRY(hipEventRecord(c->ev_index, ax), "join");
   if (!c->dm.index_after_gather) {
     MARK(1, 0, st);
     HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
@@ -401,7 +409,7 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   MARK(3, 0, st);
   HIP_TRY(mar_launch_flash(c, b, 2, nullptr, nullptr, st), "negative-gradient kernel");
   MARK(3, 1, st);
-  HIP_TRY(hipStreamWaitEvent(st, c->ev_index, 0), "join");
+  if (ax != st) HIP_TRY(hipStreamWaitEvent(st, c->ev_index, 0), "join");
   if (c->dm.index_after_gather) HIP_TRY(hipStreamWaitEvent(st, c->ev_chain, 0), "join");
   MARK(5, 0, st);
   HIP_TRY(mar_launch_reduce(c, b, loss_sum_out, dbg ? dbg->grad_rows : nullptr, nullptr, st), "reduce/Adagrad kernels");

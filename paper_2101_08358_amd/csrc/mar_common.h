@@ -71,6 +71,8 @@ struct MarDims {
   int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
   int32_t reduce_small;            // the reduce gives a lane group MAR_REDUCE_SMALL positions instead of one per lane
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
+  int32_t sort_one;                // most gradient rows that one workgroup sorts by itself
+  int32_t one_stream;              // row order on the caller's stream (smallest batches)
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
 };
 
@@ -97,6 +99,7 @@ void mar_set_error(const char* fmt, ...);
 
 // Radix sort of the gradient rows by unified id: the widest digit.
 #define MAR_SORT_MAX_BITS 9
+#define MAR_SORT_ONE (16 * 1024)  // most elements k_sort_one can hold
 #define MAR_RANK_TILE 1024        // positions per workgroup of the rank kernels
 
 // Rank metrics: ranks per partial record, records a scratch area holds, bytes per record.

@@ -53,3 +53,16 @@ def test_the_step_is_the_same_without_debug_outputs(dim, R):
         tr.close()
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dim,B,C,N", ((8, 1, 1, 1), (8, 320, 1, 64), (12, 2730, 1, 1), (12, 2731, 1, 1), (8, 5461, 1, 1), (8, 5462, 1, 1), (260, 2500, 1, 64), (8, 900, 9, 100), (8, 1600, 16, 90)))
+def test_orders_that_one_workgroup_sorts(dim, B, C, N):
+    """Three rows an edge and two or more a negative: batches up to and just beyond what one workgroup holds in 8 and in 16
+    rounds (8,192 and 16,384 rows), hot ids among them, one pass and three.  (Wide rows with 64 negatives: with one, the loss is
+    sum(-2 f + f' + f'') of scores that nearly cancel, and its rounding, 2^-24 sum(2 |f| + |f'| + |f''|), was 1.3e-4 of it.)"""
+    for V in (200, 300_000):
+        rng = np.random.default_rng(V + B)
+        hot = lambda m: np.where(rng.random(m) < 0.4, rng.integers(0, 3, m), rng.integers(0, V, m)).astype(np.int32)
+        ids = (hot(B), rng.integers(0, 2, B).astype(np.int32), hot(B), hot(C * N).reshape(C, N), hot(C * N).reshape(C, N))
+        print("case", V, dim, B, flush=True)
+        print(check_step(run_step_both(0, V, 2, dim, B, C, N, B, seed=1, std=0.2, ids=ids)), flush=True)
