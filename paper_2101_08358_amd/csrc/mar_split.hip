@@ -59,6 +59,43 @@
 // multiply-adds -- in the column order of the fp32 contraction kernels: blocks of 16 columns up to column `chain`, each
 // as columns 4 g + i for i = 0..3, g = 0..3; the rest in sequence.  So do blocks that hold an infinity or a NaN.
 constexpr int sp_chain(int dk) { return dk <= 52 ? 48 : (dk <= 100 ? 96 : 400); }
+template <bool VEC, int UB>
+__device__ __forceinline__ float sp_exact_score(const float* __restrict__ q, const float* __restrict__ y, int dim, int chain) {
+  float s = 0.f;
+  const int nb = (min(chain, dim) + 15) / 16;
+  for (int b0 = 0; b0 < nb; b0 += UB) {
+    float a[UB][16], c[UB][16];
+#pragma unroll
+    for (int b = 0; b < UB; ++b) {
+#pragma unroll
+      for (int i = 0; i < 16; i += 4) {
+        const int k = 16 * (b0 + b) + i;
+        if (VEC) {
+          float4 u = make_float4(0.f, 0.f, 0.f, 0.f), v = u;
+          if (b0 + b < nb && k < dim) { u = *reinterpret_cast<const float4*>(y + k); v = *reinterpret_cast<const float4*>(q + k); }
+          a[b][i] = u.x; a[b][i + 1] = u.y; a[b][i + 2] = u.z; a[b][i + 3] = u.w;
+          c[b][i] = v.x; c[b][i + 1] = v.y; c[b][i + 2] = v.z; c[b][i + 3] = v.w;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const bool in = b0 + b < nb && k + j < dim;
+            a[b][i + j] = in ? y[k + j] : 0.f; c[b][i + j] = in ? q[k + j] : 0.f;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < UB; ++b) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) s = __builtin_fmaf(a[b][4 * g + i], c[b][4 * g + i], s);
+      }
+    }
+  }
+  for (int k = chain; k < dim; ++k) s = __builtin_fmaf(y[k], q[k], s);
+  return s;
+}
 // Columns k .. k+3 of a row, zeros from column n on (VEC: n is a multiple of 4).
 template <bool VEC> __device__ __forceinline__ float4 sp_row_cols(const float* __restrict__ row, int k, int n) {
   if (VEC) {
@@ -513,33 +550,44 @@ __device__ __forceinline__ void split_eval() {
   }
 
   // ---- epilogue
-  // What is pending is settled 16 pairs of the wave at a time: every lane with something left offers its next one, the first
-  // 16 are taken.  (Each lane by itself, a row's loads four or eight blocks at a time and its chain as multiply-adds, was several
-  // times a load's latency at the end of every workgroup: 20,000 edges, 1,000 candidates of 400 floats 222 -> 206 us, gather
-  // included; 900 edges, 3,000 candidates 54 -> 43.)
-  constexpr int UB = NK <= 6 || NK > 16 ? NK : (NK + 1) / 2;   // as many blocks as the registers hold
-  const int items = npend % SP_FULL;
+  // What is pending.  Up to 128 floats every lane settles its own, a chain of multiply-adds.  Wider rows 16 pairs of the wave at a
+  // time: every lane with something left offers its next one, the first 16 are taken; each lane by itself, a row's loads eight
+  // blocks at a time, was several times a load's latency at the end of every workgroup: 20,000 edges, 1,000 candidates of 400
+  // floats 222 -> 206 us, gather included; 900 edges, 3,000 candidates 54 -> 43.  (Up to 128 floats a row is two loads' latencies
+  // either way and most lanes have their own endpoint to settle, four times 16: candidates of 100 floats by degree 88 -> 95.)
   int ln = lane;
   asm volatile("" : "+v"(ln));                            // lane coordinates formed afresh: kept across the tiles they would spill
   const int gl = ln >> 4, il = ln & 15, xe = x0 + (ln & 31);
-  for (int item = nown ? -1 : 0; const unsigned long long left = __builtin_amdgcn_ballot_w64(item < items);) {
-    const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(left >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)left, 0));
-    const bool take = item < items && slot < 16;
-    int id = own;
-    if (item >= 0 && item < items) {
-      const int e = pend[256 * item];
-      id = e < 0 ? cand[~e] : e;
-    }
-    // lane `slot` learns who holds pair `slot`; pairs beyond the last are the first again
-    const int who = __builtin_amdgcn_ds_permute(4 * (take ? slot : 63), ln);
-    const int from = __shfl(who, il < __popcll(left) ? il : 0);
-    const float* yrow = a.table + (size_t)__shfl(id, from) * a.dim;
-    const float* qrow = a.qrows + (q_base + x0 + (from & 31)) * dk;
-    const float s = __shfl(a.dim % 4 == 0 ? sp_exact_pairs<true, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk))
-                                          : sp_exact_pairs<false, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk)), 16 * ((slot & 15) >> 2) + (slot & 15));
-    if (take) {
+  const int items = npend % SP_FULL;
+  if constexpr (NK <= 8) {
+    const float* qrow = a.qrows + (q_base + min(xe, n_x - 1)) * dk;
+    for (int item = nown ? -1 : 0; item < items; ++item) {
+      const int e = item < 0 ? own : pend[256 * item], id = e < 0 ? cand[~e] : e;
+      const float* yrow = a.table + (size_t)id * a.dim;
+      const float s = a.dim % 4 == 0 ? sp_exact_score<true, 4>(qrow, yrow, a.dim, sp_chain(dk)) : sp_exact_score<false, 2>(qrow, yrow, a.dim, sp_chain(dk));
       if (s > posx) cnt += item < 0 ? nown : pend[256 * (SP_PEND + item)];
-      ++item;
+    }
+  } else {
+    constexpr int UB = NK > 16 ? NK : (NK + 1) / 2;        // as many blocks as the registers hold
+    for (int item = nown ? -1 : 0; const unsigned long long left = __builtin_amdgcn_ballot_w64(item < items);) {
+      const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(left >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)left, 0));
+      const bool take = item < items && slot < 16;
+      int id = own;
+      if (item >= 0 && item < items) {
+        const int e = pend[256 * item];
+        id = e < 0 ? cand[~e] : e;
+      }
+      // lane `slot` learns who holds pair `slot`; pairs beyond the last are the first again
+      const int who = __builtin_amdgcn_ds_permute(4 * (take ? slot : 63), ln);
+      const int from = __shfl(who, il < __popcll(left) ? il : 0);
+      const float* yrow = a.table + (size_t)__shfl(id, from) * a.dim;
+      const float* qrow = a.qrows + (q_base + x0 + (from & 31)) * dk;
+      const float s = __shfl(a.dim % 4 == 0 ? sp_exact_pairs<true, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk))
+                                            : sp_exact_pairs<false, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk)), 16 * ((slot & 15) >> 2) + (slot & 15));
+      if (take) {
+        if (s > posx) cnt += item < 0 ? nown : pend[256 * (SP_PEND + item)];
+        ++item;
+      }
     }
   }
   cnt += __shfl_xor(cnt, 32);
