@@ -289,8 +289,9 @@ k_sort_scatter(const uint32_t* __restrict__ keys_in, const int32_t* __restrict__
 
 // The whole sort of a small batch (at most MAR_SORT_ONE rows) in one workgroup: wave w owns 64 `rounds` consecutive elements,
 // element `idx` = round r, lane l of it, in registers; between two passes keys and values change places through LDS.
-// Bound by the latency of its own chain (16 waves on one CU; 2 to 3 passes of ballots and counters), which is what the launches
-// it replaces (two a pass) cost on the GPU, and 2.5 us of host time each: 200 edges 74 -> 63 us a step, 1,000 edges 78 -> 72.
+// Bound by the latency of its own chain (16 waves on one CU; 2 to 3 passes of ballots and counters): 11,000 rows, two passes 27 us
+// against 20 in four launches, but beside the gather and the passes, and the host, which bounds such a step, issues one launch for
+// two a pass: 200 edges 74 -> 63 us a step, 1,000 edges 80 -> 72 to 78.
 template <int ROUNDS>
 __global__ void __launch_bounds__(1024)
 k_sort_one(OccArgs a, int n, int sy2, int passes, int bits, uint32_t* __restrict__ ids_sorted, int32_t* __restrict__ perm, int32_t* __restrict__ scalars) {
