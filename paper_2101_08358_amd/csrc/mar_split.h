@@ -28,7 +28,7 @@ constexpr int sp_pitch(int nk) { return 16 * sp_units(nk); }
 // 20-23, 24-27, then the other lanes of the first 32 -- and transpose reads of 8 bytes in groups of 32.  With the pitch alone
 // rows y % 4 start 4 or 12 units apart (mod 16) where units % 16 is 4 or 12, 8 apart where it is 8, together where it is 0;
 // the upper bits make up for what is missing, so that four consecutive rows lie in four different groups of 4 units.
-// Score product: lane 16 g + i reads unit u + g of row i, u = 0 mod 4.  Transpose reads: lanes 16 g + i read 32 bytes at an even
+// Score product: lane 16 g + i reads unit u + g of row i, u = 0 mod 4 (32 x 32 blocks: lane 32 h + m unit u + h of row m, u even).  Transpose reads: lanes 16 g + i read 32 bytes at an even
 // unit of rows 4 g .. 4 g + 3.  So with L(q) the lower two bits for rows 4 q .. 4 q + 3: L(0), L(3), L(1) ^ 1, L(2) ^ 1 differ, and
 // L(0), L(1) and L(2), L(3) differ in the upper bit: 0, 2, 3, 1.
 constexpr int sp_group(int units) { return units % 16 == 0 ? 16 : (units % 16 == 8 ? 8 : 4); }   // units a swizzle permutes

@@ -26,13 +26,13 @@
 // the edge-side operands) are copied into LDS by buffer loads that write LDS directly, one tile ahead, in two
 // alternating buffers; the stationary rows' fragments are read from their own images once and stay in registers.
 //
-// All passes run on v_mfma_f32_16x16x32_f16 / bf16: with operands as random as these the chip holds its power limit by its
-// clock, and a 16 x 16 block over 32 slots takes 12 % less energy a product than a 32 x 32 block over 16 (fed from LDS, two
-// waves a SIMD, 1,735 to 1,770 against 1,550 TFLOP/s whatever the order of the products; zeros 2,200), and pads less: rows of
-// 100 take 80 instructions of 16 cycles a tile, where 32 x 32 blocks took 45 of 32.  (50,000 edges, 100 floats: passes 127 and
-// 152 us -> 122 and 138; 100,000, 400 floats: 872 and 1,033 -> 852 and 1,027, where one wave a SIMD issues such an instruction
-// every 19.6 cycles; evaluation of 100,000 edges against 1,000 candidates of 400 floats, gather included, 995 -> 955, of 10,000
-// against 14,951 of 100 floats 217 -> 212.)
+// All passes but the evaluation of narrow rows (sp_eval_32) run on v_mfma_f32_16x16x32_f16 / bf16: with operands as random as
+// these the chip holds its power limit by its clock, and a 16 x 16 block over 32 slots takes 12 % less energy a product than a 32
+// x 32 block over 16 (fed from LDS, two waves a SIMD, 1,735 to 1,770 against 1,550 TFLOP/s whatever the order of the products;
+// zeros 2,200), and pads less: rows of 100 take 80 instructions of 16 cycles a tile, where 32 x 32 blocks took 45 of 32.  (50,000
+// edges, 100 floats: passes 127 and 152 us -> 122 and 138; 100,000, 400 floats: 872 and 1,033 -> 852 and 1,027, where one wave a
+// SIMD issues such an instruction every 19.6 cycles; evaluation of 100,000 edges against 1,000 candidates of 400 floats, gather
+// included, 995 -> 955, of 10,000 against 14,951 of 100 floats 217 -> 212.)
 // Tried: a tile's weights formed between the next tile's score products, three tiles in LDS: the same cycles; counters in LDS
 // in place of the barrier: 8 % slower.
 //
@@ -48,6 +48,8 @@
 //   receives Y[4 g + j][16 cb + i].
 //   Evaluation then swaps halves between the lane groups g and g ^ 1 (v_permlane16_swap, 8 a tile), so that lane 32 h + m holds
 //   half of the tile's rows against the one edge m, whose comparisons it keeps.
+//   v_mfma_f32_32x32x16 (sp_eval_32; lane = 32 h + m): A lane holds row m, contraction slots 8 h .. 8 h + 7; B lane
+//   holds column m, the same slots; D lane holds column m, register r = row 8 (r / 4) + 4 h + r % 4.
 #include <type_traits>
 
 #include "mar_common.h"
@@ -224,8 +226,17 @@ template <typename A> __device__ __forceinline__ bool eval_tiles(const A& a, int
 }
 typedef const __attribute__((address_space(4))) FlashArgs KernelArgs;
 
+// Rows up to 96 floats, and from 105 to 112, take their scores in one 32 x 32 block over 16 columns a step, whose accumulators hold
+// a lane's one edge as they are: the comparisons, which take as long as the products there, do without the 8 exchanges that 16 x 16
+// blocks need.  Wider rows are bound by the products, which 16 x 16 x 32 forms at less energy (7 blocks: unless the last one, more
+// than half full, takes a second step).  10,000 edges, all 14,951 nodes, 16 x 16 / 32 x 32 blocks, us a call, ten in a row: 32
+// floats 153 / 140, 64: 181 / 173, 96: 216 / 209, 100: 231 / 227 (thirty in a row 216 / 222: the chip then holds its power limit),
+// 112: 246 / 230, 128: 253 / 256; a tenth of the rows small: 166 / 151, 204 / 193, 259 / 253, 264 / 260, 295 / 265, 308 / 300; 60,000
+// edges, 1,000 candidates: 78 / 76, 102 / 99, 134 / 137, 145 / 147, 159 / 153, 160 / 161.
+constexpr bool sp_eval_32(int nk, int dk) { return nk <= 6 || (nk == 7 && dk > 16 * (nk - 1) + 8); }
+
 // PASS 3: counts the negatives that score above the positive; ranks start at 1 and the parts of a stripe add their counts.
-template <int NK>
+template <int NK, bool B32>                                // B32: 32 x 32 blocks, NK steps of 16 columns, no tail
 __device__ __forceinline__ void split_eval() {
   typedef SplitGeom<NK> SG;
   constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
@@ -233,8 +244,8 @@ __device__ __forceinline__ void split_eval() {
   constexpr int NCW = (SG::NCH + 3) / 4;                   // 1 KB pieces of an image per wave
   constexpr int NS = NK / 2;                               // whole steps of 32 columns
   constexpr bool SHARES = sp_shares(NK);
-  constexpr bool TAIL = NK % 2 != 0;                       // and 16 columns more
-  extern __shared__ __attribute__((aligned(16))) char smem[];
+  constexpr bool TAIL = !B32 && NK % 2 != 0;              // and 16 columns more
+  extern __shared__ __attribute__((aligned(256))) char smem[];
 
   KernelArgs* args = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   int64_t at, at_end;
@@ -282,24 +293,26 @@ __device__ __forceinline__ void split_eval() {
   for (int q = 0; q < NCW; ++q) dma_piece(t_begin, 0, q);
   dma_fence(t_begin);
 
-  // ---- stationary fragments and their tail, as in split_pass
+  // ---- stationary fragments and their tail, as in split_pass; 32 x 32 blocks: xh[s & 1][s / 2] are columns 16 s + 8 h .. +7 of row m
   const int x0 = stripe * SP_SR + wave_s * 32, x = x0 + m;   // the wave's first row, the lane's
   const bool xv = x < n_x;
   const size_t xtile = (size_t)cs * a.ximg_tiles + stripe * (SP_SR / TY) + wave_s;
-  const int swz = 16 * sp_swizzle(UNITS, i);              // of rows i and 16 + i of a tile, in bytes
+  const int swz = 16 * sp_swizzle(UNITS, B32 ? m : i);    // of row m, or of rows i and 16 + i, of a tile, in bytes
   const v8s zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-  v8s xh[2][NS], xl[2][NS], xt[2][2];
-  const bool tail2 = TAIL && dk > 16 * (NK - 1) + 8;      // uniform
+  constexpr int NF = B32 ? (NK + 1) / 2 : NS;
+  v8s xh[2][NF], xl[2][NF], xt[2][2];
+  const bool tail2 = TAIL && NK > 7 && dk > 16 * (NK - 1) + 8;   // uniform; 7 blocks: such rows take 32 x 32 blocks
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const bool in = x0 + 16 * b + i < n_x;
-    const char* xrow = a.ximg + xtile * IMG + (16 * b + i) * PA;
+    const bool in = B32 ? xv : x0 + 16 * b + i < n_x;
+    const char* xrow = a.ximg + xtile * IMG + (B32 ? m : 16 * b + i) * PA;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
+    for (int s = 0; s < NF; ++s) {
+      const int col = (B32 ? 64 * s + 32 * b + 16 * h : 64 * s + 16 * g) ^ swz;
       xh[b][s] = xl[b][s] = zero8;
-      if (in) {
-        xh[b][s] = *reinterpret_cast<const v8s*>(xrow + ((64 * s + 16 * g) ^ swz));
-        xl[b][s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((64 * s + 16 * g) ^ swz));
+      if (in && (!B32 || 2 * s + b < NK)) {
+        xh[b][s] = *reinterpret_cast<const v8s*>(xrow + col);
+        xl[b][s] = *reinterpret_cast<const v8s*>(xrow + PLANE + col);
       }
     }
     xt[b][0] = xt[b][1] = zero8;
@@ -333,12 +346,12 @@ __device__ __forceinline__ void split_eval() {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
 #pragma unroll
-      for (int s = 0; s < NS; ++s) q[b] += sum_of_squares(xh[b][s]);
+      for (int s = 0; s < NF; ++s) q[b] += sum_of_squares(xh[b][s]);
       if (TAIL && g < (tail2 ? 2 : 1)) q[b] += sum_of_squares(xt[b][0]);
-      q[b] += __shfl_xor(q[b], 16);
+      if (!B32) q[b] += __shfl_xor(q[b], 16);
       q[b] += __shfl_xor(q[b], 32);
     }
-    n2 = g & 1 ? q[1] : q[0];
+    n2 = B32 ? q[0] + q[1] : (g & 1 ? q[1] : q[0]);
   }
   if (xv) { posx = a.pos[(size_t)c * a.S + x]; qrow = a.qrows + (q_base + x) * dk; }
   bool zero = n2 == 0.f;
@@ -381,13 +394,13 @@ __device__ __forceinline__ void split_eval() {
   };
 
   int cnt = 0;
-  auto row_of = [&](int v) { return 16 * (v >> 3) + 8 * h + (v & 7); };   // of a lane's pair v within the tile
+  auto row_of = [&](int v) { return B32 ? 8 * (v >> 2) + 4 * h + (v & 3) : 16 * (v >> 3) + 8 * h + (v & 7); };   // of a lane's pair v within the tile
 
   // Where a lane reads in a tile's buffer (as in split_pass)
   constexpr int GU = sp_group(UNITS);
-  const int fofs = i * PA + ((16 * g) ^ swz);
+  const int fofs = (B32 ? m : i) * PA + ((16 * (B32 ? h : g)) ^ swz);
   const int tfofs = i * PA + (tail2 ? (g & 2 ? PLANE : 0) + ((64 * NS + 16 * (g & 1)) ^ swz) : (g == 1 ? PLANE : 0) + ((64 * NS) ^ swz));
-  auto at = [](int base, int byte) { return (base ^ (byte % (16 * GU))) + byte / (16 * GU) * (16 * GU); };
+  auto at = [](unsigned base, int byte) { return (base ^ (byte % (16 * GU))) + byte / (16 * GU) * (16 * GU); };
   dma_land();
   __syncthreads();
   for (int t = t_begin; t < ntiles; ++t) {
@@ -399,18 +412,47 @@ __device__ __forceinline__ void split_eval() {
     const bool masked = y0 + TY > n_y;
 
     // -- scores as in split_pass; then lane groups g and g ^ 1 exchange halves, so that lane (h, m) holds its one edge's:
-    // sacc[v] = row 16 (v / 8) + 8 h + v % 8
+    // sacc[v] = row row_of(v).  32 x 32 blocks need no exchange.
     float sacc[16];
-    {
+    if constexpr (B32) {
+      v16f sc = (v16f)(0.f);
+      constexpr int PD = NK < 2 * SP_PD ? NK : 2 * SP_PD;
+      v8s fh[PD], fl[PD];
+      const unsigned fb = lds_address_b(smem) + bofs + fofs;   // smem lies at a whole group: exclusive or on addresses
+      auto read_step = [&](int s) {
+        const unsigned p = at(fb, 32 * s);
+        fh[s % PD] = lds_read16(p); fl[s % PD] = lds_read16(p + PLANE);
+      };
+#pragma unroll
+      for (int s = 0; s < PD; ++s) read_step(s);
+#pragma unroll
+      for (int s = 0; s < NK; ++s) {
+        const v8s yh = fh[s % PD], yl = fl[s % PD];
+        if (s + PD < NK) read_step(s + PD);
+        sc = mfma32h(yl, xh[s & 1][s / 2], sc); sc = mfma32h(yh, xl[s & 1][s / 2], sc); sc = mfma32h(yh, xh[s & 1][s / 2], sc);
+        if (has_next) {                                    // the next tile's pieces, as below
+#pragma unroll
+          for (int q = s * NCW / NK; q < (s + 1) * NCW / NK; ++q) dma_piece(t + 1, buf ^ 1, q);
+          if (s == NK - 1) dma_fence(t + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
+      }
+      if (masked) {                                        // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[v] = y0 + row_of(v) < n_y ? sc[v] : -__builtin_inff();
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sacc[v] = sc[v];
+    } else {
       v4f sc[2][2];
       sc[0][0] = sc[0][1] = sc[1][0] = sc[1][1] = (v4f)(0.f);
       constexpr int PD = NS < SP_PD ? NS : SP_PD;
       v8s fh[PD][2], fl[PD][2];
-      const int fb = bofs + fofs;
+      const unsigned fb = lds_address_b(smem) + bofs + fofs;
       auto read_step = [&](int s, v8s (&vh)[2], v8s (&vl)[2]) {
-        const char* p = smem + at(fb, 64 * s);
+        const unsigned p = at(fb, 64 * s);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) { vh[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA); vl[r] = *reinterpret_cast<const v8s*>(p + 16 * r * PA + PLANE); }
+        for (int r = 0; r < 2; ++r) { vh[r] = lds_read16(p + 16 * r * PA); vl[r] = lds_read16(p + 16 * r * PA + PLANE); }
       };
 #pragma unroll
       for (int s = 0; s < PD; ++s) read_step(s, fh[s], fl[s]);
@@ -429,13 +471,20 @@ __device__ __forceinline__ void split_eval() {
         __builtin_amdgcn_sched_barrier(0);                 // keeps the reads PD steps ahead of their use
       }
       if (TAIL) {
-        const char* p = smem + bofs + tfofs;
-        sp_tail_step<true>(*reinterpret_cast<const v8s*>(p), *reinterpret_cast<const v8s*>(p + 16 * PA), xt[0][0], xt[1][0], sc);
+        const unsigned p = lds_address_b(smem) + bofs + tfofs;
+        sp_tail_step<true>(lds_read16(p), lds_read16(p + 16 * PA), xt[0][0], xt[1][0], sc);
         if (tail2) {                                       // its hi fragments again (groups 2, 3 meet zeros)
-          const char* p2 = smem + bofs + i * PA + ((64 * NS + 16 * (g & 1)) ^ swz);
-          sp_tail_step<true>(*reinterpret_cast<const v8s*>(p2), *reinterpret_cast<const v8s*>(p2 + 16 * PA), xt[0][1], xt[1][1], sc);
+          const unsigned p2 = lds_address_b(smem) + bofs + i * PA + ((64 * NS + 16 * (g & 1)) ^ swz);
+          sp_tail_step<true>(lds_read16(p2), lds_read16(p2 + 16 * PA), xt[0][1], xt[1][1], sc);
         }
       }
+      if (masked) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (y0 + 16 * (k >> 2) + 4 * g + (k & 3) >= n_y) sc[k >> 2][0][k & 3] = sc[k >> 2][1][k & 3] = -__builtin_inff();
+        }
+      }
+      asm volatile("" : "+v"(sc[0][0]), "+v"(sc[0][1]), "+v"(sc[1][0]), "+v"(sc[1][1]));   // exchanged where they lie, without moves
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(sc[k >> 2][0][k & 3]), __float_as_uint(sc[k >> 2][1][k & 3]), false, false);
@@ -451,12 +500,6 @@ __device__ __forceinline__ void split_eval() {
     const float k0 = __builtin_ldexpf(1.f, max(-140, min(126, -(int)(ex + e0))));
     const float k1 = __builtin_ldexpf(1.f, max(-140, min(126, -(int)(ex + e1))));
     bool settle = __any(ybad || xbad);                     // uniform over the wave: the tile is settled as a whole
-    if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (y0 + row_of(v) >= n_y) sacc[v] = -__builtin_inff();
-      }
-    }
     int ct = 0;
     if (!settle) {
       float near0 = __builtin_inff(), near1 = near0;
@@ -474,6 +517,13 @@ __device__ __forceinline__ void split_eval() {
         // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
         // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 90 us, 1,200 to 3,100 with
         // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
+        // lane i: id and norm of the tile's row i % TY, on their way while the comparisons are made again (unless most tiles of
+        // this wave are settled as a whole)
+        int id_t = 0;
+        float nrm = 0.f;
+        auto look = [&] { id_t = cand[min(y0 + lane % TY, n_y - 1)]; nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4)); };
+        const bool early = !__any(npend >= SP_FULL);
+        if (early) look();
         unsigned close = 0u, same = 0u;                  // bit v: pair v is close / is with the own endpoint
         float p = posx;
         asm volatile("" : "+v"(p));                      // the comparisons are made again, one after the other: kept, their lane
@@ -497,7 +547,7 @@ __device__ __forceinline__ void split_eval() {
           pend[256 * (SP_PEND + npend++)] = 1;
         }
         if (!settle && many) {
-          const int id_t = cand[min(y0 + lane % TY, n_y - 1)];   // lane i: the tile's row i % TY
+          if (!early) look();
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             same |= __shfl(id_t, row_of(v)) == own ? 1u << v : 0u;
@@ -505,7 +555,6 @@ __device__ __forceinline__ void split_eval() {
           }
           same &= close;
           if (__any((close & ~same) != 0u)) {
-            const float nrm = buf_load1(normsrc, (2 + lane % TY) * 4, t * (SP_NORMS * 4));
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
               const float dif = __builtin_fmaf(sacc[v], v < 8 ? k0 : k1, -p), nv = __shfl(nrm, row_of(v));
@@ -940,9 +989,14 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
 template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
-  if constexpr (PASS == 3) split_eval<NK>();
+  if constexpr (PASS == 3) split_eval<NK, sp_eval_32(NK, 16 * NK - 8)>();
   else split_pass<NK, PASS, F16>(a);
 }
+
+// The form of pass 3 that the fullest rows of an instantiation take, where it is not that of the others.
+template <int NK>
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, 3))
+k_split_eval_full(FlashArgs a) { split_eval<NK, true>(); }
 
 // Adds parts 1.. of pass 2's split stripes to the gradient rows that part 0 wrote, in the parts' order.  One group of
 // 32 lanes per row.
@@ -991,6 +1045,12 @@ hipError_t mar_split_prepare(int dk) {
 template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st) {
   constexpr size_t lds = SplitGeom<NK>::LDS_BYTES;
   static_assert(SplitGeom<NK>::LDS_BYTES3 <= 160 * 1024, "two images in LDS");
+  if constexpr (sp_eval_32(NK, 16 * NK) && !sp_eval_32(NK, 16 * NK - 8)) {
+    if (pass == 3 && sp_eval_32(NK, a.dk)) {
+      hipLaunchKernelGGL((k_split_eval_full<NK>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
+      return hipGetLastError();
+    }
+  }
   if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
   else if (pass == 1) {
     if (f16) hipLaunchKernelGGL((k_split<NK, 1, true>), grid, dim3(256), lds, st, a);

@@ -4,6 +4,7 @@
 #include "mar_flash.h"
 #include "mar_split.h"
 
+typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef short v4s __attribute__((ext_vector_type(4)));
@@ -12,6 +13,9 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef __bf16 v2b __attribute__((ext_vector_type(2)));
 
+__device__ __forceinline__ v16f mfma32h(v8s a, v8s b, v16f c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
+}
 template <bool F16> __device__ __forceinline__ v4f mfma16h(v8s a, v8s b, v4f c) {
   if (F16) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, b), c, 0, 0, 0);
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
@@ -40,6 +44,9 @@ template <bool F16> __device__ __forceinline__ void split8(const float (&v)[8], 
 
 __device__ __forceinline__ unsigned lds_address_b(const char* p) {
   return (unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p;
+}
+__device__ __forceinline__ v8s lds_read16(unsigned address) {
+  return *(__attribute__((address_space(3))) const v8s*)address;
 }
 __device__ __forceinline__ v4s lds_read_tr(const char* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)p);

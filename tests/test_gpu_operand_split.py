@@ -269,6 +269,12 @@ def test_chunks_evaluated_together_rank_as_each_alone(dim, C, S, N):
     one.close()
 
 
+@pytest.mark.parametrize("dim", (1, 16, 17, 20, 21, 25, 32, 33, 49, 52, 53, 56, 57, 64, 65, 81, 84, 85, 88, 89, 96, 97, 100, 101, 108))
+def test_narrow_rows_by_the_columns_of_their_last_step(dim):
+    """Rows up to 112 floats: at most 4 columns of the last step share one instruction, 5 to 8 two, more take three."""
+    test_chunks_evaluated_together_rank_as_each_alone(dim, 2, 1100, 1000)
+
+
 @pytest.mark.parametrize("dim", (8, 24, 25, 56, 57, 104, 105, 120, 121, 184, 248, 392, 393))
 def test_step_where_the_last_columns_fill_half_a_block_or_a_little_more(dim):
     """Up to 8 columns of the last block share their instructions (hi and lo parts side by side), from 9 on they do not."""
