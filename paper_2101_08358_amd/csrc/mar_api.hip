@@ -192,9 +192,7 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   d->sort_items = ((d->n_pos_max + 1023) / 1024) << d->sort_bits <= 32768 ? 4 : 16;
   // score pairs x row width per step: above ~2e9 the contraction passes are long enough to hide the index build
   d->index_after_gather = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 2.0e9;
-  // A small batch's order is one workgroup's work: one launch for two a pass, which the host cannot issue as fast as the step
-  // runs.  Above 256 floats the kernels take longer than the host, and 11,000 rows in one workgroup 4 % longer than they do.
-  d->sort_one = d->dk <= 256 ? MAR_SORT_ONE : MAR_SORT_ONE / 2;
+  d->sort_one = mar_sort_one_limit(d->dk, false);
   // The smallest ones are ordered on the caller's stream: the fork and the join are half of the host's time (200 edges, 50
   // negatives, 100 floats: a step 63 us forked, 48 on one stream; 1,000 edges, 100 negatives 72 and 76).
   d->one_stream = d->n_pos_max <= MAR_SORT_ONE / 4 && !d->index_after_gather;
@@ -587,6 +585,7 @@ extern "C" int mar_pipe_create(const mar_config* cfg, float* host_node_emb, floa
     // the slot's context: the compact table stands in for the node table (no fill; its accumulators are never used)
     const int rc2 = mar_init_tables(cfg, ps.sg.compact, ps.sg.compact, rel_emb, rel_state, sb, ctx_bytes, 0, hip_stream, &ps.ctx);
     if (rc2) { mar_pipe_destroy(p); return rc2; }
+    ps.ctx->dm.sort_one = mar_sort_one_limit(d.dk, true);
     hipEvent_t* evs[3] = {&ps.ev_in, &ps.ev_step, &ps.ev_out};
     for (int k = 0; k < 3 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(evs[k], hipEventDisableTiming);
   }

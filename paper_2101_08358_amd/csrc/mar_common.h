@@ -100,6 +100,12 @@ void mar_set_error(const char* fmt, ...);
 // Radix sort of the gradient rows by unified id: the widest digit.
 #define MAR_SORT_MAX_BITS 9
 #define MAR_SORT_ONE (16 * 1024)  // most elements k_sort_one can hold
+// Most gradient rows that one workgroup sorts by itself.  A small batch's order is one launch then in place of two a pass, which
+// the host cannot issue as fast as a step runs (1,000 edges of 50 floats, 11,000 rows: 80 -> 72 to 78 us).  Half as many where the
+// sort's own time counts (11,000 rows 27 us, in four launches 20): above 256 floats, where the kernels take longer than the host,
+// and in the pipeline, where it stands alone ahead of the staging (us a batch, one workgroup / launches: 4,000 rows of 100 floats
+// 94 / 101, 8,000 125 / 129, 9,300 171 / 167, 11,000 177 / 171, 15,600 176 / 163).
+static inline int32_t mar_sort_one_limit(int dk, bool alone) { return alone || dk > 256 ? MAR_SORT_ONE / 2 : MAR_SORT_ONE; }
 #define MAR_RANK_TILE 1024        // positions per workgroup of the rank kernels
 
 // Rank metrics: ranks per partial record, records a scratch area holds, bytes per record.

@@ -108,7 +108,8 @@ __device__ __forceinline__ int32_t occ_unified_id(const OccArgs& a, int64_t k) {
 }
 
 // Blocks of the index kernels stay at 256 threads: they run beside the contraction kernels on a second stream and have
-// to fit into the wave slots and registers those leave free on a CU.
+// to fit into the wave slots and registers those leave free on a CU.  (k_sort_one, 1,024 threads and 96 KB of LDS, is launched for
+// small batches only, ahead of the gather, while CUs are free.)
 
 // Block-wide exclusive scan of one value per thread (BT threads); returns the exclusive
 // prefix and the block total through `total`.
@@ -141,7 +142,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
 // of negative occurrence roles*n + (gr - roles*n) / sy2; its sort key is the unified id of the occurrence's
 // table row.  A least-significant-digit radix sort with digits of `bits` bits puts the gradient rows in key order;
 // every pass is stable, so equal keys stay in gradient-row order.
-// Small batches: k_sort_one.  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements) + k_sort_scatter (each tile derives its digits'
+// Small batches: k_sort_one (mar_sort_one_limit).  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements) + k_sort_scatter (each tile derives its digits'
 // global offsets from the counts of all tiles and scatters its elements).  Counts are kept digit by digit, the tiles'
 // counts of a digit side by side, so that the thread that owns a digit reads them 16 bytes at a time.
 // Small batches take small tiles (few elements per thread, many workgroups: their time is latency), large ones tiles of
@@ -291,7 +292,7 @@ k_sort_scatter(const uint32_t* __restrict__ keys_in, const int32_t* __restrict__
 // element `idx` = round r, lane l of it, in registers; between two passes keys and values change places through LDS.
 // Bound by the latency of its own chain (16 waves on one CU; 2 to 3 passes of ballots and counters): 11,000 rows, two passes 27 us
 // against 20 in four launches, but beside the gather and the passes, and the host, which bounds such a step, issues one launch for
-// two a pass: 200 edges 74 -> 63 us a step, 1,000 edges 80 -> 72 to 78.
+// two a pass (200 edges 74 -> 63 us a step).
 template <int ROUNDS>
 __global__ void __launch_bounds__(1024)
 k_sort_one(OccArgs a, int n, int sy2, int passes, int bits, uint32_t* __restrict__ ids_sorted, int32_t* __restrict__ perm, int32_t* __restrict__ scalars) {
