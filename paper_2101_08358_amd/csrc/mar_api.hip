@@ -79,7 +79,7 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
 // 37 x 611, 777: 207 / 204, 100 x 1,000, 1,000: 925 / 933, 1 x 900, 3,000: 43 / 48.  With two or three workgroups a CU the other
 // ones fill the round: shares of 100 floats took 2 to 8 % longer at all sizes.
 bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps) {
-  if (!mar_split_shares(d.dk) || units * ntiles < 8 * MAR_SHARES) return false;
+  if (!mar_split_shares(d.dk) || ntiles < 3 || units * ntiles < 8 * MAR_SHARES) return false;   // fewer than 3: sp_share_border
   const long share = (units * ntiles + MAR_SHARES - 1) / MAR_SHARES, pieces = 1 + (share - 2 + ntiles) / ntiles;
   return (double)(share + 8 * pieces) < 0.9 * (double)((units * sy + 255) / 256 * (tps + 8));
 }

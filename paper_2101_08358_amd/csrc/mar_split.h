@@ -43,6 +43,12 @@ constexpr int sp_nk(int dk) { return dk <= 32 ? 2 : (dk <= 64 ? 4 : (dk <= 96 ? 
 constexpr int sp_plane(int nk) { return SP_TY * sp_pitch(nk); }
 constexpr int sp_image(int nk) { return (2 * sp_plane(nk) + 1023) / 1024 * 1024; }
 constexpr int SP_NORMS = 2 + SP_TY;
+// Where share q of all units' tiles begins: shares of `share` tiles, the first `rest` one more.  A border one tile off a unit's is
+// moved there, for a piece of one tile costs its stationary rows all the same (units of at least three tiles: mar_plan_shares).
+MAR_HD inline int64_t sp_share_border(int64_t share, int32_t rest, int ntiles, int q) {
+  const int64_t b = q * share + (q < rest ? q : rest), in = b % ntiles;
+  return in == 1 ? b - 1 : (in == ntiles - 1 ? b + 1 : b);
+}
 static inline int sp_tiles(int rows) { return (rows + SP_TY - 1) / SP_TY; }
 
 // Where the gather writes an image set: [chunk-sides][tiles][IMG].

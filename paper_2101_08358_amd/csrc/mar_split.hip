@@ -204,7 +204,6 @@ constexpr int sp_waves(int nk, int pass) { return pass == 3 ? (nk <= 8 ? 3 : (nk
 // ---------------------------------------------------------------------------- evaluation -----
 // What a workgroup takes of all units' tiles, counted one unit after the other: a unit's part, or (rows above 256 floats) an
 // equal share wherever it ends, for counts need no merging.  As in flash_unit an XCD's workgroups take neighbouring shares.
-// A border one tile off a unit's is moved there: a piece of one tile costs its stationary rows all the same.
 constexpr bool sp_shares(int nk) { return nk > 16; }
 template <typename A> __device__ __forceinline__ bool eval_tiles(const A& a, int64_t& at, int64_t& at_end) {
   const int ntiles = (a.N + SP_TY - 1) / SP_TY;
@@ -216,12 +215,8 @@ template <typename A> __device__ __forceinline__ bool eval_tiles(const A& a, int
     return true;
   }
   const int p = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  auto border = [&](int q) {
-    const int64_t b = q * a.share + min(q, a.share_rest), in = b % ntiles;
-    return in == 1 ? b - 1 : (in == ntiles - 1 ? b + 1 : b);
-  };
-  at = border(p);
-  at_end = border(p + 1);
+  at = sp_share_border(a.share, a.share_rest, ntiles, p);
+  at_end = sp_share_border(a.share, a.share_rest, ntiles, p + 1);
   return at < at_end;
 }
 typedef const __attribute__((address_space(4))) FlashArgs KernelArgs;

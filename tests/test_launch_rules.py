@@ -28,3 +28,31 @@ def test_one_workgroup_sorts_less_where_nothing_runs_beside_it(tmp_path):
     where its own time counts, half as many rows."""
     out = _run(tmp_path, """for (int alone = 0; alone < 2; ++alone) for (int dk : {16, 256, 260, 400}) printf("%d ", mar_sort_one_limit(dk, alone));""")
     assert [int(x) for x in out] == [16384, 16384, 8192, 8192] + [8192] * 4
+
+
+def test_shares_of_an_evaluation_cover_every_tile_once(tmp_path):
+    """Units of one or two tiles are never cut into shares (their borders could not be moved to a unit's); in all others the
+    shares follow one another from the first tile to the last, and no piece of a unit is a single tile."""
+    out = _run(tmp_path, """
+  MarDims d = {};
+  d.dk = 400; d.bilinear = 1;
+  long taken = 0, bad = 0;
+  for (int ntiles = 1; ntiles <= 70; ++ntiles) for (long units : {30L, 257L, 684L, 2048L, 9001L}) for (int sy : {1, 2, 4, 64}) {
+    const int tps = (ntiles + sy - 1) / sy;
+    if (!mar_plan_shares(d, units, ntiles, sy, tps)) continue;
+    ++taken;
+    const int64_t tiles = (int64_t)units * ntiles, share = tiles / MAR_SHARES;
+    const int32_t rest = (int32_t)(tiles % MAR_SHARES);
+    if (ntiles < 3 || sp_share_border(share, rest, ntiles, 0) != 0 || sp_share_border(share, rest, ntiles, MAR_SHARES) != tiles) ++bad;
+    for (int p = 0; p < MAR_SHARES; ++p) {
+      const int64_t at = sp_share_border(share, rest, ntiles, p), end = sp_share_border(share, rest, ntiles, p + 1);
+      if (end < at) ++bad;
+      for (int64_t t = at; t < end;) {
+        const int64_t unit_end = (t / ntiles + 1) * ntiles, piece = (unit_end < end ? unit_end : end) - t;
+        if (piece < 2) ++bad;
+        t += piece;
+      }
+    }
+  }
+  printf("%ld %ld", taken, bad);""")
+    assert int(out[0]) > 100 and out[1] == "0", out
