@@ -142,12 +142,12 @@ __device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, cons
 
 // Up to 16 pairs settled: lanes (G, i) pass the rows of pair i; the lanes with G = i / 4 receive its score.  The loads of UB
 // blocks of 16 columns are in flight at once (blocks the rows do not have read the last one again), then comes their chain.
+// Rows above 128 floats, all of whose columns lie in the chain's blocks.
 template <bool VEC, int UB>
-__device__ __forceinline__ float sp_exact_pairs(const float* __restrict__ q, const float* __restrict__ y, int G, int i, int dim, int dk, int chain) {
-  const int end = min(chain, dim), whole = end / 16, part = 16 * whole + 4 * G;   // uniform: whole
-  const float4 ap = sp_row_cols<VEC>(y, part, end), bp = sp_row_cols<true>(q, part, min(chain, dk));
-  const bool rest = chain + G < dim;                       // at most four columns behind the chain: one step more
-  const float ar = rest ? y[chain + G] : 0.f, br = rest ? q[chain + G] : 0.f;
+__device__ __forceinline__ float sp_exact_pairs(const float* __restrict__ q, const float* __restrict__ y, int G, int i, int dim, int dk) {
+  static_assert(sp_chain(129) >= 400, "no column behind the chain");
+  const int whole = dim / 16, part = 16 * whole + 4 * G;   // uniform: whole
+  const float4 ap = sp_row_cols<VEC>(y, part, dim), bp = sp_row_cols<true>(q, part, dk);
   v4f acc = (v4f)(0.f);
 #pragma unroll 1
   for (int n0 = 0; n0 < whole; n0 += UB) {
@@ -168,7 +168,6 @@ __device__ __forceinline__ float sp_exact_pairs(const float* __restrict__ q, con
   }
   acc = mfma16(ap.x, bp.x, acc); acc = mfma16(ap.y, bp.y, acc);
   acc = mfma16(ap.z, bp.z, acc); acc = mfma16(ap.w, bp.w, acc);
-  acc = mfma16(ar, br, acc);
   return i & 2 ? (i & 1 ? acc[3] : acc[2]) : (i & 1 ? acc[1] : acc[0]);
 }
 
@@ -626,8 +625,8 @@ __device__ __forceinline__ void split_eval() {
       const int from = __shfl(who, il < __popcll(left) ? il : 0);
       const float* yrow = a.table + (size_t)__shfl(id, from) * a.dim;
       const float* qrow = a.qrows + (q_base + x0 + (from & 31)) * dk;
-      const float s = __shfl(a.dim % 4 == 0 ? sp_exact_pairs<true, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk))
-                                            : sp_exact_pairs<false, UB>(qrow, yrow, gl, il, a.dim, dk, sp_chain(dk)), 16 * ((slot & 15) >> 2) + (slot & 15));
+      const float s = __shfl(a.dim % 4 == 0 ? sp_exact_pairs<true, UB>(qrow, yrow, gl, il, a.dim, dk)
+                                            : sp_exact_pairs<false, UB>(qrow, yrow, gl, il, a.dim, dk), 16 * ((slot & 15) >> 2) + (slot & 15));
       if (take) {
         if (s > posx) cnt += item < 0 ? nown : pend[256 * (SP_PEND + item)];
         ++item;
