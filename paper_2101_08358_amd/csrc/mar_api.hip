@@ -231,7 +231,6 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.qq = (float*)take(bl ? 0 : 2 * B * 4);
   l.kk = (float*)take(bl ? 0 : 2 * CN * 4);
   l.pos = (float*)take(B * 4);
-  l.lse = (float*)take(2 * B * 4);
   l.gQ = (float*)take((size_t)d.sy1 * 2 * B * dk * 4);
   l.ml = (float*)take((size_t)d.sy1 * 2 * B * 2 * 4);
   l.gQx = (float*)take((size_t)(d.rem1.k - 1) * (size_t)d.rem1.rows * dk * 4);

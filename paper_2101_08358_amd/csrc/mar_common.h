@@ -27,7 +27,6 @@ struct MarLayout {
   float*    qq;           // [2][batch] squared norms of Q rows (TransE)
   float*    kk;           // [2][chunks*N] squared norms of Km rows (TransE)
   float*    pos;          // [batch] positive scores
-  float*    lse;          // [2][batch] log-sum-exp per edge and side, where no caller asks for it
   float*    gQ;           // [sy1][2][batch][dk] per-part unnormalised gradient w.r.t. Q rows; bilinear models' evaluation: fp32 operands
   float*    ml;           // [sy1][2][batch][2] per-part softmax reference (bilinear models: in log2 units) and sum
   float*    gQx;          // [rem1.k - 1][rem1.rows][dk] parts 1.. of the stripes that are split to fill the last round

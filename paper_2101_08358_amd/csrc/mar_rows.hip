@@ -449,7 +449,8 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
     const float lse_u = merge_parts(ml, row_u, part_rows, sy1, a.ml_log2, facu);
     const float lse_w = merge_parts(ml, row_w, part_rows, sy1, a.ml_log2, facw);
     const float pe = pos[e];
-    if (l == 0) { lse_dst[e] = lse_u; lse_src[e] = lse_w; }
+    if (l == 0 && lse_dst) lse_dst[e] = lse_u;             // where the caller asks for them
+    if (l == 0 && lse_src) lse_src[e] = lse_w;
     le = -2.f * pe + lse_u + lse_w;
     const float* gu0 = gQ + row_u * dk;
     const float* gw0 = gQ + row_w * dk;
@@ -1188,8 +1189,7 @@ hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug
   RowArgs a = row_args(c, b);
   const int GL = mar_lane_group(a.dk), gpb = 256 / GL;
   const dim3 grid((b.n + gpb - 1) / gpb);
-  float* lse_dst = dbg && dbg->lse_dst ? dbg->lse_dst : L.lse + (size_t)MAR_SIDE_DST * c->dm.B;
-  float* lse_src = dbg && dbg->lse_src ? dbg->lse_src : L.lse + (size_t)MAR_SIDE_SRC * c->dm.B;
+  float *lse_dst = dbg ? dbg->lse_dst : nullptr, *lse_src = dbg ? dbg->lse_src : nullptr;
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
   if (GL == 16) launch_chain_model<16, 1>(a, L, lse_dst, lse_src, grid, st);
   else if (GL == 32) launch_chain_model<32, 1>(a, L, lse_dst, lse_src, grid, st);
