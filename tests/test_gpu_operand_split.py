@@ -242,9 +242,13 @@ def test_small_and_large_evaluations_rank_alike(model, dim):
             assert np.array_equal(a, b)
 
 
+# Above the line of dense operands, and cut into equal shares (tests/test_launch_rules.py asks the library): dim, chunks, edges and
+# candidates of each.
+SHARED = ((400, 19, 1000, 997), (393, 33, 500, 340), (260, 34, 500, 338))
+
+
 @pytest.mark.parametrize("dim,C,S,N", ((4, 3, 1100, 1000), (24, 3, 1100, 1000), (28, 3, 1100, 1000), (104, 3, 1100, 1000), (105, 3, 1100, 1000),
-                                       (112, 3, 1100, 1000), (124, 3, 1100, 1000), (392, 3, 1100, 1000),
-                                       (400, 19, 1000, 997), (393, 33, 500, 333), (260, 34, 500, 338)))
+                                       (112, 3, 1100, 1000), (124, 3, 1100, 1000), (392, 3, 1100, 1000)) + SHARED)
 def test_chunks_evaluated_together_rank_as_each_alone(dim, C, S, N):
     """A chunk alone takes the fp32 instructions, all together the operand images: rows whose last columns fill a whole, half or
     quarter step, and (the last three) tiles cut into shares that end inside a stripe, with stripes of the last chunk empty."""

@@ -55,12 +55,18 @@ def test_the_step_is_the_same_without_debug_outputs(dim, R):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("dim,B,C,N", ((8, 1, 1, 1), (8, 320, 1, 64), (12, 2730, 1, 1), (12, 2731, 1, 1), (8, 5461, 1, 1), (8, 5462, 1, 1), (260, 2500, 1, 64), (8, 900, 9, 100), (8, 1600, 16, 90)))
+# dim, edges, chunks, negatives of each -> gradient rows: three an edge, and for each of the 2 C N negatives one per part of pass 2
+# (tests/test_launch_rules.py asks the library)
+ROWS = {(8, 1, 1, 1): 5, (8, 320, 1, 64): 1600, (8, 1500, 1, 16): 4756, (12, 2720, 1, 2): 8192, (12, 2721, 1, 2): 8195, (8, 900, 9, 100): 9900,
+        (8, 1600, 16, 90): 16320, (8, 5456, 1, 1): 16384, (8, 5457, 1, 1): 16387, (260, 2400, 1, 62): 8192, (260, 2401, 1, 62): 8195}
+
+
+@pytest.mark.parametrize("dim,B,C,N", ROWS)
 def test_orders_that_one_workgroup_sorts(dim, B, C, N):
-    """Three rows an edge and two or more a negative: batches up to and just beyond what one workgroup holds in 8 and in 16
-    rounds (8,192 and 16,384 rows), hot ids among them, one pass and three.  (Wide rows with 64 negatives: with one, the loss is
+    """Batches up to, exactly at and just beyond what one workgroup holds in 8 and in 16 rounds (8,192 and 16,384 rows; above 256
+    floats 8,192 at most), hot ids among them, one, two and three passes.  (Wide rows with 62 negatives: with one, the loss is
     sum(-2 f + f' + f'') of scores that nearly cancel, and its rounding, 2^-24 sum(2 |f| + |f'| + |f''|), was 1.3e-4 of it.)"""
-    for V in (200, 300_000):
+    for V in (200, 100_000, 300_000):
         rng = np.random.default_rng(V + B)
         hot = lambda m: np.where(rng.random(m) < 0.4, rng.integers(0, 3, m), rng.integers(0, V, m)).astype(np.int32)
         ids = (hot(B), rng.integers(0, 2, B).astype(np.int32), hot(B), hot(C * N).reshape(C, N), hot(C * N).reshape(C, N))

@@ -56,3 +56,41 @@ def test_shares_of_an_evaluation_cover_every_tile_once(tmp_path):
   }
   printf("%ld %ld", taken, bad);""")
     assert int(out[0]) > 100 and out[1] == "0", out
+
+
+def test_sizes_of_the_row_order_tests(tmp_path):
+    """The batches that are meant to fill one workgroup's sort exactly, or to be just beyond it, do."""
+    from test_gpu_row_order import ROWS
+    sizes = list(ROWS)
+    out = _run(tmp_path, """
+  const int c[][4] = {%s};
+  for (auto& k : c) {
+    MarDims d = {};
+    d.bilinear = 1; d.dim = k[0]; d.dk = (k[0] + 3) & ~3; d.B = k[1]; d.C = k[2]; d.S = k[1] / k[2]; d.N = k[3];
+    const int sr = mar_stripe_rows(d, 2);
+    int32_t sy, tps;
+    mar_plan_parts(d, 2, 2L * d.C * ((d.N + sr - 1) / sr), d.S, &sy, &tps);
+    printf("%%ld ", 3L * d.B + 2L * d.C * d.N * sy);
+  }""" % ", ".join("{%d, %d, %d, %d}" % k for k in sizes))
+    assert [int(x) for x in out] == [ROWS[k] for k in sizes]
+
+
+def test_sizes_of_the_shared_evaluation_tests(tmp_path):
+    """The evaluations that are meant to be cut into shares are: not on dense operands as a whole, each chunk alone is."""
+    from test_gpu_operand_split import SHARED
+    out = _run(tmp_path, """
+  const int c[][4] = {%s};
+  for (auto& k : c) {
+    MarDims d = {};
+    d.bilinear = 1; d.dim = k[0]; d.dk = (k[0] + 3) & ~3; d.C = k[1]; d.S = k[2]; d.N = k[3]; d.B = d.C * d.S;
+    MarBatch b = {};
+    b.n = d.B - d.S / 2; b.nchunks = (b.n + d.S - 1) / d.S;
+    const int sr = mar_stripe_rows(d, 3), ntiles = (d.N + 31) / 32;
+    const long units = 2L * b.nchunks * ((d.S + sr - 1) / sr);
+    int32_t sy, tps;
+    mar_plan_parts(d, 3, units, d.N, &sy, &tps);
+    MarBatch one = {};
+    one.n = d.S;
+    printf("%%d%%d%%d ", (int)mar_eval_dense(d, b), (int)mar_plan_shares(d, units, ntiles, sy, tps), (int)mar_eval_dense(d, one));
+  }""" % ", ".join("{%d, %d, %d, %d}" % k for k in SHARED))
+    assert out == ["011"] * len(SHARED), out
