@@ -261,9 +261,11 @@ int mar_pipe_drain(mar_pipe* pipe, void* hip_stream);
 int mar_pipe_destroy(mar_pipe* pipe);
 
 /*
- * Per-phase device timing of mar_train_batch with HIP events on the stream each phase runs on
- * (phases 0 and 4 run on the context's second stream beside phases 1-3, so the six times
- * overlap and do not add up to the step time).
+ * Per-phase device timing of mar_train_batch with HIP events on the stream each phase runs on.
+ * Phase 0 runs on the context's second stream beside phases 1-3, except in the smallest batches
+ * (up to 4,096 gradient rows), whose phases all run on the caller's stream; phase 4 runs on the
+ * second stream in large batches (batch_size x negs_per_chunk x dim from 2e9 on) only.  Phases
+ * that run beside others overlap them: the six times then do not add up to the step time.
  * Phases: 0 index build (unique set, occurrence order), 1 row gather and operand build,
  * 2 score + softmax + gradient w.r.t. the edge side (MFMA), 3 gradient w.r.t. the
  * negatives (MFMA), 4 chain rule, 5 per-row reduce + Adagrad scatter.

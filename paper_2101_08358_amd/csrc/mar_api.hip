@@ -42,7 +42,7 @@ static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_spli
 // candidates of 400 floats: 1 part 48 us, 4 parts 60).  16-bit instructions: as many parts as the least estimated time
 // of the busiest CU asks for -- a workgroup costs its tiles plus about three tiles' time for its operand fragments, its
 // first tile and its rows (pass 3, whose tiles are half the work and whose close comparisons are settled at the end:
-// eight); a CU that holds one of two possible workgroups runs it at about 0.6 of its full rate.
+// eight, from the time when every lane settled its own); a CU that holds one of two possible workgroups runs it at about 0.6 of its full rate.
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps) {
   const int ty = mar_tile_rows(d, pass);
   const int ntiles = (n_y + ty - 1) / ty;
@@ -75,9 +75,9 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
 
 // Evaluation of rows above 256 floats (a workgroup a CU): equal shares, one a CU, in place of parts.  A share has no last,
 // partly filled round, but its workgroup begins anew at every unit it enters; where that does not save a tenth by the estimate
-// above, parts of units stay.  400 floats, gather included, us (parts / shares): 20 x 1,000 edges, 1,000 candidates 206 / 188,
-// 37 x 611, 777: 207 / 204, 100 x 1,000, 1,000: 925 / 933, 1 x 900, 3,000: 43 / 48.  With two or three workgroups a CU the other
-// ones fill the round: shares of 100 floats took 2 to 8 % longer at all sizes.
+// above, parts of units stay.  400 floats, gather included, us (parts / shares): 20 x 1,000 edges, 1,000 candidates 201 / 186,
+// 37 x 611, 777: 207 / 205, 100 x 1,000, 1,000: 912 / 934, 60 x 1,000, 1,000: 531 / 546, 10 x 700, 1,000: 75 / 82, 1 x 900, 3,000:
+// 39 / 45.  With two or three workgroups a CU the other ones fill the round: shares of 100 floats took 2 to 8 % longer at all sizes.
 bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps) {
   if (!mar_split_shares(d.dk) || ntiles < 3 || units * ntiles < 8 * MAR_SHARES) return false;   // fewer than 3: sp_share_border
   const long share = (units * ntiles + MAR_SHARES - 1) / MAR_SHARES, pieces = 1 + (share - 2 + ntiles) / ntiles;
@@ -89,7 +89,8 @@ bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps) 
 // whole round are split into k parts.  TransE (pass 1 only): as many as fill one round.  Bilinear models: the
 // remainder often exceeds half a round (units of 128 rows), so the parts may take several rounds of their own; every
 // part beyond the first costs a write and a read of the units' output rows.  Estimated in microseconds from the rates
-// these passes reach (about 1000 TFLOP/s of 16-bit work over all slots, 4.5 TB/s of memory traffic).
+// these passes reach (about 1,000 TFLOP/s of 16-bit work over all slots -- 100 floats 970 and 880, 400 floats 1,150 and 1,020 --
+// and 4.5 TB/s of memory traffic).
 static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, int sr, MarRem* r) {
   r->whole_units = (int32_t)units; r->k = 1; r->tps = 0; r->rows = 0;
   const long slots = 256L * wgs_per_cu(d, pass);
@@ -118,11 +119,12 @@ static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, in
 // Evaluation of the bilinear models: on images and 16-bit products (mar_split.hip), or on dense fp32 operands and fp32
 // matrix instructions (k_flash, PASS 4), whose gather writes no images and whose two kernels are a third of the code to be
 // fetched.  What the images cost goes with a chunk's rows, S edges and N candidates, what the faster products save with
-// its S N pairs, so the line is one of S N / (S + N); and where all pairs together are few, latency decides.  Measured over
-// 16 to 400 floats, 1 to 100 chunks of 100 to 1,000 edges, 50 to 1,000 candidates (fp32 / images, us, 100 and 400 floats):
-// 20 x 400 edges, 100 candidates 18 / 24 and 41 / 54; 100 x 100, 300: 32 / 37 and 111 / 113; 100 x 300, 600: 90 / 82 and
-// 361 / 341; 100 x 1,000, 1,000: 374 / 235 and 1,577 / 1,021.  With 200 and 2 million no point is more than 3% slower than
-// fp32 throughout, and the mean is 2.4% off the better of the two at every point.  Ranks are the same bits either way.
+// its S N pairs, so the line is one of S N / (S + N); and where all pairs together are few, latency decides.  fp32 / images,
+// us, 50, 100 and 400 floats: 20 x 400 edges, 100 candidates 12 / 19, 16 / 23, 43 / 40; 100 x 100, 300: 23 / 30, 32 / 36,
+// 112 / 111; 20 x 400, 400 (on the line) 20 / 23, 32 / 29, 93 / 66; 100 x 300, 600 (on the line) 54 / 53, 89 / 78, 363 / 309;
+// 20 x 500, 500: 23 / 25, 34 / 31, 106 / 76; 4 x 1,000, 600: 13 / 19, 18 / 21, 47 / 36; 100 x 1,000, 1,000: 216 / 144, 373 / 231,
+// 1,603 / 912.  The line was drawn with slower image kernels over all widths at once (mean then 2.4 % off the better of the two):
+// above 128 floats it now lies too far towards fp32, below 100 too near for few chunks.  Ranks are the same bits either way.
 bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
   const double S = b.n < d.S ? b.n : d.S, N = d.N;
   return d.bilinear && (S * N <= 200.0 * (S + N) || (double)b.n * N <= 2.0e6);

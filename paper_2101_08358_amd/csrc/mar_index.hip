@@ -142,9 +142,10 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
 // of negative occurrence roles*n + (gr - roles*n) / sy2; its sort key is the unified id of the occurrence's
 // table row.  A least-significant-digit radix sort with digits of `bits` bits puts the gradient rows in key order;
 // every pass is stable, so equal keys stay in gradient-row order.
-// Small batches: k_sort_one (mar_sort_one_limit).  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements) + k_sort_scatter (each tile derives its digits'
-// global offsets from the counts of all tiles and scatters its elements).  Counts are kept digit by digit, the tiles'
-// counts of a digit side by side, so that the thread that owns a digit reads them 16 bytes at a time.
+// Small batches: k_sort_one (mar_sort_one_limit).  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements)
+// + k_sort_scatter (each tile derives its digits' global offsets from the counts of all tiles and scatters its elements).
+// Counts are kept digit by digit, the tiles' counts of a digit side by side, so that the thread that owns a digit reads
+// them 16 bytes at a time.
 // Small batches take small tiles (few elements per thread, many workgroups: their time is latency), large ones tiles of
 // 4096 (see sort_items).  Every tile reads bins x tiles counts, so that the reads grow with the square of the batch:
 // 250,000 gradient rows and 27-bit ids (three passes of 9 bits) 62 tiles x 31,744 counts a pass, 8 MB of cached reads;

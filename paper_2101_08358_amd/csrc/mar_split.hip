@@ -6,9 +6,9 @@
 //     a_hi b_hi + a_lo b_hi + a_hi b_lo
 // with 16-bit matrix instructions (fp32 accumulation), which run at 16 times the rate of the fp32 ones.
 // hi + lo holds 23-24 significant bits of every value down to 2^-17 of its block's largest (below that an absolute
-// 2^-40 of the largest), the dropped product is below 2^-22 of its pair, and the sums see 3 roundings per 16 terms
-// where the fp32 instruction sees 4, so a pass is as accurate as its fp32 form: against 64 bits a dot product of 128
-// (1024) normal values is off by 1.5e-7 (3.5e-7) of its norm, with v_mfma_f32_16x16x4_f32 by 1.9e-7 (5.6e-7).
+// 2^-40 of the largest), the dropped product is below 2^-22 of its pair, and the sums are rounded less often than the fp32
+// instruction's, so a pass is as accurate as its fp32 form: against 64 bits a dot product of 128 (1,024) normal values is
+// off by 1.5e-7 (3.6e-7) of its norm on 16x16x32 and on 32x32x16, with v_mfma_f32_16x16x4_f32 by 2.0e-7 (5.7e-7).
 // SPLIT_BF16 (F16 = false): v = hi + lo in bf16 without exponents, the same three products; errors of 2^-16 .. 2^-17
 // per product.
 //
@@ -32,7 +32,7 @@
 // zeros 2,200), and pads less: rows of 100 take 80 instructions of 16 cycles a tile, where 32 x 32 blocks took 45 of 32.  (50,000
 // edges, 100 floats: passes 127 and 152 us -> 122 and 138; 100,000, 400 floats: 872 and 1,033 -> 852 and 1,027, where one wave a
 // SIMD issues such an instruction every 19.6 cycles; evaluation of 100,000 edges against 1,000 candidates of 400 floats, gather
-// included, 995 -> 955, of 10,000 against 14,951 of 100 floats 217 -> 212.)
+// included, 995 -> 955.)
 // Tried: a tile's weights formed between the next tile's score products, three tiles in LDS: the same cycles; counters in LDS
 // in place of the barrier: 8 % slower.
 //
@@ -113,8 +113,8 @@ template <bool VEC> __device__ __forceinline__ float4 sp_row_cols(const float* _
 // in step j of a 16-column block lane group G holds column 4 G + j of it.  acc[y half][x half]: register r is candidate
 // 4 G + r against edge i.  16 matrix instructions and four 16-byte loads a lane per 16 columns.  All 14,951 nodes as
 // candidates, 100 floats, half of the rows equal: 1,050 us; one comparison after the other 16,700, as fp32 contraction
-// throughout 1,110, no two rows equal 229.  (20,000 edges, 1,000 candidates of 400 floats, half equal: 1,075 us, 25,000
-// and 355; 233 without.  One wave per SIMD hides little of the loads.)
+// throughout 1,110, no two rows equal 230.  (20,000 edges, 1,000 candidates of 400 floats, half equal: 1,000 us, 25,000
+// and 355; 186 without.  One wave per SIMD hides little of the loads.)
 template <bool VEC>
 __device__ __forceinline__ void sp_exact_tile(const float* __restrict__ q0, const float* __restrict__ q1, const float* __restrict__ y0,
                                               const float* __restrict__ y1, int G, int dim, int dk, int chain, v4f (&acc)[2][2]) {
@@ -509,8 +509,8 @@ __device__ __forceinline__ void split_eval() {
       if (__any(xv && (near0 < tol0 || near1 < tol1))) {
         // An edge's close candidates are mostly its own endpoint, as often as the candidates hold it: it is counted, and
         // compared once at the end, like up to SP_PEND others.  Where there are more the tile is settled as a whole.
-        // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 90 us, 1,200 to 3,100 with
-        // every copy compared, 91 as fp32 contraction, 59 for uniform candidates.)
+        // (20,000 edges, 1,000 candidates of 100 floats drawn by degree from a power law: 78 to 85 us, 1,200 to 3,100 with
+        // every copy compared, 91 as fp32 contraction, 58 for uniform candidates.)
         // lane i: id and norm of the tile's row i % TY, on their way while the comparisons are made again (unless most tiles of
         // this wave are settled as a whole)
         int id_t = 0;
