@@ -33,7 +33,7 @@ static int hip_fail(hipError_t e, const char* what) {
 // ------------------------------------------------------------------ configuration -----
 #define MAR_FLASH_TARGET_WGS 640
 
-static int wgs_per_cu(const MarDims& d, int pass) { return d.bilinear ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass); }
+static int wgs_per_cu(const MarDims& d, int pass) { return mar_on_images(d) ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass); }
 
 // Small batches give too few (chunk-side, stripe) units to fill 256 CUs: several workgroups share a unit, each
 // streaming a slice of the other matrix.  fp32 instructions: until a pass has at least MAR_FLASH_TARGET_WGS workgroups;
@@ -47,7 +47,7 @@ void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy
   const int ty = mar_tile_rows(d, pass);
   const int ntiles = (n_y + ty - 1) / ty;
   long want = 1;
-  if (!d.bilinear) {
+  if (!mar_on_images(d)) {
     want = (MAR_FLASH_TARGET_WGS + units - 1) / units;
     if (want > MAR_MAX_PARTS) want = MAR_MAX_PARTS;
     if (want > ntiles) want = ntiles;
@@ -94,13 +94,13 @@ bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps) 
 static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, int sr, MarRem* r) {
   r->whole_units = (int32_t)units; r->k = 1; r->tps = 0; r->rows = 0;
   const long slots = 256L * wgs_per_cu(d, pass);
-  if (sy != 1 || units < slots || units % slots == 0 || (!d.bilinear && pass == 2)) return;
+  if (sy != 1 || units < slots || units % slots == 0 || (!mar_on_images(d) && pass == 2)) return;
   const int ty = mar_tile_rows(d, pass);
   const long ntiles = (n_y + ty - 1) / ty, rem = units % slots;
   long k = slots / rem;
   if (k > MAR_MAX_PARTS) k = MAR_MAX_PARTS;
   if (k > ntiles) k = ntiles;
-  if (d.bilinear) {
+  if (mar_on_images(d)) {
     const double unit_us = 12.0 * sr * (double)n_y * d.dk * (double)slots / 1.0e9;
     double best = 1e30;
     k = 1;
@@ -129,6 +129,13 @@ bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
   const double S = b.n < d.S ? b.n : d.S, N = d.N;
   return d.bilinear && (S * N <= 200.0 * (S + N) || (double)b.n * N <= 2.0e6);
 }
+
+// Training passes of TransE: on images and 16-bit products (k_split_dist), or on dense fp32 operands with stored weights (k_flash,
+// k_flash_bwd), whose code is a quarter as long and whose gather writes no images.  What the faster products save goes with
+// pairs x columns.  A step, us, dense / images: 1e9 (10,000 edges, 1,000 negatives, 100 floats, outputs) 222 / 177, 4e9 (the same,
+// 400 floats) 776 / 578; 5e8 178 / 139 (84 floats), 296 / 265 (320); 2 to 2.5e8: 143 / 133 (61), 145 / 136 (191), 150 / 152 (304);
+// 1e8: 126 / 113 (144), 95 / 113 (58), 114 / 126 (148); 200 to 2,000 edges mostly 5 to 20 % slower on images.
+bool mar_dist_images(const MarDims& d) { return !d.bilinear && (double)d.B * d.N * d.dk >= 2.0e8; }
 
 static int check_config(const mar_config* cfg, MarDims* d) {
   if (!cfg) return fail(MAR_EINVAL, "config is NULL");
@@ -174,6 +181,7 @@ static int check_config(const mar_config* cfg, MarDims* d) {
     if (d->split_bf16 && ((rows + 31) / 32) * (int64_t)mar_split_image_bytes(d->dk) >= ((int64_t)1 << 31))
       return fail(MAR_ERANGE, "chunk too large for the split-precision operand images (2^31 bytes per chunk and side)");
   }
+  d->dist_img = mar_dist_images(*d);
   const int sr1 = mar_stripe_rows(*d, 1), sr2 = mar_stripe_rows(*d, 2);
   const long units1 = 2L * d->C * ((d->S + sr1 - 1) / sr1), units2 = 2L * d->C * ((d->N + sr2 - 1) / sr2);
   mar_plan_parts(*d, 1, units1, d->N, &d->sy1, &d->tps1);
@@ -226,10 +234,11 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.ids_sorted = (uint32_t*)take(n_pos * 4);
   l.rank_sorted = (int32_t*)take(n_pos * 4);
   l.owners = (int32_t*)take(blocks * 4);
-  // TransE: dense operands and stored weights; bilinear models: operand images, no weights (pass 2 computes the scores again)
-  const bool bl = d.bilinear != 0;
+  // On images no weights are stored (pass 2 computes the scores again).  TransE keeps its fp32 edge-side operands and the norms
+  // there too; its evaluation, on dense operands, then has the negatives' rows in the gradient rows' place.
+  const bool bl = d.bilinear != 0, img = mar_on_images(d);
   l.Q = (float*)take(bl ? 0 : 2 * B * dk * 4);
-  l.Km = (float*)take(bl ? 0 : 2 * CN * dk * 4);
+  l.Km = (float*)take(img ? 0 : 2 * CN * dk * 4);
   l.qq = (float*)take(bl ? 0 : 2 * B * 4);
   l.kk = (float*)take(bl ? 0 : 2 * CN * 4);
   l.pos = (float*)take(B * 4);
@@ -237,17 +246,18 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.ml = (float*)take((size_t)d.sy1 * 2 * B * 2 * 4);
   l.gQx = (float*)take((size_t)(d.rem1.k - 1) * (size_t)d.rem1.rows * dk * 4);
   l.mlx = (float*)take((size_t)(d.rem1.k - 1) * (size_t)d.rem1.rows * 2 * 4);
-  l.T = (float*)take(bl ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)((d.N + 127) & ~127) * 4);
-  l.R = (float*)take(bl ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)(((d.N + 127) & ~127) / 16) * 4);
+  l.T = (float*)take(img ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)((d.N + 127) & ~127) * 4);
+  l.R = (float*)take(img ? 0 : 2 * (size_t)d.C * (size_t)((d.S + 63) & ~63) * (size_t)(((d.N + 127) & ~127) / 16) * 4);
   const size_t ktiles = 2 * (size_t)d.C * (size_t)((d.N + 31) / 32), qtiles = 2 * (size_t)d.C * (size_t)((d.S + 31) / 32);
-  l.Kimg = (char*)take(bl ? ktiles * mar_split_image_bytes(d.dk) : 0);
-  l.Qimg = (char*)take(bl ? qtiles * mar_split_image_bytes(d.dk) : 0);
+  l.Kimg = (char*)take(img ? ktiles * mar_split_image_bytes(d.dk) : 0);
+  l.Qimg = (char*)take(img ? qtiles * mar_split_image_bytes(d.dk) : 0);
   l.Gx = (float*)take((size_t)(d.rem2.k - 1) * (size_t)d.rem2.rows * dk * 4);
   const size_t eval_floats = bl ? ktiles * (2 + 2 + MAR_SPLIT_TILE_ROWS) + qtiles * 2 : 0;
   l.G = (float*)take((n_pos * dk > eval_floats ? n_pos * dk : eval_floats) * 4);
+  if (d.dist_img) l.Km = l.G;
   // evaluation's norms, and with bf16 images (which have no exponents) its exponents, lie in the gradient rows, for which it
   // has no other use
-  const bool own_exp = bl && !d.split_bf16;
+  const bool own_exp = img && !d.split_bf16;
   l.Kexp = own_exp ? (float*)take(ktiles * 8) : l.G;
   l.Qexp = own_exp ? (float*)take(qtiles * 8) : l.G + ktiles * 2;
   l.Knorm = l.G + ktiles * 2 + qtiles * 2;
@@ -282,7 +292,7 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
   if (workspace_bytes < need) return fail(MAR_ENOMEM, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
   {
     hipError_t e_ = mar_flash_prepare(d.dk);
-    if (e_ == hipSuccess && d.bilinear) e_ = mar_split_prepare(d.dk);
+    if (e_ == hipSuccess && mar_on_images(d)) e_ = mar_split_prepare(d.dk);
     if (e_ != hipSuccess) return hip_fail(e_, "kernel attributes");
   }
   mar_ctx* c = new (std::nothrow) mar_ctx();

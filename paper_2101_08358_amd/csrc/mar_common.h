@@ -23,7 +23,7 @@ struct MarLayout {
   int32_t*  rank_sorted;  // position -> rank among the unique rows (where a caller asks for ranks)
   int32_t*  owners;       // [reduce blocks] workgroups of the reduce in which a segment begins that continues into later ones
   float*    Q;            // TransE: [2][batch][dk] edge-side operands (side-major)
-  float*    Km;           // TransE: [2][chunks][N][dk] gathered negative rows
+  float*    Km;           // TransE on dense operands: [2][chunks][N][dk] gathered negative rows
   float*    qq;           // [2][batch] squared norms of Q rows (TransE)
   float*    kk;           // [2][chunks*N] squared norms of Km rows (TransE)
   float*    pos;          // [batch] positive scores
@@ -68,6 +68,7 @@ struct MarDims {
   int64_t u_max;                   // min(num_nodes + num_rels, n_occ_max)
   int32_t sort_passes, sort_bits, sort_items;  // radix sort of the gradient rows by unified id: passes, bits per pass, elements per thread
   int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
+  int32_t dist_img;                // TransE whose training passes are those of mar_split.hip too (mar_dist_images)
   int32_t reduce_small;            // the reduce gives a lane group MAR_REDUCE_SMALL positions instead of one per lane
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t sort_one;                // most gradient rows that one workgroup sorts by itself
@@ -180,8 +181,10 @@ int mar_split_wgs_per_cu(int dk, int pass);
 #define MAR_SPLIT_STRIPE_ROWS 128
 #define MAR_SPLIT_TILE_ROWS 32
 #define MAR_SHARES 256            // workgroups of an evaluation cut into equal shares: one a CU
-static inline int mar_stripe_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }
-static inline int mar_tile_rows(const MarDims& d, int pass) { return d.bilinear ? MAR_SPLIT_TILE_ROWS : mar_flash_tile_rows(d.dk, pass); }
+static inline bool mar_on_images(const MarDims& d) { return d.bilinear || d.dist_img; }
+bool mar_dist_images(const MarDims& d);            // TransE's training: images and 16-bit products, or dense fp32 operands
+static inline int mar_stripe_rows(const MarDims& d, int pass) { return mar_on_images(d) ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }
+static inline int mar_tile_rows(const MarDims& d, int pass) { return mar_on_images(d) ? MAR_SPLIT_TILE_ROWS : mar_flash_tile_rows(d.dk, pass); }
 // How many workgroups share one of `units` units of a pass, and the streamed tiles each takes (n_y streamed rows).
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps);
 bool mar_split_shares(int dk);                     // an evaluation on images can cut all units' tiles into equal shares

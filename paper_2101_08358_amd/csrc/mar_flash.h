@@ -38,8 +38,9 @@ struct FlashArgs {
   // split-precision passes: bf16 hi/lo images of the streamed matrix, [2*nchunks][yimg_tiles][image bytes]
   const char* yimg; int32_t yimg_tiles;
   const char* ximg; int32_t ximg_tiles;   // the same of the stationary matrix
-  // evaluation of the bilinear models: fp32 edge-side operands [2][B][dk], the node table and the ids, from which
-  // close comparisons are settled
+  int32_t dist;        // TransE's training passes on images
+  // evaluation of the bilinear models and TransE's training on images: fp32 edge-side operands [2][B][dk], the node table and the
+  // ids, from which close comparisons / near pairs are settled
   const float *qrows, *ynorm, *table; const int32_t *neg_dst, *neg_src, *src, *dst; int32_t dim;
   // evaluation on images, where share > 0: workgroup p takes `share` tiles of the units' tiles, one more if p < share_rest
   int64_t share; int32_t share_rest;

@@ -897,11 +897,14 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   const bool dense = pass == 3 && mar_eval_dense(c->dm, b);
   MarDims d = c->dm;
   if (dense) d.bilinear = 0;                               // geometry and parts of the fp32 kernel
+  if (pass == 3) d.dist_img = 0;
+  const bool img = mar_on_images(d);
   FlashArgs a = {};
   a.X = pass == 2 ? L.Km : L.Q;  a.Y = pass == 2 ? L.Q : L.Km;   // stationary / streamed matrix
   if (dense) { a.X = L.gQ; a.Y = L.G; }
+  a.dist = d.dist_img;
   a.xx = L.qq; a.yy = L.kk;
-  a.ml = L.ml; a.pos = L.pos; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
+  a.ml = L.ml; a.pos = L.pos; a.ml_log2 = img ? MAR_LN2 : 1.f;
   a.T = L.T; a.R = L.R; a.tpitch = (d.N + 127) & ~127; a.trows = (d.S + 63) & ~63;
   a.out = pass == 1 ? L.gQ : L.G;
   a.rank_dst = rank_dst; a.rank_src = rank_src;
@@ -910,7 +913,7 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   const bool f16 = !d.split_bf16 || pass == 3;             // evaluation always runs at fp32 precision
   a.yimg = pass == 2 ? L.Qimg : L.Kimg; a.yexp = pass == 2 ? L.Qexp : L.Kexp; a.yimg_tiles = ((pass == 2 ? d.S : d.N) + 31) / 32;
   a.ximg = pass == 2 ? L.Kimg : L.Qimg; a.xexp = pass == 2 ? L.Kexp : L.Qexp; a.ximg_tiles = ((pass == 2 ? d.N : d.S) + 31) / 32;
-  a.qrows = L.gQ; a.ynorm = L.Knorm; a.table = c->node_emb; a.neg_dst = b.neg_dst; a.neg_src = b.neg_src; a.src = b.src; a.dst = b.dst; a.dim = d.dim;
+  a.qrows = a.dist ? L.Q : L.gQ; a.ynorm = L.Knorm; a.table = c->node_emb; a.neg_dst = b.neg_dst; a.neg_src = b.neg_src; a.src = b.src; a.dst = b.dst; a.dim = d.dim;
   a.sr = mar_stripe_rows(d, pass);
   a.nstripes = (max_nx + a.sr - 1) / a.sr;
   a.units = a.whole_units = 2 * b.nchunks * a.nstripes;
@@ -935,7 +938,7 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
     a.share = tiles / MAR_SHARES; a.share_rest = (int32_t)(tiles % MAR_SHARES);
   }
   if (dense) pass = 4;
-  if (d.bilinear) return mar_split_launch(a, pass, f16, grid, st);
+  if (img) return mar_split_launch(a, pass, f16, grid, st);
   const int nk = d.dk / 4;
 #ifndef MAR_BWD_TAIL_MFMA
 #define MAR_BWD_TAIL_MFMA 0
@@ -954,7 +957,7 @@ hipError_t mar_launch_flash_merge(const mar_ctx* c, const MarBatch& b, hipStream
   const MarDims& d = c->dm;
   if (d.rem1.k <= 1 || b.n != d.B) return hipSuccess;
   FlashArgs a = {};
-  a.ml = c->L.ml; a.mlx = c->L.mlx; a.out = c->L.gQ; a.outx = c->L.gQx; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
+  a.ml = c->L.ml; a.mlx = c->L.mlx; a.out = c->L.gQ; a.outx = c->L.gQx; a.ml_log2 = mar_on_images(d) ? MAR_LN2 : 1.f;
   a.n = b.n; a.B = d.B; a.S = d.S; a.dk = d.dk; a.sr = mar_stripe_rows(d, 1); a.nstripes = (d.S + a.sr - 1) / a.sr;
   a.whole_units = d.rem1.whole_units; a.rem_k = d.rem1.k; a.rem_rows = d.rem1.rows;
   hipLaunchKernelGGL(k_flash_merge, dim3((unsigned)((d.rem1.rows + 7) / 8)), dim3(256), 0, st, a);

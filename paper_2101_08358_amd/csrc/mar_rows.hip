@@ -1102,7 +1102,7 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
   a.src = b.src; a.rel = b.rel; a.dst = b.dst; a.neg_src = b.neg_src; a.neg_dst = b.neg_dst;
   a.n = b.n; a.cn = b.cn; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.dim = d.dim; a.dk = d.dk; a.model = c->cfg.model;
   a.n_occ = b.n_occ; a.num_nodes = (int32_t)d.num_nodes;
-  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = d.bilinear ? MAR_LN2 : 1.f;
+  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = mar_on_images(d) ? MAR_LN2 : 1.f;
   return a;
 }
 
@@ -1137,7 +1137,10 @@ hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, 
 #define PREP(GLV, NVV) do { switch (a.model) { \
     case MAR_MODEL_DISTMULT: PREP3(GLV, NVV, MAR_MODEL_DISTMULT); break; \
     case MAR_MODEL_COMPLEX: PREP3(GLV, NVV, MAR_MODEL_COMPLEX); break; \
-    case MAR_MODEL_TRANSE: launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); break; \
+    case MAR_MODEL_TRANSE: \
+      if (c->dm.dist_img && !rank_dst) launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+      else launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+      break; \
     default: PREP3(GLV, NVV, MAR_MODEL_DOT); break; } } while (0)
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
   if (GL == 16) PREP(16, 1); else if (GL == 32) PREP(32, 1); else if (a.dk <= 256) PREP(64, 1); else PREP(64, 2);

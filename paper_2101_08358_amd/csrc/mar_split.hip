@@ -639,13 +639,38 @@ __device__ __forceinline__ void split_eval() {
 }
 
 // ------------------------------------------------------------------------ the training passes -----
+// Squared norm of a row of TransE as the passes use it; none above 1e37, so that a squared distance stays finite (a NaN makes every
+// pair of the row a near one, whose distance is formed from the rows).
+__device__ __forceinline__ float dist_norm(float n2) { return n2 < 1e37f ? n2 : __builtin_nanf(""); }
+
 // PASS 1: scores, online softmax and gQ = P K for 128 edges of one chunk-side (32 per wave) against the chunk's
 // negatives.
 // PASS 2: gK = P^T Q for 128 negatives of one chunk-side against the chunk's edges, with the scores computed again and
 // P = exp(score - lse) from the finished log-sum-exp.  Writing the weights out and reading them back costs 8 bytes of
 // memory traffic per pair, computing a score again 6 d 16-bit flops: at this matrix rate the second is cheaper.
-template <int NK, int PASS, bool F16>
+// TransE: a row in fp32 (EDGE: of the edge-side operands; else a negative's, of the node table).  Formed from
+// arguments that the compiler cannot see through: what the addresses take would otherwise be kept across the tiles.
+template <bool EDGE> struct DistRow {
+  const float* row;
+  int left;
+  __device__ __forceinline__ DistRow(int cs, int x, int g) {
+    KernelArgs* args = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args), "+v"(g));
+    KernelArgs& a = *args;
+    const int side = cs & 1, c = cs >> 1;
+    if (EDGE) row = a.qrows + ((size_t)side * a.B + (size_t)c * a.S + x) * a.dk;
+    else row = a.table + (size_t)((side == MAR_SIDE_DST ? a.neg_dst : a.neg_src) + (size_t)c * a.N)[x] * a.dim;
+    left = EDGE ? a.dk : a.dim;
+  }
+  __device__ __forceinline__ float4 cols(int k) const { return sp_row_cols<EDGE>(row, k, left); }
+};
+
+// DIST (TransE): the score is -|x - y|, its square expanded as |x|^2 + |y|^2 - 2 x.y with the norms in fp32.  Pairs for which the
+// expansion cancels (below 2^-8 of the norms' sum) are formed from the differences of their columns (rare in training; a wave
+// without one skips the loop).  The second product then runs with W = softmax weight / distance, less x times the sum of the W.
+template <int NK, int PASS, bool F16, bool DIST>
 __device__ __forceinline__ void split_pass(const FlashArgs& a) {
+  static_assert(F16 || !DIST, "TransE's operands are f16 pairs");
   typedef SplitGeom<NK> SG;
   constexpr int UNITS = SG::UNITS, PA = SG::PA, PLANE = SG::PLANE, IMG = SG::IMG;
   constexpr int TY = SP_TY;
@@ -656,6 +681,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   constexpr float LOG2E = 1.44269504088896341f;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][2][TY] log-sum-exp of the tile's edges, log2 units
+  float* const nrm_all = aux_all + 4 * TY;                // DIST: [2][TY] squared norms of the tile's rows
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, i = lane & 15;
@@ -712,7 +738,13 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
 #pragma unroll
   for (int cb = 0; cb < NO; ++cb) oacc[cb][0] = oacc[cb][1] = (v4f)(0.f);
   float mref[2] = {-3.0e38f, -3.0e38f}, lrun[2] = {0.f, 0.f};   // softmax reference (log2 units; F16: an integer) and sum
-
+  // DIST: squared norms (of rows there are not: 1, so that no pair with them is near), sums of the weights, where rows lie
+  const size_t k_base = (size_t)side * a.C * a.N + (size_t)c * a.N;   // first row of the chunk's negatives
+  float xn[2] = {1.f, 1.f}, wsum[2] = {0.f, 0.f};
+  if (DIST) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) if (xv[b]) xn[b] = dist_norm(PASS == 1 ? a.xx[q_base + x0 + 16 * b + i] : a.yy[k_base + x0 + 16 * b + i]);
+  }
   const int ntiles_all = (n_y + TY - 1) / TY;
   const int t_begin = u.part * u.tps;
   const int ntiles = min(ntiles_all, t_begin + u.tps);
@@ -725,7 +757,9 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   const BufRsrc mlsrc = buf_rsrc(a.ml + q_base * 2, PASS == 2 ? (uint32_t)ne * 8 : 0u);
   const int f_row = threadIdx.x % TY;
   const size_t ml_stride = (size_t)2 * a.B;               // rows per part of pass 1's statistics
+  const BufRsrc nrmsrc = buf_rsrc(!DIST ? (const void*)ybase : (const void*)(PASS == 1 ? a.yy + k_base : a.xx + q_base), DIST ? (uint32_t)n_y * 4 : 0u);
   float2 ye_next = make_float2(0.f, 0.f), st_ml = make_float2(0.f, 0.f);
+  float st_nrm = 0.f;
   int token = 0;
   auto dma_piece = [&](int t, int buf, int q) {            // piece q of this wave of tile t into buffer `buf`
     const v4i ywords = buf_words(ybase + (size_t)t * IMG, IMG);
@@ -735,9 +769,11 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   auto dma_fence = [&](int t) {
     ye_next = buf_load2(expsrc, token, t * 8);
     if (PASS == 2) st_ml = buf_load2(mlsrc, f_row * 8 + token, t * TY * 8);
+    if (DIST) st_nrm = buf_load1(nrmsrc, f_row * 4 + token, t * TY * 4);
   };
   auto dma_land = [&](int t, int buf) {
     asm volatile("" : "+v"(ye_next.x), "+v"(ye_next.y));
+    if (DIST) nrm_all[buf * TY + f_row] = t * TY + f_row < n_y ? dist_norm(st_nrm) : 1.f;   // threads that share a row write the same value
     if (PASS == 2) {
       const int yr = t * TY + f_row;
       float mm = st_ml.x, ll = st_ml.y;
@@ -820,91 +856,239 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
         }
       }
     }
-    // -- score log2(e) = sc k, k = log2(e) 2^-(ex + ey): never 0, or a masked row's -inf would become NaN (two blocks at the
-    // largest exponent: scores below 2^-85 either way)
-    float k[2][2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      k[0][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e0)) << 23)) : LOG2E;
-      k[1][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e1)) << 23)) : LOG2E;
-    }
     const float ef[2] = {(float)e0, (float)e1};
-    if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        if (y0 + 16 * (r >> 2) + 4 * g + (r & 3) >= n_y) sc[r >> 2][0][r & 3] = sc[r >> 2][1][r & 3] = -__builtin_inff();
-      }
-    }
-    // -- weights of the lane's 2 x 8 pairs, split: w[b][4 ah + r] is row 16 ah + 4 g + r against column 16 b + i
+    // -- weights of the lane's 2 x 8 pairs: w[b][4 ah + r] is row 16 ah + 4 g + r against column 16 b + i
     float w[2][8];
-    if (PASS == 1 || F16) {
-      float tmax[2];
-      if (PASS == 1) {
+    if constexpr (DIST) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          float m[2];
+      for (int b = 0; b < 2; ++b) {
+        // squared distances; near: the expansion is left with fewer than 14 good bits (or is no number)
+        float d2[8];
+        bool near = false;
+        const auto is_near = [&](int v, float yn) { return !(d2[v] > 0.00390625f * (xn[b] + yn)); };
+        const float4 yn4[2] = {*reinterpret_cast<const float4*>(nrm_all + buf * TY + 4 * g), *reinterpret_cast<const float4*>(nrm_all + buf * TY + 16 + 4 * g)};
+        const float yn[8] = {yn4[0].x, yn4[0].y, yn4[0].z, yn4[0].w, yn4[1].x, yn4[1].y, yn4[1].z, yn4[1].w};
+        const float k2[2] = {-__builtin_ldexpf(1.f, 1 - ex[b] - e0), -__builtin_ldexpf(1.f, 1 - ex[b] - e1)};
 #pragma unroll
-          for (int h = 0; h < 2; ++h) m[h] = __builtin_fmaf(fmaxf(fmaxf(sc[h][b][0], sc[h][b][1]), fmaxf(sc[h][b][2], sc[h][b][3])), k[h][b], -ef[h]);
-          tmax[b] = fmaxf(m[0], m[1]);
+        for (int v = 0; v < 8; ++v) {
+          d2[v] = __builtin_fmaf(sc[v >> 2][b][v & 3], k2[v >> 2], xn[b] + yn[v]);
+          near |= is_near(v, yn[v]);
         }
-      } else {
-        float m[2][2];
+        unsigned none = 0u;                                // pairs at distance 0: no gradient
+        if (__builtin_expect(__any(near), 0)) {
+          unsigned left = 0u;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
-          const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 16 * h + 4 * g);
+          for (int v = 0; v < 8; ++v) left |= is_near(v, yn[v]) ? 1u << (16 * (v >> 2) + 4 * g + (v & 3)) : 0u;
+          left |= __shfl_xor(left, 16);                    // near pairs of the column: a bit for each of the tile's rows
+          left |= __shfl_xor(left, 32);
+          for (; __any(left != 0u); left &= left - 1u) {
+            // one pair of every column at a time: its four lanes each take the columns they hold fragments of
+            const int at_row = left ? __ffs((int)left) - 1 : 0;
+            const int ey = at_row < 16 ? e0 : e1;
+            const float r = __builtin_ldexpf(1.f, max(-126, min(126, ey - ex[b])));   // differences in units of the streamed row's block
+            const char* const yp = smem + bofs + at_row * PA;
+            const int ysw = 16 * sp_swizzle(UNITS, at_row);
+            float part = 0.f;
+            auto add_unit = [&](v8s ah, v8s al, int byte) {
+              asm volatile("" : "+v"(ah), "+v"(al));         // or their conversions are moved out of the loop, into registers that there are not
+              const v8h x0h = __builtin_bit_cast(v8h, ah), x0l = __builtin_bit_cast(v8h, al);
+              const v8h y0h = *reinterpret_cast<const v8h*>(yp + (byte ^ ysw)), y0l = *reinterpret_cast<const v8h*>(yp + PLANE + (byte ^ ysw));
 #pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            w[b][4 * h] = __builtin_fmaf(sc[h][b][0], k[h][b], -l4.x) - m4.x;
-            w[b][4 * h + 1] = __builtin_fmaf(sc[h][b][1], k[h][b], -l4.y) - m4.y;
-            w[b][4 * h + 2] = __builtin_fmaf(sc[h][b][2], k[h][b], -l4.z) - m4.z;
-            w[b][4 * h + 3] = __builtin_fmaf(sc[h][b][3], k[h][b], -l4.w) - m4.w;
-            m[h][b] = fmaxf(fmaxf(w[b][4 * h], w[b][4 * h + 1]), fmaxf(w[b][4 * h + 2], w[b][4 * h + 3])) - ef[h];
+              for (int j = 0; j < 8; ++j) {
+                float d = __builtin_fmaf((float)x0h[j], r, -(float)y0h[j]);
+                d = __builtin_fmaf((float)x0l[j], r, d);
+                d = __builtin_fmaf((float)y0l[j], neg1, d);
+                part = __builtin_fmaf(d, d, part);
+              }
+            };
+#pragma unroll
+            for (int s = 0; s < NS; ++s) { add_unit(xh[b][s], xl[b][s], 64 * s + 16 * g); if (s % 2) __builtin_amdgcn_sched_barrier(0); }
+            if (TAIL) {
+              // the 16 columns behind: units 0 and 1 lie with lane groups 0 and (more than 8 columns) 1; groups 0, 1 / group 2 hold the lo part
+              const v8s tl = tail2 ? xt[b][1] : __builtin_bit_cast(v8s, sp_shfl16(__builtin_bit_cast(v4i, xt[b][0]), 32 + i));
+              if (g < (tail2 ? 2 : 1)) add_unit(xt[b][0], tl, 64 * NS + 16 * g);
+            }
+            part += __shfl_xor(part, 16);
+            part = __builtin_ldexpf(part + __shfl_xor(part, 32), -2 * ey);
+            // closer than hi + lo of the two rows can tell (2^-20 of the norm): by the rows themselves, so that rows that are
+            // the same are found to be
+            const float both = xn[b] + nrm_all[buf * TY + at_row];
+            const bool same = left && !(part > 0x1p-40f * both);
+            if (__builtin_expect(__any(same), 0)) {
+              const int xr = min(x0 + 16 * b + i, n_x - 1), yr = min(y0 + at_row, n_y - 1);
+              const DistRow<true> q(u.cs, PASS == 1 ? xr : yr, g);
+              const DistRow<false> n(u.cs, PASS == 1 ? yr : xr, g);
+              float exact = 0.f;
+#pragma unroll 1
+              for (int k = 4 * g; k < dk; k += 16) {
+                const float4 qc = q.cols(k), nc = n.cols(k);
+                const float d[4] = {qc.x - nc.x, qc.y - nc.y, qc.z - nc.z, qc.w - nc.w};
+                exact += (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+              }
+              exact += __shfl_xor(exact, 16);
+              exact += __shfl_xor(exact, 32);
+              part = same ? exact : part;
+            }
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+              if (left && at_row == 16 * (v >> 2) + 4 * g + (v & 3)) {
+                d2[v] = part < 2e-38f ? 2e-38f : (part > 3e38f ? 3e38f : part);   // normal numbers; a NaN stays one
+                none |= part < 2e-38f ? 1u << v : 0u;
+              }
+            }
           }
         }
+        // log2 of the softmax weight (pass 2: of the probability) of a pair at 1 / rs, less the pieces of the reference
+        float lg[8], mm[8];
+        auto read_lse = [&]() {
+          if (PASS == 2) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) tmax[b] = fmaxf(m[0][b], m[1][b]);
-      }
-      constexpr float SLACK = F16 ? 15.f : 16.f * LOG2E;
-      if (__any(tmax[0] > mref[0] + SLACK || tmax[1] > mref[1] + SLACK)) {
+            for (int h = 0; h < 2; ++h) {
+              const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+              const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 16 * h + 4 * g);
+              lg[4 * h] = l4.x; lg[4 * h + 1] = l4.y; lg[4 * h + 2] = l4.z; lg[4 * h + 3] = l4.w;
+              mm[4 * h] = m4.x; mm[4 * h + 1] = m4.y; mm[4 * h + 2] = m4.z; mm[4 * h + 3] = m4.w;
+            }
+          }
+        };
+        auto log2w = [&](int v, float rs) {
+          const float dist = d2[v] * rs;
+          if (PASS == 2) return __builtin_fmaf(dist, -LOG2E, -lg[v]) - mm[v];
+          return masked && y0 + 16 * (v >> 2) + 4 * g + (v & 3) >= n_y ? -__builtin_inff() : -LOG2E * dist;
+        };
+        float l[2];
+        auto weigh = [&]() {                               // the weights; returns the largest
+          read_lse();
+          l[0] = l[1] = 0.f;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          float tall = fmaxf(tmax[b], __shfl_xor(tmax[b], 16));
+          for (int v = 0; v < 8; ++v) {
+            const float rs = __builtin_amdgcn_rsqf(d2[v]);
+            const float p = __builtin_amdgcn_exp2f(log2w(v, rs) - (ef[v >> 2] + mref[b]));
+            if (PASS == 1) l[v >> 2] += p;
+            w[b][v] = p * rs;
+          }
+          if (__builtin_expect(__any(none != 0u), 0)) {
+#pragma unroll
+            for (int v = 0; v < 8; ++v) w[b][v] = none >> v & 1u ? 0.f : w[b][v];
+          }
+          float most = w[b][0];
+#pragma unroll
+          for (int v = 1; v < 8; ++v) most = fmaxf(most, w[b][v]);
+          return fmaxf(most, fmaxf(l[0], l[1]) * 0x1p-64f);   // (a pair at distance 0 has only a softmax weight)
+        };
+        if (__builtin_expect(__any(weigh() > 32768.f), 0)) {
+          float tall = -3.0e38f;
+#pragma unroll
+          for (int v = 0; v < 8; ++v) {
+            const float rs = __builtin_amdgcn_rsqf(d2[v]);
+            tall = fmaxf(tall, log2w(v, rs) - ef[v >> 2] + (none >> v & 1u ? 0.f : __builtin_amdgcn_logf(rs)));
+          }
+          tall = fmaxf(tall, __shfl_xor(tall, 16));
           tall = fmaxf(tall, __shfl_xor(tall, 32));
-          const float mnew = fmaxf(mref[b], F16 ? __builtin_ceilf(tall) - 8.f : tall);
+          const float mnew = fmaxf(mref[b], __builtin_ceilf(tall) - 8.f);
           float alpha = __builtin_amdgcn_exp2f(mref[b] - mnew);
-          asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
+          asm volatile("" : "+v"(alpha));
           lrun[b] *= alpha;
+          wsum[b] *= alpha;
 #pragma unroll
           for (int cb = 0; cb < NO; ++cb) {
             if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));
             oacc[cb][b] *= alpha;
-            if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));   // wide rows: back to the accumulation registers, one block at a time
+            if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));
           }
           mref[b] = mnew;
+          (void)weigh();
         }
+        if (PASS == 1) lrun[b] += __builtin_ldexpf(l[0], e0) + __builtin_ldexpf(l[1], e1);
+        float ws[2] = {0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 8; ++v) ws[v >> 2] += w[b][v];
+        wsum[b] += __builtin_ldexpf(ws[0], e0) + __builtin_ldexpf(ws[1], e1);
       }
+    } else {
+      // -- score log2(e) = sc k, k = log2(e) 2^-(ex + ey): never 0, or a masked row's -inf would become NaN (two blocks at the
+      // largest exponent: scores below 2^-85 either way)
+      float k[2][2];
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        float l[2] = {0.f, 0.f};
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const float ref = ef[v >> 2] + mref[b];          // exact: integers (bf16: no exponents)
-          w[b][v] = __builtin_amdgcn_exp2f(PASS == 1 ? __builtin_fmaf(sc[v >> 2][b][v & 3], k[v >> 2][b], -ref) : w[b][v] - ref);
-          if (PASS == 1) l[v >> 2] += w[b][v];
-        }
-        if (PASS == 1) lrun[b] += F16 ? __builtin_ldexpf(l[0], e0) + __builtin_ldexpf(l[1], e1) : l[0] + l[1];
+        k[0][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e0)) << 23)) : LOG2E;
+        k[1][b] = F16 ? __int_as_float(0x3fb8aa3b - (max(-126, min(125, ex[b] + e1)) << 23)) : LOG2E;
       }
-    } else {                                               // pass 2, bf16: no reference needed
+      if (masked) {                                          // the chunk's last, partial tile (uniform): rows beyond it weigh nothing
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+        for (int r = 0; r < 8; ++r) {
+          if (y0 + 16 * (r >> 2) + 4 * g + (r & 3) >= n_y) sc[r >> 2][0][r & 3] = sc[r >> 2][1][r & 3] = -__builtin_inff();
+        }
+      }
+      if (PASS == 1 || F16) {
+        float tmax[2];
+        if (PASS == 1) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float m[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) m[h] = __builtin_fmaf(fmaxf(fmaxf(sc[h][b][0], sc[h][b][1]), fmaxf(sc[h][b][2], sc[h][b][3])), k[h][b], -ef[h]);
+            tmax[b] = fmaxf(m[0], m[1]);
+          }
+        } else {
+          float m[2][2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+            const float4 m4 = *reinterpret_cast<const float4*>(aux_all + (2 * buf + 1) * TY + 16 * h + 4 * g);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+              w[b][4 * h] = __builtin_fmaf(sc[h][b][0], k[h][b], -l4.x) - m4.x;
+              w[b][4 * h + 1] = __builtin_fmaf(sc[h][b][1], k[h][b], -l4.y) - m4.y;
+              w[b][4 * h + 2] = __builtin_fmaf(sc[h][b][2], k[h][b], -l4.z) - m4.z;
+              w[b][4 * h + 3] = __builtin_fmaf(sc[h][b][3], k[h][b], -l4.w) - m4.w;
+              m[h][b] = fmaxf(fmaxf(w[b][4 * h], w[b][4 * h + 1]), fmaxf(w[b][4 * h + 2], w[b][4 * h + 3])) - ef[h];
+            }
+          }
+#pragma unroll
+          for (int b = 0; b < 2; ++b) tmax[b] = fmaxf(m[0][b], m[1][b]);
+        }
+        constexpr float SLACK = F16 ? 15.f : 16.f * LOG2E;
+        if (__any(tmax[0] > mref[0] + SLACK || tmax[1] > mref[1] + SLACK)) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            float tall = fmaxf(tmax[b], __shfl_xor(tmax[b], 16));
+            tall = fmaxf(tall, __shfl_xor(tall, 32));
+            const float mnew = fmaxf(mref[b], F16 ? __builtin_ceilf(tall) - 8.f : tall);
+            float alpha = __builtin_amdgcn_exp2f(mref[b] - mnew);
+            asm volatile("" : "+v"(alpha));                  // a real branch: keeps the rescale from being executed speculatively
+            lrun[b] *= alpha;
+#pragma unroll
+            for (int cb = 0; cb < NO; ++cb) {
+              if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));
+              oacc[cb][b] *= alpha;
+              if (NK > 8) asm volatile("" : "+a"(oacc[cb][b]));   // wide rows: back to the accumulation registers, one block at a time
+            }
+            mref[b] = mnew;
+          }
+        }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-          w[b][4 * h] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][0], LOG2E, -l4.x));
-          w[b][4 * h + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][1], LOG2E, -l4.y));
-          w[b][4 * h + 2] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][2], LOG2E, -l4.z));
-          w[b][4 * h + 3] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][3], LOG2E, -l4.w));
+          float l[2] = {0.f, 0.f};
+#pragma unroll
+          for (int v = 0; v < 8; ++v) {
+            const float ref = ef[v >> 2] + mref[b];          // exact: integers (bf16: no exponents)
+            w[b][v] = __builtin_amdgcn_exp2f(PASS == 1 ? __builtin_fmaf(sc[v >> 2][b][v & 3], k[v >> 2][b], -ref) : w[b][v] - ref);
+            if (PASS == 1) l[v >> 2] += w[b][v];
+          }
+          if (PASS == 1) lrun[b] += F16 ? __builtin_ldexpf(l[0], e0) + __builtin_ldexpf(l[1], e1) : l[0] + l[1];
+        }
+      } else {                                               // pass 2, bf16: no reference needed
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float4 l4 = *reinterpret_cast<const float4*>(aux_all + 2 * buf * TY + 16 * h + 4 * g);
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            w[b][4 * h] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][0], LOG2E, -l4.x));
+            w[b][4 * h + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][1], LOG2E, -l4.y));
+            w[b][4 * h + 2] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][2], LOG2E, -l4.z));
+            w[b][4 * h + 3] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][b][3], LOG2E, -l4.w));
+          }
         }
       }
     }
@@ -967,7 +1151,21 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       orow = a.out + (a.roles * (size_t)a.n + ((side == MAR_SIDE_DST ? 0 : (size_t)a.cn) + (size_t)c * a.N + x) * a.sy + (u.rem ? 0 : u.part)) * dk;
       if (u.rem && u.part > 0) orow = a.outx + ((size_t)(u.part - 1) * a.rem_rows + (size_t)(u.unit - a.whole_units) * SP_SR + wave * 32 + 16 * b + i) * dk;
     }
+    float ws = 0.f;
+    if (DIST) {                                            // sum of W (y - x): less the stationary row times the sum of its weights
+      ws = wsum[b] + __shfl_xor(wsum[b], 16);
+      ws += __shfl_xor(ws, 32);
+    }
     if (xv[b]) {
+      if constexpr (DIST) {
+        const DistRow<PASS == 1> row(u.cs, x, g);
+#pragma unroll
+        for (int cb = 0; cb < NO; ++cb) {
+          const float4 xs = row.cols(16 * cb + 4 * g);
+          oacc[cb][b] -= (v4f){xs.x * ws, xs.y * ws, xs.z * ws, xs.w * ws};
+          if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few blocks' loads at a time: registers are full
+        }
+      }
 #pragma unroll
       for (int cb = 0; cb < NO; ++cb) {
         const int col = 16 * cb + 4 * g;
@@ -984,8 +1182,17 @@ template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
   if constexpr (PASS == 3) split_eval<NK, sp_eval_32(NK, 16 * NK - 8)>();
-  else split_pass<NK, PASS, F16>(a);
+  else split_pass<NK, PASS, F16, false>(a);
 }
+
+// The training passes of TransE.  Bound by instruction issue: a pair takes 11 vector instructions and two of a quarter's rate beside
+// its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 46 and 54 us where fp32 matrix instructions
+// with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits are those of fp32 instructions or half of
+// them (gradients 2e-7 against 3e-7, close pairs 1e-3 apart 3e-5 against 8e-5).  Tables in which most pairs are near (values of 5 +- 0.3) take
+// three times as long as on fp32 operands: their loop is for few.
+template <int NK, int PASS>
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
+k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true>(a); }
 
 // The form of pass 3 that the fullest rows of an instantiation take, where it is not that of the others.
 template <int NK>
@@ -1025,6 +1232,9 @@ template <int NK> static hipError_t sp_prepare() {
 #define PREP(P, F) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(P == 3 ? SplitGeom<NK>::LDS_BYTES3 : lds))
   PREP(1, true); PREP(2, true); PREP(3, true); PREP(1, false); PREP(2, false);
 #undef PREP
+#define PREP(P) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_dist<NK, P>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)SplitGeom<NK>::LDS_BYTES_DIST)
+  PREP(1); PREP(2);
+#undef PREP
   return e;
 }
 hipError_t mar_split_prepare(int dk) {
@@ -1032,20 +1242,24 @@ hipError_t mar_split_prepare(int dk) {
     case 12: return sp_prepare<12>();
     case 16: return sp_prepare<16>();
     case 25: return sp_prepare<25>();
-    default: static_assert(SplitGeom<8>::LDS_BYTES <= 64 * 1024 && SplitGeom<8>::LDS_BYTES3 <= 64 * 1024, "narrower instantiations stay below the default limit"); return hipSuccess;
+    default: static_assert(SplitGeom<8>::LDS_BYTES <= 64 * 1024 && SplitGeom<8>::LDS_BYTES3 <= 64 * 1024 && SplitGeom<8>::LDS_BYTES_DIST <= 64 * 1024, "narrower instantiations stay below the default limit"); return hipSuccess;
   }
 }
 
 template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool f16, dim3 grid, hipStream_t st) {
-  constexpr size_t lds = SplitGeom<NK>::LDS_BYTES;
-  static_assert(SplitGeom<NK>::LDS_BYTES3 <= 160 * 1024, "two images in LDS");
+  constexpr size_t lds = SplitGeom<NK>::LDS_BYTES, ldsd = SplitGeom<NK>::LDS_BYTES_DIST;
+  static_assert(SplitGeom<NK>::LDS_BYTES3 <= 160 * 1024 && SplitGeom<NK>::LDS_BYTES_DIST <= 160 * 1024, "two images in LDS");
   if constexpr (sp_eval_32(NK, 16 * NK) && !sp_eval_32(NK, 16 * NK - 8)) {
     if (pass == 3 && sp_eval_32(NK, a.dk)) {
       hipLaunchKernelGGL((k_split_eval_full<NK>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
       return hipGetLastError();
     }
   }
-  if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
+  if (a.dist) {
+    if (pass == 1) hipLaunchKernelGGL((k_split_dist<NK, 1>), grid, dim3(256), ldsd, st, a);
+    else hipLaunchKernelGGL((k_split_dist<NK, 2>), grid, dim3(256), ldsd, st, a);
+  }
+  else if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
   else if (pass == 1) {
     if (f16) hipLaunchKernelGGL((k_split<NK, 1, true>), grid, dim3(256), lds, st, a);
     else hipLaunchKernelGGL((k_split<NK, 1, false>), grid, dim3(256), lds, st, a);

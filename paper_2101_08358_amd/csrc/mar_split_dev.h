@@ -53,6 +53,11 @@ __device__ __forceinline__ v4s lds_read_tr(const char* p) {
 }
 __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 
+// The 16 bytes that lane `from` holds.
+__device__ __forceinline__ v4i sp_shfl16(v4i v, int from) {
+  return (v4i){__shfl(v[0], from), __shfl(v[1], from), __shfl(v[2], from), __shfl(v[3], from)};
+}
+
 #define SP_PEND 6                                          // candidates whose comparisons a lane of pass 3 keeps for the end (5 bits of a word each)
 #define SP_FULL 8                                          // added to their number: this lane takes no more (above SP_PEND)
 template <int NK>
@@ -63,5 +68,6 @@ struct SplitGeom {
   static constexpr int IMG = sp_image(NK);
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
   static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
+  static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4;      // TransE: and the squared norms of two tiles' rows
   static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };
