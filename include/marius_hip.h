@@ -13,7 +13,7 @@
  *     the workspace handed to mar_init_tables.
  *   - Calls only enqueue work on `hip_stream` (a hipStream_t cast to void*, NULL = the
  *     default stream); they do not synchronise.  Scalar results land in device memory.
- *     mar_train_batch also runs part of its work on a second stream owned by the context,
+ *     mar_train_batch runs part of the work of a large batch on a second stream owned by the context,
  *     forked from and joined back into `hip_stream` with events (default priority), so for the
  *     caller everything is ordered on `hip_stream`.
  *   - Return value: MAR_OK (0) or a negative MAR_E* code.  Nothing is enqueued when an
@@ -262,8 +262,9 @@ int mar_pipe_destroy(mar_pipe* pipe);
 
 /*
  * Per-phase device timing of mar_train_batch with HIP events on the stream each phase runs on.
- * Phase 0 runs on the context's second stream beside phases 1-3, except in the smallest batches
- * (up to 4,096 gradient rows), whose phases all run on the caller's stream; phase 4 runs on the
+ * Phase 0 runs on the context's second stream beside phases 1-3.  In small batches (batch_size x
+ * negs_per_chunk x dim below 2e9 and some 100,000 gradient rows) the launches of phases 1-4 carry it
+ * along, everything runs on the caller's stream and phase 0 reads 0.  Phase 4 runs on the
  * second stream in large batches (batch_size x negs_per_chunk x dim from 2e9 on) only.  Phases
  * that run beside others overlap them: the six times then do not add up to the step time.
  * Phases: 0 index build (unique set, occurrence order), 1 row gather and operand build,

@@ -137,6 +137,21 @@ bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
 // 1e8: 126 / 113 (144), 95 / 113 (58), 114 / 126 (148); 200 to 2,000 edges mostly 5 to 20 % slower on images.
 bool mar_dist_images(const MarDims& d) { return !d.bilinear && (double)d.B * d.N * d.dk >= 2.0e8; }
 
+// Whether the step's own launches carry the row order along (MarSortJob), or the second stream takes it.  Carried along it costs
+// neither launches nor events, which bound small steps, but its workgroups (a tile of 1,024 gradient rows each, about 10 us) take
+// slots of the passes.  us a step, second stream / carried along: 1,000 edges of 50 floats, 100 negatives 73 / 54; 20,000 gradient
+// rows (2,000 edges, 5 chunks, 31 floats) 81 / 50; 32,000 (13,600 edges, 28 chunks of 88 negatives, 39 floats) 107 / 91; 60,000 where
+// they fit beside both passes (18,700 edges, 111 negatives of 36) 92 / 76; 90,000 beside passes of 33 us (10,000 edges, 1,000 negatives of
+// 100) 139 / 128; where neither holds 120,000 (33,000 edges, 191 negatives of 76) 135 / 141, 230,000 (57,000 edges of 20 floats) 135 / 168,
+// 72,000 (4,200 edges, 755 negatives of 272: one workgroup a CU) 194 / 201.
+static bool order_rides(const MarDims& d, long units1, long units2) {
+  if (d.index_after_gather || d.sort_items != MAR_SORT_RIDE_ITEMS || d.sort_passes > 3 || d.n_pos_max > 96 * 1024) return false;
+  if (d.n_pos_max <= 72 * 1024 && d.dk <= 256) return true;
+  const long tiles = (d.n_pos_max + 1023) / 1024 + 7;
+  if (units1 * d.sy1 + tiles <= 256L * wgs_per_cu(d, 1) && units2 * d.sy2 + tiles <= 256L * wgs_per_cu(d, 2)) return true;
+  return d.long_passes && d.dk <= 256;
+}
+
 static int check_config(const mar_config* cfg, MarDims* d) {
   if (!cfg) return fail(MAR_EINVAL, "config is NULL");
   if (cfg->num_nodes < 1 || cfg->num_rels < 1) return fail(MAR_EINVAL, "num_nodes and num_rels must be >= 1");
@@ -203,9 +218,8 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   // score pairs x row width per step: above ~2e9 the contraction passes are long enough to hide the index build
   d->index_after_gather = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 2.0e9;
   d->sort_one = mar_sort_one_limit(d->dk, false);
-  // The smallest ones are ordered on the caller's stream: the fork and the join are half of the host's time (200 edges, 50
-  // negatives, 100 floats: a step 63 us forked, 48 on one stream; 1,000 edges, 100 negatives 72 and 76).
-  d->one_stream = d->n_pos_max <= MAR_SORT_ONE / 4 && !d->index_after_gather;
+  d->long_passes = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 6.0e8;
+  d->order_rides = order_rides(*d, units1, units2);
   return MAR_OK;
 }
 
@@ -229,7 +243,8 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
     l.kbuf[i] = (uint32_t*)take(d.sort_passes > i + 1 ? n_pos * 4 : 0);
     l.vbuf[i] = (int32_t*)take(d.sort_passes > i + 1 ? n_pos * 4 : 0);
   }
-  l.hist = (uint32_t*)take(((tiles << d.sort_bits) > rank_tiles ? (tiles << d.sort_bits) : rank_tiles) * 4);
+  const size_t counts = (tiles << d.sort_bits) * (d.order_rides ? d.sort_passes : 1);
+  l.hist = (uint32_t*)take((counts > rank_tiles ? counts : rank_tiles) * 4);
   l.perm = (int32_t*)take(n_pos * 4);
   l.ids_sorted = (uint32_t*)take(n_pos * 4);
   l.rank_sorted = (int32_t*)take(n_pos * 4);
@@ -369,13 +384,15 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   }
   // Two streams: the caller's carries the gather and the two contraction passes; the index build
   // (needed only by the per-row reduce) and the chain rule (needs pass 1 only) run beside them on `aux`.
-  hipStream_t ax = c->dm.one_stream ? st : c->aux;
+  // Small batches stay on the caller's, whose launches carry the row order along (MarSortJob).
+  const bool rides = c->dm.order_rides;
+  hipStream_t ax = rides ? st : c->aux;
   hipEvent_t* ev = nullptr;
   if (c->prof_events && c->prof_steps < c->prof_max) ev = c->prof_events + (size_t)c->prof_steps * 2 * MAR_NUM_PHASES;
 #define MARK(phase, end, stream) do { if (ev && (c->prof_mask >> (phase) & 1u)) HIP_TRY(hipEventRecord(ev[2 * (phase) + (end)], stream), "event record"); } while (0)
   // Two orders of the first launches.  Large batches: the gather runs alone at memory speed and the index build
-  // starts behind it, beside the first contraction pass that hides it.  Small batches: the index build is the
-  // longer path to the reduce, so it starts first and the gather runs beside it.
+  // starts behind it, beside the first contraction pass that hides it.  Others whose order is not carried along (ids of more than
+  // 27 bits): the index build is the longer path to the reduce, so it starts first and the gather runs beside it.
   if (c->dm.index_after_gather) {
     MARK(1, 0, st);
     HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
@@ -387,17 +404,22 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   }
   MARK(0, 0, ax);
   const int ranks = dbg && (dbg->num_uniq || dbg->uniq_nodes || dbg->uniq_rels || dbg->grad_rows);
-  HIP_TRY(mar_launch_index(c, b, ranks, ax), "index kernels");
-  if (dbg) HIP_TRY(mar_launch_debug_copy(c, b, dbg, ax), "debug copy");
+  MarSortJob job[4];
+  if (rides) {
+    for (int k = 0; k < 4; ++k) job[k] = mar_sort_slot(c, b, k, ranks, dbg);
+  } else {
+    HIP_TRY(mar_launch_index(c, b, ranks, ax), "index kernels");
+    if (dbg) HIP_TRY(mar_launch_debug_copy(c, b, dbg, ax), "debug copy");
+  }
   MARK(0, 1, ax);
   if (ax != st) HIP_TRY(hipEventRecord(c->ev_index, ax), "join");
   if (!c->dm.index_after_gather) {
     MARK(1, 0, st);
-    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
+    HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st, rides ? &job[0] : nullptr), "gather kernel");
     MARK(1, 1, st);
   }
   MARK(2, 0, st);
-  HIP_TRY(mar_launch_flash(c, b, 1, nullptr, nullptr, st), "score/softmax kernel");
+  HIP_TRY(mar_launch_flash(c, b, 1, nullptr, nullptr, st, rides ? &job[1] : nullptr), "score/softmax kernel");
   MARK(2, 1, st);
   HIP_TRY(mar_launch_flash_merge(c, b, st), "stripe merge kernel");
   // The chain rule needs pass 1 only.  Large batches run it on `aux` beside pass 2, which leaves memory bandwidth
@@ -412,12 +434,16 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
     HIP_TRY(hipEventRecord(c->ev_chain, ax), "join");
   } else {
     MARK(4, 0, st);
-    HIP_TRY(mar_launch_chain(c, b, dbg, st), "chain-rule kernel");
+    HIP_TRY(mar_launch_chain(c, b, dbg, st, rides ? &job[2] : nullptr), "chain-rule kernel");
     MARK(4, 1, st);
   }
   MARK(3, 0, st);
-  HIP_TRY(mar_launch_flash(c, b, 2, nullptr, nullptr, st), "negative-gradient kernel");
+  HIP_TRY(mar_launch_flash(c, b, 2, nullptr, nullptr, st, rides ? &job[3] : nullptr), "negative-gradient kernel");
   MARK(3, 1, st);
+  if (rides && ranks && job[3].kind != MAR_SORT_RANKS) {   // three passes over the ids: pass 2 carries the last of them
+    HIP_TRY(mar_launch_ranks(c, b, st), "rank kernels");
+    HIP_TRY(mar_launch_debug_copy(c, b, dbg, st), "debug copy");
+  }
   if (ax != st) HIP_TRY(hipStreamWaitEvent(st, c->ev_index, 0), "join");
   if (c->dm.index_after_gather) HIP_TRY(hipStreamWaitEvent(st, c->ev_chain, 0), "join");
   MARK(5, 0, st);

@@ -72,7 +72,8 @@ struct MarDims {
   int32_t reduce_small;            // the reduce gives a lane group MAR_REDUCE_SMALL positions instead of one per lane
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t sort_one;                // most gradient rows that one workgroup sorts by itself
-  int32_t one_stream;              // row order on the caller's stream (smallest batches)
+  int32_t long_passes;             // a contraction pass takes some 25 us or more
+  int32_t order_rides;             // the row order is carried along by the step's own launches (MarSortJob)
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
 };
 
@@ -100,8 +101,8 @@ void mar_set_error(const char* fmt, ...);
 // Radix sort of the gradient rows by unified id: the widest digit.
 #define MAR_SORT_MAX_BITS 9
 #define MAR_SORT_ONE (16 * 1024)  // most elements k_sort_one can hold
-// Most gradient rows that one workgroup sorts by itself.  A small batch's order is one launch then in place of two a pass, which
-// the host cannot issue as fast as a step runs (1,000 edges of 50 floats, 11,000 rows: 80 -> 72 to 78 us).  Half as many where the
+// Most gradient rows that one workgroup sorts by itself (the pipeline; steps whose order is not carried along): one launch in place of
+// two a pass, which the host cannot issue as fast as a small step runs.  Half as many where the
 // sort's own time counts (11,000 rows 27 us, in four launches 20): above 256 floats, where the kernels take longer than the host,
 // and in the pipeline, where it stands alone ahead of the staging (us a batch, one workgroup / launches: 4,000 rows of 100 floats
 // 94 / 101, 8,000 125 / 129, 9,300 171 / 167, 11,000 177 / 171, 15,600 176 / 163).
@@ -121,6 +122,32 @@ static inline int32_t mar_sort_one_limit(int dk, bool alone) { return alone || d
 static inline int mar_lane_group(int dk) { return dk <= 64 ? 16 : (dk <= 128 ? 32 : 64); }
 static inline int mar_reduce_block(const MarDims& d) { return d.reduce_small ? 256 / mar_lane_group(d.dk) * MAR_REDUCE_SMALL : 256; }
 
+// Occurrences of a batch (mar_sort_dev.h).
+struct OccArgs {
+  const int32_t *src, *rel, *dst, *neg_src, *neg_dst;
+  int32_t n, cn;
+  int32_t num_nodes;
+  int32_t roles;
+};
+// A piece of the row-sorted order that a kernel of the step carries along: its first `blocks` workgroups do it and nothing else.
+// Small batches are bound by the host and by the order's own chain of launches on a second stream (1,000 edges of 50 floats,
+// 100 negatives: 78 us a step of which 55 were kernels); carried along, it takes no launch, no event and no second stream.
+#define MAR_SORT_HIST 1
+#define MAR_SORT_SCATTER 2
+#define MAR_SORT_RANKS 4
+#define MAR_SORT_RIDE_ITEMS 4     // elements a thread: tiles of 1,024
+#define SORT_LDS_BYTES ((5 << MAR_SORT_MAX_BITS) * 4 + 16)
+struct MarSortJob {
+  int32_t kind, blocks, tiles;     // blocks: a multiple of 8, 0 for none; tiles of the work that they share
+  int32_t n_pos, sy2, shift, bits, tpad, zero_words;
+  OccArgs occ;
+  const uint32_t* keys_in; const int32_t* vals_in;
+  uint32_t* keys_out; int32_t* vals_out;
+  uint32_t *hist, *next_hist;      // counts of this pass; of the next (of all later ones, zeroed, in MAR_SORT_HIST)
+  int32_t* scalars;
+  int32_t *rank_sorted, *num_uniq, *uniq_nodes, *uniq_rels;
+};
+
 // ---- launchers (each returns a hipError_t from the launch) --------------------------
 hipError_t mar_launch_init(const mar_ctx* c, int fill, hipStream_t st);
 hipError_t mar_launch_sample(const mar_ctx* c, uint64_t step, const int32_t* es, const int32_t* ed,
@@ -138,16 +165,18 @@ struct MarBatch {
 
 // ranks != 0: also the rows' ranks, the unique list and the counts in scalars
 hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, int ranks, hipStream_t st);
+hipError_t mar_launch_ranks(const mar_ctx* c, const MarBatch& b, hipStream_t st);
+MarSortJob mar_sort_slot(const mar_ctx* c, const MarBatch& b, int slot, bool ranks, const mar_debug_out* dbg);
 // bf16 != 0 (SPLIT_BF16 training): the operand images hold bf16 instead of scaled f16 parts
 // rank_dst / rank_src (evaluation): set to 1
 hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
-                           hipStream_t st);
+                           hipStream_t st, const MarSortJob* job = nullptr);
 // Small evaluations of the bilinear models run on dense fp32 operands and fp32 matrix instructions (see mar_api.hip).
 bool mar_eval_dense(const MarDims& d, const MarBatch& b);
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
-                            hipStream_t st);
+                            hipStream_t st, const MarSortJob* job = nullptr);
 // dbg: where the log-sum-exps go if a caller asks for them
-hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st);
+hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st, const MarSortJob* job = nullptr);
 hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t* dst_off, const int32_t* dst_ids,
                              const int64_t* src_off, const int32_t* src_ids, const float* pos, int32_t* rank_dst,
                              int32_t* rank_src, hipStream_t st);

@@ -25,6 +25,7 @@ struct FlashArgs {
   // rem_tps tiles each, whose parts 1.. write to mlx / outx [part - 1][rem_rows] (sr rows per unit) and are merged by
   // a small kernel.  wslots / rslots: workgroups per XCD for the two kinds.
   int32_t units, whole_units, wslots, rslots, sr, rem_k, rem_tps;
+  int32_t carried;     // workgroups ahead of the pass's own that do a.sort: beside what flash_unit reads
   int64_t rem_rows;
   float* mlx; float* outx;
   float ml_log2;       // natural-log units of one unit of the references in ml: 1, or ln 2 where they are kept in log2 units
@@ -44,6 +45,7 @@ struct FlashArgs {
   const float *qrows, *ynorm, *table; const int32_t *neg_dst, *neg_src, *src, *dst; int32_t dim;
   // evaluation on images, where share > 0: workgroup p takes `share` tiles of the units' tiles, one more if p < share_rest
   int64_t share; int32_t share_rest;
+  MarSortJob sort;     // training passes: carried along by the first `carried` workgroups
   const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
 
@@ -52,7 +54,7 @@ struct FlashArgs {
 // number of units however few chunk-sides there are.
 struct FlashUnit { int unit, cs, stripe, part, tps; bool rem; };
 template <typename A> __device__ __forceinline__ bool flash_unit(const A& a, FlashUnit& u) {
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = blockIdx.x & 7, slot = ((int)blockIdx.x - a.carried) >> 3;   // carried: a multiple of 8
   u.rem = slot >= a.wslots;
   if (!u.rem) {
     const int w = xcd * a.wslots + slot;

@@ -23,6 +23,7 @@
 
 #include "mar_common.h"
 #include "mar_flash.h"
+#include "mar_sort_dev.h"
 
 // A operands of the second product O^T[c][x] += sum_y Y[y][c] W[y][x] for one streamed row y.
 // The 16 lanes m of a lane group supply the 16 output rows i of a matrix block; which output
@@ -150,6 +151,7 @@ k_flash(FlashArgs a) {
   constexpr int NU = DMA ? 1 : StageMap<NK, TY>::NU;      // float4 units staged per thread
   constexpr int SR = 64 * XB;                             // stationary rows per workgroup
   extern __shared__ __attribute__((aligned(16))) float smem[];
+  if (PASS == 1 && __builtin_expect((int)blockIdx.x < a.carried, 0)) { sort_job<MAR_SORT_SCATTER>(a.sort, reinterpret_cast<uint32_t*>(smem)); return; }
   const float* tile = (const float*)__builtin_assume_aligned(smem, 16);   // the tile being read
   float* const auy_all = smem + FG::NBUF * FG::TILE;      // [NBUF][TY] per streamed row: squared norm (TransE)
   const float* auy = auy_all;
@@ -596,6 +598,8 @@ k_flash_bwd(FlashArgs a) {
   static_assert(XB == 1 && 4 * TY <= 256, "one scale factor per thread: (wave's 16-negative block, streamed edge)");
   __shared__ __attribute__((aligned(16))) float aux[4][TY];   // per wave: exp(reference - lse) of the streamed edges
 
+  static_assert(sizeof(tile) >= SORT_LDS_BYTES, "the row order's pieces work in the tile's place");
+  if (__builtin_expect((int)blockIdx.x < a.carried, 0)) { sort_job<MAR_SORT_SCATTER | MAR_SORT_RANKS>(a.sort, reinterpret_cast<uint32_t*>(tile)); return; }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, m = lane & 15;
   FlashUnit u;
@@ -870,6 +874,7 @@ static hipError_t launch_sized(const FlashArgs& a, int pass, dim3 grid, hipStrea
 #define FL(P) do { \
     if (dma) hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, DM>), grid, dim3(256), lds_dma, st, a); \
     else hipLaunchKernelGGL((k_flash<NK, NC, VT, TY, XB, P, 0>), grid, dim3(256), lds_reg, st, a); } while (0)
+  static_assert(lds_reg >= SORT_LDS_BYTES && lds_dma >= SORT_LDS_BYTES, "the row order's pieces work in the tiles' place");
   if (pass == 1) FL(1);
   else if (pass == 4) FL(4);
   else if (pass == 2) hipLaunchKernelGGL((k_flash_bwd<NK, BNC, BVT, BTY, BXB>), grid, dim3(256), 0, st, a);
@@ -892,7 +897,7 @@ static hipError_t prepare_sized() {
 hipError_t mar_flash_prepare(int dk) { return dk / 4 > 64 ? prepare_sized<100, 25, 0, 32, 1>() : hipSuccess; }
 
 hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32_t* rank_dst, int32_t* rank_src,
-                            hipStream_t st) {
+                            hipStream_t st, const MarSortJob* job) {
   const MarLayout& L = c->L;
   const bool dense = pass == 3 && mar_eval_dense(c->dm, b);
   MarDims d = c->dm;
@@ -931,7 +936,16 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   }
   a.wslots = (a.whole_units * a.sy + 7) / 8;
   a.rslots = ((a.units - a.whole_units) * a.rem_k + 7) / 8;
-  dim3 grid(8u * (unsigned)(a.wslots + a.rslots));
+  // Workgroups of the row order beside a long pass that leaves slots free are as many as those, up to four tiles (about 10 us) each;
+  // one more than the chip holds would put a unit of the pass behind them (a pass of 33 us took 39 so).  Beside a short pass two tiles
+  // one after the other take longer than the pass (16 us; 31 so, 21 with a unit behind a tile).
+  if (job && job->kind) {
+    a.sort = *job;
+    const int free = (256 * (img ? mar_split_wgs_per_cu(d.dk, pass) : mar_flash_wgs_per_cu(d.dk, pass)) - 8 * (a.wslots + a.rslots)) & ~7;
+    if (d.long_passes && free >= 8 && free < a.sort.blocks && a.sort.tiles <= 4 * free) a.sort.blocks = free;
+  }
+  a.carried = a.sort.blocks;
+  dim3 grid(8u * (unsigned)(a.wslots + a.rslots) + (unsigned)a.carried);
   if (d.bilinear && pass == 3 && mar_plan_shares(d, a.units, a.yimg_tiles, a.sy, a.tps)) {
     const int64_t tiles = (int64_t)a.units * a.yimg_tiles;
     grid.x = MAR_SHARES;

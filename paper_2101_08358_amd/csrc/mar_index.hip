@@ -7,6 +7,7 @@
 // follow are bit-reproducible.  The reduce reads segment borders off the sorted ids; ranks of the rows among the unique
 // rows and the ascending unique list are formed only where a caller asks for them.
 #include "mar_common.h"
+#include "mar_sort_dev.h"
 
 // ---------------------------------------------------------------- Philox4x32-10 -----
 // Salmon, Moraes, Dror, Shaw, "Parallel random numbers: as easy as 1, 2, 3" (SC'11).
@@ -85,64 +86,17 @@ __global__ void __launch_bounds__(256) k_fill_u32(uint32_t* __restrict__ p, int6
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// ------------------------------------------------------------ occurrence numbering -----
-// Occurrence k of a batch with n edges and cn = chunks*N negatives per side (roles = 3, or 2 for
-// the relation-free Dot score, which has no relation occurrences):
-//   [0,n) source of edge k | [n,2n) destination | [2n,3n) relation (roles = 3 only) |
-//   [roles*n, +cn) destination-replacing negatives | then cn source-replacing negatives
-struct OccArgs {
-  const int32_t *src, *rel, *dst, *neg_src, *neg_dst;
-  int32_t n, cn;
-  int32_t num_nodes;
-  int32_t roles;
-};
-
-__device__ __forceinline__ int32_t occ_unified_id(const OccArgs& a, int64_t k) {
-  const int64_t n = a.n;
-  if (k < n) return a.src[k];
-  if (k < 2 * n) return a.dst[k - n];
-  if (k < a.roles * n) return a.num_nodes + a.rel[k - 2 * n];
-  k -= a.roles * n;
-  if (k < a.cn) return a.neg_dst[k];
-  return a.neg_src[k - a.cn];
-}
-
 // Blocks of the index kernels stay at 256 threads: they run beside the contraction kernels on a second stream and have
-// to fit into the wave slots and registers those leave free on a CU.  (k_sort_one, 1,024 threads and 96 KB of LDS, is launched for
-// small batches only, ahead of the gather, while CUs are free.)
-
-// Block-wide exclusive scan of one value per thread (BT threads); returns the exclusive
-// prefix and the block total through `total`.
-template <int BT>
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* total) {
-  __shared__ uint32_t wave_tot[BT / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t t = __shfl_up(inc, o);
-    if (lane >= o) inc += t;
-  }
-  __syncthreads();                    // protects wave_tot across successive calls
-  if (lane == 63) wave_tot[wave] = inc;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < BT / 64; ++w) {
-    const uint32_t t = wave_tot[w];
-    if (w < wave) base += t;
-    tot += t;
-  }
-  *total = tot;
-  return base + inc - v;
-}
+// to fit into the wave slots and registers those leave free on a CU.  (k_sort_one, 1,024 threads and 96 KB of LDS, stands alone in
+// the pipeline, or ahead of the gather of a small batch with ids of more than 27 bits.)
 
 // ------------------------------------------------ row-sorted order of the gradient rows -----
 // Gradient row gr belongs to occurrence k = gr (edge side, gr < roles*n) or to part (gr - roles*n) % sy2
 // of negative occurrence roles*n + (gr - roles*n) / sy2; its sort key is the unified id of the occurrence's
 // table row.  A least-significant-digit radix sort with digits of `bits` bits puts the gradient rows in key order;
 // every pass is stable, so equal keys stay in gradient-row order.
-// Small batches: k_sort_one (mar_sort_one_limit).  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements)
+// Small batches: the step's own launches carry the pieces along (MarSortJob, mar_sort_slot); in the pipeline k_sort_one up to
+// mar_sort_one_limit.  Else one pass = k_sort_hist (digit counts per tile of 256 ITEMS elements)
 // + k_sort_scatter (each tile derives its digits' global offsets from the counts of all tiles and scatters its elements).
 // Counts are kept digit by digit, the tiles' counts of a digit side by side, so that the thread that owns a digit reads
 // them 16 bytes at a time.
@@ -151,153 +105,30 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
 // 250,000 gradient rows and 27-bit ids (three passes of 9 bits) 62 tiles x 31,744 counts a pass, 8 MB of cached reads;
 // sixteen times the batch 2 GB.
 
-// Lanes of the wave that hold the same digit as this lane (valid lanes only).
-__device__ __forceinline__ uint64_t match_digit(uint32_t digit, int bits, bool valid) {
-  uint64_t mask = __ballot(valid);
-  for (int b = 0; b < bits; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t bal = __ballot(bit);
-    mask &= bit ? bal : ~bal;
-  }
-  return mask;
-}
-
-// FIRST: computes the keys from the batch's ids and stores them; also resets the owner list's counter.
 template <int FIRST, int ITEMS>
 __global__ void __launch_bounds__(256)
 k_sort_hist(OccArgs a, int64_t n_pos, int sy2, const uint32_t* __restrict__ keys_in, uint32_t* __restrict__ keys_out, int shift, int bits,
             int tpad, uint32_t* __restrict__ hist, int32_t* __restrict__ scalars) {
   __shared__ uint32_t h[1 << MAR_SORT_MAX_BITS];
-  const int bins = 1 << bits;
-  const int lane = threadIdx.x & 63;
-  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS);
-  const int64_t n3 = a.roles * (int64_t)a.n;
-  uint32_t key[ITEMS];
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const int64_t gr = base + j * 256 + threadIdx.x;
-    const int64_t grc = gr < n_pos ? gr : n_pos - 1;
-    key[j] = FIRST ? (uint32_t)occ_unified_id(a, grc < n3 ? grc : n3 + (grc - n3) / sy2) : keys_in[grc];
-  }
-  for (int i = threadIdx.x; i < bins; i += 256) h[i] = 0u;
-  if (FIRST && blockIdx.x == 0 && threadIdx.x == 0) scalars[2] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    const int64_t gr = base + j * 256 + threadIdx.x;
-    const bool valid = gr < n_pos;
-    if (FIRST && valid) keys_out[gr] = key[j];
-    // one LDS atomic per distinct digit of the wave (a hot row fills whole waves with one key)
-    const uint32_t digit = (key[j] >> shift) & (uint32_t)(bins - 1);
-    const uint64_t same = match_digit(digit, bits, valid);
-    if (valid && (same & ((1ull << lane) - 1ull)) == 0ull) atomicAdd(&h[digit], (uint32_t)__popcll(same));
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < bins; i += 256) hist[(size_t)i * tpad + blockIdx.x] = h[i];
+  sort_hist_tile<FIRST, ITEMS>(blockIdx.x, h, a, n_pos, sy2, keys_in, keys_out, shift, bits, tpad, hist, scalars);
 }
 
-// Scatters the tile's elements to their places in digit order.  Global place of an element =
-// (elements with a smaller digit anywhere) + (same digit in earlier tiles) + (same digit earlier in this
-// tile).  Inside the tile wave w owns a contiguous quarter and walks it 64 consecutive elements at a time,
-// so "earlier in this tile" = same digit in earlier waves + earlier rounds of this wave + lower lanes.
-// vals_in == NULL: the values are the element indices (first pass).
 template <int ITEMS>
 __global__ void __launch_bounds__(256)
-k_sort_scatter(const uint32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in,
-               uint32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out, const uint32_t* __restrict__ hist,
-               int64_t n, int shift, int bits, int ntiles, int tpad) {
-  __shared__ uint32_t wcnt[4][1 << MAR_SORT_MAX_BITS];      // per wave: elements per digit, then their exclusive prefix over waves
-  __shared__ uint32_t gbase[1 << MAR_SORT_MAX_BITS];        // global place of the tile's first element of each digit
-  const int bins = 1 << bits;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < 4 * bins; i += 256) wcnt[i >> bits][i & (bins - 1)] = 0u;
-
-  // keys and values of this wave's quarter, round r = 64 consecutive elements
-  const int64_t q0 = (int64_t)blockIdx.x * (256 * ITEMS) + (int64_t)wave * (64 * ITEMS) + lane;
-  uint32_t key[ITEMS];
-  int32_t val[ITEMS];
-#pragma unroll
-  for (int r = 0; r < ITEMS; ++r) {
-    const int64_t idx = q0 + 64 * r;
-    key[r] = idx < n ? keys_in[idx] : 0u;
-    val[r] = (vals_in && idx < n) ? vals_in[idx] : (int32_t)idx;
-  }
-
-  // digit offsets: thread t owns digits [t*per, (t+1)*per), per = 1 or 2; a digit's counts beyond the last tile are not used
-  const int per = (bins + 255) / 256;
-  uint32_t before[2] = {0u, 0u}, total[2] = {0u, 0u};
-  const int d0 = threadIdx.x * per;
-  for (int b0 = 0; b0 < ntiles; b0 += 32) {                 // 32 tiles' counts in flight per digit
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (j < per && d0 + j < bins) {
-        uint4 v[8];
-        const uint4* hrow = reinterpret_cast<const uint4*>(hist + (size_t)(d0 + j) * tpad + b0);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = b0 + 4 * i < tpad ? hrow[i] : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint32_t c[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int tile = b0 + 4 * i + k;
-            if (tile < ntiles) total[j] += c[k];
-            if (tile < (int)blockIdx.x) before[j] += c[k];
-          }
-        }
-      }
-    }
-  }
-  uint32_t tot_all;
-  uint32_t run = block_exclusive_scan<256>(total[0] + total[1], &tot_all);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (j < per && d0 + j < bins) { gbase[d0 + j] = run + before[j]; run += total[j]; }
-  }
-  __syncthreads();                                          // counters cleared, gbase written
-
-  uint32_t loc[ITEMS];
-#pragma unroll
-  for (int r = 0; r < ITEMS; ++r) {
-    const bool valid = q0 + 64 * r < n;
-    const uint32_t digit = (key[r] >> shift) & (uint32_t)(bins - 1);
-    const uint64_t same = match_digit(digit, bits, valid);
-    const uint32_t lower = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
-    loc[r] = 0u;
-    if (valid) {
-      // every lane of a group reads the wave's counter before the group's first lane advances it: one wave
-      // executes both accesses in program order
-      const uint32_t old = wcnt[wave][digit];
-      loc[r] = old + lower;
-      if (lower == 0u) wcnt[wave][digit] = old + (uint32_t)__popcll(same);
-    }
-  }
-  __syncthreads();
-  for (int d = threadIdx.x; d < bins; d += 256) {
-    const uint32_t c0 = wcnt[0][d], c1 = wcnt[1][d], c2 = wcnt[2][d];
-    wcnt[0][d] = 0u; wcnt[1][d] = c0; wcnt[2][d] = c0 + c1; wcnt[3][d] = c0 + c1 + c2;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < ITEMS; ++r) {
-    if (q0 + 64 * r < n) {
-      const uint32_t digit = (key[r] >> shift) & (uint32_t)(bins - 1);
-      const uint32_t p = gbase[digit] + wcnt[wave][digit] + loc[r];
-      keys_out[p] = key[r];
-      vals_out[p] = val[r];
-    }
-  }
+k_sort_scatter(const uint32_t* __restrict__ keys_in, const int32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
+               int32_t* __restrict__ vals_out, const uint32_t* __restrict__ hist, int64_t n, int shift, int bits, int ntiles, int tpad) {
+  __shared__ uint32_t lds[SORT_LDS_BYTES / 4];
+  sort_scatter_tile<ITEMS>(blockIdx.x, lds, keys_in, vals_in, keys_out, vals_out, hist, nullptr, n, shift, bits, ntiles, tpad);
 }
 
 // The whole sort of a small batch (at most MAR_SORT_ONE rows) in one workgroup: wave w owns 64 `rounds` consecutive elements,
 // element `idx` = round r, lane l of it, in registers; between two passes keys and values change places through LDS.
 // Bound by the latency of its own chain (16 waves on one CU; 2 to 3 passes of ballots and counters): 11,000 rows, two passes 27 us
-// against 20 in four launches, but beside the gather and the passes, and the host, which bounds such a step, issues one launch for
-// two a pass (200 edges 74 -> 63 us a step).
+// against 20 in four launches, but the host issues one launch for two a pass.
 template <int ROUNDS>
 __global__ void __launch_bounds__(1024)
 k_sort_one(OccArgs a, int n, int sy2, int passes, int bits, uint32_t* __restrict__ ids_sorted, int32_t* __restrict__ perm, int32_t* __restrict__ scalars) {
-  __shared__ uint32_t buf[1024 * ROUNDS];
+  __shared__ uint32_t buf[1024 * ROUNDS], wave_tot[16];
   __shared__ uint32_t cnt[16][1 << MAR_SORT_MAX_BITS];      // per wave: elements per digit, then the place of its first of each digit
   const int bins = 1 << bits, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n3 = a.roles * a.n;
   const int rounds = (n + 1023) / 1024;                     // uniform, at most ROUNDS
@@ -336,7 +167,7 @@ k_sort_one(OccArgs a, int n, int sy2, int passes, int bits, uint32_t* __restrict
     const int d = threadIdx.x;
 #pragma unroll
     for (int w = 0; w < 16; ++w) { c[w] = d < bins ? cnt[w][d] : 0u; sum += c[w]; }
-    uint32_t first = block_exclusive_scan<1024>(sum, &all);
+    uint32_t first = block_exclusive_scan<1024>(sum, &all, wave_tot);
     if (d < bins) {
 #pragma unroll
       for (int w = 0; w < 16; ++w) { cnt[w][d] = first; first += c[w]; }
@@ -368,14 +199,13 @@ k_sort_one(OccArgs a, int n, int sy2, int passes, int bits, uint32_t* __restrict
 // is the number of heads before it.  k_rank_count counts the heads of MAR_RANK_TILE positions each; k_rank_apply adds
 // up the counts of the tiles before its own and writes the rank of every position and of every gradient row, the
 // ascending unique list and, into scalars, the number of unique rows and of unique nodes.
-__device__ __forceinline__ bool is_head(const uint32_t* __restrict__ ids, int64_t p, int64_t n) { return p < n && (p == 0 || ids[p - 1] != ids[p]); }
-
 __global__ void __launch_bounds__(256) k_rank_count(const uint32_t* __restrict__ ids, int64_t n, uint32_t* __restrict__ counts) {
   uint32_t c = 0;
 #pragma unroll
   for (int j = 0; j < MAR_RANK_TILE / 256; ++j) c += is_head(ids, (int64_t)blockIdx.x * MAR_RANK_TILE + threadIdx.x * (MAR_RANK_TILE / 256) + j, n) ? 1u : 0u;
   uint32_t tot;
-  block_exclusive_scan<256>(c, &tot);
+  __shared__ uint32_t wave_tot[4];
+  block_exclusive_scan<256>(c, &tot, wave_tot);
   if (threadIdx.x == 0) counts[blockIdx.x] = tot;
 }
 
@@ -386,12 +216,13 @@ k_rank_apply(const uint32_t* __restrict__ ids, const int32_t* __restrict__ perm,
   uint32_t before = 0;
   for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) before += counts[i];
   uint32_t base, c = 0, tot;
-  block_exclusive_scan<256>(before, &base);
+  __shared__ uint32_t wave_tot[4];
+  block_exclusive_scan<256>(before, &base, wave_tot);
   const int64_t p0 = (int64_t)blockIdx.x * MAR_RANK_TILE + threadIdx.x * PER;
   bool head[PER];
 #pragma unroll
   for (int j = 0; j < PER; ++j) { head[j] = is_head(ids, p0 + j, n); c += head[j] ? 1u : 0u; }
-  uint32_t heads = base + block_exclusive_scan<256>(c, &tot);   // heads before this thread's positions
+  uint32_t heads = base + block_exclusive_scan<256>(c, &tot, wave_tot);   // heads before this thread's positions
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int64_t p = p0 + j;
@@ -477,6 +308,48 @@ static void launch_sort(const mar_ctx* c, const MarBatch& b, const OccArgs& a, h
   }
 }
 
+// Slots of a step that carry the order along: 0 the gather (counts of the first digit), 1 pass 1 (first scatter), 2 the chain rule
+// (the second of three, or of two before the ranks), 3 pass 2 (the last, or the ranks).
+MarSortJob mar_sort_slot(const mar_ctx* c, const MarBatch& b, int slot, bool ranks, const mar_debug_out* dbg) {
+  const MarDims& d = c->dm;
+  const MarLayout& L = c->L;
+  MarSortJob j = {};
+  const int tile = 256 * MAR_SORT_RIDE_ITEMS;
+  const bool rank = ranks && slot == 3 && d.sort_passes < 3, early = ranks || d.sort_passes > 2;
+  const int p = early || slot < 2 ? slot - 1 : slot - 2;    // scatter pass of the slot
+  if ((p >= d.sort_passes || (!early && slot == 2)) && !rank) return j;
+  j.occ = OccArgs{b.src, b.rel, b.dst, b.neg_src, b.neg_dst, b.n, b.cn, (int32_t)d.num_nodes, d.roles};
+  j.n_pos = (int32_t)b.n_pos; j.sy2 = d.sy2; j.bits = d.sort_bits; j.scalars = L.scalars;
+  j.tiles = (j.n_pos + (rank ? MAR_RANK_TILE : tile) - 1) / (rank ? MAR_RANK_TILE : tile);
+  j.blocks = (j.tiles + 7) & ~7;
+  j.tpad = (j.tiles + 3) & ~3;
+  const int words = j.tpad << d.sort_bits;                  // of one pass's counts
+  if (rank) {
+    j.kind = MAR_SORT_RANKS;
+    j.keys_in = L.ids_sorted; j.rank_sorted = L.rank_sorted;
+    j.num_uniq = dbg->num_uniq; j.uniq_nodes = dbg->uniq_nodes; j.uniq_rels = dbg->uniq_rels;
+  } else if (slot == 0) {
+    j.kind = MAR_SORT_HIST;
+    j.keys_out = L.keys0; j.hist = L.hist; j.next_hist = L.hist + words; j.zero_words = (d.sort_passes - 1) * words;
+  } else {
+    const bool last = p == d.sort_passes - 1;
+    j.kind = MAR_SORT_SCATTER;
+    j.keys_in = p == 0 ? L.keys0 : L.kbuf[(p - 1) & 1]; j.vals_in = p == 0 ? nullptr : L.vbuf[(p - 1) & 1];
+    j.keys_out = last ? L.ids_sorted : L.kbuf[p & 1]; j.vals_out = last ? L.perm : L.vbuf[p & 1];
+    j.hist = L.hist + (size_t)p * words; j.next_hist = last ? nullptr : j.hist + words; j.shift = p * d.sort_bits;
+  }
+  return j;
+}
+
+hipError_t mar_launch_ranks(const mar_ctx* c, const MarBatch& b, hipStream_t st) {
+  const MarDims& d = c->dm;
+  const MarLayout& L = c->L;
+  const unsigned nt = (unsigned)((b.n_pos + MAR_RANK_TILE - 1) / MAR_RANK_TILE);
+  hipLaunchKernelGGL(k_rank_count, dim3(nt), dim3(256), 0, st, L.ids_sorted, b.n_pos, L.hist);
+  hipLaunchKernelGGL(k_rank_apply, dim3(nt), dim3(256), 0, st, L.ids_sorted, L.perm, b.n_pos, L.hist, (int32_t)d.num_nodes, L.rank_sorted, L.keys0, L.uniq, L.scalars);
+  return hipGetLastError();
+}
+
 hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, int ranks, hipStream_t st) {
   const MarDims& d = c->dm;
   const MarLayout& L = c->L;
@@ -484,11 +357,7 @@ hipError_t mar_launch_index(const mar_ctx* c, const MarBatch& b, int ranks, hipS
   if (b.n_pos <= 8 * 1024 && b.n_pos <= d.sort_one) hipLaunchKernelGGL((k_sort_one<8>), dim3(1), dim3(1024), 0, st, a, (int)b.n_pos, (int)d.sy2, (int)d.sort_passes, (int)d.sort_bits, L.ids_sorted, L.perm, L.scalars);
   else if (b.n_pos <= d.sort_one) hipLaunchKernelGGL((k_sort_one<16>), dim3(1), dim3(1024), 0, st, a, (int)b.n_pos, (int)d.sy2, (int)d.sort_passes, (int)d.sort_bits, L.ids_sorted, L.perm, L.scalars);
   else if (d.sort_items == 4) launch_sort<4>(c, b, a, st); else launch_sort<16>(c, b, a, st);
-  if (ranks) {
-    const unsigned nt = (unsigned)((b.n_pos + MAR_RANK_TILE - 1) / MAR_RANK_TILE);
-    hipLaunchKernelGGL(k_rank_count, dim3(nt), dim3(256), 0, st, L.ids_sorted, b.n_pos, L.hist);
-    hipLaunchKernelGGL(k_rank_apply, dim3(nt), dim3(256), 0, st, L.ids_sorted, L.perm, b.n_pos, L.hist, (int32_t)d.num_nodes, L.rank_sorted, L.keys0, L.uniq, L.scalars);
-  }
+  if (ranks) return mar_launch_ranks(c, b, st);
   return hipGetLastError();
 }
 

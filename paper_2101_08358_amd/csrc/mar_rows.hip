@@ -6,6 +6,7 @@
 
 #include "mar_common.h"
 #include "mar_split.h"
+#include "mar_sort_dev.h"
 
 struct RowArgs {
   const float *node_emb, *rel_emb;
@@ -153,11 +154,16 @@ __device__ __forceinline__ void store_dense_row(float* row, const float4 (&v)[NV
 constexpr int prep_edges(int gl, bool img) { return img && gl == 64 ? 4 : 2; }
 constexpr int PREP_NEGS = 4;
 
-template <int GL, int NV, bool VEC, int MODEL, int FORM>
+// CARRY: the first `carried` workgroups do a piece of the row order (small batches; instantiations of their own, because the piece
+// costs the others registers: 50,000 edges 1.2 % of a step, 20,000 edges' evaluation of 400 floats 2.7 %).
+template <int GL, int NV, bool VEC, int MODEL, int FORM, bool CARRY>
 __global__ void __launch_bounds__(256)
-k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* __restrict__ Km, float* __restrict__ qq,
+k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* __restrict__ Km, float* __restrict__ qq,
        float* __restrict__ kk, float* __restrict__ pos, float* __restrict__ pos_user, int32_t* __restrict__ rank_dst,
-       int32_t* __restrict__ rank_src, SplitImages qi, SplitImages ki) {
+       int32_t* __restrict__ rank_src, SplitImages qi, SplitImages ki, MarSortJob job) {
+  extern __shared__ uint32_t sort_lds[];         // launched with the digits' counts where a job rides along
+  if (CARRY && (int)blockIdx.x < carried) { sort_job<MAR_SORT_HIST>(job, sort_lds); return; }
+  const int block = CARRY ? (int)blockIdx.x - carried : (int)blockIdx.x;
   constexpr bool IMG = FORM != PREP_DENSE, CPLX = MODEL == MAR_MODEL_COMPLEX, F16 = FORM == PREP_F16;
   constexpr int GPB = 256 / GL;                  // lane groups per block
   constexpr int E = prep_edges(GL, IMG), P = PREP_NEGS;
@@ -181,9 +187,9 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
     if (l == 0) atomicMax(&s_max[which][rw / SP_EB], __float_as_int(mx));
     if (bad) s_bad[which][rw / SP_EB] = 1;
   };
-  if ((int)blockIdx.x < nbB) {
-    const int chunk = IMG ? blockIdx.x / wpc_e : 0;
-    const int r0 = (IMG ? blockIdx.x % wpc_e : blockIdx.x) * RE + grp * E;         // first row of the group in its chunk
+  if (block < nbB) {
+    const int chunk = IMG ? block / wpc_e : 0;
+    const int r0 = (IMG ? block % wpc_e : block) * RE + grp * E;         // first row of the group in its chunk
     const int nr = IMG ? min(a.S, a.n - chunk * a.S) : a.n;                         // edges of the chunk
     if (IMG) { if (r0 - grp * E >= ((nr + SP_TY - 1) & ~(SP_TY - 1))) return; }     // uniform over the workgroup
     else if (r0 >= nr) return;
@@ -284,7 +290,7 @@ k_prep(RowArgs a, int nbB, int wpc_e, int wpc_n, float* __restrict__ Q, float* _
     return;
   }
   {
-    const int blk = (int)blockIdx.x - nbB;
+    const int blk = block - nbB;
     const int cs = IMG ? blk / wpc_n : 0;                        // 2 * chunk + side
     const int r0 = (IMG ? blk % wpc_n : blk) * RN + grp * P;     // first row: in its chunk-side, or among the 2*cn negatives
     const int nr = IMG ? a.N : 2 * a.cn;
@@ -429,15 +435,18 @@ __device__ __forceinline__ void chain_complex(float sr, float si, float rr, floa
 // One group of GL lanes per edge.  VEC (dim % 4 == 0): a lane moves NV float4s per row (for ComplEx NV float2s of
 // the real half and the matching float2s of the imaginary half), every load of the edge is issued before the
 // first use; SY1 > 0: pass 1 was split into exactly SY1 parts (1 for the large batch shapes), SY1 = 0: a.sy1 parts.
-template <int GL, int NV, int MODEL, bool VEC, int SY1>
+template <int GL, int NV, int MODEL, bool VEC, int SY1, bool CARRY>
 __global__ void __launch_bounds__(256)
-k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, const float* __restrict__ pos,
-        float* __restrict__ lse_dst, float* __restrict__ lse_src, float* __restrict__ G, float* __restrict__ loss_part) {
+k_chain(RowArgs a, int carried, const float* __restrict__ gQ, const float* __restrict__ ml, const float* __restrict__ pos,
+        float* __restrict__ lse_dst, float* __restrict__ lse_src, float* __restrict__ G, float* __restrict__ loss_part, MarSortJob job) {
+  extern __shared__ uint32_t sort_lds[];
+  if (CARRY && (int)blockIdx.x < carried) { sort_job<MAR_SORT_SCATTER>(job, sort_lds); return; }
+  const int block = CARRY ? (int)blockIdx.x - carried : (int)blockIdx.x;
   constexpr int GPB = 256 / GL;
   constexpr int P = SY1 ? SY1 : MAR_MAX_PARTS;
   __shared__ float lsum[GPB];
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
-  const int e = blockIdx.x * GPB + grp;
+  const int e = block * GPB + grp;
   const int dim = a.dim, dk = a.dk;
   const int sy1 = SY1 ? SY1 : a.sy1;
   const size_t part_rows = (size_t)2 * a.B;
@@ -559,7 +568,7 @@ k_chain(RowArgs a, const float* __restrict__ gQ, const float* __restrict__ ml, c
   if (threadIdx.x == 0) {
     float t = 0.f;
     for (int i = 0; i < GPB; ++i) t += lsum[i];
-    loss_part[blockIdx.x] = t;
+    loss_part[block] = t;
   }
 }
 
@@ -1108,38 +1117,42 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
 
 template <int GL, int NV, int MODEL, int FORM>
 static void launch_prep(const RowArgs& a, const MarLayout& L, float* pos_out, int32_t* rank_dst, int32_t* rank_src, const SplitImages& qi,
-                        const SplitImages& ki, hipStream_t st) {
+                        const SplitImages& ki, const MarSortJob& job, hipStream_t st) {
   constexpr bool img = FORM != PREP_DENSE;
   constexpr int gpb = 256 / GL, re = gpb * prep_edges(GL, img), rn = gpb * PREP_NEGS;
   const int wpc_e = (qi.tiles * SP_TY + re - 1) / re, wpc_n = (ki.tiles * SP_TY + rn - 1) / rn;
   const int nchunks = a.cn / a.N;
   const int nbB = img ? nchunks * wpc_e : (a.n + re - 1) / re;
   const int nbC = img ? 2 * nchunks * wpc_n : (2 * a.cn + rn - 1) / rn;
-  const dim3 grid(nbB + nbC), blk(256);
+  const dim3 grid(nbB + nbC + job.blocks), blk(256);
+  const unsigned lds = job.blocks ? 4u << MAR_SORT_MAX_BITS : 0u;
   // evaluation keeps the fp32 operands for close comparisons, or (dense) works on them: they lie in the gradients' places
   float* q = MODEL == MAR_MODEL_TRANSE ? L.Q : (rank_dst ? L.gQ : nullptr);
   float* km = MODEL == MAR_MODEL_TRANSE ? L.Km : L.G;
-  if (a.dim % 4 == 0) hipLaunchKernelGGL((k_prep<GL, NV, true, MODEL, FORM>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
-  else hipLaunchKernelGGL((k_prep<GL, NV, false, MODEL, FORM>), grid, blk, 0, st, a, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki);
+#define PREP_LAUNCH(V, CARRY) hipLaunchKernelGGL((k_prep<GL, NV, V, MODEL, FORM, CARRY>), grid, blk, lds, st, a, job.blocks, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki, job)
+  if (a.dim % 4 == 0) { if (job.blocks) PREP_LAUNCH(true, true); else PREP_LAUNCH(true, false); }
+  else { if (job.blocks) PREP_LAUNCH(false, true); else PREP_LAUNCH(false, false); }
+#undef PREP_LAUNCH
 }
 
 hipError_t mar_launch_prep(const mar_ctx* c, const MarBatch& b, float* pos_out, int bf16, int32_t* rank_dst, int32_t* rank_src,
-                           hipStream_t st) {
+                           hipStream_t st, const MarSortJob* job) {
   const MarLayout& L = c->L;
+  const MarSortJob jb = job ? *job : MarSortJob{};
   RowArgs a = row_args(c, b);
   const SplitImages qi = sp_images(L.Qimg, L.Qexp, nullptr, a.dk, c->dm.S), ki = sp_images(L.Kimg, L.Kexp, L.Knorm, a.dk, c->dm.N);
   const int GL = mar_lane_group(a.dk);
   const int form = rank_dst && mar_eval_dense(c->dm, b) ? PREP_DENSE : (bf16 ? PREP_BF16 : PREP_F16);
 #define PREP3(GLV, NVV, M) do { \
-    if (form == PREP_F16) launch_prep<GLV, NVV, M, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-    else if (form == PREP_BF16) launch_prep<GLV, NVV, M, PREP_BF16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-    else launch_prep<GLV, NVV, M, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); } while (0)
+    if (form == PREP_F16) launch_prep<GLV, NVV, M, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, jb, st); \
+    else if (form == PREP_BF16) launch_prep<GLV, NVV, M, PREP_BF16>(a, L, pos_out, rank_dst, rank_src, qi, ki, jb, st); \
+    else launch_prep<GLV, NVV, M, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, jb, st); } while (0)
 #define PREP(GLV, NVV) do { switch (a.model) { \
     case MAR_MODEL_DISTMULT: PREP3(GLV, NVV, MAR_MODEL_DISTMULT); break; \
     case MAR_MODEL_COMPLEX: PREP3(GLV, NVV, MAR_MODEL_COMPLEX); break; \
     case MAR_MODEL_TRANSE: \
-      if (c->dm.dist_img && !rank_dst) launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
-      else launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, st); \
+      if (c->dm.dist_img && !rank_dst) launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_F16>(a, L, pos_out, rank_dst, rank_src, qi, ki, jb, st); \
+      else launch_prep<GLV, NVV, MAR_MODEL_TRANSE, PREP_DENSE>(a, L, pos_out, rank_dst, rank_src, qi, ki, jb, st); \
       break; \
     default: PREP3(GLV, NVV, MAR_MODEL_DOT); break; } } while (0)
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
@@ -1170,34 +1183,37 @@ hipError_t mar_launch_filter(const mar_ctx* c, const MarBatch& b, const int64_t*
 }
 
 template <int GL, int NV, int MODEL>
-static void launch_chain(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, hipStream_t st) {
-#define CHAIN(V, S) hipLaunchKernelGGL((k_chain<GL, NV, MODEL, V, S>), grid, dim3(256), 0, st, a, L.gQ, L.ml, L.pos, lse_dst, lse_src, L.G, L.loss_part)
+static void launch_chain(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, const MarSortJob& job, hipStream_t st) {
+#define CHAIN2(V, S, CARRY) hipLaunchKernelGGL((k_chain<GL, NV, MODEL, V, S, CARRY>), grid, dim3(256), CARRY ? SORT_LDS_BYTES : 0, st, a, job.blocks, L.gQ, L.ml, L.pos, lse_dst, lse_src, L.G, L.loss_part, job)
+#define CHAIN(V, S) do { if (job.blocks) CHAIN2(V, S, true); else CHAIN2(V, S, false); } while (0)
   if (a.dim % 4 == 0) { if (a.sy1 == 1) CHAIN(true, 1); else if (a.sy1 == 2) CHAIN(true, 2); else CHAIN(true, 0); }
   else CHAIN(false, 0);
 #undef CHAIN
+#undef CHAIN2
 }
 
 template <int GL, int NV>
-static void launch_chain_model(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, hipStream_t st) {
+static void launch_chain_model(const RowArgs& a, const MarLayout& L, float* lse_dst, float* lse_src, dim3 grid, const MarSortJob& job, hipStream_t st) {
   switch (a.model) {
-    case MAR_MODEL_DISTMULT: launch_chain<GL, NV, MAR_MODEL_DISTMULT>(a, L, lse_dst, lse_src, grid, st); break;
-    case MAR_MODEL_COMPLEX:  launch_chain<GL, NV, MAR_MODEL_COMPLEX>(a, L, lse_dst, lse_src, grid, st); break;
-    case MAR_MODEL_TRANSE:   launch_chain<GL, NV, MAR_MODEL_TRANSE>(a, L, lse_dst, lse_src, grid, st); break;
-    default:                 launch_chain<GL, NV, MAR_MODEL_DOT>(a, L, lse_dst, lse_src, grid, st); break;
+    case MAR_MODEL_DISTMULT: launch_chain<GL, NV, MAR_MODEL_DISTMULT>(a, L, lse_dst, lse_src, grid, job, st); break;
+    case MAR_MODEL_COMPLEX:  launch_chain<GL, NV, MAR_MODEL_COMPLEX>(a, L, lse_dst, lse_src, grid, job, st); break;
+    case MAR_MODEL_TRANSE:   launch_chain<GL, NV, MAR_MODEL_TRANSE>(a, L, lse_dst, lse_src, grid, job, st); break;
+    default:                 launch_chain<GL, NV, MAR_MODEL_DOT>(a, L, lse_dst, lse_src, grid, job, st); break;
   }
 }
 
-hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st) {
+hipError_t mar_launch_chain(const mar_ctx* c, const MarBatch& b, const mar_debug_out* dbg, hipStream_t st, const MarSortJob* carried) {
   const MarLayout& L = c->L;
   RowArgs a = row_args(c, b);
   const int GL = mar_lane_group(a.dk), gpb = 256 / GL;
-  const dim3 grid((b.n + gpb - 1) / gpb);
+  const MarSortJob job = carried ? *carried : MarSortJob{};
+  const dim3 grid((b.n + gpb - 1) / gpb + job.blocks);
   float *lse_dst = dbg ? dbg->lse_dst : nullptr, *lse_src = dbg ? dbg->lse_src : nullptr;
   // lanes x float4s per lane cover a row (ComplEx: lanes x float2s cover half a row)
-  if (GL == 16) launch_chain_model<16, 1>(a, L, lse_dst, lse_src, grid, st);
-  else if (GL == 32) launch_chain_model<32, 1>(a, L, lse_dst, lse_src, grid, st);
-  else if (a.dk <= 256) launch_chain_model<64, 1>(a, L, lse_dst, lse_src, grid, st);
-  else launch_chain_model<64, 2>(a, L, lse_dst, lse_src, grid, st);
+  if (GL == 16) launch_chain_model<16, 1>(a, L, lse_dst, lse_src, grid, job, st);
+  else if (GL == 32) launch_chain_model<32, 1>(a, L, lse_dst, lse_src, grid, job, st);
+  else if (a.dk <= 256) launch_chain_model<64, 1>(a, L, lse_dst, lse_src, grid, job, st);
+  else launch_chain_model<64, 2>(a, L, lse_dst, lse_src, grid, job, st);
   return hipGetLastError();
 }
 

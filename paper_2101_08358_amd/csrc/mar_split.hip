@@ -54,6 +54,7 @@
 
 #include "mar_common.h"
 #include "mar_split_dev.h"
+#include "mar_sort_dev.h"
 
 // Evaluation compares scores with the positive's, and where the two are within rounding of one another the outcome
 // belongs to the arithmetic (an edge's own endpoint among the candidates scores what the edge does).  Comparisons
@@ -668,7 +669,8 @@ template <bool EDGE> struct DistRow {
 // DIST (TransE): the score is -|x - y|, its square expanded as |x|^2 + |y|^2 - 2 x.y with the norms in fp32.  Pairs for which the
 // expansion cancels (below 2^-8 of the norms' sum) are formed from the differences of their columns (rare in training; a wave
 // without one skips the loop).  The second product then runs with W = softmax weight / distance, less x times the sum of the W.
-template <int NK, int PASS, bool F16, bool DIST>
+// CARRY: the first a.carried workgroups do a piece of the row order (small batches).
+template <int NK, int PASS, bool F16, bool DIST, bool CARRY>
 __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   static_assert(F16 || !DIST, "TransE's operands are f16 pairs");
   typedef SplitGeom<NK> SG;
@@ -680,6 +682,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   constexpr int NO = NK;                                   // 16-column output blocks
   constexpr float LOG2E = 1.44269504088896341f;
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  if (CARRY && __builtin_expect((int)blockIdx.x < a.carried, 0)) { sort_job<PASS == 1 ? MAR_SORT_SCATTER : MAR_SORT_SCATTER | MAR_SORT_RANKS>(a.sort, reinterpret_cast<uint32_t*>(smem)); return; }
   float* const aux_all = reinterpret_cast<float*>(smem + 2 * IMG);   // PASS 2: [2][2][TY] log-sum-exp of the tile's edges, log2 units
   float* const nrm_all = aux_all + 4 * TY;                // DIST: [2][TY] squared norms of the tile's rows
 
@@ -1183,8 +1186,12 @@ template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split(FlashArgs a) {
   if constexpr (PASS == 3) split_eval<NK, sp_eval_32(NK, 16 * NK - 8)>();
-  else split_pass<NK, PASS, F16, false>(a);
+  else split_pass<NK, PASS, F16, false, false>(a);
 }
+
+template <int NK, int PASS, bool F16>
+__global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
+k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 
 // The training passes of TransE.  Bound by instruction issue: a pair takes 11 vector instructions and two of a quarter's rate beside
 // its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 46 and 54 us where fp32 matrix instructions
@@ -1193,7 +1200,7 @@ k_split(FlashArgs a) {
 // three times as long as on fp32 operands: their loop is for few.
 template <int NK, int PASS>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
-k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true>(a); }
+k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true, true>(a); }
 
 // The form of pass 3 that the fullest rows of an instantiation take, where it is not that of the others.
 template <int NK>
@@ -1236,6 +1243,9 @@ template <int NK> static hipError_t sp_prepare() {
 #define PREP(P) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_dist<NK, P>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)SplitGeom<NK>::LDS_BYTES_DIST)
   PREP(1); PREP(2);
 #undef PREP
+#define PREP(P, F) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_carry<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
+  PREP(1, true); PREP(2, true); PREP(1, false); PREP(2, false);
+#undef PREP
   return e;
 }
 hipError_t mar_split_prepare(int dk) {
@@ -1262,10 +1272,18 @@ template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool
   }
   else if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
   else if (pass == 1) {
-    if (f16) hipLaunchKernelGGL((k_split<NK, 1, true>), grid, dim3(256), lds, st, a);
+    if (a.carried) {
+      if (f16) hipLaunchKernelGGL((k_split_carry<NK, 1, true>), grid, dim3(256), lds, st, a);
+      else hipLaunchKernelGGL((k_split_carry<NK, 1, false>), grid, dim3(256), lds, st, a);
+    }
+    else if (f16) hipLaunchKernelGGL((k_split<NK, 1, true>), grid, dim3(256), lds, st, a);
     else hipLaunchKernelGGL((k_split<NK, 1, false>), grid, dim3(256), lds, st, a);
   } else {
-    if (f16) hipLaunchKernelGGL((k_split<NK, 2, true>), grid, dim3(256), lds, st, a);
+    if (a.carried) {
+      if (f16) hipLaunchKernelGGL((k_split_carry<NK, 2, true>), grid, dim3(256), lds, st, a);
+      else hipLaunchKernelGGL((k_split_carry<NK, 2, false>), grid, dim3(256), lds, st, a);
+    }
+    else if (f16) hipLaunchKernelGGL((k_split<NK, 2, true>), grid, dim3(256), lds, st, a);
     else hipLaunchKernelGGL((k_split<NK, 2, false>), grid, dim3(256), lds, st, a);
   }
   return hipGetLastError();

@@ -67,7 +67,8 @@ struct SplitGeom {
   static constexpr int PLANE = sp_plane(NK);
   static constexpr int IMG = sp_image(NK);
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
-  static constexpr size_t LDS_BYTES = 2 * (size_t)IMG + 4 * SP_TY * 4;   // two images, and (pass 2) the log-sum-exp of a tile's edges
+  static constexpr size_t LDS_TILES = 2 * (size_t)IMG + 4 * SP_TY * 4;
+  static constexpr size_t LDS_BYTES = LDS_TILES < SORT_LDS_BYTES ? SORT_LDS_BYTES : LDS_TILES;   // two images, and (pass 2) the log-sum-exp of a tile's edges
   static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4;      // TransE: and the squared norms of two tiles' rows
   static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };
