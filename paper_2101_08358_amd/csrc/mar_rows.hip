@@ -432,6 +432,27 @@ __device__ __forceinline__ void chain_complex(float sr, float si, float rr, floa
   gri = sr * uim - si * ure + wre * di - wim * dr - 2.f * (sr * di - si * dr);
 }
 
+// Columns col .. col + 3 of a table row (col a multiple of 4 below dim), zeros from dim on.  Rows of no whole 16 bytes lie at any multiple
+// of 4 bytes, which the memory pipeline takes 16 bytes at a time all the same (the type says so).  A row's last columns are read
+// with those before them and moved down.  (In place of one column a lane and step, each waiting for the last one's loads: the chain rule of
+// 1,000 edges of 50 floats 11 -> 6 us.  In the reduce, which has no such chain, four single loads are faster: 15 against 18.)
+typedef float RowCols __attribute__((ext_vector_type(4), aligned(4)));
+template <bool VEC> __device__ __forceinline__ float4 load_any4(const float* __restrict__ row, int col, int dim) {
+  if (VEC) return *reinterpret_cast<const float4*>(row + col);
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (dim < 4) {                                           // uniform
+    v.x = row[0];
+    if (dim > 1) v.y = row[1];
+    if (dim > 2) v.z = row[2];
+    return v;
+  }
+  const int at = min(col, dim - 4);
+  const RowCols r = *reinterpret_cast<const RowCols*>(row + at);
+  const bool m1 = ((col - at) & 1) != 0, m2 = ((col - at) & 2) != 0;
+  const float x = m1 ? r.y : r.x, y = m1 ? r.z : r.y, z = m1 ? r.w : r.z, w = m1 ? 0.f : r.w;
+  v.x = m2 ? z : x; v.y = m2 ? w : y; v.z = m2 ? 0.f : z; v.w = m2 ? 0.f : w;
+  return v;
+}
 // One group of GL lanes per edge.  VEC (dim % 4 == 0): a lane moves NV float4s per row (for ComplEx NV float2s of
 // the real half and the matching float2s of the imaginary half), every load of the edge is issued before the
 // first use; SY1 > 0: pass 1 was split into exactly SY1 parts (1 for the large batch shapes), SY1 = 0: a.sy1 parts.
@@ -506,14 +527,14 @@ k_chain(RowArgs a, int carried, const float* __restrict__ gQ, const float* __res
           *reinterpret_cast<float2*>(gr + k) = orr; *reinterpret_cast<float2*>(gr + h + k) = ori;
         }
       }
-    } else if (VEC) {
+    } else if (MODEL != MAR_MODEL_COMPLEX) {
       float4 s4[NV], r4[NV], d4[NV], u4[NV], w4[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int k = 4 * (l + GL * v);
         if (k < dim) {
-          s4[v] = *reinterpret_cast<const float4*>(s_row + k); d4[v] = *reinterpret_cast<const float4*>(d_row + k);
-          r4[v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : *reinterpret_cast<const float4*>(r_row + k);
+          s4[v] = load_any4<VEC>(s_row, k, dim); d4[v] = load_any4<VEC>(d_row, k, dim);
+          r4[v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : load_any4<VEC>(r_row, k, dim);
           u4[v] = w4[v] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
           for (int p = 0; p < P; ++p) {
@@ -539,28 +560,19 @@ k_chain(RowArgs a, int carried, const float* __restrict__ gQ, const float* __res
         }
       }
     } else {
-      // any width: one element (ComplEx: one complex element) per lane and step
+      // ComplEx of any width: one complex element per lane and step
       auto merged = [&](const float* base, const float (&f)[MAR_MAX_PARTS], int k) {
         float v = 0.f;
 #pragma unroll
         for (int p = 0; p < P; ++p) if (SY1 || p < sy1) v += f[p] * base[p * pstride + k];
         return v;
       };
-      if (MODEL == MAR_MODEL_COMPLEX) {
-        const int h = dim >> 1;
-        for (int k = l; k < h; k += GL) {
-          chain_complex(s_row[k], s_row[h + k], r_row[k], r_row[h + k], d_row[k], d_row[h + k], merged(gu0, facu, k), merged(gu0, facu, h + k),
-                        merged(gw0, facw, k), merged(gw0, facw, h + k), gs[k], gs[h + k], gd[k], gd[h + k], gr[k], gr[h + k]);
-        }
-      } else {
-        for (int k = l; k < dim; k += GL) {
-          float os, od, og;
-          chain1<MODEL>(s_row[k], MODEL == MAR_MODEL_DOT ? 0.f : r_row[k], d_row[k], merged(gu0, facu, k), merged(gw0, facw, k), inv2, os, od, og);
-          gs[k] = os; gd[k] = od;
-          if (MODEL != MAR_MODEL_DOT) gr[k] = og;
-        }
+      const int h = dim >> 1;
+      for (int k = l; k < h; k += GL) {
+        chain_complex(s_row[k], s_row[h + k], r_row[k], r_row[h + k], d_row[k], d_row[h + k], merged(gu0, facu, k), merged(gu0, facu, h + k),
+                      merged(gw0, facw, k), merged(gw0, facw, h + k), gs[k], gs[h + k], gd[k], gd[h + k], gr[k], gr[h + k]);
       }
-      for (int k = dim + l; k < dk; k += GL) { gs[k] = 0.f; gd[k] = 0.f; if (MODEL != MAR_MODEL_DOT) gr[k] = 0.f; }
+      for (int k = dim + l; k < dk; k += GL) { gs[k] = 0.f; gd[k] = 0.f; gr[k] = 0.f; }
     }
   }
   if (l == 0) lsum[grp] = le;
@@ -670,6 +682,7 @@ struct ReduceArgs {
 __device__ __forceinline__ void add4(float4& a, const float4& b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
 
 // Four consecutive floats of a table row starting at column `col`.  VEC: rows are 16-byte aligned (dim % 4 == 0).
+
 template <bool VEC> __device__ __forceinline__ float4 load_row4(const float* __restrict__ row, int col, int dim) {
   if (VEC) return *reinterpret_cast<const float4*>(row + col);
   float4 v;
