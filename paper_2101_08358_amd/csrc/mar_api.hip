@@ -207,7 +207,11 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   // Few positions per lane group while whole ones would leave CUs without a workgroup of the reduce.  Above that the
   // segments that cross the smaller workgroups' borders cost more than the shorter chains gain (52,000 gradient rows of 75
   // floats: a step 125 -> 116 us; 90,000 of 100: 147 -> 156).
-  d->reduce_small = d->n_pos_max < 256 * 256;
+  // And half as many again while those would: what a task costs beside its rows is then the same (1,000 edges of 50 floats, 11,000
+  // gradient rows in 86 workgroups: the reduce 15 -> 12 us, a step 49 -> 45; 300 edges 70 -> 66); with a workgroup a CU or more it is slower
+  // (55,000 rows of 75 floats 91 -> 98, 21,000 of 148 84 -> 90).
+  d->reduce_small = d->n_pos_max < 256 * 256 ? 8 : 0;
+  if (d->n_pos_max < 256 * (256 / mar_lane_group(d->dk) * 8)) d->reduce_small = 4;
   // Sort keys are unified ids: as few passes as digits of at most MAR_SORT_MAX_BITS bits allow.
   int nbits = 1;
   while (((int64_t)1 << nbits) < ids) ++nbits;

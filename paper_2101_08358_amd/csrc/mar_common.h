@@ -69,7 +69,7 @@ struct MarDims {
   int32_t sort_passes, sort_bits, sort_items;  // radix sort of the gradient rows by unified id: passes, bits per pass, elements per thread
   int32_t bilinear;                // DistMult, ComplEx, Dot: the passes of mar_split.hip; TransE: those of mar_flash.hip
   int32_t dist_img;                // TransE whose training passes are those of mar_split.hip too (mar_dist_images)
-  int32_t reduce_small;            // the reduce gives a lane group MAR_REDUCE_SMALL positions instead of one per lane
+  int32_t reduce_small;            // positions that the reduce gives a lane group (8, or 4 in the smallest batches); 0: one per lane
   int32_t split_bf16;              // training passes on bf16 hi + lo operands (precision SPLIT_BF16)
   int32_t sort_one;                // most gradient rows that one workgroup sorts by itself
   int32_t long_passes;             // a contraction pass takes some 25 us or more
@@ -114,13 +114,11 @@ static inline int32_t mar_sort_one_limit(int dk, bool alone) { return alone || d
 #define MAR_METRIC_MAX_PARTS 4096
 #define MAR_METRIC_PART_BYTES 72
 
-// Positions of the row-sorted order per lane group of the reduce in small batches (in large ones: as many as it has lanes),
-// and per workgroup.
-#define MAR_REDUCE_SMALL 8
 
 // Lanes that move one table row as float4s.
 static inline int mar_lane_group(int dk) { return dk <= 64 ? 16 : (dk <= 128 ? 32 : 64); }
-static inline int mar_reduce_block(const MarDims& d) { return d.reduce_small ? 256 / mar_lane_group(d.dk) * MAR_REDUCE_SMALL : 256; }
+// Positions of the row-sorted order per workgroup of the reduce.
+static inline int mar_reduce_block(const MarDims& d) { return d.reduce_small ? 256 / mar_lane_group(d.dk) * d.reduce_small : 256; }
 
 // Occurrences of a batch (mar_sort_dev.h).
 struct OccArgs {

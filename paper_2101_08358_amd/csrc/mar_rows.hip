@@ -736,7 +736,7 @@ __device__ __forceinline__ void load_old4(const ReduceArgs& a, int32_t id, const
 
 // A workgroup takes 256 / GL tasks of PPT consecutive positions, one per group of GL lanes (the lanes of a group move one
 // row as float4s, NV per lane).  PPT = GL (256 positions per workgroup) for large batches, which are bound by memory;
-// MAR_REDUCE_SMALL = BATCH or twice that for small ones, which are bound by the latency of the batches a group works
+// 8 or 4 (BATCH or twice that) for small ones, which are bound by the latency of the batches a group works
 // through one after the other and of too few workgroups.  Each lane first fetches the id and the gradient row of one
 // position of its task, and the group the ids on either side of it: equal neighbours are one segment, so the segments'
 // borders follow without further loads and no later load depends on another.
@@ -1247,7 +1247,8 @@ hipError_t mar_launch_reduce(const mar_ctx* c, const MarBatch& b, float* loss_ou
 #define RED2(GLV, NVV, BT, P) do { \
     if (vec) hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, true, P>), grid, blk, 0, st, a); \
     else hipLaunchKernelGGL((k_reduce_apply<GLV, NVV, BT, false, P>), grid, blk, 0, st, a); } while (0)
-#define RED(GLV, NVV, BT) do { if (d.reduce_small) RED2(GLV, NVV, BT, MAR_REDUCE_SMALL); else RED2(GLV, NVV, BT, GLV); } while (0)
+#define RED(GLV, NVV, BT) do { \
+    if (d.reduce_small == 4) RED2(GLV, NVV, 4, 4); else if (d.reduce_small) RED2(GLV, NVV, BT, 8); else RED2(GLV, NVV, BT, GLV); } while (0)
   if (GL == 16) RED(16, 1, 8); else if (GL == 32) RED(32, 1, 8); else if (d.dk <= 256) RED(64, 1, 8); else RED(64, 2, 4);
 #undef RED
 #undef RED2
