@@ -120,14 +120,15 @@ static void plan_rem(const MarDims& d, int pass, long units, int n_y, int sy, in
 // matrix instructions (k_flash, PASS 4), whose gather writes no images and whose two kernels are a third of the code to be
 // fetched.  What the images cost goes with a chunk's rows, S edges and N candidates, what the faster products save with
 // its S N pairs, so the line is one of S N / (S + N); and where all pairs together are few, latency decides.  fp32 / images,
-// us, 50, 100 and 400 floats: 20 x 400 edges, 100 candidates 12 / 19, 16 / 23, 43 / 40; 100 x 100, 300: 23 / 30, 32 / 36,
-// 112 / 111; 20 x 400, 400 (on the line) 20 / 23, 32 / 29, 93 / 66; 100 x 300, 600 (on the line) 54 / 53, 89 / 78, 363 / 309;
-// 20 x 500, 500: 23 / 25, 34 / 31, 106 / 76; 4 x 1,000, 600: 13 / 19, 18 / 21, 47 / 36; 100 x 1,000, 1,000: 216 / 144, 373 / 231,
-// 1,603 / 912.  The line was drawn with slower image kernels over all widths at once (mean then 2.4 % off the better of the two):
-// above 128 floats it now lies too far towards fp32, below 100 too near for few chunks.  Ranks are the same bits either way.
+// us, 50 and 100 floats: 20 x 400 edges, 100 candidates 12 / 19, 16 / 23; 20 x 400, 400 (on the line) 20 / 23, 32 / 29; 100 x 300, 600
+// (on the line) 54 / 53, 89 / 78; 4 x 1,000, 600: 13 / 19, 18 / 21; 100 x 1,000, 1,000: 216 / 144, 373 / 231; 28 x 370, 213 of 78
+// floats 34 / 38.  Above 128 floats products cost more and the line lies nearer: 512 edges, 4 chunks, all 12,326 nodes of 374 floats
+// 247 / 132; 15,500, 77, 515 of 262 223 / 180; 768, 4, all 7,371 of 244 119 / 87; 290, 1, all 4,137 of 185 (1.2e6 pairs) 59 / 34; 11,800, 18,
+// 132 of 240 (S N / (S + N) = 110) 48 / 44; 33,000, 43, 112 of 279 (98) 115 / 119.  Ranks are the same bits either way.
 bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
   const double S = b.n < d.S ? b.n : d.S, N = d.N;
-  return d.bilinear && (S * N <= 200.0 * (S + N) || (double)b.n * N <= 2.0e6);
+  const bool wide = d.dk > 128;
+  return d.bilinear && (S * N <= (wide ? 100.0 : 200.0) * (S + N) || (double)b.n * N <= (wide ? 1.1e6 : 2.0e6));
 }
 
 // Training passes of TransE: on images and 16-bit products (k_split_dist), or on dense fp32 operands with stored weights (k_flash,
