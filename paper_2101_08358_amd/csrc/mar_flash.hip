@@ -17,7 +17,8 @@
 // per HBM byte on this chip while recomputing a score costs 2d flops, so k_flash_bwd reads them
 // back, scales them by exp(reference - lse) and runs only the second product, with the roles of Q
 // and K swapped.  Evaluation only counts negatives scoring above the positive: PASS 3 for TransE, PASS 4 for small
-// evaluations of the bilinear models, whose training runs in mar_split.hip.  TransE uses |q - n|^2 = |q|^2 + |n|^2 - 2 q.n for the scores (pairs for which that expansion
+// evaluations of the bilinear models, whose training runs in mar_split.hip, as TransE's does from 2e8 pairs x columns a batch up
+// (mar_dist_images).  TransE uses |q - n|^2 = |q|^2 + |n|^2 - 2 q.n for the scores (pairs for which that expansion
 // cancels are recomputed from the differences) and W = P / distance.
 #include <type_traits>
 

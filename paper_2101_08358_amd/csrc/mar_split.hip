@@ -1,5 +1,5 @@
 // Contraction passes of the bilinear models (DistMult, ComplEx, Dot) on the 16-bit matrix pipe (gfx950): scores with
-// online softmax and the edge-side gradient, the negatives' gradient, and rank counts.
+// online softmax and the edge-side gradient, the negatives' gradient, and rank counts; and TransE's training passes (k_split_dist).
 //
 // fp32 precision (F16 = true).  Every operand value is written as v 2^e = hi + lo, both f16 (mar_split.h; one exponent
 // per 16 rows puts the largest value just below 2^15), and every product a b is taken as
@@ -1193,11 +1193,11 @@ template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 
-// The training passes of TransE.  Bound by instruction issue: a pair takes 11 vector instructions and two of a quarter's rate beside
-// its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 46 and 54 us where fp32 matrix instructions
+// The training passes of TransE.  Bound by instruction issue: a pair takes 14 vector instructions and two of a quarter's rate beside
+// its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 48 and 58 us where fp32 matrix instructions
 // with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits are those of fp32 instructions or half of
-// them (gradients 2e-7 against 3e-7, close pairs 1e-3 apart 3e-5 against 8e-5).  Tables in which most pairs are near (values of 5 +- 0.3) take
-// three times as long as on fp32 operands: their loop is for few.
+// them (node gradients 2e-7 against 3e-7, pairs 1e-3 apart 3e-5 against 8e-5).  Tables in which nearly all pairs are near (values of 5 +- 0.3)
+// take 2.4 times as long a step as on fp32 operands (1,412 us, 589): the loop over near pairs is for few.
 template <int NK, int PASS>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true, true>(a); }
