@@ -707,6 +707,9 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   const size_t xtile = (size_t)cs * a.ximg_tiles + u.stripe * (SP_SR / TY) + wave_s;
   const int swz = 16 * sp_swizzle(UNITS, i);              // of rows i and 16 + i of a tile, in bytes
   const v8s zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  // DIST, widest rows: the fragments of the last XL steps lie in LDS, each lane's own (its registers would spill; 400 floats: 351 of them)
+  constexpr int XL = DIST ? sp_dist_lds_steps(NK) : 0;
+  char* const xlds = smem + SG::LDS_BYTES + 2 * TY * 4 + threadIdx.x * 16;   // [4 XL][256] 16-byte units
   v8s xh[2][NS], xl[2][NS], xt[2][2];
   // Tail: 16 columns more as one or two steps of 32 slots.  At most 8 of them: lane groups 0, 1, 2 hold the first 8
   // columns of hi * hi, lo * hi and hi * lo.  Else groups 0, 1 / 2, 3 hold both halves of hi * hi and lo * hi, and a second step hi * lo.
@@ -723,6 +726,11 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       if (xv[b]) {
         xh[b][s] = *reinterpret_cast<const v8s*>(xrow + ((64 * s + 16 * g) ^ swz));
         xl[b][s] = *reinterpret_cast<const v8s*>(xrow + PLANE + ((64 * s + 16 * g) ^ swz));
+      }
+      if (s >= NS - XL) {
+        char* const p = xlds + (4 * (s - (NS - XL)) + 2 * b) * 4096;
+        *reinterpret_cast<v8s*>(p) = xh[b][s];
+        *reinterpret_cast<v8s*>(p + 4096) = xl[b][s];
       }
     }
     xt[b][0] = xt[b][1] = zero8;
@@ -840,7 +848,13 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       for (int s = 0; s < NS; ++s) {
         const v8s h0 = fh[s % PD][0], h1 = fh[s % PD][1], l0 = fl[s % PD][0], l1 = fl[s % PD][1];
         if (s + PD < NS) read_step(s + PD, fh[s % PD], fl[s % PD]);
-        sp_score_step<F16>(h0, h1, l0, l1, xh[0][s], xh[1][s], xl[0][s], xl[1][s], sc);
+        if (s >= NS - XL) {
+          const char* const p = xlds + 4 * (s - (NS - XL)) * 4096;
+          sp_score_step<F16>(h0, h1, l0, l1, *reinterpret_cast<const v8s*>(p), *reinterpret_cast<const v8s*>(p + 2 * 4096),
+                             *reinterpret_cast<const v8s*>(p + 4096), *reinterpret_cast<const v8s*>(p + 3 * 4096), sc);
+        } else {
+          sp_score_step<F16>(h0, h1, l0, l1, xh[0][s], xh[1][s], xl[0][s], xl[1][s], sc);
+        }
         // the next tile's pieces are issued between the steps: a burst of them holds the wave at the memory pipeline's
         // queue (rows of 400: a pass 1075 us with the copies at the tile's start, 915 spread, 810 without any)
         if (has_next) {
@@ -860,6 +874,12 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       }
     }
     const float ef[2] = {(float)e0, (float)e1};
+    // image row of row `row` of the wave (there is one only where xv says so); formed anew from the arguments, as DistRow is
+    auto dist_image_row = [&](int row) {
+      KernelArgs* args = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(args), "+v"(row));
+      return args->ximg + ((size_t)u.cs * args->ximg_tiles + u.stripe * (SP_SR / TY) + wave_s) * IMG + row * PA;
+    };
     // -- weights of the lane's 2 x 8 pairs: w[b][4 ah + r] is row 16 ah + 4 g + r against column 16 b + i
     float w[2][8];
     if constexpr (DIST) {
@@ -868,7 +888,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
         // squared distances; near: the expansion is left with fewer than 14 good bits (or is no number)
         float d2[8];
         bool near = false;
-        const auto is_near = [&](int v, float yn) { return !(d2[v] > 0.00390625f * (xn[b] + yn)); };
+        const auto is_near = [&](int v, float yn) { return xv[b] && !(d2[v] > 0.00390625f * (xn[b] + yn)); };
         const float4 yn4[2] = {*reinterpret_cast<const float4*>(nrm_all + buf * TY + 4 * g), *reinterpret_cast<const float4*>(nrm_all + buf * TY + 16 + 4 * g)};
         const float yn[8] = {yn4[0].x, yn4[0].y, yn4[0].z, yn4[0].w, yn4[1].x, yn4[1].y, yn4[1].z, yn4[1].w};
         const float k2[2] = {-__builtin_ldexpf(1.f, 1 - ex[b] - e0), -__builtin_ldexpf(1.f, 1 - ex[b] - e1)};
@@ -892,9 +912,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
             const char* const yp = smem + bofs + at_row * PA;
             const int ysw = 16 * sp_swizzle(UNITS, at_row);
             float part = 0.f;
-            auto add_unit = [&](v8s ah, v8s al, int byte) {
-              asm volatile("" : "+v"(ah), "+v"(al));         // or their conversions are moved out of the loop, into registers that there are not
-              const v8h x0h = __builtin_bit_cast(v8h, ah), x0l = __builtin_bit_cast(v8h, al);
+            auto add_unit = [&](const v8h& x0h, const v8h& x0l, int byte) {
               const v8h y0h = *reinterpret_cast<const v8h*>(yp + (byte ^ ysw)), y0l = *reinterpret_cast<const v8h*>(yp + PLANE + (byte ^ ysw));
 #pragma unroll
               for (int j = 0; j < 8; ++j) {
@@ -904,13 +922,23 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
                 part = __builtin_fmaf(d, d, part);
               }
             };
+            const char* const xp = dist_image_row(16 * b + i);
+            auto add_image = [&](int byte) { add_unit(*reinterpret_cast<const v8h*>(xp + (byte ^ swz)), *reinterpret_cast<const v8h*>(xp + PLANE + (byte ^ swz)), byte); };
+            if (XL > 0) {                                  // registers are full: all columns from the row's image
+              if (left) {
+#pragma unroll 1
+                for (int s = 0; s < NS; ++s) add_image(64 * s + 16 * g);
+              }
+            } else {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) { add_unit(xh[b][s], xl[b][s], 64 * s + 16 * g); if (s % 2) __builtin_amdgcn_sched_barrier(0); }
-            if (TAIL) {
-              // the 16 columns behind: units 0 and 1 lie with lane groups 0 and (more than 8 columns) 1; groups 0, 1 / group 2 hold the lo part
-              const v8s tl = tail2 ? xt[b][1] : __builtin_bit_cast(v8s, sp_shfl16(__builtin_bit_cast(v4i, xt[b][0]), 32 + i));
-              if (g < (tail2 ? 2 : 1)) add_unit(xt[b][0], tl, 64 * NS + 16 * g);
+              for (int s = 0; s < NS; ++s) {
+                v8s ah = xh[b][s], al = xl[b][s];
+                asm volatile("" : "+v"(ah), "+v"(al));     // or their conversions are moved out of the loop, into registers that there are not
+                add_unit(__builtin_bit_cast(v8h, ah), __builtin_bit_cast(v8h, al), 64 * s + 16 * g);
+                if (s % 2) __builtin_amdgcn_sched_barrier(0);
+              }
             }
+            if (TAIL && left && g < 2) add_image(64 * NS + 16 * g);   // the 16 columns behind: units 0 and 1 (zeros from dk on)
             part += __shfl_xor(part, 16);
             part = __builtin_ldexpf(part + __shfl_xor(part, 32), -2 * ey);
             // closer than hi + lo of the two rows can tell (2^-20 of the norm): by the rows themselves, so that rows that are
@@ -1160,20 +1188,22 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       ws = wsum[b] + __shfl_xor(wsum[b], 16);
       ws += __shfl_xor(ws, 32);
     }
+    int go = g;
+    if (DIST) asm volatile("" : "+v"(go));                 // the rows' columns are not kept across the tiles either
     if (xv[b]) {
       if constexpr (DIST) {
         const DistRow<PASS == 1> row(u.cs, x, g);
 #pragma unroll
         for (int cb = 0; cb < NO; ++cb) {
-          const float4 xs = row.cols(16 * cb + 4 * g);
+          const float4 xs = row.cols(16 * cb + 4 * go);
           oacc[cb][b] -= (v4f){xs.x * ws, xs.y * ws, xs.z * ws, xs.w * ws};
           if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few blocks' loads at a time: registers are full
         }
       }
 #pragma unroll
       for (int cb = 0; cb < NO; ++cb) {
-        const int col = 16 * cb + 4 * g;
-        if (col < dk && (cb < NO - 1 || !pack || g < 2))
+        const int col = 16 * cb + 4 * go;
+        if (col < dk && (cb < NO - 1 || !pack || go < 2))
           *reinterpret_cast<float4*>(orow + col) =
               make_float4(__builtin_ldexpf(oacc[cb][b][0], oshift), __builtin_ldexpf(oacc[cb][b][1], oshift),
                           __builtin_ldexpf(oacc[cb][b][2], oshift), __builtin_ldexpf(oacc[cb][b][3], oshift));
@@ -1198,9 +1228,11 @@ k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 // with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits are those of fp32 instructions or half of
 // them (node gradients 2e-7 against 3e-7, pairs 1e-3 apart 3e-5 against 8e-5).  Tables in which nearly all pairs are near (values of 5 +- 0.3)
 // take 2.4 times as long a step as on fp32 operands (1,412 us, 589): the loop over near pairs is for few.
-template <int NK, int PASS>
+// Registers decide: nothing may spill (a step of 10,000 edges, 1,000 negatives of 400 floats 585 us with 351 registers spilled, 503 with
+// three steps' fragments in LDS and the near loop on the row's image; 50,000 edges 2,390 and 1,847).
+template <int NK, int PASS, bool CARRY>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
-k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true, true>(a); }
+k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true, CARRY>(a); }
 
 // The form of pass 3 that the fullest rows of an instantiation take, where it is not that of the others.
 template <int NK>
@@ -1240,8 +1272,8 @@ template <int NK> static hipError_t sp_prepare() {
 #define PREP(P, F) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(P == 3 ? SplitGeom<NK>::LDS_BYTES3 : lds))
   PREP(1, true); PREP(2, true); PREP(3, true); PREP(1, false); PREP(2, false);
 #undef PREP
-#define PREP(P) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_dist<NK, P>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)SplitGeom<NK>::LDS_BYTES_DIST)
-  PREP(1); PREP(2);
+#define PREP(P, C) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_dist<NK, P, C>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)SplitGeom<NK>::LDS_BYTES_DIST)
+  PREP(1, false); PREP(2, false); PREP(1, true); PREP(2, true);
 #undef PREP
 #define PREP(P, F) if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_split_carry<NK, P, F>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
   PREP(1, true); PREP(2, true); PREP(1, false); PREP(2, false);
@@ -1267,8 +1299,12 @@ template <int NK> static hipError_t sp_launch(const FlashArgs& a, int pass, bool
     }
   }
   if (a.dist) {
-    if (pass == 1) hipLaunchKernelGGL((k_split_dist<NK, 1>), grid, dim3(256), ldsd, st, a);
-    else hipLaunchKernelGGL((k_split_dist<NK, 2>), grid, dim3(256), ldsd, st, a);
+    if (pass == 1) {
+      if (a.carried) hipLaunchKernelGGL((k_split_dist<NK, 1, true>), grid, dim3(256), ldsd, st, a);
+      else hipLaunchKernelGGL((k_split_dist<NK, 1, false>), grid, dim3(256), ldsd, st, a);
+    }
+    else if (a.carried) hipLaunchKernelGGL((k_split_dist<NK, 2, true>), grid, dim3(256), ldsd, st, a);
+    else hipLaunchKernelGGL((k_split_dist<NK, 2, false>), grid, dim3(256), ldsd, st, a);
   }
   else if (pass == 3) hipLaunchKernelGGL((k_split<NK, 3, true>), grid, dim3(256), SplitGeom<NK>::LDS_BYTES3, st, a);
   else if (pass == 1) {

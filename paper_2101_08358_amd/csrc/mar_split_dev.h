@@ -53,13 +53,11 @@ __device__ __forceinline__ v4s lds_read_tr(const char* p) {
 }
 __device__ __forceinline__ v8s join8(v4s a, v4s b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
 
-// The 16 bytes that lane `from` holds.
-__device__ __forceinline__ v4i sp_shfl16(v4i v, int from) {
-  return (v4i){__shfl(v[0], from), __shfl(v[1], from), __shfl(v[2], from), __shfl(v[3], from)};
-}
-
 #define SP_PEND 6                                          // candidates whose comparisons a lane of pass 3 keeps for the end (5 bits of a word each)
 #define SP_FULL 8                                          // added to their number: this lane takes no more (above SP_PEND)
+// Steps of 32 columns whose stationary fragments TransE's passes keep in LDS: 400 floats' sums and fragments leave too few registers
+// for the weights (all in registers 62 and 73 spilled; one step in LDS 14 and 41, two 0 and 13).
+constexpr int sp_dist_lds_steps(int nk) { return nk > 16 ? 3 : 0; }
 template <int NK>
 struct SplitGeom {
   static constexpr int UNITS = sp_units(NK);
@@ -69,6 +67,6 @@ struct SplitGeom {
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
   static constexpr size_t LDS_TILES = 2 * (size_t)IMG + 4 * SP_TY * 4;
   static constexpr size_t LDS_BYTES = LDS_TILES < SORT_LDS_BYTES ? SORT_LDS_BYTES : LDS_TILES;   // two images, and (pass 2) the log-sum-exp of a tile's edges
-  static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4;      // TransE: and the squared norms of two tiles' rows
+  static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4 + (size_t)sp_dist_lds_steps(NK) * 4 * 4096;   // TransE: and the squared norms of two tiles' rows, stationary fragments
   static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };
