@@ -271,6 +271,7 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   const size_t ktiles = 2 * (size_t)d.C * (size_t)((d.N + 31) / 32), qtiles = 2 * (size_t)d.C * (size_t)((d.S + 31) / 32);
   l.Kimg = (char*)take(img ? ktiles * mar_split_image_bytes(d.dk) : 0);
   l.Qimg = (char*)take(img ? qtiles * mar_split_image_bytes(d.dk) : 0);
+  l.shift = (float*)take(d.dist_img ? 512 * 4 : 0);
   l.Gx = (float*)take((size_t)(d.rem2.k - 1) * (size_t)d.rem2.rows * dk * 4);
   const size_t eval_floats = bl ? ktiles * (2 + 2 + MAR_SPLIT_TILE_ROWS) + qtiles * 2 : 0;
   l.G = (float*)take((n_pos * dk > eval_floats ? n_pos * dk : eval_floats) * 4);

@@ -39,6 +39,7 @@ struct MarLayout {
   float*    Kexp;         // exponents of the images' 16-row blocks, [2*chunks][2 * image tiles]
   float*    Qexp;
   float*    Knorm;        // evaluation: bounds of the norms of Kimg's scaled rows, per 16-row block and per row
+  float*    shift;        // TransE on images: [512] what k_prep takes off every operand
   float*    Gx;           // [rem2.k - 1][rem2.rows][dk] parts 1.. of pass 2's split stripes (bilinear models)
   float*    G;            // [roles*n + 2*cn*sy2][dk] gradient rows: edge-side occurrence k < roles*n at row k, part i
                           // of negative occurrence k at row roles*n + (k - roles*n)*sy2 + i

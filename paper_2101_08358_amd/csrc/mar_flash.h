@@ -46,6 +46,7 @@ struct FlashArgs {
   // evaluation on images, where share > 0: workgroup p takes `share` tiles of the units' tiles, one more if p < share_rest
   int64_t share; int32_t share_rest;
   MarSortJob sort;     // training passes: carried along by the first `carried` workgroups
+  const float* shift;  // TransE on images: [16 NK] what the operands on images have lost
   const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
 

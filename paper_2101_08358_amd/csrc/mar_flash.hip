@@ -919,6 +919,7 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   const bool f16 = !d.split_bf16 || pass == 3;             // evaluation always runs at fp32 precision
   a.yimg = pass == 2 ? L.Qimg : L.Kimg; a.yexp = pass == 2 ? L.Qexp : L.Kexp; a.yimg_tiles = ((pass == 2 ? d.S : d.N) + 31) / 32;
   a.ximg = pass == 2 ? L.Kimg : L.Qimg; a.xexp = pass == 2 ? L.Kexp : L.Qexp; a.ximg_tiles = ((pass == 2 ? d.N : d.S) + 31) / 32;
+  a.shift = L.shift;
   a.qrows = a.dist ? L.Q : L.gQ; a.ynorm = L.Knorm; a.table = c->node_emb; a.neg_dst = b.neg_dst; a.neg_src = b.neg_src; a.src = b.src; a.dst = b.dst; a.dim = d.dim;
   a.sr = mar_stripe_rows(d, pass);
   a.nstripes = (max_nx + a.sr - 1) / a.sr;

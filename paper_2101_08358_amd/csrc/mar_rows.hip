@@ -17,6 +17,7 @@ struct RowArgs {
   int32_t sy1, sy2;      // parts per stripe in the two contraction passes
   int32_t roles;         // 3, or 2 for the relation-free Dot score
   float ml_log2;         // natural-log units of one unit of the softmax references (see FlashArgs)
+  float* shift;          // TransE on images: what all rows of the batch have in common (batch_shift), for the passes
 };
 
 template <int GL> __device__ __forceinline__ float group_sum(float v) {
@@ -150,6 +151,27 @@ __device__ __forceinline__ void store_dense_row(float* row, const float4 (&v)[NV
                               [&](int k, const float4& x) { *reinterpret_cast<float4*>(row + k) = x; });
 }
 
+// TransE on images: a vector that k_prep takes off every operand, which leaves all distances as they are.  Per column the mean of eight of
+// the batch's negatives where they are of one sign and within a factor of 4 of one another, else 0 (columns drawn around 0: one in
+// some 500 is taken for more by chance; it then grows by less than it varies).  Rows that share an offset are closer to one another
+// than to 0: |x|^2 + |y|^2 - 2 x.y cancels, and nearly all pairs are near ones.  10,000 edges, 1,000 negatives of 100 floats, values of
+// 5 +- 0.3: a step 568 us without, 154 with (fp32 instructions: 325; 0 +- 0.3: 157 and 159); 400 floats, 1 +- 0.2: relation gradients
+// 3.4e-6 off without, 1.0e-6 with (fp32 instructions on the rows as they are: 1.5e-6), which is what rounding s + r to fp32 takes.
+constexpr int SHIFT_ROWS = 8;
+__device__ __forceinline__ float common_offset(const float (&v)[SHIFT_ROWS]) {
+  float sum = v[0], lo = v[0], hi = v[0];
+#pragma unroll
+  for (int j = 1; j < SHIFT_ROWS; ++j) { sum += v[j]; lo = fminf(lo, v[j]); hi = fmaxf(hi, v[j]); }
+  const bool close = (lo > 0.f && hi <= 4.f * lo) || (hi < 0.f && lo >= 4.f * hi);
+  return close && fabsf(sum) <= 1e37f ? sum * (1.f / SHIFT_ROWS) : 0.f;   // (a NaN among them: 0)
+}
+// Row j of the eight: of either side, spread over the chunks and, from the last on, over a chunk's negatives (the first ones may be
+// drawn by degree).
+__device__ __forceinline__ const float* shift_row(const RowArgs& a, int j) {
+  const size_t at = (size_t)(j * (int64_t)(a.cn / a.N) / SHIFT_ROWS) * a.N + (a.N - 1 - (int)(j * (int64_t)a.N / SHIFT_ROWS));
+  return a.node_emb + (size_t)(j & 1 ? a.neg_src : a.neg_dst)[at] * a.dim;
+}
+
 // Rows per lane group: edges, negatives.
 constexpr int prep_edges(int gl, bool img) { return img && gl == 64 ? 4 : 2; }
 constexpr int PREP_NEGS = 4;
@@ -181,6 +203,44 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
   }
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int dim = a.dim, dk = a.dk;
+  // The rows of the shift: fetched by a lane group or two each, exchanged through LDS behind the loads of the workgroup's own rows
+  constexpr bool SHIFT = MODEL == MAR_MODEL_TRANSE && IMG;
+  constexpr int SPG = (SHIFT_ROWS + GPB - 1) / GPB;
+  __shared__ float4 s_rows[SHIFT ? SHIFT_ROWS : 1][NV][GL];
+  float4 sample[SPG][NV], shift[NV];
+  if constexpr (SHIFT) {
+#pragma unroll
+    for (int k = 0; k < SPG; ++k) {
+      if (grp * SPG + k < SHIFT_ROWS) {
+        const float* row = shift_row(a, grp * SPG + k);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sample[k][v] = load_cols<GL, VEC, false>(row, l, v, dim);
+      }
+    }
+  }
+  auto take_shift = [&]() {
+    if constexpr (SHIFT) {
+#pragma unroll
+      for (int k = 0; k < SPG; ++k) {
+        if (grp * SPG + k < SHIFT_ROWS) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) s_rows[grp * SPG + k][v][l] = sample[k][v];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        float c[4][SHIFT_ROWS];
+#pragma unroll
+        for (int j = 0; j < SHIFT_ROWS; ++j) { const float4 x = s_rows[j][v][l]; c[0][j] = x.x; c[1][j] = x.y; c[2][j] = x.z; c[3][j] = x.w; }
+        shift[v] = make_float4(common_offset(c[0]), common_offset(c[1]), common_offset(c[2]), common_offset(c[3]));
+      }
+      if (block == 0 && grp == 0) {
+        store_dense_row<GL, NV, VEC, false>(a.shift, shift, l, dim, dk);
+        for (int k = dk + l; k < qi.dkp; k += GL) a.shift[k] = 0.f;
+      }
+    }
+  };
   // exponent of the 16-row block of workgroup row `rw` (two operands: which), after all groups have put in their maxima
   auto put_max = [&](int which, int rw, float mx, bool bad) {
     mx = group_max<GL>(mx);
@@ -214,10 +274,12 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
         r[j][v] = MODEL == MAR_MODEL_DOT ? make_float4(0.f, 0.f, 0.f, 0.f) : load_cols<GL, VEC, CPLX>(r_row[j], l, v, dim);
       }
     }
+    take_shift();
     float mxu = 0.f, mxw = 0.f;
     bool badu = false, badw = false;
 #pragma unroll
     for (int j = 0; j < E; ++j) {
+      float4 qu[NV], qw[NV];
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const float4 S = s[j][v], R = r[j][v], D = d[j][v];
@@ -230,6 +292,10 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
         if (MODEL == MAR_MODEL_TRANSE) {
           const float4 df = sub4(U, D);
           add_dot<VEC, false>(acc[j], df, df);
+          if constexpr (SHIFT) {                           // the rows as they are: for near pairs and the passes' ends
+            qu[v] = U; qw[v] = W;
+            U = sub4(U, shift[v]); W = sub4(W, shift[v]);
+          }
           add_dot<VEC, false>(nd[j], U, U);
           add_dot<VEC, false>(ns[j], W, W);
         } else {
@@ -239,6 +305,12 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
         if (IMG && F16 && r0 + j < nr) {
           mxu = finite_max4(mxu, U); mxw = finite_max4(mxw, W);
           badu |= !finite4(U); badw |= !finite4(W);
+        }
+      }
+      if constexpr (SHIFT) {
+        if (r0 + j < nr) {
+          store_dense_row<GL, NV, VEC, false>(Q + ((size_t)MAR_SIDE_DST * a.B + eb + r0 + j) * dk, qu, l, dim, dk);
+          store_dense_row<GL, NV, VEC, false>(Q + ((size_t)MAR_SIDE_SRC * a.B + eb + r0 + j) * dk, qw, l, dim, dk);
         }
       }
     }
@@ -271,7 +343,7 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
           store_image_row<GL, NV, VEC, CPLX, F16>(qi, sp_row(qi, 2 * chunk + MAR_SIDE_SRC, row), w[j], scw, l, dim);
         }
       }
-      if (valid && (!IMG || Q)) {                            // dense; evaluation
+      if (!SHIFT && valid && (!IMG || Q)) {                  // dense; evaluation
         store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_DST * a.B + e) * dk, u[j], l, dim, dk);
         store_dense_row<GL, NV, VEC, CPLX>(Q + ((size_t)MAR_SIDE_SRC * a.B + e) * dk, w[j], l, dim, dk);
       }
@@ -309,6 +381,14 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         x[j][v] = load_cols<GL, VEC, false>(row, l, v, dim);
+      }
+    }
+    if constexpr (SHIFT) {
+      take_shift();
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) x[j][v] = sub4(x[j][v], shift[v]);
       }
     }
     float scale = 1.f;
@@ -1124,7 +1204,7 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
   a.src = b.src; a.rel = b.rel; a.dst = b.dst; a.neg_src = b.neg_src; a.neg_dst = b.neg_dst;
   a.n = b.n; a.cn = b.cn; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.dim = d.dim; a.dk = d.dk; a.model = c->cfg.model;
   a.n_occ = b.n_occ; a.num_nodes = (int32_t)d.num_nodes;
-  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = mar_on_images(d) ? MAR_LN2 : 1.f;
+  a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = mar_on_images(d) ? MAR_LN2 : 1.f; a.shift = c->L.shift;
   return a;
 }
 

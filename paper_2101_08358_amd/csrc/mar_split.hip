@@ -653,17 +653,23 @@ __device__ __forceinline__ float dist_norm(float n2) { return n2 < 1e37f ? n2 : 
 // arguments that the compiler cannot see through: what the addresses take would otherwise be kept across the tiles.
 template <bool EDGE> struct DistRow {
   const float* row;
+  const float* shift;
   int left;
-  __device__ __forceinline__ DistRow(int cs, int x, int g) {
+  __device__ __forceinline__ DistRow(int cs, int x) {
     KernelArgs* args = (KernelArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(args), "+v"(g));
+    asm volatile("" : "+s"(args));
     KernelArgs& a = *args;
     const int side = cs & 1, c = cs >> 1;
     if (EDGE) row = a.qrows + ((size_t)side * a.B + (size_t)c * a.S + x) * a.dk;
     else row = a.table + (size_t)((side == MAR_SIDE_DST ? a.neg_dst : a.neg_src) + (size_t)c * a.N)[x] * a.dim;
     left = EDGE ? a.dk : a.dim;
+    shift = a.shift;
   }
   __device__ __forceinline__ float4 cols(int k) const { return sp_row_cols<EDGE>(row, k, left); }
+  __device__ __forceinline__ float4 shifted(int k) const { // as the images have it (k below 16 NK)
+    const float4 v = cols(k), m = *reinterpret_cast<const float4*>(shift + k);
+    return make_float4(v.x - m.x, v.y - m.y, v.z - m.z, v.w - m.w);
+  }
 };
 
 // DIST (TransE): the score is -|x - y|, its square expanded as |x|^2 + |y|^2 - 2 x.y with the norms in fp32.  Pairs for which the
@@ -947,8 +953,8 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
             const bool same = left && !(part > 0x1p-40f * both);
             if (__builtin_expect(__any(same), 0)) {
               const int xr = min(x0 + 16 * b + i, n_x - 1), yr = min(y0 + at_row, n_y - 1);
-              const DistRow<true> q(u.cs, PASS == 1 ? xr : yr, g);
-              const DistRow<false> n(u.cs, PASS == 1 ? yr : xr, g);
+              const DistRow<true> q(u.cs, PASS == 1 ? xr : yr);
+              const DistRow<false> n(u.cs, PASS == 1 ? yr : xr);
               float exact = 0.f;
 #pragma unroll 1
               for (int k = 4 * g; k < dk; k += 16) {
@@ -1189,13 +1195,16 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       ws += __shfl_xor(ws, 32);
     }
     int go = g;
-    if (DIST) asm volatile("" : "+v"(go));                 // the rows' columns are not kept across the tiles either
+    if (DIST) {                                            // formed anew: nor are the rows' columns to be kept across the tiles
+      go = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 4;
+      asm volatile("" : "+v"(go));
+    }
     if (xv[b]) {
       if constexpr (DIST) {
-        const DistRow<PASS == 1> row(u.cs, x, g);
+        const DistRow<PASS == 1> row(u.cs, x);
 #pragma unroll
         for (int cb = 0; cb < NO; ++cb) {
-          const float4 xs = row.cols(16 * cb + 4 * go);
+          const float4 xs = row.shifted(16 * cb + 4 * go);
           oacc[cb][b] -= (v4f){xs.x * ws, xs.y * ws, xs.z * ws, xs.w * ws};
           if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few blocks' loads at a time: registers are full
         }
@@ -1226,8 +1235,8 @@ k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 // The training passes of TransE.  Bound by instruction issue: a pair takes 14 vector instructions and two of a quarter's rate beside
 // its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 48 and 58 us where fp32 matrix instructions
 // with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits are those of fp32 instructions or half of
-// them (node gradients 2e-7 against 3e-7, pairs 1e-3 apart 3e-5 against 8e-5).  Tables in which nearly all pairs are near (values of 5 +- 0.3)
-// take 2.4 times as long a step as on fp32 operands (1,412 us, 589): the loop over near pairs is for few.
+// them (node gradients 2e-7 against 3e-7, pairs 1e-3 apart 3e-5 against 8e-5).  Tables whose rows share an
+// offset are taken without it (common_offset); the loop over near pairs is for few.
 // Registers decide: nothing may spill (a step of 10,000 edges, 1,000 negatives of 400 floats 585 us with 351 registers spilled, 503 with
 // three steps' fragments in LDS and the near loop on the row's image; 50,000 edges 2,390 and 1,847).
 template <int NK, int PASS, bool CARRY>
