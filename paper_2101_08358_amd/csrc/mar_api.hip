@@ -153,7 +153,7 @@ static bool order_rides(const MarDims& d, long units1, long units2) {
   return d.long_passes && d.dk <= 256;
 }
 
-static int check_config(const mar_config* cfg, MarDims* d) {
+int mar_check_config(const mar_config* cfg, MarDims* d) {
   if (!cfg) return fail(MAR_EINVAL, "config is NULL");
   if (cfg->num_nodes < 1 || cfg->num_rels < 1) return fail(MAR_EINVAL, "num_nodes and num_rels must be >= 1");
   if (cfg->num_nodes + (int64_t)cfg->num_rels >= ((int64_t)1 << 31))
@@ -225,6 +225,10 @@ static int check_config(const mar_config* cfg, MarDims* d) {
   d->sort_one = mar_sort_one_limit(d->dk, false);
   d->long_passes = (double)cfg->batch_size * cfg->negs_per_chunk * d->dk >= 6.0e8;
   d->order_rides = order_rides(*d, units1, units2);
+  // The smallest steps that cannot carry it, for ids above 27 bits take a fourth pass, have it on the caller's stream all the same: the
+  // fork and the join are half of the host's time (1,400 gradient rows 65 -> 51 us a step, 1,100 64 -> 52, 3,800 65 -> 64).  Wide rows
+  // beside passes that fill the chip stay on two (1,280 edges of 300 floats, 3,840 rows 78 and 77, with outputs 80 and 86).
+  d->one_stream = d->order_rides || (d->sort_passes > 3 && d->n_pos_max <= MAR_SORT_ONE / 4 && !d->index_after_gather);
   return MAR_OK;
 }
 
@@ -291,7 +295,7 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
 
 extern "C" int mar_workspace_bytes(const mar_config* cfg, size_t* out_bytes) {
   MarDims d;
-  const int rc = check_config(cfg, &d);
+  const int rc = mar_check_config(cfg, &d);
   if (rc) return rc;
   if (!out_bytes) return fail(MAR_EINVAL, "out_bytes is NULL");
   *out_bytes = carve(d, nullptr, nullptr);
@@ -302,7 +306,7 @@ extern "C" int mar_init_tables(const mar_config* cfg, float* node_emb, float* no
                                float* rel_state, void* workspace, size_t workspace_bytes, int fill,
                                void* hip_stream, mar_ctx** out) {
   MarDims d;
-  const int rc = check_config(cfg, &d);
+  const int rc = mar_check_config(cfg, &d);
   if (rc) return rc;
   if (!out) return fail(MAR_EINVAL, "out is NULL");
   if (!node_emb || !node_state || !rel_emb || !rel_state) return fail(MAR_EINVAL, "a table pointer is NULL");
@@ -392,13 +396,13 @@ extern "C" int mar_train_batch(mar_ctx* c, const int32_t* src, const int32_t* re
   // (needed only by the per-row reduce) and the chain rule (needs pass 1 only) run beside them on `aux`.
   // Small batches stay on the caller's, whose launches carry the row order along (MarSortJob).
   const bool rides = c->dm.order_rides;
-  hipStream_t ax = rides ? st : c->aux;
+  hipStream_t ax = c->dm.one_stream ? st : c->aux;
   hipEvent_t* ev = nullptr;
   if (c->prof_events && c->prof_steps < c->prof_max) ev = c->prof_events + (size_t)c->prof_steps * 2 * MAR_NUM_PHASES;
 #define MARK(phase, end, stream) do { if (ev && (c->prof_mask >> (phase) & 1u)) HIP_TRY(hipEventRecord(ev[2 * (phase) + (end)], stream), "event record"); } while (0)
   // Two orders of the first launches.  Large batches: the gather runs alone at memory speed and the index build
-  // starts behind it, beside the first contraction pass that hides it.  Others whose order is not carried along (ids of more than
-  // 27 bits): the index build is the longer path to the reduce, so it starts first and the gather runs beside it.
+  // starts behind it, beside the first contraction pass that hides it.  Others whose order is not carried along (order_rides):
+  // the index build is the longer path to the reduce, so it starts first and the gather runs beside it.
   if (c->dm.index_after_gather) {
     MARK(1, 0, st);
     HIP_TRY(mar_launch_prep(c, b, dbg ? dbg->pos : nullptr, c->dm.split_bf16, nullptr, nullptr, st), "gather kernel");
@@ -553,7 +557,7 @@ static size_t pipe_slot_extra(const MarDims& d, char* base, PipeSlot* ps) {
 }
 
 static int pipe_check(const mar_config* cfg, int32_t depth, MarDims* d) {
-  const int rc = check_config(cfg, d);
+  const int rc = mar_check_config(cfg, d);
   if (rc) return rc;
   if (depth < 1 || depth > MAR_PIPE_MAX_DEPTH) return fail(MAR_ERANGE, "depth %d outside 1..%d", depth, MAR_PIPE_MAX_DEPTH);
   return MAR_OK;

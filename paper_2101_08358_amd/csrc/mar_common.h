@@ -75,6 +75,7 @@ struct MarDims {
   int32_t sort_one;                // most gradient rows that one workgroup sorts by itself
   int32_t long_passes;             // a contraction pass takes some 25 us or more
   int32_t order_rides;             // the row order is carried along by the step's own launches (MarSortJob)
+  int32_t one_stream;              // everything on the caller's stream: the order carried along, or (smallest batches) ahead of the gather
   int32_t index_after_gather;      // launch order of a step: gather first, index build behind it (large batches)
 };
 
@@ -214,6 +215,7 @@ bool mar_dist_images(const MarDims& d);            // TransE's training: images 
 static inline int mar_stripe_rows(const MarDims& d, int pass) { return mar_on_images(d) ? MAR_SPLIT_STRIPE_ROWS : mar_flash_stripe_rows(d.dk, pass); }
 static inline int mar_tile_rows(const MarDims& d, int pass) { return mar_on_images(d) ? MAR_SPLIT_TILE_ROWS : mar_flash_tile_rows(d.dk, pass); }
 // How many workgroups share one of `units` units of a pass, and the streamed tiles each takes (n_y streamed rows).
+int mar_check_config(const mar_config* cfg, MarDims* d);   // refuses, or plans: every rule a context follows
 void mar_plan_parts(const MarDims& d, int pass, long units, int n_y, int32_t* sy, int32_t* tps);
 bool mar_split_shares(int dk);                     // an evaluation on images can cut all units' tiles into equal shares
 bool mar_plan_shares(const MarDims& d, long units, int ntiles, int sy, int tps);   // and should, rather than `sy` parts a unit

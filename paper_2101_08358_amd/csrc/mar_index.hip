@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(256) k_fill_u32(uint32_t* __restrict__ p, int6
 
 // Blocks of the index kernels stay at 256 threads: they run beside the contraction kernels on a second stream and have
 // to fit into the wave slots and registers those leave free on a CU.  (k_sort_one, 1,024 threads and 96 KB of LDS, stands alone in
-// the pipeline, or ahead of the gather of a small batch with ids of more than 27 bits.)
+// the pipeline, or ahead of or beside the gather of a small batch that does not carry the order.)
 
 // ------------------------------------------------ row-sorted order of the gradient rows -----
 // Gradient row gr belongs to occurrence k = gr (edge side, gr < roles*n) or to part (gr - roles*n) % sy2

@@ -32,6 +32,24 @@ def test_four_passes():
     print(check_step(out), flush=True)
 
 
+# edges, chunks, negatives -> gradient rows (tests/test_launch_rules.py asks the library)
+ONE_WORKGROUP = {(200, 2, 50): 1400, (1000, 1, 9): 3144, (2720, 1, 2): 8192, (2721, 1, 2): 8195, (5456, 1, 1): 16384, (5457, 1, 1): 16387}
+
+
+@pytest.mark.parametrize("B,C,N", ONE_WORKGROUP)
+def test_four_passes_in_one_workgroup(B, C, N):
+    """Steps with ids above 27 bits cannot carry their row order: one workgroup sorts it, in 8 or 16 rounds, on the caller's stream (up
+    to 4,096 gradient rows) or on the second one; just beyond 16,384 rows launches do."""
+    rng = np.random.default_rng(B)
+    V, R = (1 << 27) + 1000, 3
+    draw = lambda m: np.where(rng.random(m) < 0.3, V - 1 - rng.integers(0, 4, m), rng.integers(0, V, m)).astype(np.int32)
+    ids = (draw(B), rng.integers(0, R, B).astype(np.int32), draw(B), draw(C * N).reshape(C, N), draw(C * N).reshape(C, N))
+    print("case", B, flush=True)
+    out = run_step_device_tables(0, V, R, 4, B, C, N, ids, seed=2, std=0.2)
+    assert out["gpu"]["untouched_ok"]
+    print(check_step(out), flush=True)
+
+
 @pytest.mark.parametrize("dim,R", ((16, 1), (100, 2), (400, 700)))
 def test_the_step_is_the_same_without_debug_outputs(dim, R):
     """Ranks are formed only for the outputs that need them; tables and loss have the same bits either way.  One relation
@@ -63,8 +81,8 @@ ROWS = {(8, 1, 1, 1): 5, (8, 320, 1, 64): 1600, (8, 1500, 1, 16): 4756, (12, 272
 
 @pytest.mark.parametrize("dim,B,C,N", ROWS)
 def test_orders_that_one_workgroup_sorts(dim, B, C, N):
-    """Batches up to, exactly at and just beyond what one workgroup holds in 8 and in 16 rounds (8,192 and 16,384 rows; above 256
-    floats 8,192 at most), hot ids among them, one, two and three passes.  (Wide rows with 62 negatives: with one, the loss is
+    """Batches up to, exactly at and just beyond what one workgroup holds in 8 and in 16 rounds (8,192 and 16,384 rows).  With these
+    ids, of at most 27 bits, steps carry the order along; k_sort_one itself: test_four_passes_in_one_workgroup.  Hot ids among them, one, two and three passes.  (Wide rows with 62 negatives: with one, the loss is
     sum(-2 f + f' + f'') of scores that nearly cancel, and its rounding, 2^-24 sum(2 |f| + |f'| + |f''|), was 1.3e-4 of it.)"""
     for V in (200, 100_000, 300_000):
         rng = np.random.default_rng(V + B)

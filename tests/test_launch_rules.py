@@ -94,3 +94,33 @@ def test_sizes_of_the_shared_evaluation_tests(tmp_path):
     printf("%%d%%d%%d ", (int)mar_eval_dense(d, b), (int)mar_plan_shares(d, units, ntiles, sy, tps), (int)mar_eval_dense(d, one));
   }""" % ", ".join("{%d, %d, %d, %d}" % k for k in SHARED))
     assert out == ["011"] * len(SHARED), out
+
+
+def plan(tmp_path, configs, fields):
+    """What the library plans for configurations (nodes, relations, dim, model, batch, chunks, negatives): the printed C expressions of d."""
+    out = _run(tmp_path, """
+  const long c[][7] = {%s};
+  for (auto& k : c) {
+    mar_config cfg = {k[0], (int32_t)k[1], (int32_t)k[2], (int32_t)k[3], (int32_t)k[4], (int32_t)k[5], (int32_t)k[6], 0, 0.1f, 1e-10f, 0.001f, 0, 0, 0};
+    MarDims d = {};
+    if (mar_check_config(&cfg, &d)) return 1;
+    printf("%s ", %s);
+  }""" % (", ".join("{%s}" % ", ".join(map(str, k)) for k in configs), " ".join(["%ld"] * len(fields)), ", ".join("(long)(%s)" % f for f in fields)))
+    out = [int(x) for x in out]
+    return [tuple(out[i:i + len(fields)]) for i in range(0, len(out), len(fields))]
+
+
+def test_smallest_steps_stay_on_the_callers_stream(tmp_path):
+    """Also those that cannot carry the row order because their ids have more than 27 bits, up to 4,096 gradient rows."""
+    big = (1 << 27) + 1000
+    got = plan(tmp_path, [(big, 3, 4, 0, 200, 2, 50), (big, 3, 4, 0, 1000, 1, 90), (10_000, 3, 300, 0, 1280, 128, 1), (10_000, 10, 50, 0, 1000, 10, 100)],
+               ("d.n_pos_max <= 4096", "d.order_rides", "d.one_stream"))
+    assert got == [(1, 0, 1), (0, 0, 0), (1, 0, 0), (0, 1, 1)], got
+
+
+def test_sizes_of_the_one_workgroup_tests(tmp_path):
+    """Steps with ids above 27 bits: none carries its order, those up to 16,384 gradient rows are sorted by one workgroup."""
+    from test_gpu_row_order import ONE_WORKGROUP
+    sizes = list(ONE_WORKGROUP)
+    got = plan(tmp_path, [((1 << 27) + 1000, 3, 4, 0) + k for k in sizes], ("d.n_pos_max", "d.order_rides", "d.n_pos_max <= d.sort_one", "d.one_stream"))
+    assert got == [(n, 0, int(n <= 16384), int(n <= 4096)) for n in (ONE_WORKGROUP[k] for k in sizes)], got
