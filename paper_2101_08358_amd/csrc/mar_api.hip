@@ -143,11 +143,17 @@ bool mar_dist_images(const MarDims& d) { return !d.bilinear && (double)d.B * d.N
 // slots of the passes.  us a step, second stream / carried along: 1,000 edges of 50 floats, 100 negatives 73 / 54; 20,000 gradient
 // rows (2,000 edges, 5 chunks, 31 floats) 81 / 50; 32,000 (13,600 edges, 28 chunks of 88 negatives, 39 floats) 107 / 91; 60,000 where
 // they fit beside both passes (18,700 edges, 111 negatives of 36) 92 / 76; 90,000 beside passes of 33 us (10,000 edges, 1,000 negatives of
-// 100) 139 / 128; where neither holds 120,000 (33,000 edges, 191 negatives of 76) 135 / 141, 230,000 (57,000 edges of 20 floats) 135 / 168,
-// 72,000 (4,200 edges, 755 negatives of 272: one workgroup a CU) 194 / 201.
+// 100) 139 / 128, of 64 floats, TransE 135 / 124, 81,000 (9,000, 950 of 120) 127 / 117, 88,000 (8,000, 2,000 of 100) 150 / 149, 75,000
+// (5,000, 1,500 of 100, three sort passes) 126 / 127, 86,000 (22,000, 300 of 200) 208 / 211; where neither holds 120,000 (33,000
+// edges, 191 negatives of 76) 135 / 141, 230,000 (57,000 edges of 20 floats) 135 / 168, 72,000 (4,200 edges, 755 negatives of 272: one
+// workgroup a CU) 194 / 201.  Images above 128 floats have one workgroup a CU and no slots beside their own: there the order costs more
+// than the second stream from 36,000 rows with three sort passes (a scatter beside each of pass 1, the chain rule and pass 2: 45,700
+// rows of 154 floats 162 / 170, 40,600 of 133 108 / 112, 61,000 of 192 148 / 154; 33,500 of 208 107 / 104), from 50,000 with two
+// (54,000 of 140 141 / 149, 58,800 of 176 110 / 113; 44,000 of 196 97 / 90, 49,900 of 152, TransE 171 / 158).
 static bool order_rides(const MarDims& d, long units1, long units2) {
   if (d.index_after_gather || d.sort_items != MAR_SORT_RIDE_ITEMS || d.sort_passes > 3 || d.n_pos_max > 96 * 1024) return false;
-  if (d.n_pos_max <= 72 * 1024 && d.dk <= 256) return true;
+  const bool crowded = wgs_per_cu(d, 1) == 1 && d.n_pos_max > (d.sort_passes > 2 ? 36 : 50) * 1024;
+  if (d.n_pos_max <= 72 * 1024 && d.dk <= 256 && !crowded) return true;
   const long tiles = (d.n_pos_max + 1023) / 1024 + 7;
   if (units1 * d.sy1 + tiles <= 256L * wgs_per_cu(d, 1) && units2 * d.sy2 + tiles <= 256L * wgs_per_cu(d, 2)) return true;
   return d.long_passes && d.dk <= 256;

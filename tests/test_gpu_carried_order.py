@@ -1,6 +1,6 @@
 """Row order carried along by the step's own launches: beside passes that leave it slots and passes that do not, with one, two and three
 passes over the ids, with the ranks of the debug outputs and without, against the oracle and against itself; and sizes at both sides of
-the line to the second stream."""
+the lines to the second stream (RIDES; tests/test_launch_rules.py asks the library)."""
 import numpy as np
 import pytest
 import torch
@@ -17,11 +17,20 @@ def _ids(rng, V, R, B, C, N):
     return hot(B), rng.integers(0, R, B).astype(np.int32), hot(B), hot(C * N).reshape(C, N), hot(C * N).reshape(C, N)
 
 
-# model, nodes, dim, edges, chunks, negatives: a pass that fills the chip but for 32 workgroups (long: each takes several tiles), ranks
-# over 70 tiles, TransE on dense operands and on images, 24,000 and 25,000 edges of one chunk and few negatives (72,000 rows and beyond)
-@pytest.mark.parametrize("model,V,dim,B,C,N", ((1, 14_951, 100, 6_000, 6, 1000), (0, 300, 24, 9_030, 7, 333), (0, 400_000, 76, 5_005, 7, 211),
-                                               (2, 5_000, 40, 3_000, 5, 200), (2, 5_000, 100, 2_500, 5, 900), (3, 600_000, 16, 24_000, 1, 20),
-                                               (0, 300_000, 8, 24_000, 1, 16), (0, 300_000, 8, 25_000, 1, 16)))
+# model, nodes, dim, edges, chunks, negatives -> whether the step carries its order: a pass that fills the chip but for 32 workgroups
+# (long: each takes several tiles), ranks over 70 tiles, TransE on dense operands and on images, 72,000 rows and more that fit beside
+# both passes; then, each after one that does, rows of one workgroup a CU with two and three sort passes, more than 72 x 1,024 rows beside
+# passes that fill the chip, rows above 256 floats that do not fit
+RIDES = {(1, 14_951, 100, 6_000, 6, 1000): True, (0, 300, 24, 9_030, 7, 333): True, (0, 400_000, 76, 5_005, 7, 211): True,
+         (2, 5_000, 40, 3_000, 5, 200): True, (2, 5_000, 100, 2_500, 5, 900): True, (3, 600_000, 16, 24_000, 1, 20): True,
+         (0, 300_000, 8, 24_000, 1, 16): True, (0, 300_000, 8, 25_000, 1, 16): True,
+         (0, 200_000, 132, 4_992, 8, 483): True, (0, 300_000, 132, 4_992, 8, 483): False,
+         (0, 100_000, 140, 15_000, 15, 250): False,
+         (3, 14_951, 32, 26_000, 13, 150): True, (3, 14_951, 32, 20_000, 40, 200): False,
+         (0, 10_000, 300, 1_200, 120, 10): True, (0, 10_000, 300, 1_280, 128, 10): False}
+
+
+@pytest.mark.parametrize("model,V,dim,B,C,N", RIDES)
 def test_one_step(model, V, dim, B, C, N):
     rng = np.random.default_rng(B + N)
     print("case", model, V, dim, B, flush=True)

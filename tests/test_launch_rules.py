@@ -124,3 +124,9 @@ def test_sizes_of_the_one_workgroup_tests(tmp_path):
     sizes = list(ONE_WORKGROUP)
     got = plan(tmp_path, [((1 << 27) + 1000, 3, 4, 0) + k for k in sizes], ("d.n_pos_max", "d.order_rides", "d.n_pos_max <= d.sort_one", "d.one_stream"))
     assert got == [(n, 0, int(n <= 16384), int(n <= 4096)) for n in (ONE_WORKGROUP[k] for k in sizes)], got
+
+
+def test_lines_of_the_carried_order(tmp_path):
+    from test_gpu_carried_order import RIDES
+    got = plan(tmp_path, [(V, 5, dim, model, B, C, N) for model, V, dim, B, C, N in RIDES], ("d.order_rides",))
+    assert [bool(x) for x, in got] == list(RIDES.values()), dict(zip(RIDES, got))
