@@ -165,11 +165,11 @@ __device__ __forceinline__ float common_offset(const float (&v)[SHIFT_ROWS]) {
   const bool close = (lo > 0.f && hi <= 4.f * lo) || (hi < 0.f && lo >= 4.f * hi);
   return close && fabsf(sum) <= 1e37f ? sum * (1.f / SHIFT_ROWS) : 0.f;   // (a NaN among them: 0)
 }
-// Row j of the eight: of either side, spread over the chunks and, from the last on, over a chunk's negatives (the first ones may be
-// drawn by degree).
-__device__ __forceinline__ const float* shift_row(const RowArgs& a, int j) {
+// Node of row j of the eight: of either side, spread over the chunks and, from the last on, over a chunk's negatives (the first ones may
+// be drawn by degree).
+__device__ __forceinline__ int32_t shift_node(const RowArgs& a, int j) {
   const size_t at = (size_t)(j * (int64_t)(a.cn / a.N) / SHIFT_ROWS) * a.N + (a.N - 1 - (int)(j * (int64_t)a.N / SHIFT_ROWS));
-  return a.node_emb + (size_t)(j & 1 ? a.neg_src : a.neg_dst)[at] * a.dim;
+  return (j & 1 ? a.neg_src : a.neg_dst)[at];
 }
 
 // Rows per lane group: edges, negatives.
@@ -203,21 +203,26 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
   }
   const int grp = threadIdx.x / GL, l = threadIdx.x % GL;
   const int dim = a.dim, dk = a.dk;
-  // The rows of the shift: fetched by a lane group or two each, exchanged through LDS behind the loads of the workgroup's own rows
+  // The rows of the shift: fetched by a lane group or two each, their ids and then they in flight with the workgroup's own, and
+  // exchanged through LDS
   constexpr bool SHIFT = MODEL == MAR_MODEL_TRANSE && IMG;
   constexpr int SPG = (SHIFT_ROWS + GPB - 1) / GPB;
   __shared__ float4 s_rows[SHIFT ? SHIFT_ROWS : 1][NV][GL];
+  int32_t sample_id[SPG];
   float4 sample[SPG][NV], shift[NV];
   if constexpr (SHIFT) {
 #pragma unroll
-    for (int k = 0; k < SPG; ++k) {
-      if (grp * SPG + k < SHIFT_ROWS) {
-        const float* row = shift_row(a, grp * SPG + k);
+    for (int k = 0; k < SPG; ++k) sample_id[k] = shift_node(a, min(grp * SPG + k, SHIFT_ROWS - 1));
+  }
+  auto fetch_shift = [&]() {
+    if constexpr (SHIFT) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) sample[k][v] = load_cols<GL, VEC, false>(row, l, v, dim);
+      for (int k = 0; k < SPG; ++k) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sample[k][v] = load_cols<GL, VEC, false>(a.node_emb + (size_t)sample_id[k] * dim, l, v, dim);
       }
     }
-  }
+  };
   auto take_shift = [&]() {
     if constexpr (SHIFT) {
 #pragma unroll
@@ -262,6 +267,7 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
       r_row[j] = a.rel_emb + (size_t)(MODEL == MAR_MODEL_DOT ? 0 : a.rel[e]) * dim;     // unused by Dot
       d_row[j] = a.node_emb + (size_t)a.dst[e] * dim;
     }
+    fetch_shift();
     float acc[E], nd[E], ns[E];
     float4 u[E][NV], w[E][NV], s[E][NV], r[E][NV], d[E][NV];
 #pragma unroll
@@ -378,6 +384,7 @@ k_prep(RowArgs a, int carried, int nbB, int wpc_e, int wpc_n, float* __restrict_
       const int32_t id = side == MAR_SIDE_DST ? a.neg_dst[cj] : a.neg_src[cj];
       const float* row = a.node_emb + (size_t)id * dim;
       krow[j] = (size_t)side * a.C * a.N + cj;
+      if (j == 0) fetch_shift();
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         x[j][v] = load_cols<GL, VEC, false>(row, l, v, dim);
