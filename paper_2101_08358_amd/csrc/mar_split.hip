@@ -672,9 +672,13 @@ template <bool EDGE> struct DistRow {
   }
 };
 
+// Close pairs: 2^-15 of the root of their norms' sum, squared.
+#define SP_CLOSE 0x1p-30f
 // DIST (TransE): the score is -|x - y|, its square expanded as |x|^2 + |y|^2 - 2 x.y with the norms in fp32.  Pairs for which the
 // expansion cancels (below 2^-8 of the norms' sum) are formed from the differences of their columns (rare in training; a wave
 // without one skips the loop).  The second product then runs with W = softmax weight / distance, less x times the sum of the W.
+// A close pair (SP_CLOSE) stays out of the product: its weight over its distance would leave the others' no bits of the f16 range, and
+// W y - W x cancels.  Its lane keeps it, two at most (further ones go through the product), and the end adds W (y - x) from the rows.
 // CARRY: the first a.carried workgroups do a piece of the row order (small batches).
 template <int NK, int PASS, bool F16, bool DIST, bool CARRY>
 __device__ __forceinline__ void split_pass(const FlashArgs& a) {
@@ -716,6 +720,10 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
   // DIST, widest rows: the fragments of the last XL steps lie in LDS, each lane's own (its registers would spill; 400 floats: 351 of them)
   constexpr int XL = DIST ? sp_dist_lds_steps(NK) : 0;
   char* const xlds = smem + SG::LDS_BYTES + 2 * TY * 4 + threadIdx.x * 16;   // [4 XL][256] 16-byte units
+  // DIST: a lane's close pairs, added at the end: streamed row and column block (-1: none), weight, its reference: [3][2][256]
+  int* const close_id = reinterpret_cast<int*>(smem + SG::LDS_BYTES + 2 * TY * 4 + XL * 4 * 4096);
+  // formed anew where it is rarely used: kept across the tiles it would cost a register
+  const auto fresh_lane = []() { int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); asm volatile("" : "+v"(l)); return l; };
   v8s xh[2][NS], xl[2][NS], xt[2][2];
   // Tail: 16 columns more as one or two steps of 32 slots.  At most 8 of them: lane groups 0, 1, 2 hold the first 8
   // columns of hi * hi, lo * hi and hi * lo.  Else groups 0, 1 / 2, 3 hold both halves of hi * hi and lo * hi, and a second step hi * lo.
@@ -751,6 +759,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
     }
   }
 
+  if (DIST) close_id[threadIdx.x] = close_id[256 + threadIdx.x] = -1;
   v4f oacc[NO][2];
 #pragma unroll
   for (int cb = 0; cb < NO; ++cb) oacc[cb][0] = oacc[cb][1] = (v4f)(0.f);
@@ -903,7 +912,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
           d2[v] = __builtin_fmaf(sc[v >> 2][b][v & 3], k2[v >> 2], xn[b] + yn[v]);
           near |= is_near(v, yn[v]);
         }
-        unsigned none = 0u;                                // pairs at distance 0: no gradient
+        unsigned none = 0u;                                // pairs at distance 0: no gradient; << 8, << 16: close pairs in slots 0 and 1
         if (__builtin_expect(__any(near), 0)) {
           unsigned left = 0u;
 #pragma unroll
@@ -947,12 +956,12 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
             if (TAIL && left && g < 2) add_image(64 * NS + 16 * g);   // the 16 columns behind: units 0 and 1 (zeros from dk on)
             part += __shfl_xor(part, 16);
             part = __builtin_ldexpf(part + __shfl_xor(part, 32), -2 * ey);
-            // closer than hi + lo of the two rows can tell (2^-20 of the norm): by the rows themselves, so that rows that are
-            // the same are found to be
+            // close (2^-15 of the norm): by the rows themselves, for hi + lo of two rows tell them apart to 2^-20 of the norm, and
+            // rows that are the same have to be found to be
             const float both = xn[b] + nrm_all[buf * TY + at_row];
-            const bool same = left && !(part > 0x1p-40f * both);
-            if (__builtin_expect(__any(same), 0)) {
-              const int xr = min(x0 + 16 * b + i, n_x - 1), yr = min(y0 + at_row, n_y - 1);
+            const bool close = left && !(part > SP_CLOSE * both);
+            if (__builtin_expect(__any(close), 0)) {
+              const int xr = min(u.stripe * SP_SR + wave_s * 32 + 16 * b + (fresh_lane() & 15), n_x - 1), yr = min(y0 + at_row, n_y - 1);
               const DistRow<true> q(u.cs, PASS == 1 ? xr : yr);
               const DistRow<false> n(u.cs, PASS == 1 ? yr : xr);
               float exact = 0.f;
@@ -964,7 +973,17 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
               }
               exact += __shfl_xor(exact, 16);
               exact += __shfl_xor(exact, 32);
-              part = same ? exact : part;
+              part = close ? exact : part;
+              // a close pair's weight over its distance would leave the others' no bits of the f16 range, and its part in the sums
+              // of W y cancels: it stays out of the product where its lane has a slot left
+              if (close && part >= 2e-38f && g == (at_row & 15) >> 2) {
+                int* const own = close_id + wave_s * 64 + fresh_lane();
+                const int slot = own[0] < 0 ? 0 : (own[256] < 0 ? 1 : 2);
+                if (slot < 2) {
+                  own[256 * slot] = (y0 + at_row) | b << 30;
+                  none |= 256u << (8 * slot + 4 * (at_row >> 4) + (at_row & 3));
+                }
+              }
             }
 #pragma unroll
             for (int v = 0; v < 8; ++v) {
@@ -1006,20 +1025,28 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
             w[b][v] = p * rs;
           }
           if (__builtin_expect(__any(none != 0u), 0)) {
+            float* const close_w = reinterpret_cast<float*>(close_id) + 2 * 256 + wave_s * 64 + fresh_lane();
 #pragma unroll
-            for (int v = 0; v < 8; ++v) w[b][v] = none >> v & 1u ? 0.f : w[b][v];
+            for (int v = 0; v < 8; ++v) {
+              if (none >> v & 0x10100u) {
+                float* const at = close_w + (none >> v & 0x100u ? 0 : 256);
+                at[0] = fminf(w[b][v], 3e38f);
+                at[2 * 256] = ef[v >> 2] + mref[b];
+              }
+              w[b][v] = none >> v & 0x10101u ? 0.f : w[b][v];
+            }
           }
           float most = w[b][0];
 #pragma unroll
           for (int v = 1; v < 8; ++v) most = fmaxf(most, w[b][v]);
-          return fmaxf(most, fmaxf(l[0], l[1]) * 0x1p-64f);   // (a pair at distance 0 has only a softmax weight)
+          return fmaxf(most, fmaxf(l[0], l[1]) * 0x1p-64f);   // (a pair at distance 0, and a close one, has only a softmax weight here)
         };
         if (__builtin_expect(__any(weigh() > 32768.f), 0)) {
           float tall = -3.0e38f;
 #pragma unroll
           for (int v = 0; v < 8; ++v) {
             const float rs = __builtin_amdgcn_rsqf(d2[v]);
-            tall = fmaxf(tall, log2w(v, rs) - ef[v >> 2] + (none >> v & 1u ? 0.f : __builtin_amdgcn_logf(rs)));
+            tall = fmaxf(tall, log2w(v, rs) - ef[v >> 2] + (none >> v & 0x10101u ? 0.f : __builtin_amdgcn_logf(rs)));
           }
           tall = fmaxf(tall, __shfl_xor(tall, 16));
           tall = fmaxf(tall, __shfl_xor(tall, 32));
@@ -1194,11 +1221,10 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
       ws = wsum[b] + __shfl_xor(wsum[b], 16);
       ws += __shfl_xor(ws, 32);
     }
+    bool has_close = false;
+    if (DIST) has_close = __any(close_id[wave_s * 64 + fresh_lane()] >= 0);   // (slot 0 is taken first)
     int go = g;
-    if (DIST) {                                            // formed anew: nor are the rows' columns to be kept across the tiles
-      go = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 4;
-      asm volatile("" : "+v"(go));
-    }
+    if (DIST) go = fresh_lane() >> 4;                      // nor are the rows' columns to be kept
     if (xv[b]) {
       if constexpr (DIST) {
         const DistRow<PASS == 1> row(u.cs, x);
@@ -1207,6 +1233,26 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
           const float4 xs = row.shifted(16 * cb + 4 * go);
           oacc[cb][b] -= (v4f){xs.x * ws, xs.y * ws, xs.z * ws, xs.w * ws};
           if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few blocks' loads at a time: registers are full
+        }
+        if (__builtin_expect(has_close, 0)) {
+          // the column's close pairs, which its four lanes keep: W (y - x) from the rows, at the end's reference
+#pragma unroll 1
+          for (int k = 0; k < 8; ++k) {
+            const int at = 256 * (k >> 2) + wave_s * 64 + 16 * (k & 3) + (fresh_lane() & 15), id = close_id[at];
+            if (id < 0 || id >> 30 != b) continue;
+            const float* const close_w = reinterpret_cast<const float*>(close_id) + 2 * 256 + at;
+            const float wc = __builtin_ldexpf(close_w[0], (int)fmaxf(-300.f, fminf(300.f, close_w[2 * 256] - mref[b])));
+            const int y = id & 0x3fffffff;
+            const DistRow<true> q(u.cs, PASS == 1 ? x : y);
+            const DistRow<false> n(u.cs, PASS == 1 ? y : x);
+#pragma unroll
+            for (int cb = 0; cb < NO; ++cb) {
+              const float4 qc = q.cols(16 * cb + 4 * go), nc = n.cols(16 * cb + 4 * go);
+              const v4f d = {nc.x - qc.x, nc.y - qc.y, nc.z - qc.z, nc.w - qc.w};
+              oacc[cb][b] += d * (PASS == 1 ? wc : -wc);
+              if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+          }
         }
       }
 #pragma unroll
@@ -1234,9 +1280,12 @@ k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 
 // The training passes of TransE.  Bound by instruction issue: a pair takes 14 vector instructions and two of a quarter's rate beside
 // its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 48 and 58 us where fp32 matrix instructions
-// with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits are those of fp32 instructions or half of
-// them (node gradients 2e-7 against 3e-7, pairs 1e-3 apart 3e-5 against 8e-5).  Tables whose rows share an
-// offset are taken without it (common_offset); the loop over near pairs is for few.
+// with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits over 42
+// drawn steps, fp32 instructions / these, mean: node gradients 1.1e-7 / 9e-8, relation gradients 4.1e-7 / 3.1e-7, log-sum-exps 2.1e-7 /
+// 8e-8, worst row 8.8e-7 / 4.8e-7.  Near pairs: 3e-2 to 3e-5 apart as on fp32 instructions (100 floats, 1e-3: 6.3e-7 / 6.7e-7), closer
+// ones (SP_CLOSE) exact to 1.6e-7 where those have 3e-5 (1e-5 apart) to 7e-2 (one unit in the last place, 400 floats).  Tables whose
+// rows share an offset are taken without it (common_offset); the loop over near pairs is for few (after 200 and 1,000 steps of training
+// from 0 +- 0.3: 153 and 156 us a step, 210 on fp32 instructions).
 // Registers decide: nothing may spill (a step of 10,000 edges, 1,000 negatives of 400 floats 585 us with 351 registers spilled, 503 with
 // three steps' fragments in LDS and the near loop on the row's image; 50,000 edges 2,390 and 1,847).
 template <int NK, int PASS, bool CARRY>

@@ -67,6 +67,6 @@ struct SplitGeom {
   static constexpr int NCH = IMG / 1024;                   // 1 KB pieces of an image
   static constexpr size_t LDS_TILES = 2 * (size_t)IMG + 4 * SP_TY * 4;
   static constexpr size_t LDS_BYTES = LDS_TILES < SORT_LDS_BYTES ? SORT_LDS_BYTES : LDS_TILES;   // two images, and (pass 2) the log-sum-exp of a tile's edges
-  static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4 + (size_t)sp_dist_lds_steps(NK) * 4 * 4096;   // TransE: and the squared norms of two tiles' rows, stationary fragments
+  static constexpr size_t LDS_BYTES_DIST = LDS_BYTES + 2 * SP_TY * 4 + (size_t)sp_dist_lds_steps(NK) * 4 * 4096 + 3 * 2 * 256 * 4;   // TransE: and the squared norms of two tiles' rows, stationary fragments, close pairs
   static constexpr size_t LDS_BYTES3 = 2 * (size_t)IMG + 2 * SP_PEND * 256 * 4;   // two images, and the lanes' pending candidates: id, how often
 };

@@ -1,8 +1,11 @@
 """TransE's training passes on images and 16-bit products against the oracle: every instantiation's widths (whole and half-filled last
 blocks, rows of no whole 16 bytes), chunks that fill no stripe, tile or part, negatives that coincide with their target or nearly do,
-rows of different size, and the line between images and dense operands."""
+rows of different size, full batches whose last round of stripes is split, a graph, and the line between images and dense operands."""
 import numpy as np
 import pytest
+import torch
+
+import paper_2101_08358_amd as mar
 
 from parity_util import run_step_both, check_step
 
@@ -74,3 +77,132 @@ def test_rows_of_different_size(low):
     ids[3][0, :320] = 2 * rng.integers(0, V // 2, 320)      # whole blocks of small rows
     out = run_step_both(TRANSE, V, R, dim, B, C, N, B, seed=1, tables=(ne.astype(np.float32), re_.astype(np.float32)), ids=tuple(ids))
     print(check_step(out), flush=True)
+
+
+# dim, edges, chunks, negatives -> parts of the stripes beyond the last whole round, in both passes (tests/test_launch_rules.py asks the
+# library); the first two carry their row order
+SPLIT = {(200, 9_030, 70, 129): 3, (200, 13_500, 45, 300): 5, (140, 11_610, 90, 200): 2, (300, 13_500, 45, 300): 5, (100, 28_270, 110, 257): 3}
+
+
+@pytest.mark.parametrize("dim,B,C,N", SPLIT)
+def test_full_batches_that_split_their_last_round(dim, B, C, N):
+    print("case", dim, B, flush=True)
+    print(check_step(run_step_both(TRANSE, 20_000, 7, dim, B, C, N, B, seed=dim + C, std=0.3)), flush=True)
+
+
+def _near(dim, level, S=400, C=10, N=1000, V=3000, R=4):
+    """As test_negatives_at_or_near_the_target, 20 such negatives a chunk and side; level None: one unit in the last place of the largest column."""
+    rng = np.random.default_rng(dim)
+    B = S * C
+    ne, re_ = (rng.standard_normal((V, dim)) * 0.2).astype(np.float32), (rng.standard_normal((R, dim)) * 0.2).astype(np.float32)
+    re_[0] = 0.0
+    spare = V - 500
+    src, dst = (rng.integers(0, spare, B).astype(np.int32) for _ in range(2))
+    rel = rng.integers(0, R, B).astype(np.int32)
+    neg_src, neg_dst = (rng.integers(0, spare, (C, N)).astype(np.int32) for _ in range(2))
+    for c in range(C):
+        for k in range(20):
+            e = c * S + 19 * k
+            rel[e] = 0
+            for neg, end, slot in ((neg_dst, src, 25 * k), (neg_src, dst, 25 * k + 3)):
+                row = ne[end[e]].copy()
+                if level is None:
+                    j = int(np.argmax(np.abs(row)))
+                    row[j] = np.nextafter(row[j], np.float32(9))
+                else:
+                    d = rng.standard_normal(dim)
+                    row = row + d / np.linalg.norm(d) * level * np.linalg.norm(row)
+                ne[spare] = row
+                neg[c, slot] = spare
+                spare += 1
+    return (ne, re_), (src, rel, dst, neg_src, neg_dst)
+
+
+def _gradient_errors(tables, ids, C, N):
+    V, R, dim, B = tables[0].shape[0], tables[1].shape[0], tables[0].shape[1], ids[0].size
+    out = run_step_both(TRANSE, V, R, dim, B, C, N, B, seed=0, tables=tables, ids=ids)
+    res, un = out["ora"]["res"], out["ora"]["res"].uniq_nodes.size
+    return [(float(np.sum((a.astype(np.float64) - b) ** 2)), float(np.sum(b ** 2)))
+            for a, b in ((out["gpu"]["G"][:un], res.G_nodes), (out["gpu"]["G"][un:], res.G_rels))]
+
+
+@pytest.mark.parametrize("dim", (53, 100, 400))
+@pytest.mark.parametrize("level", (3e-2, 1e-3, 1e-5, 1e-6, 5e-7, None))
+def test_near_pairs_are_as_exact_as_on_dense_operands(dim, level):
+    """The whole batch on images against its chunks one by one, which lie below the line, on dense operands: gradient errors against the
+    oracle in the 2-norm.  A near pair's weight is its softmax weight over its distance: what the sums of W y lose to rounding goes
+    with 1 / level, on either.  Pairs closer than 2^-15 = 3e-5 of the norm are kept out of the product and added from their rows:
+    two parts in 1e7 however close (400 floats, 1e-6: 1e-2 while their weights shared the f16 range with the others', dense 3e-3).
+    Factor 1.5: what two batches of the same kind differ by (measured 0.8 to 1.25)."""
+    tables, ids = _near(dim, level)
+    C, N = ids[3].shape
+    S = ids[0].size // C
+    assert ids[0].size * N * ((dim + 3) // 4 * 4) >= 2e8 > S * N * ((dim + 3) // 4 * 4)
+    print("case", dim, level, flush=True)
+    image = _gradient_errors(tables, ids, C, N)
+    chunks = [_gradient_errors(tables, tuple(x[c * S:(c + 1) * S] for x in ids[:3]) + tuple(x[c:c + 1] for x in ids[3:]), 1, N) for c in (0, 4, 9)]
+    for k, name in enumerate(("nodes", "relations")):
+        on_images = (image[k][0] / image[k][1]) ** 0.5
+        dense = (sum(c[k][0] for c in chunks) / sum(c[k][1] for c in chunks)) ** 0.5
+        print(name, "images %.2e dense %.2e" % (on_images, dense), flush=True)
+        assert on_images <= 1.5 * dense, (name, on_images, dense)
+        assert level is not None and level > 2e-5 or on_images <= 5e-7, (name, on_images)
+
+
+@pytest.mark.parametrize("dim,B,C,N", ((100, 2_100, 3, 1000), (300, 3_000, 4, 600), (200, 9_030, 70, 129)))
+def test_captured_step_replays_like_the_eager_step(dim, B, C, N):
+    """With tables that share an offset, so that the vector taken off the operands is formed anew in every replay; eager steps on other
+    negatives between."""
+    rng = np.random.default_rng(dim)
+    V, R = 4000, 5
+    ne, re_ = (rng.standard_normal((V, dim)) * 0.2 + 1.0).astype(np.float32), (rng.standard_normal((R, dim)) * 0.2).astype(np.float32)
+    tr = mar.Trainer(V, R, dim, TRANSE, B, C, N, seed=2, node_emb=ne, rel_emb=re_)
+    ids = [torch.from_numpy(rng.integers(0, k, B).astype(np.int32)).to(tr.device) for k in (V, R, V)]
+    other = [torch.from_numpy(rng.integers(0, V, C * N).astype(np.int32)).to(tr.device) for _ in range(2)]
+    tr.sample_negatives(3, ids[0], ids[2])
+    init = [x.clone() for x in (tr.node_emb, tr.node_state, tr.rel_emb, tr.rel_state)]
+
+    def restore():
+        for t, t0 in zip((tr.node_emb, tr.node_state, tr.rel_emb, tr.rel_state), init):
+            t.copy_(t0)
+        torch.cuda.synchronize()
+
+    tr.train_batch(*ids)
+    torch.cuda.synchronize()
+    want = [x.clone() for x in (tr.node_emb, tr.node_state, tr.rel_emb, tr.rel_state, tr.loss)]
+    restore()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            mar.mar_train_batch(tr.ctx, *ids, B, tr.neg_src, tr.neg_dst, tr.loss, None, stream)
+    torch.cuda.synchronize()
+    for replay in range(3):
+        restore()
+        graph.replay()
+        torch.cuda.synchronize()
+        for t, w in zip((tr.node_emb, tr.node_state, tr.rel_emb, tr.rel_state, tr.loss), want):
+            assert torch.equal(t, w), replay
+        mar.mar_train_batch(tr.ctx, *ids, B, *other, tr.loss, None, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    tr.close()
+
+
+@pytest.mark.parametrize("dim", (100, 300))
+def test_more_close_pairs_than_a_lane_keeps(dim):
+    """A lane keeps two: eight close negatives of one edge whose rows lie with one lane (every fourth tile's first rows) leave six in the
+    product, as exact there as near pairs are."""
+    tables, ids = _near(dim, 1e-5)
+    ne, neg_dst = tables[0], ids[3 + 1]
+    rng = np.random.default_rng(1)
+    for c in range(4):
+        ids[1][c * 400] = 0                                  # relation 0 is zero
+        row = ne[ids[0][c * 400]]
+        for k in range(8):
+            d = rng.standard_normal(dim)
+            ne[2_990 - 8 * c - k] = row + d / np.linalg.norm(d) * 1e-5 * np.linalg.norm(row)
+            neg_dst[c, 32 * k] = 2_990 - 8 * c - k
+    C, N = ids[3].shape
+    errors = _gradient_errors(tables, ids, C, N)
+    print("case", dim, errors, flush=True)
+    for d2, n2 in errors:                                    # 2^-23 / level, the share of the batch's gradient that these pairs are
+        assert (d2 / n2) ** 0.5 <= 1e-3
