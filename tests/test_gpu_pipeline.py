@@ -101,6 +101,30 @@ def test_depth_one_is_the_resident_step_when_pass_one_splits_its_last_round():
     assert abs(want[4][0] / B - 2 * np.log(N)) < 0.5
 
 
+@pytest.mark.parametrize("dim,B,C,N", ((100, 2_100, 3, 1000), (300, 3_000, 4, 600)))
+def test_depth_one_is_the_resident_step_for_transe_on_images(dim, B, C, N):
+    """At least 2e8 pairs x columns: the passes read fp32 rows from the staged tables by rank, where rows share an offset too."""
+    V, R = 5000, 6
+    ne, ns, re_, rs, batches = _setup(mar.MODEL_TRANSE, V, R, dim, B, C, N, nb=3, seed=dim)
+    ne += np.float32(0.5)
+    got = _run_pipe(mar.MODEL_TRANSE, V, R, dim, B, C, N, 1, (ne, ns, re_, rs), batches)
+    want = _run_resident(mar.MODEL_TRANSE, V, R, dim, B, C, N, (ne, ns, re_, rs), batches)
+    for g, w, name in zip(got, want, ("node_emb", "node_state", "rel_emb", "rel_state", "loss")):
+        assert np.array_equal(g, w), name
+
+
+def test_transe_on_images_follows_the_oracle_with_staleness_one():
+    model, V, R, dim, B, C, N = mar.MODEL_TRANSE, 3000, 5, 100, 2_100, 3, 1000
+    ne, ns, re_, rs, batches = _setup(model, V, R, dim, B, C, N, nb=4, seed=2, state0=0.05)
+    got = _run_pipe(model, V, R, dim, B, C, N, 2, (ne, ns, re_, rs), batches)
+    one, ons, ore, ors = ne.copy(), ns.copy(), re_.copy(), rs.copy()
+    ol = opipe.train_pipelined(model, np.float32(0.1), np.float32(1e-10), B // C, one, ons, ore, ors, batches, staleness=1)
+    for g, w, name in zip(got[:4], (one, ons, ore, ors), ("node_emb", "node_state", "rel_emb", "rel_state")):
+        err = np.max(np.abs(g.astype(np.float64) - w)) / np.max(np.abs(w))
+        assert err <= 1e-4, (name, err)
+    assert np.max(np.abs(got[4] - np.array(ol)) / np.abs(np.array(ol))) <= 1e-4
+
+
 @pytest.mark.parametrize("depth", (2, 4))
 def test_depth_k_follows_the_oracle_with_staleness_k_minus_one(depth):
     """Warm accumulators (of the size of the squared gradients) make the update smooth in the gradient, so tables can

@@ -32,12 +32,14 @@ def test_one_step_other_widths(model, dim):
     print(check_step(out), flush=True)
 
 
-@pytest.mark.parametrize("model", (DISTMULT, COMPLEX, TRANSE))
-def test_one_step_when_pass_one_splits_its_last_round(model):
-    """96 chunk-sides x 7 stripes = 672 units of the first contraction pass on 512 workgroup slots: the stripes of
-    the last 24 chunk-sides are split into two parts over the negatives' tiles and merged afterwards."""
-    print("case", model, flush=True)
-    out = run_step_both(model, 30000, 3, 100, 21504, 48, 128, 21504, seed=40 + model)
+@pytest.mark.parametrize("model,dim", ((DISTMULT, 100), (COMPLEX, 100), (TRANSE, 100), (TRANSE, 36)))
+def test_one_step_when_pass_one_splits_its_last_round(model, dim):
+    """Dense operands (TransE of 36 floats): 96 chunk-sides x 7 stripes = 672 units of the first contraction pass on 512 workgroup slots:
+    the stripes of the last 24 chunk-sides are split into two parts over the negatives' tiles and merged afterwards.  The others, on
+    images, have stripes of 128 rows, 384 units, and no such round (tests/test_launch_rules.py asks the library; splits on images:
+    test_gpu_dist_images.py, and the batches of 100,000 edges of test_gpu_large.py)."""
+    print("case", model, dim, flush=True)
+    out = run_step_both(model, 30000, 3, dim, 21504, 48, 128, 21504, seed=40 + model)
     print(check_step(out), flush=True)
 
 

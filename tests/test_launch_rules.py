@@ -145,3 +145,13 @@ def test_transe_on_images_where_their_padding_leaves_a_gain(tmp_path):
     got = plan(tmp_path, [(5_000, 5, dim, 2, B, C, N) for dim, B, C, N in sizes], ("(double)d.B * d.N * d.dk >= 2.0e8", "d.dist_img"))
     assert all(g[0] for g in got)
     assert [g[1] for g in got] == [0] * len(wide + dense) + [1] * (len(sizes) - len(wide + dense)), list(zip(sizes, got))
+
+
+def test_splits_of_the_last_round_on_images_and_on_dense_operands(tmp_path):
+    """Parts of the stripes beyond the last whole round: of TransE's images in both passes, of its dense form in the first."""
+    from test_gpu_dist_images import SPLIT
+    got = plan(tmp_path, [(20_000, 7, dim, 2, B, C, N) for dim, B, C, N in SPLIT], ("d.dist_img", "d.rem1.k", "d.rem2.k"))
+    assert got == [(1, k, k) for k in SPLIT.values()], got
+    got = plan(tmp_path, [(30_000, 3, dim, model, 21_504, 48, 128) for model, dim in ((2, 36), (2, 100), (0, 100), (1, 100))],
+               ("d.bilinear || d.dist_img", "d.rem1.k", "d.rem2.k"))
+    assert got == [(0, 2, 1)] + 3 * [(1, 1, 1)], got
