@@ -1230,8 +1230,10 @@ static void launch_prep(const RowArgs& a, const MarLayout& L, float* pos_out, in
   float* q = MODEL == MAR_MODEL_TRANSE ? L.Q : (rank_dst ? L.gQ : nullptr);
   float* km = MODEL == MAR_MODEL_TRANSE ? L.Km : L.G;
 #define PREP_LAUNCH(V, CARRY) hipLaunchKernelGGL((k_prep<GL, NV, V, MODEL, FORM, CARRY>), grid, blk, lds, st, a, job.blocks, nbB, wpc_e, wpc_n, q, km, L.qq, L.kk, L.pos, pos_out, rank_dst, rank_src, qi, ki, job)
-  if (a.dim % 4 == 0) { if (job.blocks) PREP_LAUNCH(true, true); else PREP_LAUNCH(true, false); }
-  else { if (job.blocks) PREP_LAUNCH(false, true); else PREP_LAUNCH(false, false); }
+  if constexpr (img || MODEL == MAR_MODEL_TRANSE) {         // (the bilinear models' dense form is evaluation's: it carries nothing)
+    if (job.blocks) { if (a.dim % 4 == 0) PREP_LAUNCH(true, true); else PREP_LAUNCH(false, true); return; }
+  }
+  if (a.dim % 4 == 0) PREP_LAUNCH(true, false); else PREP_LAUNCH(false, false);
 #undef PREP_LAUNCH
 }
 

@@ -199,7 +199,7 @@ __device__ __forceinline__ void sort_scatter_tile(int tile, uint32_t* lds, const
 __device__ __forceinline__ bool is_head(const uint32_t* __restrict__ ids, int64_t p, int64_t n) { return p < n && (p == 0 || ids[p - 1] != ids[p]); }
 
 // Ranks in one launch: each of j.blocks workgroups takes `per` neighbouring tiles of MAR_RANK_TILE positions, counts the heads before
-// them itself (at most 131,072 ids from the cache, beside a pass; 16 loads a thread in flight, or it would outlast the pass), and
+// them itself (at most 98,304 ids from the cache, beside a pass; 16 loads a thread in flight, or it would outlast the pass), and
 // writes what k_rank_count, k_rank_apply and k_debug_uniq do.
 __device__ __forceinline__ void sort_rank_tiles(int first, int last, uint32_t* lds, const MarSortJob& j) {
   static_assert(MAR_RANK_TILE == 1024, "16 bytes of ids a thread");
