@@ -263,8 +263,10 @@ int mar_pipe_destroy(mar_pipe* pipe);
 /*
  * Per-phase device timing of mar_train_batch with HIP events on the stream each phase runs on.
  * Phase 0 runs on the context's second stream beside phases 1-3.  In small batches (batch_size x
- * negs_per_chunk x dim below 2e9 and some 100,000 gradient rows) the launches of phases 1-4 carry it
- * along, everything runs on the caller's stream and phase 0 reads 0.  Phase 4 runs on the
+ * negs_per_chunk x dim below 2e9, num_nodes + num_rels at most 2^27 and, by width and by what else fills
+ * the device, up to 36,000 to 98,000 gradient rows) the launches of phases 1-4 carry it along,
+ * everything runs on the caller's stream and phase 0 reads 0; in the smallest batches with more rows in
+ * the tables it runs on the caller's stream ahead of phase 1.  Phase 4 runs on the
  * second stream in large batches (batch_size x negs_per_chunk x dim from 2e9 on) only.  Phases
  * that run beside others overlap them: the six times then do not add up to the step time.
  * Phases: 0 index build (unique set, occurrence order), 1 row gather and operand build,

@@ -1278,11 +1278,11 @@ template <int NK, int PASS, bool F16>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 
-// The training passes of TransE.  Bound by instruction issue: a pair takes 14 vector instructions and two of a quarter's rate beside
-// its products, twice a bilinear model's.  10,000 edges, 1,000 negatives of 100 floats: 48 and 58 us where fp32 matrix instructions
-// with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits over 42
-// drawn steps, fp32 instructions / these, mean: node gradients 1.1e-7 / 9e-8, relation gradients 4.1e-7 / 3.1e-7, log-sum-exps 2.1e-7 /
-// 8e-8, worst row 8.8e-7 / 4.8e-7.  Near pairs: 3e-2 to 3e-5 apart as on fp32 instructions (100 floats, 1e-3: 6.3e-7 / 6.7e-7), closer
+// The training passes of TransE.  Counted, a pair takes 40 vector instructions, matrix ones included, in a bilinear model's pass 18; the
+// vector pipe is busy 0.46 and 0.37 of the time, the matrix pipe 0.22 and 0.18, the rest is one tile's chain of products, distances,
+// weights and products with two waves a SIMD.  10,000 edges, 1,000 negatives of 100 floats: 47 and 58 us where fp32 matrix
+// instructions with stored weights (k_flash, k_flash_bwd) take 111 and 61.  Errors against 64 bits over 42 drawn steps, fp32 instructions / these, mean: node gradients 1.1e-7 / 9e-8, relation gradients 4.1e-7 / 3.1e-7, log-sum-exps 2.1e-7 /
+// 8e-8, worst row 8.8e-7 / 4.9e-7.  Near pairs: 3e-2 to 3e-5 apart as on fp32 instructions (100 floats, 1e-3: 6.3e-7 / 6.7e-7), closer
 // ones (SP_CLOSE) exact to 1.6e-7 where those have 3e-5 (1e-5 apart) to 7e-2 (one unit in the last place, 400 floats).  Tables whose
 // rows share an offset are taken without it (common_offset); the loop over near pairs is for few (after 200 and 1,000 steps of training
 // from 0 +- 0.3: 153 and 156 us a step, 210 on fp32 instructions).
