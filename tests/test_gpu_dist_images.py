@@ -90,9 +90,10 @@ def test_full_batches_that_split_their_last_round(dim, B, C, N):
     print(check_step(run_step_both(TRANSE, 20_000, 7, dim, B, C, N, B, seed=dim + C, std=0.3)), flush=True)
 
 
-def _near(dim, level, S=400, C=10, N=1000, V=3000, R=4):
+def _near(dim, level, S=400, N=1000, V=3000, R=4):
     """As test_negatives_at_or_near_the_target, 20 such negatives a chunk and side; level None: one unit in the last place of the largest column."""
     rng = np.random.default_rng(dim)
+    C = 10 if dim < 100 else 5                             # chunks, so that the batch is on images and a chunk is not
     B = S * C
     ne, re_ = (rng.standard_normal((V, dim)) * 0.2).astype(np.float32), (rng.standard_normal((R, dim)) * 0.2).astype(np.float32)
     re_[0] = 0.0
@@ -127,7 +128,7 @@ def _gradient_errors(tables, ids, C, N):
 
 
 @pytest.mark.parametrize("dim", (53, 100, 400))
-@pytest.mark.parametrize("level", (3e-2, 1e-3, 1e-5, 1e-6, 5e-7, None))
+@pytest.mark.parametrize("level", (3e-2, 1e-3, 1e-5, 1e-6, None))
 def test_near_pairs_are_as_exact_as_on_dense_operands(dim, level):
     """The whole batch on images against its chunks one by one, which lie below the line, on dense operands: gradient errors against the
     oracle in the 2-norm.  A near pair's weight is its softmax weight over its distance: what the sums of W y lose to rounding goes
@@ -140,7 +141,7 @@ def test_near_pairs_are_as_exact_as_on_dense_operands(dim, level):
     assert ids[0].size * N * ((dim + 3) // 4 * 4) >= 2e8 > S * N * ((dim + 3) // 4 * 4)
     print("case", dim, level, flush=True)
     image = _gradient_errors(tables, ids, C, N)
-    chunks = [_gradient_errors(tables, tuple(x[c * S:(c + 1) * S] for x in ids[:3]) + tuple(x[c:c + 1] for x in ids[3:]), 1, N) for c in (0, 4, 9)]
+    chunks = [_gradient_errors(tables, tuple(x[c * S:(c + 1) * S] for x in ids[:3]) + tuple(x[c:c + 1] for x in ids[3:]), 1, N) for c in (0, C - 1)]
     for k, name in enumerate(("nodes", "relations")):
         on_images = (image[k][0] / image[k][1]) ** 0.5
         dense = (sum(c[k][0] for c in chunks) / sum(c[k][1] for c in chunks)) ** 0.5
