@@ -30,9 +30,12 @@ struct FlashArgs {
   float* mlx; float* outx;
   float ml_log2;       // natural-log units of one unit of the references in ml: 1, or ln 2 where they are kept in log2 units
   int32_t roles;       // edge-side occurrences per edge (3, or 2 for Dot)
-  float* T;            // [2*nchunks][trows][tpitch] softmax weight exp(score - reference) of every (edge, negative)
-                       // pair (TransE: divided by the distance): written by pass 1, read by the negatives' gradient
-                       // pass, which then needs no score product and no exponential
+  union {
+    const float* shift;  // TransE on images: [16 NK] what the operands on images have lost
+    float* T;            // [2*nchunks][trows][tpitch] softmax weight exp(score - reference) of every (edge, negative)
+                         // pair (TransE: divided by the distance): written by pass 1, read by the negatives' gradient
+                         // pass, which then needs no score product and no exponential
+  };
   float* R;            // [2*nchunks][tpitch/16][trows] the reference pass 1 used for a 16-negative block of an edge
   int32_t tpitch;      // N rounded up to 128 (whole tiles of pass 1 and whole stripes of pass 2)
   int32_t trows;       // chunk size rounded up to 64
@@ -46,7 +49,6 @@ struct FlashArgs {
   // evaluation on images, where share > 0: workgroup p takes `share` tiles of the units' tiles, one more if p < share_rest
   int64_t share; int32_t share_rest;
   MarSortJob sort;     // training passes: carried along by the first `carried` workgroups
-  const float* shift;  // TransE on images: [16 NK] what the operands on images have lost
   const float* yexp; const float* xexp;   // exponents of their 16-row blocks, [2*nchunks][2 tiles] (fp32 precision)
 };
 

@@ -911,7 +911,9 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   a.dist = d.dist_img;
   a.xx = L.qq; a.yy = L.kk;
   a.ml = L.ml; a.pos = L.pos; a.ml_log2 = img ? MAR_LN2 : 1.f;
-  a.T = L.T; a.R = L.R; a.tpitch = (d.N + 127) & ~127; a.trows = (d.S + 63) & ~63;
+  if (a.dist) a.shift = L.shift;
+  else a.T = L.T;
+  a.R = L.R; a.tpitch = (d.N + 127) & ~127; a.trows = (d.S + 63) & ~63;
   a.out = pass == 1 ? L.gQ : L.G;
   a.rank_dst = rank_dst; a.rank_src = rank_src;
   a.n = b.n; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.cn = b.cn; a.nchunks = b.nchunks; a.dk = d.dk;
@@ -919,7 +921,6 @@ hipError_t mar_launch_flash(const mar_ctx* c, const MarBatch& b, int pass, int32
   const bool f16 = !d.split_bf16 || pass == 3;             // evaluation always runs at fp32 precision
   a.yimg = pass == 2 ? L.Qimg : L.Kimg; a.yexp = pass == 2 ? L.Qexp : L.Kexp; a.yimg_tiles = ((pass == 2 ? d.S : d.N) + 31) / 32;
   a.ximg = pass == 2 ? L.Kimg : L.Qimg; a.xexp = pass == 2 ? L.Kexp : L.Qexp; a.ximg_tiles = ((pass == 2 ? d.N : d.S) + 31) / 32;
-  a.shift = L.shift;
   a.qrows = a.dist ? L.Q : L.gQ; a.ynorm = L.Knorm; a.table = c->node_emb; a.neg_dst = b.neg_dst; a.neg_src = b.neg_src; a.src = b.src; a.dst = b.dst; a.dim = d.dim;
   a.sr = mar_stripe_rows(d, pass);
   a.nstripes = (max_nx + a.sr - 1) / a.sr;

@@ -12,12 +12,11 @@ struct RowArgs {
   const float *node_emb, *rel_emb;
   const int32_t *src, *rel, *dst, *neg_src, *neg_dst;
   int32_t n, cn, B, C, N, S, dim, dk, model;
-  int64_t n_occ;
+  float* shift;          // TransE on images: what all rows of the batch have in common (common_offset), for the passes
   int32_t num_nodes;
   int32_t sy1, sy2;      // parts per stripe in the two contraction passes
   int32_t roles;         // 3, or 2 for the relation-free Dot score
   float ml_log2;         // natural-log units of one unit of the softmax references (see FlashArgs)
-  float* shift;          // TransE on images: what all rows of the batch have in common (batch_shift), for the passes
 };
 
 template <int GL> __device__ __forceinline__ float group_sum(float v) {
@@ -1210,7 +1209,7 @@ static RowArgs row_args(const mar_ctx* c, const MarBatch& b) {
   a.node_emb = c->node_emb; a.rel_emb = c->rel_emb;
   a.src = b.src; a.rel = b.rel; a.dst = b.dst; a.neg_src = b.neg_src; a.neg_dst = b.neg_dst;
   a.n = b.n; a.cn = b.cn; a.B = d.B; a.C = d.C; a.N = d.N; a.S = d.S; a.dim = d.dim; a.dk = d.dk; a.model = c->cfg.model;
-  a.n_occ = b.n_occ; a.num_nodes = (int32_t)d.num_nodes;
+  a.num_nodes = (int32_t)d.num_nodes;
   a.sy1 = d.sy1; a.sy2 = d.sy2; a.roles = d.roles; a.ml_log2 = mar_on_images(d) ? MAR_LN2 : 1.f; a.shift = c->L.shift;
   return a;
 }

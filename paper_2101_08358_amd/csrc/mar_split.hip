@@ -1238,7 +1238,7 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
           // the column's close pairs, which its four lanes keep: W (y - x) from the rows, at the end's reference
 #pragma unroll 1
           for (int k = 0; k < 8; ++k) {
-            const int at = 256 * (k >> 2) + wave_s * 64 + 16 * (k & 3) + (fresh_lane() & 15), id = close_id[at];
+            const int lane_c = fresh_lane(), at = 256 * (k >> 2) + wave_s * 64 + 16 * (k & 3) + (lane_c & 15), id = close_id[at];
             if (id < 0 || id >> 30 != b) continue;
             const float* const close_w = reinterpret_cast<const float*>(close_id) + 2 * 256 + at;
             const float wc = __builtin_ldexpf(close_w[0], (int)fmaxf(-300.f, fminf(300.f, close_w[2 * 256] - mref[b])));
@@ -1247,7 +1247,8 @@ __device__ __forceinline__ void split_pass(const FlashArgs& a) {
             const DistRow<false> n(u.cs, PASS == 1 ? y : x);
 #pragma unroll
             for (int cb = 0; cb < NO; ++cb) {
-              const float4 qc = q.cols(16 * cb + 4 * go), nc = n.cols(16 * cb + 4 * go);
+              const int col = 16 * cb + 4 * (lane_c >> 4);
+              const float4 qc = q.cols(col), nc = n.cols(col);
               const v4f d = {nc.x - qc.x, nc.y - qc.y, nc.z - qc.z, nc.w - qc.w};
               oacc[cb][b] += d * (PASS == 1 ? wc : -wc);
               if (cb % 4 == 3) __builtin_amdgcn_sched_barrier(0);
@@ -1286,8 +1287,8 @@ k_split_carry(FlashArgs a) { split_pass<NK, PASS, F16, false, true>(a); }
 // ones (SP_CLOSE) exact to 1.6e-7 where those have 3e-5 (1e-5 apart) to 7e-2 (one unit in the last place, 400 floats).  Tables whose
 // rows share an offset are taken without it (common_offset); the loop over near pairs is for few (after 200 and 1,000 steps of training
 // from 0 +- 0.3: 153 and 156 us a step, 210 on fp32 instructions).
-// Registers decide: nothing may spill (a step of 10,000 edges, 1,000 negatives of 400 floats 585 us with 351 registers spilled, 503 with
-// three steps' fragments in LDS and the near loop on the row's image; 50,000 edges 2,390 and 1,847).
+// Registers decide: nothing may spill (a step of 10,000 edges, 1,000 negatives of 400 floats 585 us with 351 registers spilled, 511 with
+// three steps' fragments in LDS and the near loop on the row's image; 50,000 edges 2,390 and 1,880).
 template <int NK, int PASS, bool CARRY>
 __global__ void __launch_bounds__(256) MAR_WAVES_PER_SIMD(sp_waves(NK, PASS))
 k_split_dist(FlashArgs a) { split_pass<NK, PASS, true, true, CARRY>(a); }
